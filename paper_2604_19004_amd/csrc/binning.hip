@@ -12,6 +12,21 @@ struct BinTable {
     int32_t slots[OCEAN_MAX_BINS];
 };
 
+// Sort class of a row (products pr, entries ne, hash bin `bin`): the smallest class that holds it, or 0 (hash table).
+// Sorting costs what the products cost, a hash table what its slots and the products cost, so a row whose many
+// products fall on few columns is left to its small table.  Measured, ns per row, fp64, whole numeric stage of 200 000
+// equal rows: no merging (table of 1.15 slots per product) 49 products 0.6 sorted / 0.7 hashed, 225 1.6 / 2.7, 484 2.9 /
+// 5.3, 961 5.3 / 13.0, 1444 7.9 / 17, 1936 12.1 / 26; 408 products on 103 columns 1.8 / 2.8, 707 on 180 3.1 / 4.1, but
+// 1090 on 129 (256 slots) 5.1 / 4.3 and 1682 on 281 (512 slots) 8.5 / 6.4.
+__device__ __forceinline__ int sort_class(long long pr, long long ne, int bin, unsigned mask)
+{
+    const int most = bin <= NB_W64 ? 768 : bin == NB_S512 ? 1024 : 2048;
+    for (int c = 1; c < SORT_CLASSES; ++c)
+        if (pr <= kSortClass[c].cap && ne <= kSortClass[c].entries)
+            return kSortClass[c].cap <= most && ((mask >> c) & 1u) ? c : 0;
+    return 0;
+}
+
 // need = table slots the row asks for, cap = output entries reserved for it.
 //   mode 0  upper bound: cap = ub = min(prod, n), need = ceil(bound_coef * ub)   (Section 3.2, upper-bound workflow)
 //   (in modes 1 and 2 the table is limited to ceil(bound_coef * ub) slots as well: more cannot be of use)
@@ -21,18 +36,22 @@ struct BinTable {
 //   mode 3  symbolic:    need = ceil(1.25 * e), no capacity; e = ub, or with assisted binning (coef > 1,
 //                        Section 4.1) ceil(prod / coef) kept inside [longest referenced row of B, ub]
 // max_cap receives the largest capacity among the rows of the last (global-memory) bin.
+// sort_mask: bit c set = sort class c may be used (modes 0, 1, 2; see kSortClass); a_rp: row offsets of A.
+// bin_of_row receives the row's key, class * OCEAN_MAX_BINS + bin, which is the bin itself for rows that are not
+// sorted; bin_count and bin_prod have one counter per key.
 __global__ void __launch_bounds__(TPB)
 k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coef, double scale, BinTable bt, int64_t n_cols,
            const int64_t *__restrict__ prod, const double *__restrict__ est, const int32_t *__restrict__ nnz_exact,
            const int32_t *__restrict__ row_mask, const int32_t *__restrict__ lower_bound,
-           const int32_t *__restrict__ cmin, const int32_t *__restrict__ cmax, int vbytes,
-           uint8_t *__restrict__ bin_of_row, int32_t *__restrict__ cap,
+           const int32_t *__restrict__ cmin, const int32_t *__restrict__ cmax, int vbytes, unsigned sort_mask,
+           const int64_t *__restrict__ a_rp, uint8_t *__restrict__ bin_of_row, int32_t *__restrict__ cap,
            unsigned long long *bin_count, unsigned long long *bin_prod, unsigned long long *max_cap)
 {
-    __shared__ unsigned int s_cnt[OCEAN_MAX_BINS];
-    __shared__ unsigned long long s_prod[OCEAN_MAX_BINS];
+    __shared__ unsigned int s_cnt[ROW_KEYS];
+    __shared__ unsigned long long s_prod[ROW_KEYS];
     __shared__ unsigned int s_maxcap;
-    if (threadIdx.x < OCEAN_MAX_BINS) { s_cnt[threadIdx.x] = 0; s_prod[threadIdx.x] = 0ull; }
+    static_assert(ROW_KEYS <= TPB && ROW_KEYS <= BIN_NONE, "one thread per key, keys in a byte");
+    if (threadIdx.x < ROW_KEYS) { s_cnt[threadIdx.x] = 0; s_prod[threadIdx.x] = 0ull; }
     if (threadIdx.x == 0) s_maxcap = 0;
     __syncthreads();
     for (int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x; i < m; i += (int64_t)gridDim.x * TPB) {
@@ -83,16 +102,20 @@ k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coe
                     if (c > span) c = span;
                 }
             }
+            if (bin == bt.n - 1 && c > 0) atomicMax(&s_maxcap, (unsigned int)c);
+            if (sort_mask != 0u && bin < NB_COUNT && pr <= kSortClass[SORT_CLASSES - 1].cap) {
+                const int cls = sort_class(pr, a_rp[i + 1] - a_rp[i], bin, sort_mask);
+                bin += cls * OCEAN_MAX_BINS;
+            }
             atomicAdd(&s_cnt[bin], 1u);
             if (bin_prod != nullptr) atomicAdd(&s_prod[bin], (unsigned long long)pr);
-            if (bin == bt.n - 1 && c > 0) atomicMax(&s_maxcap, (unsigned int)c);
         }
         bin_of_row[i] = (uint8_t)bin;
         if (cap != nullptr) cap[i] = (int32_t)c;
     }
     __syncthreads();
-    if (threadIdx.x < OCEAN_MAX_BINS && s_cnt[threadIdx.x]) atomicAdd(&bin_count[threadIdx.x], (unsigned long long)s_cnt[threadIdx.x]);
-    if (bin_prod != nullptr && threadIdx.x < OCEAN_MAX_BINS && s_prod[threadIdx.x]) atomicAdd(&bin_prod[threadIdx.x], s_prod[threadIdx.x]);
+    if (threadIdx.x < ROW_KEYS && s_cnt[threadIdx.x]) atomicAdd(&bin_count[threadIdx.x], (unsigned long long)s_cnt[threadIdx.x]);
+    if (bin_prod != nullptr && threadIdx.x < ROW_KEYS && s_prod[threadIdx.x]) atomicAdd(&bin_prod[threadIdx.x], s_prod[threadIdx.x]);
     if (threadIdx.x == 0 && s_maxcap && max_cap != nullptr) atomicMax(max_cap, (unsigned long long)s_maxcap);
 }
 
@@ -109,22 +132,27 @@ hipError_t launch_classify(int64_t m, const BinParams &p, double scale, const in
     int64_t blocks = (m + TPB - 1) / TPB;
     if (blocks > 1024) blocks = 1024;   // one set of atomics per workgroup: keep the workgroups few
     hipLaunchKernelGGL(k_classify, dim3((unsigned)blocks), dim3(TPB), 0, s, m, p.mode, p.coef, (p.table_coef > 0.0 && p.table_coef < p.coef) ? p.table_coef : p.coef, p.bound_coef, scale, bt, p.n_cols,
-                       prod, est, nnz_exact, row_mask, lower_bound, p.mode != 3 ? p.cmin : nullptr, p.cmax, p.vbytes, bin_of_row,
+                       prod, est, nnz_exact, row_mask, lower_bound, p.mode != 3 ? p.cmin : nullptr, p.cmax, p.vbytes, p.sort_mask, p.a_rp, bin_of_row,
                        cap, bin_count, bin_prod, max_cap);
     return hipGetLastError();
 }
 
-// Row ids grouped by bin: bin b occupies bin_rows[prefix(b) .. prefix(b)+count(b)).  A workgroup
-// counts its rows per bin in LDS, claims one contiguous range per bin, then fills it.
+// Row ids grouped by key (bin, or sort class and bin): key b occupies bin_rows[prefix(b) .. prefix(b)+count(b)).  A
+// workgroup counts its rows per key in LDS, claims one contiguous range per key, then fills it.
 constexpr int SC_ITEMS = 8;
 __global__ void __launch_bounds__(TPB)
-k_scatter(int64_t m, int n_bins, const uint8_t *__restrict__ bin_of_row,
+k_scatter(int64_t m, int n_keys, const uint8_t *__restrict__ bin_of_row,
           const unsigned long long *__restrict__ bin_count, unsigned long long *bin_cursor,
           int32_t *__restrict__ bin_rows)
 {
-    __shared__ unsigned int s_cnt[OCEAN_MAX_BINS];
-    __shared__ unsigned long long s_base[OCEAN_MAX_BINS];
-    if (threadIdx.x < OCEAN_MAX_BINS) s_cnt[threadIdx.x] = 0;
+    __shared__ unsigned int s_cnt[ROW_KEYS];
+    __shared__ unsigned int s_base[ROW_KEYS];
+    __shared__ unsigned int s_wave[TPB / WAVE];
+    if (threadIdx.x < ROW_KEYS) s_cnt[threadIdx.x] = 0;
+    // first place of every key: prefix sum of the counts (fewer than 2^31 rows in all)
+    const unsigned int total = (int)threadIdx.x < n_keys ? (unsigned int)bin_count[threadIdx.x] : 0u;
+    const unsigned int upto = wave_inclusive_scan_u32(total);
+    if (lane_id() == WAVE - 1) s_wave[threadIdx.x / WAVE] = upto;
     __syncthreads();
     const int64_t tile = (int64_t)blockIdx.x * TPB * SC_ITEMS;
     int bin[SC_ITEMS];
@@ -140,12 +168,10 @@ k_scatter(int64_t m, int n_bins, const uint8_t *__restrict__ bin_of_row,
         }
     }
     __syncthreads();
-    if ((int)threadIdx.x < n_bins) {
-        unsigned long long start = 0;
-        for (int b = 0; b < (int)threadIdx.x; ++b) start += bin_count[b];
-        unsigned long long off = s_cnt[threadIdx.x] ? atomicAdd(&bin_cursor[threadIdx.x], (unsigned long long)s_cnt[threadIdx.x]) : 0ull;
-        s_base[threadIdx.x] = start + off;
-    }
+    unsigned int start = upto - total;
+    for (int w = 0; w < (int)threadIdx.x / WAVE; ++w) start += s_wave[w];
+    if ((int)threadIdx.x < n_keys)
+        s_base[threadIdx.x] = start + (s_cnt[threadIdx.x] ? (unsigned int)atomicAdd(&bin_cursor[threadIdx.x], (unsigned long long)s_cnt[threadIdx.x]) : 0u);
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < SC_ITEMS; ++q) {
@@ -154,12 +180,12 @@ k_scatter(int64_t m, int n_bins, const uint8_t *__restrict__ bin_of_row,
     }
 }
 
-hipError_t launch_scatter(int64_t m, int n_bins, const uint8_t *bin_of_row, const unsigned long long *bin_count,
+hipError_t launch_scatter(int64_t m, int n_keys, const uint8_t *bin_of_row, const unsigned long long *bin_count,
                           unsigned long long *bin_cursor, int32_t *bin_rows, hipStream_t s)
 {
     if (m == 0) return hipSuccess;
     const int64_t blocks = (m + TPB * SC_ITEMS - 1) / (TPB * SC_ITEMS);
-    hipLaunchKernelGGL(k_scatter, dim3((unsigned)blocks), dim3(TPB), 0, s, m, n_bins, bin_of_row, bin_count,
+    hipLaunchKernelGGL(k_scatter, dim3((unsigned)blocks), dim3(TPB), 0, s, m, n_keys, bin_of_row, bin_count,
                        bin_cursor, bin_rows);
     return hipGetLastError();
 }
@@ -359,8 +385,9 @@ k_bin_work(int64_t m, const uint8_t *__restrict__ bin_of_row, const int64_t *__r
     if (threadIdx.x < 3 * OCEAN_MAX_BINS) s_sum[threadIdx.x] = 0;
     __syncthreads();
     for (int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x; i < m; i += (int64_t)gridDim.x * TPB) {
-        const int b = bin_of_row[i];
-        if (b != BIN_NONE) {
+        const int key = bin_of_row[i];
+        if (key != BIN_NONE) {
+            const int b = key % OCEAN_MAX_BINS;
             atomicAdd(&s_sum[b], (unsigned long long)prod[i]);
             atomicAdd(&s_sum[OCEAN_MAX_BINS + b], (unsigned long long)(a_rp[i + 1] - a_rp[i]));
             const int32_t c = row_nnz[i];

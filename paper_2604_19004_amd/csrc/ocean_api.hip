@@ -40,9 +40,9 @@ int fail(int code, const std::string &msg)
 // Device scalars of one call; zeroed at the start.
 struct Scalars {
     unsigned long long totals[4];                 // [0]: a total copied here to be read back (slots reserved, nnz(C))
-    unsigned long long bin_count[OCEAN_MAX_BINS];
-    unsigned long long bin_cursor[OCEAN_MAX_BINS];
-    unsigned long long bin_prod[OCEAN_MAX_BINS];  // intermediate products of the rows of each bin
+    unsigned long long bin_count[ROW_KEYS];       // rows by key (sort class and bin; the bin itself in the symbolic pass)
+    unsigned long long bin_cursor[ROW_KEYS];
+    unsigned long long bin_prod[ROW_KEYS];        // intermediate products of the rows of each key
     unsigned long long max_cap;
     unsigned long long ovf_count;
     unsigned long long queue[4];
@@ -86,6 +86,7 @@ struct Ctx {
     int n_win = 0;
     bool query_bitmap = false;
     bool fine_buckets = false;
+    unsigned sort_mask = 0;   // sort classes this call may use
 
     void *alloc(size_t bytes)
     {
@@ -316,7 +317,7 @@ int zero_bins(Ctx &c, Work &w)
         return OCEAN_OK;
     }
     HIP_TRY(hipMemsetAsync(w.sc->bin_count, 0,
-                           sizeof(unsigned long long) * (3 * OCEAN_MAX_BINS + 2 + 4), c.s));   // counts, cursors, products, max_cap, ovf, queues
+                           sizeof(unsigned long long) * (3 * ROW_KEYS + 2 + 4), c.s));   // counts, cursors, products, max_cap, ovf, queues
     return OCEAN_OK;
 }
 
@@ -439,7 +440,7 @@ double conservative_cr(const ocean_stats *S, const ocean_options &o)
 // Launches every non-empty bin, largest tables first.  Scratch for the hybrid
 // and global bins is obtained here and kept until the caller releases all.
 int run_numeric(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int gb_log2, const unsigned long long *count,
-                const unsigned long long * /*bin_prod*/, int64_t max_cap_global, double global_coef, const int64_t *out_ptr, int32_t *out_col, void *out_val,
+                const unsigned long long *bin_prod, int64_t max_cap_global, double global_coef, const int64_t *out_ptr, int32_t *out_col, void *out_val,
                 int32_t *row_nnz, int queue_base, int stage, bool time_bins, bool esc)
 {
     // With the window table, the column-window kernel takes every row beyond the 4096-slot table (measured:
@@ -449,6 +450,46 @@ int run_numeric(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int gb_l
     start[0] = 0;
     for (int b = 0; b < NB_ALL; ++b) start[b + 1] = start[b] + (int64_t)count[b];
     const size_t vbytes = dtype == OCEAN_F64 ? 8 : 4;
+    // The sort classes, smallest first.  A kernel takes the rows of smaller classes too, so the rows of a class go with
+    // those of the next one that has rows (their lists are adjacent) where sorting them at its size costs less than
+    // the launch it saves, 6 us with its event: a power-law matrix of 16 384 rows has a few hundred rows in each
+    // of the twelve classes (0.91 ms a call with a launch for each, 0.86 before there were any).
+    // A launch's time is reported under the bin that holds most of its products.
+    auto run_sorted = [&]() -> int {
+        constexpr int64_t LAUNCH_PS = 6000000;
+        int64_t first = start[NB_ALL], rows = 0, own_ps = 0;
+        unsigned long long prod_of[OCEAN_MAX_BINS] = {};
+        for (int cls = 1; cls < SORT_CLASSES; ++cls) {
+            int64_t n = 0;
+            for (int b = 0; b < OCEAN_MAX_BINS; ++b) {
+                n += (int64_t)count[cls * OCEAN_MAX_BINS + b];
+                prod_of[b] += bin_prod[cls * OCEAN_MAX_BINS + b];
+            }
+            rows += n;
+            own_ps += n * kSortClass[cls].ps;
+            if (n == 0) continue;   // (rows of smaller classes wait for a class that has some of its own)
+            int next = cls + 1;
+            auto empty = [&](int k) {
+                for (int b = 0; b < OCEAN_MAX_BINS; ++b)
+                    if (count[k * OCEAN_MAX_BINS + b]) return false;
+                return true;
+            };
+            while (next < SORT_CLASSES && empty(next)) ++next;
+            if (next < SORT_CLASSES && rows * kSortClass[next].ps - own_ps < LAUNCH_PS) continue;
+            if (time_bins) {
+                int most = 0;
+                for (int b = 1; b < OCEAN_MAX_BINS; ++b)
+                    if (prod_of[b] > prod_of[most]) most = b;
+                c.bin_ev.emplace_back(most, (int)c.ev.size());
+                OC_TRY(mark(c, stage));
+            }
+            HIP_TRY(launch_numeric_sort(A, B, dtype, SortLaunch{w.bin_rows + first, rows, cls, out_ptr, out_col, out_val, row_nnz}, c.s));
+            first += rows;
+            rows = own_ps = 0;
+            for (unsigned long long &p : prod_of) p = 0;
+        }
+        return OCEAN_OK;
+    };
     for (int b = NB_ALL - 1; b >= 0; --b) {
         NumLaunch l{};
         l.rows = w.bin_rows + start[b];
@@ -532,6 +573,7 @@ int run_numeric(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int gb_l
         }
         HIP_TRY(launch_numeric_bin(A, B, dtype, l, gb_log2, c.s));
     }
+    OC_TRY(run_sorted());
     if (time_bins) OC_TRY(mark(c, stage));
     return OCEAN_OK;
 }
@@ -654,6 +696,20 @@ void sample_rows_of(int64_t rows, const ocean_options &o, int64_t *out)
 int lanes_div_of(const ocean_stats *S)
 {
     return (double)S->max_row_products <= 16.0 * S->avg_products ? 4 : 1;
+}
+
+// Sort classes that can hold column ids and positions of B: a key is the column id above the number of the product.
+// With expand-sort-compress asked for, the classes that would take its rows stay out.
+unsigned sort_mask_of(const Csr &B, bool esc)
+{
+    if (B.nnz >= 0xffffffffLL) return 0u;
+    unsigned mask = 0u;
+    for (int c = esc ? 2 : 1; c < SORT_CLASSES; ++c) {
+        int bits = 0;   // of a product's number
+        while ((1 << bits) < kSortClass[c].cap) ++bits;
+        if (B.cols < (1LL << (32 - bits))) mask |= 1u << c;
+    }
+    return mask;
 }
 
 int registers_of(double er, const ocean_options &o)
@@ -799,6 +855,8 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         HIP_TRY(launch_row_spans(A, B, nullptr, m, w.cmin, w.cmax, c.s));
         w.spans = true;
     }
+    const bool esc_ok = o.esc_short_rows != 0 && n >= 32 && n <= ESC_MAX_COLS;
+    c.sort_mask = o.force_hash_kernels ? 0u : sort_mask_of(B, esc_ok);
     int32_t *t_col = nullptr;   // output region of the first attempt (C itself on the two-pass path)
     void *t_val = nullptr;
     int64_t total_slots = 0;
@@ -810,6 +868,8 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         bp.n_bins = NB_COUNT;
         for (int b = 0; b < NB_COUNT; ++b) bp.slots[b] = kNumericSlots[b];
         bp.n_cols = n;
+        bp.sort_mask = c.sort_mask;
+        bp.a_rp = A.rp;
         if (w.spans) {
             bp.cmin = w.cmin;
             bp.cmax = w.cmax;
@@ -843,10 +903,13 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         HIP_TRY(launch_classify(m, bp, o.estimate_scale, w.prod, w.est, w.nnz_final, nullptr, nullptr, w.bin, w.cap,
                                 w.sc->bin_count, w.sc->bin_prod, &w.sc->max_cap, c.s));
         HIP_TRY(launch_scan_i32_to_i64(w.cap, m, ptr, w.scan_tmp, &w.sc->totals[0], c.s));   // totals[0]: total slots
-        HIP_TRY(launch_scatter(m, NB_ALL, w.bin, w.sc->bin_count, w.sc->bin_cursor, w.bin_rows, c.s));
+        HIP_TRY(launch_scatter(m, ROW_KEYS, w.bin, w.sc->bin_count, w.sc->bin_cursor, w.bin_rows, c.s));
         OC_TRY(fetch_scalars(c, w.sc));
         total_slots = (int64_t)c.h->totals[0];
-        for (int b = 0; b < NB_ALL; ++b) S->rows_per_bin[b] = (int64_t)c.h->bin_count[b];
+        for (int b = 0; b < NB_ALL; ++b) {
+            S->rows_per_bin[b] = 0;
+            for (int k = b; k < ROW_KEYS; k += OCEAN_MAX_BINS) S->rows_per_bin[b] += (int64_t)c.h->bin_count[k];
+        }
         c.bw = (bw_try != nullptr && !(c.h->flags & 8)) ? bw_try : nullptr;
         if (bw_try != nullptr && (c.h->flags & 8) && !tried_sorted_copy && o.sort_b_ratio > 0.0 &&
             (double)S->heavy_products >= o.sort_b_ratio * (double)B.nnz) {
@@ -887,7 +950,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         out_ptr = ptr;
         break;
     }
-    unsigned long long bin_count[OCEAN_MAX_BINS], bin_prod[OCEAN_MAX_BINS];
+    unsigned long long bin_count[ROW_KEYS], bin_prod[ROW_KEYS];
     std::memcpy(bin_count, c.h->bin_count, sizeof(bin_count));
     std::memcpy(bin_prod, c.h->bin_prod, sizeof(bin_prod));
     const int64_t max_cap = (int64_t)c.h->max_cap;
@@ -898,7 +961,6 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     HIP_TRY(launch_fill_i32(w.row_nnz, m, 0, c.s));
     // expand-sort-compress needs every row of its bins to have no more products than lanes (true when the bins come
     // from the product bound and B has at least 32 columns) and column ids that leave room for the lane number
-    const bool esc_ok = o.esc_short_rows != 0 && n >= 32 && n <= ESC_MAX_COLS;
     OC_TRY(run_numeric(c, w, A, Bnum, dtype, gb_log2, bin_count, bin_prod, max_cap, global_coef, out_ptr, t_col, t_val, w.row_nnz, 0,
                        OCEAN_ST_NUMERIC, st != nullptr, esc_ok && workflow == OCEAN_WF_UPPER_BOUND));
     if (st) {
@@ -951,17 +1013,19 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         bp.n_bins = NB_COUNT;
         for (int b = 0; b < NB_COUNT; ++b) bp.slots[b] = kNumericSlots[b];
         bp.n_cols = n;
+        bp.sort_mask = c.sort_mask;
+        bp.a_rp = A.rp;
         OC_TRY(zero_bins(c, w));
         HIP_TRY(launch_classify(m, bp, 1.0, w.prod, nullptr, nullptr, w.row_nnz, nullptr, w.bin, w.cap, w.sc->bin_count,
                                 w.sc->bin_prod, &w.sc->max_cap, c.s));
         HIP_TRY(launch_scan_i32_to_i64(w.cap, m, w.tmp_ptr2, w.scan_tmp, &w.sc->totals[0], c.s));
-        HIP_TRY(launch_scatter(m, NB_COUNT, w.bin, w.sc->bin_count, w.sc->bin_cursor, w.bin_rows, c.s));
+        HIP_TRY(launch_scatter(m, ROW_KEYS, w.bin, w.sc->bin_count, w.sc->bin_cursor, w.bin_rows, c.s));
         OC_TRY(fetch_scalars(c, w.sc));
         const int64_t slots2 = (int64_t)c.h->totals[0];
         r_col = static_cast<int32_t *>(c.alloc((size_t)slots2 * 4));
         r_val = r_col ? c.alloc((size_t)slots2 * vbytes) : nullptr;
         if (!r_col || !r_val) return fail(OCEAN_EALLOC, "retry output allocation failed");
-        unsigned long long bc2[OCEAN_MAX_BINS], bp2[OCEAN_MAX_BINS];
+        unsigned long long bc2[ROW_KEYS], bp2[ROW_KEYS];
         std::memcpy(bc2, c.h->bin_count, sizeof(bc2));
         std::memcpy(bp2, c.h->bin_prod, sizeof(bp2));
         HIP_TRY(launch_fill_i32(w.row_nnz2, m, 0, c.s));

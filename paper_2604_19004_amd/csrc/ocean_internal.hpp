@@ -59,6 +59,17 @@ __host__ __device__ inline bool dense_span_pays(long long span, long long slots,
     return span > 0 && span <= DS_MAX_COLS && slots >= 512 && span * (8 * vbytes + 1) <= slots * 8 * (4 + vbytes);
 }
 
+// Rows of few products are accumulated by sorting them (sortrow.hip) instead of through their bin's hash table.  A
+// sort class takes rows of at most `cap` intermediate products and `entries` entries of A.
+// ps: picoseconds a row of the class costs where there are many (fp64, one MI355X; see sort_class).
+struct SortClass { int cap, entries, ps; };
+constexpr int SORT_CLASSES = 13;            // class 0: not sorted, the bin's own kernel
+constexpr SortClass kSortClass[SORT_CLASSES] = {
+    {0, 0, 0}, {32, 32, 400}, {64, 64, 600}, {96, 64, 800}, {128, 64, 1000}, {192, 64, 1300}, {256, 64, 1600},
+    {384, 64, 2300}, {512, 64, 2900}, {768, 64, 4100}, {1024, 64, 5300}, {1536, 64, 7900}, {2048, 64, 12100}};
+// Rows are grouped by (class, bin): key = class * OCEAN_MAX_BINS + bin, so that the rows of a class are adjacent.
+constexpr int ROW_KEYS = SORT_CLASSES * OCEAN_MAX_BINS;
+
 // ------------------------------------------------------------- CSR view ----
 struct Csr {
     const int64_t *rp;
@@ -238,6 +249,8 @@ struct BinParams {
     const int32_t *cmin; // per row: first and last column the row can reach (k_row_spans), or null: rows whose range
     const int32_t *cmax; // pays for it go to the dense-range bin NB_DSPAN (modes 0, 1, 2)
     int vbytes;          // bytes of a value (with cmin)
+    unsigned sort_mask;  // sort classes that may be used (bit c; modes 0, 1, 2), 0: none
+    const int64_t *a_rp; // row offsets of A (with sort_mask)
     int n_bins;
     int32_t slots[OCEAN_MAX_BINS];
     int64_t n_cols;
@@ -247,7 +260,7 @@ hipError_t launch_classify(int64_t m, const BinParams &p, double scale, const in
                            uint8_t *bin_of_row, int32_t *cap, unsigned long long *bin_count,
                            unsigned long long *bin_prod /*products per bin, may be null*/, unsigned long long *max_cap,
                            hipStream_t s);
-hipError_t launch_scatter(int64_t m, int n_bins, const uint8_t *bin_of_row, const unsigned long long *bin_count,
+hipError_t launch_scatter(int64_t m, int n_keys, const uint8_t *bin_of_row, const unsigned long long *bin_count,
                           unsigned long long *bin_cursor, int32_t *bin_rows, hipStream_t s);
 hipError_t launch_scan_i32_to_i64(const int32_t *in, int64_t n, int64_t *out, int64_t *block_tmp,
                                   unsigned long long *total_out, hipStream_t s);
@@ -317,6 +330,18 @@ struct EscLaunch {
 };
 constexpr int64_t ESC_MAX_COLS = (1ll << 26) - 1;   // column id and lane number share one 32-bit sort key
 hipError_t launch_numeric_esc(const Csr &A, const Csr &B, int dtype, const EscLaunch &l, hipStream_t s);
+
+// sortrow.hip
+struct SortLaunch {
+    const int32_t *rows;      // row ids of one sort class
+    int64_t count;
+    int cls;
+    const int64_t *out_ptr;
+    int32_t *out_col;
+    void *out_val;
+    int32_t *row_nnz;
+};
+hipError_t launch_numeric_sort(const Csr &A, const Csr &B, int dtype, const SortLaunch &l, hipStream_t s);
 
 // compact.hip
 hipError_t launch_compact(int64_t m, int dtype, const int64_t *c_rp, const int32_t *nnz1, const int64_t *ptr1,
