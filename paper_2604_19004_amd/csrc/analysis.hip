@@ -289,28 +289,38 @@ hipError_t launch_publish_totals(const unsigned long long *totals, const int32_t
 // row, walked by one group of 16 lanes, was most of the kernel's time (R-MAT: 0.77 ms).  "Long" is relative: a row
 // of long_from entries or more, which the launcher sets to 1024 or eight times the average row, whichever is more
 // (where every row is long, sixteen groups side by side are 6 - 12 % faster than the workgroup on one row at a time).
+// Where the rows are known or suspected to be skewed, the long ones (from LONG_SKEWED entries on) are skipped here and
+// left to k_hll_sketch_long: the long rows of a power-law matrix sit side by side, and the workgroup that met
+// rows 0 .. 15 was the whole kernel's time (R-MAT scale 18: 2 % of the entries, 72 us; now 23 + 22 us).
 constexpr int SK_LONG = 1024;
+constexpr int LONG_SKEWED = 256;
+constexpr int LONG_THREADS = 1024;
+constexpr int LONG_ROWS = 4;        // neighbouring rows a workgroup of the long-row kernels looks at together
+
+template <int M>
+__device__ __forceinline__ void hll_add(uint32_t *regs, int32_t c)
+{
+    constexpr int P = (M == 32) ? 5 : (M == 64) ? 6 : 7;
+    const uint32_t h = hll_hash(c);
+    const uint32_t w = h >> P;
+    const uint32_t rank = w ? (uint32_t)(__clz((int)w) - P + 1) : (uint32_t)(32 - P + 1);
+    atomicMax(&regs[h & (M - 1)], rank);
+}
+
 template <int M>
 __global__ void __launch_bounds__(TPB)
 k_hll_sketch(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, int64_t rows, int g_log2,
-             int64_t long_from, uint8_t *__restrict__ out)
+             int64_t long_from, bool skip_long, uint8_t *__restrict__ out)
 {
     extern __shared__ uint32_t s_regs[];  // [TPB >> g_log2][M]
     __shared__ uint32_t s_big[M];
     __shared__ long long s_long[TPB / 8];   // (at most TPB / 8 rows per turn: groups have 8 lanes or more)
     __shared__ int s_nlong;
-    constexpr int P = (M == 32) ? 5 : (M == 64) ? 6 : 7;
     const int G = 1 << g_log2;
     const int sub = threadIdx.x & (G - 1);
     const int rl = threadIdx.x >> g_log2;
     const int R = TPB >> g_log2;
     uint32_t *my = s_regs + rl * M;
-    auto add = [&](uint32_t *regs, int32_t c) {
-        const uint32_t h = hll_hash(c);
-        const uint32_t w = h >> P;
-        const uint32_t rank = w ? (uint32_t)(__clz((int)w) - P + 1) : (uint32_t)(32 - P + 1);
-        atomicMax(&regs[h & (M - 1)], rank);
-    };
     auto store = [&](const uint32_t *regs, int64_t row, int first, int step) {
         uint32_t *dst = reinterpret_cast<uint32_t *>(out + row * M);
         for (int j = first; j < M / 4; j += step)
@@ -325,7 +335,7 @@ k_hll_sketch(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, in
         if (row < rows) {
             const int64_t p0 = rp[row], p1 = rp[row + 1];
             mine = p1 - p0 < long_from;
-            if (!mine && sub == 0) s_long[atomicAdd(&s_nlong, 1)] = row;
+            if (!mine && !skip_long && sub == 0) s_long[atomicAdd(&s_nlong, 1)] = row;
             // four column ids per lane and turn (unconditional reads, index clamped): a long row is bound by
             // the latency of one load after the other otherwise
             for (int64_t p = p0 + sub; mine && p < p1; p += 4 * (int64_t)G) {
@@ -337,7 +347,7 @@ k_hll_sketch(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, in
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (p + (int64_t)i * G < p1) add(my, c[i]);
+                    if (p + (int64_t)i * G < p1) hll_add<M>(my, c[i]);
             }
         }
         wave_sync();
@@ -358,7 +368,7 @@ k_hll_sketch(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, in
                 }
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    if (p + (int64_t)k * TPB < p1) add(s_big, c[k]);
+                    if (p + (int64_t)k * TPB < p1) hll_add<M>(s_big, c[k]);
             }
             __syncthreads();
             store(s_big, lrow, (int)threadIdx.x, TPB);
@@ -366,6 +376,61 @@ k_hll_sketch(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, in
         }
         __syncthreads();   // (everyone has read s_nlong before the next turn clears it)
     }
+}
+
+// The rows of long_from entries or more, a workgroup of 1024 threads on one after the other.  Workgroup b looks at
+// rows 4 b .. 4 b + 3 of every stretch of 4 gridDim rows: neighbouring long rows go to different workgroups (an odd
+// number of them, so that rows a power of two apart do not meet again).
+template <int M>
+__global__ void __launch_bounds__(LONG_THREADS)
+k_hll_sketch_long(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, int64_t rows, int64_t long_from,
+                  uint8_t *__restrict__ out)
+{
+    __shared__ uint32_t s_regs[M];
+    __shared__ int32_t s_list[LONG_THREADS];
+    __shared__ int s_n;
+    const int tid = threadIdx.x;
+    const int64_t stretch = (int64_t)gridDim.x * LONG_ROWS;
+    const int64_t first = (int64_t)blockIdx.x * LONG_ROWS + tid % LONG_ROWS + (int64_t)(tid / LONG_ROWS) * stretch;
+    const int64_t turn = stretch * (LONG_THREADS / LONG_ROWS);
+    for (int64_t base = 0; base < rows; base += turn) {   // uniform
+        if (tid == 0) s_n = 0;
+        __syncthreads();
+        const int64_t r = base + first;
+        if (r < rows && rp[r + 1] - rp[r] >= long_from) s_list[atomicAdd(&s_n, 1)] = (int32_t)r;
+        __syncthreads();
+        const int n = s_n;
+        for (int i = 0; i < n; ++i) {   // uniform
+            const int64_t row = s_list[i];
+            const int64_t p0 = rp[row], p1 = rp[row + 1];
+            if (tid < M) s_regs[tid] = 0;
+            __syncthreads();
+            for (int64_t p = p0 + tid; p < p1; p += 4 * (int64_t)LONG_THREADS) {
+                int32_t c[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int64_t q = p + (int64_t)k * LONG_THREADS;
+                    c[k] = col[q < p1 ? q : p1 - 1];
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (p + (int64_t)k * LONG_THREADS < p1) hll_add<M>(s_regs, c[k]);
+            }
+            __syncthreads();
+            if (tid < M / 4)
+                reinterpret_cast<uint32_t *>(out + row * M)[tid] =
+                    s_regs[4 * tid] | (s_regs[4 * tid + 1] << 8) | (s_regs[4 * tid + 2] << 16) | (s_regs[4 * tid + 3] << 24);
+            __syncthreads();
+        }
+        __syncthreads();
+    }
+}
+
+// Workgroups of the long-row kernels: an odd number, fewer where there are few rows.
+static int long_row_blocks(int64_t rows)
+{
+    const int64_t want = (rows + LONG_ROWS - 1) / LONG_ROWS;
+    return (int)(want < 1021 ? want | 1 : 1021);
 }
 
 // lanes_div: 1, or 4 when the rows are known to be of similar lengths - a lane keeps four entries in flight, so a
@@ -380,12 +445,22 @@ hipError_t launch_hll_sketch(const Csr &B, int m, uint8_t *sketches, int lanes_d
     int64_t blocks = (B.rows + R - 1) / R;
     if (blocks > 256 * 64) blocks = 256 * 64;
     const size_t lds = (size_t)R * m * sizeof(uint32_t);
-    const int64_t long_from = 8.0 * avg > (double)SK_LONG ? (int64_t)(8.0 * avg) : (int64_t)SK_LONG;
+    const bool skip_long = lanes_div == 1;
+    const int64_t least = skip_long ? LONG_SKEWED : SK_LONG;
+    const int64_t long_from = 8.0 * avg > (double)least ? (int64_t)(8.0 * avg) : least;
     switch (m) {
-    case 32: hipLaunchKernelGGL(k_hll_sketch<32>, dim3((unsigned)blocks), dim3(TPB), lds, s, B.rp, B.col, B.rows, g_log2, long_from, sketches); break;
-    case 64: hipLaunchKernelGGL(k_hll_sketch<64>, dim3((unsigned)blocks), dim3(TPB), lds, s, B.rp, B.col, B.rows, g_log2, long_from, sketches); break;
-    case 128: hipLaunchKernelGGL(k_hll_sketch<128>, dim3((unsigned)blocks), dim3(TPB), lds, s, B.rp, B.col, B.rows, g_log2, long_from, sketches); break;
+    case 32: hipLaunchKernelGGL(k_hll_sketch<32>, dim3((unsigned)blocks), dim3(TPB), lds, s, B.rp, B.col, B.rows, g_log2, long_from, skip_long, sketches); break;
+    case 64: hipLaunchKernelGGL(k_hll_sketch<64>, dim3((unsigned)blocks), dim3(TPB), lds, s, B.rp, B.col, B.rows, g_log2, long_from, skip_long, sketches); break;
+    case 128: hipLaunchKernelGGL(k_hll_sketch<128>, dim3((unsigned)blocks), dim3(TPB), lds, s, B.rp, B.col, B.rows, g_log2, long_from, skip_long, sketches); break;
     default: return hipErrorInvalidValue;
+    }
+    if (skip_long && B.nnz >= long_from) {   // (a matrix of fewer entries has no such row)
+        const int n = long_row_blocks(B.rows);
+        switch (m) {
+        case 32: hipLaunchKernelGGL(k_hll_sketch_long<32>, dim3(n), dim3(LONG_THREADS), 0, s, B.rp, B.col, B.rows, long_from, sketches); break;
+        case 64: hipLaunchKernelGGL(k_hll_sketch_long<64>, dim3(n), dim3(LONG_THREADS), 0, s, B.rp, B.col, B.rows, long_from, sketches); break;
+        default: hipLaunchKernelGGL(k_hll_sketch_long<128>, dim3(n), dim3(LONG_THREADS), 0, s, B.rp, B.col, B.rows, long_from, sketches); break;
+        }
     }
     return hipGetLastError();
 }
@@ -415,11 +490,80 @@ __device__ __forceinline__ double hll_alpha(int m)
 // entries, merged by one group, was most of the sampled merge's time.  "Long" is long_from entries or more: 2048
 // or eight times the average row of A, whichever is more (see k_hll_sketch).
 constexpr int MG_LONG = 2048;
+
+// Entries first, first + step, ... of a row, for one slice (8 registers) of the sketch: four per lane and turn
+// (unconditional reads, index clamped; merging a sketch twice is harmless), so that the dependent loads entry ->
+// sketch of four entries overlap.
+template <int L>
+__device__ __forceinline__ void hll_walk(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
+                                         const uint64_t *__restrict__ sk, const int64_t *__restrict__ b_rp, int64_t row,
+                                         int slice, int first, int step, uint64_t &acc, long long &blen_max)
+{
+    const int64_t e1 = a_rp[row + 1];
+    for (int64_t e = a_rp[row] + first; e < e1; e += 4 * (int64_t)step) {
+        int64_t k[4];
+        uint64_t word[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t q = e + (int64_t)i * step;
+            k[i] = a_col[q < e1 ? q : e1 - 1];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) word[i] = sk[k[i] * L + slice];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc = bytemax8(acc, word[i]);
+        if (b_rp != nullptr && slice == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const long long len = b_rp[k[i] + 1] - b_rp[k[i]];
+                blen_max = len > blen_max ? len : blen_max;
+            }
+        }
+    }
+}
+
+// L consecutive lanes hold the merged sketch of slot t (row `row`), 8 registers each: estimate and store.
+template <int M>
+__device__ __forceinline__ void hll_finish(uint64_t acc, long long blen_max, int64_t t, int64_t row, int slice, bool write,
+                                           const int64_t *__restrict__ prod, const int32_t *__restrict__ maxb,
+                                           int64_t b_cols, double *__restrict__ est, uint64_t *__restrict__ merged)
+{
+    constexpr int L = M / 8;
+    double ssum = 0.0;
+    int zeros = 0;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        const unsigned r = (unsigned)(acc >> (8 * b)) & 0xFFu;
+        ssum += __longlong_as_double((long long)(1023 - (int)r) << 52);  // 2^-r, exact
+        zeros += (r == 0);
+    }
+    for (int off = L >> 1; off > 0; off >>= 1) {
+        ssum += __shfl_xor(ssum, off, WAVE);
+        zeros += __shfl_xor(zeros, off, WAVE);
+    }
+    if (write) {
+        if (merged != nullptr) merged[t * L + slice] = acc;
+        if (slice == 0) {
+            const double dm = (double)M;
+            double e = hll_alpha(M) * dm * dm / ssum;
+            if (e <= 2.5 * dm && zeros > 0) e = dm * log(dm / (double)zeros);
+            if (prod != nullptr) {
+                const long long pr = prod[row];
+                const double hi = (double)(pr < b_cols ? pr : b_cols);
+                const double lo = (double)(maxb != nullptr ? (long long)maxb[row] : blen_max);
+                e = e < lo ? lo : e;
+                e = e > hi ? hi : e;
+            }
+            est[t] = e;
+        }
+    }
+}
+
 template <int M>
 __global__ void __launch_bounds__(TPB)
 k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
             const uint64_t *__restrict__ sk, const int64_t *__restrict__ rows, int64_t n_rows, int g_log2,
-            int64_t long_from, const int64_t *__restrict__ prod, const int32_t *__restrict__ maxb, const int64_t *__restrict__ b_rp,
+            int64_t long_from, bool skip_long, const int64_t *__restrict__ prod, const int32_t *__restrict__ maxb, const int64_t *__restrict__ b_rp,
             int64_t b_cols, double *__restrict__ est, uint64_t *__restrict__ merged)
 {
     constexpr int L = M / 8;
@@ -433,63 +577,6 @@ k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
     const int sub = (int)(gt & (G - 1));
     if (threadIdx.x == 0) s_nlong = 0;
     __syncthreads();
-    // entries first, first + step, ... of a row, for this lane's slice of the sketch: four per lane and turn
-    // (unconditional reads, index clamped; merging a sketch twice is harmless), so that the dependent loads
-    // entry -> sketch of four entries overlap
-    auto walk = [&](int64_t row, int slice, int first, int step, uint64_t &acc, long long &blen_max) {
-        const int64_t e1 = a_rp[row + 1];
-        for (int64_t e = a_rp[row] + first; e < e1; e += 4 * (int64_t)step) {
-            int64_t k[4];
-            uint64_t word[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int64_t q = e + (int64_t)i * step;
-                k[i] = a_col[q < e1 ? q : e1 - 1];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) word[i] = sk[k[i] * L + slice];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc = bytemax8(acc, word[i]);
-            if (b_rp != nullptr && slice == 0) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const long long len = b_rp[k[i] + 1] - b_rp[k[i]];
-                    blen_max = len > blen_max ? len : blen_max;
-                }
-            }
-        }
-    };
-    // L consecutive lanes hold the merged sketch of slot t2 (row row2), 8 registers each: estimate and store
-    auto finish = [&](uint64_t acc, long long blen_max, int64_t t2, int64_t row2, int slice, bool first_part) {
-        double ssum = 0.0;
-        int zeros = 0;
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const unsigned r = (unsigned)(acc >> (8 * b)) & 0xFFu;
-            ssum += __longlong_as_double((long long)(1023 - (int)r) << 52);  // 2^-r, exact
-            zeros += (r == 0);
-        }
-        for (int off = L >> 1; off > 0; off >>= 1) {
-            ssum += __shfl_xor(ssum, off, WAVE);
-            zeros += __shfl_xor(zeros, off, WAVE);
-        }
-        if (t2 < n_rows && first_part) {
-            if (merged != nullptr) merged[t2 * L + slice] = acc;
-            if (slice == 0) {
-                const double dm = (double)M;
-                double e = hll_alpha(M) * dm * dm / ssum;
-                if (e <= 2.5 * dm && zeros > 0) e = dm * log(dm / (double)zeros);
-                if (prod != nullptr) {
-                    const long long pr = prod[row2];
-                    const double hi = (double)(pr < b_cols ? pr : b_cols);
-                    const double lo = (double)(maxb != nullptr ? (long long)maxb[row2] : blen_max);
-                    e = e < lo ? lo : e;
-                    e = e > hi ? hi : e;
-                }
-                est[t2] = e;
-            }
-        }
-    };
     const int slice = sub & (L - 1);
     const int part = sub / L;
     const int parts = G / L;
@@ -500,12 +587,12 @@ k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
     if (t < n_rows) {
         row = rows ? rows[t] : t;
         mine = a_rp[row + 1] - a_rp[row] < long_from;
-        if (mine) walk(row, slice, part, parts, acc, blen_max);
-        else if (sub == 0) s_long[atomicAdd(&s_nlong, 1)] = t;
+        if (mine) hll_walk<L>(a_rp, a_col, sk, b_rp, row, slice, part, parts, acc, blen_max);
+        else if (!skip_long && sub == 0) s_long[atomicAdd(&s_nlong, 1)] = t;
     }
     for (int off = L; off < G; off <<= 1) acc = bytemax8(acc, __shfl_xor((unsigned long long)acc, off, WAVE));
     if (b_rp != nullptr) blen_max = group_reduce_max(blen_max, G);
-    finish(acc, blen_max, mine ? t : n_rows, row, slice, part == 0);
+    hll_finish<M>(acc, blen_max, t, row, slice, mine && part == 0, prod, maxb, b_cols, est, merged);
     __syncthreads();
     const int nlong = s_nlong;
     for (int i = 0; i < nlong; ++i) {   // uniform
@@ -514,7 +601,7 @@ k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
         const int wslice = (int)threadIdx.x & (L - 1), wpart = (int)threadIdx.x / L;
         uint64_t a2 = 0;
         long long b2 = 0;
-        walk(row2, wslice, wpart, TPB / L, a2, b2);
+        hll_walk<L>(a_rp, a_col, sk, b_rp, row2, wslice, wpart, TPB / L, a2, b2);
         s_acc[threadIdx.x] = a2;
         if (wslice == 0) s_blen[wpart] = b2;
         __syncthreads();
@@ -527,7 +614,59 @@ k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
                 fb = s_blen[p] > fb ? s_blen[p] : fb;
             }
         }
-        if (threadIdx.x < WAVE) finish(f, fb, threadIdx.x < L ? t2 : n_rows, row2, (int)threadIdx.x & (L - 1), true);   // (whole first wave: lane swaps)
+        if (threadIdx.x < WAVE)   // (whole first wave: lane swaps)
+            hll_finish<M>(f, fb, t2, row2, (int)threadIdx.x & (L - 1), threadIdx.x < L, prod, maxb, b_cols, est, merged);
+        __syncthreads();
+    }
+}
+
+// The rows of long_from entries or more of a merge over all rows, a workgroup of 1024 threads on one after the other,
+// spread over the workgroups as in k_hll_sketch_long.
+template <int M>
+__global__ void __launch_bounds__(LONG_THREADS)
+k_hll_merge_long(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, const uint64_t *__restrict__ sk,
+                 int64_t n_rows, int64_t long_from, const int64_t *__restrict__ prod, const int32_t *__restrict__ maxb,
+                 const int64_t *__restrict__ b_rp, int64_t b_cols, double *__restrict__ est, uint64_t *__restrict__ merged)
+{
+    constexpr int L = M / 8;
+    constexpr int NW = LONG_THREADS / WAVE;
+    __shared__ uint64_t s_acc[NW][L];
+    __shared__ long long s_blen[NW];
+    __shared__ int32_t s_list[LONG_THREADS];
+    __shared__ int s_n;
+    const int tid = threadIdx.x;
+    const int slice = tid & (L - 1), wave = tid / WAVE;
+    const int64_t stretch = (int64_t)gridDim.x * LONG_ROWS;
+    const int64_t first = (int64_t)blockIdx.x * LONG_ROWS + tid % LONG_ROWS + (int64_t)(tid / LONG_ROWS) * stretch;
+    const int64_t turn = stretch * (LONG_THREADS / LONG_ROWS);
+    for (int64_t base = 0; base < n_rows; base += turn) {   // uniform
+        if (tid == 0) s_n = 0;
+        __syncthreads();
+        const int64_t r = base + first;
+        if (r < n_rows && a_rp[r + 1] - a_rp[r] >= long_from) s_list[atomicAdd(&s_n, 1)] = (int32_t)r;
+        __syncthreads();
+        const int n = s_n;
+        for (int i = 0; i < n; ++i) {   // uniform
+            const int64_t row = s_list[i];
+            uint64_t acc = 0;
+            long long blen = 0;
+            hll_walk<L>(a_rp, a_col, sk, b_rp, row, slice, tid / L, LONG_THREADS / L, acc, blen);
+            for (int off = L; off < WAVE; off <<= 1) acc = bytemax8(acc, __shfl_xor((unsigned long long)acc, off, WAVE));
+            blen = group_reduce_max(blen, WAVE);
+            if (lane_id() < L) s_acc[wave][lane_id()] = acc;
+            if (lane_id() == 0) s_blen[wave] = blen;
+            __syncthreads();
+            if (tid < WAVE) {   // (the whole first wave: lane swaps)
+                uint64_t f = 0;
+                long long fb = 0;
+                for (int w = 0; w < NW; ++w) {
+                    f = bytemax8(f, s_acc[w][slice]);
+                    fb = s_blen[w] > fb ? s_blen[w] : fb;
+                }
+                hll_finish<M>(f, fb, row, row, slice, tid < L, prod, maxb, b_cols, est, merged);
+            }
+            __syncthreads();
+        }
         __syncthreads();
     }
 }
@@ -539,18 +678,33 @@ hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const 
     if (n_rows == 0) return hipSuccess;
     const int L = m / 8;
     const double avg = A.rows ? (double)A.nnz / (double)A.rows : 1.0;
-    int g_log2 = ilog2_ceil(avg * L / (double)lanes_div, 0, 6);   // (lanes_div: see launch_hll_sketch)
+    // All rows of a matrix that is or may be skewed: the long rows go to a kernel of their own (see k_hll_sketch), so the
+    // others can have an eighth of the lanes (four entries in flight per lane, and twice the rows).  R-MAT scale 18, 64
+    // registers: 355 us with a wave per row and the long rows by the workgroup that met them, now 132 + 126 us, with a
+    // quarter of the lanes and long rows from 512 entries on 200 + 75; the gather of 4 M sketches of 64 bytes at the 1.2
+    // TB/s this GPU reaches for such pieces is 210 us.
+    const bool skip_long = lanes_div == 1 && rows == nullptr;
+    int g_log2 = ilog2_ceil(avg * L / (double)(skip_long ? 8 : lanes_div), 0, 6);   // (lanes_div: see launch_hll_sketch)
     while ((1 << g_log2) < L) ++g_log2;
     const int64_t threads = n_rows << g_log2;
     const int64_t blocks = (threads + TPB - 1) / TPB;
     const uint64_t *sk = reinterpret_cast<const uint64_t *>(sketches);
     uint64_t *mg = reinterpret_cast<uint64_t *>(merged);
-    const int64_t long_from = 8.0 * avg > (double)MG_LONG ? (int64_t)(8.0 * avg) : (int64_t)MG_LONG;
+    const int64_t least = skip_long ? LONG_SKEWED : MG_LONG;
+    const int64_t long_from = 8.0 * avg > (double)least ? (int64_t)(8.0 * avg) : least;
     switch (m) {
-    case 32: hipLaunchKernelGGL(k_hll_merge<32>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, prod, maxb, b_rp, b_cols, est, mg); break;
-    case 64: hipLaunchKernelGGL(k_hll_merge<64>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, prod, maxb, b_rp, b_cols, est, mg); break;
-    case 128: hipLaunchKernelGGL(k_hll_merge<128>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, prod, maxb, b_rp, b_cols, est, mg); break;
+    case 32: hipLaunchKernelGGL(k_hll_merge<32>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, skip_long, prod, maxb, b_rp, b_cols, est, mg); break;
+    case 64: hipLaunchKernelGGL(k_hll_merge<64>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, skip_long, prod, maxb, b_rp, b_cols, est, mg); break;
+    case 128: hipLaunchKernelGGL(k_hll_merge<128>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, skip_long, prod, maxb, b_rp, b_cols, est, mg); break;
     default: return hipErrorInvalidValue;
+    }
+    if (skip_long && A.nnz >= long_from) {   // (a matrix of fewer entries has no such row)
+        const int n = long_row_blocks(n_rows);
+        switch (m) {
+        case 32: hipLaunchKernelGGL(k_hll_merge_long<32>, dim3(n), dim3(LONG_THREADS), 0, s, A.rp, A.col, sk, n_rows, long_from, prod, maxb, b_rp, b_cols, est, mg); break;
+        case 64: hipLaunchKernelGGL(k_hll_merge_long<64>, dim3(n), dim3(LONG_THREADS), 0, s, A.rp, A.col, sk, n_rows, long_from, prod, maxb, b_rp, b_cols, est, mg); break;
+        default: hipLaunchKernelGGL(k_hll_merge_long<128>, dim3(n), dim3(LONG_THREADS), 0, s, A.rp, A.col, sk, n_rows, long_from, prod, maxb, b_rp, b_cols, est, mg); break;
+        }
     }
     return hipGetLastError();
 }
