@@ -6,6 +6,25 @@
 namespace ocean {
 
 constexpr int TPB = 256;
+// Rows a workgroup of the kernels below handles, ROW_ITEMS per thread: a tile.  The kernel that fixes the rows' capacities
+// also sums them per tile, so that one more launch, which adds up the sums of the tiles before its own, places the rows.
+constexpr int ROW_ITEMS = 4;
+constexpr int ROW_TILE = TPB * ROW_ITEMS;
+constexpr int64_t DIRECT_TILES = 4096;   // up to here every workgroup adds up the tiles before it (4 M rows: 16 loads a thread)
+
+int64_t scan_tmp_elems(int64_t n) { return (n + ROW_TILE - 1) / ROW_TILE + 1; }
+
+// Sum over the workgroup, in every thread.  s_part: one word per wave; barriers inside, s_part may be reused after.
+__device__ __forceinline__ long long block_sum(long long v, long long *s_part)
+{
+    v = group_reduce_sum(v, WAVE);
+    if (lane_id() == 0) s_part[threadIdx.x / WAVE] = v;
+    __syncthreads();
+    long long t = 0;
+    for (int w = 0; w < TPB / WAVE; ++w) t += s_part[w];
+    __syncthreads();
+    return t;
+}
 
 struct BinTable {
     int n;
@@ -45,16 +64,25 @@ k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coe
            const int32_t *__restrict__ row_mask, const int32_t *__restrict__ lower_bound,
            const int32_t *__restrict__ cmin, const int32_t *__restrict__ cmax, int vbytes, unsigned sort_mask,
            const int64_t *__restrict__ a_rp, uint8_t *__restrict__ bin_of_row, int32_t *__restrict__ cap,
-           unsigned long long *bin_count, unsigned long long *bin_prod, unsigned long long *max_cap)
+           int64_t *__restrict__ tile_cap, int32_t *zero, unsigned long long *bin_count, unsigned long long *bin_prod,
+           unsigned long long *max_cap, unsigned long long *work)
 {
     __shared__ unsigned int s_cnt[ROW_KEYS];
     __shared__ unsigned long long s_prod[ROW_KEYS];
     __shared__ unsigned int s_maxcap;
     static_assert(ROW_KEYS <= TPB && ROW_KEYS <= BIN_NONE, "one thread per key, keys in a byte");
     if (threadIdx.x < ROW_KEYS) { s_cnt[threadIdx.x] = 0; s_prod[threadIdx.x] = 0ull; }
+    // (1024 rows of fewer than 2^20 entries: below 2^30; longer rows are added to the totals one by one)
+    __shared__ unsigned int s_nnz_a[OCEAN_MAX_BINS], s_nnz_c[OCEAN_MAX_BINS];
+    __shared__ long long s_part[TPB / WAVE];
+    if (threadIdx.x < OCEAN_MAX_BINS) { s_nnz_a[threadIdx.x] = 0u; s_nnz_c[threadIdx.x] = 0u; }
     if (threadIdx.x == 0) s_maxcap = 0;
     __syncthreads();
-    for (int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x; i < m; i += (int64_t)gridDim.x * TPB) {
+    long long caps = 0;
+#pragma unroll
+    for (int q = 0; q < ROW_ITEMS; ++q) {
+        const int64_t i = (int64_t)blockIdx.x * ROW_TILE + q * TPB + threadIdx.x;
+        if (i >= m) break;
         int bin = BIN_NONE;
         long long c = 0;
         const bool active = (row_mask == nullptr) || (row_mask[i] < 0);
@@ -103,222 +131,224 @@ k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coe
                 }
             }
             if (bin == bt.n - 1 && c > 0) atomicMax(&s_maxcap, (unsigned int)c);
-            if (sort_mask != 0u && bin < NB_COUNT && pr <= kSortClass[SORT_CLASSES - 1].cap) {
-                const int cls = sort_class(pr, a_rp[i + 1] - a_rp[i], bin, sort_mask);
-                bin += cls * OCEAN_MAX_BINS;
+            const long long ne = a_rp != nullptr ? a_rp[i + 1] - a_rp[i] : 0;
+            if (work != nullptr) {
+                if (ne < (1 << 20)) atomicAdd(&s_nnz_a[bin], (unsigned int)ne);
+                else atomicAdd(&work[bin], (unsigned long long)ne);
+                if (mode == 2) {
+                    if (c < (1 << 20)) atomicAdd(&s_nnz_c[bin], (unsigned int)c);
+                    else atomicAdd(&work[OCEAN_MAX_BINS + bin], (unsigned long long)c);
+                }
             }
+            if (sort_mask != 0u && bin < NB_COUNT && pr <= kSortClass[SORT_CLASSES - 1].cap)
+                bin += sort_class(pr, ne, bin, sort_mask) * OCEAN_MAX_BINS;
             atomicAdd(&s_cnt[bin], 1u);
             if (bin_prod != nullptr) atomicAdd(&s_prod[bin], (unsigned long long)pr);
         }
         bin_of_row[i] = (uint8_t)bin;
         if (cap != nullptr) cap[i] = (int32_t)c;
+        if (zero != nullptr) zero[i] = 0;
+        caps += c;
+    }
+    if (tile_cap != nullptr) {
+        const long long sum = block_sum(caps, s_part);
+        if (threadIdx.x == 0) tile_cap[blockIdx.x] = sum;
     }
     __syncthreads();
+    if (work != nullptr && threadIdx.x < OCEAN_MAX_BINS) {
+        if (s_nnz_a[threadIdx.x]) atomicAdd(&work[threadIdx.x], (unsigned long long)s_nnz_a[threadIdx.x]);
+        if (s_nnz_c[threadIdx.x]) atomicAdd(&work[OCEAN_MAX_BINS + threadIdx.x], (unsigned long long)s_nnz_c[threadIdx.x]);
+    }
     if (threadIdx.x < ROW_KEYS && s_cnt[threadIdx.x]) atomicAdd(&bin_count[threadIdx.x], (unsigned long long)s_cnt[threadIdx.x]);
     if (bin_prod != nullptr && threadIdx.x < ROW_KEYS && s_prod[threadIdx.x]) atomicAdd(&bin_prod[threadIdx.x], s_prod[threadIdx.x]);
     if (threadIdx.x == 0 && s_maxcap && max_cap != nullptr) atomicMax(max_cap, (unsigned long long)s_maxcap);
 }
 
+// tile_cap (may be null): receives the sum of the capacities of every tile of rows (scan_tmp_elems(m) words).
+// zero (may be null): an array of m words to clear.  work (may be null): [0 .. bins) += entries of A, [bins .. 2 bins) +=
+// exact entries of C (mode 2) of the rows of each bin.
 hipError_t launch_classify(int64_t m, const BinParams &p, double scale, const int64_t *prod, const double *est,
                            const int32_t *nnz_exact, const int32_t *row_mask, const int32_t *lower_bound,
-                           uint8_t *bin_of_row, int32_t *cap, unsigned long long *bin_count,
-                           unsigned long long *bin_prod, unsigned long long *max_cap, hipStream_t s)
+                           uint8_t *bin_of_row, int32_t *cap, int64_t *tile_cap, int32_t *zero, unsigned long long *bin_count,
+                           unsigned long long *bin_prod, unsigned long long *max_cap, unsigned long long *work, hipStream_t s)
 {
     static_assert(NB_ALL <= OCEAN_MAX_BINS, "the dense-range bin has a place in the per-bin arrays");
     if (m == 0) return hipSuccess;
     BinTable bt;
     bt.n = p.n_bins;
     for (int b = 0; b < OCEAN_MAX_BINS; ++b) bt.slots[b] = b < p.n_bins ? p.slots[b] : 0;
-    int64_t blocks = (m + TPB - 1) / TPB;
-    if (blocks > 1024) blocks = 1024;   // one set of atomics per workgroup: keep the workgroups few
-    hipLaunchKernelGGL(k_classify, dim3((unsigned)blocks), dim3(TPB), 0, s, m, p.mode, p.coef, (p.table_coef > 0.0 && p.table_coef < p.coef) ? p.table_coef : p.coef, p.bound_coef, scale, bt, p.n_cols,
-                       prod, est, nnz_exact, row_mask, lower_bound, p.mode != 3 ? p.cmin : nullptr, p.cmax, p.vbytes, p.sort_mask, p.a_rp, bin_of_row,
-                       cap, bin_count, bin_prod, max_cap);
+    const int64_t tiles = (m + ROW_TILE - 1) / ROW_TILE;
+    const double table_coef = (p.table_coef > 0.0 && p.table_coef < p.coef) ? p.table_coef : p.coef;
+    hipLaunchKernelGGL(k_classify, dim3((unsigned)tiles), dim3(TPB), 0, s, m, p.mode, p.coef, table_coef, p.bound_coef, scale, bt,
+                       p.n_cols, prod, est, nnz_exact, row_mask, lower_bound, p.mode != 3 ? p.cmin : nullptr, p.cmax, p.vbytes,
+                       p.sort_mask, p.a_rp, bin_of_row, cap, tile_cap, zero, bin_count, bin_prod, max_cap, work);
     return hipGetLastError();
 }
 
-// Row ids grouped by key (bin, or sort class and bin): key b occupies bin_rows[prefix(b) .. prefix(b)+count(b)).  A
-// workgroup counts its rows per key in LDS, claims one contiguous range per key, then fills it.
-constexpr int SC_ITEMS = 8;
+// Where the rows go, from the tiles' sums and the keys' counts, in one launch:
+//   out (may be null)       exclusive prefix sum of in[0 .. m) with m + 1 elements; total_out receives the last one
+//   bin_rows (may be null)  row ids grouped by key: key b occupies bin_rows[prefix(b) .. prefix(b) + count(b)).  A
+//                           workgroup counts its rows per key in LDS, claims one contiguous range per key, then fills it
+// tile_sum: sums of in over the tiles, or, with `scanned`, their exclusive prefix sums.  It replaced a three-launch scan
+// (one workgroup for up to 65 536 rows: 39 us for 32 768) and a scatter: 5 us a launch.
 __global__ void __launch_bounds__(TPB)
-k_scatter(int64_t m, int n_keys, const uint8_t *__restrict__ bin_of_row,
-          const unsigned long long *__restrict__ bin_count, unsigned long long *bin_cursor,
-          int32_t *__restrict__ bin_rows)
+k_place(int64_t m, const int32_t *__restrict__ in, const int64_t *__restrict__ tile_sum, bool scanned,
+        int64_t *__restrict__ out, unsigned long long *total_out, int n_keys, const uint8_t *__restrict__ bin_of_row,
+        const unsigned long long *__restrict__ bin_count, unsigned long long *bin_cursor, int32_t *__restrict__ bin_rows)
 {
     __shared__ unsigned int s_cnt[ROW_KEYS];
     __shared__ unsigned int s_base[ROW_KEYS];
     __shared__ unsigned int s_wave[TPB / WAVE];
-    if (threadIdx.x < ROW_KEYS) s_cnt[threadIdx.x] = 0;
-    // first place of every key: prefix sum of the counts (fewer than 2^31 rows in all)
-    const unsigned int total = (int)threadIdx.x < n_keys ? (unsigned int)bin_count[threadIdx.x] : 0u;
-    const unsigned int upto = wave_inclusive_scan_u32(total);
-    if (lane_id() == WAVE - 1) s_wave[threadIdx.x / WAVE] = upto;
-    __syncthreads();
-    const int64_t tile = (int64_t)blockIdx.x * TPB * SC_ITEMS;
-    int bin[SC_ITEMS];
-    unsigned int rank[SC_ITEMS];
+    __shared__ long long s_part[TPB / WAVE];
+    const int tid = threadIdx.x;
+    const int64_t tile = blockIdx.x;
+    // every thread: ROW_ITEMS rows in a stretch
+    const int64_t first = tile * ROW_TILE + (int64_t)tid * ROW_ITEMS;
+    if (out != nullptr) {
+        long long before = 0;
+        if (!scanned)
+            for (int64_t t = tid; t < tile; t += TPB) before += tile_sum[t];
+        else if (tid == 0) before = tile_sum[tile];
+        before = block_sum(before, s_part);
+        int32_t item[ROW_ITEMS];
+        long long mine = 0;
 #pragma unroll
-    for (int q = 0; q < SC_ITEMS; ++q) {
-        const int64_t i = tile + (int64_t)q * TPB + threadIdx.x;
-        bin[q] = BIN_NONE;
-        rank[q] = 0;
-        if (i < m) {
-            bin[q] = bin_of_row[i];
-            if (bin[q] != BIN_NONE) rank[q] = atomicAdd(&s_cnt[bin[q]], 1u);
+        for (int q = 0; q < ROW_ITEMS; ++q) {
+            item[q] = first + q < m ? in[first + q] : 0;
+            mine += item[q];
+        }
+        long long inc = mine;
+        for (int off = 1; off < WAVE; off <<= 1) {
+            const long long o = __shfl_up(inc, off, WAVE);
+            if (lane_id() >= off) inc += o;
+        }
+        if (lane_id() == WAVE - 1) s_part[tid / WAVE] = inc;
+        __syncthreads();
+        long long run = before + inc - mine;
+        for (int w = 0; w < tid / WAVE; ++w) run += s_part[w];
+#pragma unroll
+        for (int q = 0; q < ROW_ITEMS; ++q) {
+            if (first + q < m) {
+                out[first + q] = run;
+                run += item[q];
+                if (first + q == m - 1) {
+                    out[m] = run;
+                    if (total_out != nullptr) *total_out = (unsigned long long)run;
+                }
+            }
         }
     }
+    if (bin_rows == nullptr) return;   // uniform
+    if (tid < ROW_KEYS) s_cnt[tid] = 0u;
+    // first place of every key: prefix sum of the counts (fewer than 2^31 rows in all)
+    const unsigned int total = tid < n_keys ? (unsigned int)bin_count[tid] : 0u;
+    const unsigned int upto = wave_inclusive_scan_u32(total);
+    if (lane_id() == WAVE - 1) s_wave[tid / WAVE] = upto;
     __syncthreads();
-    unsigned int start = upto - total;
-    for (int w = 0; w < (int)threadIdx.x / WAVE; ++w) start += s_wave[w];
-    if ((int)threadIdx.x < n_keys)
-        s_base[threadIdx.x] = start + (s_cnt[threadIdx.x] ? (unsigned int)atomicAdd(&bin_cursor[threadIdx.x], (unsigned long long)s_cnt[threadIdx.x]) : 0u);
+    int key[ROW_ITEMS];
+    unsigned int rank[ROW_ITEMS];
+#pragma unroll
+    for (int q = 0; q < ROW_ITEMS; ++q) {
+        key[q] = first + q < m ? (int)bin_of_row[first + q] : BIN_NONE;
+        rank[q] = key[q] != BIN_NONE ? atomicAdd(&s_cnt[key[q]], 1u) : 0u;
+    }
+    __syncthreads();
+    if (tid < n_keys) {
+        unsigned int start = upto - total;
+        for (int w = 0; w < tid / WAVE; ++w) start += s_wave[w];
+        s_base[tid] = start + (s_cnt[tid] ? (unsigned int)atomicAdd(&bin_cursor[tid], (unsigned long long)s_cnt[tid]) : 0u);
+    }
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < SC_ITEMS; ++q) {
-        const int64_t i = tile + (int64_t)q * TPB + threadIdx.x;
-        if (bin[q] != BIN_NONE) bin_rows[s_base[bin[q]] + rank[q]] = (int32_t)i;
+    for (int q = 0; q < ROW_ITEMS; ++q)
+        if (key[q] != BIN_NONE) bin_rows[s_base[key[q]] + rank[q]] = (int32_t)(first + q);
+}
+
+// Exclusive prefix sums of the tiles' sums, in place, by one workgroup (more than DIRECT_TILES tiles).
+__global__ void __launch_bounds__(TPB)
+k_scan_tiles(int64_t *tile_sum, int64_t tiles)
+{
+    __shared__ long long s_part[TPB / WAVE];
+    long long carry = 0;
+    for (int64_t base = 0; base < tiles; base += TPB) {
+        const int64_t i = base + threadIdx.x;
+        const long long v = i < tiles ? tile_sum[i] : 0;
+        long long inc = v;
+        for (int off = 1; off < WAVE; off <<= 1) {
+            const long long o = __shfl_up(inc, off, WAVE);
+            if (lane_id() >= off) inc += o;
+        }
+        if (lane_id() == WAVE - 1) s_part[threadIdx.x / WAVE] = inc;
+        __syncthreads();
+        long long before = carry;
+        for (int w = 0; w < (int)threadIdx.x / WAVE; ++w) before += s_part[w];
+        if (i < tiles) tile_sum[i] = before + inc - v;
+        for (int w = 0; w < TPB / WAVE; ++w) carry += s_part[w];
+        __syncthreads();
     }
 }
 
-hipError_t launch_scatter(int64_t m, int n_keys, const uint8_t *bin_of_row, const unsigned long long *bin_count,
-                          unsigned long long *bin_cursor, int32_t *bin_rows, hipStream_t s)
+// in / tile_sum / out: see k_place, out null: no prefix sum.  bin_rows null: no grouping.
+hipError_t launch_place(int64_t m, const int32_t *in, int64_t *tile_sum, int64_t *out, unsigned long long *total_out,
+                        int n_keys, const uint8_t *bin_of_row, const unsigned long long *bin_count,
+                        unsigned long long *bin_cursor, int32_t *bin_rows, hipStream_t s)
 {
     if (m == 0) return hipSuccess;
-    const int64_t blocks = (m + TPB * SC_ITEMS - 1) / (TPB * SC_ITEMS);
-    hipLaunchKernelGGL(k_scatter, dim3((unsigned)blocks), dim3(TPB), 0, s, m, n_keys, bin_of_row, bin_count,
-                       bin_cursor, bin_rows);
+    const int64_t tiles = (m + ROW_TILE - 1) / ROW_TILE;
+    const bool scan_first = out != nullptr && tiles > DIRECT_TILES;
+    if (scan_first) hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(TPB), 0, s, tile_sum, tiles);
+    hipLaunchKernelGGL(k_place, dim3((unsigned)tiles), dim3(TPB), 0, s, m, in, tile_sum, scan_first, out, total_out, n_keys,
+                       bin_of_row, bin_count, bin_cursor, bin_rows);
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ scan
-// Exclusive prefix sum int32 -> int64 with n+1 outputs (out[n] = total), in
-// three launches: per-block sums, scan of the block sums, per-block scan.
-constexpr int SCAN_ITEMS = 8;
-constexpr int SCAN_TILE = TPB * SCAN_ITEMS;
-
-int64_t scan_tmp_elems(int64_t n) { return (n + SCAN_TILE - 1) / SCAN_TILE + 1; }
-
-__device__ __forceinline__ long long block_exclusive_scan(long long v, long long *s_wave, long long &total)
+// Produced entries per row: their sums per tile (for launch_place), the rows that overflowed (< 0), and, with work, the
+// entries of C per bin of the other rows.  nnz2 (may be null): a row's entries where the first attempt overflowed; then
+// final_nnz receives what counts and that is what is summed.
+__global__ void __launch_bounds__(TPB)
+k_count_rows(int64_t m, const int32_t *__restrict__ nnz1, const int32_t *__restrict__ nnz2, int32_t *__restrict__ final_nnz,
+             int64_t *__restrict__ tile_sum, unsigned long long *overflowed, const uint8_t *__restrict__ bin_of_row,
+             unsigned long long *work)
 {
-    // inclusive scan inside the wave
-    long long inc = v;
-    for (int off = 1; off < WAVE; off <<= 1) {
-        long long o = __shfl_up(inc, off, WAVE);
-        if (lane_id() >= off) inc += o;
-    }
-    const int w = threadIdx.x / WAVE;
-    if (lane_id() == WAVE - 1) s_wave[w] = inc;
+    __shared__ unsigned int s_nnz_c[OCEAN_MAX_BINS];
+    __shared__ long long s_part[TPB / WAVE];
+    if (threadIdx.x < OCEAN_MAX_BINS) s_nnz_c[threadIdx.x] = 0u;
     __syncthreads();
-    long long wave_off = 0, tot = 0;
-    for (int i = 0; i < TPB / WAVE; ++i) {
-        if (i < w) wave_off += s_wave[i];
-        tot += s_wave[i];
-    }
-    __syncthreads();
-    total = tot;
-    return wave_off + inc - v;
-}
-
-__global__ void __launch_bounds__(TPB)
-k_scan_block_sums(const int32_t *__restrict__ in, int64_t n, int64_t *__restrict__ block_sum)
-{
-    __shared__ long long s_wave[TPB / WAVE];
-    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
-    long long v = 0;
+    long long sum = 0;
+    int bad = 0;
 #pragma unroll
-    for (int k = 0; k < SCAN_ITEMS; ++k)
-        if (base + k < n) v += in[base + k];
-    long long total;
-    block_exclusive_scan(v, s_wave, total);
-    if (threadIdx.x == 0) block_sum[blockIdx.x] = total;
-}
-
-__global__ void __launch_bounds__(TPB)
-k_scan_of_sums(int64_t *block_sum, int64_t n_blocks, unsigned long long *total_out)
-{
-    __shared__ long long s_wave[TPB / WAVE];
-    long long carry = 0;
-    for (int64_t base = 0; base < n_blocks; base += TPB) {
-        const int64_t i = base + threadIdx.x;
-        long long v = i < n_blocks ? block_sum[i] : 0;
-        long long total;
-        long long ex = block_exclusive_scan(v, s_wave, total);
-        if (i < n_blocks) block_sum[i] = carry + ex;
-        carry += total;
-    }
-    if (threadIdx.x == 0) {
-        block_sum[n_blocks] = carry;
-        if (total_out != nullptr) *total_out = (unsigned long long)carry;
-    }
-}
-
-// The whole scan by one workgroup, tile after tile with a running carry: for inputs so short that three
-// launches would cost more than the work (up to SCAN_SMALL_MAX elements).
-constexpr int64_t SCAN_SMALL_MAX = 65536;
-__global__ void __launch_bounds__(TPB)
-k_scan_small(const int32_t *__restrict__ in, int64_t n, int64_t *__restrict__ out, unsigned long long *total_out)
-{
-    __shared__ long long s_wave[TPB / WAVE];
-    long long carry = 0;
-    for (int64_t tile = 0; tile < n; tile += SCAN_TILE) {
-        const int64_t base = tile + (int64_t)threadIdx.x * SCAN_ITEMS;
-        long long item[SCAN_ITEMS];
-        long long v = 0;
-#pragma unroll
-        for (int k = 0; k < SCAN_ITEMS; ++k) {
-            item[k] = (base + k < n) ? in[base + k] : 0;
-            v += item[k];
+    for (int q = 0; q < ROW_ITEMS; ++q) {
+        const int64_t i = (int64_t)blockIdx.x * ROW_TILE + q * TPB + threadIdx.x;
+        if (i >= m) break;
+        int32_t c = nnz1[i];
+        bad += c < 0;
+        if (work != nullptr && c > 0) {
+            const int b = (int)bin_of_row[i] % OCEAN_MAX_BINS;
+            if (c < (1 << 20)) atomicAdd(&s_nnz_c[b], (unsigned int)c);   // (1024 rows: below 2^30)
+            else atomicAdd(&work[OCEAN_MAX_BINS + b], (unsigned long long)c);
         }
-        long long total;
-        long long run = carry + block_exclusive_scan(v, s_wave, total);
-#pragma unroll
-        for (int k = 0; k < SCAN_ITEMS; ++k) {
-            if (base + k < n) out[base + k] = run;
-            run += item[k];
+        if (nnz2 != nullptr) {
+            c = c >= 0 ? c : nnz2[i];
+            final_nnz[i] = c;
         }
-        carry += total;
+        sum += c;
     }
+    const unsigned long long rows = (unsigned long long)block_sum(bad, s_part);
+    sum = block_sum(sum, s_part);
     if (threadIdx.x == 0) {
-        out[n] = carry;
-        if (total_out != nullptr) *total_out = (unsigned long long)carry;
+        if (tile_sum != nullptr) tile_sum[blockIdx.x] = sum;
+        if (rows != 0 && overflowed != nullptr) atomicAdd(overflowed, rows);
     }
+    if (work != nullptr && threadIdx.x < OCEAN_MAX_BINS && s_nnz_c[threadIdx.x])
+        atomicAdd(&work[OCEAN_MAX_BINS + threadIdx.x], (unsigned long long)s_nnz_c[threadIdx.x]);
 }
 
-__global__ void __launch_bounds__(TPB)
-k_scan_apply(const int32_t *__restrict__ in, int64_t n, const int64_t *__restrict__ block_sum, int64_t n_blocks,
-             int64_t *__restrict__ out)
+hipError_t launch_count_rows(int64_t m, const int32_t *nnz1, const int32_t *nnz2, int32_t *final_nnz, int64_t *tile_sum,
+                             unsigned long long *overflowed, const uint8_t *bin_of_row, unsigned long long *work, hipStream_t s)
 {
-    __shared__ long long s_wave[TPB / WAVE];
-    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
-    long long item[SCAN_ITEMS];
-    long long v = 0;
-#pragma unroll
-    for (int k = 0; k < SCAN_ITEMS; ++k) {
-        item[k] = (base + k < n) ? in[base + k] : 0;
-        v += item[k];
-    }
-    long long total;
-    long long run = block_sum[blockIdx.x] + block_exclusive_scan(v, s_wave, total);
-#pragma unroll
-    for (int k = 0; k < SCAN_ITEMS; ++k) {
-        if (base + k < n) out[base + k] = run;
-        run += item[k];
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = block_sum[n_blocks];
-}
-
-// total_out (may be null): a device word that receives the sum of all elements as well.
-hipError_t launch_scan_i32_to_i64(const int32_t *in, int64_t n, int64_t *out, int64_t *block_tmp,
-                                  unsigned long long *total_out, hipStream_t s)
-{
-    const int64_t n_blocks = (n + SCAN_TILE - 1) / SCAN_TILE;
-    if (n <= SCAN_SMALL_MAX) {   // (also n == 0: out[0] = 0)
-        hipLaunchKernelGGL(k_scan_small, dim3(1), dim3(TPB), 0, s, in, n, out, total_out);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(k_scan_block_sums, dim3((unsigned)n_blocks), dim3(TPB), 0, s, in, n, block_tmp);
-    hipLaunchKernelGGL(k_scan_of_sums, dim3(1), dim3(TPB), 0, s, block_tmp, n_blocks, total_out);
-    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)n_blocks), dim3(TPB), 0, s, in, n, block_tmp, n_blocks, out);
+    if (m == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_count_rows, dim3((unsigned)((m + ROW_TILE - 1) / ROW_TILE)), dim3(TPB), 0, s, m, nnz1, nnz2, final_nnz,
+                       tile_sum, overflowed, bin_of_row, work);
     return hipGetLastError();
 }
 
@@ -339,74 +369,6 @@ static hipError_t fill(T *p, int64_t n, T v, hipStream_t s)
     hipLaunchKernelGGL(k_fill<T>, dim3((unsigned)blocks), dim3(TPB), 0, s, p, n, v);
     return hipGetLastError();
 }
-hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s) { return fill<int32_t>(p, n, v, s); }
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s) { return fill<unsigned long long>(p, n, v, s); }
-
-// -------------------------------------------------- overflow bookkeeping
-__global__ void __launch_bounds__(TPB)
-k_count_overflow(int64_t m, const int32_t *__restrict__ row_nnz, unsigned long long *count)
-{
-    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    const bool ovf = i < m && row_nnz[i] < 0;
-    const unsigned long long b = __ballot(ovf);
-    if (b != 0 && lane_id() == 0) atomicAdd(count, (unsigned long long)__popcll(b));
-}
-
-hipError_t launch_count_overflow(int64_t m, const int32_t *row_nnz, unsigned long long *count, hipStream_t s)
-{
-    if (m == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_count_overflow, dim3((unsigned)((m + TPB - 1) / TPB)), dim3(TPB), 0, s, m, row_nnz, count);
-    return hipGetLastError();
-}
-
-// final size of each row: first attempt unless it overflowed, then the retry's
-__global__ void __launch_bounds__(TPB)
-k_final_nnz(int64_t m, const int32_t *__restrict__ nnz1, const int32_t *__restrict__ nnz2, int32_t *__restrict__ out)
-{
-    const int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (i < m) out[i] = nnz1[i] >= 0 ? nnz1[i] : nnz2[i];
-}
-
-hipError_t launch_final_nnz(int64_t m, const int32_t *nnz1, const int32_t *nnz2, int32_t *out, hipStream_t s)
-{
-    if (m == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_final_nnz, dim3((unsigned)((m + TPB - 1) / TPB)), dim3(TPB), 0, s, m, nnz1, nnz2, out);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------ per-bin work sums
-// For reporting only: intermediate products, entries of A and entries of C
-// handled by each numeric bin.  sums[3 * OCEAN_MAX_BINS], zero on entry.
-__global__ void __launch_bounds__(TPB)
-k_bin_work(int64_t m, const uint8_t *__restrict__ bin_of_row, const int64_t *__restrict__ prod,
-           const int64_t *__restrict__ a_rp, const int32_t *__restrict__ row_nnz, unsigned long long *sums)
-{
-    __shared__ unsigned long long s_sum[3 * OCEAN_MAX_BINS];
-    if (threadIdx.x < 3 * OCEAN_MAX_BINS) s_sum[threadIdx.x] = 0;
-    __syncthreads();
-    for (int64_t i = (int64_t)blockIdx.x * TPB + threadIdx.x; i < m; i += (int64_t)gridDim.x * TPB) {
-        const int key = bin_of_row[i];
-        if (key != BIN_NONE) {
-            const int b = key % OCEAN_MAX_BINS;
-            atomicAdd(&s_sum[b], (unsigned long long)prod[i]);
-            atomicAdd(&s_sum[OCEAN_MAX_BINS + b], (unsigned long long)(a_rp[i + 1] - a_rp[i]));
-            const int32_t c = row_nnz[i];
-            if (c > 0) atomicAdd(&s_sum[2 * OCEAN_MAX_BINS + b], (unsigned long long)c);
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < 3 * OCEAN_MAX_BINS && s_sum[threadIdx.x]) atomicAdd(&sums[threadIdx.x], s_sum[threadIdx.x]);
-}
-
-hipError_t launch_bin_work(int64_t m, const uint8_t *bin_of_row, const int64_t *prod, const int64_t *a_rp,
-                           const int32_t *row_nnz, unsigned long long *sums, hipStream_t s)
-{
-    if (m == 0) return hipSuccess;
-    int64_t blocks = (m + TPB - 1) / TPB;
-    if (blocks > 512) blocks = 512;
-    hipLaunchKernelGGL(k_bin_work, dim3((unsigned)blocks), dim3(TPB), 0, s, m, bin_of_row, prod, a_rp,
-                       row_nnz, sums);
-    return hipGetLastError();
-}
 
 }  // namespace ocean

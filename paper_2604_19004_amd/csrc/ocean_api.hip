@@ -43,13 +43,13 @@ struct Scalars {
     unsigned long long bin_count[ROW_KEYS];       // rows by key (sort class and bin; the bin itself in the symbolic pass)
     unsigned long long bin_cursor[ROW_KEYS];
     unsigned long long bin_prod[ROW_KEYS];        // intermediate products of the rows of each key
+    unsigned long long bin_work[2 * OCEAN_MAX_BINS];   // entries of A, entries of C per numeric bin
     unsigned long long max_cap;
     unsigned long long ovf_count;
     unsigned long long queue[4];
     double sample_sums[6];                        // products, estimates, per-row CR, its squares, rows counted
     int32_t flags;
     int32_t pad;
-    unsigned long long bin_work[3 * OCEAN_MAX_BINS];   // products, entries of A, entries of C per numeric bin
     unsigned long long near_pairs[2];             // sampled entries of B, and those whose successor's column is 1 .. 4 larger
     unsigned long long row_totals[ROW_TOTAL_SLOTS * ROW_TOTAL_STRIDE];   // totals of the row-products pass, by slot
 };
@@ -78,6 +78,7 @@ struct Ctx {
     int lanes_div = 1;      // see lanes_div_of
     Scalars *h = nullptr;   // pinned host mirror
     // stage timing
+    bool timed = false;     // the caller asked for statistics
     std::vector<hipEvent_t> ev;
     std::vector<int> ev_stage;
     std::vector<std::pair<int, int>> bin_ev;   // (numeric bin, index of the event recorded before its launch)
@@ -178,8 +179,10 @@ int ctx_init(Ctx &c, const ocean_options *opt, ocean_stream_t stream)
     return OCEAN_OK;
 }
 
+// An event that ends the stage before and begins `stage` (2 us of the stream each; none without statistics).
 int mark(Ctx &c, int stage)
 {
+    if (!c.timed) return OCEAN_OK;
     const size_t i = c.ev.size();
     if (g_pinned.events.size() <= i) {
         hipEvent_t e;
@@ -317,7 +320,7 @@ int zero_bins(Ctx &c, Work &w)
         return OCEAN_OK;
     }
     HIP_TRY(hipMemsetAsync(w.sc->bin_count, 0,
-                           sizeof(unsigned long long) * (3 * ROW_KEYS + 2 + 4), c.s));   // counts, cursors, products, max_cap, ovf, queues
+                           sizeof(unsigned long long) * (3 * ROW_KEYS + 2 * OCEAN_MAX_BINS + 2 + 4), c.s));   // .. up to the queues
     return OCEAN_OK;
 }
 
@@ -357,7 +360,6 @@ void sample_rows_of(int64_t rows, const ocean_options &o, int64_t *out);
 int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, double assist_cr, bool query_bitmap,
                  int32_t *nnz_out, ocean_stats *st)
 {
-    HIP_TRY(launch_fill_i32(nnz_out, A.rows, 0, c.s));
     // With at most 2^20 columns the bitmap kernel covers a row in one window, and one pass over such a
     // window costs less than building a key table of 16384 or 32768 slots: those two bins go with it
     // (the row lists of consecutive bins are adjacent).
@@ -372,8 +374,9 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
         bp.n_cols = B.cols;
         OC_TRY(zero_bins(c, w));
         HIP_TRY(launch_classify(A.rows, bp, 1.0, w.prod, nullptr, nullptr, round == 0 ? nullptr : nnz_out, w.maxb, w.bin,
-                                nullptr, w.sc->bin_count, nullptr, nullptr, c.s));
-        HIP_TRY(launch_scatter(A.rows, SB_COUNT, w.bin, w.sc->bin_count, w.sc->bin_cursor, w.bin_rows, c.s));
+                                nullptr, nullptr, round == 0 ? nnz_out : nullptr, w.sc->bin_count, nullptr, nullptr, nullptr, c.s));
+        HIP_TRY(launch_place(A.rows, nullptr, nullptr, nullptr, nullptr, SB_COUNT, w.bin, w.sc->bin_count, w.sc->bin_cursor,
+                             w.bin_rows, c.s));
         OC_TRY(fetch_scalars(c, w.sc));
         int64_t start[SB_COUNT + 1];
         start[0] = 0;
@@ -393,7 +396,7 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
             HIP_TRY(launch_symbolic_bin(A, B, l, gb_log2, nnz_out, n_wg, &w.sc->queue[round], c.s));
         }
         if (!assisted) break;
-        HIP_TRY(launch_count_overflow(A.rows, nnz_out, &w.sc->ovf_count, c.s));
+        HIP_TRY(launch_count_rows(A.rows, nnz_out, nullptr, nullptr, nullptr, &w.sc->ovf_count, nullptr, nullptr, c.s));
         OC_TRY(fetch_scalars(c, w.sc));
         if (st) st->symbolic_overflow_rows = (int64_t)c.h->ovf_count;
         if (c.h->ovf_count == 0) break;
@@ -776,6 +779,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
 
     const int64_t n_sample = sample_size_of(m, o);
     Work w;
+    c.timed = st != nullptr;
     OC_TRY(mark(c, OCEAN_ST_ANALYSIS));
     OC_TRY(work_alloc(c, w, m, n_sample));
     ocean_stats local{};
@@ -863,7 +867,6 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     const int64_t *out_ptr = nullptr;
     for (;;) {   // at most two rounds: an estimation workflow may fall back to the two-pass one when memory is short
         // ---- size prediction ----
-        OC_TRY(mark(c, OCEAN_ST_PREDICT));
         BinParams bp{};
         bp.n_bins = NB_COUNT;
         for (int b = 0; b < NB_COUNT; ++b) bp.slots[b] = kNumericSlots[b];
@@ -883,6 +886,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
             bp.coef = o.expand_coef > 0.0 ? o.expand_coef : (m_regs == 32 ? 2.0 : 1.5);
             bp.table_coef = o.estimate_table_coef;
         } else if (workflow == OCEAN_WF_SYMBOLIC) {
+            OC_TRY(mark(c, OCEAN_ST_PREDICT));
             S->assist_cr = o.assisted_symbolic ? conservative_cr(S, o) : 1.0;
             if (!(S->assist_cr > 1.0)) S->assist_cr = 0.0;
             OC_TRY(run_symbolic(c, w, A, B, gb_log2, S->assist_cr, query_bitmap, w.nnz_final, S));
@@ -900,10 +904,10 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         OC_TRY(mark(c, OCEAN_ST_BINNING));
         OC_TRY(zero_bins(c, w));
         int64_t *ptr = workflow == OCEAN_WF_SYMBOLIC ? c_rp : w.tmp_ptr;
-        HIP_TRY(launch_classify(m, bp, o.estimate_scale, w.prod, w.est, w.nnz_final, nullptr, nullptr, w.bin, w.cap,
-                                w.sc->bin_count, w.sc->bin_prod, &w.sc->max_cap, c.s));
-        HIP_TRY(launch_scan_i32_to_i64(w.cap, m, ptr, w.scan_tmp, &w.sc->totals[0], c.s));   // totals[0]: total slots
-        HIP_TRY(launch_scatter(m, ROW_KEYS, w.bin, w.sc->bin_count, w.sc->bin_cursor, w.bin_rows, c.s));
+        HIP_TRY(launch_classify(m, bp, o.estimate_scale, w.prod, w.est, w.nnz_final, nullptr, nullptr, w.bin, w.cap, w.scan_tmp,
+                                w.row_nnz, w.sc->bin_count, w.sc->bin_prod, &w.sc->max_cap, st ? w.sc->bin_work : nullptr, c.s));
+        HIP_TRY(launch_place(m, w.cap, w.scan_tmp, ptr, &w.sc->totals[0], ROW_KEYS, w.bin, w.sc->bin_count, w.sc->bin_cursor,
+                             w.bin_rows, c.s));   // totals[0]: total slots
         OC_TRY(fetch_scalars(c, w.sc));
         total_slots = (int64_t)c.h->totals[0];
         for (int b = 0; b < NB_ALL; ++b) {
@@ -957,28 +961,27 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     double global_coef = workflow == OCEAN_WF_SYMBOLIC ? o.exact_load_coef : 1.25;
 
     // ---- numeric ----
-    OC_TRY(mark(c, OCEAN_ST_NUMERIC));
-    HIP_TRY(launch_fill_i32(w.row_nnz, m, 0, c.s));
+    {   // (the first launch marks the stage, unless the heavy rows are put in order before theirs)
+        unsigned long long heavy = 0;
+        for (int b = NB_S8K; b < NB_COUNT; ++b) heavy += bin_count[b];
+        if (heavy > 0) OC_TRY(mark(c, OCEAN_ST_NUMERIC));
+    }
     // expand-sort-compress needs every row of its bins to have no more products than lanes (true when the bins come
     // from the product bound and B has at least 32 columns) and column ids that leave room for the lane number
     OC_TRY(run_numeric(c, w, A, Bnum, dtype, gb_log2, bin_count, bin_prod, max_cap, global_coef, out_ptr, t_col, t_val, w.row_nnz, 0,
                        OCEAN_ST_NUMERIC, st != nullptr, esc_ok && workflow == OCEAN_WF_UPPER_BOUND));
-    if (st) {
-        HIP_TRY(hipMemsetAsync(w.sc->bin_work, 0, sizeof(w.sc->bin_work), c.s));
-        HIP_TRY(launch_bin_work(m, w.bin, w.prod, A.rp, w.row_nnz, w.sc->bin_work, c.s));
-    }
-
     auto copy_bin_work = [&]() {
         for (int b = 0; b < OCEAN_MAX_BINS; ++b) {
-            S->bin_products[b] = (int64_t)c.h->bin_work[b];
-            S->bin_nnz_a[b] = (int64_t)c.h->bin_work[OCEAN_MAX_BINS + b];
-            S->bin_nnz_c[b] = (int64_t)c.h->bin_work[2 * OCEAN_MAX_BINS + b];
+            S->bin_products[b] = 0;
+            for (int k = b; k < ROW_KEYS; k += OCEAN_MAX_BINS) S->bin_products[b] += (int64_t)bin_prod[k];
+            S->bin_nnz_a[b] = (int64_t)c.h->bin_work[b];
+            S->bin_nnz_c[b] = (int64_t)c.h->bin_work[OCEAN_MAX_BINS + b];
         }
     };
     if (workflow == OCEAN_WF_SYMBOLIC) {
         OC_TRY(mark(c, -1));
-        OC_TRY(fetch_scalars(c, w.sc));
-        copy_bin_work();
+        HIP_TRY(hipStreamSynchronize(c.s));
+        copy_bin_work();   // (fetched with the bins: the exact sizes were known then)
         S->nnz_c = total_slots;
         C->row_ptr = c_rp;
         C->col_idx = t_col;
@@ -993,11 +996,9 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     // ---- overflow rows: redo them with bound-sized tables (Section 3.2) ----
     S->temp_slots = total_slots;
     OC_TRY(mark(c, workflow == OCEAN_WF_UPPER_BOUND ? OCEAN_ST_COMPACT : OCEAN_ST_RETRY));
-    // (sizes from the product bound cannot fall short: nothing to count in the upper-bound workflow, unless rows ran
-    // with the dense accumulator over a guessed column range)
-    if (workflow != OCEAN_WF_UPPER_BOUND || w.spans) HIP_TRY(launch_count_overflow(m, w.row_nnz, &w.sc->ovf_count, c.s));
+    HIP_TRY(launch_count_rows(m, w.row_nnz, nullptr, nullptr, w.scan_tmp, &w.sc->ovf_count, w.bin, st ? w.sc->bin_work : nullptr, c.s));
     // optimistic: if nothing overflowed this scan already is the final row_ptr
-    HIP_TRY(launch_scan_i32_to_i64(w.row_nnz, m, c_rp, w.scan_tmp, &w.sc->totals[0], c.s));
+    HIP_TRY(launch_place(m, w.row_nnz, w.scan_tmp, c_rp, &w.sc->totals[0], 0, nullptr, nullptr, nullptr, nullptr, c.s));
     OC_TRY(fetch_scalars(c, w.sc));
     copy_bin_work();
     const int64_t n_ovf = (int64_t)c.h->ovf_count;
@@ -1016,10 +1017,10 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         bp.sort_mask = c.sort_mask;
         bp.a_rp = A.rp;
         OC_TRY(zero_bins(c, w));
-        HIP_TRY(launch_classify(m, bp, 1.0, w.prod, nullptr, nullptr, w.row_nnz, nullptr, w.bin, w.cap, w.sc->bin_count,
-                                w.sc->bin_prod, &w.sc->max_cap, c.s));
-        HIP_TRY(launch_scan_i32_to_i64(w.cap, m, w.tmp_ptr2, w.scan_tmp, &w.sc->totals[0], c.s));
-        HIP_TRY(launch_scatter(m, ROW_KEYS, w.bin, w.sc->bin_count, w.sc->bin_cursor, w.bin_rows, c.s));
+        HIP_TRY(launch_classify(m, bp, 1.0, w.prod, nullptr, nullptr, w.row_nnz, nullptr, w.bin, w.cap, w.scan_tmp, w.row_nnz2,
+                                w.sc->bin_count, w.sc->bin_prod, &w.sc->max_cap, nullptr, c.s));
+        HIP_TRY(launch_place(m, w.cap, w.scan_tmp, w.tmp_ptr2, &w.sc->totals[0], ROW_KEYS, w.bin, w.sc->bin_count,
+                             w.sc->bin_cursor, w.bin_rows, c.s));
         OC_TRY(fetch_scalars(c, w.sc));
         const int64_t slots2 = (int64_t)c.h->totals[0];
         r_col = static_cast<int32_t *>(c.alloc((size_t)slots2 * 4));
@@ -1028,11 +1029,10 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         unsigned long long bc2[ROW_KEYS], bp2[ROW_KEYS];
         std::memcpy(bc2, c.h->bin_count, sizeof(bc2));
         std::memcpy(bp2, c.h->bin_prod, sizeof(bp2));
-        HIP_TRY(launch_fill_i32(w.row_nnz2, m, 0, c.s));
         OC_TRY(run_numeric(c, w, A, Bnum, dtype, gb_log2, bc2, bp2, (int64_t)c.h->max_cap, 1.25, w.tmp_ptr2, r_col, r_val,
                            w.row_nnz2, 2, OCEAN_ST_RETRY, false, esc_ok));
-        HIP_TRY(launch_final_nnz(m, w.row_nnz, w.row_nnz2, w.nnz_final, c.s));
-        HIP_TRY(launch_scan_i32_to_i64(w.nnz_final, m, c_rp, w.scan_tmp, &w.sc->totals[0], c.s));
+        HIP_TRY(launch_count_rows(m, w.row_nnz, w.row_nnz2, w.nnz_final, w.scan_tmp, nullptr, nullptr, nullptr, c.s));
+        HIP_TRY(launch_place(m, w.nnz_final, w.scan_tmp, c_rp, &w.sc->totals[0], 0, nullptr, nullptr, nullptr, nullptr, c.s));
         OC_TRY(fetch_scalars(c, w.sc));
         nnz_c = (int64_t)c.h->totals[0];
     }

@@ -250,27 +250,23 @@ struct BinParams {
     const int32_t *cmax; // pays for it go to the dense-range bin NB_DSPAN (modes 0, 1, 2)
     int vbytes;          // bytes of a value (with cmin)
     unsigned sort_mask;  // sort classes that may be used (bit c; modes 0, 1, 2), 0: none
-    const int64_t *a_rp; // row offsets of A (with sort_mask)
+    const int64_t *a_rp; // row offsets of A (with sort_mask or work sums)
     int n_bins;
     int32_t slots[OCEAN_MAX_BINS];
     int64_t n_cols;
 };
 hipError_t launch_classify(int64_t m, const BinParams &p, double scale, const int64_t *prod, const double *est,
                            const int32_t *nnz_exact, const int32_t *row_mask, const int32_t *lower_bound,
-                           uint8_t *bin_of_row, int32_t *cap, unsigned long long *bin_count,
-                           unsigned long long *bin_prod /*products per bin, may be null*/, unsigned long long *max_cap,
-                           hipStream_t s);
-hipError_t launch_scatter(int64_t m, int n_keys, const uint8_t *bin_of_row, const unsigned long long *bin_count,
-                          unsigned long long *bin_cursor, int32_t *bin_rows, hipStream_t s);
-hipError_t launch_scan_i32_to_i64(const int32_t *in, int64_t n, int64_t *out, int64_t *block_tmp,
-                                  unsigned long long *total_out, hipStream_t s);
-int64_t scan_tmp_elems(int64_t n);
-hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
+                           uint8_t *bin_of_row, int32_t *cap, int64_t *tile_cap, int32_t *zero, unsigned long long *bin_count,
+                           unsigned long long *bin_prod /*products per key, may be null*/, unsigned long long *max_cap,
+                           unsigned long long *work, hipStream_t s);
+hipError_t launch_place(int64_t m, const int32_t *in, int64_t *tile_sum, int64_t *out, unsigned long long *total_out,
+                        int n_keys, const uint8_t *bin_of_row, const unsigned long long *bin_count,
+                        unsigned long long *bin_cursor, int32_t *bin_rows, hipStream_t s);
+hipError_t launch_count_rows(int64_t m, const int32_t *nnz1, const int32_t *nnz2, int32_t *final_nnz, int64_t *tile_sum,
+                             unsigned long long *overflowed, const uint8_t *bin_of_row, unsigned long long *work, hipStream_t s);
+int64_t scan_tmp_elems(int64_t n);   // words of tile sums for n rows
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s);
-hipError_t launch_count_overflow(int64_t m, const int32_t *row_nnz, unsigned long long *count, hipStream_t s);
-hipError_t launch_bin_work(int64_t m, const uint8_t *bin_of_row, const int64_t *prod, const int64_t *a_rp,
-                           const int32_t *row_nnz, unsigned long long *sums /*3*OCEAN_MAX_BINS, zero*/, hipStream_t s);
-hipError_t launch_final_nnz(int64_t m, const int32_t *nnz1, const int32_t *nnz2, int32_t *out, hipStream_t s);
 
 // symbolic.hip
 struct SymLaunch {
