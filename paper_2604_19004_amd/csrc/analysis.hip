@@ -60,19 +60,15 @@ __global__ void k_validate(const int64_t *rp, const int32_t *col, int64_t rows, 
     }
 }
 
-// b_near_pairs: two zeroed device counters that receive the clustering measure of B's columns (see k_validate).
-hipError_t launch_validate(const Csr &A, const Csr &B, int32_t *flags, unsigned long long *b_near_pairs, hipStream_t s)
+// Input check of B, bit 2 of flags.  near_pairs: two zeroed device counters (see k_validate).  A is checked by the kernel
+// that counts its products; where B is the same matrix that kernel takes the sample as well.
+hipError_t launch_validate(const Csr &B, int32_t *flags, unsigned long long *near_pairs, hipStream_t s)
 {
-    auto go = [&](const Csr &M, int bit, unsigned long long *near) {
-        int64_t work = M.nnz > M.rows ? M.nnz : M.rows;
-        int blocks = (int)((work + TPB * 4 - 1) / (TPB * 4));
-        if (blocks < 1) blocks = 1;
-        if (blocks > 65536) blocks = 65536;
-        hipLaunchKernelGGL(k_validate, dim3(blocks), dim3(TPB), 0, s, M.rp, M.col, M.rows, M.cols, M.nnz, flags, bit, near);
-    };
-    const bool same = B.rp == A.rp && B.col == A.col && B.rows == A.rows && B.cols == A.cols;
-    go(A, 1, same ? b_near_pairs : nullptr);
-    if (!same) go(B, 2, b_near_pairs);
+    int64_t work = B.nnz > B.rows ? B.nnz : B.rows;
+    int blocks = (int)((work + TPB * 4 - 1) / (TPB * 4));
+    if (blocks < 1) blocks = 1;
+    if (blocks > 65536) blocks = 65536;
+    hipLaunchKernelGGL(k_validate, dim3(blocks), dim3(TPB), 0, s, B.rp, B.col, B.rows, B.cols, B.nnz, flags, 2, near_pairs);
     return hipGetLastError();
 }
 
@@ -112,8 +108,12 @@ __global__ void __launch_bounds__(TPB)
 k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, int64_t m, int64_t a_nnz,
                const int64_t *__restrict__ b_rp, int64_t b_rows, int g_log2, int64_t *__restrict__ prod,
                int32_t *__restrict__ maxb, unsigned long long *totals, int32_t *flags,
-               int32_t *__restrict__ long_rows, unsigned long long *long_count, int64_t heavy_from)
+               int32_t *__restrict__ long_rows, unsigned long long *long_count, int64_t heavy_from, int bad_bit,
+               unsigned long long *near_pairs)
 {
+    __shared__ unsigned int s_near, s_seen;
+    const bool sampling = near_pairs != nullptr && (blockIdx.x & 15u) == 0u;   // uniform
+    unsigned int near = 0, seen = 0;
     __shared__ long long s_sum[TPB / WAVE];
     __shared__ long long s_max[TPB / WAVE];
     __shared__ long long s_heavy[TPB / WAVE];
@@ -123,7 +123,7 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
     const int sub = threadIdx.x & (G - 1);
     const int64_t long_len = (int64_t)G * 16;
     long long tsum = 0, tmax = 0, theavy = 0;
-    bool bad = false, bad_rp = false;
+    bool bad = false, bad_rp = bad_bit != 0 && blockIdx.x == 0 && threadIdx.x == 0 && (a_rp[0] != 0 || a_rp[m] != a_nnz);
     for (int64_t base = (int64_t)blockIdx.x * R; base < m; base += (int64_t)gridDim.x * R) {
         const int64_t row = base + rl;
         long long p = 0, mx = 0;
@@ -148,6 +148,10 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
                         const int64_t idx = e + (int64_t)i * G;
                         ok[i] = idx < e1;
                         k[i] = a_col[ok[i] ? idx : e];
+                        if (sampling && ok[i] && idx + 1 < a_nnz) {
+                            near += (uint32_t)(a_col[idx + 1] - k[i] - 1) < 4u;
+                            ++seen;
+                        }
                         if ((uint32_t)k[i] >= (uint64_t)b_rows) { bad = true; k[i] = 0; ok[i] = false; }
                     }
                     long long len[4];
@@ -174,8 +178,19 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
         }
     }
     block_totals(tsum, tmax, theavy, s_sum, s_max, s_heavy, totals);
-    if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(flags, 4);
+    if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(flags, 4 | bad_bit);
     if (__ballot(bad_rp) != 0 && lane_id() == 0) atomicOr(flags, 1);
+    if (sampling) {
+        if (threadIdx.x == 0) { s_near = 0u; s_seen = 0u; }
+        __syncthreads();
+        const unsigned int wave_near = wave_sum_u32(near), wave_seen = wave_sum_u32(seen);
+        if (lane_id() == 0) { atomicAdd(&s_near, wave_near); atomicAdd(&s_seen, wave_seen); }
+        __syncthreads();
+        if (threadIdx.x == 0 && s_seen) {
+            atomicAdd(&near_pairs[0], (unsigned long long)s_seen);
+            atomicAdd(&near_pairs[1], (unsigned long long)s_near);
+        }
+    }
 }
 
 // The listed long rows: one workgroup per row at a time.
@@ -183,7 +198,7 @@ __global__ void __launch_bounds__(TPB)
 k_row_products_long(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
                     const int64_t *__restrict__ b_rp, int64_t b_rows, int64_t *__restrict__ prod,
                     int32_t *__restrict__ maxb, unsigned long long *totals, int32_t *flags,
-                    const int32_t *__restrict__ long_rows, const unsigned long long *long_count, int64_t heavy_from)
+                    const int32_t *__restrict__ long_rows, const unsigned long long *long_count, int64_t heavy_from, int bad_bit)
 {
     __shared__ long long s_sum[TPB / WAVE];
     __shared__ long long s_max[TPB / WAVE];
@@ -233,15 +248,19 @@ k_row_products_long(const int64_t *__restrict__ a_rp, const int32_t *__restrict_
         __syncthreads();
     }
     block_totals(tsum, tmax, theavy, s_sum, s_max, s_heavy, totals);
-    if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(flags, 4);
+    if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(flags, 4 | bad_bit);
 }
 
+// validate: A's offsets must begin at 0 and end at its number of entries as well, and any fault of A sets bit 1 of flags
+// (offsets that descend or leave [0, nnz] always do, column ids outside [0, b_rows) always set bit 4).  near_pairs (may
+// be null): see k_validate.
 // long_rows: scratch for A.rows row ids, long_count: a zeroed device counter; both may be null
 // (then every row is handled by its lane group).
 hipError_t launch_row_products(const Csr &A, const int64_t *b_rp, int64_t b_rows, int64_t *prod, int32_t *maxb,
                                unsigned long long *totals, int32_t *flags, int32_t *long_rows,
-                               unsigned long long *long_count, hipStream_t s)
+                               unsigned long long *long_count, bool validate, unsigned long long *near_pairs, hipStream_t s)
 {
+    const int bad_bit = validate ? 1 : 0;
     const int64_t heavy_from = kNumericSlots[NB_S4K];   // beyond the largest LDS hash table that sorted inputs use
     if (A.rows == 0) return hipSuccess;
     const double avg = A.rows ? (double)A.nnz / (double)A.rows : 0.0;
@@ -251,10 +270,10 @@ hipError_t launch_row_products(const Csr &A, const int64_t *b_rp, int64_t b_rows
     if (blocks > 2048) blocks = 2048;
     if (long_count == nullptr) long_rows = nullptr;
     hipLaunchKernelGGL(k_row_products, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, A.rows, A.nnz, b_rp,
-                       b_rows, g_log2, prod, maxb, totals, flags, long_rows, long_count, heavy_from);
+                       b_rows, g_log2, prod, maxb, totals, flags, long_rows, long_count, heavy_from, bad_bit, near_pairs);
     if (long_rows != nullptr)
         hipLaunchKernelGGL(k_row_products_long, dim3(2048), dim3(TPB), 0, s, A.rp, A.col, b_rp, b_rows, prod, maxb,
-                           totals, flags, long_rows, long_count, heavy_from);
+                           totals, flags, long_rows, long_count, heavy_from, bad_bit);
     return hipGetLastError();
 }
 

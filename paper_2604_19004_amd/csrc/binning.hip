@@ -39,7 +39,7 @@ struct BinTable {
 // 1090 on 129 (256 slots) 5.1 / 4.3 and 1682 on 281 (512 slots) 8.5 / 6.4.
 __device__ __forceinline__ int sort_class(long long pr, long long ne, int bin, unsigned mask)
 {
-    const int most = bin <= NB_W64 ? 768 : bin == NB_S512 ? 1024 : 2048;
+    const int most = bin <= NB_S512 ? 1024 : 2048;
     for (int c = 1; c < SORT_CLASSES; ++c)
         if (pr <= kSortClass[c].cap && ne <= kSortClass[c].entries)
             return kSortClass[c].cap <= most && ((mask >> c) & 1u) ? c : 0;
@@ -245,11 +245,15 @@ k_place(int64_t m, const int32_t *__restrict__ in, const int64_t *__restrict__ t
     const unsigned int upto = wave_inclusive_scan_u32(total);
     if (lane_id() == WAVE - 1) s_wave[tid / WAVE] = upto;
     __syncthreads();
+    // (here a thread takes rows TPB apart: the rows of a list then stay nearly in order, and the kernels that read the list
+    // find the offsets and entries of neighbouring rows together - 4 neighbouring rows per thread cost the Laplacian's
+    // numeric kernel a sixth: 147 -> 172 us)
+    const int64_t row0 = tile * ROW_TILE + tid;
     int key[ROW_ITEMS];
     unsigned int rank[ROW_ITEMS];
 #pragma unroll
     for (int q = 0; q < ROW_ITEMS; ++q) {
-        key[q] = first + q < m ? (int)bin_of_row[first + q] : BIN_NONE;
+        key[q] = row0 + q * TPB < m ? (int)bin_of_row[row0 + q * TPB] : BIN_NONE;
         rank[q] = key[q] != BIN_NONE ? atomicAdd(&s_cnt[key[q]], 1u) : 0u;
     }
     __syncthreads();
@@ -261,7 +265,7 @@ k_place(int64_t m, const int32_t *__restrict__ in, const int64_t *__restrict__ t
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < ROW_ITEMS; ++q)
-        if (key[q] != BIN_NONE) bin_rows[s_base[key[q]] + rank[q]] = (int32_t)(first + q);
+        if (key[q] != BIN_NONE) bin_rows[s_base[key[q]] + rank[q]] = (int32_t)(row0 + q * TPB);
 }
 
 // Exclusive prefix sums of the tiles' sums, in place, by one workgroup (more than DIRECT_TILES tiles).

@@ -327,10 +327,11 @@ int zero_bins(Ctx &c, Work &w)
 // ---- analysis: validation + products per row ------------------------------------------------------
 int run_analysis(Ctx &c, Work &w, const Csr &A, const Csr &B, bool validate, ocean_stats *st)
 {
-    if (validate) HIP_TRY(launch_validate(A, B, &w.sc->flags, w.sc->near_pairs, c.s));
+    const bool same = B.rp == A.rp && B.col == A.col && B.rows == A.rows && B.cols == A.cols;
+    if (validate && !same) HIP_TRY(launch_validate(B, &w.sc->flags, w.sc->near_pairs, c.s));
     // (the row list of the bins and the last row counter are free at this point: scratch of the long-row list)
     HIP_TRY(launch_row_products(A, B.rp, B.rows, w.prod, w.maxb, w.sc->row_totals, &w.sc->flags, w.bin_rows,
-                                &w.sc->queue[3], c.s));
+                                &w.sc->queue[3], validate, validate && same ? w.sc->near_pairs : nullptr, c.s));
     OC_TRY(fetch_scalars(c, w.sc));
     unsigned long long tot[3];
     sum_row_totals(c.h, tot);
@@ -1201,7 +1202,7 @@ int ocean_row_products(const ocean_csr *A, const ocean_csr *B, int64_t *prod, in
     int rc = [&]() -> int {
         HIP_TRY(hipMemsetAsync(sc, 0, sizeof(Scalars), c.s));
         HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, long_rows,
-                                    &sc->queue[3], c.s));
+                                    &sc->queue[3], false, nullptr, c.s));
         OC_TRY(fetch_scalars(c, sc));
         unsigned long long tot[3];
         sum_row_totals(c.h, tot);
@@ -1255,7 +1256,8 @@ int ocean_row_products_noalloc(const ocean_csr *A, const ocean_csr *B, int64_t *
     // the scalars keep the last call's sums: clear them (a fill kernel, so that the call can be captured
     // into a graph); the per-row arrays are written before they are read
     HIP_TRY(launch_fill_u64(reinterpret_cast<unsigned long long *>(sc), (int64_t)(NOALLOC_SCALARS / 8), 0ull, s));
-    HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, long_rows, &sc->queue[3], s));
+    HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, long_rows, &sc->queue[3], false,
+                                nullptr, s));
     HIP_TRY(launch_publish_totals(sc->row_totals, &sc->flags, totals, s));
     return OCEAN_OK;
 }

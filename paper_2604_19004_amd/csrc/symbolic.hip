@@ -164,12 +164,14 @@ k_symbolic_wg(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_co
 constexpr int BM_THREADS = 1024;
 constexpr int BM_U = 16;                 // column ids per lane and batch (R-MAT: 16.2 ms against 16.9 with 8, 20.9 with 4)
 constexpr int BM_WIN = 1 << 20;          // columns per window
-constexpr int BM_WORDS = BM_WIN / 32;    // 32768 words = 128 KB
+constexpr int BM_MAX_WORDS = BM_WIN / 32;    // 32768 words = 128 KB
 
-// ONE_WINDOW: B has at most BM_WIN columns, so every column id falls into the one window.
+// BM_WORDS: words of the bitmap, 32 columns each: 32768, or fewer where B has fewer columns - a smaller bitmap is swept
+// (counted and cleared) faster after every row, and leaves room for a second workgroup on the compute unit.
+// ONE_WINDOW: B has at most 32 * BM_WORDS columns, so every column id falls into the one window.
 // QUERY: a column's bit is read first and set only when it is clear (Section 4.1).
-template <bool ONE_WINDOW, bool QUERY>
-__global__ void __launch_bounds__(BM_THREADS)
+template <int BM_WORDS, bool ONE_WINDOW, bool QUERY>
+__global__ void __launch_bounds__(BM_THREADS, BM_WORDS < BM_MAX_WORDS ? 8 : 4)
 k_symbolic_bitmap(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
                   const int64_t *__restrict__ b_rp, const int32_t *__restrict__ b_col,
                   const int32_t *__restrict__ rows, int64_t count, int64_t n_cols,
@@ -224,8 +226,12 @@ k_symbolic_bitmap(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ 
             // Only the number of set bits matters, so neighbouring columns (the sorted entries of one row of
             // B in neighbouring lanes) go to neighbouring words, i.e. different LDS banks, not to one word.
             if ((ALL || cj[u] >= 0) && (ONE_WINDOW || d < (uint32_t)BM_WIN)) {
-                const uint32_t bit = 1u << (d / (uint32_t)BM_WORDS);
-                uint32_t *word = &s_bm[d & (uint32_t)(BM_WORDS - 1)];
+                // Columns BM_WORDS apart share neither word nor bank (each bit's columns are turned by another amount):
+                // the much used columns of a power-law matrix are powers of two apart, and lanes that meet at one word
+                // take turns.
+                const uint32_t h = d / (uint32_t)BM_WORDS;
+                const uint32_t bit = 1u << h;
+                uint32_t *word = &s_bm[(d + h * 1021u) & (uint32_t)(BM_WORDS - 1)];
                 if (!QUERY || !(*word & bit)) atomicOr(word, bit);
             }
         }
@@ -315,14 +321,22 @@ hipError_t launch_symbolic_bin(const Csr &A, const Csr &B, const SymLaunch &l, i
     case SB_S16K: OCEAN_SYM_WG(14, 1024); break;
     case SB_S32K: OCEAN_SYM_WG(15, 1024); break;
     case SB_BITMAP: {
-#define OCEAN_SYM_BM(ONE, QUERY)                                                                                  \
-    hipLaunchKernelGGL((k_symbolic_bitmap<ONE, QUERY>), dim3((unsigned)n_wg), dim3(BM_THREADS), 0, s, A.rp, A.col, B.rp,  \
-                       B.col, l.rows, l.count, B.cols, queue, nnz_out)
-        const bool one = B.cols <= BM_WIN;
-        if (one && l.query_bitmap) OCEAN_SYM_BM(true, true);
-        else if (one) OCEAN_SYM_BM(true, false);
-        else if (l.query_bitmap) OCEAN_SYM_BM(false, true);
-        else OCEAN_SYM_BM(false, false);
+#define OCEAN_SYM_BM(WORDS, ONE, QUERY)                                                                            \
+    hipLaunchKernelGGL((k_symbolic_bitmap<WORDS, ONE, QUERY>), dim3((unsigned)(n_wg < l.count ? n_wg : l.count)),           \
+                       dim3(BM_THREADS), 0, s, A.rp, A.col, B.rp, B.col, l.rows, l.count, B.cols, queue, nnz_out)
+#define OCEAN_SYM_BM_Q(WORDS, ONE)                                                                                 \
+    do {                                                                                                          \
+        if (l.query_bitmap) OCEAN_SYM_BM(WORDS, ONE, true);                                                        \
+        else OCEAN_SYM_BM(WORDS, ONE, false);                                                                      \
+    } while (0)
+        if (B.cols > BM_WIN) OCEAN_SYM_BM_Q(BM_MAX_WORDS, false);
+        else if (B.cols > 32 * 16384) OCEAN_SYM_BM_Q(BM_MAX_WORDS, true);
+        else {
+            n_wg *= 2;   // (two workgroups per compute unit)
+            if (B.cols > 32 * 4096) OCEAN_SYM_BM_Q(16384, true);
+            else OCEAN_SYM_BM_Q(4096, true);
+        }
+#undef OCEAN_SYM_BM_Q
 #undef OCEAN_SYM_BM
         break;
     }
