@@ -236,8 +236,8 @@ int ocean_row_products(const ocean_csr *A, const ocean_csr *B, int64_t *prod, in
  * ocean_row_products for callers that cannot allocate device memory: code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same kernels as ocean_row_products; the per-row scratch they
- * need (4 + 4 bytes per row of A, and the call's device scalars) lives in a
- * fixed array inside the library's code object, 8 MiB + 256 B per GPU, held
+ * need (4 bytes per row of A, and the call's device scalars) lives in a
+ * fixed array inside the library's code object, 4 MiB + 16 KiB per GPU, held
  * until the process ends.  Hence A->rows <= OCEAN_NOALLOC_MAX_ROWS; more rows
  * give OCEAN_EINVAL and nothing is launched.  The call allocates and frees
  * nothing, does not synchronise and reads nothing back: it enqueues its

@@ -1,7 +1,7 @@
 // Analysis step and HyperLogLog size prediction (paper Sections 2.4, 3.1, 3.2).
 //
 //   k_validate        input check (row offsets ascending, column ids in range)
-//   k_row_products    prod[i] = sum_{k in A_i} nnz(B_k); P and the largest row; longest B row per A row
+//   k_row_products    input check of A; prod[i] = sum_{k in A_i} nnz(B_k); P and the largest row; longest B row per A row
 //   k_hll_sketch      construct: one m-register sketch per row of B, registers live in LDS per lane group
 //   k_hll_merge       merge along each row of A (byte-wise max of 8 registers per lane) + estimate
 //   k_sample_reduce   sums over the sampled rows for the sampled compression ratio
@@ -72,14 +72,46 @@ hipError_t launch_validate(const Csr &B, int32_t *flags, unsigned long long *nea
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- long rows
+// The long rows of a power-law matrix sit side by side (their numbers share bit patterns), so the workgroup that meets
+// them in its stretch of rows is the whole kernel's time.  The kernels below therefore leave them to workgroups of their
+// own, the first n_long of the same launch: workgroup b of them looks at rows 4 b .. 4 b + 3 of every stretch of 4 n_long
+// rows (n_long is odd, so that rows a power of two apart do not meet again) and takes the long ones among them one
+// after the other with all its threads.  A second launch for them cost matrices without any 5 us.
+constexpr int LONG_ROWS = 4;        // neighbouring rows that such a workgroup looks at together
+
+static int long_row_blocks(int64_t rows)
+{
+    const int64_t want = rows / 16;
+    return (int)(want < 1023 ? want : 1023) | 1;
+}
+
+// take(row) for every row of 0 .. rows - 1 that is_long names, by the whole workgroup (uniform, barriers allowed).
+// s_list: TPB words, s_n: one.
+template <typename IsLong, typename Take>
+__device__ __forceinline__ void for_long_rows(int64_t rows, int n_long, int32_t *s_list, int *s_n, IsLong is_long, Take take)
+{
+    const int tid = threadIdx.x;
+    const int64_t stretch = (int64_t)n_long * LONG_ROWS;
+    const int64_t first = (int64_t)blockIdx.x * LONG_ROWS + tid % LONG_ROWS + (int64_t)(tid / LONG_ROWS) * stretch;
+    for (int64_t base = 0; base < rows; base += stretch * (TPB / LONG_ROWS)) {   // uniform
+        if (tid == 0) *s_n = 0;
+        __syncthreads();
+        const int64_t r = base + first;
+        if (r < rows && is_long(r)) s_list[atomicAdd(s_n, 1)] = (int32_t)r;
+        __syncthreads();
+        const int n = *s_n;
+        for (int i = 0; i < n; ++i) take((int64_t)s_list[i]);
+        __syncthreads();
+    }
+}
+
 // ------------------------------------------------------------ row products
 // One group of 2^g_log2 lanes per row, a fixed number of workgroups striding
 // over the rows: the totals cost one atomic per workgroup, not one per row tile
 // (same-address atomics from all XCDs serialise in the memory fabric).  A row
-// far longer than the average would keep its few lanes busy for a long time,
-// and on power-law inputs such rows cluster (their indices share bit patterns,
-// so whole workgroups would get nothing else): they are put on a list and a
-// second kernel gives each of them a workgroup of its own.
+// far longer than the average would keep its few lanes busy for a long time:
+// it is left to the workgroups for long rows.
 // Totals of the row-products pass.  Same-address atomics from all over the chip serialise in the L2 at about 12
 // ns each, and there is one set per workgroup: they are spread over ROW_TOTAL_SLOTS slots of 128 bytes (one
 // cache line each) by workgroup index and added up by whoever reads them (sum_row_totals on the host).
@@ -104,176 +136,139 @@ __device__ __forceinline__ void block_totals(long long tsum, long long tmax, lon
     }
 }
 
+// bad_bit: bit of flags that any fault of A sets besides its own (0: none, and A's ends are not looked at).
+// near_pairs: see k_validate.
 __global__ void __launch_bounds__(TPB)
 k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, int64_t m, int64_t a_nnz,
-               const int64_t *__restrict__ b_rp, int64_t b_rows, int g_log2, int64_t *__restrict__ prod,
-               int32_t *__restrict__ maxb, unsigned long long *totals, int32_t *flags,
-               int32_t *__restrict__ long_rows, unsigned long long *long_count, int64_t heavy_from, int bad_bit,
-               unsigned long long *near_pairs)
+               const int64_t *__restrict__ b_rp, int64_t b_rows, int g_log2, int64_t long_from, int n_long,
+               int64_t *__restrict__ prod, int32_t *__restrict__ maxb, unsigned long long *totals, int32_t *flags,
+               int64_t heavy_from, int bad_bit, unsigned long long *near_pairs)
 {
     __shared__ unsigned int s_near, s_seen;
-    const bool sampling = near_pairs != nullptr && (blockIdx.x & 15u) == 0u;   // uniform
-    unsigned int near = 0, seen = 0;
     __shared__ long long s_sum[TPB / WAVE];
     __shared__ long long s_max[TPB / WAVE];
     __shared__ long long s_heavy[TPB / WAVE];
+    __shared__ int32_t s_list[TPB];
+    __shared__ int s_n;
+    const int tid = threadIdx.x;
     const int G = 1 << g_log2;
     const int R = TPB >> g_log2;
-    const int rl = threadIdx.x >> g_log2;
-    const int sub = threadIdx.x & (G - 1);
-    const int64_t long_len = (int64_t)G * 16;
+    const int rl = tid >> g_log2;
+    const int sub = tid & (G - 1);
+    const bool for_long = (int)blockIdx.x < n_long;   // uniform
+    const int64_t block = (int64_t)blockIdx.x - n_long, blocks = (int64_t)gridDim.x - n_long;
+    const bool sampling = near_pairs != nullptr && !for_long && (block & 15) == 0;   // uniform
+    unsigned int near = 0, seen = 0;
     long long tsum = 0, tmax = 0, theavy = 0;
-    bool bad = false, bad_rp = bad_bit != 0 && blockIdx.x == 0 && threadIdx.x == 0 && (a_rp[0] != 0 || a_rp[m] != a_nnz);
-    for (int64_t base = (int64_t)blockIdx.x * R; base < m; base += (int64_t)gridDim.x * R) {
-        const int64_t row = base + rl;
-        long long p = 0, mx = 0;
-        bool mine = row < m;
-        if (mine) {
-            // offsets outside [0, nnz] or descending are reported and never used as they stand: this kernel
-            // runs before the host has seen the verdict of the input check
-            int64_t e0 = a_rp[row], e1 = a_rp[row + 1];
-            if (e0 < 0 || e1 < e0 || e1 > a_nnz) { bad_rp = true; e0 = 0; e1 = 0; }
-            if (long_rows != nullptr && e1 - e0 > long_len) {   // uniform for the group
-                if (sub == 0) long_rows[atomicAdd(long_count, 1ull)] = (int32_t)row;
-                mine = false;
+    bool bad = false, bad_rp = bad_bit != 0 && blockIdx.x == 0 && tid == 0 && (a_rp[0] != 0 || a_rp[m] != a_nnz);
+    // entries first, first + step, ... below e1: four independent chains (entry -> row offsets of B) in flight per lane;
+    // reads are unconditional (index clamped) so that they are issued together
+    auto walk = [&](int64_t first, int64_t e1, int step, long long &p, long long &mx) {
+        for (int64_t e = first; e < e1; e += 4 * (int64_t)step) {
+            int32_t k[4];
+            bool ok[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int64_t idx = e + (int64_t)i * step;
+                ok[i] = idx < e1;
+                k[i] = a_col[ok[i] ? idx : e];
+                if (sampling && ok[i] && idx + 1 < a_nnz) {
+                    near += (uint32_t)(a_col[idx + 1] - k[i] - 1) < 4u;
+                    ++seen;
+                }
+                if ((uint32_t)k[i] >= (uint64_t)b_rows) { bad = true; k[i] = 0; ok[i] = false; }
             }
-            if (mine) {
-                // four independent chains (entry -> row offsets of B) in flight per lane; reads are
-                // unconditional (index clamped) so that they are issued together
-                for (int64_t e = e0 + sub; e < e1; e += 4 * G) {
-                    int32_t k[4];
-                    bool ok[4];
+            long long len[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int64_t idx = e + (int64_t)i * G;
-                        ok[i] = idx < e1;
-                        k[i] = a_col[ok[i] ? idx : e];
-                        if (sampling && ok[i] && idx + 1 < a_nnz) {
-                            near += (uint32_t)(a_col[idx + 1] - k[i] - 1) < 4u;
-                            ++seen;
-                        }
-                        if ((uint32_t)k[i] >= (uint64_t)b_rows) { bad = true; k[i] = 0; ok[i] = false; }
-                    }
-                    long long len[4];
+            for (int i = 0; i < 4; ++i) len[i] = b_rows > 0 ? b_rp[k[i] + 1] - b_rp[k[i]] : 0;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) len[i] = b_rows > 0 ? b_rp[k[i] + 1] - b_rp[k[i]] : 0;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if (ok[i]) {
-                            p += len[i];
-                            mx = len[i] > mx ? len[i] : mx;
-                        }
-                    }
+            for (int i = 0; i < 4; ++i) {
+                if (ok[i]) {
+                    p += len[i];
+                    mx = len[i] > mx ? len[i] : mx;
                 }
             }
         }
-        p = group_reduce_sum(p, G);
-        mx = group_reduce_max(mx, G);
-        if (mine && sub == 0) {
-            prod[row] = p;
-            maxb[row] = (int32_t)(mx > 0x7fffffffLL ? 0x7fffffffLL : mx);
-            tsum += p;
-            tmax = p > tmax ? p : tmax;
-            theavy += p > heavy_from ? p : 0;
+    };
+    auto store = [&](int64_t row, long long p, long long mx) {
+        prod[row] = p;
+        maxb[row] = (int32_t)(mx > 0x7fffffffLL ? 0x7fffffffLL : mx);
+        tsum += p;
+        tmax = p > tmax ? p : tmax;
+        theavy += p > heavy_from ? p : 0;
+    };
+    if (for_long) {
+        for_long_rows(m, n_long, s_list, &s_n,
+                      [&](int64_t r) {
+                          const int64_t e0 = a_rp[r], e1 = a_rp[r + 1];
+                          return e0 >= 0 && e1 <= a_nnz && e1 - e0 >= long_from;   // (others are reported below)
+                      },
+                      [&](int64_t row) {
+                          long long p = 0, mx = 0;
+                          walk(a_rp[row] + tid, a_rp[row + 1], TPB, p, mx);
+                          const long long wsum = group_reduce_sum(p, WAVE);
+                          const long long wmax = group_reduce_max(mx, WAVE);
+                          if (lane_id() == 0) { s_sum[tid / WAVE] = wsum; s_max[tid / WAVE] = wmax; }
+                          __syncthreads();
+                          if (tid == 0) {
+                              p = mx = 0;
+                              for (int j = 0; j < TPB / WAVE; ++j) { p += s_sum[j]; mx = s_max[j] > mx ? s_max[j] : mx; }
+                              store(row, p, mx);
+                          }
+                          __syncthreads();
+                      });
+    } else {
+        for (int64_t base = block * R; base < m; base += blocks * R) {
+            const int64_t row = base + rl;
+            long long p = 0, mx = 0;
+            bool mine = row < m;
+            if (mine) {
+                // offsets outside [0, nnz] or descending are reported and never used as they stand: this kernel
+                // runs before the host has seen the verdict of the input check
+                int64_t e0 = a_rp[row], e1 = a_rp[row + 1];
+                if (e0 < 0 || e1 < e0 || e1 > a_nnz) { bad_rp = true; e0 = 0; e1 = 0; }
+                mine = n_long == 0 || e1 - e0 < long_from;   // uniform for the group
+                if (mine) walk(e0 + sub, e1, G, p, mx);
+            }
+            p = group_reduce_sum(p, G);
+            mx = group_reduce_max(mx, G);
+            if (mine && sub == 0) store(row, p, mx);
         }
     }
     block_totals(tsum, tmax, theavy, s_sum, s_max, s_heavy, totals);
     if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(flags, 4 | bad_bit);
     if (__ballot(bad_rp) != 0 && lane_id() == 0) atomicOr(flags, 1);
     if (sampling) {
-        if (threadIdx.x == 0) { s_near = 0u; s_seen = 0u; }
+        if (tid == 0) { s_near = 0u; s_seen = 0u; }
         __syncthreads();
         const unsigned int wave_near = wave_sum_u32(near), wave_seen = wave_sum_u32(seen);
         if (lane_id() == 0) { atomicAdd(&s_near, wave_near); atomicAdd(&s_seen, wave_seen); }
         __syncthreads();
-        if (threadIdx.x == 0 && s_seen) {
+        if (tid == 0 && s_seen) {
             atomicAdd(&near_pairs[0], (unsigned long long)s_seen);
             atomicAdd(&near_pairs[1], (unsigned long long)s_near);
         }
     }
 }
 
-// The listed long rows: one workgroup per row at a time.
-__global__ void __launch_bounds__(TPB)
-k_row_products_long(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
-                    const int64_t *__restrict__ b_rp, int64_t b_rows, int64_t *__restrict__ prod,
-                    int32_t *__restrict__ maxb, unsigned long long *totals, int32_t *flags,
-                    const int32_t *__restrict__ long_rows, const unsigned long long *long_count, int64_t heavy_from, int bad_bit)
-{
-    __shared__ long long s_sum[TPB / WAVE];
-    __shared__ long long s_max[TPB / WAVE];
-    __shared__ long long s_heavy[TPB / WAVE];
-    const int64_t n = (int64_t)*long_count;
-    const int w = threadIdx.x / WAVE;
-    long long tsum = 0, tmax = 0, theavy = 0;
-    bool bad = false;
-    for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
-        const int64_t row = long_rows[i];
-        const int64_t e0 = a_rp[row], e1 = a_rp[row + 1];   // (only rows with valid offsets are listed)
-        long long p = 0, mx = 0;
-        for (int64_t e = e0 + threadIdx.x; e < e1; e += 4 * TPB) {
-            int32_t k[4];
-            bool ok[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t idx = e + (int64_t)j * TPB;
-                ok[j] = idx < e1;
-                k[j] = a_col[ok[j] ? idx : e];
-                if ((uint32_t)k[j] >= (uint64_t)b_rows) { bad = true; k[j] = 0; ok[j] = false; }
-            }
-            long long len[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) len[j] = b_rows > 0 ? b_rp[k[j] + 1] - b_rp[k[j]] : 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (ok[j]) {
-                    p += len[j];
-                    mx = len[j] > mx ? len[j] : mx;
-                }
-            }
-        }
-        const long long wsum = group_reduce_sum(p, WAVE);
-        const long long wmax = group_reduce_max(mx, WAVE);
-        if (lane_id() == 0) { s_sum[w] = wsum; s_max[w] = wmax; }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            long long rp = 0, rm = 0;
-            for (int j = 0; j < TPB / WAVE; ++j) { rp += s_sum[j]; rm = s_max[j] > rm ? s_max[j] : rm; }
-            prod[row] = rp;
-            maxb[row] = (int32_t)(rm > 0x7fffffffLL ? 0x7fffffffLL : rm);
-            tsum += rp;
-            tmax = rp > tmax ? rp : tmax;
-            theavy += rp > heavy_from ? rp : 0;
-        }
-        __syncthreads();
-    }
-    block_totals(tsum, tmax, theavy, s_sum, s_max, s_heavy, totals);
-    if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(flags, 4 | bad_bit);
-}
-
 // validate: A's offsets must begin at 0 and end at its number of entries as well, and any fault of A sets bit 1 of flags
 // (offsets that descend or leave [0, nnz] always do, column ids outside [0, b_rows) always set bit 4).  near_pairs (may
 // be null): see k_validate.
-// long_rows: scratch for A.rows row ids, long_count: a zeroed device counter; both may be null
-// (then every row is handled by its lane group).
 hipError_t launch_row_products(const Csr &A, const int64_t *b_rp, int64_t b_rows, int64_t *prod, int32_t *maxb,
-                               unsigned long long *totals, int32_t *flags, int32_t *long_rows,
-                               unsigned long long *long_count, bool validate, unsigned long long *near_pairs, hipStream_t s)
+                               unsigned long long *totals, int32_t *flags, bool validate, unsigned long long *near_pairs,
+                               hipStream_t s)
 {
-    const int bad_bit = validate ? 1 : 0;
     const int64_t heavy_from = kNumericSlots[NB_S4K];   // beyond the largest LDS hash table that sorted inputs use
     if (A.rows == 0) return hipSuccess;
-    const double avg = A.rows ? (double)A.nnz / (double)A.rows : 0.0;
+    const double avg = (double)A.nnz / (double)A.rows;
     const int g_log2 = ilog2_ceil(avg / 4.0, 1, 6);   // (a lane keeps four entries in flight)
+    const int64_t long_from = (int64_t)32 << g_log2;    // eight turns of the group
     const int R = TPB >> g_log2;
     int64_t blocks = (A.rows + R - 1) / R;
     if (blocks > 2048) blocks = 2048;
-    if (long_count == nullptr) long_rows = nullptr;
-    hipLaunchKernelGGL(k_row_products, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, A.rows, A.nnz, b_rp,
-                       b_rows, g_log2, prod, maxb, totals, flags, long_rows, long_count, heavy_from, bad_bit, near_pairs);
-    if (long_rows != nullptr)
-        hipLaunchKernelGGL(k_row_products_long, dim3(2048), dim3(TPB), 0, s, A.rp, A.col, b_rp, b_rows, prod, maxb,
-                           totals, flags, long_rows, long_count, heavy_from, bad_bit);
+    const int n_long = A.nnz >= long_from ? long_row_blocks(A.rows) : 0;
+    hipLaunchKernelGGL(k_row_products, dim3((unsigned)(blocks + n_long)), dim3(TPB), 0, s, A.rp, A.col, A.rows, A.nnz, b_rp,
+                       b_rows, g_log2, long_from, n_long, prod, maxb, totals, flags, heavy_from, validate ? 1 : 0, near_pairs);
     return hipGetLastError();
 }
 
@@ -308,13 +303,10 @@ hipError_t launch_publish_totals(const unsigned long long *totals, const int32_t
 // row, walked by one group of 16 lanes, was most of the kernel's time (R-MAT: 0.77 ms).  "Long" is relative: a row
 // of long_from entries or more, which the launcher sets to 1024 or eight times the average row, whichever is more
 // (where every row is long, sixteen groups side by side are 6 - 12 % faster than the workgroup on one row at a time).
-// Where the rows are known or suspected to be skewed, the long ones (from LONG_SKEWED entries on) are skipped here and
-// left to k_hll_sketch_long: the long rows of a power-law matrix sit side by side, and the workgroup that met
-// rows 0 .. 15 was the whole kernel's time (R-MAT scale 18: 2 % of the entries, 72 us; now 23 + 22 us).
+// Where the rows are known or suspected to be skewed, the rows of LONG_SKEWED entries or more go to the workgroups for
+// long rows (see for_long_rows): R-MAT scale 18, 64 registers: 72 us with the long rows by the workgroup that met them.
 constexpr int SK_LONG = 1024;
 constexpr int LONG_SKEWED = 256;
-constexpr int LONG_THREADS = 1024;
-constexpr int LONG_ROWS = 4;        // neighbouring rows a workgroup of the long-row kernels looks at together
 
 template <int M>
 __device__ __forceinline__ void hll_add(uint32_t *regs, int32_t c)
@@ -329,11 +321,11 @@ __device__ __forceinline__ void hll_add(uint32_t *regs, int32_t c)
 template <int M>
 __global__ void __launch_bounds__(TPB)
 k_hll_sketch(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, int64_t rows, int g_log2,
-             int64_t long_from, bool skip_long, uint8_t *__restrict__ out)
+             int64_t long_from, int n_long, uint8_t *__restrict__ out)
 {
     extern __shared__ uint32_t s_regs[];  // [TPB >> g_log2][M]
     __shared__ uint32_t s_big[M];
-    __shared__ long long s_long[TPB / 8];   // (at most TPB / 8 rows per turn: groups have 8 lanes or more)
+    __shared__ int32_t s_long[TPB];   // (at most TPB / 8 rows per turn of the groups, which have 8 lanes or more)
     __shared__ int s_nlong;
     const int G = 1 << g_log2;
     const int sub = threadIdx.x & (G - 1);
@@ -345,7 +337,31 @@ k_hll_sketch(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, in
         for (int j = first; j < M / 4; j += step)
             dst[j] = regs[4 * j] | (regs[4 * j + 1] << 8) | (regs[4 * j + 2] << 16) | (regs[4 * j + 3] << 24);
     };
-    for (int64_t base = (int64_t)blockIdx.x * R; base < rows; base += (int64_t)gridDim.x * R) {   // uniform
+    // a long row, by the whole workgroup
+    auto take = [&](int64_t lrow) {
+        for (int j = threadIdx.x; j < M; j += TPB) s_big[j] = 0;
+        __syncthreads();
+        const int64_t p1 = rp[lrow + 1];
+        for (int64_t p = rp[lrow] + threadIdx.x; p < p1; p += 8 * (int64_t)TPB) {
+            int32_t c[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int64_t q = p + (int64_t)k * TPB;
+                c[k] = col[q < p1 ? q : p1 - 1];
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (p + (int64_t)k * TPB < p1) hll_add<M>(s_big, c[k]);
+        }
+        __syncthreads();
+        store(s_big, lrow, (int)threadIdx.x, TPB);
+        __syncthreads();
+    };
+    if ((int)blockIdx.x < n_long) {   // uniform
+        for_long_rows(rows, n_long, s_long, &s_nlong, [&](int64_t r) { return rp[r + 1] - rp[r] >= long_from; }, take);
+        return;
+    }
+    for (int64_t base = ((int64_t)blockIdx.x - n_long) * R; base < rows; base += ((int64_t)gridDim.x - n_long) * R) {   // uniform
         const int64_t row = base + rl;
         if (threadIdx.x == 0) s_nlong = 0;
         for (int j = sub; j < M; j += G) my[j] = 0;
@@ -354,7 +370,7 @@ k_hll_sketch(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, in
         if (row < rows) {
             const int64_t p0 = rp[row], p1 = rp[row + 1];
             mine = p1 - p0 < long_from;
-            if (!mine && !skip_long && sub == 0) s_long[atomicAdd(&s_nlong, 1)] = row;
+            if (!mine && n_long == 0 && sub == 0) s_long[atomicAdd(&s_nlong, 1)] = (int32_t)row;
             // four column ids per lane and turn (unconditional reads, index clamped): a long row is bound by
             // the latency of one load after the other otherwise
             for (int64_t p = p0 + sub; mine && p < p1; p += 4 * (int64_t)G) {
@@ -373,83 +389,9 @@ k_hll_sketch(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, in
         if (mine) store(my, row, sub, G);
         __syncthreads();
         const int nlong = s_nlong;
-        for (int i = 0; i < nlong; ++i) {   // uniform
-            const int64_t lrow = s_long[i];
-            for (int j = threadIdx.x; j < M; j += TPB) s_big[j] = 0;
-            __syncthreads();
-            const int64_t p1 = rp[lrow + 1];
-            for (int64_t p = rp[lrow] + threadIdx.x; p < p1; p += 4 * (int64_t)TPB) {
-                int32_t c[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int64_t q = p + (int64_t)k * TPB;
-                    c[k] = col[q < p1 ? q : p1 - 1];
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (p + (int64_t)k * TPB < p1) hll_add<M>(s_big, c[k]);
-            }
-            __syncthreads();
-            store(s_big, lrow, (int)threadIdx.x, TPB);
-            __syncthreads();
-        }
+        for (int i = 0; i < nlong; ++i) take((int64_t)s_long[i]);   // uniform
         __syncthreads();   // (everyone has read s_nlong before the next turn clears it)
     }
-}
-
-// The rows of long_from entries or more, a workgroup of 1024 threads on one after the other.  Workgroup b looks at
-// rows 4 b .. 4 b + 3 of every stretch of 4 gridDim rows: neighbouring long rows go to different workgroups (an odd
-// number of them, so that rows a power of two apart do not meet again).
-template <int M>
-__global__ void __launch_bounds__(LONG_THREADS)
-k_hll_sketch_long(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, int64_t rows, int64_t long_from,
-                  uint8_t *__restrict__ out)
-{
-    __shared__ uint32_t s_regs[M];
-    __shared__ int32_t s_list[LONG_THREADS];
-    __shared__ int s_n;
-    const int tid = threadIdx.x;
-    const int64_t stretch = (int64_t)gridDim.x * LONG_ROWS;
-    const int64_t first = (int64_t)blockIdx.x * LONG_ROWS + tid % LONG_ROWS + (int64_t)(tid / LONG_ROWS) * stretch;
-    const int64_t turn = stretch * (LONG_THREADS / LONG_ROWS);
-    for (int64_t base = 0; base < rows; base += turn) {   // uniform
-        if (tid == 0) s_n = 0;
-        __syncthreads();
-        const int64_t r = base + first;
-        if (r < rows && rp[r + 1] - rp[r] >= long_from) s_list[atomicAdd(&s_n, 1)] = (int32_t)r;
-        __syncthreads();
-        const int n = s_n;
-        for (int i = 0; i < n; ++i) {   // uniform
-            const int64_t row = s_list[i];
-            const int64_t p0 = rp[row], p1 = rp[row + 1];
-            if (tid < M) s_regs[tid] = 0;
-            __syncthreads();
-            for (int64_t p = p0 + tid; p < p1; p += 4 * (int64_t)LONG_THREADS) {
-                int32_t c[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int64_t q = p + (int64_t)k * LONG_THREADS;
-                    c[k] = col[q < p1 ? q : p1 - 1];
-                }
-#pragma unroll
-                for (int k = 0; k < 4; ++k)
-                    if (p + (int64_t)k * LONG_THREADS < p1) hll_add<M>(s_regs, c[k]);
-            }
-            __syncthreads();
-            if (tid < M / 4)
-                reinterpret_cast<uint32_t *>(out + row * M)[tid] =
-                    s_regs[4 * tid] | (s_regs[4 * tid + 1] << 8) | (s_regs[4 * tid + 2] << 16) | (s_regs[4 * tid + 3] << 24);
-            __syncthreads();
-        }
-        __syncthreads();
-    }
-}
-
-// Workgroups of the long-row kernels: an odd number, fewer where there are few rows.
-static int long_row_blocks(int64_t rows)
-{
-    const int64_t want = (rows + LONG_ROWS - 1) / LONG_ROWS;
-    return (int)(want < 1021 ? want | 1 : 1021);
 }
 
 // lanes_div: 1, or 4 when the rows are known to be of similar lengths - a lane keeps four entries in flight, so a
@@ -464,22 +406,15 @@ hipError_t launch_hll_sketch(const Csr &B, int m, uint8_t *sketches, int lanes_d
     int64_t blocks = (B.rows + R - 1) / R;
     if (blocks > 256 * 64) blocks = 256 * 64;
     const size_t lds = (size_t)R * m * sizeof(uint32_t);
-    const bool skip_long = lanes_div == 1;
-    const int64_t least = skip_long ? LONG_SKEWED : SK_LONG;
+    const int64_t least = lanes_div == 1 ? LONG_SKEWED : SK_LONG;
     const int64_t long_from = 8.0 * avg > (double)least ? (int64_t)(8.0 * avg) : least;
+    const int n_long = lanes_div == 1 && B.nnz >= long_from ? long_row_blocks(B.rows) : 0;
+    blocks += n_long;
     switch (m) {
-    case 32: hipLaunchKernelGGL(k_hll_sketch<32>, dim3((unsigned)blocks), dim3(TPB), lds, s, B.rp, B.col, B.rows, g_log2, long_from, skip_long, sketches); break;
-    case 64: hipLaunchKernelGGL(k_hll_sketch<64>, dim3((unsigned)blocks), dim3(TPB), lds, s, B.rp, B.col, B.rows, g_log2, long_from, skip_long, sketches); break;
-    case 128: hipLaunchKernelGGL(k_hll_sketch<128>, dim3((unsigned)blocks), dim3(TPB), lds, s, B.rp, B.col, B.rows, g_log2, long_from, skip_long, sketches); break;
+    case 32: hipLaunchKernelGGL(k_hll_sketch<32>, dim3((unsigned)blocks), dim3(TPB), lds, s, B.rp, B.col, B.rows, g_log2, long_from, n_long, sketches); break;
+    case 64: hipLaunchKernelGGL(k_hll_sketch<64>, dim3((unsigned)blocks), dim3(TPB), lds, s, B.rp, B.col, B.rows, g_log2, long_from, n_long, sketches); break;
+    case 128: hipLaunchKernelGGL(k_hll_sketch<128>, dim3((unsigned)blocks), dim3(TPB), lds, s, B.rp, B.col, B.rows, g_log2, long_from, n_long, sketches); break;
     default: return hipErrorInvalidValue;
-    }
-    if (skip_long && B.nnz >= long_from) {   // (a matrix of fewer entries has no such row)
-        const int n = long_row_blocks(B.rows);
-        switch (m) {
-        case 32: hipLaunchKernelGGL(k_hll_sketch_long<32>, dim3(n), dim3(LONG_THREADS), 0, s, B.rp, B.col, B.rows, long_from, sketches); break;
-        case 64: hipLaunchKernelGGL(k_hll_sketch_long<64>, dim3(n), dim3(LONG_THREADS), 0, s, B.rp, B.col, B.rows, long_from, sketches); break;
-        default: hipLaunchKernelGGL(k_hll_sketch_long<128>, dim3(n), dim3(LONG_THREADS), 0, s, B.rp, B.col, B.rows, long_from, sketches); break;
-        }
     }
     return hipGetLastError();
 }
@@ -508,32 +443,34 @@ __device__ __forceinline__ double hll_alpha(int m)
 // long rows of its groups one after the other: on a power-law matrix a sampled row of tens of thousands of
 // entries, merged by one group, was most of the sampled merge's time.  "Long" is long_from entries or more: 2048
 // or eight times the average row of A, whichever is more (see k_hll_sketch).
+// n_long: workgroups for long rows at the front of the grid; 0: the workgroup that meets a long row takes it; -1: long rows
+// are left out.
 constexpr int MG_LONG = 2048;
 
-// Entries first, first + step, ... of a row, for one slice (8 registers) of the sketch: four per lane and turn
+// Entries first, first + step, ... of a row, for one slice (8 registers) of the sketch: U per lane and turn
 // (unconditional reads, index clamped; merging a sketch twice is harmless), so that the dependent loads entry ->
-// sketch of four entries overlap.
-template <int L>
+// sketch of U entries overlap.
+template <int L, int U>
 __device__ __forceinline__ void hll_walk(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
                                          const uint64_t *__restrict__ sk, const int64_t *__restrict__ b_rp, int64_t row,
                                          int slice, int first, int step, uint64_t &acc, long long &blen_max)
 {
     const int64_t e1 = a_rp[row + 1];
-    for (int64_t e = a_rp[row] + first; e < e1; e += 4 * (int64_t)step) {
-        int64_t k[4];
-        uint64_t word[4];
+    for (int64_t e = a_rp[row] + first; e < e1; e += U * (int64_t)step) {
+        int32_t k[U];
+        uint64_t word[U];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < U; ++i) {
             const int64_t q = e + (int64_t)i * step;
             k[i] = a_col[q < e1 ? q : e1 - 1];
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) word[i] = sk[k[i] * L + slice];
+        for (int i = 0; i < U; ++i) word[i] = sk[(int64_t)k[i] * L + slice];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc = bytemax8(acc, word[i]);
+        for (int i = 0; i < U; ++i) acc = bytemax8(acc, word[i]);
         if (b_rp != nullptr && slice == 0) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < U; ++i) {
                 const long long len = b_rp[k[i] + 1] - b_rp[k[i]];
                 blen_max = len > blen_max ? len : blen_max;
             }
@@ -578,49 +515,28 @@ __device__ __forceinline__ void hll_finish(uint64_t acc, long long blen_max, int
     }
 }
 
+// (8: with the code for long rows beside it the compiler would take 96 registers and leave 5 waves per SIMD; 10 % slower
+// on 256 000 rows of 34 entries)
 template <int M>
-__global__ void __launch_bounds__(TPB)
+__global__ void __launch_bounds__(TPB, 8)
 k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
             const uint64_t *__restrict__ sk, const int64_t *__restrict__ rows, int64_t n_rows, int g_log2,
-            int64_t long_from, bool skip_long, const int64_t *__restrict__ prod, const int32_t *__restrict__ maxb, const int64_t *__restrict__ b_rp,
+            int64_t long_from, int n_long, const int64_t *__restrict__ prod, const int32_t *__restrict__ maxb, const int64_t *__restrict__ b_rp,
             int64_t b_cols, double *__restrict__ est, uint64_t *__restrict__ merged)
 {
     constexpr int L = M / 8;
-    __shared__ long long s_long[TPB / L];   // (slot of the row, i.e. its position among the selected rows)
+    __shared__ int32_t s_long[TPB];   // (slot of the row, i.e. its position among the selected rows)
     __shared__ int s_nlong;
     __shared__ uint64_t s_acc[TPB];
     __shared__ long long s_blen[TPB / L];
     const int G = 1 << g_log2;  // >= L
-    const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t t = gt >> g_log2;
-    const int sub = (int)(gt & (G - 1));
-    if (threadIdx.x == 0) s_nlong = 0;
-    __syncthreads();
-    const int slice = sub & (L - 1);
-    const int part = sub / L;
-    const int parts = G / L;
-    uint64_t acc = 0;
-    long long blen_max = 0;
-    int64_t row = -1;
-    bool mine = false;
-    if (t < n_rows) {
-        row = rows ? rows[t] : t;
-        mine = a_rp[row + 1] - a_rp[row] < long_from;
-        if (mine) hll_walk<L>(a_rp, a_col, sk, b_rp, row, slice, part, parts, acc, blen_max);
-        else if (!skip_long && sub == 0) s_long[atomicAdd(&s_nlong, 1)] = t;
-    }
-    for (int off = L; off < G; off <<= 1) acc = bytemax8(acc, __shfl_xor((unsigned long long)acc, off, WAVE));
-    if (b_rp != nullptr) blen_max = group_reduce_max(blen_max, G);
-    hll_finish<M>(acc, blen_max, t, row, slice, mine && part == 0, prod, maxb, b_cols, est, merged);
-    __syncthreads();
-    const int nlong = s_nlong;
-    for (int i = 0; i < nlong; ++i) {   // uniform
-        const int64_t t2 = s_long[i];
+    // a long row, by the whole workgroup
+    auto take = [&](int64_t t2) {
         const int64_t row2 = rows ? rows[t2] : t2;
         const int wslice = (int)threadIdx.x & (L - 1), wpart = (int)threadIdx.x / L;
         uint64_t a2 = 0;
         long long b2 = 0;
-        hll_walk<L>(a_rp, a_col, sk, b_rp, row2, wslice, wpart, TPB / L, a2, b2);
+        hll_walk<L, 4>(a_rp, a_col, sk, b_rp, row2, wslice, wpart, TPB / L, a2, b2);
         s_acc[threadIdx.x] = a2;
         if (wslice == 0) s_blen[wpart] = b2;
         __syncthreads();
@@ -636,11 +552,41 @@ k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
         if (threadIdx.x < WAVE)   // (whole first wave: lane swaps)
             hll_finish<M>(f, fb, t2, row2, (int)threadIdx.x & (L - 1), threadIdx.x < L, prod, maxb, b_cols, est, merged);
         __syncthreads();
+    };
+    if ((int)blockIdx.x < n_long) {   // uniform (all rows, no row list)
+        for_long_rows(n_rows, n_long, s_long, &s_nlong, [&](int64_t r) { return a_rp[r + 1] - a_rp[r] >= long_from; }, take);
+        return;
     }
+    const int64_t gt = ((int64_t)blockIdx.x - (n_long > 0 ? n_long : 0)) * blockDim.x + threadIdx.x;
+    const int64_t t = gt >> g_log2;
+    const int sub = (int)(gt & (G - 1));
+    if (threadIdx.x == 0) s_nlong = 0;
+    __syncthreads();
+    const int slice = sub & (L - 1);
+    const int part = sub / L;
+    const int parts = G / L;
+    uint64_t acc = 0;
+    long long blen_max = 0;
+    int64_t row = -1;
+    bool mine = false;
+    if (t < n_rows) {
+        row = rows ? rows[t] : t;
+        mine = a_rp[row + 1] - a_rp[row] < long_from;
+        if (mine) hll_walk<L, 4>(a_rp, a_col, sk, b_rp, row, slice, part, parts, acc, blen_max);
+        else if (n_long == 0 && sub == 0) s_long[atomicAdd(&s_nlong, 1)] = (int32_t)t;
+    }
+    for (int off = L; off < G; off <<= 1) acc = bytemax8(acc, __shfl_xor((unsigned long long)acc, off, WAVE));
+    if (b_rp != nullptr) blen_max = group_reduce_max(blen_max, G);
+    hll_finish<M>(acc, blen_max, t, row, slice, mine && part == 0, prod, maxb, b_cols, est, merged);
+    __syncthreads();
+    const int nlong = s_nlong;
+    for (int i = 0; i < nlong; ++i) take((int64_t)s_long[i]);   // uniform
 }
 
-// The rows of long_from entries or more of a merge over all rows, a workgroup of 1024 threads on one after the other,
-// spread over the workgroups as in k_hll_sketch_long.
+// The long rows of a merge over all rows of a large matrix, a workgroup of 1024 threads on one after the other: a row of
+// 28 000 entries, four in flight per lane, takes a workgroup of 256 threads 290 us (R-MAT scale 18: whole estimate 641 us,
+// 480 with this kernel), and a launch is 5.  Rows are spread over the workgroups as in for_long_rows.
+constexpr int LONG_THREADS = 1024;
 template <int M>
 __global__ void __launch_bounds__(LONG_THREADS)
 k_hll_merge_long(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, const uint64_t *__restrict__ sk,
@@ -669,7 +615,7 @@ k_hll_merge_long(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a
             const int64_t row = s_list[i];
             uint64_t acc = 0;
             long long blen = 0;
-            hll_walk<L>(a_rp, a_col, sk, b_rp, row, slice, tid / L, LONG_THREADS / L, acc, blen);
+            hll_walk<L, 4>(a_rp, a_col, sk, b_rp, row, slice, tid / L, LONG_THREADS / L, acc, blen);
             for (int off = L; off < WAVE; off <<= 1) acc = bytemax8(acc, __shfl_xor((unsigned long long)acc, off, WAVE));
             blen = group_reduce_max(blen, WAVE);
             if (lane_id() < L) s_acc[wave][lane_id()] = acc;
@@ -697,27 +643,29 @@ hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const 
     if (n_rows == 0) return hipSuccess;
     const int L = m / 8;
     const double avg = A.rows ? (double)A.nnz / (double)A.rows : 1.0;
-    // All rows of a matrix that is or may be skewed: the long rows go to a kernel of their own (see k_hll_sketch), so the
-    // others can have an eighth of the lanes (four entries in flight per lane, and twice the rows).  R-MAT scale 18, 64
-    // registers: 355 us with a wave per row and the long rows by the workgroup that met them, now 132 + 126 us, with a
-    // quarter of the lanes and long rows from 512 entries on 200 + 75; the gather of 4 M sketches of 64 bytes at the 1.2
-    // TB/s this GPU reaches for such pieces is 210 us.
-    const bool skip_long = lanes_div == 1 && rows == nullptr;
-    int g_log2 = ilog2_ceil(avg * L / (double)(skip_long ? 8 : lanes_div), 0, 6);   // (lanes_div: see launch_hll_sketch)
+    // All rows of a matrix that is or may be skewed: the long rows go to workgroups of their own (see k_hll_sketch), so
+    // the others can have an eighth of the lanes (four entries in flight per lane, and twice the rows).  R-MAT scale 18,
+    // 64 registers: 355 us with a wave per row and the long rows by the workgroup that met them; the gather of 4 M
+    // sketches of 64 bytes at the 1.2 TB/s this GPU reaches for such pieces is 210 us.
+    const bool spread = lanes_div == 1 && rows == nullptr;
+    int g_log2 = ilog2_ceil(avg * L / (double)(spread ? 8 : lanes_div), 0, 6);   // (lanes_div: see launch_hll_sketch)
     while ((1 << g_log2) < L) ++g_log2;
     const int64_t threads = n_rows << g_log2;
-    const int64_t blocks = (threads + TPB - 1) / TPB;
+    int64_t blocks = (threads + TPB - 1) / TPB;
     const uint64_t *sk = reinterpret_cast<const uint64_t *>(sketches);
     uint64_t *mg = reinterpret_cast<uint64_t *>(merged);
-    const int64_t least = skip_long ? LONG_SKEWED : MG_LONG;
+    const int64_t least = spread ? LONG_SKEWED : MG_LONG;
     const int64_t long_from = 8.0 * avg > (double)least ? (int64_t)(8.0 * avg) : least;
+    const bool own_launch = spread && A.nnz >= (1 << 20);
+    const int n_long = own_launch ? -1 : spread && A.nnz >= long_from ? long_row_blocks(n_rows) : 0;
+    blocks += n_long > 0 ? n_long : 0;
     switch (m) {
-    case 32: hipLaunchKernelGGL(k_hll_merge<32>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, skip_long, prod, maxb, b_rp, b_cols, est, mg); break;
-    case 64: hipLaunchKernelGGL(k_hll_merge<64>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, skip_long, prod, maxb, b_rp, b_cols, est, mg); break;
-    case 128: hipLaunchKernelGGL(k_hll_merge<128>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, skip_long, prod, maxb, b_rp, b_cols, est, mg); break;
+    case 32: hipLaunchKernelGGL(k_hll_merge<32>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, n_long, prod, maxb, b_rp, b_cols, est, mg); break;
+    case 64: hipLaunchKernelGGL(k_hll_merge<64>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, n_long, prod, maxb, b_rp, b_cols, est, mg); break;
+    case 128: hipLaunchKernelGGL(k_hll_merge<128>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, n_long, prod, maxb, b_rp, b_cols, est, mg); break;
     default: return hipErrorInvalidValue;
     }
-    if (skip_long && A.nnz >= long_from) {   // (a matrix of fewer entries has no such row)
+    if (own_launch) {
         const int n = long_row_blocks(n_rows);
         switch (m) {
         case 32: hipLaunchKernelGGL(k_hll_merge_long<32>, dim3(n), dim3(LONG_THREADS), 0, s, A.rp, A.col, sk, n_rows, long_from, prod, maxb, b_rp, b_cols, est, mg); break;

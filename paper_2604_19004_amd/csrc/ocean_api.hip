@@ -315,8 +315,8 @@ int work_alloc(Ctx &c, Work &w, int64_t m, int64_t n_sample)
 
 int zero_bins(Ctx &c, Work &w)
 {
-    if (w.bins_clean) {   // (the analysis step in between touches none of them but the last row counter, which only
-        w.bins_clean = false;   // the retry uses, after a clearing of its own)
+    if (w.bins_clean) {   // (the analysis step in between touches none of them)
+        w.bins_clean = false;
         return OCEAN_OK;
     }
     HIP_TRY(hipMemsetAsync(w.sc->bin_count, 0,
@@ -329,9 +329,8 @@ int run_analysis(Ctx &c, Work &w, const Csr &A, const Csr &B, bool validate, oce
 {
     const bool same = B.rp == A.rp && B.col == A.col && B.rows == A.rows && B.cols == A.cols;
     if (validate && !same) HIP_TRY(launch_validate(B, &w.sc->flags, w.sc->near_pairs, c.s));
-    // (the row list of the bins and the last row counter are free at this point: scratch of the long-row list)
-    HIP_TRY(launch_row_products(A, B.rp, B.rows, w.prod, w.maxb, w.sc->row_totals, &w.sc->flags, w.bin_rows,
-                                &w.sc->queue[3], validate, validate && same ? w.sc->near_pairs : nullptr, c.s));
+    HIP_TRY(launch_row_products(A, B.rp, B.rows, w.prod, w.maxb, w.sc->row_totals, &w.sc->flags, validate,
+                                validate && same ? w.sc->near_pairs : nullptr, c.s));
     OC_TRY(fetch_scalars(c, w.sc));
     unsigned long long tot[3];
     sum_row_totals(c.h, tot);
@@ -1086,10 +1085,10 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
 
 // ---- scratch of the entry point that allocates nothing ----------------------------------------------
 // Layout: the call's device scalars (one 256-byte aligned block), then the longest referenced row of B per
-// row of A, then the list of long rows.  The array lives in every GPU's copy of the code object; the name
+// row of A.  The array lives in every GPU's copy of the code object; the name
 // below is only a host-side handle, the device address comes from hipGetSymbolAddress, once per device.
 constexpr size_t NOALLOC_SCALARS = (sizeof(Scalars) + ALIGN - 1) / ALIGN * ALIGN;
-constexpr size_t NOALLOC_BYTES = NOALLOC_SCALARS + 2 * (size_t)OCEAN_NOALLOC_MAX_ROWS * sizeof(int32_t);
+constexpr size_t NOALLOC_BYTES = NOALLOC_SCALARS + (size_t)OCEAN_NOALLOC_MAX_ROWS * sizeof(int32_t);
 constexpr int NOALLOC_MAX_DEVICES = 64;
 
 }  // namespace
@@ -1192,17 +1191,13 @@ int ocean_row_products(const ocean_csr *A, const ocean_csr *B, int64_t *prod, in
     Ctx c;
     OC_TRY(ctx_init(c, nullptr, stream));
     const size_t mm = (size_t)(A->rows > 0 ? A->rows : 1);
-    // (with the list of long rows: a row of 16 000 entries walked by the few lanes of its group was 1.78 of the 1.83 ms
-    // of a power-law matrix of 2^18 rows)
-    char *buf = static_cast<char *>(c.alloc(up(sizeof(Scalars)) + up(mm * 4) + mm * 4));
+    char *buf = static_cast<char *>(c.alloc(up(sizeof(Scalars)) + mm * 4));
     if (!buf) return fail(OCEAN_EALLOC, "workspace allocation failed");
     Scalars *sc = reinterpret_cast<Scalars *>(buf);
     int32_t *maxb = reinterpret_cast<int32_t *>(buf + up(sizeof(Scalars)));
-    int32_t *long_rows = reinterpret_cast<int32_t *>(buf + up(sizeof(Scalars)) + up(mm * 4));
     int rc = [&]() -> int {
         HIP_TRY(hipMemsetAsync(sc, 0, sizeof(Scalars), c.s));
-        HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, long_rows,
-                                    &sc->queue[3], false, nullptr, c.s));
+        HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, false, nullptr, c.s));
         OC_TRY(fetch_scalars(c, sc));
         unsigned long long tot[3];
         sum_row_totals(c.h, tot);
@@ -1252,12 +1247,10 @@ int ocean_row_products_noalloc(const ocean_csr *A, const ocean_csr *B, int64_t *
     hipStream_t s = static_cast<hipStream_t>(stream);
     Scalars *sc = reinterpret_cast<Scalars *>(base);
     int32_t *maxb = reinterpret_cast<int32_t *>(base + NOALLOC_SCALARS);
-    int32_t *long_rows = maxb + OCEAN_NOALLOC_MAX_ROWS;
     // the scalars keep the last call's sums: clear them (a fill kernel, so that the call can be captured
     // into a graph); the per-row arrays are written before they are read
     HIP_TRY(launch_fill_u64(reinterpret_cast<unsigned long long *>(sc), (int64_t)(NOALLOC_SCALARS / 8), 0ull, s));
-    HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, long_rows, &sc->queue[3], false,
-                                nullptr, s));
+    HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, false, nullptr, s));
     HIP_TRY(launch_publish_totals(sc->row_totals, &sc->flags, totals, s));
     return OCEAN_OK;
 }

@@ -167,7 +167,10 @@ constexpr int BM_WIN = 1 << 20;          // columns per window
 constexpr int BM_MAX_WORDS = BM_WIN / 32;    // 32768 words = 128 KB
 
 // BM_WORDS: words of the bitmap, 32 columns each: 32768, or fewer where B has fewer columns - a smaller bitmap is swept
-// (counted and cleared) faster after every row, and leaves room for a second workgroup on the compute unit.
+// (counted and cleared) faster after every row, and leaves room for a second workgroup on the compute unit (64
+// registers): symbolic stage of R-MAT scale 18 (16384 words) 2.80 -> 1.94 ms, whole call of scale 17 (4096) 1.39 -> 0.99
+// ms.  Eight workgroups of 256 threads for the rows of up to 32768 products were slower (1.33 ms): the set-up of a
+// chunk is most of such a row's time, and smaller chunks are more of them.
 // ONE_WINDOW: B has at most 32 * BM_WORDS columns, so every column id falls into the one window.
 // QUERY: a column's bit is read first and set only when it is clear (Section 4.1).
 template <int BM_WORDS, bool ONE_WINDOW, bool QUERY>
