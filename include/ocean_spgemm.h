@@ -176,7 +176,8 @@ typedef struct ocean_stats {
     int32_t fell_back;         /* 1: estimation workflow abandoned for the two-pass one (out of memory) */
     int64_t rows_per_bin[OCEAN_MAX_BINS];          /* numeric bins: the hash bins of ocean_bin_layout, then (at index
                                                       n_numeric) the rows of the dense accumulator over the row's range */
-    int64_t symbolic_rows_per_bin[OCEAN_MAX_BINS]; /* symbolic bins (two-pass workflow) */
+    int64_t symbolic_rows_per_bin[OCEAN_MAX_BINS]; /* symbolic bins (two-pass workflow), then (at index n_symbolic) the
+                                                      rows counted by a bitmap over their own column range */
     int64_t overflow_rows;
     int64_t symbolic_overflow_rows; /* rows whose assisted key table filled up and that were recounted */
     int64_t temp_slots;        /* output slots reserved before compaction (estimation workflows) */

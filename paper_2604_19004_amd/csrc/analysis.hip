@@ -744,6 +744,40 @@ hipError_t launch_row_spans(const Csr &A, const Csr &B, const int64_t *rows, int
     return hipGetLastError();
 }
 
+// flags |= 8 when some row of B is not in ascending column order (then the ranges of k_row_spans are guesses).  Eight
+// lanes per row.
+__global__ void __launch_bounds__(TPB)
+k_check_sorted(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, int64_t rows, int32_t *flags)
+{
+    constexpr int G = 8;
+    const int sub = threadIdx.x & (G - 1);
+    bool bad = false;
+    for (int64_t r = ((int64_t)blockIdx.x * TPB + threadIdx.x) / G; r < rows; r += (int64_t)gridDim.x * (TPB / G)) {
+        const int64_t last = rp[r + 1] - 1;
+        for (int64_t p = rp[r] + sub; p < last; p += 4 * G) {
+            int32_t a[4], b[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int64_t q = p + i * G < last ? p + i * G : p;   // (p < last)
+                a[i] = col[q];
+                b[i] = col[q + 1];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) bad |= a[i] > b[i];
+        }
+    }
+    if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(flags, 8);
+}
+
+hipError_t launch_check_sorted(const Csr &B, int32_t *flags, hipStream_t s)
+{
+    if (B.rows == 0) return hipSuccess;
+    int64_t blocks = (B.rows * 8 + TPB - 1) / TPB;
+    if (blocks > 4096) blocks = 4096;
+    hipLaunchKernelGGL(k_check_sorted, dim3((unsigned)blocks), dim3(TPB), 0, s, B.rp, B.col, B.rows, flags);
+    return hipGetLastError();
+}
+
 // ----------------------------------------------------------- sample rows
 // The stratified sample of Section 3.2 (one row out of each of ns equal strata, chosen by a hash of the
 // stratum's number and the seed), written on the device: the same rows as the host helper behind

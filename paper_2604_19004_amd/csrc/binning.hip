@@ -118,6 +118,7 @@ k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coe
                 }
                 need = e + (e + 3) / 4;
             }
+            int span_class = 0;
             bin = bt.n - 1;
             for (int b = 0; b < bt.n; ++b)
                 if ((long long)bt.slots[b] >= need) { bin = b; break; }
@@ -125,12 +126,16 @@ k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coe
                 // Section 3.3, accumulator selection: the dense accumulator over the row's own column range where
                 // it needs no more memory than the hash table the row would get
                 const long long span = (long long)cmax[i] - (long long)cmin[i] + 1;
-                if (dense_span_pays(span, (long long)bt.slots[bin], vbytes)) {
+                if (mode == 3) {
+                    if (span > 0 && span <= DS_MAX_COLS && bin > SB_W64) bin = SB_SPAN;
+                } else if (dense_span_pays(span, (long long)bt.slots[bin], vbytes)) {
                     bin = NB_DSPAN;
+                    for (int d = DSPAN_CLASSES - 1; d >= 0; --d)
+                        if (span <= kDspanCols[d]) span_class = SORT_CLASSES + d;
                     if (c > span) c = span;
                 }
             }
-            if (bin == bt.n - 1 && c > 0) atomicMax(&s_maxcap, (unsigned int)c);
+            if (mode != 3 && bin == bt.n - 1 && c > 0) atomicMax(&s_maxcap, (unsigned int)c);
             const long long ne = a_rp != nullptr ? a_rp[i + 1] - a_rp[i] : 0;
             if (work != nullptr) {
                 if (ne < (1 << 20)) atomicAdd(&s_nnz_a[bin], (unsigned int)ne);
@@ -142,6 +147,7 @@ k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coe
             }
             if (sort_mask != 0u && bin < NB_COUNT && pr <= kSortClass[SORT_CLASSES - 1].cap)
                 bin += sort_class(pr, ne, bin, sort_mask) * OCEAN_MAX_BINS;
+            bin += span_class * OCEAN_MAX_BINS;
             atomicAdd(&s_cnt[bin], 1u);
             if (bin_prod != nullptr) atomicAdd(&s_prod[bin], (unsigned long long)pr);
         }
@@ -180,7 +186,7 @@ hipError_t launch_classify(int64_t m, const BinParams &p, double scale, const in
     const int64_t tiles = (m + ROW_TILE - 1) / ROW_TILE;
     const double table_coef = (p.table_coef > 0.0 && p.table_coef < p.coef) ? p.table_coef : p.coef;
     hipLaunchKernelGGL(k_classify, dim3((unsigned)tiles), dim3(TPB), 0, s, m, p.mode, p.coef, table_coef, p.bound_coef, scale, bt,
-                       p.n_cols, prod, est, nnz_exact, row_mask, lower_bound, p.mode != 3 ? p.cmin : nullptr, p.cmax, p.vbytes,
+                       p.n_cols, prod, est, nnz_exact, row_mask, lower_bound, p.cmin, p.cmax, p.vbytes,
                        p.sort_mask, p.a_rp, bin_of_row, cap, tile_cap, zero, bin_count, bin_prod, max_cap, work);
     return hipGetLastError();
 }

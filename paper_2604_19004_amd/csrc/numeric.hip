@@ -597,9 +597,11 @@ k_numeric_wg(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col
 // prefix popcount.  QUERY: the presence bit is read first and set only when it is clear (Section 4.1).  A product
 // outside the range (B's rows not in column order: the range was a guess) makes the row report overflow, like a
 // row with more entries than were reserved for it; the caller redoes such rows with hash tables.
+// COLS: columns the range may have (4096, or less where the rows' ranges allow it: what LDS a row takes decides how many
+// rows a compute unit works on, and every column is cleared and looked at.  100 000 rows of 2500 products in blocks of
+// 1000 columns: 842 us with 4096).
 constexpr int DS_THREADS = 256;
-constexpr int DS_WORDS = (int)DS_MAX_COLS / 32;
-template <typename V, bool QUERY>
+template <typename V, bool QUERY, int COLS>
 __global__ void __launch_bounds__(DS_THREADS)
 k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, const V *__restrict__ a_val,
                 const int64_t *__restrict__ b_rp, const int32_t *__restrict__ b_col, const V *__restrict__ b_val,
@@ -607,9 +609,10 @@ k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                 const int64_t *__restrict__ out_ptr, int32_t *__restrict__ out_col, V *__restrict__ out_val,
                 int32_t *__restrict__ row_nnz)
 {
+    constexpr int DS_WORDS = COLS / 32;
     static_assert(DS_WORDS <= DS_THREADS, "one bitmap word per thread in the prefix sum");
     using AV = acc_t<V>;
-    __shared__ AV s_vals[DS_MAX_COLS];
+    __shared__ AV s_vals[COLS];
     __shared__ uint32_t s_bm[DS_WORDS];
     __shared__ uint32_t s_pre[DS_WORDS];
     __shared__ WgChunk<V, DS_THREADS> s_fc;
@@ -620,7 +623,7 @@ k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
     if (r >= count) return;
     const int64_t row = rows[r];
     const int32_t c0 = cmin[row];
-    for (int j = tid; j < (int)DS_MAX_COLS; j += DS_THREADS) s_vals[j] = (AV)0;
+    for (int j = tid; j < COLS; j += DS_THREADS) s_vals[j] = (AV)0;
     if (tid < DS_WORDS) s_bm[tid] = 0u;
     if (tid == 0) s_bad = 0;
     __syncthreads();
@@ -632,7 +635,7 @@ k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                                       for (int u = 0; u < U; ++u) {
                                           if (cj[u] < 0) continue;
                                           const uint32_t d = (uint32_t)(cj[u] - c0);   // (a column before c0 wraps to a large number)
-                                          if (d < (uint32_t)DS_MAX_COLS) {
+                                          if (d < (uint32_t)COLS) {
                                               lds_add(&s_vals[d], (AV)cv[u]);
                                               const uint32_t bit = 1u << (d & 31u);
                                               if (!QUERY || !(s_bm[d >> 5] & bit)) atomicOr(&s_bm[d >> 5], bit);
@@ -655,7 +658,7 @@ k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
     }
     // thread t looks at columns t, t + 256, ...: the lanes of a wave read consecutive values and the present ones
     // among them go to consecutive places of the output
-    for (int j = tid; j < (int)DS_MAX_COLS; j += DS_THREADS) {
+    for (int j = tid; j < COLS; j += DS_THREADS) {
         const uint32_t wbits = s_bm[j >> 5];
         if ((wbits >> (j & 31)) & 1u) {
             const int rank = (int)s_pre[j >> 5] + __popc(wbits & ((1u << (j & 31)) - 1u));
@@ -1445,12 +1448,19 @@ static hipError_t dispatch(const Csr &A, const Csr &B, const NumLaunch &l, int /
     case NB_S8K: OCEAN_WG(13, 1024); break;
     case NB_DSPAN:
         if (l.cmin == nullptr) return hipErrorInvalidValue;
-        if (l.query_bitmap)
-            hipLaunchKernelGGL((k_numeric_dspan<V, true>), dim3((unsigned)l.count), dim3(DS_THREADS), 0, s, A.rp, A.col, av, B.rp,
-                               B.col, bv, l.rows, l.count, l.cmin, l.out_ptr, l.out_col, ov, l.row_nnz);
-        else
-            hipLaunchKernelGGL((k_numeric_dspan<V, false>), dim3((unsigned)l.count), dim3(DS_THREADS), 0, s, A.rp, A.col, av, B.rp,
-                               B.col, bv, l.rows, l.count, l.cmin, l.out_ptr, l.out_col, ov, l.row_nnz);
+#define OCEAN_DSPAN(QUERY, COLS)                                                                                          \
+    hipLaunchKernelGGL((k_numeric_dspan<V, QUERY, COLS>), dim3((unsigned)l.count), dim3(DS_THREADS), 0, s, A.rp, A.col, av,    \
+                       B.rp, B.col, bv, l.rows, l.count, l.cmin, l.out_ptr, l.out_col, ov, l.row_nnz)
+#define OCEAN_DSPAN_COLS(QUERY)                                                                                           \
+    do {                                                                                                                  \
+        if (l.span_cols <= 1024) OCEAN_DSPAN(QUERY, 1024);                                                                \
+        else if (l.span_cols <= 2048) OCEAN_DSPAN(QUERY, 2048);                                                           \
+        else OCEAN_DSPAN(QUERY, (int)DS_MAX_COLS);                                                                        \
+    } while (0)
+        if (l.query_bitmap) OCEAN_DSPAN_COLS(true);
+        else OCEAN_DSPAN_COLS(false);
+#undef OCEAN_DSPAN_COLS
+#undef OCEAN_DSPAN
         break;
     case NB_HYBRID:
         if (l.bw != nullptr) return hipErrorInvalidValue;   // such rows go with the last bin

@@ -372,20 +372,29 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
         bp.n_bins = SB_COUNT;
         for (int b = 0; b < SB_COUNT; ++b) bp.slots[b] = kSymbolicSlots[b];
         bp.n_cols = B.cols;
+        const bool spans = round == 0 && w.spans;
+        if (spans) { bp.cmin = w.cmin; bp.cmax = w.cmax; }
         OC_TRY(zero_bins(c, w));
         HIP_TRY(launch_classify(A.rows, bp, 1.0, w.prod, nullptr, nullptr, round == 0 ? nullptr : nnz_out, w.maxb, w.bin,
                                 nullptr, nullptr, round == 0 ? nnz_out : nullptr, w.sc->bin_count, nullptr, nullptr, nullptr, c.s));
-        HIP_TRY(launch_place(A.rows, nullptr, nullptr, nullptr, nullptr, SB_COUNT, w.bin, w.sc->bin_count, w.sc->bin_cursor,
+        HIP_TRY(launch_place(A.rows, nullptr, nullptr, nullptr, nullptr, SB_ALL, w.bin, w.sc->bin_count, w.sc->bin_cursor,
                              w.bin_rows, c.s));
         OC_TRY(fetch_scalars(c, w.sc));
-        int64_t start[SB_COUNT + 1];
+        if (spans && (c.h->flags & 8)) {
+            // B's rows are not in column order: the ranges are guesses, and the exact sizes that this pass is asked for must
+            // not depend on them, nor may the numeric pass, which has no second attempt in this workflow
+            w.spans = false;
+            --round;
+            continue;
+        }
+        int64_t start[SB_ALL + 1];
         start[0] = 0;
-        for (int b = 0; b < SB_COUNT; ++b) {
+        for (int b = 0; b < SB_ALL; ++b) {
             start[b + 1] = start[b] + (int64_t)c.h->bin_count[b];
             if (st && round == 0) st->symbolic_rows_per_bin[b] = (int64_t)c.h->bin_count[b];
         }
-        for (int b = SB_COUNT - 1; b >= 0; --b) {
-            SymLaunch l{w.bin_rows + start[b], start[b + 1] - start[b], b, query_bitmap, assisted};
+        for (int b = SB_ALL - 1; b >= 0; --b) {
+            SymLaunch l{w.bin_rows + start[b], start[b + 1] - start[b], b, query_bitmap, spans ? w.cmin : nullptr, assisted};
             if (wide_bitmap && (b == SB_S16K || b == SB_S32K)) continue;
             if (wide_bitmap && b == SB_BITMAP) {
                 l.rows = w.bin_rows + start[SB_S16K];
@@ -395,7 +404,7 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
             const int n_wg = (int)(l.count < c.n_cu ? l.count : c.n_cu);
             HIP_TRY(launch_symbolic_bin(A, B, l, gb_log2, nnz_out, n_wg, &w.sc->queue[round], c.s));
         }
-        if (!assisted) break;
+        if (!assisted && start[SB_ALL] == start[SB_SPAN]) break;   // (no row's table or range can have been too small)
         HIP_TRY(launch_count_rows(A.rows, nnz_out, nullptr, nullptr, nullptr, &w.sc->ovf_count, nullptr, nullptr, c.s));
         OC_TRY(fetch_scalars(c, w.sc));
         if (st) st->symbolic_overflow_rows = (int64_t)c.h->ovf_count;
@@ -493,10 +502,17 @@ int run_numeric(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int gb_l
         }
         return OCEAN_OK;
     };
-    for (int b = NB_ALL - 1; b >= 0; --b) {
+    // (slots from NB_ALL on: the dense-range bin's classes, whose lists follow those of the sort classes)
+    int64_t dspan_at = start[NB_ALL];
+    for (int k = OCEAN_MAX_BINS; k < SORT_CLASSES * OCEAN_MAX_BINS; ++k) dspan_at += (int64_t)count[k];
+    for (int slot = NB_ALL + DSPAN_CLASSES - 1; slot >= 0; --slot) {
         NumLaunch l{};
-        l.rows = w.bin_rows + start[b];
-        l.count = start[b + 1] - start[b];
+        const int d = slot - NB_ALL;
+        const int b = d >= 0 ? NB_DSPAN : slot;
+        l.rows = w.bin_rows + (d >= 0 ? dspan_at : start[b]);
+        l.count = d >= 0 ? (int64_t)count[(SORT_CLASSES + d) * OCEAN_MAX_BINS + NB_DSPAN] : start[b + 1] - start[b];
+        for (int e = 0; e < d; ++e) l.rows += count[(SORT_CLASSES + e) * OCEAN_MAX_BINS + NB_DSPAN];
+        l.span_cols = d >= 0 ? kDspanCols[d] : (int)DS_MAX_COLS;
         l.bin = b;
         l.out_ptr = out_ptr;
         l.out_col = out_col;
@@ -857,6 +873,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     if ((o.dense_range == 2 || (o.dense_range == 1 && S->sampled_rows > 0 && (int64_t)S->dense_range_rows * 50 >= S->sampled_rows)) &&
         !(c.h->flags & 8)) {
         HIP_TRY(launch_row_spans(A, B, nullptr, m, w.cmin, w.cmax, c.s));
+        if (bw_try == nullptr) HIP_TRY(launch_check_sorted(B, &w.sc->flags, c.s));   // (known from the window table otherwise)
         w.spans = true;
     }
     const bool esc_ok = o.esc_short_rows != 0 && n >= 32 && n <= ESC_MAX_COLS;
@@ -873,11 +890,6 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         bp.n_cols = n;
         bp.sort_mask = c.sort_mask;
         bp.a_rp = A.rp;
-        if (w.spans) {
-            bp.cmin = w.cmin;
-            bp.cmax = w.cmax;
-            bp.vbytes = (int)vbytes;
-        }
         if (workflow == OCEAN_WF_HLL) {
             OC_TRY(build_sketches());
             OC_TRY(mark(c, OCEAN_ST_PREDICT));
@@ -895,6 +907,11 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         } else {
             bp.mode = 0;
             bp.coef = 1.0;
+        }
+        if (w.spans) {
+            bp.cmin = w.cmin;
+            bp.cmax = w.cmax;
+            bp.vbytes = (int)vbytes;
         }
         bp.bound_coef = o.bound_load_coef;
         S->workflow = workflow;

@@ -43,6 +43,9 @@ enum SymbolicBin {
     SB_BITMAP,    // LDS bitmap over column windows
     SB_COUNT
 };
+// (after the bins of ocean_bin_layout) rows whose column range is known and at most DS_MAX_COLS columns: a bitmap over it
+constexpr int SB_SPAN = SB_COUNT;
+constexpr int SB_ALL = SB_COUNT + 1;
 constexpr int32_t kSymbolicSlots[SB_COUNT] = {64, 256, 1024, 4096, 16384, 32768, 0x7fffffff};
 
 constexpr int32_t BIN_NONE = 255;          // row takes no part in this launch set
@@ -67,8 +70,11 @@ constexpr int SORT_CLASSES = 13;            // class 0: not sorted, the bin's ow
 constexpr SortClass kSortClass[SORT_CLASSES] = {
     {0, 0, 0}, {32, 32, 400}, {64, 64, 600}, {96, 64, 800}, {128, 64, 1000}, {192, 64, 1300}, {256, 64, 1600},
     {384, 64, 2300}, {512, 64, 2900}, {768, 64, 4100}, {1024, 64, 5300}, {1536, 64, 7900}, {2048, 64, 12100}};
+// Rows of the dense-range bin (NB_DSPAN below) whose range is at most kDspanCols[d] columns form a class of their own.
+constexpr int DSPAN_CLASSES = 2;
+constexpr int kDspanCols[DSPAN_CLASSES] = {1024, 2048};
 // Rows are grouped by (class, bin): key = class * OCEAN_MAX_BINS + bin, so that the rows of a class are adjacent.
-constexpr int ROW_KEYS = SORT_CLASSES * OCEAN_MAX_BINS;
+constexpr int ROW_KEYS = (SORT_CLASSES + DSPAN_CLASSES) * OCEAN_MAX_BINS;
 
 // ------------------------------------------------------------- CSR view ----
 struct Csr {
@@ -231,6 +237,7 @@ hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const 
 hipError_t launch_sample_rows(int64_t rows, int64_t ns, uint32_t seed, int64_t *out, hipStream_t s);
 hipError_t launch_row_spans(const Csr &A, const Csr &B, const int64_t *rows, int64_t n, int32_t *cmin, int32_t *cmax,
                             hipStream_t s);
+hipError_t launch_check_sorted(const Csr &B, int32_t *flags, hipStream_t s);
 hipError_t launch_sample_reduce(const int64_t *rows, int64_t n_rows, const int64_t *prod, const double *est,
                                 const int32_t *cmin, const int32_t *cmax /*of the sampled rows, may be null*/,
                                 int64_t n_cols, int vbytes, double bound_coef,
@@ -247,7 +254,8 @@ struct BinParams {
     double bound_coef;   // table slots per intermediate product beyond which a table is of no use (modes 0, 1, 2;
                          // at most 1.0 = the product bound itself)
     const int32_t *cmin; // per row: first and last column the row can reach (k_row_spans), or null: rows whose range
-    const int32_t *cmax; // pays for it go to the dense-range bin NB_DSPAN (modes 0, 1, 2)
+    const int32_t *cmax; // pays for it go to the dense-range bin NB_DSPAN (modes 0, 1, 2), rows whose range is at most
+                         // DS_MAX_COLS columns and that need more than 256 keys to SB_SPAN (mode 3)
     int vbytes;          // bytes of a value (with cmin)
     unsigned sort_mask;  // sort classes that may be used (bit c; modes 0, 1, 2), 0: none
     const int64_t *a_rp; // row offsets of A (with sort_mask or work sums)
@@ -274,6 +282,7 @@ struct SymLaunch {
     int64_t count;
     int bin;
     bool query_bitmap;     // bitmap kernel: read a column's bit before setting it (Section 4.1)
+    const int32_t *cmin;   // SB_SPAN: first column each row can reach
     bool may_overflow;     // tables were sized from a guess (assisted binning): a row whose table fills up
                            // reports -1 instead of a count and probing gives up early
 };
@@ -308,6 +317,7 @@ struct NumLaunch {
     bool query_bitmap;        // dense windows: read a column's presence bit before setting it (Section 4.1)
     bool fine_buckets;        // 512- and 1024-slot bins: order the row through 2048 column buckets (clustered columns)
     const int32_t *cmin;      // dense-range bin: first column each row can reach
+    int span_cols;            // dense-range bin: the rows' ranges are at most so many columns (kDspanCols or DS_MAX_COLS)
 };
 hipError_t launch_window_table(const Csr &B, int dtype, uint32_t *bw, int *n_win_out, int32_t *flags, hipStream_t s);
 int heavy_workgroups_per_cu();   // workgroups of the column-window kernel that one compute unit holds
