@@ -6,13 +6,15 @@
 namespace ocean {
 
 constexpr int TPB = 256;
-// Rows a workgroup of the kernels below handles, ROW_ITEMS per thread: a tile.  The kernel that fixes the rows' capacities
+// Rows a workgroup of the kernels below handles, 4 or 8 per thread: a tile.  The kernel that fixes the rows' capacities
 // also sums them per tile, so that one more launch, which adds up the sums of the tiles before its own, places the rows.
-constexpr int ROW_ITEMS = 4;
-constexpr int ROW_TILE = TPB * ROW_ITEMS;
+// Workgroups add to the same few global counters, 12 ns apart, so large matrices have larger tiles: 1 M rows in 512 instead
+// of 1024 workgroups.
+static int row_items(int64_t m) { return m > 262144 ? 8 : 4; }
 constexpr int64_t DIRECT_TILES = 4096;   // up to here every workgroup adds up the tiles before it (4 M rows: 16 loads a thread)
 
-int64_t scan_tmp_elems(int64_t n) { return (n + ROW_TILE - 1) / ROW_TILE + 1; }
+static int64_t row_tiles(int64_t m) { return (m + TPB * row_items(m) - 1) / (TPB * row_items(m)); }
+int64_t scan_tmp_elems(int64_t n) { return row_tiles(n) + 1; }
 
 // Sum over the workgroup, in every thread.  s_part: one word per wave; barriers inside, s_part may be reused after.
 __device__ __forceinline__ long long block_sum(long long v, long long *s_part)
@@ -58,6 +60,7 @@ __device__ __forceinline__ int sort_class(long long pr, long long ne, int bin, u
 // sort_mask: bit c set = sort class c may be used (modes 0, 1, 2; see kSortClass); a_rp: row offsets of A.
 // bin_of_row receives the row's key, class * OCEAN_MAX_BINS + bin, which is the bin itself for rows that are not
 // sorted; bin_count and bin_prod have one counter per key.
+template <int ROW_ITEMS>
 __global__ void __launch_bounds__(TPB)
 k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coef, double scale, BinTable bt, int64_t n_cols,
            const int64_t *__restrict__ prod, const double *__restrict__ est, const int32_t *__restrict__ nnz_exact,
@@ -67,12 +70,13 @@ k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coe
            int64_t *__restrict__ tile_cap, int32_t *zero, unsigned long long *bin_count, unsigned long long *bin_prod,
            unsigned long long *max_cap, unsigned long long *work)
 {
+    constexpr int ROW_TILE = TPB * ROW_ITEMS;
     __shared__ unsigned int s_cnt[ROW_KEYS];
     __shared__ unsigned long long s_prod[ROW_KEYS];
     __shared__ unsigned int s_maxcap;
     static_assert(ROW_KEYS <= TPB && ROW_KEYS <= BIN_NONE, "one thread per key, keys in a byte");
     if (threadIdx.x < ROW_KEYS) { s_cnt[threadIdx.x] = 0; s_prod[threadIdx.x] = 0ull; }
-    // (1024 rows of fewer than 2^20 entries: below 2^30; longer rows are added to the totals one by one)
+    // (2048 rows of fewer than 2^20 entries: below 2^31; longer rows are added to the totals one by one)
     __shared__ unsigned int s_nnz_a[OCEAN_MAX_BINS], s_nnz_c[OCEAN_MAX_BINS];
     __shared__ long long s_part[TPB / WAVE];
     if (threadIdx.x < OCEAN_MAX_BINS) { s_nnz_a[threadIdx.x] = 0u; s_nnz_c[threadIdx.x] = 0u; }
@@ -183,9 +187,10 @@ hipError_t launch_classify(int64_t m, const BinParams &p, double scale, const in
     BinTable bt;
     bt.n = p.n_bins;
     for (int b = 0; b < OCEAN_MAX_BINS; ++b) bt.slots[b] = b < p.n_bins ? p.slots[b] : 0;
-    const int64_t tiles = (m + ROW_TILE - 1) / ROW_TILE;
+    const int64_t tiles = row_tiles(m);
     const double table_coef = (p.table_coef > 0.0 && p.table_coef < p.coef) ? p.table_coef : p.coef;
-    hipLaunchKernelGGL(k_classify, dim3((unsigned)tiles), dim3(TPB), 0, s, m, p.mode, p.coef, table_coef, p.bound_coef, scale, bt,
+    const auto kernel = row_items(m) == 4 ? k_classify<4> : k_classify<8>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(TPB), 0, s, m, p.mode, p.coef, table_coef, p.bound_coef, scale, bt,
                        p.n_cols, prod, est, nnz_exact, row_mask, lower_bound, p.cmin, p.cmax, p.vbytes,
                        p.sort_mask, p.a_rp, bin_of_row, cap, tile_cap, zero, bin_count, bin_prod, max_cap, work);
     return hipGetLastError();
@@ -197,11 +202,13 @@ hipError_t launch_classify(int64_t m, const BinParams &p, double scale, const in
 //                           workgroup counts its rows per key in LDS, claims one contiguous range per key, then fills it
 // tile_sum: sums of in over the tiles, or, with `scanned`, their exclusive prefix sums.  It replaced a three-launch scan
 // (one workgroup for up to 65 536 rows: 39 us for 32 768) and a scatter: 5 us a launch.
+template <int ROW_ITEMS>
 __global__ void __launch_bounds__(TPB)
 k_place(int64_t m, const int32_t *__restrict__ in, const int64_t *__restrict__ tile_sum, bool scanned,
         int64_t *__restrict__ out, unsigned long long *total_out, int n_keys, const uint8_t *__restrict__ bin_of_row,
         const unsigned long long *__restrict__ bin_count, unsigned long long *bin_cursor, int32_t *__restrict__ bin_rows)
 {
+    constexpr int ROW_TILE = TPB * ROW_ITEMS;
     __shared__ unsigned int s_cnt[ROW_KEYS];
     __shared__ unsigned int s_base[ROW_KEYS];
     __shared__ unsigned int s_wave[TPB / WAVE];
@@ -304,10 +311,11 @@ hipError_t launch_place(int64_t m, const int32_t *in, int64_t *tile_sum, int64_t
                         unsigned long long *bin_cursor, int32_t *bin_rows, hipStream_t s)
 {
     if (m == 0) return hipSuccess;
-    const int64_t tiles = (m + ROW_TILE - 1) / ROW_TILE;
+    const int64_t tiles = row_tiles(m);
     const bool scan_first = out != nullptr && tiles > DIRECT_TILES;
     if (scan_first) hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(TPB), 0, s, tile_sum, tiles);
-    hipLaunchKernelGGL(k_place, dim3((unsigned)tiles), dim3(TPB), 0, s, m, in, tile_sum, scan_first, out, total_out, n_keys,
+    const auto kernel = row_items(m) == 4 ? k_place<4> : k_place<8>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(TPB), 0, s, m, in, tile_sum, scan_first, out, total_out, n_keys,
                        bin_of_row, bin_count, bin_cursor, bin_rows);
     return hipGetLastError();
 }
@@ -315,11 +323,13 @@ hipError_t launch_place(int64_t m, const int32_t *in, int64_t *tile_sum, int64_t
 // Produced entries per row: their sums per tile (for launch_place), the rows that overflowed (< 0), and, with work, the
 // entries of C per bin of the other rows.  nnz2 (may be null): a row's entries where the first attempt overflowed; then
 // final_nnz receives what counts and that is what is summed.
+template <int ROW_ITEMS>
 __global__ void __launch_bounds__(TPB)
 k_count_rows(int64_t m, const int32_t *__restrict__ nnz1, const int32_t *__restrict__ nnz2, int32_t *__restrict__ final_nnz,
              int64_t *__restrict__ tile_sum, unsigned long long *overflowed, const uint8_t *__restrict__ bin_of_row,
              unsigned long long *work)
 {
+    constexpr int ROW_TILE = TPB * ROW_ITEMS;
     __shared__ unsigned int s_nnz_c[OCEAN_MAX_BINS];
     __shared__ long long s_part[TPB / WAVE];
     if (threadIdx.x < OCEAN_MAX_BINS) s_nnz_c[threadIdx.x] = 0u;
@@ -334,7 +344,7 @@ k_count_rows(int64_t m, const int32_t *__restrict__ nnz1, const int32_t *__restr
         bad += c < 0;
         if (work != nullptr && c > 0) {
             const int b = (int)bin_of_row[i] % OCEAN_MAX_BINS;
-            if (c < (1 << 20)) atomicAdd(&s_nnz_c[b], (unsigned int)c);   // (1024 rows: below 2^30)
+            if (c < (1 << 20)) atomicAdd(&s_nnz_c[b], (unsigned int)c);   // (2048 rows: below 2^31)
             else atomicAdd(&work[OCEAN_MAX_BINS + b], (unsigned long long)c);
         }
         if (nnz2 != nullptr) {
@@ -357,7 +367,8 @@ hipError_t launch_count_rows(int64_t m, const int32_t *nnz1, const int32_t *nnz2
                              unsigned long long *overflowed, const uint8_t *bin_of_row, unsigned long long *work, hipStream_t s)
 {
     if (m == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_count_rows, dim3((unsigned)((m + ROW_TILE - 1) / ROW_TILE)), dim3(TPB), 0, s, m, nnz1, nnz2, final_nnz,
+    const auto kernel = row_items(m) == 4 ? k_count_rows<4> : k_count_rows<8>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)row_tiles(m)), dim3(TPB), 0, s, m, nnz1, nnz2, final_nnz,
                        tile_sum, overflowed, bin_of_row, work);
     return hipGetLastError();
 }
