@@ -137,14 +137,17 @@ k_symbolic_wg(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_co
               const int32_t *__restrict__ rows, int64_t count, int32_t *__restrict__ nnz_out)
 {
     constexpr int SLOTS = 1 << BITS;
-    __shared__ int32_t s_keys[SLOTS];
+    __shared__ __align__(16) int32_t s_keys[SLOTS];
     __shared__ WgChunk<NoVal, THREADS> s_fc;
     __shared__ int s_count, s_ovf;
     const int tid = threadIdx.x;
     const int64_t r = blockIdx.x;
     if (r >= count) return;
     const int64_t row = rows[r];
-    for (int s = tid; s < SLOTS; s += THREADS) s_keys[s] = EMPTY_KEY;
+    static_assert(SLOTS % (4 * THREADS) == 0, "cleared 16 bytes per thread and step");
+#pragma unroll
+    for (int s = 0; s < SLOTS / 4 / THREADS; ++s)
+        reinterpret_cast<int4 *>(s_keys)[s * THREADS + tid] = make_int4(EMPTY_KEY, EMPTY_KEY, EMPTY_KEY, EMPTY_KEY);
     if (tid == 0) { s_count = 0; s_ovf = 0; }
     __syncthreads();
     int fresh = 0;
