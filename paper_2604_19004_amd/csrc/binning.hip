@@ -6,11 +6,13 @@
 namespace ocean {
 
 constexpr int TPB = 256;
-// Rows a workgroup of the kernels below handles, 4 or 8 per thread: a tile.  The kernel that fixes the rows' capacities
+// Rows a workgroup of the kernels below handles, 1, 4 or 8 per thread: a tile.  The kernel that fixes the rows' capacities
 // also sums them per tile, so that one more launch, which adds up the sums of the tiles before its own, places the rows.
 // Workgroups add to the same few global counters, 12 ns apart, so large matrices have larger tiles: 1 M rows in 512 instead
 // of 1024 workgroups.
-static int row_items(int64_t m) { return m > 262144 ? 8 : 4; }
+// Small ones have small tiles: 4096 rows are a handful of workgroups either way, and a thread's rows are one latency
+// after the other (classification of 4096 rows 9 us with four rows per thread).
+static int row_items(int64_t m) { return m > 262144 ? 8 : m > 65536 ? 4 : 1; }
 constexpr int64_t DIRECT_TILES = 4096;   // up to here every workgroup adds up the tiles before it (4 M rows: 16 loads a thread)
 
 static int64_t row_tiles(int64_t m) { return (m + TPB * row_items(m) - 1) / (TPB * row_items(m)); }
@@ -189,7 +191,7 @@ hipError_t launch_classify(int64_t m, const BinParams &p, double scale, const in
     for (int b = 0; b < OCEAN_MAX_BINS; ++b) bt.slots[b] = b < p.n_bins ? p.slots[b] : 0;
     const int64_t tiles = row_tiles(m);
     const double table_coef = (p.table_coef > 0.0 && p.table_coef < p.coef) ? p.table_coef : p.coef;
-    const auto kernel = row_items(m) == 4 ? k_classify<4> : k_classify<8>;
+    const auto kernel = row_items(m) == 1 ? k_classify<1> : row_items(m) == 4 ? k_classify<4> : k_classify<8>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(TPB), 0, s, m, p.mode, p.coef, table_coef, p.bound_coef, scale, bt,
                        p.n_cols, prod, est, nnz_exact, row_mask, lower_bound, p.cmin, p.cmax, p.vbytes,
                        p.sort_mask, p.a_rp, bin_of_row, cap, tile_cap, zero, bin_count, bin_prod, max_cap, work);
@@ -314,7 +316,7 @@ hipError_t launch_place(int64_t m, const int32_t *in, int64_t *tile_sum, int64_t
     const int64_t tiles = row_tiles(m);
     const bool scan_first = out != nullptr && tiles > DIRECT_TILES;
     if (scan_first) hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(TPB), 0, s, tile_sum, tiles);
-    const auto kernel = row_items(m) == 4 ? k_place<4> : k_place<8>;
+    const auto kernel = row_items(m) == 1 ? k_place<1> : row_items(m) == 4 ? k_place<4> : k_place<8>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(TPB), 0, s, m, in, tile_sum, scan_first, out, total_out, n_keys,
                        bin_of_row, bin_count, bin_cursor, bin_rows);
     return hipGetLastError();
@@ -367,7 +369,7 @@ hipError_t launch_count_rows(int64_t m, const int32_t *nnz1, const int32_t *nnz2
                              unsigned long long *overflowed, const uint8_t *bin_of_row, unsigned long long *work, hipStream_t s)
 {
     if (m == 0) return hipSuccess;
-    const auto kernel = row_items(m) == 4 ? k_count_rows<4> : k_count_rows<8>;
+    const auto kernel = row_items(m) == 1 ? k_count_rows<1> : row_items(m) == 4 ? k_count_rows<4> : k_count_rows<8>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)row_tiles(m)), dim3(TPB), 0, s, m, nnz1, nnz2, final_nnz,
                        tile_sum, overflowed, bin_of_row, work);
     return hipGetLastError();
