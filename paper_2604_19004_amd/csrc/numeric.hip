@@ -1,6 +1,8 @@
 // Numeric pass: Gustavson's row-wise product (paper Section 2.1) with
 // open-addressing hash accumulators (Section 2.2) sized per bin, followed by
-// the per-row sort that makes the output CSR-compliant (Section 4.2).
+// the per-row sort that makes the output CSR-compliant (Section 4.2).  Rows of at
+// most 2048 products are sorted instead (sortrow.hip) unless they fall on few
+// columns or have more than 64 entries.
 //
 //   k_numeric_group   several short rows per wave (8 or 16 lanes per row), 32- or 64-slot tables in LDS
 //   k_numeric_wave    one wave per row, 256-slot table in LDS

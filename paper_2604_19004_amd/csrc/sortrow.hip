@@ -14,7 +14,8 @@
 //             openers store their value at the entry's place in LDS, the others add theirs, and the row leaves with
 //             coalesced stores, in column order.
 // What bounds it is vector issue: 880 vector instructions per row of the 512-product class, of which the sort is 530, are
-// 489 us for the 341 000 rows of the rectangular input's class at one per four cycles and SIMD, 541 us measured.  The work
+// 489 us for 341 000 rows (of the rectangular input, before there was a class of 384) at one per four cycles and SIMD,
+// 541 us measured.  The work
 // does not depend on where the columns lie or how many products merge.  Sizes of 3 * 2^i products cost a third less
 // per row than the next power of two (see settle).  Against the hash kernels (one MI355X, fp64 unless said): numeric
 // stage of the rectangular input (264 products a row) 1.50 -> 0.94 ms, clustered fp32 (762 products, 234 columns) 2.55 ->
