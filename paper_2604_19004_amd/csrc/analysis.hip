@@ -137,7 +137,7 @@ __device__ __forceinline__ void block_totals(long long tsum, long long tmax, lon
 }
 
 // bad_bit: bit of flags that any fault of A sets besides its own (0: none, and A's ends are not looked at).
-// near_pairs: see k_validate.
+// near_pairs (given where B is the same matrix): see k_validate; a descending pair of columns in a sampled row sets bit 8.
 __global__ void __launch_bounds__(TPB)
 k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, int64_t m, int64_t a_nnz,
                const int64_t *__restrict__ b_rp, int64_t b_rows, int g_log2, int64_t long_from, int n_long,
@@ -160,6 +160,7 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
     const bool sampling = near_pairs != nullptr && !for_long && (block & 15) == 0;   // uniform
     unsigned int near = 0, seen = 0;
     long long tsum = 0, tmax = 0, theavy = 0;
+    bool unsorted = false;
     bool bad = false, bad_rp = bad_bit != 0 && blockIdx.x == 0 && tid == 0 && (a_rp[0] != 0 || a_rp[m] != a_nnz);
     // entries first, first + step, ... below e1: four independent chains (entry -> row offsets of B) in flight per lane;
     // reads are unconditional (index clamped) so that they are issued together
@@ -173,8 +174,10 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
                 ok[i] = idx < e1;
                 k[i] = a_col[ok[i] ? idx : e];
                 if (sampling && ok[i] && idx + 1 < a_nnz) {
-                    near += (uint32_t)(a_col[idx + 1] - k[i] - 1) < 4u;
+                    const int32_t next = a_col[idx + 1];
+                    near += (uint32_t)(next - k[i] - 1) < 4u;
                     ++seen;
+                    unsorted |= idx + 1 < e1 && next < k[i];
                 }
                 if ((uint32_t)k[i] >= (uint64_t)b_rows) { bad = true; k[i] = 0; ok[i] = false; }
             }
@@ -238,6 +241,7 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
     block_totals(tsum, tmax, theavy, s_sum, s_max, s_heavy, totals);
     if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(flags, 4 | bad_bit);
     if (__ballot(bad_rp) != 0 && lane_id() == 0) atomicOr(flags, 1);
+    if (__ballot(unsorted) != 0 && lane_id() == 0) atomicOr(flags, 8);
     if (sampling) {
         if (tid == 0) { s_near = 0u; s_seen = 0u; }
         __syncthreads();
