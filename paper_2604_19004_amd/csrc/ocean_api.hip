@@ -867,7 +867,8 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     c.query_bitmap = o.bitmap_query >= 1 || (o.bitmap_query < 0 && S->sampled_rows > 0 && S->sampled_cr >= o.bitmap_query_cr);
     const bool query_bitmap = o.bitmap_query == 2;
     Csr Bnum = B;   // what the numeric kernels read: B, or a copy of it with sorted rows (see below)
-    bool tried_sorted_copy = false;
+    bool tried_sorted_copy = false, sorted_copy = false;
+    bool b_unsorted = false;   // a row of B is out of column order: kept here, as the copy's own check clears the flags word
     // Section 3.3, accumulator selection: rows whose column range is no larger than the hash table they would get
     // use the dense accumulator over that range.  The ranges of all rows cost a pass over A; it is taken when the
     // sample found such rows (2 % of it or more) or when told to (dense_range = 2), and not when B's rows are known
@@ -933,8 +934,9 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
             S->rows_per_bin[b] = 0;
             for (int k = b; k < ROW_KEYS; k += OCEAN_MAX_BINS) S->rows_per_bin[b] += (int64_t)c.h->bin_count[k];
         }
-        c.bw = (bw_try != nullptr && !(c.h->flags & 8)) ? bw_try : nullptr;
-        if (bw_try != nullptr && (c.h->flags & 8) && !tried_sorted_copy && o.sort_b_ratio > 0.0 &&
+        b_unsorted = b_unsorted || (c.h->flags & 8) != 0;
+        c.bw = (bw_try != nullptr && (!b_unsorted || sorted_copy)) ? bw_try : nullptr;
+        if (bw_try != nullptr && b_unsorted && !tried_sorted_copy && o.sort_b_ratio > 0.0 &&
             (double)S->heavy_products >= o.sort_b_ratio * (double)B.nnz) {
             // Throughput-bound case of the accumulators that keep values in global memory (Section 5.4): B's rows
             // are unsorted, so heavy rows would go to those kernels, and they hold many times more products than B
@@ -952,6 +954,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
                 OC_TRY(fetch_scalars(c, w.sc));
                 if (!(c.h->flags & (8 | 16))) {
                     Bnum = Bs;
+                    sorted_copy = true;
                     c.bw = bw_try;
                     S->b_sorted_copy = 1;
                 }
@@ -966,6 +969,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
                 // Section 5.2: with too little memory for the estimation workflow, take the two-pass one
                 workflow = OCEAN_WF_SYMBOLIC;
                 S->fell_back = 1;
+                if (b_unsorted) w.spans = false;   // (guesses: exact sizes must not rest on them, see run_symbolic)
                 continue;
             }
             return fail(OCEAN_EALLOC, "output allocation failed");
