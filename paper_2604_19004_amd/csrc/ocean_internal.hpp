@@ -223,6 +223,18 @@ __device__ __forceinline__ T group_reduce_max(T v, int width)
 constexpr int ROW_TOTAL_SLOTS = 32;
 constexpr int ROW_TOTAL_STRIDE = 16;
 
+// Most workgroups of `threads` threads in one launch.  The runtime takes a grid's size in threads modulo 2^32 and reports
+// nothing (16 778 240 workgroups of 256 threads ran as 1024), so longer lists of rows go in several launches.
+constexpr int64_t most_blocks(int threads) { return 0xffffffffLL / threads; }
+
+// go(first, n): one launch for rows first .. first + n - 1 of a list of count rows, rows_per_block of them a workgroup.
+template <typename Go>
+inline void launch_in_pieces(int64_t count, int rows_per_block, int threads, Go go)
+{
+    const int64_t most = most_blocks(threads) * rows_per_block;
+    for (int64_t first = 0; first < count; first += most) go(first, count - first < most ? count - first : most);
+}
+
 // --------------------------------------------------- launcher prototypes ----
 // analysis.hip
 hipError_t launch_validate(const Csr &B, int32_t *flags, unsigned long long *near_pairs, hipStream_t s);

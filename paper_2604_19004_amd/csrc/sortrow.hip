@@ -336,9 +336,11 @@ static hipError_t dispatch_sort(const Csr &A, const Csr &B, const SortLaunch &l,
 #define OCEAN_SORT(CLS, G, PPT, THREADS)                                                                              \
     case CLS:                                                                                                        \
         static_assert(kSortClass[CLS].cap == G * PPT, "products of the class");                                       \
-        hipLaunchKernelGGL((k_numeric_sort<V, G, PPT, kSortClass[CLS].entries, THREADS>),                             \
-                           dim3((unsigned)((l.count + THREADS / G - 1) / (THREADS / G))), dim3(THREADS), 0, s, A.rp,    \
-                           A.col, av, B.rp, B.col, bv, l.rows, l.count, l.out_ptr, l.out_col, ov, l.row_nnz);          \
+        launch_in_pieces(l.count, THREADS / G, THREADS, [&](int64_t first, int64_t n) {                               \
+            hipLaunchKernelGGL((k_numeric_sort<V, G, PPT, kSortClass[CLS].entries, THREADS>),                         \
+                               dim3((unsigned)((n + THREADS / G - 1) / (THREADS / G))), dim3(THREADS), 0, s, A.rp,      \
+                               A.col, av, B.rp, B.col, bv, l.rows + first, n, l.out_ptr, l.out_col, ov, l.row_nnz);     \
+        });                                                                                                          \
         break
     switch (l.cls) {
         OCEAN_SORT(1, 8, 4, 256);

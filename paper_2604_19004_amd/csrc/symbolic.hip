@@ -374,8 +374,10 @@ hipError_t launch_symbolic_bin(const Csr &A, const Csr &B, const SymLaunch &l, i
     case SB_S32K: OCEAN_SYM_WG(15, 1024); break;
     case SB_SPAN:
         if (l.cmin == nullptr) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(k_symbolic_span, dim3((unsigned)l.count), dim3(SS_THREADS), 0, s, A.rp, A.col, B.rp, B.col, l.rows,
-                           l.count, l.cmin, nnz_out);
+        launch_in_pieces(l.count, 1, SS_THREADS, [&](int64_t first, int64_t n) {
+            hipLaunchKernelGGL(k_symbolic_span, dim3((unsigned)n), dim3(SS_THREADS), 0, s, A.rp, A.col, B.rp, B.col,
+                               l.rows + first, n, l.cmin, nnz_out);
+        });
         break;
     case SB_BITMAP: {
 #define OCEAN_SYM_BM(WORDS, ONE, QUERY)                                                                            \
