@@ -654,20 +654,24 @@ hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const 
     const bool spread = lanes_div == 1 && rows == nullptr;
     int g_log2 = ilog2_ceil(avg * L / (double)(spread ? 8 : lanes_div), 0, 6);   // (lanes_div: see launch_hll_sketch)
     while ((1 << g_log2) < L) ++g_log2;
-    const int64_t threads = n_rows << g_log2;
-    int64_t blocks = (threads + TPB - 1) / TPB;
     const uint64_t *sk = reinterpret_cast<const uint64_t *>(sketches);
     uint64_t *mg = reinterpret_cast<uint64_t *>(merged);
     const int64_t least = spread ? LONG_SKEWED : MG_LONG;
     const int64_t long_from = 8.0 * avg > (double)least ? (int64_t)(8.0 * avg) : least;
     const bool own_launch = spread && A.nnz >= (1 << 20);
-    const int n_long = own_launch ? -1 : spread && A.nnz >= long_from ? long_row_blocks(n_rows) : 0;
-    blocks += n_long > 0 ? n_long : 0;
-    switch (m) {
-    case 32: hipLaunchKernelGGL(k_hll_merge<32>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, n_long, prod, maxb, b_rp, b_cols, est, mg); break;
-    case 64: hipLaunchKernelGGL(k_hll_merge<64>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, n_long, prod, maxb, b_rp, b_cols, est, mg); break;
-    case 128: hipLaunchKernelGGL(k_hll_merge<128>, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, sk, rows, n_rows, g_log2, long_from, n_long, prod, maxb, b_rp, b_cols, est, mg); break;
-    default: return hipErrorInvalidValue;
+    const int rows_per_block = TPB >> g_log2;
+    const auto kernel = m == 32 ? k_hll_merge<32> : m == 64 ? k_hll_merge<64> : k_hll_merge<128>;
+    if (m != 32 && m != 64 && m != 128) return hipErrorInvalidValue;
+    // (pieces that leave room for the workgroups for long rows: see most_blocks)
+    const int64_t most = (most_blocks(TPB) - 1024) * rows_per_block;
+    for (int64_t t0 = 0; t0 < n_rows; t0 += most) {
+        const int64_t n = n_rows - t0 < most ? n_rows - t0 : most;
+        const int n_long = own_launch ? -1 : spread && A.nnz >= long_from ? long_row_blocks(n) : 0;
+        const int64_t blocks = (n + rows_per_block - 1) / rows_per_block + (n_long > 0 ? n_long : 0);
+        const int64_t r0 = rows ? 0 : t0;   // (without a list, slot t is row t: the rows' own arrays move along)
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp + r0, A.col, sk, rows ? rows + t0 : nullptr, n,
+                           g_log2, long_from, n_long, prod ? prod + r0 : nullptr, maxb ? maxb + r0 : nullptr, b_rp, b_cols,
+                           est + t0, mg ? mg + t0 * L : nullptr);
     }
     if (own_launch) {
         const int n = long_row_blocks(n_rows);

@@ -171,16 +171,18 @@ hipError_t launch_compact(int64_t m, int dtype, const int64_t *c_rp, const int32
                                static_cast<const float *>(val2), c_col, static_cast<float *>(c_val));
         return hipGetLastError();
     }
-    const int64_t threads = m << g_log2;
-    const int64_t blocks = (threads + 255) / 256;
-    if (dtype == OCEAN_F64)
-        hipLaunchKernelGGL(k_compact<double>, dim3((unsigned)blocks), dim3(256), 0, s, m, g_log2, c_rp, nnz1, ptr1, col1,
-                           static_cast<const double *>(val1), ptr2, col2, static_cast<const double *>(val2), c_col,
-                           static_cast<double *>(c_val));
-    else
-        hipLaunchKernelGGL(k_compact<float>, dim3((unsigned)blocks), dim3(256), 0, s, m, g_log2, c_rp, nnz1, ptr1, col1,
-                           static_cast<const float *>(val1), ptr2, col2, static_cast<const float *>(val2), c_col,
-                           static_cast<float *>(c_val));
+    const int rows_per_block = 256 >> g_log2;
+    launch_in_pieces(m, rows_per_block, 256, [&](int64_t first, int64_t n) {
+        const dim3 blocks((unsigned)((n + rows_per_block - 1) / rows_per_block));
+        if (dtype == OCEAN_F64)
+            hipLaunchKernelGGL(k_compact<double>, blocks, dim3(256), 0, s, n, g_log2, c_rp + first, nnz1 + first, ptr1 + first,
+                               col1, static_cast<const double *>(val1), ptr2 + first, col2, static_cast<const double *>(val2),
+                               c_col, static_cast<double *>(c_val));
+        else
+            hipLaunchKernelGGL(k_compact<float>, blocks, dim3(256), 0, s, n, g_log2, c_rp + first, nnz1 + first, ptr1 + first,
+                               col1, static_cast<const float *>(val1), ptr2 + first, col2, static_cast<const float *>(val2),
+                               c_col, static_cast<float *>(c_val));
+    });
     return hipGetLastError();
 }
 

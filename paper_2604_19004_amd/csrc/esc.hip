@@ -190,13 +190,15 @@ static hipError_t esc_dispatch(const Csr &A, const Csr &B, const EscLaunch &l, h
     const V *bv = static_cast<const V *>(B.val);
     V *ov = static_cast<V *>(l.out_val);
     if (l.lanes == 16) {
-        const int64_t blocks = (l.count + 15) / 16;
-        hipLaunchKernelGGL((k_numeric_esc<V, 16>), dim3((unsigned)blocks), dim3(256), 0, s, A.rp, A.col, av, B.rp, B.col, bv,
-                           l.rows, l.count, l.out_ptr, l.out_col, ov, l.row_nnz);
+        launch_in_pieces(l.count, 16, 256, [&](int64_t first, int64_t n) {
+            hipLaunchKernelGGL((k_numeric_esc<V, 16>), dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, A.rp, A.col, av, B.rp,
+                               B.col, bv, l.rows + first, n, l.out_ptr, l.out_col, ov, l.row_nnz);
+        });
     } else if (l.lanes == 32) {
-        const int64_t blocks = (l.count + 7) / 8;
-        hipLaunchKernelGGL((k_numeric_esc<V, 32>), dim3((unsigned)blocks), dim3(256), 0, s, A.rp, A.col, av, B.rp, B.col, bv,
-                           l.rows, l.count, l.out_ptr, l.out_col, ov, l.row_nnz);
+        launch_in_pieces(l.count, 8, 256, [&](int64_t first, int64_t n) {
+            hipLaunchKernelGGL((k_numeric_esc<V, 32>), dim3((unsigned)((n + 7) / 8)), dim3(256), 0, s, A.rp, A.col, av, B.rp,
+                               B.col, bv, l.rows + first, n, l.out_ptr, l.out_col, ov, l.row_nnz);
+        });
     } else {
         return hipErrorInvalidValue;
     }

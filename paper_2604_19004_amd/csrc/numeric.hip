@@ -1252,12 +1252,13 @@ hipError_t launch_window_table(const Csr &B, int dtype, uint32_t *bw, int *n_win
     const int n_win = (int)((B.cols + (1ll << win_log2) - 1) >> win_log2);
     *n_win_out = n_win;
     if (B.rows == 0) return hipSuccess;
-    const int64_t threads = B.rows * 16;
     // ("long" is relative: 1024 entries or eight times the average row, whichever is more)
     const double avg = (double)B.nnz / (double)B.rows;
     const int64_t long_from = 8.0 * avg > (double)WT_LONG ? (int64_t)(8.0 * avg) : (int64_t)WT_LONG;
-    hipLaunchKernelGGL(k_window_table, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, B.rp, B.col, B.rows,
-                       win_log2, n_win, long_from, bw, flags);
+    launch_in_pieces(B.rows, 16, 256, [&](int64_t first, int64_t n) {
+        hipLaunchKernelGGL(k_window_table, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, B.rp + first, B.col, n, win_log2,
+                           n_win, long_from, bw + (size_t)first * ((size_t)n_win + 1), flags);
+    });
     return hipGetLastError();
 }
 
@@ -1414,26 +1415,30 @@ static hipError_t dispatch(const Csr &A, const Csr &B, const NumLaunch &l, int /
     const V *bv = static_cast<const V *>(B.val);
     V *ov = static_cast<V *>(l.out_val);
 #define OCEAN_WG_BF(BITS, THREADS, BF)                                                                              \
-    hipLaunchKernelGGL((k_numeric_wg<V, BITS, THREADS, BF>), dim3((unsigned)l.count), dim3(THREADS), 0, s, A.rp, A.col, \
-                       av, B.rp, B.col, bv, l.rows, l.count, l.out_ptr, l.out_col, ov, l.row_nnz)
+    launch_in_pieces(l.count, 1, THREADS, [&](int64_t first, int64_t n) {                                           \
+        hipLaunchKernelGGL((k_numeric_wg<V, BITS, THREADS, BF>), dim3((unsigned)n), dim3(THREADS), 0, s, A.rp, A.col,   \
+                           av, B.rp, B.col, bv, l.rows + first, n, l.out_ptr, l.out_col, ov, l.row_nnz);            \
+    })
 #define OCEAN_WG(BITS, THREADS) OCEAN_WG_BF(BITS, THREADS, 1)
     switch (l.bin) {
     case NB_E16:
-    case NB_G8: {
-        const int64_t blocks = (l.count + 31) / 32;
-        hipLaunchKernelGGL((k_numeric_group<V, 8, 5>), dim3((unsigned)blocks), dim3(256), 0, s, A.rp, A.col, av, B.rp, B.col,
-                           bv, l.rows, l.count, l.out_ptr, l.out_col, ov, l.row_nnz);
+    case NB_G8:
+        launch_in_pieces(l.count, 32, 256, [&](int64_t first, int64_t n) {
+            hipLaunchKernelGGL((k_numeric_group<V, 8, 5>), dim3((unsigned)((n + 31) / 32)), dim3(256), 0, s, A.rp, A.col, av,
+                               B.rp, B.col, bv, l.rows + first, n, l.out_ptr, l.out_col, ov, l.row_nnz);
+        });
         break;
-    }
-    case NB_G16: {
-        const int64_t blocks = (l.count + 15) / 16;
-        hipLaunchKernelGGL((k_numeric_group<V, 16, 6>), dim3((unsigned)blocks), dim3(256), 0, s, A.rp, A.col, av, B.rp, B.col,
-                           bv, l.rows, l.count, l.out_ptr, l.out_col, ov, l.row_nnz);
+    case NB_G16:
+        launch_in_pieces(l.count, 16, 256, [&](int64_t first, int64_t n) {
+            hipLaunchKernelGGL((k_numeric_group<V, 16, 6>), dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, A.rp, A.col, av,
+                               B.rp, B.col, bv, l.rows + first, n, l.out_ptr, l.out_col, ov, l.row_nnz);
+        });
         break;
-    }
 #define OCEAN_WAVE(BITS, R)                                                                                        \
-    hipLaunchKernelGGL((k_numeric_wave<V, BITS, R>), dim3((unsigned)((l.count + (R) - 1) / (R))), dim3(WAVE * (R)), 0, s, A.rp, \
-                       A.col, av, B.rp, B.col, bv, l.rows, l.count, l.out_ptr, l.out_col, ov, l.row_nnz)
+    launch_in_pieces(l.count, R, WAVE * (R), [&](int64_t first, int64_t n) {                                         \
+        hipLaunchKernelGGL((k_numeric_wave<V, BITS, R>), dim3((unsigned)((n + (R) - 1) / (R))), dim3(WAVE * (R)), 0, s,  \
+                           A.rp, A.col, av, B.rp, B.col, bv, l.rows + first, n, l.out_ptr, l.out_col, ov, l.row_nnz); \
+    })
     case NB_W64: OCEAN_WAVE(8, 4); break;
     // a wave per row while the rows of the bin are light; a workgroup per row when they hold many products each
     // (a wave per row was measured for the 512- and 1024-slot bins too: 1.3 - 1.6 x slower than a workgroup per row)
@@ -1451,8 +1456,10 @@ static hipError_t dispatch(const Csr &A, const Csr &B, const NumLaunch &l, int /
     case NB_DSPAN:
         if (l.cmin == nullptr) return hipErrorInvalidValue;
 #define OCEAN_DSPAN(QUERY, COLS)                                                                                          \
-    hipLaunchKernelGGL((k_numeric_dspan<V, QUERY, COLS>), dim3((unsigned)l.count), dim3(DS_THREADS), 0, s, A.rp, A.col, av,    \
-                       B.rp, B.col, bv, l.rows, l.count, l.cmin, l.out_ptr, l.out_col, ov, l.row_nnz)
+    launch_in_pieces(l.count, 1, DS_THREADS, [&](int64_t first, int64_t n) {                                              \
+        hipLaunchKernelGGL((k_numeric_dspan<V, QUERY, COLS>), dim3((unsigned)n), dim3(DS_THREADS), 0, s, A.rp, A.col, av,      \
+                           B.rp, B.col, bv, l.rows + first, n, l.cmin, l.out_ptr, l.out_col, ov, l.row_nnz);              \
+    })
 #define OCEAN_DSPAN_COLS(QUERY)                                                                                           \
     do {                                                                                                                  \
         if (l.span_cols <= 1024) OCEAN_DSPAN(QUERY, 1024);                                                                \

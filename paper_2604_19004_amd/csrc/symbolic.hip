@@ -344,29 +344,26 @@ hipError_t launch_symbolic_bin(const Csr &A, const Csr &B, const SymLaunch &l, i
     if (l.count <= 0) return hipSuccess;
 #define OCEAN_SYM_WG(BITS, THREADS)                                                                               \
     do {                                                                                                          \
-        if (l.may_overflow)                                                                                       \
-            hipLaunchKernelGGL((k_symbolic_wg<BITS, THREADS, true>), dim3((unsigned)l.count), dim3(THREADS), 0, s,  \
-                               A.rp, A.col, B.rp, B.col, l.rows, l.count, nnz_out);                               \
-        else                                                                                                      \
-            hipLaunchKernelGGL((k_symbolic_wg<BITS, THREADS, false>), dim3((unsigned)l.count), dim3(THREADS), 0, s, \
-                               A.rp, A.col, B.rp, B.col, l.rows, l.count, nnz_out);                               \
+        launch_in_pieces(l.count, 1, THREADS, [&](int64_t first, int64_t n) {                                     \
+            const auto kernel = l.may_overflow ? k_symbolic_wg<BITS, THREADS, true> : k_symbolic_wg<BITS, THREADS, false>; \
+            hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(THREADS), 0, s, A.rp, A.col, B.rp, B.col,            \
+                               l.rows + first, n, nnz_out);                                                       \
+        });                                                                                                       \
     } while (0)
     switch (l.bin) {
     case SB_G16:
-        if (l.may_overflow)
-            hipLaunchKernelGGL(k_symbolic_group<true>, dim3((unsigned)((l.count + 15) / 16)), dim3(256), 0, s, A.rp, A.col,
-                               B.rp, B.col, l.rows, l.count, nnz_out);
-        else
-            hipLaunchKernelGGL(k_symbolic_group<false>, dim3((unsigned)((l.count + 15) / 16)), dim3(256), 0, s, A.rp, A.col,
-                               B.rp, B.col, l.rows, l.count, nnz_out);
+        launch_in_pieces(l.count, 16, 256, [&](int64_t first, int64_t n) {
+            const auto kernel = l.may_overflow ? k_symbolic_group<true> : k_symbolic_group<false>;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, A.rp, A.col, B.rp, B.col,
+                               l.rows + first, n, nnz_out);
+        });
         break;
     case SB_W64:
-        if (l.may_overflow)
-            hipLaunchKernelGGL(k_symbolic_wave<true>, dim3((unsigned)((l.count + 3) / 4)), dim3(256), 0, s, A.rp, A.col, B.rp,
-                               B.col, l.rows, l.count, nnz_out);
-        else
-            hipLaunchKernelGGL(k_symbolic_wave<false>, dim3((unsigned)((l.count + 3) / 4)), dim3(256), 0, s, A.rp, A.col, B.rp,
-                               B.col, l.rows, l.count, nnz_out);
+        launch_in_pieces(l.count, 4, 256, [&](int64_t first, int64_t n) {
+            const auto kernel = l.may_overflow ? k_symbolic_wave<true> : k_symbolic_wave<false>;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, A.rp, A.col, B.rp, B.col,
+                               l.rows + first, n, nnz_out);
+        });
         break;
     case SB_S1K: OCEAN_SYM_WG(10, 64); break;    // (rect: 64 threads 0.68 ms, 128 0.76, 256 1.08 for the whole stage)
     case SB_S4K: OCEAN_SYM_WG(12, 256); break;   // (clustered: 256 threads 1.16 ms, 128 1.23, 512 1.40)

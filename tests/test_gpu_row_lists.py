@@ -3,6 +3,7 @@ holds fewer.  Rows repeat every 64, so the CPU oracle multiplies the first 64 an
 import numpy as np
 import pytest
 
+from oracle import hll as ohll
 from oracle import spgemm as O
 from paper_2604_19004_amd.workloads import CSR
 
@@ -20,12 +21,22 @@ def ob():
     return binding
 
 
-# sorted rows: 64 lanes each from 257 products on; rows counted over their column range: 256 threads each
-@pytest.mark.parametrize("kernel, rows, length, n", [("sort", (1 << 26) + 1024, 33, 40), ("span", (1 << 24) + 1024, 26, 300)])
-def test_more_rows_than_one_launch_takes(ob, kernel, rows, length, n):
+TWO_PASSES = dict(workflow=3, dense_range=0)   # WF_SYMBOLIC
+CASES = {                                      # rows, entries of A, entries of B, columns, options
+    "sort": ((1 << 26) + 1024, 8, 33, 40, TWO_PASSES),                                     # 64 threads a row from 257 products on
+    "symbolic span": ((1 << 24) + 1024, 8, 26, 300, dict(TWO_PASSES, dense_range=2)),      # 256 threads a row
+    "256-slot tables": ((1 << 26) + 1024, 8, 33, 60, dict(TWO_PASSES, force_hash_kernels=1)),   # 64, both passes
+    "1024-slot tables": ((1 << 24) + 1024, 2, 240, 1000, dict(TWO_PASSES, force_hash_kernels=1)),   # 256
+    "dense range": ((1 << 24) + 1024, 2, 130, 300, dict(TWO_PASSES, dense_range=2)),       # 256
+    "compaction": ((1 << 26) + 1024, 8, 33, 40, dict(workflow=1)),                         # 64, output of the upper bound
+}
+
+
+@pytest.mark.parametrize("kernel", CASES)
+def test_more_rows_than_one_launch_takes(ob, kernel):
     import torch
+    rows, entries, length, n, options = CASES[kernel]
     rng = np.random.default_rng(length)
-    entries = 8
     b_col = np.concatenate([np.sort(rng.choice(n, length, replace=False)) for _ in range(PERIOD)]).astype(np.int32)
     B = CSR(PERIOD, n, np.arange(PERIOD + 1, dtype=np.int64) * length, b_col, rng.uniform(-1, 1, b_col.size).astype(np.float32))
     head_col = ((np.arange(PERIOD)[:, None] + np.arange(entries)[None, :] % 2) % PERIOD).astype(np.int32).reshape(-1)
@@ -36,9 +47,14 @@ def test_more_rows_than_one_launch_takes(ob, kernel, rows, length, n):
     dA = ob.DeviceCSR(rows, PERIOD, torch.arange(rows + 1, dtype=torch.int64, device="cuda:0") * entries,
                       torch.from_numpy(head_col).cuda().repeat(rows // PERIOD), torch.from_numpy(head.val).cuda().repeat(rows // PERIOD))
     print(f"{kernel}: {rows} rows of {entries * length} products", flush=True)
-    Cd, st = ob.spgemm(dA, ob.to_device(B), workflow=ob.WF_SYMBOLIC, dense_range=2 if kernel == "span" else 0)
-    if kernel == "span":
-        assert st["symbolic_rows_per_bin"][len(ob.bin_layout()[1])] == rows
+    Cd, st = ob.spgemm(dA, ob.to_device(B), **options)
+    slots, keys = ob.bin_layout()
+    if kernel == "symbolic span":
+        assert st["symbolic_rows_per_bin"][len(keys)] == rows
+    elif kernel == "dense range":
+        assert st["rows_per_bin"][len(slots)] == rows
+    elif kernel.endswith("tables"):
+        assert st["rows_per_bin"][slots.index(int(kernel.split("-")[0]))] > rows // 2
     assert st["nnz_c"] == per * (rows // PERIOD) and int(Cd.row_ptr[-1]) == st["nnz_c"]
     starts = Cd.row_ptr[:-1].view(-1, PERIOD)
     first = torch.arange(rows // PERIOD, device="cuda:0")[:, None] * per + torch.from_numpy(ref.row_ptr[:-1]).cuda()
@@ -49,4 +65,27 @@ def test_more_rows_than_one_launch_takes(ob, kernel, rows, length, n):
         assert bool((col[at:at + (1 << 16)] == want_col).all()), f"columns from period {at} on"
         assert bool(((val[at:at + (1 << 16)].double() - want).abs() <= bound).all()), f"values from period {at} on"
     del dA, Cd, col, val, starts, first
+    torch.cuda.empty_cache()
+
+
+def test_more_estimates_than_one_launch_takes(ob):
+    """Sketches of 64 registers merged along listed rows of 8 entries: 64 threads a row."""
+    import torch
+    rng = np.random.default_rng(3)
+    rows, entries, n, m = (1 << 26) + 1024, 8, 5000, 64
+    lengths = rng.integers(0, 60, PERIOD)
+    b_ptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    B = CSR(PERIOD, n, b_ptr, np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lengths]).astype(np.int32),
+            rng.uniform(-1, 1, int(b_ptr[-1])).astype(np.float32))
+    head_col = rng.integers(0, PERIOD, PERIOD * entries).astype(np.int32)
+    head = CSR(PERIOD, PERIOD, np.arange(PERIOD + 1, dtype=np.int64) * entries, head_col, np.ones(head_col.size, np.float32))
+    sketches = ohll.sketch_rows(B, m)
+    want = torch.from_numpy(ohll.estimate(ohll.merge_rows(head, sketches))).cuda()
+    dA = ob.DeviceCSR(rows, PERIOD, torch.arange(rows + 1, dtype=torch.int64, device="cuda:0") * entries,
+                      torch.from_numpy(head_col).cuda().repeat(rows // PERIOD), torch.ones(rows * entries, device="cuda:0"))
+    dS = torch.from_numpy(sketches).cuda()
+    print(f"{rows} estimates", flush=True)
+    est, _ = ob.hll_merge_estimate(dA, dS, m, rows=torch.arange(rows, dtype=torch.int64, device="cuda:0"))
+    assert bool(((est.view(-1, PERIOD) - want).abs() <= 1e-12 * want).all())
+    del dA, est
     torch.cuda.empty_cache()
