@@ -327,7 +327,8 @@ int zero_bins(Ctx &c, Work &w)
 // ---- analysis: validation + products per row ------------------------------------------------------
 int run_analysis(Ctx &c, Work &w, const Csr &A, const Csr &B, bool validate, ocean_stats *st)
 {
-    const bool same = B.rp == A.rp && B.col == A.col && B.rows == A.rows && B.cols == A.cols;
+    // (the same arrays under another number of entries are two matrices, of which one is not valid)
+    const bool same = B.rp == A.rp && B.col == A.col && B.rows == A.rows && B.cols == A.cols && B.nnz == A.nnz;
     if (validate && !same) HIP_TRY(launch_validate(B, &w.sc->flags, w.sc->near_pairs, c.s));
     HIP_TRY(launch_row_products(A, B.rp, B.rows, w.prod, w.maxb, w.sc->row_totals, &w.sc->flags, validate,
                                 validate && same ? w.sc->near_pairs : nullptr, c.s));

@@ -919,3 +919,15 @@ def test_malformed_row_offsets_are_rejected(ob, bad_rp):
         ob.row_products(dA, dB)
     assert e.value.code == 1
 
+
+@pytest.mark.parametrize("fewer", ["A", "B"])
+def test_one_matrix_under_two_numbers_of_entries_is_rejected(ob, fewer):
+    """The same arrays as A and as B, one of them with an entry less than its row offsets say: not a valid matrix, though
+    the input check looks at arrays that both share only once."""
+    dA = ob.to_device(_csr(3, 3, [0, 2, 3, 5], [0, 2, 1, 0, 1], [1., 2., 3., 4., 5.]))
+    short = ob.DeviceCSR(3, 3, dA.row_ptr, dA.col_idx[:4], dA.val[:4])
+    pair = (short, dA) if fewer == "A" else (dA, short)
+    for call in (ob.spgemm, ob.symbolic):
+        with pytest.raises(ob.OceanError) as e:
+            call(*pair)
+        assert e.value.code == 1 and f"{fewer} is not a valid CSR" in str(e.value)
