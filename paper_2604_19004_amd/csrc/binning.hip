@@ -39,8 +39,11 @@ struct BinTable {
 // Sorting costs what the products cost, a hash table what its slots and the products cost, so a row whose many
 // products fall on few columns is left to its small table.  Measured, ns per row, fp64, whole numeric stage of 200 000
 // equal rows: no merging (table of 1.15 slots per product) 49 products 0.6 sorted / 0.7 hashed, 225 1.6 / 2.7, 484 2.9 /
-// 5.3, 961 5.3 / 13.0, 1444 7.9 / 17, 1936 12.1 / 26; 408 products on 103 columns 1.8 / 2.8, 707 on 180 3.1 / 4.1, but
-// 1090 on 129 (256 slots) 5.1 / 4.3 and 1682 on 281 (512 slots) 8.5 / 6.4.
+// 5.3, 961 5.3 / 13.0, 1444 7.9 / 17, 1936 12.1 / 26; 408 products on 103 columns 1.8 / 2.8, 707 on 180 3.1 / 4.1; tables
+// of 512 slots: 800 products on 205 columns 3.3 / 3.0, 896 on 286 3.3 / 3.3, 1024 on 294 3.4 / 3.4, but 1090 on 129 (256
+// slots) 5.1 / 4.3 and 1682 on 281 (512 slots) 8.5 / 6.4: with up to 512 slots the line lies at 1024 products.
+// Rows of at most 1024 products in small tables are cheaper hashed as well; whether they are is decided for the class,
+// from the bins of its rows (see run_numeric).
 __device__ __forceinline__ int sort_class(long long pr, long long ne, int bin, unsigned mask)
 {
     const int most = bin <= NB_S512 ? 1024 : 2048;

@@ -467,41 +467,79 @@ int run_numeric(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int gb_l
     // those of the next one that has rows (their lists are adjacent) where sorting them at its size costs less than
     // the launch it saves, 6 us with its event: a power-law matrix of 16 384 rows has a few hundred rows in each
     // of the twelve classes (0.91 ms a call with a launch for each, 0.86 before there were any).
+    // Sorting costs what the products cost, a hash table what its slots and the products cost, so a class whose rows merge
+    // into few columns, which shows in small tables, goes to the smallest table that holds nine tenths of it, where that
+    // saves more than the launch, 16 us (the rows of larger tables, the end of the class's list, are sorted).  The class decides and not
+    // the row, because sizes may be estimates: a few rows in tables of their own, some of them too small, cost a launch
+    // and a retry (band of 17 diagonals, 289 products on 33 columns: 0.56 ms by class, 0.66 by row).  Measured, ns
+    // per row, fp64 (fp32 within 6 percent), numeric stage of 200 000 to 500 000 equal rows, products on columns,
+    // sorted / hashed, for the first table that is cheaper and the one above:
+    //   64, 96   48 on 15 0.21 / 0.17     48 on 23 0.22 / 0.28     128       128 on 19 0.37 / 0.30    128 on 27 0.38 / 0.39
+    //   192      192 on 19 0.56 / 0.45    192 on 35 0.59 / 0.65    256       256 on 19 0.73 / 0.56    256 on 35 0.77 / 0.79
+    //   384      384 on 32 1.09 / 0.79    384 on 47 1.10 / 1.35    512       512 on 32 1.38 / 0.94    512 on 63 1.43 / 1.50
+    //   768      640 on 95 2.32 / 1.82    768 on 204 2.41 / 3.05   1024      1024 on 95 3.24 / 2.33   1024 on 294 3.38 / 3.44
+    //   1536     1376 on 498 6.00 / 5.19  1376 on 724 6.28 / 9.57  2048      1984 on 529 9.33 / 5.72  1984 on 833 9.56 / 10.13
     // A launch's time is reported under the bin that holds most of its products.
     auto run_sorted = [&]() -> int {
-        constexpr int64_t LAUNCH_PS = 6000000;
+        constexpr int64_t LAUNCH_PS = 6000000, TABLE_LAUNCH_PS = 16000000;
         int64_t first = start[NB_ALL], rows = 0, own_ps = 0;
+        int cls = 0;   // of the rows that wait
         unsigned long long prod_of[OCEAN_MAX_BINS] = {};
-        for (int cls = 1; cls < SORT_CLASSES; ++cls) {
-            int64_t n = 0;
-            for (int b = 0; b < OCEAN_MAX_BINS; ++b) {
-                n += (int64_t)count[cls * OCEAN_MAX_BINS + b];
-                prod_of[b] += bin_prod[cls * OCEAN_MAX_BINS + b];
-            }
-            rows += n;
-            own_ps += n * kSortClass[cls].ps;
-            if (n == 0) continue;   // (rows of smaller classes wait for a class that has some of its own)
-            int next = cls + 1;
-            auto empty = [&](int k) {
-                for (int b = 0; b < OCEAN_MAX_BINS; ++b)
-                    if (count[k * OCEAN_MAX_BINS + b]) return false;
-                return true;
-            };
-            while (next < SORT_CLASSES && empty(next)) ++next;
-            if (next < SORT_CLASSES && rows * kSortClass[next].ps - own_ps < LAUNCH_PS) continue;
-            if (time_bins) {
-                int most = 0;
-                for (int b = 1; b < OCEAN_MAX_BINS; ++b)
-                    if (prod_of[b] > prod_of[most]) most = b;
-                c.bin_ev.emplace_back(most, (int)c.ev.size());
-                OC_TRY(mark(c, stage));
-            }
+        auto mark_most = [&](const unsigned long long *prod) -> int {
+            if (!time_bins) return OCEAN_OK;
+            int most = 0;
+            for (int b = 1; b < OCEAN_MAX_BINS; ++b)
+                if (prod[b] > prod[most]) most = b;
+            c.bin_ev.emplace_back(most, (int)c.ev.size());
+            return mark(c, stage);
+        };
+        auto sort_waiting = [&]() -> int {
+            if (rows == 0) return OCEAN_OK;
+            OC_TRY(mark_most(prod_of));
             HIP_TRY(launch_numeric_sort(A, B, dtype, SortLaunch{w.bin_rows + first, rows, cls, out_ptr, out_col, out_val, row_nnz}, c.s));
             first += rows;
             rows = own_ps = 0;
             for (unsigned long long &p : prod_of) p = 0;
+            return OCEAN_OK;
+        };
+        for (int k = 1; k < SORT_CLASSES; ++k) {
+            const unsigned long long *n_of = count + k * OCEAN_MAX_BINS, *p_of = bin_prod + k * OCEAN_MAX_BINS;
+            int64_t n = 0;
+            for (int b = 0; b < OCEAN_MAX_BINS; ++b) n += (int64_t)n_of[b];
+            if (n == 0) continue;   // (rows of smaller classes wait for a class that has some of its own)
+            // sorting the rows that wait with this class's must cost less than a launch of their own
+            if (rows > 0 && rows * kSortClass[k].ps - own_ps >= LAUNCH_PS) OC_TRY(sort_waiting());
+            int64_t in_table = 0;
+            int table = 0;
+            while (table <= kSortClass[k].table_bin && in_table * 10 < n * 9) in_table += (int64_t)n_of[table++];
+            --table;
+            int taken = 0;   // bins of this class that went to the table
+            if (in_table * 10 >= n * 9 && in_table * kSortClass[k].table_ps > TABLE_LAUNCH_PS) {
+                OC_TRY(sort_waiting());
+                taken = table + 1;
+                unsigned long long prod[OCEAN_MAX_BINS] = {};
+                std::memcpy(prod, p_of, sizeof(*p_of) * taken);
+                OC_TRY(mark_most(prod));
+                NumLaunch l{};
+                l.rows = w.bin_rows + first;
+                l.count = in_table;
+                l.bin = table;
+                l.out_ptr = out_ptr;
+                l.out_col = out_col;
+                l.out_val = out_val;
+                l.row_nnz = row_nnz;
+                l.coef = global_coef;
+                l.fine_buckets = c.fine_buckets;
+                HIP_TRY(launch_numeric_bin(A, B, dtype, l, gb_log2, c.s));
+                first += in_table;
+                n -= in_table;
+            }
+            for (int b = taken; b < OCEAN_MAX_BINS; ++b) prod_of[b] += p_of[b];
+            rows += n;
+            own_ps += n * kSortClass[k].ps;
+            if (n > 0) cls = k;
         }
-        return OCEAN_OK;
+        return sort_waiting();
     };
     // (slots from NB_ALL on: the dense-range bin's classes, whose lists follow those of the sort classes)
     int64_t dspan_at = start[NB_ALL];

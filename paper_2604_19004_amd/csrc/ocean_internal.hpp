@@ -65,11 +65,14 @@ __host__ __device__ inline bool dense_span_pays(long long span, long long slots,
 // Rows of few products are accumulated by sorting them (sortrow.hip) instead of through their bin's hash table.  A
 // sort class takes rows of at most `cap` intermediate products and `entries` entries of A.
 // ps: picoseconds a row of the class costs where there are many (fp64, one MI355X; see sort_class).
-struct SortClass { int cap, entries, ps; };
+// table_bin, table_ps: the largest hash bin whose table takes a row of the class in less time than sorting it (0: none), and
+// the picoseconds it saves: rows whose products fall on few columns (see run_numeric).
+struct SortClass { int cap, entries, ps, table_bin, table_ps; };
 constexpr int SORT_CLASSES = 13;            // class 0: not sorted, the bin's own kernel
 constexpr SortClass kSortClass[SORT_CLASSES] = {
-    {0, 0, 0}, {32, 32, 400}, {64, 64, 600}, {96, 64, 800}, {128, 64, 1000}, {192, 64, 1300}, {256, 64, 1600},
-    {384, 64, 2300}, {512, 64, 2900}, {768, 64, 4100}, {1024, 64, 5300}, {1536, 64, 7900}, {2048, 64, 12100}};
+    {0, 0, 0, 0, 0}, {32, 32, 400, 0, 0}, {64, 64, 600, NB_G8, 40}, {96, 64, 800, NB_G8, 50}, {128, 64, 1000, NB_G8, 70},
+    {192, 64, 1300, NB_G8, 150}, {256, 64, 1600, NB_G8, 200}, {384, 64, 2300, NB_G16, 300}, {512, 64, 2900, NB_G16, 400},
+    {768, 64, 4100, NB_W64, 500}, {1024, 64, 5300, NB_W64, 900}, {1536, 64, 7900, NB_S1K, 600}, {2048, 64, 12100, NB_S1K, 2500}};
 // Rows of the dense-range bin (NB_DSPAN below) whose range is at most kDspanCols[d] columns form a class of their own.
 constexpr int DSPAN_CLASSES = 2;
 constexpr int kDspanCols[DSPAN_CLASSES] = {1024, 2048};

@@ -73,3 +73,51 @@ def test_sorted_rows_at_the_edges_of_the_classes(ob, n, dtype, shuffle_b):
         Cd, st = ob.spgemm(dA, dB, **kw)
         check_result(Cd, ref, A, f"n={n} {kw}")
         assert sum(st["rows_per_bin"]) == int((O.row_products(A, B) > 0).sum())
+
+
+# Rows per class from which its smallest tables are worth a launch, and columns that fill the largest table that is cheaper
+# than sorting (tables ask for 1.5 slots per entry: 32, 64, 256 and 1024 slots).
+MANY = {64: (420000, 20), 96: (330000, 20), 128: (240000, 20), 192: (112000, 20), 256: (84000, 20), 384: (56000, 40), 512: (42000, 40),
+        768: (34000, 160), 1024: (19000, 160), 1536: (28000, 600), 2048: (7000, 600)}
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("width", [10, None], ids=["10 columns", "largest table"])
+def test_classes_whose_products_fall_on_few_columns(ob, width, dtype):
+    """Classes of so many rows on few columns that nearly all of them go to hash tables, and among them one row in thirty
+    whose products hardly merge, which is sorted.  Rows repeat, so the oracle multiplies each kind once."""
+    rng = np.random.default_rng(width or 1)
+    n = 5000
+    b_rows, kinds, per_kind = [], [], []
+    for cap, (many, widest) in MANY.items():
+        columns = width or widest
+        step = max(1, -(-cap // 60))                 # entries of B's rows, 60 of A's rows at most
+        first = len(b_rows)
+        for at in range(64):                         # few columns: the same ones over and over
+            b_rows.append(np.sort((at * step + np.arange(min(step, columns))) % columns) * (n // columns))
+        for at in range(64):                         # hardly any merge
+            b_rows.append(np.sort(rng.choice(n, step, replace=False)))
+        length = min(step, columns)
+        for low, share in ((0, 29), (64, 1)):
+            entries = min(64, cap // (length if low == 0 else step))
+            for kind in range(3):
+                kinds.append(first + low + (np.arange(entries) + 7 * kind) % 64)
+                per_kind.append(many * share // 90 + 1)
+    order = rng.permutation(np.repeat(np.arange(len(kinds)), per_kind))
+    B = _matrix(rng, b_rows, n, dtype)
+    head = _matrix(rng, kinds, len(b_rows), dtype)
+    ref = O.multiply_rows(head, B)
+
+    def repeated(ptr, *arrays):
+        lengths = np.diff(ptr)[order]
+        out = np.concatenate([[0], np.cumsum(lengths)])
+        at = np.repeat(ptr[:-1][order] - out[:-1], lengths) + np.arange(out[-1])
+        return (out, *(x[at] for x in arrays))
+    a_ptr, a_col, a_val = repeated(head.row_ptr, head.col_idx, head.val)
+    c_ptr, c_col, c_val, c_abs = repeated(ref.row_ptr, ref.col_idx, ref.val, ref.absval)
+    A = CSR(order.size, len(b_rows), a_ptr, a_col, a_val)
+    whole = type(ref)(0, A.rows, c_ptr, c_col, c_val, c_abs)
+    dA, dB = ob.to_device(A), ob.to_device(B)
+    for kw in (dict(workflow=ob.WF_SYMBOLIC), dict(workflow=ob.WF_HLL), dict(workflow=ob.WF_HLL, estimate_scale=0.6)):
+        Cd, st = ob.spgemm(dA, dB, **kw)
+        check_result(Cd, whole, A, f"{width} columns {kw}")
