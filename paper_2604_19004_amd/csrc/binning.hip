@@ -136,7 +136,13 @@ k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coe
                 // it needs no more memory than the hash table the row would get
                 const long long span = (long long)cmax[i] - (long long)cmin[i] + 1;
                 if (mode == 3) {
-                    if (span > 0 && span <= DS_MAX_COLS && bin > SB_W64) bin = SB_SPAN;
+                    // A bitmap of 4096 columns costs a workgroup per row whatever the row, so rows of few products are
+                    // cheaper in a key table (see run_symbolic for what becomes of them).  Predict stage of 200 000 rows, us,
+                    // bitmap / keys: 512 products on 800 columns 321 / 215, 768 330 / 289, 800 334 / 324, 832 (4096 keys)
+                    // 332 / 376, 2500 547 / 707; on 1500 columns 640 328 / 299, 768 331 / 334; on 400 columns, 1024 keys,
+                    // 1280 399 / 381, 1536 408 / 436.
+                    if (span > 0 && span <= DS_MAX_COLS && bin > SB_W64)
+                        bin = bin == SB_S1K && pr <= (span > 512 ? 768 : 1280) ? SB_SPAN_FEW : SB_SPAN;
                 } else if (dense_span_pays(span, (long long)bt.slots[bin], vbytes)) {
                     bin = NB_DSPAN;
                     for (int d = DSPAN_CLASSES - 1; d >= 0; --d)

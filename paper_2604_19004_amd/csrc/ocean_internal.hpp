@@ -43,9 +43,11 @@ enum SymbolicBin {
     SB_BITMAP,    // LDS bitmap over column windows
     SB_COUNT
 };
-// (after the bins of ocean_bin_layout) rows whose column range is known and at most DS_MAX_COLS columns: a bitmap over it
+// (after the bins of ocean_bin_layout) rows whose column range is known and at most DS_MAX_COLS columns: a bitmap over it;
+// then those of them with so few products that a table of 1024 keys is cheaper
 constexpr int SB_SPAN = SB_COUNT;
-constexpr int SB_ALL = SB_COUNT + 1;
+constexpr int SB_SPAN_FEW = SB_COUNT + 1;
+constexpr int SB_ALL = SB_COUNT + 2;
 constexpr int32_t kSymbolicSlots[SB_COUNT] = {64, 256, 1024, 4096, 16384, 32768, 0x7fffffff};
 
 constexpr int32_t BIN_NONE = 255;          // row takes no part in this launch set
@@ -270,7 +272,7 @@ struct BinParams {
                          // at most 1.0 = the product bound itself)
     const int32_t *cmin; // per row: first and last column the row can reach (k_row_spans), or null: rows whose range
     const int32_t *cmax; // pays for it go to the dense-range bin NB_DSPAN (modes 0, 1, 2), rows whose range is at most
-                         // DS_MAX_COLS columns and that need more than 256 keys to SB_SPAN (mode 3)
+                         // DS_MAX_COLS columns and that need more than 256 keys to SB_SPAN or SB_SPAN_FEW (mode 3)
     int vbytes;          // bytes of a value (with cmin)
     unsigned sort_mask;  // sort classes that may be used (bit c; modes 0, 1, 2), 0: none
     const int64_t *a_rp; // row offsets of A (with sort_mask or work sums)

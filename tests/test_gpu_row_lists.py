@@ -24,7 +24,7 @@ def ob():
 TWO_PASSES = dict(workflow=3, dense_range=0)   # WF_SYMBOLIC
 CASES = {                                      # rows, entries of A, entries of B, columns, options
     "sort": ((1 << 26) + 1024, 8, 33, 40, TWO_PASSES),                                     # 64 threads a row from 257 products on
-    "symbolic span": ((1 << 24) + 1024, 8, 26, 300, dict(TWO_PASSES, dense_range=2)),      # 256 threads a row
+    "symbolic span": ((1 << 24) + 1024, 8, 97, 600, dict(TWO_PASSES, dense_range=2)),      # 256 threads a row
     "256-slot tables": ((1 << 26) + 1024, 8, 33, 60, dict(TWO_PASSES, force_hash_kernels=1)),   # 64, both passes
     "1024-slot tables": ((1 << 24) + 1024, 2, 240, 1000, dict(TWO_PASSES, force_hash_kernels=1)),   # 256
     "dense range": ((1 << 24) + 1024, 2, 130, 300, dict(TWO_PASSES, dense_range=2)),       # 256

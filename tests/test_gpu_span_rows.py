@@ -58,3 +58,29 @@ def test_rows_over_their_own_column_range(ob, n, dtype, shuffle_b):
             assert st["rows_per_bin"][nb] > 0 and st["overflow_rows"] == 0
             if kw["workflow"] == ob.WF_SYMBOLIC:
                 assert st["symbolic_rows_per_bin"][ns] == 9 * 30
+
+
+@pytest.mark.parametrize("few", [199, 201])
+@pytest.mark.parametrize("span, line", [(500, 1280), (513, 768), (700, 768)])
+def test_rows_on_both_sides_of_the_bitmaps_line(ob, span, line, few):
+    """Rows of one product less than, as many as and one more than a range of so many columns needs to be cheaper by a bitmap,
+    in a matrix of as many columns: 1024 keys hold any row, so the products alone decide.  The few products are counted
+    with key tables where those rows are four fifths of all, by bitmaps otherwise."""
+    rng = np.random.default_rng(span)
+    b_rows = [np.array([7])] * 20
+    b_rows += [np.concatenate([[0], np.sort(rng.choice(span - 2, 62, replace=False)) + 1, [span - 1]]) for _ in range(20)]
+    totals = [line + 1] * 50 + [line - 1, line] * (few // 2) + [line] * (few % 2)
+    a_rows = [np.concatenate([rng.integers(0, 20, t % 64), rng.integers(20, 40, t // 64)]) for t in rng.permutation(totals)]
+
+    def csr(rows, cols):
+        ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64)
+        idx = np.concatenate(rows).astype(np.int32)
+        return CSR(len(rows), cols, ptr, idx, rng.uniform(-1, 1, idx.size))
+    A, B = csr(a_rows, len(b_rows)), csr(b_rows, span)
+    ref = O.multiply_rows(A, B)
+    Cd, st = ob.spgemm(ob.to_device(A), ob.to_device(B), workflow=ob.WF_SYMBOLIC, dense_range=2)
+    check_result(Cd, ref, A, f"span {span}")
+    slots, keys = ob.bin_layout()
+    by_keys = few if few >= 4 * 50 else 0
+    assert st["symbolic_rows_per_bin"][keys.index(1024)] == by_keys
+    assert st["symbolic_rows_per_bin"][len(keys)] == 50 + few - by_keys
