@@ -53,3 +53,30 @@ def test_long_rows_side_by_side(ob, rows, long_lengths, m):
 def _all_rows(n):
     import torch
     return torch.arange(n, dtype=torch.int64, device="cuda:0")
+
+
+@pytest.mark.parametrize("m", [32, 64, 128])
+def test_long_rows_of_a_large_matrix(ob, m):
+    """2^20 entries and more: the long rows are merged by a launch of their own, 1024 threads a row.  Estimates bare, and
+    limited by the products and the longest row of B."""
+    import torch
+    rng = np.random.default_rng(m)
+    n = 40000
+    lengths = rng.integers(0, 52, n)
+    lengths[:12] = [255, 256, 257, 4095, 4096, 4097, 30000, 1024, 1023, 300, 0, 40000]      # side by side, and
+    lengths[[4096, 8192, 20000, n - 1]] = [5000, 257, 256, 2000]                             # at the ends of stretches
+    ptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    assert ptr[-1] >= 1 << 20 and 8 * ptr[-1] / n < 256
+    idx = np.concatenate([np.sort(rng.choice(n, k, replace=False)) if k > 52 else rng.integers(0, n, k) for k in lengths]).astype(np.int32)
+    A = CSR(n, n, ptr, idx, np.ones(idx.size))
+    dA = ob.to_device(A)
+    ref_sk = ohll.sketch_rows(A, m)
+    sk = ob.hll_sketch_rows(dA, m)
+    assert np.array_equal(sk.cpu().numpy(), ref_sk)
+    ref_merged = ohll.merge_rows(A, ref_sk)
+    est, merged = ob.hll_merge_estimate(dA, sk, m, want_merged=True)
+    assert np.array_equal(merged.cpu().numpy(), ref_merged)
+    np.testing.assert_allclose(est.cpu().numpy(), ohll.estimate(ref_merged), rtol=1e-12, atol=0)
+    prod = torch.from_numpy(O.row_products(A, A)).cuda()
+    est = ob.hll_merge_estimate(dA, sk, m, prod=prod, B=dA)[0]
+    np.testing.assert_allclose(est.cpu().numpy(), ohll.estimate_rows(A, A, m), rtol=1e-12, atol=0)

@@ -760,8 +760,11 @@ def test_esc_short_rows(ob, seed, dtype):
     Cd, st = ob.spgemm(dA, dB, workflow=ob.WF_UPPER_BOUND, esc_short_rows=1)
     check_result(Cd, ref, A, f"esc seed {seed}")
     assert st["rows_per_bin"][0] > 0 and st["rows_per_bin"][1] > 0
-    Cd, st = ob.spgemm(dA, dB, workflow=ob.WF_UPPER_BOUND, esc_short_rows=0)          # the hash kernels on the same bins
+    Cd, st = ob.spgemm(dA, dB, workflow=ob.WF_UPPER_BOUND, esc_short_rows=0)          # sorted, several products per lane
     check_result(Cd, ref, A, f"esc off seed {seed}")
+    Cd, st = ob.spgemm(dA, dB, workflow=ob.WF_UPPER_BOUND, esc_short_rows=0, force_hash_kernels=1)   # hash kernels, same bins
+    check_result(Cd, ref, A, f"esc off, hash kernels seed {seed}")
+    assert st["rows_per_bin"][0] > 0 and st["rows_per_bin"][1] > 0
     Cd, st = ob.spgemm(dA, dB, workflow=ob.WF_HLL, estimate_scale=0.3, esc_short_rows=1)   # retry rows go through ESC too
     check_result(Cd, ref, A, f"esc in the retry seed {seed}")
     assert st["overflow_rows"] > 0
@@ -804,9 +807,10 @@ def test_short_rows_with_every_number_of_keys(ob, dtype):
     for kw in (dict(workflow=ob.WF_UPPER_BOUND, bound_load_coef=1.0), dict(workflow=ob.WF_UPPER_BOUND),
                dict(workflow=ob.WF_SYMBOLIC, exact_load_coef=1.0), dict(workflow=ob.WF_SYMBOLIC),
                dict(workflow=ob.WF_HLL), dict(workflow=ob.WF_AUTO)):
-        Cd, st = ob.spgemm(dA, dB, **kw)
-        check_result(Cd, ref, A, f"short rows {kw}")
-        assert st["rows_per_bin"][0] + st["rows_per_bin"][1] + st["rows_per_bin"][2] > 0
+        for force in (0, 1):   # sorted, and (forced: no row is sorted) in the tables
+            Cd, st = ob.spgemm(dA, dB, force_hash_kernels=force, **kw)
+            check_result(Cd, ref, A, f"short rows {kw} force {force}")
+            assert st["rows_per_bin"][0] + st["rows_per_bin"][1] + st["rows_per_bin"][2] > 0
 
 
 def test_skewed_row_lengths_of_b(ob):
