@@ -23,8 +23,8 @@ static inline int ilog2_ceil(double x, int lo, int hi)
 }
 
 // ---------------------------------------------------------------- validate
-// near_pairs (may be null): a measure of how clustered the columns of the matrix are, taken on a sample - every
-// 16th workgroup adds the number of entries it looked at to near_pairs[0] and the number of those whose
+// near_pairs (may be null): a measure of how clustered the columns of the matrix are, taken on a sample (for a B that is A
+// itself by k_row_products, from the rows that are not long) - every 16th workgroup adds the number of entries it looked at to near_pairs[0] and the number of those whose
 // successor's column id is 1 .. 4 larger to near_pairs[1] (pairs across a row boundary count too; they are few).
 // One pair of atomics per sampling workgroup: same-address atomics serialise at about 12 ns each.
 __global__ void k_validate(const int64_t *rp, const int32_t *col, int64_t rows, int64_t cols, int64_t nnz,
@@ -86,15 +86,15 @@ static int long_row_blocks(int64_t rows)
     return (int)(want < 1023 ? want : 1023) | 1;
 }
 
-// take(row) for every row of 0 .. rows - 1 that is_long names, by the whole workgroup (uniform, barriers allowed).
-// s_list: TPB words, s_n: one.
-template <typename IsLong, typename Take>
+// take(row) for every row of 0 .. rows - 1 that is_long names, by the whole workgroup of THREADS threads (uniform, barriers
+// allowed).  s_list: THREADS words, s_n: one.
+template <int THREADS = TPB, typename IsLong, typename Take>
 __device__ __forceinline__ void for_long_rows(int64_t rows, int n_long, int32_t *s_list, int *s_n, IsLong is_long, Take take)
 {
     const int tid = threadIdx.x;
     const int64_t stretch = (int64_t)n_long * LONG_ROWS;
     const int64_t first = (int64_t)blockIdx.x * LONG_ROWS + tid % LONG_ROWS + (int64_t)(tid / LONG_ROWS) * stretch;
-    for (int64_t base = 0; base < rows; base += stretch * (TPB / LONG_ROWS)) {   // uniform
+    for (int64_t base = 0; base < rows; base += stretch * (THREADS / LONG_ROWS)) {   // uniform
         if (tid == 0) *s_n = 0;
         __syncthreads();
         const int64_t r = base + first;
@@ -137,7 +137,10 @@ __device__ __forceinline__ void block_totals(long long tsum, long long tmax, lon
 }
 
 // bad_bit: bit of flags that any fault of A sets besides its own (0: none, and A's ends are not looked at).
-// near_pairs (given where B is the same matrix): see k_validate; a descending pair of columns in a sampled row sets bit 8.
+// near_pairs (given where B is the same matrix): see k_validate; the sample is every 16th workgroup of those for rows that
+// are not long, so the long rows of a power-law matrix are not in it.  It decides nothing but which of two orderings of a
+// small hash table is used and, by a descending pair of columns in a sampled row, which sets bit 8, whether B's window
+// table is tried: never the result.
 __global__ void __launch_bounds__(TPB)
 k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, int64_t m, int64_t a_nnz,
                const int64_t *__restrict__ b_rp, int64_t b_rows, int g_log2, int64_t long_from, int n_long,
@@ -605,18 +608,9 @@ k_hll_merge_long(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a
     __shared__ int s_n;
     const int tid = threadIdx.x;
     const int slice = tid & (L - 1), wave = tid / WAVE;
-    const int64_t stretch = (int64_t)gridDim.x * LONG_ROWS;
-    const int64_t first = (int64_t)blockIdx.x * LONG_ROWS + tid % LONG_ROWS + (int64_t)(tid / LONG_ROWS) * stretch;
-    const int64_t turn = stretch * (LONG_THREADS / LONG_ROWS);
-    for (int64_t base = 0; base < n_rows; base += turn) {   // uniform
-        if (tid == 0) s_n = 0;
-        __syncthreads();
-        const int64_t r = base + first;
-        if (r < n_rows && a_rp[r + 1] - a_rp[r] >= long_from) s_list[atomicAdd(&s_n, 1)] = (int32_t)r;
-        __syncthreads();
-        const int n = s_n;
-        for (int i = 0; i < n; ++i) {   // uniform
-            const int64_t row = s_list[i];
+    for_long_rows<LONG_THREADS>(
+        n_rows, (int)gridDim.x, s_list, &s_n, [&](int64_t r) { return a_rp[r + 1] - a_rp[r] >= long_from; },
+        [&](int64_t row) {
             uint64_t acc = 0;
             long long blen = 0;
             hll_walk<L, 4>(a_rp, a_col, sk, b_rp, row, slice, tid / L, LONG_THREADS / L, acc, blen);
@@ -635,9 +629,7 @@ k_hll_merge_long(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a
                 hll_finish<M>(f, fb, row, row, slice, tid < L, prod, maxb, b_cols, est, merged);
             }
             __syncthreads();
-        }
-        __syncthreads();
-    }
+        });
 }
 
 hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const int64_t *rows, int64_t n_rows,
