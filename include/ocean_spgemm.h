@@ -95,8 +95,9 @@ typedef struct ocean_options {
     uint32_t sample_seed;
     double estimate_scale;           /* test hook: every estimate is multiplied by this before binning (1.0) */
     int32_t validate_inputs;         /* 1: check column ids and row offsets on the device first */
-    int32_t force_hash_kernels;      /* 1: no row is accumulated by sorting its products (see bin_ms), and rows beyond the 8192-slot LDS table always use the hybrid (LDS keys, global
-                                        values) and global-table hash kernels, as they do when B's rows are unsorted */
+    int32_t force_hash_kernels;      /* 1: no row is accumulated by sorting its products (see bin_ms), and rows beyond the
+                                        8192-slot LDS table always use the hybrid (LDS keys, global values) and
+                                        global-table hash kernels, as they do when B's rows are unsorted */
     int32_t assisted_symbolic;       /* assisted symbolic binning (Section 4.1): the key tables of the exact symbolic pass
                                         are sized from products / conservative CR instead of the products.  0: off;
                                         1 (default): whenever the analysis sampled rows, i.e. under OCEAN_WF_AUTO;
@@ -193,8 +194,8 @@ typedef struct ocean_stats {
      * are sorted and some row outgrows the largest LDS hash table, the rows of the last three bins of
      * ocean_bin_layout run in ONE launch of the column-window kernel: its time is reported under the last
      * bin and bin_ms of the two before it is 0.  Rows of few products are sorted instead of hashed, in one launch
-     * per size class whatever their bins: a launch's time is reported under the bin that holds most of its
-     * products. */
+     * per size class whatever their bins (a class whose rows merge into few columns: in one hash table): a launch's
+     * time is reported under the bin that holds most of its products. */
     float bin_ms[OCEAN_MAX_BINS];
     int64_t bin_products[OCEAN_MAX_BINS];
     int64_t bin_nnz_a[OCEAN_MAX_BINS];
@@ -238,7 +239,7 @@ int ocean_row_products(const ocean_csr *A, const ocean_csr *B, int64_t *prod, in
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same kernels as ocean_row_products; the per-row scratch they
  * need (4 bytes per row of A, and the call's device scalars) lives in a
- * fixed array inside the library's code object, 4 MiB + 16 KiB per GPU, held
+ * fixed array inside the library's code object, under 4 MiB + 16 KiB per GPU, held
  * until the process ends.  Hence A->rows <= OCEAN_NOALLOC_MAX_ROWS; more rows
  * give OCEAN_EINVAL and nothing is launched.  The call allocates and frees
  * nothing, does not synchronise and reads nothing back: it enqueues its

@@ -13,7 +13,7 @@ constexpr int TPB = 256;
 // Small ones have small tiles: 4096 rows are a handful of workgroups either way, and a thread's rows are one latency
 // after the other (classification of 4096 rows 9 us with four rows per thread).
 static int row_items(int64_t m) { return m > 262144 ? 8 : m > 65536 ? 4 : 1; }
-constexpr int64_t DIRECT_TILES = 4096;   // up to here every workgroup adds up the tiles before it (4 M rows: 16 loads a thread)
+constexpr int64_t DIRECT_TILES = 4096;   // up to here every workgroup adds up the tiles before it (8.4 M rows: 16 loads a thread)
 
 static int64_t row_tiles(int64_t m) { return (m + TPB * row_items(m) - 1) / (TPB * row_items(m)); }
 int64_t scan_tmp_elems(int64_t n) { return row_tiles(n) + 1; }

@@ -479,16 +479,17 @@ int run_numeric(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int gb_l
     // of the twelve classes (0.91 ms a call with a launch for each, 0.86 before there were any).
     // Sorting costs what the products cost, a hash table what its slots and the products cost, so a class whose rows merge
     // into few columns, which shows in small tables, goes to the smallest table that holds nine tenths of it, where that
-    // saves more than the launch, 16 us (the rows of larger tables, the end of the class's list, are sorted).  The class decides and not
-    // the row, because sizes may be estimates: a few rows in tables of their own, some of them too small, cost a launch
-    // and a retry (band of 17 diagonals, 289 products on 33 columns: 0.56 ms by class, 0.66 by row).  Measured, ns
-    // per row, fp64 (fp32 within 6 percent), numeric stage of 200 000 to 500 000 equal rows, products on columns,
-    // sorted / hashed, for the first table that is cheaper and the one above:
+    // saves more than the launch, 16 us (the rows of larger tables, the end of the class's list, are sorted).  The class
+    // decides and not the row, because sizes may be estimates: a few rows in tables of their own, some of them too
+    // small, cost a launch and a retry (band of 17 diagonals, 289 products on 33 columns: whole call 0.56 ms by class, 0.66
+    // by row).  Measured, ns per row, fp64 (fp32: the same lines), numeric stage of 200 000 to 500 000 equal rows,
+    // products on columns, sorted / hashed, for the largest table that is cheaper and the one above:
     //   64, 96   48 on 15 0.21 / 0.17     48 on 23 0.22 / 0.28     128       128 on 19 0.37 / 0.30    128 on 27 0.38 / 0.39
     //   192      192 on 19 0.56 / 0.45    192 on 35 0.59 / 0.65    256       256 on 19 0.73 / 0.56    256 on 35 0.77 / 0.79
     //   384      384 on 32 1.09 / 0.79    384 on 47 1.10 / 1.35    512       512 on 32 1.38 / 0.94    512 on 63 1.43 / 1.50
     //   768      640 on 95 2.32 / 1.82    768 on 204 2.41 / 3.05   1024      1024 on 95 3.24 / 2.33   1024 on 294 3.38 / 3.44
     //   1536     1376 on 498 6.00 / 5.19  1376 on 724 6.28 / 9.57  2048      1984 on 529 9.33 / 5.72  1984 on 833 9.56 / 10.13
+    // (Where a table is nearly full the two are even: 640 on 166 2.37 / 2.37, 1376 on 663 6.27 / 7.16.)
     // A launch's time is reported under the bin that holds most of its products.
     auto run_sorted = [&]() -> int {
         constexpr int64_t LAUNCH_PS = 6000000, TABLE_LAUNCH_PS = 16000000;
@@ -766,7 +767,9 @@ int lanes_div_of(const ocean_stats *S)
     return (double)S->max_row_products <= 16.0 * S->avg_products ? 4 : 1;
 }
 
-// Sort classes that can hold column ids and positions of B: a key is the column id above the number of the product.
+// Sort classes that can hold column ids and positions of B: a key is the column id above the number of the product.  One
+// column more and the rows of a class are hashed (numeric stage of 200 000 rows of 1024 products, B of 2^22 - 1 and 2^22
+// columns: 0.92 and 2.5 ms; 1936 products, 2^21 - 1 and 2^21: 2.2 and 5.1 ms).
 // With expand-sort-compress asked for, the classes that would take its rows stay out.
 unsigned sort_mask_of(const Csr &B, bool esc)
 {
@@ -797,24 +800,27 @@ int select_of(double avg, double er, double cr, const ocean_options &o)
 // "chosen empirically to amortize the cost of output compaction" on an A100 (Section 4.3).  Here the
 // compaction copy runs at 4.3 - 5.8 TB/s, so what it has to beat is the symbolic pass it replaces:
 // estimation wins when products / r_sym > 2 (4 + v) products / (CR * bw), i.e. CR > 2 (4 + v) r_sym / bw.
-// Rows that fit the LDS key tables are counted at r_sym = 250 - 460 G products/s (break-even CR 1.2 - 1.5 by
-// the rates alone; with the estimate's own pass, its retries and the larger tables it gives the numeric pass
-// the two workflows measure the same at CR 3.3 and two passes win by 14 % at CR 1.03: threshold 3),
-// rows that outgrow them go through the bitmap kernel at about 1.4 T products/s (break-even CR above 4.5).
-// So the threshold slides between the two with the share of the products that heavy rows hold.  Small
-// problems (below tuned_min_products) run the two-pass workflow unsampled: there the sketches and the sample
-// cost more than any choice between the workflows can gain (4096 rows of 8 entries: 0.29 ms sampled, 0.24 ms not).
+// Rows that fit the LDS key tables are counted at r_sym = 280 - 470 G products/s (break-even CR 1.3 - 1.5 by the rates
+// alone; the estimate's own pass and its retries come on top), rows that outgrow them by the bitmap kernel at about
+// 1.5 T products/s (break-even CR above 4.5).  So the threshold slides from 3.0 to 4.5 with the share of the
+// products that heavy rows hold.  Measured, forced, library's wall clock, bound / estimate / two passes in ms:
+// rectangular input, CR 1.03, 1.76 / 1.87 / 1.59; clustered, CR 3.3, 2.11 / 2.40 / 2.48; R-MAT scale 20, CR 2.2,
+// 143.0 / 149.6 / 113.3.  Two passes win on the first and the third.  On the clustered input the rule takes the
+// estimate, which beats two passes by 3 % and loses 14 % to the bound: rows that are sorted cost the same whatever size
+// is predicted for them, so for them the estimate's pass and retry buy only a smaller reservation (2.8 against
+// 3.9 GiB at the peak).  The rule dates from before rows were sorted and is kept: which workflow AUTO picks is
+// part of the interface, and the reservation is what a program with little memory chooses it for.
+// Small problems (below tuned_min_products) run the two-pass workflow unsampled: there the sketches and the sample
+// cost more than any choice between the workflows can gain (4096 rows of 8 entries, forced: 0.11 / 0.14 / 0.11 ms).
 int select_tuned(double avg, double er, double cr, double products, double heavy_products, const ocean_options &o)
 {
     if (avg < o.upper_bound_avg_products) return OCEAN_WF_UPPER_BOUND;
     if (products < o.tuned_min_products) return OCEAN_WF_SYMBOLIC;
     const double share = products > 0.0 ? heavy_products / products : 0.0;
     const double thr = o.tuned_cr_light + (o.tuned_cr_heavy - o.tuned_cr_light) * share;
-    // (an estimate is worth its pass, its expansion factor and its retries only if it undercuts the product
-    // bound by more than its own error: below tuned_cr_bound the bound itself is the reservation.  Measured on
-    // the rectangular input, CR 1.03: 2.43 ms against 2.61 ms; on the clustered one, CR 3.3: 4.44 against 3.51 ms.
-    // With the default thresholds the rule is not reached: below a CR of 3 two passes are faster than either,
-    // 2.20 ms on the rectangular input)
+    // (below tuned_cr_bound the product bound itself is the reservation: an estimate cannot undercut it by more than its
+    // own error.  Rectangular input, CR 1.03: 1.76 ms against 1.87.  With the default thresholds the rule is not reached:
+    // below a CR of 3 two passes run, 1.59 ms there)
     if (er >= o.er_threshold && cr >= thr) return cr < o.tuned_cr_bound ? OCEAN_WF_UPPER_BOUND : OCEAN_WF_HLL;
     return OCEAN_WF_SYMBOLIC;
 }
@@ -1161,6 +1167,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
 // below is only a host-side handle, the device address comes from hipGetSymbolAddress, once per device.
 constexpr size_t NOALLOC_SCALARS = (sizeof(Scalars) + ALIGN - 1) / ALIGN * ALIGN;
 constexpr size_t NOALLOC_BYTES = NOALLOC_SCALARS + (size_t)OCEAN_NOALLOC_MAX_ROWS * sizeof(int32_t);
+static_assert(NOALLOC_BYTES < ((size_t)4 << 20) + ((size_t)16 << 10), "the header promises less than 4 MiB + 16 KiB");
 constexpr int NOALLOC_MAX_DEVICES = 64;
 
 }  // namespace
