@@ -181,7 +181,7 @@ typedef struct ocean_stats {
                                                       rows counted by a bitmap over their own column range */
     int64_t overflow_rows;
     int64_t symbolic_overflow_rows; /* rows whose assisted key table filled up and that were recounted */
-    int64_t temp_slots;        /* output slots reserved before compaction (estimation workflows) */
+    int64_t temp_slots;        /* output slots reserved at first (estimation workflows) */
     int64_t peak_bytes;        /* largest total obtained from the allocator at one time */
     int32_t compacted_in_place; /* 1: C's col_idx / val are the temporary output, compacted in place */
     int32_t b_sorted_copy;      /* 1: the numeric pass read a copy of B with sorted rows (see sort_b_ratio) */
@@ -195,7 +195,10 @@ typedef struct ocean_stats {
      * ocean_bin_layout run in ONE launch of the column-window kernel: its time is reported under the last
      * bin and bin_ms of the two before it is 0.  Rows of few products are sorted instead of hashed, in one launch
      * per size class whatever their bins (a class whose rows merge into few columns: in one hash table): a launch's
-     * time is reported under the bin that holds most of its products. */
+     * time is reported under the bin that holds most of its products.  Where every row is one of those (at most 2048 products
+     * and 64 entries of A) and nothing else was asked for, AUTO and the upper-bound workflow sort all rows in one launch
+     * and write them straight to C: no symbolic pass (symbolic_rows_per_bin and assist_cr stay 0), no binning stage, no
+     * overflow; rows count in the bin that the workflow's prediction, exact for the two others, would have given them. */
     float bin_ms[OCEAN_MAX_BINS];
     int64_t bin_products[OCEAN_MAX_BINS];
     int64_t bin_nnz_a[OCEAN_MAX_BINS];

@@ -116,9 +116,11 @@ __device__ __forceinline__ void for_long_rows(int64_t rows, int n_long, int32_t 
 // ns each, and there is one set per workgroup: they are spread over ROW_TOTAL_SLOTS slots of 128 bytes (one
 // cache line each) by workgroup index and added up by whoever reads them (sum_row_totals on the host).
 // slot[0] += products, slot[1] = max(products of a row), slot[2] += products of the rows whose product count
-// exceeds heavy_from (the rows that outgrow the LDS hash tables).
+// exceeds heavy_from (the rows that outgrow the LDS hash tables), slot[3] += rows without products, and the rows of each
+// sort class, s_cls: words 3 .. of the slot.
 __device__ __forceinline__ void block_totals(long long tsum, long long tmax, long long theavy, long long *s_sum,
-                                             long long *s_max, long long *s_heavy, unsigned long long *totals)
+                                             long long *s_max, long long *s_heavy, const unsigned int *s_cls,
+                                             int lds_most, unsigned long long *totals)
 {
     const long long wsum = group_reduce_sum(tsum, WAVE);
     const long long wmax = group_reduce_max(tmax, WAVE);
@@ -133,7 +135,24 @@ __device__ __forceinline__ void block_totals(long long tsum, long long tmax, lon
         if (bs) atomicAdd(&slot[0], (unsigned long long)bs);
         if (bm) atomicMax(&slot[1], (unsigned long long)bm);
         if (bh) atomicAdd(&slot[2], (unsigned long long)bh);
+    } else if (threadIdx.x >= WAVE && threadIdx.x < WAVE + 1 + SORT_CLASSES) {
+        const int c = threadIdx.x - WAVE;
+        unsigned long long *slot = totals + (size_t)(blockIdx.x % ROW_TOTAL_SLOTS) * ROW_TOTAL_STRIDE;
+        if (s_cls[c]) atomicAdd(&slot[ROW_TOTAL_CLASS - 1 + c], (unsigned long long)s_cls[c]);
     }
+    const int most = (int)wave_max_u32((uint32_t)lds_most);
+    if (lane_id() == 0 && most > 0)
+        atomicMax(&totals[(size_t)(blockIdx.x % ROW_TOTAL_SLOTS) * ROW_TOTAL_STRIDE + ROW_TOTAL_LDS], (unsigned long long)most);
+}
+
+// Smallest sort class that holds a row of pr products from ne entries, 0: none.
+__device__ __forceinline__ int smallest_sort_class(long long pr, long long ne)
+{
+    int cls = 0;
+#pragma unroll
+    for (int c = SORT_CLASSES - 1; c >= 1; --c)
+        if (pr <= kSortClass[c].cap && ne <= kSortClass[c].entries) cls = c;
+    return cls;
 }
 
 // bad_bit: bit of flags that any fault of A sets besides its own (0: none, and A's ends are not looked at).
@@ -145,9 +164,11 @@ __global__ void __launch_bounds__(TPB)
 k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, int64_t m, int64_t a_nnz,
                const int64_t *__restrict__ b_rp, int64_t b_rows, int g_log2, int64_t long_from, int n_long,
                int64_t *__restrict__ prod, int32_t *__restrict__ maxb, unsigned long long *totals, int32_t *flags,
-               int64_t heavy_from, int bad_bit, unsigned long long *near_pairs)
+               int64_t heavy_from, int bad_bit, unsigned long long *near_pairs, unsigned long long *zero, int64_t zero_words,
+               int vbytes)
 {
     __shared__ unsigned int s_near, s_seen;
+    __shared__ unsigned int s_cls[1 + SORT_CLASSES];   // rows without products, rows of each sort class
     __shared__ long long s_sum[TPB / WAVE];
     __shared__ long long s_max[TPB / WAVE];
     __shared__ long long s_heavy[TPB / WAVE];
@@ -164,6 +185,10 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
     unsigned int near = 0, seen = 0;
     long long tsum = 0, tmax = 0, theavy = 0;
     bool unsorted = false;
+    int lds_most = 0;
+    if (tid < 1 + SORT_CLASSES) s_cls[tid] = 0u;
+    for (int64_t i = (int64_t)blockIdx.x * TPB + tid; i < zero_words; i += (int64_t)gridDim.x * TPB) zero[i] = 0ull;
+    __syncthreads();
     bool bad = false, bad_rp = bad_bit != 0 && blockIdx.x == 0 && tid == 0 && (a_rp[0] != 0 || a_rp[m] != a_nnz);
     // entries first, first + step, ... below e1: four independent chains (entry -> row offsets of B) in flight per lane;
     // reads are unconditional (index clamped) so that they are issued together
@@ -196,12 +221,13 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
             }
         }
     };
-    auto store = [&](int64_t row, long long p, long long mx) {
+    auto store = [&](int64_t row, long long ne, long long p, long long mx) {
         prod[row] = p;
         maxb[row] = (int32_t)(mx > 0x7fffffffLL ? 0x7fffffffLL : mx);
         tsum += p;
         tmax = p > tmax ? p : tmax;
         theavy += p > heavy_from ? p : 0;
+        atomicAdd(&s_cls[p == 0 ? 0 : 1 + smallest_sort_class(p, ne)], 1u);
     };
     if (for_long) {
         for_long_rows(m, n_long, s_list, &s_n,
@@ -219,7 +245,7 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
                           if (tid == 0) {
                               p = mx = 0;
                               for (int j = 0; j < TPB / WAVE; ++j) { p += s_sum[j]; mx = s_max[j] > mx ? s_max[j] : mx; }
-                              store(row, p, mx);
+                              store(row, a_rp[row + 1] - a_rp[row], p, mx);
                           }
                           __syncthreads();
                       });
@@ -228,20 +254,28 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
             const int64_t row = base + rl;
             long long p = 0, mx = 0;
             bool mine = row < m;
+            int64_t ne = 0;
             if (mine) {
                 // offsets outside [0, nnz] or descending are reported and never used as they stand: this kernel
                 // runs before the host has seen the verdict of the input check
                 int64_t e0 = a_rp[row], e1 = a_rp[row + 1];
                 if (e0 < 0 || e1 < e0 || e1 > a_nnz) { bad_rp = true; e0 = 0; e1 = 0; }
-                mine = n_long == 0 || e1 - e0 < long_from;   // uniform for the group
+                ne = e1 - e0;
+                mine = n_long == 0 || ne < long_from;   // uniform for the group
                 if (mine) walk(e0 + sub, e1, G, p, mx);
             }
             p = group_reduce_sum(p, G);
             mx = group_reduce_max(mx, G);
-            if (mine && sub == 0) store(row, p, mx);
+            if (mine && sub == 0) store(row, ne, p, mx);
+            if (G <= 16) {   // (more lanes: rows that a wave does not sort)
+                int lds = sort_row_bytes((int)(p < 2048 ? p : 2048), vbytes);
+                lds += __shfl_xor(lds, G, WAVE);
+                lds += __shfl_xor(lds, 2 * G, WAVE);
+                lds_most = lds > lds_most ? lds : lds_most;
+            }
         }
     }
-    block_totals(tsum, tmax, theavy, s_sum, s_max, s_heavy, totals);
+    block_totals(tsum, tmax, theavy, s_sum, s_max, s_heavy, s_cls, lds_most, totals);
     if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(flags, 4 | bad_bit);
     if (__ballot(bad_rp) != 0 && lane_id() == 0) atomicOr(flags, 1);
     if (__ballot(unsorted) != 0 && lane_id() == 0) atomicOr(flags, 8);
@@ -260,10 +294,11 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
 
 // validate: A's offsets must begin at 0 and end at its number of entries as well, and any fault of A sets bit 1 of flags
 // (offsets that descend or leave [0, nnz] always do, column ids outside [0, b_rows) always set bit 4).  near_pairs (may
-// be null): see k_validate.
+// be null): see k_validate.  zero: zero_words words that the kernel clears on the way, for a later one.  vbytes:
+// bytes of a value, for the LDS that sorted rows take.
 hipError_t launch_row_products(const Csr &A, const int64_t *b_rp, int64_t b_rows, int64_t *prod, int32_t *maxb,
                                unsigned long long *totals, int32_t *flags, bool validate, unsigned long long *near_pairs,
-                               hipStream_t s)
+                               unsigned long long *zero, int64_t zero_words, int vbytes, hipStream_t s)
 {
     const int64_t heavy_from = kNumericSlots[NB_S4K];   // beyond the largest LDS hash table that sorted inputs use
     if (A.rows == 0) return hipSuccess;
@@ -275,7 +310,8 @@ hipError_t launch_row_products(const Csr &A, const int64_t *b_rp, int64_t b_rows
     if (blocks > 2048) blocks = 2048;
     const int n_long = A.nnz >= long_from ? long_row_blocks(A.rows) : 0;
     hipLaunchKernelGGL(k_row_products, dim3((unsigned)(blocks + n_long)), dim3(TPB), 0, s, A.rp, A.col, A.rows, A.nnz, b_rp,
-                       b_rows, g_log2, long_from, n_long, prod, maxb, totals, flags, heavy_from, validate ? 1 : 0, near_pairs);
+                       b_rows, g_log2, long_from, n_long, prod, maxb, totals, flags, heavy_from, validate ? 1 : 0, near_pairs, zero,
+                       zero_words, vbytes);
     return hipGetLastError();
 }
 

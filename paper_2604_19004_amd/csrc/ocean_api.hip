@@ -54,15 +54,17 @@ struct Scalars {
     unsigned long long row_totals[ROW_TOTAL_SLOTS * ROW_TOTAL_STRIDE];   // totals of the row-products pass, by slot
 };
 
-// P, largest row, products of the heavy rows from the slots of a fetched Scalars
-void sum_row_totals(const Scalars *h, unsigned long long (&out)[3])
+// P, largest row, and the other totals of the row-products pass from the slots of a fetched Scalars
+using RowTotals = unsigned long long[ROW_TOTAL_LDS + 1];
+void sum_row_totals(const Scalars *h, RowTotals &out)
 {
-    out[0] = out[1] = out[2] = 0;
+    for (unsigned long long &o : out) o = 0;
     for (int i = 0; i < ROW_TOTAL_SLOTS; ++i) {
         const unsigned long long *slot = h->row_totals + (size_t)i * ROW_TOTAL_STRIDE;
-        out[0] += slot[0];
-        out[1] = slot[1] > out[1] ? slot[1] : out[1];
-        out[2] += slot[2];
+        for (int k = 0; k <= ROW_TOTAL_LDS; ++k) {
+            if (k == 1 || k == ROW_TOTAL_LDS) out[k] = slot[k] > out[k] ? slot[k] : out[k];
+            else out[k] += slot[k];
+        }
     }
 }
 
@@ -270,9 +272,15 @@ struct Work {
     double *est = nullptr;
     int64_t *sample_rows = nullptr;
     double *sample_est = nullptr;
+    // rows that are placed as they are sorted (placed.hip): words for units of four rows and more, cleared by the analysis
+    unsigned long long *places = nullptr;
+    uint32_t *counts = nullptr;
+    int64_t place_words = 0;                               // 64-bit words of both
+    int four_rows_lds = 0;                                 // see ROW_TOTAL_LDS
+    unsigned long long class_rows[SORT_CLASSES] = {};      // rows of each sort class, [0]: of none (known after the analysis)
 };
 
-int work_alloc(Ctx &c, Work &w, int64_t m, int64_t n_sample)
+int work_alloc(Ctx &c, Work &w, int64_t m, int64_t n_sample, bool placing)
 {
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += up(bytes); return o; };
@@ -286,9 +294,16 @@ int work_alloc(Ctx &c, Work &w, int64_t m, int64_t n_sample)
     const size_t o_sr = take((size_t)(n_sample + 1) * 8), o_se = take((size_t)(n_sample + 1) * 8);
     const size_t o_cmin = take(mm * 4), o_cmax = take(mm * 4);
     const size_t o_scmin = take((size_t)(n_sample + 1) * 4), o_scmax = take((size_t)(n_sample + 1) * 4);
+    const size_t units = (mm + 3) / 4;
+    const size_t place_words = placing ? units + (units + 1) / 2 : 0, o_places = take(place_words * 8);
     char *b = static_cast<char *>(c.alloc(off));
     if (!b) return fail(OCEAN_EALLOC, "workspace allocation failed");
     w.base = b;
+    if (placing) {
+        w.places = reinterpret_cast<unsigned long long *>(b + o_places);
+        w.counts = reinterpret_cast<uint32_t *>(w.places + units);
+        w.place_words = (int64_t)place_words;
+    }
     w.sc = reinterpret_cast<Scalars *>(b + o_sc);
     w.prod = reinterpret_cast<int64_t *>(b + o_prod);
     w.maxb = reinterpret_cast<int32_t *>(b + o_maxb);
@@ -325,16 +340,18 @@ int zero_bins(Ctx &c, Work &w)
 }
 
 // ---- analysis: validation + products per row ------------------------------------------------------
-int run_analysis(Ctx &c, Work &w, const Csr &A, const Csr &B, bool validate, ocean_stats *st)
+int run_analysis(Ctx &c, Work &w, const Csr &A, const Csr &B, int vbytes, bool validate, ocean_stats *st)
 {
     // (the same arrays under another number of entries are two matrices, of which one is not valid)
     const bool same = B.rp == A.rp && B.col == A.col && B.rows == A.rows && B.cols == A.cols && B.nnz == A.nnz;
     if (validate && !same) HIP_TRY(launch_validate(B, &w.sc->flags, w.sc->near_pairs, c.s));
     HIP_TRY(launch_row_products(A, B.rp, B.rows, w.prod, w.maxb, w.sc->row_totals, &w.sc->flags, validate,
-                                validate && same ? w.sc->near_pairs : nullptr, c.s));
+                                validate && same ? w.sc->near_pairs : nullptr, w.places, w.place_words, vbytes, c.s));
     OC_TRY(fetch_scalars(c, w.sc));
-    unsigned long long tot[3];
+    RowTotals tot;
     sum_row_totals(c.h, tot);
+    std::memcpy(w.class_rows, tot + ROW_TOTAL_CLASS, sizeof(w.class_rows));
+    w.four_rows_lds = (int)tot[ROW_TOTAL_LDS];
     if (c.h->flags & 1) return fail(OCEAN_EINVAL, "A is not a valid CSR matrix (row offsets or column ids out of range)");
     if (c.h->flags & 2) return fail(OCEAN_EINVAL, "B is not a valid CSR matrix (row offsets or column ids out of range)");
     if (c.h->flags & 4) return fail(OCEAN_EINVAL, "a column id of A is outside [0, rows(B))");
@@ -825,6 +842,124 @@ int select_tuned(double avg, double er, double cr, double products, double heavy
     return OCEAN_WF_SYMBOLIC;
 }
 
+// Sort class whose kernel takes every row and places it as it is sorted (placed.hip), 0: the rows go the general way.
+// Placing leaves out the binning (60 us with its read-back) and the symbolic pass or the compaction (3 ps a product and more:
+// 3.2 and 5.1 for 200 000 rows of 361 products in fp64).  What it costs: below a wave's class every row is sorted as the
+// largest class; of rows that have a wave each, all that are in flight wait for the longest among them, and a long row is
+// nearly always among them.  Measured, 200 000 rows, fp64, whole call in us, placed / general (the faster of compaction and
+// symbolic pass), rows of 49, 121 and 196 products with one of 361, 1024 or 2025 among every thousand: 308 / 297, 395 / 305, 795 / 311;
+// 347 / 452, 431 / 457, 831 / 471; 410 / 603, 490 / 615, 876 / 625.  Equal rows: 25 products 221 / 330 (400 000), 225 390 / 560, 484 689 / 944,
+// 961 929 / 1272 (150 000), 2025 1390 / 1709 (100 000).
+int placed_class(const Csr &A, const Work &w, const Ctx &c, double products)
+{
+    constexpr double kWavePs[SORT_CLASSES] = {0, 1050, 1050, 1050, 1050, 1300, 1600, 2300, 2950, 4300, 5600, 10000, 12900};
+    if (w.class_rows[0] != 0) return 0;   // a row with more products or entries than the sort takes
+    int cls = 0;
+    for (int k = 1; k < SORT_CLASSES; ++k)
+        if (w.class_rows[k] != 0) cls = k;
+    if (cls == 0 || !((c.sort_mask >> cls) & 1u)) return 0;
+    if (placed_units(A.rows, cls) + 1 > most_blocks(256)) return 0;
+    double general = 60e6 + 3.0 * products, placed;   // ps
+    for (int k = 1; k <= cls; ++k) general += (double)w.class_rows[k] * kSortClass[k].ps;
+    if (kPlacedRows[cls] > 4) {
+        placed = (double)A.rows * kSortClass[cls].ps;
+    } else {
+        const int by_lds = 160 * 1024 / w.four_rows_lds, by_registers = cls <= 10 ? 7 : cls == 11 ? 5 : 4;   // workgroups of a CU
+        const double in_flight = 4.0 * c.n_cu * (by_lds < by_registers ? by_lds : by_registers);
+        placed = (double)A.rows / in_flight * (7.5e6 + 3.4e3 * kSortClass[cls].cap);   // the longest row's time
+        double sorted = 0.0;
+        for (int k = 1; k <= cls; ++k) sorted += (double)w.class_rows[k] * kWavePs[k];
+        if (sorted > placed) placed = sorted;
+    }
+    return placed < general ? cls : 0;
+}
+
+// C in one pass over the products.  What is reserved for it is the products, or, where the sample knows how they merge, an
+// eighth more than that promises (estimates are cut off at the products, which makes the ratio of rows that hardly merge up
+// to 7 % too large: 1.09 for 1.03); what does not fit is not written, the total tells, and the pass is repeated with as much as it needs.  *done = false: a
+// reservation was refused or a wait ran out, nothing is kept and the general way is open.
+int run_placed(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int cls, int workflow, const ocean_options &o, ocean_stats *st,
+               ocean_stats *S, int64_t *c_rp, ocean_csr *C, bool *done)
+{
+    *done = false;
+    const int64_t m = A.rows;
+    const size_t vbytes = dtype == OCEAN_F64 ? 8 : 4;
+    int64_t slots = S->products;
+    if (workflow != OCEAN_WF_UPPER_BOUND && S->sampled_rows > 0 && S->sampled_cr > 1.0) {
+        const double want = (double)S->products / S->sampled_cr * 1.125 + 4096.0;
+        if (want < (double)slots) slots = (int64_t)want;
+    }
+    const size_t mem_total = device_facts().total_mem;
+    const int64_t reserved = slots;
+    int32_t *col = nullptr;
+    void *val = nullptr;
+    int64_t nnz_c = 0;
+    size_t launch_ev = 0;
+    for (int round = 0; round < 2; ++round) {
+        if (mem_total > 0 && (double)slots * (double)(4 + vbytes) > 0.4 * (double)mem_total) return OCEAN_OK;
+        col = static_cast<int32_t *>(c.alloc((size_t)slots * 4));
+        val = col ? c.alloc((size_t)slots * vbytes) : nullptr;
+        if (!val) {
+            c.release(col);
+            return OCEAN_OK;
+        }
+        if (round > 0) HIP_TRY(hipMemsetAsync(w.places, 0, (size_t)w.place_words * 8, c.s));
+        launch_ev = c.ev.size();
+        OC_TRY(mark(c, OCEAN_ST_NUMERIC));
+        HIP_TRY(launch_placed(A, B, dtype, PlacedLaunch{cls, w.prod, w.four_rows_lds, c_rp, col, val, slots, w.counts, w.places,
+                                                        &w.sc->totals[0], &w.sc->flags}, c.s));
+        OC_TRY(mark(c, OCEAN_ST_COMPACT));
+        if (st && round == 0) {   // (complete even where C was cut short)
+            OC_TRY(zero_bins(c, w));
+            HIP_TRY(launch_row_stats(m, workflow == OCEAN_WF_UPPER_BOUND ? 0 : 2, o.exact_load_coef, o.bound_load_coef, B.cols, w.prod,
+                                     A.rp, c_rp, w.sc->bin_count, w.sc->bin_prod, w.sc->bin_work, c.s));
+        }
+        OC_TRY(fetch_scalars(c, w.sc));
+        nnz_c = (int64_t)c.h->totals[0];
+        if ((c.h->flags & 32) == 0 && nnz_c <= slots) break;
+        c.release(col);
+        c.release(val);
+        if (c.h->flags & 32) return OCEAN_OK;
+        slots = nnz_c;
+    }
+    // C keeps what was reserved where little of it is unused
+    const int64_t unused = slots - nnz_c;
+    if (unused > slots / 8 && unused > 65536) {
+        int32_t *t_col = static_cast<int32_t *>(c.alloc((size_t)nnz_c * 4));
+        void *t_val = t_col ? c.alloc((size_t)nnz_c * vbytes) : nullptr;
+        if (t_val) {
+            HIP_TRY(launch_trim(dtype, col, val, nnz_c, t_col, t_val, c.s));
+            col = t_col;
+            val = t_val;
+        }
+    }
+    OC_TRY(mark(c, -1));
+    HIP_TRY(hipStreamSynchronize(c.s));
+    if (st) {
+        int most = 0;
+        for (int b = 0; b < OCEAN_MAX_BINS; ++b) {
+            S->rows_per_bin[b] = (int64_t)c.h->bin_count[b];
+            S->bin_products[b] = (int64_t)c.h->bin_prod[b];
+            S->bin_nnz_a[b] = (int64_t)c.h->bin_work[b];
+            S->bin_nnz_c[b] = (int64_t)c.h->bin_work[OCEAN_MAX_BINS + b];
+            if (S->bin_products[b] > S->bin_products[most]) most = b;
+        }
+        c.bin_ev.emplace_back(most, (int)launch_ev);
+    }
+    S->workflow = workflow;
+    S->nnz_c = nnz_c;
+    if (workflow != OCEAN_WF_SYMBOLIC) S->temp_slots = reserved;
+    C->row_ptr = c_rp;
+    C->col_idx = col;
+    C->val = val;
+    C->nnz = nnz_c;
+    c.detach(c_rp);
+    c.detach(col);
+    c.detach(val);
+    *done = true;
+    return OCEAN_OK;
+}
+
 // The whole pipeline.  Everything obtained from the allocator is tracked in c;
 // the caller releases what is left on any exit path.
 int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C, const ocean_options &o,
@@ -852,10 +987,16 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     Work w;
     c.timed = st != nullptr;
     OC_TRY(mark(c, OCEAN_ST_ANALYSIS));
-    OC_TRY(work_alloc(c, w, m, n_sample));
+    const bool esc_ok = o.esc_short_rows != 0 && n >= 32 && n <= ESC_MAX_COLS;
+    c.sort_mask = o.force_hash_kernels ? 0u : sort_mask_of(B, esc_ok);
+    // Rows are placed as they are sorted where the caller left the way to C open: not where exact sizes, estimates, the column
+    // ranges of all rows or the compaction inside the slab were asked for.
+    const bool placing = c.sort_mask != 0u && !esc_ok && B.nnz < (1LL << 29) && (o.workflow == OCEAN_WF_AUTO || o.workflow == OCEAN_WF_UPPER_BOUND) &&
+                         o.estimate_scale == 1.0 && o.dense_range != 2 && o.compact_in_place < 0;
+    OC_TRY(work_alloc(c, w, m, n_sample, placing));
     ocean_stats local{};
     ocean_stats *S = st ? st : &local;
-    OC_TRY(run_analysis(c, w, A, B, o.validate_inputs != 0, S));
+    OC_TRY(run_analysis(c, w, A, B, (int)vbytes, o.validate_inputs != 0, S));
     const int64_t P = S->products;
     if (P == 0) {
         HIP_TRY(hipMemsetAsync(c_rp, 0, (size_t)(m + 1) * 8, c.s));
@@ -934,8 +1075,13 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         if (bw_try == nullptr) HIP_TRY(launch_check_sorted(B, &w.sc->flags, c.s));   // (known from the window table otherwise)
         w.spans = true;
     }
-    const bool esc_ok = o.esc_short_rows != 0 && n >= 32 && n <= ESC_MAX_COLS;
-    c.sort_mask = o.force_hash_kernels ? 0u : sort_mask_of(B, esc_ok);
+    const int placed = placing && !w.spans ? placed_class(A, w, c, (double)P) : 0;
+    if (placed != 0) {
+        bool done = false;
+        S->hll_registers = m_regs;
+        OC_TRY(run_placed(c, w, A, B, dtype, placed, workflow, o, st, S, c_rp, C, &done));
+        if (done) return OCEAN_OK;
+    }
     int32_t *t_col = nullptr;   // output region of the first attempt (C itself on the two-pass path)
     void *t_val = nullptr;
     int64_t total_slots = 0;
@@ -1276,9 +1422,9 @@ int ocean_row_products(const ocean_csr *A, const ocean_csr *B, int64_t *prod, in
     int32_t *maxb = reinterpret_cast<int32_t *>(buf + up(sizeof(Scalars)));
     int rc = [&]() -> int {
         HIP_TRY(hipMemsetAsync(sc, 0, sizeof(Scalars), c.s));
-        HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, false, nullptr, c.s));
+        HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, false, nullptr, nullptr, 0, 8, c.s));
         OC_TRY(fetch_scalars(c, sc));
-        unsigned long long tot[3];
+        RowTotals tot;
         sum_row_totals(c.h, tot);
         if (c.h->flags & 1) return fail(OCEAN_EINVAL, "A is not a valid CSR matrix (row offsets out of range or descending)");
         if (c.h->flags & 4) return fail(OCEAN_EINVAL, "a column id of A is outside [0, rows(B))");
@@ -1329,7 +1475,7 @@ int ocean_row_products_noalloc(const ocean_csr *A, const ocean_csr *B, int64_t *
     // the scalars keep the last call's sums: clear them (a fill kernel, so that the call can be captured
     // into a graph); the per-row arrays are written before they are read
     HIP_TRY(launch_fill_u64(reinterpret_cast<unsigned long long *>(sc), (int64_t)(NOALLOC_SCALARS / 8), 0ull, s));
-    HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, false, nullptr, s));
+    HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, false, nullptr, nullptr, 0, 8, s));
     HIP_TRY(launch_publish_totals(sc->row_totals, &sc->flags, totals, s));
     return OCEAN_OK;
 }
@@ -1379,9 +1525,9 @@ int ocean_symbolic(const ocean_csr *A, const ocean_csr *B, int32_t *nnz_per_row,
     int rc = [&]() -> int {
         Work w;
         const int64_t n_sample = o.assisted_symbolic == 2 ? sample_size_of(A->rows, o) : 0;
-        OC_TRY(work_alloc(c, w, A->rows, n_sample));
+        OC_TRY(work_alloc(c, w, A->rows, n_sample, false));
         const Csr a = view(A), b = view(B);
-        OC_TRY(run_analysis(c, w, a, b, o.validate_inputs != 0, S));
+        OC_TRY(run_analysis(c, w, a, b, A->dtype == OCEAN_F64 ? 8 : 4, o.validate_inputs != 0, S));
         const int gb_log2 = ilog2_ceil_d(S->er, 0, 6);
         double assist_cr = 0.0;
         if (n_sample > 0 && S->products > 0) {

@@ -226,10 +226,24 @@ __device__ __forceinline__ T group_reduce_max(T v, int width)
 }
 #endif
 
-// Totals of the row-products pass are kept in ROW_TOTAL_SLOTS slots of ROW_TOTAL_STRIDE 64-bit words each (128
-// bytes apart): [0] sum of products, [1] largest row, [2] products of the heavy rows; see analysis.hip.
+// LDS of a row of pr products that a wave sorts (a SortRow of 64 lanes, the fewest products per lane there is a sort for, and
+// 64 entries).
+__host__ __device__ constexpr int sort_row_bytes(int pr, int vbytes)
+{
+    const int ppt = pr <= 128 ? 2 : pr <= 192 ? 3 : pr <= 256 ? 4 : pr <= 384 ? 6 : pr <= 512 ? 8 : pr <= 768 ? 12 : pr <= 1024 ? 16 : pr <= 1536 ? 24 : 32;
+    const int acc = vbytes * (64 * ppt + (64 * ppt >> (ppt >= 12 ? 4 : 3)));   // (a multiple of 8)
+    return acc + 64 * (4 + vbytes) + 8 * ppt;
+}
+
+// Totals of the row-products pass are kept in ROW_TOTAL_SLOTS slots of ROW_TOTAL_STRIDE 64-bit words each (256
+// bytes apart): [0] sum of products, [1] largest row, [2] products of the heavy rows, [3] rows of A without a product,
+// [4 + c] rows of sort class c (the smallest that holds the row; 0: none does), then the most LDS that four rows from
+// a multiple of four on take where a wave sorts a row (sort_row_bytes); see analysis.hip.
 constexpr int ROW_TOTAL_SLOTS = 32;
-constexpr int ROW_TOTAL_STRIDE = 16;
+constexpr int ROW_TOTAL_STRIDE = 32;
+constexpr int ROW_TOTAL_CLASS = 4;
+constexpr int ROW_TOTAL_LDS = ROW_TOTAL_CLASS + SORT_CLASSES;
+static_assert(ROW_TOTAL_LDS < ROW_TOTAL_STRIDE, "a word per class");
 
 // Most workgroups of `threads` threads in one launch.  The runtime takes a grid's size in threads modulo 2^32 and reports
 // nothing (16 778 240 workgroups of 256 threads ran as 1024), so longer lists of rows go in several launches.
@@ -248,7 +262,7 @@ inline void launch_in_pieces(int64_t count, int rows_per_block, int threads, Go 
 hipError_t launch_validate(const Csr &B, int32_t *flags, unsigned long long *near_pairs, hipStream_t s);
 hipError_t launch_row_products(const Csr &A, const int64_t *b_rp, int64_t b_rows, int64_t *prod, int32_t *maxb,
                                unsigned long long *totals, int32_t *flags, bool validate, unsigned long long *near_pairs,
-                               hipStream_t s);
+                               unsigned long long *zero, int64_t zero_words, int vbytes, hipStream_t s);
 hipError_t launch_publish_totals(const unsigned long long *totals, const int32_t *flags, int64_t *out, hipStream_t s);
 hipError_t launch_hll_sketch(const Csr &B, int m, uint8_t *sketches, int lanes_div, hipStream_t s);
 hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const int64_t *rows, int64_t n_rows,
@@ -293,6 +307,9 @@ hipError_t launch_place(int64_t m, const int32_t *in, int64_t *tile_sum, int64_t
                         unsigned long long *bin_cursor, int32_t *bin_rows, hipStream_t s);
 hipError_t launch_count_rows(int64_t m, const int32_t *nnz1, const int32_t *nnz2, int32_t *final_nnz, int64_t *tile_sum,
                              unsigned long long *overflowed, const uint8_t *bin_of_row, unsigned long long *work, hipStream_t s);
+hipError_t launch_row_stats(int64_t m, int mode, double coef, double bound_coef, int64_t n_cols, const int64_t *prod,
+                            const int64_t *a_rp, const int64_t *c_rp, unsigned long long *bin_count,
+                            unsigned long long *bin_prod, unsigned long long *work, hipStream_t s);
 int64_t scan_tmp_elems(int64_t n);   // words of tile sums for n rows
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s);
 
@@ -368,6 +385,27 @@ struct SortLaunch {
     int32_t *row_nnz;
 };
 hipError_t launch_numeric_sort(const Csr &A, const Csr &B, int dtype, const SortLaunch &l, hipStream_t s);
+
+// placed.hip
+// Rows of a unit where all rows are placed as rows of a class: 256 / G for the classes below a wave, else the four of a
+// workgroup.
+constexpr int kPlacedRows[SORT_CLASSES] = {0, 32, 16, 16, 16, 8, 8, 4, 4, 4, 4, 4, 4};
+inline int64_t placed_units(int64_t m, int cls) { return (m + kPlacedRows[cls] - 1) / kPlacedRows[cls]; }
+struct PlacedLaunch {
+    int cls;                  // every row has at most this class's products and entries
+    const int64_t *prod;      // products per row
+    int pool;                 // LDS of a workgroup: the most that four rows from a multiple of four on take (classes of whole waves)
+    int64_t *c_rp;            // receives the row offsets of C
+    int32_t *out_col;
+    void *out_val;
+    int64_t slots;            // entries that fit into out_col / out_val
+    uint32_t *counts;         // placed_units words, zero
+    unsigned long long *places;   // the same
+    unsigned long long *total;    // receives the entries of C
+    int32_t *flags;           // |= 32: a wait ran out and the result is not complete
+};
+hipError_t launch_placed(const Csr &A, const Csr &B, int dtype, const PlacedLaunch &l, hipStream_t s);
+hipError_t launch_trim(int dtype, const int32_t *col, const void *val, int64_t n, int32_t *c_col, void *c_val, hipStream_t s);
 
 // compact.hip
 hipError_t launch_compact(int64_t m, int dtype, const int64_t *c_rp, const int32_t *nnz1, const int64_t *ptr1,

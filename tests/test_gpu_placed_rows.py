@@ -1,0 +1,140 @@
+"""Rows that are written to their place in C as they are sorted (placed.hip) against the CPU oracle and the general path:
+numbers of rows at the edges of the units and of the placing turns, every size of sort alone and all sizes in one matrix, rows of
+B in no order and with repeated columns, a reservation that turns out too small, and one of which little is used.  A call went
+this way when it shows no binning stage."""
+import numpy as np
+import pytest
+
+from oracle import spgemm as O
+from paper_2604_19004_amd.workloads import CSR
+from test_gpu_spgemm import check_result
+
+pytestmark = pytest.mark.gpu
+
+CLASSES = (32, 64, 96, 128, 192, 256, 384, 512, 768, 1024, 1536, 2048)
+
+
+@pytest.fixture(scope="module")
+def ob():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2604_19004_amd import binding
+    binding.load()
+    return binding
+
+
+def _csr(rows, cols, lists, rng, dtype):
+    ptr = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    idx = np.concatenate([np.asarray(x, dtype=np.int64) for x in lists]).astype(np.int32)
+    return CSR(rows, cols, ptr, idx, rng.uniform(-1, 1, idx.size).astype(dtype))
+
+
+def _b(rng, n, dtype, order):
+    """An empty row, then rows of 1 .. 64 entries at random columns and 64 rows of those lengths on 80 columns."""
+    lists = [[]]
+    for low, span in ((0, n), (n - 80, 80)):
+        for length in range(1, 65):
+            cols = low + rng.choice(span, length, replace=order == "repeated")
+            lists.append(cols if order == "unsorted" else np.sort(cols))
+    return _csr(len(lists), n, lists, rng, dtype)
+
+
+def _row(rng, total, most=64):
+    """Entries of A whose rows of B have `total` entries together."""
+    row = []
+    longest = max(1, min(64, -(-total // 30)))
+    while total > 0 and len(row) < most:
+        step = min(total, int(rng.integers(max(1, longest // 2), longest + 1)))
+        row.append(step + 64 * int(rng.integers(0, 2)))
+        total -= step
+    return row
+
+
+def _check(ob, A, B, label, placed=True, **options):
+    dA, dB = ob.to_device(A), ob.to_device(B)
+    ref = O.multiply_rows(A, B)
+    C, st = ob.spgemm(dA, dB, **options)
+    check_result(C, ref, A, f"{label} {options}")
+    assert (st["stage_ms"]["binning"] == 0.0) == placed, (label, st["stage_ms"])
+    with_products = O.row_products(A, B) > 0
+    assert st["nnz_c"] == ref.col_idx.size == sum(st["bin_nnz_c"])
+    assert sum(st["rows_per_bin"]) == int(with_products.sum())
+    assert sum(st["bin_products"]) == st["products"]
+    assert sum(st["bin_nnz_a"]) == int(np.diff(A.row_ptr)[with_products].sum())
+    return C, st
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("order", ["sorted", "unsorted", "repeated"])
+@pytest.mark.parametrize("cap", CLASSES)
+def test_each_size_of_sort(ob, cap, order, dtype):
+    rng = np.random.default_rng(cap)
+    B = _b(rng, 5000, dtype, order)
+    smaller = ([0] + list(CLASSES))[CLASSES.index(cap)] + 1
+    most = 32 if cap == 32 else 64
+    for rows in (1, 5, 33, 300):
+        lists = [_row(rng, int(rng.integers(smaller, cap + 1)), most) for _ in range(rows)]
+        lists[0] = _row(rng, cap, most)
+        if rows > 1:
+            lists[-1] = [0, 0, 0]                      # entries, but no products
+            lists[rows // 2] = []
+        A = _csr(rows, B.rows, lists, rng, dtype)
+        C, st = _check(ob, A, B, f"{cap} products, {rows} rows", workflow=ob.WF_UPPER_BOUND)
+        general, st = ob.spgemm(ob.to_device(A), ob.to_device(B), workflow=ob.WF_UPPER_BOUND, compact_in_place=0)
+        assert st["stage_ms"]["binning"] > 0.0
+        for x, y in ((C.row_ptr, general.row_ptr), (C.col_idx, general.col_idx)):
+            assert bool((x == y).all())
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("most", [512, 1024, 1536, 2048])
+def test_all_sizes_in_one_matrix(ob, most, dtype):
+    rng = np.random.default_rng(most)
+    B = _b(rng, 30000, dtype, "sorted")
+    lists = [_row(rng, int(rng.choice([0, 1, 60, 130, 190, 250, 380, 500, 700, 1000, 1500, 2000]) % (most + 1))) for _ in range(3001)]
+    lists[7] = _row(rng, most)
+    A = _csr(len(lists), B.rows, lists, rng, dtype)
+    for wf in (ob.WF_UPPER_BOUND, ob.WF_AUTO):
+        _check(ob, A, B, f"up to {most} products", workflow=wf)
+    # a row with an entry more than the sort takes, or a product: the general way
+    for extra in ([0] * 65, _row(rng, 2048) + [1] if most == 2048 else [0] * 65):
+        A = _csr(len(lists) + 1, B.rows, lists + [extra], rng, dtype)
+        if len(extra) > 64 or O.row_products(A, B)[-1] > 2048:
+            _check(ob, A, B, "a row too long", placed=extra == [0] * 65, workflow=ob.WF_UPPER_BOUND)
+
+
+# units of 32, 16, 8 and 4 rows: around a wave of counts, the 1024 of a turn and several turns
+@pytest.mark.parametrize("units", [1, 63, 64, 65, 1023, 1024, 1025, 5000])
+@pytest.mark.parametrize("rows_per_unit, products", [(32, 20), (16, 60), (8, 150), (4, 300)])
+def test_numbers_of_units(ob, rows_per_unit, products, units):
+    rng = np.random.default_rng(units)
+    B = _b(rng, 900, np.float64, "sorted")
+    for rows in {units * rows_per_unit, units * rows_per_unit - rows_per_unit + 1}:
+        lists = [_row(rng, int(p), 32) for p in rng.integers(0, products + 1, rows)]
+        lists[0] = _row(rng, products, 32)
+        A = _csr(rows, B.rows, lists, rng, np.float64)
+        _check(ob, A, B, f"{units} units", workflow=ob.WF_UPPER_BOUND)
+
+
+def test_sample_that_promises_too_little(ob):
+    """The sampled rows' products fall on few columns and nobody else's do: C needs more than was reserved."""
+    rng = np.random.default_rng(4)
+    rows, n = 20000, 100000
+    lists = [np.sort(rng.choice(n, 32, replace=False)) for _ in range(200)] + [np.arange(32) for _ in range(200)]
+    B = _csr(400, n, lists, rng, np.float64)
+    sampled = np.zeros(rows, bool)
+    sampled[ob.sample_rows(rows)] = True
+    A = _csr(rows, 400, [rng.choice(200, 6, replace=False) + 200 * sampled[r] for r in range(rows)], rng, np.float64)
+    C, st = _check(ob, A, B, "misled sample", tuned_min_products=0.0)
+    assert st["sampled_rows"] == sampled.sum() and st["products"] / st["sampled_cr"] * 1.5 < st["nnz_c"]
+
+
+@pytest.mark.parametrize("columns, kept", [(40, False), (1000, True)])
+def test_what_c_keeps_of_the_reservation(ob, columns, kept):
+    rng = np.random.default_rng(columns)
+    B = _csr(500, columns, [np.sort(rng.choice(columns, 8, replace=False)) for _ in range(500)], rng, np.float32)
+    A = _csr(30000, 500, [rng.choice(500, 7, replace=False) for _ in range(30000)], rng, np.float32)
+    C, st = _check(ob, A, B, "reservation")
+    slots = C.col_idx.untyped_storage().nbytes() // 4
+    assert slots == (st["products"] if kept else st["nnz_c"])
+    assert slots <= st["nnz_c"] * 8 // 7 + 65536
