@@ -9,6 +9,8 @@
 // All kernels are HBM/L2-bound gathers; rows are mapped to groups of G lanes
 // (G a power of two <= 64 chosen from the average row length) so that short
 // rows do not leave most of a 64-wide wave idle.
+#include <type_traits>
+
 #include "ocean_internal.hpp"
 
 namespace ocean {
@@ -79,6 +81,7 @@ hipError_t launch_validate(const Csr &B, int32_t *flags, unsigned long long *nea
 // rows (n_long is odd, so that rows a power of two apart do not meet again) and takes the long ones among them one
 // after the other with all its threads.  A second launch for them cost matrices without any 5 us.
 constexpr int LONG_ROWS = 4;        // neighbouring rows that such a workgroup looks at together
+constexpr int WAVE_ROW = 2048;      // up to here a wave takes a long row of k_row_products, four turns of eight entries a lane
 
 static int long_row_blocks(int64_t rows)
 {
@@ -86,22 +89,33 @@ static int long_row_blocks(int64_t rows)
     return (int)(want < 1023 ? want : 1023) | 1;
 }
 
-// take(row) for every row of 0 .. rows - 1 that is_long names, by the whole workgroup of THREADS threads (uniform, barriers
-// allowed).  s_list: THREADS words, s_n: one.
-template <int THREADS = TPB, typename IsLong, typename Take>
-__device__ __forceinline__ void for_long_rows(int64_t rows, int n_long, int32_t *s_list, int *s_n, IsLong is_long, Take take)
+// take(row) for every row of 0 .. rows - 1 for which size(row) is 2, by the whole workgroup of THREADS threads (uniform,
+// barriers allowed), and take_wave(row) for those where it is 1, by one wave (0: not a long row).  s_list: THREADS words,
+// s_n: one.
+template <int THREADS = TPB, typename Size, typename TakeWave, typename Take>
+__device__ __forceinline__ void for_long_rows(int64_t rows, int n_long, int32_t *s_list, int *s_n, Size size, TakeWave take_wave,
+                                              Take take)
 {
     const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int64_t stretch = (int64_t)n_long * LONG_ROWS;
     const int64_t first = (int64_t)blockIdx.x * LONG_ROWS + tid % LONG_ROWS + (int64_t)(tid / LONG_ROWS) * stretch;
     for (int64_t base = 0; base < rows; base += stretch * (THREADS / LONG_ROWS)) {   // uniform
         if (tid == 0) *s_n = 0;
         __syncthreads();
         const int64_t r = base + first;
-        if (r < rows && is_long(r)) s_list[atomicAdd(s_n, 1)] = (int32_t)r;
+        const int of = r < rows ? size(r) : 0;
+        if (of != 0) s_list[atomicAdd(s_n, 1)] = of == 1 ? (int32_t)r : ~(int32_t)r;
         __syncthreads();
         const int n = *s_n;
-        for (int i = 0; i < n; ++i) take((int64_t)s_list[i]);
+        for (int i = 0, seen = 0; i < n; ++i) {   // uniform
+            const int32_t of_wave = __builtin_amdgcn_readfirstlane(s_list[i]);
+            if (of_wave >= 0 && seen++ % (THREADS / WAVE) == wave) take_wave((int64_t)of_wave);
+        }
+        for (int i = 0; i < n; ++i) {
+            const int32_t of_all = s_list[i];
+            if (of_all < 0) take((int64_t)~of_all);
+        }
         __syncthreads();
     }
 }
@@ -116,43 +130,71 @@ __device__ __forceinline__ void for_long_rows(int64_t rows, int n_long, int32_t 
 // ns each, and there is one set per workgroup: they are spread over ROW_TOTAL_SLOTS slots of 128 bytes (one
 // cache line each) by workgroup index and added up by whoever reads them (sum_row_totals on the host).
 // slot[0] += products, slot[1] = max(products of a row), slot[2] += products of the rows whose product count
-// exceeds heavy_from (the rows that outgrow the LDS hash tables), slot[3] += rows without products, and the rows of each
-// sort class, s_cls: words 3 .. of the slot.
-__device__ __forceinline__ void block_totals(long long tsum, long long tmax, long long theavy, long long *s_sum,
-                                             long long *s_max, long long *s_heavy, const unsigned int *s_cls,
-                                             int lds_most, unsigned long long *totals)
+// exceeds heavy_from (the rows that outgrow the LDS hash tables), slot[3] += rows without products, then the rows of each
+// sort class and the most LDS of four sorted rows (ROW_TOTAL_CLASS, ROW_TOTAL_LDS).  s_tot: the workgroup's own, summed in
+// LDS, so that its sums leave in one instruction.
+__device__ __forceinline__ void block_totals(long long tsum, long long tmax, long long theavy, int lds_most,
+                                             unsigned long long *s_tot, unsigned long long *totals)
 {
     const long long wsum = group_reduce_sum(tsum, WAVE);
     const long long wmax = group_reduce_max(tmax, WAVE);
     const long long wheavy = group_reduce_sum(theavy, WAVE);
-    const int w = threadIdx.x / WAVE;
-    if (lane_id() == 0) { s_sum[w] = wsum; s_max[w] = wmax; s_heavy[w] = wheavy; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        long long bs = 0, bm = 0, bh = 0;
-        for (int i = 0; i < TPB / WAVE; ++i) { bs += s_sum[i]; bm = s_max[i] > bm ? s_max[i] : bm; bh += s_heavy[i]; }
-        unsigned long long *slot = totals + (size_t)(blockIdx.x % ROW_TOTAL_SLOTS) * ROW_TOTAL_STRIDE;
-        if (bs) atomicAdd(&slot[0], (unsigned long long)bs);
-        if (bm) atomicMax(&slot[1], (unsigned long long)bm);
-        if (bh) atomicAdd(&slot[2], (unsigned long long)bh);
-    } else if (threadIdx.x >= WAVE && threadIdx.x < WAVE + 1 + SORT_CLASSES) {
-        const int c = threadIdx.x - WAVE;
-        unsigned long long *slot = totals + (size_t)(blockIdx.x % ROW_TOTAL_SLOTS) * ROW_TOTAL_STRIDE;
-        if (s_cls[c]) atomicAdd(&slot[ROW_TOTAL_CLASS - 1 + c], (unsigned long long)s_cls[c]);
-    }
     const int most = (int)wave_max_u32((uint32_t)lds_most);
-    if (lane_id() == 0 && most > 0)
-        atomicMax(&totals[(size_t)(blockIdx.x % ROW_TOTAL_SLOTS) * ROW_TOTAL_STRIDE + ROW_TOTAL_LDS], (unsigned long long)most);
+    if (lane_id() == 0) {
+        atomicAdd(&s_tot[0], (unsigned long long)wsum);
+        atomicMax(&s_tot[1], (unsigned long long)wmax);
+        atomicAdd(&s_tot[2], (unsigned long long)wheavy);
+        atomicMax(&s_tot[ROW_TOTAL_LDS], (unsigned long long)most);
+    }
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t <= ROW_TOTAL_LDS && s_tot[t] != 0ull) {
+        unsigned long long *slot = totals + (size_t)(blockIdx.x % ROW_TOTAL_SLOTS) * ROW_TOTAL_STRIDE;
+        if (t == 1 || t == ROW_TOTAL_LDS) atomicMax(&slot[t], s_tot[t]);
+        else atomicAdd(&slot[t], s_tot[t]);
+    }
 }
 
 // Smallest sort class that holds a row of pr products from ne entries, 0: none.
-__device__ __forceinline__ int smallest_sort_class(long long pr, long long ne)
+__device__ __forceinline__ int smallest_sort_class(int pr, int ne)
 {
-    int cls = 0;
+    static_assert(kSortClass[2].entries == kSortClass[SORT_CLASSES - 1].entries, "classes differ in entries below the second only");
+    int cls = 1;
 #pragma unroll
-    for (int c = SORT_CLASSES - 1; c >= 1; --c)
-        if (pr <= kSortClass[c].cap && ne <= kSortClass[c].entries) cls = c;
-    return cls;
+    for (int c = 1; c < SORT_CLASSES; ++c) cls += pr > kSortClass[c].cap;
+    if (cls == 1 && ne > kSortClass[1].entries) cls = 2;
+    return cls < SORT_CLASSES && ne <= kSortClass[2].entries ? cls : 0;
+}
+
+// Sum and maximum over every group of 2^GL lanes, in each of its lanes: swaps of neighbours, pairs, mirrored halves and rows
+// (data-parallel moves, no trip to LDS) up to 16 lanes.
+template <int GL>
+__device__ __forceinline__ void group_totals(unsigned long long &sum, uint32_t &most)
+{
+    auto step = [&](auto ctrl) {
+        constexpr int CTRL = decltype(ctrl)::value;
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)sum, CTRL, 0xf, 0xf, false);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(sum >> 32), CTRL, 0xf, 0xf, false);
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)most, CTRL, 0xf, 0xf, false);
+        sum += ((unsigned long long)hi << 32) | lo;
+        most = o > most ? o : most;
+    };
+    if constexpr (GL >= 1) step(std::integral_constant<int, 0xB1>());    // quad_perm [1,0,3,2]
+    if constexpr (GL >= 2) step(std::integral_constant<int, 0x4E>());    // quad_perm [2,3,0,1]
+    if constexpr (GL >= 3) step(std::integral_constant<int, 0x141>());   // row_half_mirror
+    if constexpr (GL >= 4) step(std::integral_constant<int, 0x140>());   // row_mirror
+    for (int off = 16; off < (1 << GL); off <<= 1) {
+        sum += __shfl_xor(sum, off, WAVE);
+        const uint32_t o = __shfl_xor(most, off, WAVE);
+        most = o > most ? o : most;
+    }
+}
+
+// Two neighbouring row offsets, in one load.
+typedef uint32_t RowEnds __attribute__((ext_vector_type(4), aligned(8)));
+__device__ __forceinline__ unsigned long long row_length(RowEnds e)
+{
+    return (((unsigned long long)e.w << 32) | e.z) - (((unsigned long long)e.y << 32) | e.x);
 }
 
 // bad_bit: bit of flags that any fault of A sets besides its own (0: none, and A's ends are not looked at).
@@ -160,24 +202,28 @@ __device__ __forceinline__ int smallest_sort_class(long long pr, long long ne)
 // are not long, so the long rows of a power-law matrix are not in it.  It decides nothing but which of two orderings of a
 // small hash table is used and, by a descending pair of columns in a sampled row, which sets bit 8, whether B's window
 // table is tried: never the result.
-__global__ void __launch_bounds__(TPB)
+//
+// What bounds it: a gather of two row offsets of B per entry of A, one line a lane, which the address unit takes one a cycle,
+// and for rows of few entries the instructions per row.  Offsets come in one 16-byte load instead of two of 8, totals of a row go
+// through lane moves instead of LDS, and a row's class is found in 32 bits.
+template <int GL>
+__global__ void __launch_bounds__(TPB, 8)
 k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, int64_t m, int64_t a_nnz,
-               const int64_t *__restrict__ b_rp, int64_t b_rows, int g_log2, int64_t long_from, int n_long,
+               const int64_t *__restrict__ b_rp, int64_t b_rows, int64_t long_from, int n_long,
                int64_t *__restrict__ prod, int32_t *__restrict__ maxb, unsigned long long *totals, int32_t *flags,
                int64_t heavy_from, int bad_bit, unsigned long long *near_pairs, unsigned long long *zero, int64_t zero_words,
                int vbytes)
 {
+    constexpr int G = 1 << GL;
+    constexpr int R = TPB >> GL;
     __shared__ unsigned int s_near, s_seen;
-    __shared__ unsigned int s_cls[1 + SORT_CLASSES];   // rows without products, rows of each sort class
-    __shared__ long long s_sum[TPB / WAVE];
-    __shared__ long long s_max[TPB / WAVE];
-    __shared__ long long s_heavy[TPB / WAVE];
+    __shared__ unsigned long long s_tot[ROW_TOTAL_LDS + 1];
+    __shared__ unsigned long long s_sum[TPB / WAVE];
+    __shared__ uint32_t s_max[TPB / WAVE];
     __shared__ int32_t s_list[TPB];
     __shared__ int s_n;
     const int tid = threadIdx.x;
-    const int G = 1 << g_log2;
-    const int R = TPB >> g_log2;
-    const int rl = tid >> g_log2;
+    const int rl = tid >> GL;
     const int sub = tid & (G - 1);
     const bool for_long = (int)blockIdx.x < n_long;   // uniform
     const int64_t block = (int64_t)blockIdx.x - n_long, blocks = (int64_t)gridDim.x - n_long;
@@ -186,61 +232,81 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
     long long tsum = 0, tmax = 0, theavy = 0;
     bool unsorted = false;
     int lds_most = 0;
-    if (tid < 1 + SORT_CLASSES) s_cls[tid] = 0u;
+    if (tid <= ROW_TOTAL_LDS) s_tot[tid] = 0ull;
     for (int64_t i = (int64_t)blockIdx.x * TPB + tid; i < zero_words; i += (int64_t)gridDim.x * TPB) zero[i] = 0ull;
     __syncthreads();
     bool bad = false, bad_rp = bad_bit != 0 && blockIdx.x == 0 && tid == 0 && (a_rp[0] != 0 || a_rp[m] != a_nnz);
-    // entries first, first + step, ... below e1: four independent chains (entry -> row offsets of B) in flight per lane;
+    // entries first, first + step, ... below e1: U independent chains (entry -> row offsets of B) in flight per lane;
     // reads are unconditional (index clamped) so that they are issued together
-    auto walk = [&](int64_t first, int64_t e1, int step, long long &p, long long &mx) {
-        for (int64_t e = first; e < e1; e += 4 * (int64_t)step) {
-            int32_t k[4];
-            bool ok[4];
+    auto walk = [&](auto depth, int64_t first, int64_t e1, int step, unsigned long long &p, uint32_t &mx) {
+        constexpr int U = decltype(depth)::value;
+        for (int64_t e = first; e < e1; e += U * (int64_t)step) {
+            int32_t k[U];
+            bool ok[U];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < U; ++i) {
                 const int64_t idx = e + (int64_t)i * step;
                 ok[i] = idx < e1;
                 k[i] = a_col[ok[i] ? idx : e];
-                if (sampling && ok[i] && idx + 1 < a_nnz) {
-                    const int32_t next = a_col[idx + 1];
-                    near += (uint32_t)(next - k[i] - 1) < 4u;
-                    ++seen;
-                    unsorted |= idx + 1 < e1 && next < k[i];
-                }
-                if ((uint32_t)k[i] >= (uint64_t)b_rows) { bad = true; k[i] = 0; ok[i] = false; }
             }
-            long long len[4];
+            if (sampling) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) len[i] = b_rows > 0 ? b_rp[k[i] + 1] - b_rp[k[i]] : 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (ok[i]) {
-                    p += len[i];
-                    mx = len[i] > mx ? len[i] : mx;
+                for (int i = 0; i < U; ++i) {
+                    const int64_t idx = e + (int64_t)i * step;
+                    if (ok[i] && idx + 1 < a_nnz) {
+                        const int32_t next = a_col[idx + 1];
+                        near += (uint32_t)(next - k[i] - 1) < 4u;
+                        ++seen;
+                        unsorted |= idx + 1 < e1 && next < k[i];
+                    }
                 }
+            }
+#pragma unroll
+            for (int i = 0; i < U; ++i)
+                if ((uint32_t)k[i] >= (uint64_t)b_rows) { bad = true; k[i] = 0; ok[i] = false; }
+            if (b_rows == 0) continue;   // uniform
+            RowEnds ends[U];
+#pragma unroll
+            for (int i = 0; i < U; ++i) ends[i] = *reinterpret_cast<const RowEnds *>(b_rp + k[i]);
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                const unsigned long long len = ok[i] ? row_length(ends[i]) : 0ull;
+                p += len;
+                const uint32_t most = len > 0x7fffffffull ? 0x7fffffffu : (uint32_t)len;
+                mx = most > mx ? most : mx;
             }
         }
     };
-    auto store = [&](int64_t row, long long ne, long long p, long long mx) {
-        prod[row] = p;
-        maxb[row] = (int32_t)(mx > 0x7fffffffLL ? 0x7fffffffLL : mx);
-        tsum += p;
-        tmax = p > tmax ? p : tmax;
-        theavy += p > heavy_from ? p : 0;
-        atomicAdd(&s_cls[p == 0 ? 0 : 1 + smallest_sort_class(p, ne)], 1u);
+    auto store = [&](int64_t row, int64_t ne, unsigned long long p, uint32_t mx) {
+        prod[row] = (int64_t)p;
+        maxb[row] = (int32_t)mx;
+        tsum += (long long)p;
+        tmax = (long long)p > tmax ? (long long)p : tmax;
+        theavy += (long long)p > heavy_from ? (long long)p : 0;
+        const int cls = p == 0 ? -1 : smallest_sort_class(p < (1u << 20) ? (int)p : 1 << 20, ne < (1 << 20) ? (int)ne : 1 << 20);
+        atomicAdd(&s_tot[ROW_TOTAL_CLASS + cls], 1ull);
     };
     if (for_long) {
         for_long_rows(m, n_long, s_list, &s_n,
                       [&](int64_t r) {
                           const int64_t e0 = a_rp[r], e1 = a_rp[r + 1];
-                          return e0 >= 0 && e1 <= a_nnz && e1 - e0 >= long_from;   // (others are reported below)
+                          if (e0 < 0 || e1 > a_nnz || e1 - e0 < long_from) return 0;   // (bad ones are reported below)
+                          return e1 - e0 < WAVE_ROW ? 1 : 2;
                       },
                       [&](int64_t row) {
-                          long long p = 0, mx = 0;
-                          walk(a_rp[row] + tid, a_rp[row + 1], TPB, p, mx);
-                          const long long wsum = group_reduce_sum(p, WAVE);
-                          const long long wmax = group_reduce_max(mx, WAVE);
-                          if (lane_id() == 0) { s_sum[tid / WAVE] = wsum; s_max[tid / WAVE] = wmax; }
+                          const int64_t e0 = a_rp[row], e1 = a_rp[row + 1];
+                          unsigned long long p = 0;
+                          uint32_t mx = 0;
+                          walk(std::integral_constant<int, 8>(), e0 + lane_id(), e1, WAVE, p, mx);
+                          group_totals<6>(p, mx);
+                          if (lane_id() == 0) store(row, e1 - e0, p, mx);
+                      },
+                      [&](int64_t row) {
+                          unsigned long long p = 0;
+                          uint32_t mx = 0;
+                          walk(std::integral_constant<int, 8>(), a_rp[row] + tid, a_rp[row + 1], TPB, p, mx);
+                          group_totals<6>(p, mx);
+                          if (lane_id() == 0) { s_sum[tid / WAVE] = p; s_max[tid / WAVE] = mx; }
                           __syncthreads();
                           if (tid == 0) {
                               p = mx = 0;
@@ -252,7 +318,8 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
     } else {
         for (int64_t base = block * R; base < m; base += blocks * R) {
             const int64_t row = base + rl;
-            long long p = 0, mx = 0;
+            unsigned long long p = 0;
+            uint32_t mx = 0;
             bool mine = row < m;
             int64_t ne = 0;
             if (mine) {
@@ -262,20 +329,21 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
                 if (e0 < 0 || e1 < e0 || e1 > a_nnz) { bad_rp = true; e0 = 0; e1 = 0; }
                 ne = e1 - e0;
                 mine = n_long == 0 || ne < long_from;   // uniform for the group
-                if (mine) walk(e0 + sub, e1, G, p, mx);
+                if (mine) walk(std::integral_constant<int, 4>(), e0 + sub, e1, G, p, mx);
             }
-            p = group_reduce_sum(p, G);
-            mx = group_reduce_max(mx, G);
+            group_totals<GL>(p, mx);
             if (mine && sub == 0) store(row, ne, p, mx);
-            if (G <= 16) {   // (more lanes: rows that a wave does not sort)
-                int lds = sort_row_bytes((int)(p < 2048 ? p : 2048), vbytes);
+            // (more lanes: rows that a wave does not sort; where no row of the wave has more than 256 products, four rows take
+            // the least there is, which the host knows)
+            if (GL <= 4 && __ballot(p > 256ull) != 0ull) {
+                int lds = sort_row_bytes(p < 2048ull ? (int)p : 2048, vbytes);
                 lds += __shfl_xor(lds, G, WAVE);
                 lds += __shfl_xor(lds, 2 * G, WAVE);
                 lds_most = lds > lds_most ? lds : lds_most;
             }
         }
     }
-    block_totals(tsum, tmax, theavy, s_sum, s_max, s_heavy, s_cls, lds_most, totals);
+    block_totals(tsum, tmax, theavy, lds_most, s_tot, totals);
     if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(flags, 4 | bad_bit);
     if (__ballot(bad_rp) != 0 && lane_id() == 0) atomicOr(flags, 1);
     if (__ballot(unsorted) != 0 && lane_id() == 0) atomicOr(flags, 8);
@@ -309,8 +377,10 @@ hipError_t launch_row_products(const Csr &A, const int64_t *b_rp, int64_t b_rows
     int64_t blocks = (A.rows + R - 1) / R;
     if (blocks > 2048) blocks = 2048;
     const int n_long = A.nnz >= long_from ? long_row_blocks(A.rows) : 0;
-    hipLaunchKernelGGL(k_row_products, dim3((unsigned)(blocks + n_long)), dim3(TPB), 0, s, A.rp, A.col, A.rows, A.nnz, b_rp,
-                       b_rows, g_log2, long_from, n_long, prod, maxb, totals, flags, heavy_from, validate ? 1 : 0, near_pairs, zero,
+    const auto kernel = g_log2 == 1 ? k_row_products<1> : g_log2 == 2 ? k_row_products<2> : g_log2 == 3 ? k_row_products<3>
+                        : g_log2 == 4 ? k_row_products<4> : g_log2 == 5 ? k_row_products<5> : k_row_products<6>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks + n_long)), dim3(TPB), 0, s, A.rp, A.col, A.rows, A.nnz, b_rp,
+                       b_rows, long_from, n_long, prod, maxb, totals, flags, heavy_from, validate ? 1 : 0, near_pairs, zero,
                        zero_words, vbytes);
     return hipGetLastError();
 }
@@ -401,7 +471,8 @@ k_hll_sketch(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, in
         __syncthreads();
     };
     if ((int)blockIdx.x < n_long) {   // uniform
-        for_long_rows(rows, n_long, s_long, &s_nlong, [&](int64_t r) { return rp[r + 1] - rp[r] >= long_from; }, take);
+        for_long_rows(rows, n_long, s_long, &s_nlong, [&](int64_t r) { return rp[r + 1] - rp[r] >= long_from ? 2 : 0; },
+                      [](int64_t) {}, take);
         return;
     }
     for (int64_t base = ((int64_t)blockIdx.x - n_long) * R; base < rows; base += ((int64_t)gridDim.x - n_long) * R) {   // uniform
@@ -597,7 +668,8 @@ k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
         __syncthreads();
     };
     if ((int)blockIdx.x < n_long) {   // uniform (all rows, no row list)
-        for_long_rows(n_rows, n_long, s_long, &s_nlong, [&](int64_t r) { return a_rp[r + 1] - a_rp[r] >= long_from; }, take);
+        for_long_rows(n_rows, n_long, s_long, &s_nlong, [&](int64_t r) { return a_rp[r + 1] - a_rp[r] >= long_from ? 2 : 0; },
+                      [](int64_t) {}, take);
         return;
     }
     const int64_t gt = ((int64_t)blockIdx.x - (n_long > 0 ? n_long : 0)) * blockDim.x + threadIdx.x;
@@ -645,7 +717,7 @@ k_hll_merge_long(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a
     const int tid = threadIdx.x;
     const int slice = tid & (L - 1), wave = tid / WAVE;
     for_long_rows<LONG_THREADS>(
-        n_rows, (int)gridDim.x, s_list, &s_n, [&](int64_t r) { return a_rp[r + 1] - a_rp[r] >= long_from; },
+        n_rows, (int)gridDim.x, s_list, &s_n, [&](int64_t r) { return a_rp[r + 1] - a_rp[r] >= long_from ? 2 : 0; }, [](int64_t) {},
         [&](int64_t row) {
             uint64_t acc = 0;
             long long blen = 0;

@@ -351,7 +351,8 @@ int run_analysis(Ctx &c, Work &w, const Csr &A, const Csr &B, int vbytes, bool v
     RowTotals tot;
     sum_row_totals(c.h, tot);
     std::memcpy(w.class_rows, tot + ROW_TOTAL_CLASS, sizeof(w.class_rows));
-    w.four_rows_lds = (int)tot[ROW_TOTAL_LDS];
+    w.four_rows_lds = 4 * sort_row_bytes(256, vbytes);   // (at least, see k_row_products)
+    if (tot[ROW_TOTAL_LDS] > (unsigned long long)w.four_rows_lds) w.four_rows_lds = (int)tot[ROW_TOTAL_LDS];
     if (c.h->flags & 1) return fail(OCEAN_EINVAL, "A is not a valid CSR matrix (row offsets or column ids out of range)");
     if (c.h->flags & 2) return fail(OCEAN_EINVAL, "B is not a valid CSR matrix (row offsets or column ids out of range)");
     if (c.h->flags & 4) return fail(OCEAN_EINVAL, "a column id of A is outside [0, rows(B))");
