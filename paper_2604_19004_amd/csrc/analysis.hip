@@ -78,15 +78,17 @@ hipError_t launch_validate(const Csr &B, int32_t *flags, unsigned long long *nea
 // The long rows of a power-law matrix sit side by side (their numbers share bit patterns), so the workgroup that meets
 // them in its stretch of rows is the whole kernel's time.  The kernels below therefore leave them to workgroups of their
 // own, the first n_long of the same launch: workgroup b of them looks at rows 4 b .. 4 b + 3 of every stretch of 4 n_long
-// rows (n_long is odd, so that rows a power of two apart do not meet again) and takes the long ones among them one
-// after the other with all its threads.  A second launch for them cost matrices without any 5 us.
+// rows and takes the long ones among them.  n_long is a prime and not near a power of two: the long rows of a power-law matrix
+// have few one bits in their numbers, and of the 3981 rows of 256 entries and more of R-MAT scale 18 one workgroup of 1023 had
+// 35, one of 997 has 12.  A second launch for them cost matrices without any 5 us.
 constexpr int LONG_ROWS = 4;        // neighbouring rows that such a workgroup looks at together
 constexpr int WAVE_ROW = 2048;      // up to here a wave takes a long row of k_row_products, four turns of eight entries a lane
 
 static int long_row_blocks(int64_t rows)
 {
-    const int64_t want = rows / 16;
-    return (int)(want < 1023 ? want : 1023) | 1;
+    for (int n : {997, 499, 251, 127, 61, 31, 13, 7, 3})
+        if ((int64_t)n * 16 <= rows) return n;
+    return 1;
 }
 
 // take(row) for every row of 0 .. rows - 1 for which size(row) is 2, by the whole workgroup of THREADS threads (uniform,
@@ -534,15 +536,50 @@ hipError_t launch_hll_sketch(const Csr &B, int m, uint8_t *sketches, int lanes_d
 }
 
 // -------------------------------------------------------------- HLL merge
-// Registers are below 128, so a byte-wise maximum of eight registers is a few
-// 64-bit integer operations: (a|0x80)-b keeps bit 7 of a byte set exactly
-// when a >= b, and no borrow crosses a byte.
-__device__ __forceinline__ uint64_t bytemax8(uint64_t a, uint64_t b)
+// Sixteen registers of a sketch, as they are loaded and stored (sketches may come from a caller: 8-byte alignment), and the
+// maxima of many such: the packed 16-bit maximum orders by the upper byte, so one of the words as they are gives the odd
+// registers' maxima and one of the words without the upper bytes the even registers', three instructions for four registers.
+typedef uint32_t Regs16 __attribute__((ext_vector_type(4), aligned(8)));
+typedef unsigned short Pair16 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t max16x2(uint32_t a, uint32_t b)
 {
-    const uint64_t H = 0x8080808080808080ull;
-    const uint64_t ge = (((a | H) - b) & H) >> 7;
-    const uint64_t mask = ge * 0xFFull;
-    return (a & mask) | (b & ~mask);
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(Pair16, a), __builtin_bit_cast(Pair16, b)));
+}
+struct RegMax {
+    uint32_t odd[4] = {0u, 0u, 0u, 0u}, even[4] = {0u, 0u, 0u, 0u};
+    __device__ __forceinline__ void add(Regs16 r)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            odd[i] = max16x2(odd[i], r[i]);
+            even[i] = max16x2(even[i], r[i] & 0x00ff00ffu);
+        }
+    }
+    __device__ __forceinline__ Regs16 get() const
+    {
+        Regs16 r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = (odd[i] & 0xff00ff00u) | even[i];
+        return r;
+    }
+};
+__device__ __forceinline__ Regs16 max_regs(Regs16 a, Regs16 b)
+{
+    RegMax m;
+    m.add(a);
+    m.add(b);
+    return m.get();
+}
+// Maxima over lanes first, first + step, .. up to `lanes` (powers of two) that hold the same registers, in each of them.
+__device__ __forceinline__ Regs16 lanes_max(Regs16 r, int step, int lanes)
+{
+    for (int off = step; off < lanes; off <<= 1) {
+        Regs16 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = (uint32_t)__shfl_xor((int)r[i], off, WAVE);
+        r = max_regs(r, o);
+    }
+    return r;
 }
 
 __device__ __forceinline__ double hll_alpha(int m)
@@ -550,38 +587,39 @@ __device__ __forceinline__ double hll_alpha(int m)
     return m == 32 ? 0.697 : m == 64 ? 0.709 : 0.7213 / (1.0 + 1.079 / (double)m);
 }
 
-// One group of G lanes per selected row of A; L = M/8 lanes cover one sketch
-// (8 registers per lane in a 64-bit word) so G/L entries of the row are
-// merged at once.  Each 64-byte sketch of B is read as one coalesced line.
-// A row of MG_LONG or more entries is left to the whole workgroup (TPB / L entries at once), which takes the
-// long rows of its groups one after the other: on a power-law matrix a sampled row of tens of thousands of
-// entries, merged by one group, was most of the sampled merge's time.  "Long" is long_from entries or more: 2048
-// or eight times the average row of A, whichever is more (see k_hll_sketch).
-// n_long: workgroups for long rows at the front of the grid; 0: the workgroup that meets a long row takes it; -1: long rows
-// are left out.
+// One group of G lanes per selected row of A; L = M/16 lanes cover one sketch (16 registers per lane) so G/L entries of the
+// row are merged at once.  Each 64-byte sketch of B is read as one coalesced line.  What bounds it is the latency of the
+// chain offsets -> entries -> sketches and the part of the sketches that misses the L2 (with 8 registers a lane and the
+// maximum in 64-bit arithmetic it was instructions as well: all rows of R-MAT scale 18 with 64 registers, 4 M sketches,
+// 304 us, now 150 in both launches).
+// Long rows: long_from entries or more.  Where all rows of a matrix that is or may be skewed are merged, n_long workgroups
+// at the front of the grid take them, a wave each up to huge_from entries and by all threads from there on, or those are
+// left to k_hll_merge_long (huge_here false).  With n_long = 0 the workgroup that meets a long row takes it.
 constexpr int MG_LONG = 2048;
+constexpr int MG_SKEWED = 64;
+constexpr int MG_WAVE = 1024;    // a wave takes up to 64 entries a turn with 64 registers, and 16 turns are 20 us
 
-// Entries first, first + step, ... of a row, for one slice (8 registers) of the sketch: U per lane and turn
+// Entries first, first + step, ... of a row, for one slice (16 registers) of the sketch: U per lane and turn
 // (unconditional reads, index clamped; merging a sketch twice is harmless), so that the dependent loads entry ->
 // sketch of U entries overlap.
 template <int L, int U>
 __device__ __forceinline__ void hll_walk(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
                                          const uint64_t *__restrict__ sk, const int64_t *__restrict__ b_rp, int64_t row,
-                                         int slice, int first, int step, uint64_t &acc, long long &blen_max)
+                                         int slice, int first, int step, RegMax &acc, long long &blen_max)
 {
     const int64_t e1 = a_rp[row + 1];
     for (int64_t e = a_rp[row] + first; e < e1; e += U * (int64_t)step) {
         int32_t k[U];
-        uint64_t word[U];
+        Regs16 regs[U];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
             const int64_t q = e + (int64_t)i * step;
             k[i] = a_col[q < e1 ? q : e1 - 1];
         }
 #pragma unroll
-        for (int i = 0; i < U; ++i) word[i] = sk[(int64_t)k[i] * L + slice];
+        for (int i = 0; i < U; ++i) regs[i] = *reinterpret_cast<const Regs16 *>(sk + ((int64_t)k[i] * L + slice) * 2);
 #pragma unroll
-        for (int i = 0; i < U; ++i) acc = bytemax8(acc, word[i]);
+        for (int i = 0; i < U; ++i) acc.add(regs[i]);
         if (b_rp != nullptr && slice == 0) {
 #pragma unroll
             for (int i = 0; i < U; ++i) {
@@ -592,18 +630,19 @@ __device__ __forceinline__ void hll_walk(const int64_t *__restrict__ a_rp, const
     }
 }
 
-// L consecutive lanes hold the merged sketch of slot t (row `row`), 8 registers each: estimate and store.
+// L consecutive lanes hold the merged sketch of slot t (row `row`), 16 registers each: estimate and store.  (Sums of up to
+// 128 powers of two from 2^-33 on are exact, in whatever order.)
 template <int M>
-__device__ __forceinline__ void hll_finish(uint64_t acc, long long blen_max, int64_t t, int64_t row, int slice, bool write,
+__device__ __forceinline__ void hll_finish(Regs16 acc, long long blen_max, int64_t t, int64_t row, int slice, bool write,
                                            const int64_t *__restrict__ prod, const int32_t *__restrict__ maxb,
                                            int64_t b_cols, double *__restrict__ est, uint64_t *__restrict__ merged)
 {
-    constexpr int L = M / 8;
+    constexpr int L = M / 16;
     double ssum = 0.0;
     int zeros = 0;
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        const unsigned r = (unsigned)(acc >> (8 * b)) & 0xFFu;
+    for (int b = 0; b < 16; ++b) {
+        const unsigned r = (acc[b / 4] >> (8 * (b % 4))) & 0xFFu;
         ssum += __longlong_as_double((long long)(1023 - (int)r) << 52);  // 2^-r, exact
         zeros += (r == 0);
     }
@@ -612,7 +651,7 @@ __device__ __forceinline__ void hll_finish(uint64_t acc, long long blen_max, int
         zeros += __shfl_xor(zeros, off, WAVE);
     }
     if (write) {
-        if (merged != nullptr) merged[t * L + slice] = acc;
+        if (merged != nullptr) *reinterpret_cast<Regs16 *>(merged + (t * L + slice) * 2) = acc;
         if (slice == 0) {
             const double dm = (double)M;
             double e = hll_alpha(M) * dm * dm / ssum;
@@ -629,50 +668,74 @@ __device__ __forceinline__ void hll_finish(uint64_t acc, long long blen_max, int
     }
 }
 
+// A row by a whole workgroup of THREADS threads.  s_regs: 4 words per lane of a sketch and wave, s_blen: one word per wave.
+template <int M, int THREADS, int U>
+__device__ __forceinline__ void hll_row_by_all(Regs16 (*s_regs)[M / 16], long long *s_blen, const int64_t *__restrict__ a_rp,
+                                               const int32_t *__restrict__ a_col, const uint64_t *__restrict__ sk, int64_t t,
+                                               int64_t row, const int64_t *__restrict__ prod, const int32_t *__restrict__ maxb,
+                                               const int64_t *__restrict__ b_rp, int64_t b_cols, double *__restrict__ est,
+                                               uint64_t *__restrict__ merged)
+{
+    constexpr int L = M / 16, NW = THREADS / WAVE;
+    const int tid = threadIdx.x, slice = tid & (L - 1), wave = tid / WAVE;
+    RegMax acc;
+    long long blen = 0;
+    hll_walk<L, U>(a_rp, a_col, sk, b_rp, row, slice, tid / L, THREADS / L, acc, blen);
+    const Regs16 mine = lanes_max(acc.get(), L, WAVE);
+    blen = group_reduce_max(blen, WAVE);
+    if (lane_id() < L) s_regs[wave][lane_id()] = mine;
+    if (lane_id() == 0) s_blen[wave] = blen;
+    __syncthreads();
+    if (tid < WAVE) {   // (the whole first wave: lane swaps)
+        RegMax all;
+        long long longest = 0;
+        for (int w = 0; w < NW; ++w) {
+            all.add(s_regs[w][slice]);
+            longest = s_blen[w] > longest ? s_blen[w] : longest;
+        }
+        hll_finish<M>(all.get(), longest, t, row, slice, tid < L, prod, maxb, b_cols, est, merged);
+    }
+    __syncthreads();
+}
+
 // (8: with the code for long rows beside it the compiler would take 96 registers and leave 5 waves per SIMD; 10 % slower
 // on 256 000 rows of 34 entries)
 template <int M>
 __global__ void __launch_bounds__(TPB, 8)
 k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
             const uint64_t *__restrict__ sk, const int64_t *__restrict__ rows, int64_t n_rows, int g_log2,
-            int64_t long_from, int n_long, const int64_t *__restrict__ prod, const int32_t *__restrict__ maxb, const int64_t *__restrict__ b_rp,
+            int64_t long_from, int64_t huge_from, bool huge_here, int n_long, const int64_t *__restrict__ prod,
+            const int32_t *__restrict__ maxb, const int64_t *__restrict__ b_rp,
             int64_t b_cols, double *__restrict__ est, uint64_t *__restrict__ merged)
 {
-    constexpr int L = M / 8;
+    constexpr int L = M / 16;
     __shared__ int32_t s_long[TPB];   // (slot of the row, i.e. its position among the selected rows)
     __shared__ int s_nlong;
-    __shared__ uint64_t s_acc[TPB];
-    __shared__ long long s_blen[TPB / L];
+    __shared__ Regs16 s_regs[TPB / WAVE][L];
+    __shared__ long long s_blen[TPB / WAVE];
     const int G = 1 << g_log2;  // >= L
-    // a long row, by the whole workgroup
     auto take = [&](int64_t t2) {
-        const int64_t row2 = rows ? rows[t2] : t2;
-        const int wslice = (int)threadIdx.x & (L - 1), wpart = (int)threadIdx.x / L;
-        uint64_t a2 = 0;
-        long long b2 = 0;
-        hll_walk<L, 4>(a_rp, a_col, sk, b_rp, row2, wslice, wpart, TPB / L, a2, b2);
-        s_acc[threadIdx.x] = a2;
-        if (wslice == 0) s_blen[wpart] = b2;
-        __syncthreads();
-        // the first L lanes fold the partial sketches of the TPB / L parts
-        uint64_t f = 0;
-        long long fb = 0;
-        if (threadIdx.x < L) {
-            for (int p = 0; p < TPB / L; ++p) {
-                f = bytemax8(f, s_acc[p * L + threadIdx.x]);
-                fb = s_blen[p] > fb ? s_blen[p] : fb;
-            }
-        }
-        if (threadIdx.x < WAVE)   // (whole first wave: lane swaps)
-            hll_finish<M>(f, fb, t2, row2, (int)threadIdx.x & (L - 1), threadIdx.x < L, prod, maxb, b_cols, est, merged);
-        __syncthreads();
+        hll_row_by_all<M, TPB, 4>(s_regs, s_blen, a_rp, a_col, sk, t2, rows ? rows[t2] : t2, prod, maxb, b_rp, b_cols, est, merged);
     };
     if ((int)blockIdx.x < n_long) {   // uniform (all rows, no row list)
-        for_long_rows(n_rows, n_long, s_long, &s_nlong, [&](int64_t r) { return a_rp[r + 1] - a_rp[r] >= long_from ? 2 : 0; },
-                      [](int64_t) {}, take);
+        for_long_rows(n_rows, n_long, s_long, &s_nlong,
+                      [&](int64_t r) {
+                          const int64_t ne = a_rp[r + 1] - a_rp[r];
+                          return ne < long_from ? 0 : ne < huge_from ? 1 : huge_here ? 2 : 0;
+                      },
+                      [&](int64_t row) {
+                          const int lane = lane_id();
+                          RegMax acc;
+                          long long blen = 0;
+                          hll_walk<L, 4>(a_rp, a_col, sk, b_rp, row, lane & (L - 1), lane / L, WAVE / L, acc, blen);
+                          const Regs16 all = lanes_max(acc.get(), L, WAVE);
+                          if (b_rp != nullptr) blen = group_reduce_max(blen, WAVE);
+                          hll_finish<M>(all, blen, row, row, lane & (L - 1), lane < L, prod, maxb, b_cols, est, merged);
+                      },
+                      take);
         return;
     }
-    const int64_t gt = ((int64_t)blockIdx.x - (n_long > 0 ? n_long : 0)) * blockDim.x + threadIdx.x;
+    const int64_t gt = ((int64_t)blockIdx.x - n_long) * blockDim.x + threadIdx.x;
     const int64_t t = gt >> g_log2;
     const int sub = (int)(gt & (G - 1));
     if (threadIdx.x == 0) s_nlong = 0;
@@ -680,7 +743,7 @@ k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
     const int slice = sub & (L - 1);
     const int part = sub / L;
     const int parts = G / L;
-    uint64_t acc = 0;
+    RegMax acc;
     long long blen_max = 0;
     int64_t row = -1;
     bool mine = false;
@@ -690,53 +753,32 @@ k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
         if (mine) hll_walk<L, 4>(a_rp, a_col, sk, b_rp, row, slice, part, parts, acc, blen_max);
         else if (n_long == 0 && sub == 0) s_long[atomicAdd(&s_nlong, 1)] = (int32_t)t;
     }
-    for (int off = L; off < G; off <<= 1) acc = bytemax8(acc, __shfl_xor((unsigned long long)acc, off, WAVE));
+    const Regs16 all = lanes_max(acc.get(), L, G);
     if (b_rp != nullptr) blen_max = group_reduce_max(blen_max, G);
-    hll_finish<M>(acc, blen_max, t, row, slice, mine && part == 0, prod, maxb, b_cols, est, merged);
+    hll_finish<M>(all, blen_max, t, row, slice, mine && part == 0, prod, maxb, b_cols, est, merged);
     __syncthreads();
     const int nlong = s_nlong;
     for (int i = 0; i < nlong; ++i) take((int64_t)s_long[i]);   // uniform
 }
 
-// The long rows of a merge over all rows of a large matrix, a workgroup of 1024 threads on one after the other: a row of
-// 28 000 entries, four in flight per lane, takes a workgroup of 256 threads 290 us (R-MAT scale 18: whole estimate 641 us,
-// 480 with this kernel), and a launch is 5.  Rows are spread over the workgroups as in for_long_rows.
+// The rows of huge_from entries and more in a merge over all rows of a large matrix, a workgroup of 1024 threads on one after
+// the other: a row of 28 000 entries, four in flight per lane, takes a workgroup of 256 threads 100 us, and a launch is
+// 5.  Rows are spread over the workgroups as in for_long_rows.
 constexpr int LONG_THREADS = 1024;
 template <int M>
 __global__ void __launch_bounds__(LONG_THREADS)
 k_hll_merge_long(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, const uint64_t *__restrict__ sk,
-                 int64_t n_rows, int64_t long_from, const int64_t *__restrict__ prod, const int32_t *__restrict__ maxb,
+                 int64_t n_rows, int64_t huge_from, const int64_t *__restrict__ prod, const int32_t *__restrict__ maxb,
                  const int64_t *__restrict__ b_rp, int64_t b_cols, double *__restrict__ est, uint64_t *__restrict__ merged)
 {
-    constexpr int L = M / 8;
-    constexpr int NW = LONG_THREADS / WAVE;
-    __shared__ uint64_t s_acc[NW][L];
-    __shared__ long long s_blen[NW];
+    __shared__ Regs16 s_regs[LONG_THREADS / WAVE][M / 16];
+    __shared__ long long s_blen[LONG_THREADS / WAVE];
     __shared__ int32_t s_list[LONG_THREADS];
     __shared__ int s_n;
-    const int tid = threadIdx.x;
-    const int slice = tid & (L - 1), wave = tid / WAVE;
     for_long_rows<LONG_THREADS>(
-        n_rows, (int)gridDim.x, s_list, &s_n, [&](int64_t r) { return a_rp[r + 1] - a_rp[r] >= long_from ? 2 : 0; }, [](int64_t) {},
+        n_rows, (int)gridDim.x, s_list, &s_n, [&](int64_t r) { return a_rp[r + 1] - a_rp[r] >= huge_from ? 2 : 0; }, [](int64_t) {},
         [&](int64_t row) {
-            uint64_t acc = 0;
-            long long blen = 0;
-            hll_walk<L, 4>(a_rp, a_col, sk, b_rp, row, slice, tid / L, LONG_THREADS / L, acc, blen);
-            for (int off = L; off < WAVE; off <<= 1) acc = bytemax8(acc, __shfl_xor((unsigned long long)acc, off, WAVE));
-            blen = group_reduce_max(blen, WAVE);
-            if (lane_id() < L) s_acc[wave][lane_id()] = acc;
-            if (lane_id() == 0) s_blen[wave] = blen;
-            __syncthreads();
-            if (tid < WAVE) {   // (the whole first wave: lane swaps)
-                uint64_t f = 0;
-                long long fb = 0;
-                for (int w = 0; w < NW; ++w) {
-                    f = bytemax8(f, s_acc[w][slice]);
-                    fb = s_blen[w] > fb ? s_blen[w] : fb;
-                }
-                hll_finish<M>(f, fb, row, row, slice, tid < L, prod, maxb, b_cols, est, merged);
-            }
-            __syncthreads();
+            hll_row_by_all<M, LONG_THREADS, 4>(s_regs, s_blen, a_rp, a_col, sk, row, row, prod, maxb, b_rp, b_cols, est, merged);
         });
 }
 
@@ -745,19 +787,20 @@ hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const 
                             double *est, uint8_t *merged, int lanes_div, hipStream_t s)
 {
     if (n_rows == 0) return hipSuccess;
-    const int L = m / 8;
+    const int L = m / 16;
     const double avg = A.rows ? (double)A.nnz / (double)A.rows : 1.0;
-    // All rows of a matrix that is or may be skewed: the long rows go to workgroups of their own (see k_hll_sketch), so
-    // the others can have an eighth of the lanes (four entries in flight per lane, and twice the rows).  R-MAT scale 18,
-    // 64 registers: 355 us with a wave per row and the long rows by the workgroup that met them; the gather of 4 M
-    // sketches of 64 bytes at the 1.2 TB/s this GPU reaches for such pieces is 210 us.
+    // All rows of a matrix that is or may be skewed: the long rows go to waves and workgroups of their own, so the others can
+    // have an eighth of the lanes (four entries in flight per lane, and twice the rows).
     const bool spread = lanes_div == 1 && rows == nullptr;
     int g_log2 = ilog2_ceil(avg * L / (double)(spread ? 8 : lanes_div), 0, 6);   // (lanes_div: see launch_hll_sketch)
     while ((1 << g_log2) < L) ++g_log2;
     const uint64_t *sk = reinterpret_cast<const uint64_t *>(sketches);
     uint64_t *mg = reinterpret_cast<uint64_t *>(merged);
-    const int64_t least = spread ? LONG_SKEWED : MG_LONG;
-    const int64_t long_from = 8.0 * avg > (double)least ? (int64_t)(8.0 * avg) : least;
+    // (R-MAT scale 18, 64 registers, both launches: long from 8 times the average row on 160 us, from 4 times 150, from twice 155)
+    const double times = spread ? 4.0 : 8.0;
+    const int64_t least = spread ? MG_SKEWED : MG_LONG;
+    const int64_t long_from = times * avg > (double)least ? (int64_t)(times * avg) : least;
+    const int64_t huge_from = long_from > MG_WAVE ? long_from : MG_WAVE;
     const bool own_launch = spread && A.nnz >= (1 << 20);
     const int rows_per_block = TPB >> g_log2;
     const auto kernel = m == 32 ? k_hll_merge<32> : m == 64 ? k_hll_merge<64> : k_hll_merge<128>;
@@ -766,20 +809,18 @@ hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const 
     const int64_t most = (most_blocks(TPB) - 1024) * rows_per_block;
     for (int64_t t0 = 0; t0 < n_rows; t0 += most) {
         const int64_t n = n_rows - t0 < most ? n_rows - t0 : most;
-        const int n_long = own_launch ? -1 : spread && A.nnz >= long_from ? long_row_blocks(n) : 0;
-        const int64_t blocks = (n + rows_per_block - 1) / rows_per_block + (n_long > 0 ? n_long : 0);
+        const int n_long = spread && A.nnz >= long_from ? long_row_blocks(n) : 0;
+        const int64_t blocks = (n + rows_per_block - 1) / rows_per_block + n_long;
         const int64_t r0 = rows ? 0 : t0;   // (without a list, slot t is row t: the rows' own arrays move along)
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp + r0, A.col, sk, rows ? rows + t0 : nullptr, n,
-                           g_log2, long_from, n_long, prod ? prod + r0 : nullptr, maxb ? maxb + r0 : nullptr, b_rp, b_cols,
-                           est + t0, mg ? mg + t0 * L : nullptr);
+                           g_log2, long_from, huge_from, !own_launch, n_long, prod ? prod + r0 : nullptr, maxb ? maxb + r0 : nullptr,
+                           b_rp, b_cols, est + t0, mg ? mg + t0 * L * 2 : nullptr);
     }
     if (own_launch) {
         const int n = long_row_blocks(n_rows);
-        switch (m) {
-        case 32: hipLaunchKernelGGL(k_hll_merge_long<32>, dim3(n), dim3(LONG_THREADS), 0, s, A.rp, A.col, sk, n_rows, long_from, prod, maxb, b_rp, b_cols, est, mg); break;
-        case 64: hipLaunchKernelGGL(k_hll_merge_long<64>, dim3(n), dim3(LONG_THREADS), 0, s, A.rp, A.col, sk, n_rows, long_from, prod, maxb, b_rp, b_cols, est, mg); break;
-        default: hipLaunchKernelGGL(k_hll_merge_long<128>, dim3(n), dim3(LONG_THREADS), 0, s, A.rp, A.col, sk, n_rows, long_from, prod, maxb, b_rp, b_cols, est, mg); break;
-        }
+        const auto huge = m == 32 ? k_hll_merge_long<32> : m == 64 ? k_hll_merge_long<64> : k_hll_merge_long<128>;
+        hipLaunchKernelGGL(huge, dim3(n), dim3(LONG_THREADS), 0, s, A.rp, A.col, sk, n_rows, huge_from, prod, maxb, b_rp, b_cols,
+                           est, mg);
     }
     return hipGetLastError();
 }
