@@ -227,12 +227,12 @@ __device__ __forceinline__ T group_reduce_max(T v, int width)
 #endif
 
 // LDS of a row of pr products that a wave sorts (a SortRow of 64 lanes, the fewest products per lane there is a sort for, and
-// 64 entries).
+// 64 entries, cut off behind the row's own places).
 __host__ __device__ constexpr int sort_row_bytes(int pr, int vbytes)
 {
     const int ppt = pr <= 128 ? 2 : pr <= 192 ? 3 : pr <= 256 ? 4 : pr <= 384 ? 6 : pr <= 512 ? 8 : pr <= 768 ? 12 : pr <= 1024 ? 16 : pr <= 1536 ? 24 : 32;
-    const int acc = vbytes * (64 * ppt + (64 * ppt >> (ppt >= 12 ? 4 : 3)));   // (a multiple of 8)
-    return acc + 64 * (4 + vbytes) + 8 * ppt;
+    const int places = pr + (pr >> (ppt >= 12 ? 4 : 3)) + 1;
+    return (64 * (4 + vbytes) + 8 * ppt + vbytes * places + 7) & ~7;
 }
 
 // Totals of the row-products pass are kept in ROW_TOTAL_SLOTS slots of ROW_TOTAL_STRIDE 64-bit words each (256

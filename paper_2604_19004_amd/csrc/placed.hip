@@ -180,7 +180,7 @@ k_placed_group(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
     const int ne = live ? (int)(a_rp[row + 1] - e0) : 0;
     SortRow<V, G, PPT, ENT> &sr = s_row[rl];
     SortedRow<V, G, PPT, ENT> c;
-    c.sort(sr, lane, sub, e0, ne, a_col, a_val, b_rp, b_col, b_val);
+    c.template sort<true>(sr, lane, sub, e0, ne, a_col, a_val, b_rp, b_col, b_val);
     if (sub == 0) s_n[rl] = c.n_out;
     __syncthreads();
     if (first_wave) {
@@ -189,7 +189,7 @@ k_placed_group(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
         if (lane < R) s_before[lane] = inc - v;
         if (lane == WAVE - 1) post(p.counts + unit, inc + 1u);
     }
-    c.accumulate(sr, sub);
+    c.template accumulate<true>(sr, sub);
     if (first_wave) {
         const int64_t o = wait_for_place(p.places + unit, p.flags);
         if (lane == 0) s_place = o;
@@ -262,7 +262,7 @@ __device__ __forceinline__ void sort_by_size(char *lds, int64_t row, int pr, con
         if (pr <= 64 * PPT) {                                                                                    \
             SortRow<V, WAVE, PPT, 64> &sr = *reinterpret_cast<SortRow<V, WAVE, PPT, 64> *>(lds);                 \
             SortedRow<V, WAVE, PPT, 64> c;                                                                       \
-            c.sort(sr, lane, lane, e0, ne, a_col, a_val, b_rp, b_col, b_val);                                    \
+            c.template sort<true>(sr, lane, lane, e0, ne, a_col, a_val, b_rp, b_col, b_val);                                    \
             sorted(c, sr, lane);                                                                                 \
             return;                                                                                              \
         }
@@ -309,7 +309,7 @@ k_placed_wave(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_co
     }
     sort_by_size<V, MAX>(s_pool + before, row, pr, a_rp, a_col, a_val, b_rp, b_col, b_val, [&](auto &c, auto &sr, int lane) {
         publish_row(s_four, wave, c.n_out, p.counts + unit);
-        c.accumulate(sr, lane);
+        c.template accumulate<true>(sr, lane);
         const int64_t o = place_row(s_four, wave, unit, p);
         if (o < 0) return;
         if (lane == 0) {

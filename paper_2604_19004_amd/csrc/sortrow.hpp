@@ -202,13 +202,14 @@ struct SortRow {
     static constexpr int SPREAD = PPT >= 12 ? 4 : 3;
     static constexpr int PLACES = CAP + (CAP >> SPREAD);
     static __device__ __forceinline__ int place(int r) { return r + (r >> SPREAD); }
-    // the products' values by number, then the values of the row of C by rank, then its columns: what LDS a row takes
-    // decides how many rows a compute unit works on (1024 products: with a place of their own for the columns 2 waves per
-    // SIMD and 506 us for 100 003 rows, one place for all three 4 waves and 380 us)
-    V acc[PLACES];
     uint32_t pos[ENT];     // position in B of an entry's first product, minus that product's number
     V a[ENT];
     unsigned long long start[MW];
+    // the products' values by number, then the values of the row of C by rank, then its columns: what LDS a row takes
+    // decides how many rows a compute unit works on (1024 products: with a place of their own for the columns 2 waves per
+    // SIMD and 506 us for 100 003 rows, one place for all three 4 waves and 380 us).  At the end, as a row of fewer products
+    // than the class has may be given less (sort_row_bytes).
+    V acc[PLACES];
 };
 
 // A row of the sort kernels, in the order in which its steps are called; sub = lane inside the group of G lanes that own it.
@@ -222,20 +223,22 @@ struct SortedRow {
     static_assert(64 % G == 0, "whole groups");
 
     uint32_t key[PPT];
+    uint32_t total;     // products
     uint32_t n_out;     // entries of the row of C
     uint32_t heads;     // bit u: key u opens an entry of C
     uint32_t tails;     // bit u: key u closes one
     int rank0;          // entries before this lane's keys, minus one
 
-    // Entries e0 .. e0 + ne - 1 of A; ne = 0: a group without a row (the rows of a wave advance together).
+    // Entries e0 .. e0 + ne - 1 of A; ne = 0: a group without a row (the rows of a wave advance together).  CUT: see products.
+    template <bool CUT = false>
     __device__ __forceinline__ void sort(Lds &sr, int lane, int sub, int64_t e0, int ne, const int32_t *__restrict__ a_col,
                                          const V *__restrict__ a_val, const int64_t *__restrict__ b_rp,
                                          const int32_t *__restrict__ b_col, const V *__restrict__ b_val)
     {
         ne = ne < ENT ? ne : ENT;   // (holds: the caller lists no other rows)
         open(sr, sub);
-        uint32_t total = 0;
         int nseg = 0;
+        total = 0;
         const int chunks = G >= ENT ? 1 : (int)wave_max_u32((uint32_t)((ne + G - 1) / G));
         for (int ch = 0; ch < chunks; ++ch) {
             const int e = ch * G + sub;
@@ -248,9 +251,9 @@ struct SortedRow {
                 p0 = b_rp[k];
                 len = (uint32_t)(b_rp[k + 1] - p0);
             }
-            add(sr, lane, sub, (uint32_t)p0, len, a, total, nseg);
+            add(sr, lane, sub, (uint32_t)p0, len, a, nseg);
         }
-        products(sr, sub, total, b_col, b_val);
+        products<CUT>(sr, sub, b_col, b_val);
         order(lane, sub);
     }
 
@@ -260,8 +263,8 @@ struct SortedRow {
         wave_sync();
     }
 
-    // An entry of A per lane: a times len entries of B from p0 on; total and nseg: products and segments before them.
-    __device__ __forceinline__ void add(Lds &sr, int lane, int sub, uint32_t p0, uint32_t len, V a, uint32_t &total, int &nseg)
+    // An entry of A per lane: a times len entries of B from p0 on; nseg: segments before them.
+    __device__ __forceinline__ void add(Lds &sr, int lane, int sub, uint32_t p0, uint32_t len, V a, int &nseg)
     {
         const int shift = lane & ~(G - 1);
         constexpr unsigned long long GMASK = G == 64 ? ~0ull : (1ull << (G & 63)) - 1ull;
@@ -278,10 +281,11 @@ struct SortedRow {
         nseg += __popcll(some);
     }
 
-    // The products of the entries: keys and, in LDS, values by number.  NARROW: B has fewer than 2^29 entries (byte offsets
-    // in 32 bits, which leaves out an address of two registers per load).
-    template <bool NARROW = false>
-    __device__ __forceinline__ void products(Lds &sr, int sub, uint32_t total, const int32_t *__restrict__ b_col,
+    // The products of the entries: keys and, in LDS, values by number.  CUT: the row has no more places than its own
+    // products need and one (pads use that), and B has fewer than 2^29 entries (byte offsets in 32 bits, which leaves out an
+    // address of two registers per load).
+    template <bool CUT>
+    __device__ __forceinline__ void products(Lds &sr, int sub, const int32_t *__restrict__ b_col,
                                              const V *__restrict__ b_val)
     {
         total = total < (uint32_t)CAP ? total : (uint32_t)CAP;
@@ -310,7 +314,7 @@ struct SortedRow {
                 c[i] = 0;
                 b[i] = V();
                 if (q < total) {
-                    if constexpr (NARROW) {
+                    if constexpr (CUT) {
                         c[i] = *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(b_col) + p[i] * 4u);
                         b[i] = *reinterpret_cast<const V *>(reinterpret_cast<const char *>(b_val) + p[i] * (uint32_t)sizeof(V));
                     } else {
@@ -323,7 +327,7 @@ struct SortedRow {
             for (int i = 0; i < BATCH; ++i) {
                 const uint32_t q = (uint32_t)((u0 + i) * G + sub);
                 key[u0 + i] = q < total ? ((uint32_t)c[i] << LB) | q : SR_PAD;
-                sr.acc[q] = a[i] * b[i];
+                sr.acc[!CUT || q < total ? q : total] = a[i] * b[i];
             }
         }
     }
@@ -362,13 +366,15 @@ struct SortedRow {
     // 8-byte atomic for every key that is no head, took 8 bytes a product also for 4-byte values: 100 000 rows of 1444 and of
     // 2025 products fp32 653 -> 575 and 1085 -> 815 us now that a compute unit holds twice the rows; fp64, and smaller
     // classes, within 2 %.)
+    template <bool CUT = false>
     __device__ __forceinline__ void accumulate(Lds &sr, int sub)
     {
         V val[PPT];
 #pragma unroll
         for (int u = 0; u < PPT; ++u) {
             const uint32_t q = key[u] & ((1u << LB) - 1u);
-            val[u] = sr.acc[CAP == 1 << LB || q < (uint32_t)CAP ? q : 0u];   // (a pad's number is the largest there is)
+            // (a pad's number is the largest there is)
+            val[u] = sr.acc[CUT ? (q < total ? q : total) : CAP == 1 << LB || q < (uint32_t)CAP ? q : 0u];
         }
         wave_sync();
         double run = -0.0;
