@@ -602,10 +602,16 @@ constexpr int MG_WAVE = 1024;    // a wave takes up to 64 entries a turn with 64
 // Entries first, first + step, ... of a row, for one slice (16 registers) of the sketch: U per lane and turn
 // (unconditional reads, index clamped; merging a sketch twice is harmless), so that the dependent loads entry ->
 // sketch of U entries overlap.
-template <int L, int U>
+// spans: what else the sample wants to know of the row, the first and last column it can reach.
+struct Reach {
+    const int32_t *b_col = nullptr;   // null: not asked for
+    int first = 0x7fffffff, last = -1;
+};
+template <int L, int U, bool SAMPLE = false>
 __device__ __forceinline__ void hll_walk(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
                                          const uint64_t *__restrict__ sk, const int64_t *__restrict__ b_rp, int64_t row,
-                                         int slice, int first, int step, RegMax &acc, long long &blen_max)
+                                         int slice, int first, int step, RegMax &acc, long long &blen_max,
+                                         Reach *reach = nullptr)
 {
     const int64_t e1 = a_rp[row + 1];
     for (int64_t e = a_rp[row] + first; e < e1; e += U * (int64_t)step) {
@@ -620,7 +626,22 @@ __device__ __forceinline__ void hll_walk(const int64_t *__restrict__ a_rp, const
         for (int i = 0; i < U; ++i) regs[i] = *reinterpret_cast<const Regs16 *>(sk + ((int64_t)k[i] * L + slice) * 2);
 #pragma unroll
         for (int i = 0; i < U; ++i) acc.add(regs[i]);
-        if (b_rp != nullptr && slice == 0) {
+        if (SAMPLE && reach->b_col != nullptr && slice == 0) {
+            RowEnds ends[U];
+#pragma unroll
+            for (int i = 0; i < U; ++i) ends[i] = *reinterpret_cast<const RowEnds *>(b_rp + k[i]);
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                const int64_t p0 = (int64_t)(((unsigned long long)ends[i].y << 32) | ends[i].x);
+                const int64_t len = (int64_t)row_length(ends[i]);
+                if (len > 0) {
+                    const int32_t c0 = reach->b_col[p0], c1 = reach->b_col[p0 + len - 1];
+                    reach->first = c0 < reach->first ? c0 : reach->first;
+                    reach->last = c1 > reach->last ? c1 : reach->last;
+                }
+            }
+        }
+        if (!SAMPLE && b_rp != nullptr && slice == 0) {
 #pragma unroll
             for (int i = 0; i < U; ++i) {
                 const long long len = b_rp[k[i] + 1] - b_rp[k[i]];
@@ -629,6 +650,23 @@ __device__ __forceinline__ void hll_walk(const int64_t *__restrict__ a_rp, const
         }
     }
 }
+
+// Row t of the stratified sample of Section 3.2, one row out of each of ns equal strata of `rows` rows (both below 2^31), chosen
+// by a hash of the stratum's number and the seed: the same rows as the host helper behind ocean_sample_rows gives.
+struct SampleOf {
+    int64_t rows, ns;
+    uint32_t seed;
+    int64_t whole_from;             // rows of so many entries count as reaching everywhere
+    const int32_t *b_col;           // null: reach not asked for
+    int64_t *prod_out;              // products of the sampled rows
+    int32_t *span_out;              // columns they can reach, 0: none, the largest number: everywhere
+    __device__ __forceinline__ int64_t row(int64_t t) const
+    {
+        const uint64_t lo = (uint64_t)t * (uint64_t)rows / (uint64_t)ns;
+        const uint64_t hi = (uint64_t)(t + 1) * (uint64_t)rows / (uint64_t)ns;
+        return (int64_t)(lo + fmix32(seed + 0x9E3779B9u * (uint32_t)(t + 1)) % (hi - lo));
+    }
+};
 
 // L consecutive lanes hold the merged sketch of slot t (row `row`), 16 registers each: estimate and store.  (Sums of up to
 // 128 powers of two from 2^-33 on are exact, in whatever order.)
@@ -700,24 +738,26 @@ __device__ __forceinline__ void hll_row_by_all(Regs16 (*s_regs)[M / 16], long lo
 
 // (8: with the code for long rows beside it the compiler would take 96 registers and leave 5 waves per SIMD; 10 % slower
 // on 256 000 rows of 34 entries)
-template <int M>
+// SAMPLE: the rows are the sample's, whose products and reach are written beside their estimates.
+template <int M, bool SAMPLE>
 __global__ void __launch_bounds__(TPB, 8)
 k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
             const uint64_t *__restrict__ sk, const int64_t *__restrict__ rows, int64_t n_rows, int g_log2,
             int64_t long_from, int64_t huge_from, bool huge_here, int n_long, const int64_t *__restrict__ prod,
             const int32_t *__restrict__ maxb, const int64_t *__restrict__ b_rp,
-            int64_t b_cols, double *__restrict__ est, uint64_t *__restrict__ merged)
+            int64_t b_cols, double *__restrict__ est, uint64_t *__restrict__ merged, const SampleOf sample)
 {
     constexpr int L = M / 16;
+    auto row_of = [&](int64_t t) { return SAMPLE ? sample.row(t) : rows ? rows[t] : t; };
     __shared__ int32_t s_long[TPB];   // (slot of the row, i.e. its position among the selected rows)
     __shared__ int s_nlong;
     __shared__ Regs16 s_regs[TPB / WAVE][L];
     __shared__ long long s_blen[TPB / WAVE];
     const int G = 1 << g_log2;  // >= L
     auto take = [&](int64_t t2) {
-        hll_row_by_all<M, TPB, 4>(s_regs, s_blen, a_rp, a_col, sk, t2, rows ? rows[t2] : t2, prod, maxb, b_rp, b_cols, est, merged);
+        hll_row_by_all<M, TPB, 4>(s_regs, s_blen, a_rp, a_col, sk, t2, row_of(t2), prod, maxb, b_rp, b_cols, est, merged);
     };
-    if ((int)blockIdx.x < n_long) {   // uniform (all rows, no row list)
+    if (!SAMPLE && (int)blockIdx.x < n_long) {   // uniform (all rows, no row list)
         for_long_rows(n_rows, n_long, s_long, &s_nlong,
                       [&](int64_t r) {
                           const int64_t ne = a_rp[r + 1] - a_rp[r];
@@ -747,14 +787,27 @@ k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
     long long blen_max = 0;
     int64_t row = -1;
     bool mine = false;
+    Reach reach;
+    int64_t ne = 0;
     if (t < n_rows) {
-        row = rows ? rows[t] : t;
-        mine = a_rp[row + 1] - a_rp[row] < long_from;
-        if (mine) hll_walk<L, 4>(a_rp, a_col, sk, b_rp, row, slice, part, parts, acc, blen_max);
+        row = row_of(t);
+        ne = a_rp[row + 1] - a_rp[row];
+        mine = ne < long_from;
+        if (SAMPLE && ne < sample.whole_from) reach.b_col = sample.b_col;
+        if (mine) hll_walk<L, 4, SAMPLE>(a_rp, a_col, sk, b_rp, row, slice, part, parts, acc, blen_max, &reach);
         else if (n_long == 0 && sub == 0) s_long[atomicAdd(&s_nlong, 1)] = (int32_t)t;
     }
     const Regs16 all = lanes_max(acc.get(), L, G);
-    if (b_rp != nullptr) blen_max = group_reduce_max(blen_max, G);
+    if (SAMPLE) {
+        reach.first = -group_reduce_max(-reach.first, G);
+        reach.last = group_reduce_max(reach.last, G);
+        if (t < n_rows && sub == 0) {
+            sample.prod_out[t] = prod[row];
+            sample.span_out[t] = ne >= sample.whole_from ? 0x7fffffff : reach.last < reach.first ? 0 : reach.last - reach.first + 1;
+        }
+    } else if (b_rp != nullptr) {
+        blen_max = group_reduce_max(blen_max, G);
+    }
     hll_finish<M>(all, blen_max, t, row, slice, mine && part == 0, prod, maxb, b_cols, est, merged);
     __syncthreads();
     const int nlong = s_nlong;
@@ -803,7 +856,7 @@ hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const 
     const int64_t huge_from = long_from > MG_WAVE ? long_from : MG_WAVE;
     const bool own_launch = spread && A.nnz >= (1 << 20);
     const int rows_per_block = TPB >> g_log2;
-    const auto kernel = m == 32 ? k_hll_merge<32> : m == 64 ? k_hll_merge<64> : k_hll_merge<128>;
+    const auto kernel = m == 32 ? k_hll_merge<32, false> : m == 64 ? k_hll_merge<64, false> : k_hll_merge<128, false>;
     if (m != 32 && m != 64 && m != 128) return hipErrorInvalidValue;
     // (pieces that leave room for the workgroups for long rows: see most_blocks)
     const int64_t most = (most_blocks(TPB) - 1024) * rows_per_block;
@@ -814,7 +867,7 @@ hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const 
         const int64_t r0 = rows ? 0 : t0;   // (without a list, slot t is row t: the rows' own arrays move along)
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp + r0, A.col, sk, rows ? rows + t0 : nullptr, n,
                            g_log2, long_from, huge_from, !own_launch, n_long, prod ? prod + r0 : nullptr, maxb ? maxb + r0 : nullptr,
-                           b_rp, b_cols, est + t0, mg ? mg + t0 * L * 2 : nullptr);
+                           b_rp, b_cols, est + t0, mg ? mg + t0 * L * 2 : nullptr, SampleOf{});
     }
     if (own_launch) {
         const int n = long_row_blocks(n_rows);
@@ -825,85 +878,139 @@ hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const 
     return hipGetLastError();
 }
 
+// Estimates, products and, with B given, reach of the ns sampled rows: one launch for what the sample looks at.
+hipError_t launch_sample(const Csr &A, const Csr *B, int64_t b_cols, const uint8_t *sketches, int m, int64_t ns, uint32_t seed,
+                         const int64_t *prod, const int32_t *maxb, double *est, int64_t *prod_out, int32_t *span_out, int lanes_div,
+                         hipStream_t s)
+{
+    if (ns <= 0) return hipSuccess;
+    const int L = m / 16;
+    const double avg = A.rows ? (double)A.nnz / (double)A.rows : 1.0;
+    int g_log2 = ilog2_ceil(avg * L / (double)lanes_div, 0, 6);
+    while ((1 << g_log2) < L) ++g_log2;
+    const int64_t long_from = 8.0 * avg > (double)MG_LONG ? (int64_t)(8.0 * avg) : MG_LONG;
+    const int64_t whole_from = ((int64_t)64 << ilog2_ceil(avg / 4.0, 1, 6)) + 1;   // (as k_row_spans)
+    const SampleOf sample{A.rows, ns, seed, whole_from < long_from ? whole_from : long_from, B ? B->col : nullptr, prod_out, span_out};
+    const auto kernel = m == 32 ? k_hll_merge<32, true> : m == 64 ? k_hll_merge<64, true> : k_hll_merge<128, true>;
+    const int64_t blocks = ((ns << g_log2) + TPB - 1) / TPB;
+    if (blocks > most_blocks(TPB)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, reinterpret_cast<const uint64_t *>(sketches), nullptr,
+                       ns, g_log2, long_from, long_from, true, 0, prod, maxb, B ? B->rp : nullptr, b_cols, est, nullptr, sample);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------- row spans
 // Column range that a row of C can reach: from the first entry of the rows of B it references to their last
 // entry (B's rows in column order; where they are not, the range is only a guess, and the kernel that relies
 // on it checks every product against it).  Used to choose the dense accumulator for rows whose range fits it
 // (Section 3.3, accumulator selection).  One lane group per row as in k_row_products; rows of A with more than
-// 64 entries per lane of the group are left with the full range (they are heavy rows, which have a dense
-// accumulator of their own).  rows: list of row ids, or null for all rows 0 .. n-1; outputs indexed like rows.
+// 64 entries per lane of the group are left with the full range (they are heavy rows, which have a
+// dense accumulator of their own).
+// ends: first and last column of every row of B in one word of 8 bytes (k_check_sorted writes them in passing), which is a
+// gather per entry instead of three.  The rows' ranges are summed up in totals, SPAN_SLOTS slots of SPAN_STRIDE words: rows
+// with products, those of them whose range is longer than DS_MAX_COLS, the longest range of the others, the sum of the lesser
+// of range and products (which bounds C), and the rows that a dense accumulator over their range pays for, with tables sized
+// by the product bound.
 __global__ void __launch_bounds__(TPB)
-k_row_spans(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, const int64_t *__restrict__ b_rp,
-            const int32_t *__restrict__ b_col, const int64_t *__restrict__ rows, int64_t n, int g_log2,
-            int32_t *__restrict__ cmin, int32_t *__restrict__ cmax)
+k_row_spans(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, const int2 *__restrict__ ends, int64_t n, int g_log2,
+            int32_t *__restrict__ cmin, int32_t *__restrict__ cmax, const int64_t *__restrict__ prod, int64_t n_cols, int vbytes,
+            double bound_coef, unsigned long long *totals)
 {
+    __shared__ unsigned long long s_tot[SPAN_TOTALS];
     const int G = 1 << g_log2;
     const int R = TPB >> g_log2;
     const int rl = threadIdx.x >> g_log2;
     const int sub = threadIdx.x & (G - 1);
+    if (threadIdx.x < SPAN_TOTALS) s_tot[threadIdx.x] = 0ull;
+    __syncthreads();
+    unsigned long long with = 0, beyond = 0, longest = 0, most = 0, pay = 0;
     for (int64_t base = (int64_t)blockIdx.x * R; base < n; base += (int64_t)gridDim.x * R) {
-        const int64_t t = base + rl;
+        const int64_t row = base + rl;
         int lo = 0x7fffffff, hi = -1;
         bool whole = false;
-        if (t < n) {
-            const int64_t row = rows ? rows[t] : t;
+        if (row < n) {
             const int64_t e0 = a_rp[row], e1 = a_rp[row + 1];
             whole = e1 - e0 > (int64_t)G * 64;
-            if (!whole) {
-                for (int64_t e = e0 + sub; e < e1; e += 4 * G) {
-                    int64_t p0[4], p1[4];
+            for (int64_t e = e0 + sub; !whole && e < e1; e += 4 * G) {
+                int32_t k[4];
+                int2 of[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int64_t idx = e + (int64_t)i * G;
-                        const int32_t k = a_col[idx < e1 ? idx : e];
-                        p0[i] = b_rp[k];
-                        p1[i] = b_rp[k + 1];
-                    }
+                for (int i = 0; i < 4; ++i) {
+                    const int64_t idx = e + (int64_t)i * G;
+                    k[i] = a_col[idx < e1 ? idx : e];
+                }
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if (e + (int64_t)i * G < e1 && p1[i] > p0[i]) {
-                            const int32_t first = b_col[p0[i]], last = b_col[p1[i] - 1];
-                            lo = first < lo ? first : lo;
-                            hi = last > hi ? last : hi;
-                        }
-                    }
+                for (int i = 0; i < 4; ++i) of[i] = ends[k[i]];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    lo = of[i].x < lo ? of[i].x : lo;
+                    hi = of[i].y > hi ? of[i].y : hi;
                 }
             }
         }
         lo = -group_reduce_max(-lo, G);
         hi = group_reduce_max(hi, G);
-        if (t < n && sub == 0) {
-            cmin[t] = whole ? 0 : lo;
-            cmax[t] = whole ? 0x7fffffff : hi;   // (hi < lo: a row without products)
+        if (row < n && sub == 0) {
+            cmin[row] = whole ? 0 : lo;
+            cmax[row] = whole ? 0x7fffffff : hi;   // (hi < lo: a row without products)
+            const long long pr = prod[row];
+            if (pr > 0) {
+                const unsigned long long span = whole ? 0x80000000ull : (unsigned long long)((long long)hi - lo + 1);
+                const double ub = pr < n_cols ? (double)pr : (double)n_cols;
+                long long slots = 16;
+                while ((double)slots < bound_coef * ub && slots < (1ll << 40)) slots <<= 1;
+                ++with;
+                beyond += span > (unsigned long long)DS_MAX_COLS;
+                longest = span <= (unsigned long long)DS_MAX_COLS && span > longest ? span : longest;
+                most += span < (unsigned long long)pr ? span : (unsigned long long)pr;
+                pay += dense_span_pays((long long)span, slots, vbytes);
+            }
         }
+    }
+    const unsigned long long mine[SPAN_TOTALS] = {with, beyond, longest, most, pay};
+#pragma unroll
+    for (int i = 0; i < SPAN_TOTALS; ++i) {
+        const unsigned long long wave = i == 2 ? group_reduce_max(mine[i], WAVE) : group_reduce_sum(mine[i], WAVE);
+        if (lane_id() == 0 && wave != 0ull) {
+            if (i == 2) atomicMax(&s_tot[i], wave);
+            else atomicAdd(&s_tot[i], wave);
+        }
+    }
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < SPAN_TOTALS && s_tot[t] != 0ull) {
+        unsigned long long *slot = totals + (size_t)(blockIdx.x % SPAN_SLOTS) * SPAN_STRIDE;
+        if (t == 2) atomicMax(&slot[2], s_tot[2]);
+        else atomicAdd(&slot[t], s_tot[t]);
     }
 }
 
-hipError_t launch_row_spans(const Csr &A, const Csr &B, const int64_t *rows, int64_t n, int32_t *cmin, int32_t *cmax,
-                            hipStream_t s)
+hipError_t launch_row_spans(const Csr &A, const Csr &B, const int64_t *ends, const int64_t *prod, int vbytes, double bound_coef,
+                            int32_t *cmin, int32_t *cmax, unsigned long long *totals, hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
-    const double avg = A.rows ? (double)A.nnz / (double)A.rows : 0.0;
+    if (A.rows <= 0) return hipSuccess;
+    const double avg = (double)A.nnz / (double)A.rows;
     const int g_log2 = ilog2_ceil(avg / 4.0, 1, 6);
     const int R = TPB >> g_log2;
-    int64_t blocks = (n + R - 1) / R;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_row_spans, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, B.rp, B.col, rows, n, g_log2,
-                       cmin, cmax);
+    int64_t blocks = (A.rows + R - 1) / R;
+    if (blocks > 2048) blocks = 2048;
+    hipLaunchKernelGGL(k_row_spans, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, reinterpret_cast<const int2 *>(ends), A.rows,
+                       g_log2, cmin, cmax, prod, B.cols, vbytes, bound_coef, totals);
     return hipGetLastError();
 }
 
 // flags |= 8 when some row of B is not in ascending column order (then the ranges of k_row_spans are guesses).  Eight
-// lanes per row.
+// lanes per row.  ends: receives every row's first and last column (the largest number and -1 for an empty row).
 __global__ void __launch_bounds__(TPB)
-k_check_sorted(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, int64_t rows, int32_t *flags)
+k_check_sorted(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, int64_t rows, int32_t *flags, int2 *__restrict__ ends)
 {
     constexpr int G = 8;
     const int sub = threadIdx.x & (G - 1);
     bool bad = false;
     for (int64_t r = ((int64_t)blockIdx.x * TPB + threadIdx.x) / G; r < rows; r += (int64_t)gridDim.x * (TPB / G)) {
-        const int64_t last = rp[r + 1] - 1;
-        for (int64_t p = rp[r] + sub; p < last; p += 4 * G) {
+        const int64_t first = rp[r], last = rp[r + 1] - 1;
+        if (sub == 0) ends[r] = first <= last ? make_int2(col[first], col[last]) : make_int2(0x7fffffff, -1);
+        for (int64_t p = first + sub; p < last; p += 4 * G) {
             int32_t a[4], b[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -918,101 +1025,71 @@ k_check_sorted(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, 
     if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(flags, 8);
 }
 
-hipError_t launch_check_sorted(const Csr &B, int32_t *flags, hipStream_t s)
+hipError_t launch_check_sorted(const Csr &B, int32_t *flags, int64_t *ends, hipStream_t s)
 {
     if (B.rows == 0) return hipSuccess;
     int64_t blocks = (B.rows * 8 + TPB - 1) / TPB;
     if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_check_sorted, dim3((unsigned)blocks), dim3(TPB), 0, s, B.rp, B.col, B.rows, flags);
-    return hipGetLastError();
-}
-
-// ----------------------------------------------------------- sample rows
-// The stratified sample of Section 3.2 (one row out of each of ns equal strata, chosen by a hash of the
-// stratum's number and the seed), written on the device: the same rows as the host helper behind
-// ocean_sample_rows gives.
-__global__ void __launch_bounds__(TPB)
-k_sample_rows(int64_t rows, int64_t ns, uint32_t seed, int64_t *__restrict__ out)
-{
-    const int64_t t = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (t >= ns) return;
-    const int64_t lo = (int64_t)((unsigned __int128)t * (unsigned __int128)rows / (unsigned __int128)ns);
-    const int64_t hi = (int64_t)((unsigned __int128)(t + 1) * (unsigned __int128)rows / (unsigned __int128)ns);
-    const uint32_t h = fmix32(seed + 0x9E3779B9u * (uint32_t)(t + 1));
-    out[t] = lo + (int64_t)(h % (uint64_t)(hi - lo));
-}
-
-hipError_t launch_sample_rows(int64_t rows, int64_t ns, uint32_t seed, int64_t *out, hipStream_t s)
-{
-    if (ns <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_sample_rows, dim3((unsigned)((ns + TPB - 1) / TPB)), dim3(TPB), 0, s, rows, ns, seed, out);
+    hipLaunchKernelGGL(k_check_sorted, dim3((unsigned)blocks), dim3(TPB), 0, s, B.rp, B.col, B.rows, flags, reinterpret_cast<int2 *>(ends));
     return hipGetLastError();
 }
 
 // --------------------------------------------------------- sample reduce
-// Sums over the sampled rows in a fixed order (one workgroup, strided partial
-// sums, tree reduction), so the sampled CR is the same on every run.
+// Sums over the sampled rows in a fixed order (one workgroup, strided partial sums, butterflies over lanes, then the waves in
+// turn), so the sampled CR is the same on every run.
 // out[0] = sum of products, out[1] = sum of estimates (their ratio is the sampled CR, Section 3.2);
 // out[2], out[3] = sum and sum of squares of the per-row ratios products / estimate, out[4] = rows counted
 // (mean and standard deviation of the compression ratio over the sample, Section 4.1); out[5] = sampled rows
-// whose column range is narrow enough for the dense accumulator to pay (cmin / cmax of the sampled rows given).
+// whose column range is narrow enough for the dense accumulator to pay.
 constexpr int SR_THREADS = 1024;
+constexpr int SR_SUMS = 6;
 __global__ void __launch_bounds__(SR_THREADS)
-k_sample_reduce(const int64_t *__restrict__ rows, int64_t n_rows, const int64_t *__restrict__ prod,
-                const double *__restrict__ est, const int32_t *__restrict__ cmin, const int32_t *__restrict__ cmax,
+k_sample_reduce(int64_t n_rows, const int64_t *__restrict__ prod, const double *__restrict__ est, const int32_t *__restrict__ span,
                 int64_t n_cols, int vbytes, double bound_coef, double *out)
 {
-    constexpr int NS = 6;
-    __shared__ double s_acc[NS][SR_THREADS];
-    double acc[NS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    // four sampled rows per thread and turn, their dependent loads (row id -> products) issued together
+    __shared__ double s_acc[SR_THREADS / WAVE][SR_SUMS];
+    double acc[SR_SUMS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    // four sampled rows per thread and turn, their loads issued together
     for (int64_t t0 = threadIdx.x; t0 < n_rows; t0 += 4 * SR_THREADS) {
-        double e[4];
-        int64_t r[4];
+        double e[4], p[4];
+        int32_t w[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int64_t t = t0 + (int64_t)i * SR_THREADS;
-            e[i] = t < n_rows ? est[t] : 0.0;
-            r[i] = rows[t < n_rows ? t : t0];
+            const int64_t q = t < n_rows ? t : t0;
+            e[i] = t < n_rows ? est[q] : 0.0;
+            p[i] = (double)prod[q];
+            w[i] = span[q];
         }
-        double p[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) p[i] = (double)prod[r[i]];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (e[i] > 0.0) {
                 const double q = p[i] / e[i];
                 acc[0] += p[i]; acc[1] += e[i]; acc[2] += q; acc[3] += q * q; acc[4] += 1.0;
-                if (cmin != nullptr) {
-                    const int64_t t = t0 + (int64_t)i * SR_THREADS;
-                    const long long span = (long long)cmax[t] - (long long)cmin[t] + 1;
-                    const double ub = p[i] < (double)n_cols ? p[i] : (double)n_cols;
-                    long long slots = 16;
-                    while ((double)slots < bound_coef * ub && slots < (1ll << 40)) slots <<= 1;   // table from the bound
-                    if (dense_span_pays(span, slots, vbytes)) acc[5] += 1.0;
-                }
+                const double ub = p[i] < (double)n_cols ? p[i] : (double)n_cols;
+                long long slots = 16;
+                while ((double)slots < bound_coef * ub && slots < (1ll << 40)) slots <<= 1;   // table from the bound
+                if (dense_span_pays((long long)w[i], slots, vbytes)) acc[5] += 1.0;
             }
         }
     }
 #pragma unroll
-    for (int k = 0; k < NS; ++k) s_acc[k][threadIdx.x] = acc[k];
-    __syncthreads();
-    for (int off = SR_THREADS / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) {
-#pragma unroll
-            for (int k = 0; k < NS; ++k) s_acc[k][threadIdx.x] += s_acc[k][threadIdx.x + off];
-        }
-        __syncthreads();
+    for (int k = 0; k < SR_SUMS; ++k) {
+        const double wave = group_reduce_sum(acc[k], WAVE);
+        if (lane_id() == 0) s_acc[threadIdx.x / WAVE][k] = wave;
     }
-    if (threadIdx.x < NS) out[threadIdx.x] = s_acc[threadIdx.x][0];
+    __syncthreads();
+    if (threadIdx.x < SR_SUMS) {
+        double sum = 0.0;
+        for (int w = 0; w < SR_THREADS / WAVE; ++w) sum += s_acc[w][threadIdx.x];
+        out[threadIdx.x] = sum;
+    }
 }
 
-hipError_t launch_sample_reduce(const int64_t *rows, int64_t n_rows, const int64_t *prod, const double *est,
-                                const int32_t *cmin, const int32_t *cmax, int64_t n_cols, int vbytes, double bound_coef,
-                                double *out, hipStream_t s)
+hipError_t launch_sample_reduce(int64_t n_rows, const int64_t *prod, const double *est, const int32_t *span, int64_t n_cols, int vbytes,
+                                double bound_coef, double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_sample_reduce, dim3(1), dim3(SR_THREADS), 0, s, rows, n_rows, prod, est, cmin, cmax, n_cols,
-                       vbytes, bound_coef, out);
+    hipLaunchKernelGGL(k_sample_reduce, dim3(1), dim3(SR_THREADS), 0, s, n_rows, prod, est, span, n_cols, vbytes, bound_coef, out);
     return hipGetLastError();
 }
 

@@ -21,6 +21,7 @@
 // produced more entries than the space reserved for it; such rows are redone
 // by the caller with bound-sized tables (Section 3.2, overflow handling).
 #include "ocean_internal.hpp"
+#include "placed.hpp"
 #include "traverse.hpp"
 
 namespace ocean {
@@ -602,14 +603,16 @@ k_numeric_wg(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col
 // COLS: columns the range may have (4096, or less where the rows' ranges allow it: what LDS a row takes decides how many
 // rows a compute unit works on, and every column is cleared and looked at.  100 000 rows of 2500 products in blocks of
 // 1000 columns: 842 us with 4096).
+// PLACED: all rows in order, a workgroup each, which waits for the row's place in C (placed.hpp; rows, out_ptr and row_nnz are
+// not used); a product outside the range ends the attempt.  Workgroup 0 gives the places.
 constexpr int DS_THREADS = 256;
-template <typename V, bool QUERY, int COLS>
+template <typename V, bool QUERY, int COLS, bool PLACED>
 __global__ void __launch_bounds__(DS_THREADS)
 k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, const V *__restrict__ a_val,
                 const int64_t *__restrict__ b_rp, const int32_t *__restrict__ b_col, const V *__restrict__ b_val,
                 const int32_t *__restrict__ rows, int64_t count, const int32_t *__restrict__ cmin,
                 const int64_t *__restrict__ out_ptr, int32_t *__restrict__ out_col, V *__restrict__ out_val,
-                int32_t *__restrict__ row_nnz)
+                int32_t *__restrict__ row_nnz, const Placing<V> p)
 {
     constexpr int DS_WORDS = COLS / 32;
     static_assert(DS_WORDS <= DS_THREADS, "one bitmap word per thread in the prefix sum");
@@ -620,10 +623,15 @@ k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
     __shared__ WgChunk<V, DS_THREADS> s_fc;
     __shared__ int s_wave[DS_THREADS / WAVE];
     __shared__ int s_bad;
+    __shared__ long long s_place;
     const int tid = threadIdx.x;
-    const int64_t r = blockIdx.x;
-    if (r >= count) return;
-    const int64_t row = rows[r];
+    if (PLACED && blockIdx.x == 0) {   // uniform
+        place_units(p.counts, p.places, p.m, p.total, p.flags, *reinterpret_cast<Turn *>(s_vals));
+        return;
+    }
+    const int64_t r = (int64_t)blockIdx.x - (PLACED ? 1 : 0);
+    if (!PLACED && r >= count) return;
+    const int64_t row = PLACED ? r : (int64_t)rows[r];
     const int32_t c0 = cmin[row];
     for (int j = tid; j < COLS; j += DS_THREADS) s_vals[j] = (AV)0;
     if (tid < DS_WORDS) s_bm[tid] = 0u;
@@ -651,12 +659,33 @@ k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
     int total;
     const int ex = block_exclusive_scan_i32<DS_THREADS>(__popc(word), s_wave, total);
     if (tid < DS_WORDS) s_pre[tid] = (uint32_t)ex;
-    __syncthreads();
-    const int64_t o = out_ptr[row];
-    const int64_t cap = out_ptr[row + 1] - o;
-    if (s_bad || (int64_t)total > cap) {   // uniform
-        if (tid == 0) row_nnz[row] = -1;
-        return;
+    int64_t o;
+    if constexpr (PLACED) {
+        if (tid < WAVE) {
+            if (tid == 0) {
+                if (s_bad) atomicOr(p.flags, FLAG_GAVE_UP);
+                post(p.counts + row, (uint32_t)total + 1u);
+            }
+            const int64_t place = wait_for_place(p.places + row, p.flags);
+            if (tid == 0) {
+                s_place = place;
+                if (place >= 0) {
+                    p.c_rp[row] = place;
+                    if (row == p.m - 1) p.c_rp[p.m] = place + total;
+                }
+            }
+        }
+        __syncthreads();
+        o = s_place;
+        if (o < 0 || o + total > p.slots) return;   // uniform
+    } else {
+        __syncthreads();
+        o = out_ptr[row];
+        const int64_t cap = out_ptr[row + 1] - o;
+        if (s_bad || (int64_t)total > cap) {   // uniform
+            if (tid == 0) row_nnz[row] = -1;
+            return;
+        }
     }
     // thread t looks at columns t, t + 256, ...: the lanes of a wave read consecutive values and the present ones
     // among them go to consecutive places of the output
@@ -668,7 +697,33 @@ k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
             out_val[o + rank] = (V)s_vals[j];
         }
     }
-    if (tid == 0) row_nnz[row] = total;
+    if (!PLACED && tid == 0) row_nnz[row] = total;
+}
+
+// All rows through the dense accumulator over their ranges, of at most l.span_cols columns, straight to their places.
+template <typename V>
+static hipError_t dispatch_placed_span(const Csr &A, const Csr &B, const PlacedLaunch &l, hipStream_t s)
+{
+    const V *av = static_cast<const V *>(A.val);
+    const V *bv = static_cast<const V *>(B.val);
+    V *ov = static_cast<V *>(l.out_val);
+    const Placing<V> p{A.rows, l.c_rp, l.out_col, ov, l.slots, l.counts, l.places, l.total, l.flags};
+    const auto kernel = l.query_bitmap ? (l.span_cols <= 1024   ? k_numeric_dspan<V, true, 1024, true>
+                                          : l.span_cols <= 2048 ? k_numeric_dspan<V, true, 2048, true>
+                                                                : k_numeric_dspan<V, true, (int)DS_MAX_COLS, true>)
+                                       : (l.span_cols <= 1024   ? k_numeric_dspan<V, false, 1024, true>
+                                          : l.span_cols <= 2048 ? k_numeric_dspan<V, false, 2048, true>
+                                                                : k_numeric_dspan<V, false, (int)DS_MAX_COLS, true>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(A.rows + 1)), dim3(DS_THREADS), 0, s, A.rp, A.col, av, B.rp, B.col, bv, nullptr, A.rows,
+                       l.cmin, nullptr, l.out_col, ov, nullptr, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_placed_span(const Csr &A, const Csr &B, int dtype, const PlacedLaunch &l, hipStream_t s)
+{
+    if (A.rows <= 0) return hipSuccess;
+    if (l.cmin == nullptr || l.span_cols > DS_MAX_COLS) return hipErrorInvalidValue;
+    return dtype == OCEAN_F64 ? dispatch_placed_span<double>(A, B, l, s) : dispatch_placed_span<float>(A, B, l, s);
 }
 
 // ======================================================= hybrid kernel ====
@@ -1457,8 +1512,9 @@ static hipError_t dispatch(const Csr &A, const Csr &B, const NumLaunch &l, int /
         if (l.cmin == nullptr) return hipErrorInvalidValue;
 #define OCEAN_DSPAN(QUERY, COLS)                                                                                          \
     launch_in_pieces(l.count, 1, DS_THREADS, [&](int64_t first, int64_t n) {                                              \
-        hipLaunchKernelGGL((k_numeric_dspan<V, QUERY, COLS>), dim3((unsigned)n), dim3(DS_THREADS), 0, s, A.rp, A.col, av,      \
-                           B.rp, B.col, bv, l.rows + first, n, l.cmin, l.out_ptr, l.out_col, ov, l.row_nnz);              \
+        hipLaunchKernelGGL((k_numeric_dspan<V, QUERY, COLS, false>), dim3((unsigned)n), dim3(DS_THREADS), 0, s, A.rp, A.col,   \
+                           av, B.rp, B.col, bv, l.rows + first, n, l.cmin, l.out_ptr, l.out_col, ov, l.row_nnz,           \
+                           Placing<V>{});                                                                                 \
     })
 #define OCEAN_DSPAN_COLS(QUERY)                                                                                           \
     do {                                                                                                                  \

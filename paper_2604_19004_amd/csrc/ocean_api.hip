@@ -50,6 +50,7 @@ struct Scalars {
     double sample_sums[6];                        // products, estimates, per-row CR, its squares, rows counted
     int32_t flags;
     int32_t pad;
+    unsigned long long span_totals[SPAN_SLOTS * SPAN_STRIDE];   // see k_row_spans
     unsigned long long near_pairs[2];             // sampled entries of B, and those whose successor's column is 1 .. 4 larger
     unsigned long long row_totals[ROW_TOTAL_SLOTS * ROW_TOTAL_STRIDE];   // totals of the row-products pass, by slot
 };
@@ -258,7 +259,6 @@ struct Work {
     int64_t *prod = nullptr;
     int32_t *maxb = nullptr;
     int32_t *cmin = nullptr, *cmax = nullptr;            // column range a row can reach (k_row_spans)
-    int32_t *s_cmin = nullptr, *s_cmax = nullptr;        // the same of the sampled rows
     bool spans = false;                                   // cmin / cmax hold the ranges of all rows
     uint8_t *bin = nullptr;
     int32_t *cap = nullptr;
@@ -270,13 +270,15 @@ struct Work {
     int64_t *tmp_ptr2 = nullptr;
     int64_t *scan_tmp = nullptr;
     double *est = nullptr;
-    int64_t *sample_rows = nullptr;
+    int64_t *sample_prod = nullptr;                       // of the sampled rows: products, estimates, columns in reach
     double *sample_est = nullptr;
+    int32_t *sample_span = nullptr;
     // rows that are placed as they are sorted (placed.hip): words for units of four rows and more, cleared by the analysis
     unsigned long long *places = nullptr;
     uint32_t *counts = nullptr;
     int64_t place_words = 0;                               // 64-bit words of both
     int four_rows_lds = 0;                                 // see ROW_TOTAL_LDS
+    unsigned long long span_totals[SPAN_TOTALS] = {};      // of the ranges of all rows
     unsigned long long class_rows[SORT_CLASSES] = {};      // rows of each sort class, [0]: of none (known after the analysis)
 };
 
@@ -291,9 +293,9 @@ int work_alloc(Ctx &c, Work &w, int64_t m, int64_t n_sample, bool placing)
     const size_t o_tp = take((mm + 1) * 8), o_tp2 = take((mm + 1) * 8);
     const size_t o_scan = take((size_t)scan_tmp_elems(m) * 8 + 8);
     const size_t o_est = take(mm * 8);
-    const size_t o_sr = take((size_t)(n_sample + 1) * 8), o_se = take((size_t)(n_sample + 1) * 8);
+    const size_t o_sp = take((size_t)(n_sample + 1) * 8), o_se = take((size_t)(n_sample + 1) * 8);
     const size_t o_cmin = take(mm * 4), o_cmax = take(mm * 4);
-    const size_t o_scmin = take((size_t)(n_sample + 1) * 4), o_scmax = take((size_t)(n_sample + 1) * 4);
+    const size_t o_span = take((size_t)(n_sample + 1) * 4);
     const size_t units = (mm + 3) / 4;
     const size_t place_words = placing ? units + (units + 1) / 2 : 0, o_places = take(place_words * 8);
     char *b = static_cast<char *>(c.alloc(off));
@@ -317,12 +319,11 @@ int work_alloc(Ctx &c, Work &w, int64_t m, int64_t n_sample, bool placing)
     w.tmp_ptr2 = reinterpret_cast<int64_t *>(b + o_tp2);
     w.scan_tmp = reinterpret_cast<int64_t *>(b + o_scan);
     w.est = reinterpret_cast<double *>(b + o_est);
-    w.sample_rows = reinterpret_cast<int64_t *>(b + o_sr);
+    w.sample_prod = reinterpret_cast<int64_t *>(b + o_sp);
     w.sample_est = reinterpret_cast<double *>(b + o_se);
     w.cmin = reinterpret_cast<int32_t *>(b + o_cmin);
     w.cmax = reinterpret_cast<int32_t *>(b + o_cmax);
-    w.s_cmin = reinterpret_cast<int32_t *>(b + o_scmin);
-    w.s_cmax = reinterpret_cast<int32_t *>(b + o_scmax);
+    w.sample_span = reinterpret_cast<int32_t *>(b + o_span);
     HIP_TRY(hipMemsetAsync(w.sc, 0, sizeof(Scalars), c.s));
     w.bins_clean = true;
     return OCEAN_OK;
@@ -448,13 +449,10 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
 int run_sample(Ctx &c, Work &w, const Csr &A, const Csr *B, int vbytes, int64_t n_cols, const uint8_t *sketches, int m_regs,
                int64_t n_sample, const ocean_options &o, ocean_stats *S)
 {
-    HIP_TRY(launch_sample_rows(A.rows, n_sample, o.sample_seed, w.sample_rows, c.s));   // (= sample_rows_of on the host)
-    HIP_TRY(launch_hll_merge(A, sketches, m_regs, w.sample_rows, n_sample, w.prod, w.maxb, nullptr, n_cols, w.sample_est,
-                             nullptr, c.lanes_div, c.s));
-    const bool ranges = B != nullptr && o.dense_range == 1;
-    if (ranges) HIP_TRY(launch_row_spans(A, *B, w.sample_rows, n_sample, w.s_cmin, w.s_cmax, c.s));
-    HIP_TRY(launch_sample_reduce(w.sample_rows, n_sample, w.prod, w.sample_est, ranges ? w.s_cmin : nullptr, w.s_cmax, n_cols,
-                                 vbytes, o.bound_load_coef, w.sc->sample_sums, c.s));
+    HIP_TRY(launch_sample(A, o.dense_range == 1 ? B : nullptr, n_cols, sketches, m_regs, n_sample, o.sample_seed, w.prod, w.maxb, w.sample_est,
+                          w.sample_prod, w.sample_span, c.lanes_div, c.s));
+    HIP_TRY(launch_sample_reduce(n_sample, w.sample_prod, w.sample_est, w.sample_span, n_cols, vbytes, o.bound_load_coef,
+                                 w.sc->sample_sums, c.s));
     OC_TRY(fetch_scalars(c, w.sc));
     const double *ss = c.h->sample_sums;
     S->dense_range_rows = (int32_t)ss[5];
@@ -843,24 +841,37 @@ int select_tuned(double avg, double er, double cr, double products, double heavy
     return OCEAN_WF_SYMBOLIC;
 }
 
-// Sort class whose kernel takes every row and places it as it is sorted (placed.hip), 0: the rows go the general way.
+// How all rows are placed in one pass: as rows of a sort class (placed.hip), or by the dense accumulator over ranges of at
+// most span_cols columns.
+struct Placed {
+    int cls = 0;
+    int span_cols = 0;
+};
+
 // Placing leaves out the binning (60 us with its read-back) and the symbolic pass or the compaction (3 ps a product and more:
-// 3.2 and 5.1 for 200 000 rows of 361 products in fp64).  What it costs: below a wave's class every row is sorted as the
-// largest class; of rows that have a wave each, all that are in flight wait for the longest among them, and a long row is
-// nearly always among them.  Measured, 200 000 rows, fp64, whole call in us, placed / general (the faster of compaction and
-// symbolic pass), rows of 49, 121 and 196 products with one of 361, 1024 or 2025 among every thousand: 308 / 297, 395 / 305, 795 / 311;
-// 347 / 452, 431 / 457, 831 / 471; 410 / 603, 490 / 615, 876 / 625.  Equal rows: 25 products 221 / 330 (400 000), 225 390 / 560, 484 689 / 944,
-// 961 929 / 1272 (150 000), 2025 1390 / 1709 (100 000).
-int placed_class(const Csr &A, const Work &w, const Ctx &c, double products)
+// 3.2 and 5.1 for 200 000 rows of 361 products in fp64).
+// Sorted rows: below a wave's class every row is sorted as the largest class; of rows that have a wave each, all that are in
+// flight wait for the longest among them, and a long row is nearly always among them.  Measured, 200 000 rows, fp64, whole call
+// in us, placed / general (the faster of compaction and symbolic pass), rows of 49, 121 and 196 products with one of 361, 1024 or
+// 2025 among every thousand: 308 / 297, 395 / 305, 795 / 311; 347 / 452, 431 / 457, 831 / 471; 410 / 603, 490 / 615, 876 / 625.  Equal
+// rows: 25 products 221 / 330 (400 000), 225 390 / 560, 484 689 / 944, 961 929 / 1272 (150 000), 2025 1390 / 1709 (100 000).
+// Dense ranges: taken where every row has one and it is the accumulator for four fifths of them.
+bool choose_placed(const Csr &A, const Work &w, const Ctx &c, int64_t products, Placed *how)
 {
     constexpr double kWavePs[SORT_CLASSES] = {0, 1050, 1050, 1050, 1050, 1300, 1600, 2300, 2950, 4300, 5600, 10000, 12900};
-    if (w.class_rows[0] != 0) return 0;   // a row with more products or entries than the sort takes
+    if (w.spans) {
+        const unsigned long long *t = w.span_totals;
+        if ((c.h->flags & 8) || t[0] == 0 || t[1] != 0 || t[4] * 5 < t[0] * 4 || A.rows + 1 > most_blocks(256)) return false;
+        how->span_cols = (int)t[2];
+        return true;
+    }
+    if (w.class_rows[0] != 0) return false;   // a row with more products or entries than the sort takes
     int cls = 0;
     for (int k = 1; k < SORT_CLASSES; ++k)
         if (w.class_rows[k] != 0) cls = k;
-    if (cls == 0 || !((c.sort_mask >> cls) & 1u)) return 0;
-    if (placed_units(A.rows, cls) + 1 > most_blocks(256)) return 0;
-    double general = 60e6 + 3.0 * products, placed;   // ps
+    if (cls == 0 || !((c.sort_mask >> cls) & 1u)) return false;
+    if (placed_units(A.rows, cls) + 1 > most_blocks(256)) return false;
+    double general = 60e6 + 3.0 * (double)products, placed;   // ps
     for (int k = 1; k <= cls; ++k) general += (double)w.class_rows[k] * kSortClass[k].ps;
     if (kPlacedRows[cls] > 4) {
         placed = (double)A.rows * kSortClass[cls].ps;
@@ -872,26 +883,46 @@ int placed_class(const Csr &A, const Work &w, const Ctx &c, double products)
         for (int k = 1; k <= cls; ++k) sorted += (double)w.class_rows[k] * kWavePs[k];
         if (sorted > placed) placed = sorted;
     }
-    return placed < general ? cls : 0;
+    how->cls = cls;
+    return placed < general;
 }
 
 // C in one pass over the products.  What is reserved for it is the products, or, where the sample knows how they merge, an
 // eighth more than that promises (estimates are cut off at the products, which makes the ratio of rows that hardly merge up
 // to 7 % too large: 1.09 for 1.03); what does not fit is not written, the total tells, and the pass is repeated with as much as it needs.  *done = false: a
 // reservation was refused or a wait ran out, nothing is kept and the general way is open.
-int run_placed(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int cls, int workflow, const ocean_options &o, ocean_stats *st,
+int run_placed(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, const Placed &how, int workflow, const ocean_options &o, ocean_stats *st,
                ocean_stats *S, int64_t *c_rp, ocean_csr *C, bool *done)
 {
     *done = false;
     const int64_t m = A.rows;
     const size_t vbytes = dtype == OCEAN_F64 ? 8 : 4;
-    int64_t slots = S->products;
+    int64_t slots = how.span_cols != 0 ? (int64_t)w.span_totals[3] : S->products;
     if (workflow != OCEAN_WF_UPPER_BOUND && S->sampled_rows > 0 && S->sampled_cr > 1.0) {
         const double want = (double)S->products / S->sampled_cr * 1.125 + 4096.0;
         if (want < (double)slots) slots = (int64_t)want;
     }
     const size_t mem_total = device_facts().total_mem;
     const int64_t reserved = slots;
+    PlacedLaunch l{};
+    l.cls = how.cls;
+    l.prod = w.prod;
+    l.cmin = w.cmin;
+    l.span_cols = how.span_cols;
+    l.query_bitmap = c.query_bitmap;
+    l.pool = w.four_rows_lds;
+    l.c_rp = c_rp;
+    l.counts = w.counts;
+    l.places = w.places;
+    l.total = &w.sc->totals[0];
+    l.flags = &w.sc->flags;
+    int64_t place_words = w.place_words;
+    if (how.span_cols != 0) {   // (units of one row)
+        place_words = m + (m + 1) / 2;
+        l.places = static_cast<unsigned long long *>(c.alloc((size_t)place_words * 8));
+        if (!l.places) return OCEAN_OK;
+        l.counts = reinterpret_cast<uint32_t *>(l.places + m);
+    }
     int32_t *col = nullptr;
     void *val = nullptr;
     int64_t nnz_c = 0;
@@ -904,15 +935,19 @@ int run_placed(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int cls, 
             c.release(col);
             return OCEAN_OK;
         }
-        if (round > 0) HIP_TRY(hipMemsetAsync(w.places, 0, (size_t)w.place_words * 8, c.s));
+        if (round > 0 || how.span_cols != 0) HIP_TRY(hipMemsetAsync(l.places, 0, (size_t)place_words * 8, c.s));
         launch_ev = c.ev.size();
         OC_TRY(mark(c, OCEAN_ST_NUMERIC));
-        HIP_TRY(launch_placed(A, B, dtype, PlacedLaunch{cls, w.prod, w.four_rows_lds, c_rp, col, val, slots, w.counts, w.places,
-                                                        &w.sc->totals[0], &w.sc->flags}, c.s));
+        l.out_col = col;
+        l.out_val = val;
+        l.slots = slots;
+        if (how.span_cols != 0) HIP_TRY(launch_placed_span(A, B, dtype, l, c.s));
+        else HIP_TRY(launch_placed(A, B, dtype, l, c.s));
         OC_TRY(mark(c, OCEAN_ST_COMPACT));
         if (st && round == 0) {   // (complete even where C was cut short)
             OC_TRY(zero_bins(c, w));
-            HIP_TRY(launch_row_stats(m, workflow == OCEAN_WF_UPPER_BOUND ? 0 : 2, o.exact_load_coef, o.bound_load_coef, B.cols, w.prod,
+            const int fixed_bin = how.span_cols != 0 ? NB_DSPAN : -1;
+            HIP_TRY(launch_row_stats(m, workflow == OCEAN_WF_UPPER_BOUND ? 0 : 2, fixed_bin, o.exact_load_coef, o.bound_load_coef, B.cols, w.prod,
                                      A.rp, c_rp, w.sc->bin_count, w.sc->bin_prod, w.sc->bin_work, c.s));
         }
         OC_TRY(fetch_scalars(c, w.sc));
@@ -1072,15 +1107,29 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     // to be out of column order (first and last entry of a row then say nothing about its range).
     if ((o.dense_range == 2 || (o.dense_range == 1 && S->sampled_rows > 0 && (int64_t)S->dense_range_rows * 50 >= S->sampled_rows)) &&
         !(c.h->flags & 8)) {
-        HIP_TRY(launch_row_spans(A, B, nullptr, m, w.cmin, w.cmax, c.s));
-        if (bw_try == nullptr) HIP_TRY(launch_check_sorted(B, &w.sc->flags, c.s));   // (known from the window table otherwise)
-        w.spans = true;
+        int64_t *ends = static_cast<int64_t *>(c.alloc((size_t)B.rows * 8));
+        if (ends) {   // (out of memory: without ranges)
+            HIP_TRY(launch_check_sorted(B, &w.sc->flags, ends, c.s));
+            HIP_TRY(launch_row_spans(A, B, ends, w.prod, (int)vbytes, o.bound_load_coef, w.cmin, w.cmax, w.sc->span_totals, c.s));
+            w.spans = true;
+        }
     }
-    const int placed = placing && !w.spans ? placed_class(A, w, c, (double)P) : 0;
-    if (placed != 0) {
+    if (placing) {
+        Placed how;
+        if (w.spans) {
+            OC_TRY(fetch_scalars(c, w.sc));
+            for (int i = 0; i < SPAN_SLOTS * SPAN_STRIDE; ++i) {
+                const int k = i % SPAN_STRIDE;
+                if (k >= SPAN_TOTALS) continue;
+                const unsigned long long v = c.h->span_totals[i];
+                w.span_totals[k] = k == 2 ? (v > w.span_totals[k] ? v : w.span_totals[k]) : w.span_totals[k] + v;
+            }
+        }
         bool done = false;
-        S->hll_registers = m_regs;
-        OC_TRY(run_placed(c, w, A, B, dtype, placed, workflow, o, st, S, c_rp, C, &done));
+        if (choose_placed(A, w, c, P, &how)) {
+            S->hll_registers = m_regs;
+            OC_TRY(run_placed(c, w, A, B, dtype, how, workflow, o, st, S, c_rp, C, &done));
+        }
         if (done) return OCEAN_OK;
     }
     int32_t *t_col = nullptr;   // output region of the first attempt (C itself on the two-pass path)

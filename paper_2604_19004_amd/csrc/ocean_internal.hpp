@@ -245,6 +245,8 @@ constexpr int ROW_TOTAL_CLASS = 4;
 constexpr int ROW_TOTAL_LDS = ROW_TOTAL_CLASS + SORT_CLASSES;
 static_assert(ROW_TOTAL_LDS < ROW_TOTAL_STRIDE, "a word per class");
 
+constexpr int SPAN_TOTALS = 5, SPAN_SLOTS = 8, SPAN_STRIDE = 16;   // see k_row_spans (a slot has a line of its own)
+
 // Most workgroups of `threads` threads in one launch.  The runtime takes a grid's size in threads modulo 2^32 and reports
 // nothing (16 778 240 workgroups of 256 threads ran as 1024), so longer lists of rows go in several launches.
 constexpr int64_t most_blocks(int threads) { return 0xffffffffLL / threads; }
@@ -268,13 +270,14 @@ hipError_t launch_hll_sketch(const Csr &B, int m, uint8_t *sketches, int lanes_d
 hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const int64_t *rows, int64_t n_rows,
                             const int64_t *prod, const int32_t *maxb, const int64_t *b_rp, int64_t b_cols,
                             double *est, uint8_t *merged, int lanes_div, hipStream_t s);
-hipError_t launch_sample_rows(int64_t rows, int64_t ns, uint32_t seed, int64_t *out, hipStream_t s);
-hipError_t launch_row_spans(const Csr &A, const Csr &B, const int64_t *rows, int64_t n, int32_t *cmin, int32_t *cmax,
-                            hipStream_t s);
-hipError_t launch_check_sorted(const Csr &B, int32_t *flags, hipStream_t s);
-hipError_t launch_sample_reduce(const int64_t *rows, int64_t n_rows, const int64_t *prod, const double *est,
-                                const int32_t *cmin, const int32_t *cmax /*of the sampled rows, may be null*/,
-                                int64_t n_cols, int vbytes, double bound_coef,
+hipError_t launch_sample(const Csr &A, const Csr *B /*null: reach not asked for*/, int64_t b_cols, const uint8_t *sketches, int m,
+                         int64_t ns, uint32_t seed, const int64_t *prod, const int32_t *maxb, double *est, int64_t *prod_out,
+                         int32_t *span_out, int lanes_div, hipStream_t s);
+hipError_t launch_row_spans(const Csr &A, const Csr &B, const int64_t *ends, const int64_t *prod, int vbytes, double bound_coef,
+                                int32_t *cmin, int32_t *cmax, unsigned long long *totals, hipStream_t s);
+hipError_t launch_check_sorted(const Csr &B, int32_t *flags, int64_t *ends /*a word per row of B*/, hipStream_t s);
+hipError_t launch_sample_reduce(int64_t n_rows, const int64_t *prod, const double *est, const int32_t *span, int64_t n_cols, int vbytes,
+                                double bound_coef,
                                 double *out /*[6]: sum prod, sum est, sum cr, sum cr^2, rows, rows a dense range pays for*/,
                                 hipStream_t s);
 
@@ -307,7 +310,7 @@ hipError_t launch_place(int64_t m, const int32_t *in, int64_t *tile_sum, int64_t
                         unsigned long long *bin_cursor, int32_t *bin_rows, hipStream_t s);
 hipError_t launch_count_rows(int64_t m, const int32_t *nnz1, const int32_t *nnz2, int32_t *final_nnz, int64_t *tile_sum,
                              unsigned long long *overflowed, const uint8_t *bin_of_row, unsigned long long *work, hipStream_t s);
-hipError_t launch_row_stats(int64_t m, int mode, double coef, double bound_coef, int64_t n_cols, const int64_t *prod,
+hipError_t launch_row_stats(int64_t m, int mode, int fixed_bin, double coef, double bound_coef, int64_t n_cols, const int64_t *prod,
                             const int64_t *a_rp, const int64_t *c_rp, unsigned long long *bin_count,
                             unsigned long long *bin_prod, unsigned long long *work, hipStream_t s);
 int64_t scan_tmp_elems(int64_t n);   // words of tile sums for n rows
@@ -394,6 +397,9 @@ inline int64_t placed_units(int64_t m, int cls) { return (m + kPlacedRows[cls] -
 struct PlacedLaunch {
     int cls;                  // every row has at most this class's products and entries
     const int64_t *prod;      // products per row
+    const int32_t *cmin;      // dense ranges: first column each row can reach
+    int span_cols;            // and the most columns in a row's range
+    bool query_bitmap;        // and NumLaunch's
     int pool;                 // LDS of a workgroup: the most that four rows from a multiple of four on take (classes of whole waves)
     int64_t *c_rp;            // receives the row offsets of C
     int32_t *out_col;
@@ -405,6 +411,7 @@ struct PlacedLaunch {
     int32_t *flags;           // |= 32: a wait ran out and the result is not complete
 };
 hipError_t launch_placed(const Csr &A, const Csr &B, int dtype, const PlacedLaunch &l, hipStream_t s);
+hipError_t launch_placed_span(const Csr &A, const Csr &B, int dtype, const PlacedLaunch &l, hipStream_t s);   // numeric.hip; units of a row
 hipError_t launch_trim(int dtype, const int32_t *col, const void *val, int64_t n, int32_t *c_col, void *c_val, hipStream_t s);
 
 // compact.hip

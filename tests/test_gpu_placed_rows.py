@@ -138,3 +138,32 @@ def test_what_c_keeps_of_the_reservation(ob, columns, kept):
     slots = C.col_idx.untyped_storage().nbytes() // 4
     assert slots == (st["products"] if kept else st["nnz_c"])
     assert slots <= st["nnz_c"] * 8 // 7 + 65536
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("span", [600, 1024, 1025, 2048, 2049, 4096, 4097])
+def test_dense_ranges(ob, span, dtype):
+    """Rows whose columns lie in a window of exactly `span` columns, up to the accumulator's 4096 and one more; then the
+    same rows of B in no order."""
+    rng = np.random.default_rng(span)
+    windows, per, rows = 5, 70, 700
+    n = windows * span + 3
+    lists = []
+    for w in range(windows):
+        for _ in range(per):
+            inner = 1 + rng.choice(span - 2, 38, replace=False)
+            lists.append(3 + w * span + np.sort(np.concatenate([[0], inner, [span - 1]])))
+    B = _csr(len(lists), n, lists, rng, dtype)
+    a_lists = [per * int(rng.integers(0, windows)) + rng.choice(per, int(rng.integers(52, per + 1)), replace=False) for _ in range(rows)]
+    a_lists[0] = a_lists[rows // 3] = []
+    A = _csr(rows, B.rows, a_lists, rng, dtype)
+    nb = len(ob.bin_layout()[0])
+    for options in (dict(), dict(bitmap_query=0)):
+        C, st = _check(ob, A, B, f"{span} columns", placed=span <= 4096, tuned_min_products=0.0, **options)
+        if span <= 4096:
+            assert st["rows_per_bin"][nb] == rows - 2
+    mixed = _csr(len(lists), n, [rng.permutation(x) for x in lists], rng, dtype)
+    mixed.val[:] = B.val
+    C, st = ob.spgemm(ob.to_device(A), ob.to_device(mixed), tuned_min_products=0.0)
+    check_result(C, O.multiply_rows(A, mixed), A, f"{span} columns, rows of B in no order")
+    assert st["stage_ms"]["binning"] > 0.0
