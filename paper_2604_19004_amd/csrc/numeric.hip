@@ -659,13 +659,30 @@ k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
     int total;
     const int ex = block_exclusive_scan_i32<DS_THREADS>(__popc(word), s_wave, total);
     if (tid < DS_WORDS) s_pre[tid] = (uint32_t)ex;
-    int64_t o;
+    // thread t looks at columns t, t + 256, ...: the lanes of a wave read consecutive values and the present ones
+    // among them go to consecutive places of the output
+    auto rank_of = [&](int j) {   // -1: column j of the range is not there
+        const uint32_t wbits = s_bm[j >> 5];
+        return (wbits >> (j & 31)) & 1u ? (int)s_pre[j >> 5] + __popc(wbits & ((1u << (j & 31)) - 1u)) : -1;
+    };
     if constexpr (PLACED) {
-        if (tid < WAVE) {
-            if (tid == 0) {
-                if (s_bad) atomicOr(p.flags, FLAG_GAVE_UP);
-                post(p.counts + row, (uint32_t)total + 1u);
+        if (tid == 0) {
+            if (s_bad) atomicOr(p.flags, FLAG_GAVE_UP);
+            post(p.counts + row, (uint32_t)total + 1u);
+        }
+        __syncthreads();
+        // what goes out is put together while the place is being found (not for the widest ranges: 48 registers)
+        constexpr int PER = COLS <= 2048 ? COLS / DS_THREADS : 1;
+        int rank[PER];
+        V val[PER];
+        if constexpr (COLS <= 2048) {
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                rank[i] = rank_of(i * DS_THREADS + tid);
+                val[i] = (V)s_vals[i * DS_THREADS + tid];
             }
+        }
+        if (tid < WAVE) {
             const int64_t place = wait_for_place(p.places + row, p.flags);
             if (tid == 0) {
                 s_place = place;
@@ -676,28 +693,42 @@ k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
             }
         }
         __syncthreads();
-        o = s_place;
+        const int64_t o = s_place;
         if (o < 0 || o + total > p.slots) return;   // uniform
+        if constexpr (COLS <= 2048) {
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                if (rank[i] >= 0) {
+                    out_col[o + rank[i]] = c0 + i * DS_THREADS + tid;
+                    out_val[o + rank[i]] = val[i];
+                }
+            }
+        } else {
+            for (int j = tid; j < COLS; j += DS_THREADS) {
+                const int rank_j = rank_of(j);
+                if (rank_j >= 0) {
+                    out_col[o + rank_j] = c0 + j;
+                    out_val[o + rank_j] = (V)s_vals[j];
+                }
+            }
+        }
     } else {
         __syncthreads();
-        o = out_ptr[row];
+        const int64_t o = out_ptr[row];
         const int64_t cap = out_ptr[row + 1] - o;
         if (s_bad || (int64_t)total > cap) {   // uniform
             if (tid == 0) row_nnz[row] = -1;
             return;
         }
-    }
-    // thread t looks at columns t, t + 256, ...: the lanes of a wave read consecutive values and the present ones
-    // among them go to consecutive places of the output
-    for (int j = tid; j < COLS; j += DS_THREADS) {
-        const uint32_t wbits = s_bm[j >> 5];
-        if ((wbits >> (j & 31)) & 1u) {
-            const int rank = (int)s_pre[j >> 5] + __popc(wbits & ((1u << (j & 31)) - 1u));
-            out_col[o + rank] = c0 + j;
-            out_val[o + rank] = (V)s_vals[j];
+        for (int j = tid; j < COLS; j += DS_THREADS) {
+            const int rank = rank_of(j);
+            if (rank >= 0) {
+                out_col[o + rank] = c0 + j;
+                out_val[o + rank] = (V)s_vals[j];
+            }
         }
+        if (tid == 0) row_nnz[row] = total;
     }
-    if (!PLACED && tid == 0) row_nnz[row] = total;
 }
 
 // All rows through the dense accumulator over their ranges, of at most l.span_cols columns, straight to their places.

@@ -855,36 +855,53 @@ struct Placed {
 // in us, placed / general (the faster of compaction and symbolic pass), rows of 49, 121 and 196 products with one of 361, 1024 or
 // 2025 among every thousand: 308 / 297, 395 / 305, 795 / 311; 347 / 452, 431 / 457, 831 / 471; 410 / 603, 490 / 615, 876 / 625.  Equal
 // rows: 25 products 221 / 330 (400 000), 225 390 / 560, 484 689 / 944, 961 929 / 1272 (150 000), 2025 1390 / 1709 (100 000).
-// Dense ranges: taken where every row has one and it is the accumulator for four fifths of them.
+// Dense ranges, where every row has one and it is the accumulator for four fifths of them: a row waits 3 us for its place, with
+// 2048 in flight, so placing pays from some 450 products a row on; sorting, where every row can be sorted, up to 700.
+// Block-diagonal matrices, fp64, whole call in us, placed dense / placed sorted / general: 300 000 rows of 324 products in blocks
+// of 300 columns 1352 / 734 / 1245, 200 000 of 399 in 500 970 / 636 / 950, 150 000 of 900 in 500 863 / 1104 / 1022, 100 000 of 1600
+// in 1000 749 / - / 886, of 1522 in 1300 787 / - / 929, 60 000 of 3602 in 1000 698 / - / 1030.
 bool choose_placed(const Csr &A, const Work &w, const Ctx &c, int64_t products, Placed *how)
 {
     constexpr double kWavePs[SORT_CLASSES] = {0, 1050, 1050, 1050, 1050, 1300, 1600, 2300, 2950, 4300, 5600, 10000, 12900};
+    const double rows = (double)A.rows;
+    double general = 60e6 + 3.0 * (double)products;   // ps
+    bool found = false;
     if (w.spans) {
         const unsigned long long *t = w.span_totals;
-        if ((c.h->flags & 8) || t[0] == 0 || t[1] != 0 || t[4] * 5 < t[0] * 4 || A.rows + 1 > most_blocks(256)) return false;
-        how->span_cols = (int)t[2];
-        return true;
+        if (c.h->flags & 8) return false;   // (B's rows are out of column order: the ranges are guesses)
+        general = 120e6 + 2400.0 * rows + 2.2 * (double)products;
+        if (t[0] != 0 && t[1] == 0 && t[4] * 5 >= t[0] * 4 && A.rows + 1 <= most_blocks(256)) {
+            const double placed = (t[2] > 2048 ? 4100.0 : t[2] > 1024 ? 3600.0 : 3100.0) * rows + 1.5 * (double)products;
+            if (placed < general) {
+                found = true;
+                how->span_cols = (int)t[2];
+                general = placed;
+            }
+        }
     }
-    if (w.class_rows[0] != 0) return false;   // a row with more products or entries than the sort takes
+    if (w.class_rows[0] != 0) return found;   // a row with more products or entries than the sort takes
     int cls = 0;
     for (int k = 1; k < SORT_CLASSES; ++k)
         if (w.class_rows[k] != 0) cls = k;
-    if (cls == 0 || !((c.sort_mask >> cls) & 1u)) return false;
-    if (placed_units(A.rows, cls) + 1 > most_blocks(256)) return false;
-    double general = 60e6 + 3.0 * (double)products, placed;   // ps
-    for (int k = 1; k <= cls; ++k) general += (double)w.class_rows[k] * kSortClass[k].ps;
+    if (cls == 0 || !((c.sort_mask >> cls) & 1u)) return found;
+    if (placed_units(A.rows, cls) + 1 > most_blocks(256)) return found;
+    double placed;
+    if (!w.spans)
+        for (int k = 1; k <= cls; ++k) general += (double)w.class_rows[k] * kSortClass[k].ps;
     if (kPlacedRows[cls] > 4) {
-        placed = (double)A.rows * kSortClass[cls].ps;
+        placed = rows * kSortClass[cls].ps;
     } else {
         const int by_lds = 160 * 1024 / w.four_rows_lds, by_registers = cls <= 10 ? 7 : cls == 11 ? 5 : 4;   // workgroups of a CU
         const double in_flight = 4.0 * c.n_cu * (by_lds < by_registers ? by_lds : by_registers);
-        placed = (double)A.rows / in_flight * (7.5e6 + 3.4e3 * kSortClass[cls].cap);   // the longest row's time
+        placed = rows / in_flight * (7.5e6 + 3.4e3 * kSortClass[cls].cap);   // the longest row's time
         double sorted = 0.0;
         for (int k = 1; k <= cls; ++k) sorted += (double)w.class_rows[k] * kWavePs[k];
         if (sorted > placed) placed = sorted;
     }
+    if (placed >= general) return found;
     how->cls = cls;
-    return placed < general;
+    how->span_cols = 0;
+    return true;
 }
 
 // C in one pass over the products.  What is reserved for it is the products, or, where the sample knows how they merge, an

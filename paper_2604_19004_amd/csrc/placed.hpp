@@ -126,7 +126,7 @@ __device__ __forceinline__ void place_units(const uint32_t *counts, unsigned lon
 __device__ __forceinline__ int64_t wait_for_place(const unsigned long long *place, int32_t *flags)
 {
     for (int i = 0; i < UNIT_POLLS; ++i) {
-        if (i > 0) __builtin_amdgcn_s_sleep(8);
+        if (i > 0) __builtin_amdgcn_s_sleep(1);
         const unsigned long long v = peek(place);
         const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
