@@ -129,11 +129,11 @@ __device__ __forceinline__ void for_long_rows(int64_t rows, int n_long, int32_t 
 // far longer than the average would keep its few lanes busy for a long time:
 // it is left to the workgroups for long rows.
 // Totals of the row-products pass.  Same-address atomics from all over the chip serialise in the L2 at about 12
-// ns each, and there is one set per workgroup: they are spread over ROW_TOTAL_SLOTS slots of 128 bytes (one
-// cache line each) by workgroup index and added up by whoever reads them (sum_row_totals on the host).
+// ns each, and there is one set per workgroup: they are spread over ROW_TOTAL_SLOTS slots of 256 bytes (two
+// cache lines each) by workgroup index and added up by whoever reads them (sum_row_totals on the host).
 // slot[0] += products, slot[1] = max(products of a row), slot[2] += products of the rows whose product count
 // exceeds heavy_from (the rows that outgrow the LDS hash tables), slot[3] += rows without products, then the rows of each
-// sort class and the most LDS of four sorted rows (ROW_TOTAL_CLASS, ROW_TOTAL_LDS).  s_tot: the workgroup's own, summed in
+// sort class, the most LDS of four sorted rows and the sums of sampled rows (ROW_TOTAL_CLASS, _LDS, _MERGE).  s_tot: the workgroup's own, summed in
 // LDS, so that its sums leave in one instruction.
 __device__ __forceinline__ void block_totals(long long tsum, long long tmax, long long theavy, int lds_most,
                                              unsigned long long *s_tot, unsigned long long *totals)
@@ -150,7 +150,7 @@ __device__ __forceinline__ void block_totals(long long tsum, long long tmax, lon
     }
     __syncthreads();
     const int t = threadIdx.x;
-    if (t <= ROW_TOTAL_LDS && s_tot[t] != 0ull) {
+    if (t < ROW_TOTALS && s_tot[t] != 0ull) {
         unsigned long long *slot = totals + (size_t)(blockIdx.x % ROW_TOTAL_SLOTS) * ROW_TOTAL_STRIDE;
         if (t == 1 || t == ROW_TOTAL_LDS) atomicMax(&slot[t], s_tot[t]);
         else atomicAdd(&slot[t], s_tot[t]);
@@ -208,18 +208,21 @@ __device__ __forceinline__ unsigned long long row_length(RowEnds e)
 // What bounds it: a gather of two row offsets of B per entry of A, one line a lane, which the address unit takes one a cycle,
 // and for rows of few entries the instructions per row.  Offsets come in one 16-byte load instead of two of 8, totals of a row go
 // through lane moves instead of LDS, and a row's class is found in 32 bits.
-template <int GL>
+// MERGE: n_merge workgroups, after those for long rows, count the different columns of MERGE_SAMPLE rows of C.  It is bound by a
+// chain of four loads, which ends before the other workgroups do.
+template <int GL, bool MERGE>
 __global__ void __launch_bounds__(TPB, 8)
 k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, int64_t m, int64_t a_nnz,
                const int64_t *__restrict__ b_rp, int64_t b_rows, int64_t long_from, int n_long,
                int64_t *__restrict__ prod, int32_t *__restrict__ maxb, unsigned long long *totals, int32_t *flags,
                int64_t heavy_from, int bad_bit, unsigned long long *near_pairs, unsigned long long *zero, int64_t zero_words,
-               int vbytes)
+               int vbytes, const int32_t *__restrict__ b_col, int64_t b_nnz, int n_merge)
 {
     constexpr int G = 1 << GL;
     constexpr int R = TPB >> GL;
     __shared__ unsigned int s_near, s_seen;
-    __shared__ unsigned long long s_tot[ROW_TOTAL_LDS + 1];
+    __shared__ unsigned long long s_tot[ROW_TOTALS];
+    __shared__ uint32_t s_seen_col[MERGE ? TPB / WAVE : 1][MERGE ? 2 * MERGE_PRODUCTS : 1];
     __shared__ unsigned long long s_sum[TPB / WAVE];
     __shared__ uint32_t s_max[TPB / WAVE];
     __shared__ int32_t s_list[TPB];
@@ -228,13 +231,15 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
     const int rl = tid >> GL;
     const int sub = tid & (G - 1);
     const bool for_long = (int)blockIdx.x < n_long;   // uniform
-    const int64_t block = (int64_t)blockIdx.x - n_long, blocks = (int64_t)gridDim.x - n_long;
-    const bool sampling = near_pairs != nullptr && !for_long && (block & 15) == 0;   // uniform
+    if (!MERGE) n_merge = 0;
+    const int64_t block = (int64_t)blockIdx.x - n_long - n_merge, blocks = (int64_t)gridDim.x - n_long - n_merge;
+    const bool for_merge = MERGE && !for_long && block < 0;        // uniform
+    const bool sampling = near_pairs != nullptr && block >= 0 && (block & 15) == 0;   // uniform
     unsigned int near = 0, seen = 0;
     long long tsum = 0, tmax = 0, theavy = 0;
     bool unsorted = false;
     int lds_most = 0;
-    if (tid <= ROW_TOTAL_LDS) s_tot[tid] = 0ull;
+    if (tid < ROW_TOTALS) s_tot[tid] = 0ull;
     for (int64_t i = (int64_t)blockIdx.x * TPB + tid; i < zero_words; i += (int64_t)gridDim.x * TPB) zero[i] = 0ull;
     __syncthreads();
     bool bad = false, bad_rp = bad_bit != 0 && blockIdx.x == 0 && tid == 0 && (a_rp[0] != 0 || a_rp[m] != a_nnz);
@@ -317,6 +322,55 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
                           }
                           __syncthreads();
                       });
+    } else if (for_merge) {   // (never without MERGE)
+        // The different columns among a row's products, by a wave: the offsets of B are not checked yet, nor are A's.
+        const int64_t turn = (int64_t)((int)blockIdx.x - n_long) * (TPB / WAVE) + tid / WAVE;
+        const int64_t part = m / MERGE_SAMPLE;   // (at least one row)
+        const int64_t row = turn * part + (int64_t)((uint32_t)turn * 2654435769u >> 8) % part;
+        uint32_t *seen_col = s_seen_col[tid / WAVE];
+        for (int i = lane_id(); i < 2 * MERGE_PRODUCTS; i += WAVE) seen_col[i] = 0xffffffffu;
+        wave_sync();
+        const int64_t e0 = a_rp[row], e1 = a_rp[row + 1];
+        bool fits = e0 >= 0 && e1 >= e0 && e1 <= a_nnz && e1 - e0 <= WAVE;   // uniform for the wave
+        int64_t p0 = 0;
+        uint32_t len = 0;
+        if (fits && e0 + lane_id() < e1) {
+            const int32_t k = a_col[e0 + lane_id()];
+            if ((uint32_t)k < (uint64_t)b_rows) {
+                const int64_t first = b_rp[k], end = b_rp[k + 1];
+                if (first >= 0 && end >= first && end <= b_nnz) {
+                    p0 = first;
+                    len = end - first > MERGE_PRODUCTS ? MERGE_PRODUCTS + 1 : (uint32_t)(end - first);
+                }
+            }
+        }
+        const uint32_t products = wave_sum_u32(len);
+        fits = fits && products <= (uint32_t)MERGE_PRODUCTS;
+        if (!fits) len = 0;
+        uint32_t fresh = 0;
+        for (uint32_t i = 0; i < len; i += 4) {
+            uint32_t col[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) col[u] = (uint32_t)b_col[p0 + (i + u < len ? i + u : i)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (i + u >= len) continue;
+                uint32_t at = col[u] * 2654435769u >> 23;   // (at most half of the 512 places are taken: a free one is met)
+                static_assert(MERGE_PRODUCTS == 256, "nine bits");
+                for (;;) {
+                    const uint32_t was = atomicCAS(&seen_col[at], 0xffffffffu, col[u]);
+                    fresh += was == 0xffffffffu;
+                    if (was == 0xffffffffu || was == col[u]) break;
+                    at = (at + 1) & (2 * MERGE_PRODUCTS - 1);
+                }
+            }
+        }
+        fresh = wave_sum_u32(fresh);
+        if (lane_id() == 0 && fits) {
+            atomicAdd(&s_tot[ROW_TOTAL_MERGE], (unsigned long long)products);
+            atomicAdd(&s_tot[ROW_TOTAL_MERGE + 1], (unsigned long long)fresh);
+            atomicAdd(&s_tot[ROW_TOTAL_MERGE + 2], 1ull);
+        }
     } else {
         for (int64_t base = block * R; base < m; base += blocks * R) {
             const int64_t row = base + rl;
@@ -365,10 +419,11 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
 // validate: A's offsets must begin at 0 and end at its number of entries as well, and any fault of A sets bit 1 of flags
 // (offsets that descend or leave [0, nnz] always do, column ids outside [0, b_rows) always set bit 4).  near_pairs (may
 // be null): see k_validate.  zero: zero_words words that the kernel clears on the way, for a later one.  vbytes:
-// bytes of a value, for the LDS that sorted rows take.
+// bytes of a value, for the LDS that sorted rows take.  merge_sample (may be null): B, to count the different columns of
+// MERGE_SAMPLE rows of C on the way, see run_placed.
 hipError_t launch_row_products(const Csr &A, const int64_t *b_rp, int64_t b_rows, int64_t *prod, int32_t *maxb,
                                unsigned long long *totals, int32_t *flags, bool validate, unsigned long long *near_pairs,
-                               unsigned long long *zero, int64_t zero_words, int vbytes, hipStream_t s)
+                               unsigned long long *zero, int64_t zero_words, int vbytes, const Csr *merge_sample, hipStream_t s)
 {
     const int64_t heavy_from = kNumericSlots[NB_S4K];   // beyond the largest LDS hash table that sorted inputs use
     if (A.rows == 0) return hipSuccess;
@@ -379,11 +434,15 @@ hipError_t launch_row_products(const Csr &A, const int64_t *b_rp, int64_t b_rows
     int64_t blocks = (A.rows + R - 1) / R;
     if (blocks > 2048) blocks = 2048;
     const int n_long = A.nnz >= long_from ? long_row_blocks(A.rows) : 0;
-    const auto kernel = g_log2 == 1 ? k_row_products<1> : g_log2 == 2 ? k_row_products<2> : g_log2 == 3 ? k_row_products<3>
-                        : g_log2 == 4 ? k_row_products<4> : g_log2 == 5 ? k_row_products<5> : k_row_products<6>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks + n_long)), dim3(TPB), 0, s, A.rp, A.col, A.rows, A.nnz, b_rp,
-                       b_rows, long_from, n_long, prod, maxb, totals, flags, heavy_from, validate ? 1 : 0, near_pairs, zero,
-                       zero_words, vbytes);
+    const int n_merge = merge_sample != nullptr && A.rows >= MERGE_SAMPLE && g_log2 <= 4 ? MERGE_SAMPLE / (TPB / WAVE) : 0;
+    const auto kernel = n_merge != 0 ? (g_log2 == 1 ? k_row_products<1, true> : g_log2 == 2 ? k_row_products<2, true>
+                                        : g_log2 == 3 ? k_row_products<3, true> : k_row_products<4, true>)
+                        : g_log2 == 1 ? k_row_products<1, false> : g_log2 == 2 ? k_row_products<2, false>
+                        : g_log2 == 3 ? k_row_products<3, false> : g_log2 == 4 ? k_row_products<4, false>
+                        : g_log2 == 5 ? k_row_products<5, false> : k_row_products<6, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks + n_long + n_merge)), dim3(TPB), 0, s, A.rp, A.col, A.rows, A.nnz,
+                       b_rp, b_rows, long_from, n_long, prod, maxb, totals, flags, heavy_from, validate ? 1 : 0, near_pairs, zero,
+                       zero_words, vbytes, n_merge != 0 ? merge_sample->col : nullptr, n_merge != 0 ? merge_sample->nnz : 0, n_merge);
     return hipGetLastError();
 }
 

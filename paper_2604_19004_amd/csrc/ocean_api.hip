@@ -56,13 +56,13 @@ struct Scalars {
 };
 
 // P, largest row, and the other totals of the row-products pass from the slots of a fetched Scalars
-using RowTotals = unsigned long long[ROW_TOTAL_LDS + 1];
+using RowTotals = unsigned long long[ROW_TOTALS];
 void sum_row_totals(const Scalars *h, RowTotals &out)
 {
     for (unsigned long long &o : out) o = 0;
     for (int i = 0; i < ROW_TOTAL_SLOTS; ++i) {
         const unsigned long long *slot = h->row_totals + (size_t)i * ROW_TOTAL_STRIDE;
-        for (int k = 0; k <= ROW_TOTAL_LDS; ++k) {
+        for (int k = 0; k < ROW_TOTALS; ++k) {
             if (k == 1 || k == ROW_TOTAL_LDS) out[k] = slot[k] > out[k] ? slot[k] : out[k];
             else out[k] += slot[k];
         }
@@ -278,6 +278,8 @@ struct Work {
     uint32_t *counts = nullptr;
     int64_t place_words = 0;                               // 64-bit words of both
     int four_rows_lds = 0;                                 // see ROW_TOTAL_LDS
+    bool merge_sample = false;                             // the different columns of a few rows are to be counted
+    double merge_cr = 0.0;                                 // their products / columns, 0: not known of all of them
     unsigned long long span_totals[SPAN_TOTALS] = {};      // of the ranges of all rows
     unsigned long long class_rows[SORT_CLASSES] = {};      // rows of each sort class, [0]: of none (known after the analysis)
 };
@@ -347,12 +349,15 @@ int run_analysis(Ctx &c, Work &w, const Csr &A, const Csr &B, int vbytes, bool v
     const bool same = B.rp == A.rp && B.col == A.col && B.rows == A.rows && B.cols == A.cols && B.nnz == A.nnz;
     if (validate && !same) HIP_TRY(launch_validate(B, &w.sc->flags, w.sc->near_pairs, c.s));
     HIP_TRY(launch_row_products(A, B.rp, B.rows, w.prod, w.maxb, w.sc->row_totals, &w.sc->flags, validate,
-                                validate && same ? w.sc->near_pairs : nullptr, w.places, w.place_words, vbytes, c.s));
+                                validate && same ? w.sc->near_pairs : nullptr, w.places, w.place_words, vbytes,
+                                w.merge_sample ? &B : nullptr, c.s));
     OC_TRY(fetch_scalars(c, w.sc));
     RowTotals tot;
     sum_row_totals(c.h, tot);
     std::memcpy(w.class_rows, tot + ROW_TOTAL_CLASS, sizeof(w.class_rows));
     w.four_rows_lds = 4 * sort_row_bytes(256, vbytes);   // (at least, see k_row_products)
+    if (tot[ROW_TOTAL_MERGE + 2] == (unsigned long long)MERGE_SAMPLE && tot[ROW_TOTAL_MERGE + 1] != 0ull)
+        w.merge_cr = (double)tot[ROW_TOTAL_MERGE] / (double)tot[ROW_TOTAL_MERGE + 1];
     if (tot[ROW_TOTAL_LDS] > (unsigned long long)w.four_rows_lds) w.four_rows_lds = (int)tot[ROW_TOTAL_LDS];
     if (c.h->flags & 1) return fail(OCEAN_EINVAL, "A is not a valid CSR matrix (row offsets or column ids out of range)");
     if (c.h->flags & 2) return fail(OCEAN_EINVAL, "B is not a valid CSR matrix (row offsets or column ids out of range)");
@@ -919,6 +924,14 @@ int run_placed(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, const Pla
         const double want = (double)S->products / S->sampled_cr * 1.125 + 4096.0;
         if (want < (double)slots) slots = (int64_t)want;
     }
+    // The upper-bound workflow samples nothing, but the analysis counted the columns of MERGE_SAMPLE rows: an eighth is some
+    // standard deviations of what so many rows say, unless few rows hold most of the products.  Reserving every product and
+    // copying C out of it was 53 of the 354 us of a Laplacian of 1024^2 (297 now), 10 of the 116 of one of 257^2; the count
+    // ends before the pass that it is part of does (31 us, as before).
+    if (workflow == OCEAN_WF_UPPER_BOUND && w.merge_cr > 1.0 && (double)S->max_row_products <= 8.0 * S->avg_products) {
+        const double want = (double)S->products / w.merge_cr * 1.125 + 4096.0;
+        if (want < (double)slots) slots = (int64_t)want;
+    }
     const size_t mem_total = device_facts().total_mem;
     const int64_t reserved = slots;
     PlacedLaunch l{};
@@ -1047,6 +1060,11 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     const bool placing = c.sort_mask != 0u && !esc_ok && B.nnz < (1LL << 29) && (o.workflow == OCEAN_WF_AUTO || o.workflow == OCEAN_WF_UPPER_BOUND) &&
                          o.estimate_scale == 1.0 && o.dense_range != 2 && o.compact_in_place < 0;
     OC_TRY(work_alloc(c, w, m, n_sample, placing));
+    // Where the products promise to be many enough for a trim and few enough a row for the upper-bound workflow (which samples
+    // nothing), some rows' columns are counted.
+    const double expect = B.rows > 0 ? (double)A.nnz * ((double)B.nnz / (double)B.rows) : 0.0;
+    w.merge_sample = placing && expect >= 8.0 * 65536.0 &&
+                     (o.workflow == OCEAN_WF_UPPER_BOUND || expect < o.upper_bound_avg_products * (double)m);
     ocean_stats local{};
     ocean_stats *S = st ? st : &local;
     OC_TRY(run_analysis(c, w, A, B, (int)vbytes, o.validate_inputs != 0, S));
@@ -1489,7 +1507,7 @@ int ocean_row_products(const ocean_csr *A, const ocean_csr *B, int64_t *prod, in
     int32_t *maxb = reinterpret_cast<int32_t *>(buf + up(sizeof(Scalars)));
     int rc = [&]() -> int {
         HIP_TRY(hipMemsetAsync(sc, 0, sizeof(Scalars), c.s));
-        HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, false, nullptr, nullptr, 0, 8, c.s));
+        HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, false, nullptr, nullptr, 0, 8, nullptr, c.s));
         OC_TRY(fetch_scalars(c, sc));
         RowTotals tot;
         sum_row_totals(c.h, tot);
@@ -1542,7 +1560,7 @@ int ocean_row_products_noalloc(const ocean_csr *A, const ocean_csr *B, int64_t *
     // the scalars keep the last call's sums: clear them (a fill kernel, so that the call can be captured
     // into a graph); the per-row arrays are written before they are read
     HIP_TRY(launch_fill_u64(reinterpret_cast<unsigned long long *>(sc), (int64_t)(NOALLOC_SCALARS / 8), 0ull, s));
-    HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, false, nullptr, nullptr, 0, 8, s));
+    HIP_TRY(launch_row_products(view(A), B->row_ptr, B->rows, prod, maxb, sc->row_totals, &sc->flags, false, nullptr, nullptr, 0, 8, nullptr, s));
     HIP_TRY(launch_publish_totals(sc->row_totals, &sc->flags, totals, s));
     return OCEAN_OK;
 }

@@ -238,12 +238,16 @@ __host__ __device__ constexpr int sort_row_bytes(int pr, int vbytes)
 // Totals of the row-products pass are kept in ROW_TOTAL_SLOTS slots of ROW_TOTAL_STRIDE 64-bit words each (256
 // bytes apart): [0] sum of products, [1] largest row, [2] products of the heavy rows, [3] rows of A without a product,
 // [4 + c] rows of sort class c (the smallest that holds the row; 0: none does), then the most LDS that four rows from
-// a multiple of four on take where a wave sorts a row (sort_row_bytes); see analysis.hip.
+// a multiple of four on take where a wave sorts a row (sort_row_bytes), then products, different columns and number of the
+// rows whose columns were counted (MERGE_SAMPLE of them, where asked for); see analysis.hip.
 constexpr int ROW_TOTAL_SLOTS = 32;
 constexpr int ROW_TOTAL_STRIDE = 32;
 constexpr int ROW_TOTAL_CLASS = 4;
 constexpr int ROW_TOTAL_LDS = ROW_TOTAL_CLASS + SORT_CLASSES;
-static_assert(ROW_TOTAL_LDS < ROW_TOTAL_STRIDE, "a word per class");
+constexpr int ROW_TOTAL_MERGE = ROW_TOTAL_LDS + 1, ROW_TOTALS = ROW_TOTAL_MERGE + 3;
+static_assert(ROW_TOTALS <= ROW_TOTAL_STRIDE, "a word per class");
+constexpr int MERGE_SAMPLE = 512;        // rows
+constexpr int MERGE_PRODUCTS = 256;      // of a row whose columns are counted, at most
 
 constexpr int SPAN_TOTALS = 5, SPAN_SLOTS = 8, SPAN_STRIDE = 16;   // see k_row_spans (a slot has a line of its own)
 
@@ -264,7 +268,7 @@ inline void launch_in_pieces(int64_t count, int rows_per_block, int threads, Go 
 hipError_t launch_validate(const Csr &B, int32_t *flags, unsigned long long *near_pairs, hipStream_t s);
 hipError_t launch_row_products(const Csr &A, const int64_t *b_rp, int64_t b_rows, int64_t *prod, int32_t *maxb,
                                unsigned long long *totals, int32_t *flags, bool validate, unsigned long long *near_pairs,
-                               unsigned long long *zero, int64_t zero_words, int vbytes, hipStream_t s);
+                               unsigned long long *zero, int64_t zero_words, int vbytes, const Csr *merge_sample, hipStream_t s);
 hipError_t launch_publish_totals(const unsigned long long *totals, const int32_t *flags, int64_t *out, hipStream_t s);
 hipError_t launch_hll_sketch(const Csr &B, int m, uint8_t *sketches, int lanes_div, hipStream_t s);
 hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const int64_t *rows, int64_t n_rows,

@@ -136,7 +136,9 @@ def test_what_c_keeps_of_the_reservation(ob, columns, kept):
     A = _csr(30000, 500, [rng.choice(500, 7, replace=False) for _ in range(30000)], rng, np.float32)
     C, st = _check(ob, A, B, "reservation")
     slots = C.col_idx.untyped_storage().nbytes() // 4
-    assert slots == (st["products"] if kept else st["nnz_c"])
+    # (where the columns of 512 rows were counted C keeps what they promise, which the bound below covers: the trim has its
+    # cases in test_gpu_merge_sample)
+    assert slots == (st["products"] if kept else st["temp_slots"])
     assert slots <= st["nnz_c"] * 8 // 7 + 65536
 
 
