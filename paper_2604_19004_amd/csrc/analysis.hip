@@ -208,8 +208,9 @@ __device__ __forceinline__ unsigned long long row_length(RowEnds e)
 // What bounds it: a gather of two row offsets of B per entry of A, one line a lane, which the address unit takes one a cycle,
 // and for rows of few entries the instructions per row.  Offsets come in one 16-byte load instead of two of 8, totals of a row go
 // through lane moves instead of LDS, and a row's class is found in 32 bits.
-// MERGE: n_merge workgroups, after those for long rows, count the different columns of MERGE_SAMPLE rows of C.  It is bound by a
-// chain of four loads, which ends before the other workgroups do.
+// MERGE: n_merge workgroups, after those for long rows, count the different columns of MERGE_SAMPLE rows of C.  It is bound by
+// a chain of four to eleven loads, which ends before the other workgroups do; with rows of B of any length it did not (R-MAT
+// scale 15: 29 us instead of 17).
 template <int GL, bool MERGE>
 __global__ void __launch_bounds__(TPB, 8)
 k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, int64_t m, int64_t a_nnz,
@@ -340,7 +341,7 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
                 const int64_t first = b_rp[k], end = b_rp[k + 1];
                 if (first >= 0 && end >= first && end <= b_nnz) {
                     p0 = first;
-                    len = end - first > MERGE_PRODUCTS ? MERGE_PRODUCTS + 1 : (uint32_t)(end - first);
+                    len = end - first > MERGE_LENGTH ? MERGE_PRODUCTS + 1 : (uint32_t)(end - first);
                 }
             }
         }

@@ -248,6 +248,7 @@ constexpr int ROW_TOTAL_MERGE = ROW_TOTAL_LDS + 1, ROW_TOTALS = ROW_TOTAL_MERGE 
 static_assert(ROW_TOTALS <= ROW_TOTAL_STRIDE, "a word per class");
 constexpr int MERGE_SAMPLE = 512;        // rows
 constexpr int MERGE_PRODUCTS = 256;      // of a row whose columns are counted, at most
+constexpr int MERGE_LENGTH = 32;         // of the rows of B that it names: a lane walks one
 
 constexpr int SPAN_TOTALS = 5, SPAN_SLOTS = 8, SPAN_STRIDE = 16;   // see k_row_spans (a slot has a line of its own)
 

@@ -18,6 +18,20 @@ def _counted(rows):
 
 
 # `entries` entries a row, each naming a row of B of 8 entries; a merging row names 8 rows of B four times each
+@pytest.mark.parametrize("length, counted", [(32, True), (33, False)])
+def test_long_rows_of_b(ob, length, counted):  # noqa: F811
+    """A row of B longer than a lane walks: nothing is promised."""
+    rng = np.random.default_rng(length)
+    B = _csr(64, 600, [np.sort(rng.choice(600, length, replace=False)) for _ in range(64)], rng, np.float64)
+    lists = [np.resize(rng.permutation(64)[:1], 4) for _ in range(9000)]
+    A = _csr(9000, 64, lists, rng, np.float64)
+    C, st = ob.spgemm(ob.to_device(A), ob.to_device(B), workflow=ob.WF_UPPER_BOUND)
+    check_result(C, O.multiply_rows(A, B), A, f"rows of B of {length}")
+    products = 9000 * 4 * length
+    assert st["stage_ms"]["binning"] == 0.0
+    assert st["temp_slots"] == (int(products / 4 * 1.125 + 4096.0) if counted else products)
+
+
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
 @pytest.mark.parametrize("rows, entries, merging, expect", [
     (2048, 32, "all", "counted"), (2049, 32, "all", "counted"), (9001, 32, "all", "counted"), (2047, 32, "all", "products"),
