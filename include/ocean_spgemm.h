@@ -196,8 +196,8 @@ typedef struct ocean_stats {
      * bin and bin_ms of the two before it is 0.  Rows of few products are sorted instead of hashed, in one launch
      * per size class whatever their bins (a class whose rows merge into few columns: in one hash table): a launch's
      * time is reported under the bin that holds most of its products.  Where every row is one of those (at most 2048 products
-     * and 64 entries of A) and nothing else was asked for, AUTO and the upper-bound workflow sort all rows in one launch
-     * and write them straight to C: no symbolic pass (symbolic_rows_per_bin and assist_cr stay 0), no binning stage, no
+     * and 64 entries of A), or the columns of nearly every row lie in a short range, nothing else was asked for and it
+     * is expected to be faster, AUTO and the upper-bound workflow accumulate all rows in one launch and write them straight to C: no symbolic pass (symbolic_rows_per_bin and assist_cr stay 0), no binning stage, no
      * overflow; rows count in the bin that the workflow's prediction, exact for the two others, would have given them. */
     float bin_ms[OCEAN_MAX_BINS];
     int64_t bin_products[OCEAN_MAX_BINS];
