@@ -430,7 +430,10 @@ hipError_t launch_row_products(const Csr &A, const int64_t *b_rp, int64_t b_rows
     if (A.rows == 0) return hipSuccess;
     const double avg = (double)A.nnz / (double)A.rows;
     const int g_log2 = ilog2_ceil(avg / 4.0, 1, 6);   // (a lane keeps four entries in flight)
-    const int64_t long_from = (int64_t)32 << g_log2;    // eight turns of the group
+    // Long: eight turns of the group, and more entries than any sort class takes, as the LDS of four sorted rows is summed up
+    // where the rows that are not long are (with two lanes a row eight turns are 64 entries, which can be sorted).
+    const int64_t turns = (int64_t)32 << g_log2, unsorted_from = kSortClass[SORT_CLASSES - 1].entries + 1;
+    const int64_t long_from = turns > unsorted_from ? turns : unsorted_from;
     const int R = TPB >> g_log2;
     int64_t blocks = (A.rows + R - 1) / R;
     if (blocks > 2048) blocks = 2048;

@@ -103,6 +103,31 @@ def test_all_sizes_in_one_matrix(ob, most, dtype):
             _check(ob, A, B, "a row too long", placed=extra == [0] * 65, workflow=ob.WF_UPPER_BOUND)
 
 
+def _wide_row(rng, entries, total):
+    """`entries` entries of A whose rows of B have `total` entries together."""
+    row = np.full(entries, total // entries) + (np.arange(entries) < total % entries)
+    return rng.permutation(row) + 64 * rng.integers(0, 2, entries) * (row > 0)
+
+
+# 2 and 7 entries a row: 64 entries are as many as a group of two lanes takes; 9: of four lanes
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("short", [2, 7, 9])
+@pytest.mark.parametrize("products", [800, 1500, 2048])
+def test_rows_of_64_entries_among_short_ones(ob, products, short, dtype):
+    rng = np.random.default_rng(products + short)
+    B = _b(rng, 5000, dtype, "sorted")
+    lists = [_wide_row(rng, short, 30 * short) for _ in range(4096)]
+    for unit in range(4):                               # at each place of a unit of four rows
+        lists[400 * unit + unit] = _wide_row(rng, 64, products - unit)
+    lists[2001:2004] = [_wide_row(rng, 64, products) for _ in range(3)]
+    A = _csr(len(lists), B.rows, lists, rng, dtype)
+    for wf in (ob.WF_UPPER_BOUND, ob.WF_AUTO):
+        _check(ob, A, B, f"64 entries, {products} products", workflow=wf)
+    lists[9] = _wide_row(rng, 65, products)             # an entry more than the sort takes
+    A = _csr(len(lists), B.rows, lists, rng, dtype)
+    _check(ob, A, B, "65 entries", placed=False, workflow=ob.WF_UPPER_BOUND)
+
+
 # units of 32, 16, 8 and 4 rows: around a wave of counts, the 1024 of a turn and several turns
 @pytest.mark.parametrize("units", [1, 63, 64, 65, 1023, 1024, 1025, 5000])
 @pytest.mark.parametrize("rows_per_unit, products", [(32, 20), (16, 60), (8, 150), (4, 300)])
