@@ -390,12 +390,16 @@ k_row_products(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
             }
             group_totals<GL>(p, mx);
             if (mine && sub == 0) store(row, ne, p, mx);
-            // (more lanes: rows that a wave does not sort; where no row of the wave has more than 256 products, four rows take
-            // the least there is, which the host knows)
-            if (GL <= 4 && __ballot(p > 256ull) != 0ull) {
+            // (with more lanes a wave has fewer than four rows: four times the row that takes most.  Where no row of the wave
+            // has more than 256 products, four rows take the least there is, which the host knows)
+            if (__ballot(p > 256ull) != 0ull) {
                 int lds = sort_row_bytes(p < 2048ull ? (int)p : 2048, vbytes);
-                lds += __shfl_xor(lds, G, WAVE);
-                lds += __shfl_xor(lds, 2 * G, WAVE);
+                if constexpr (GL <= 4) {
+                    lds += __shfl_xor(lds, G, WAVE);
+                    lds += __shfl_xor(lds, 2 * G, WAVE);
+                } else {
+                    lds *= 4;
+                }
                 lds_most = lds > lds_most ? lds : lds_most;
             }
         }

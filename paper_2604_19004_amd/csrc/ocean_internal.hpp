@@ -238,8 +238,8 @@ __host__ __device__ constexpr int sort_row_bytes(int pr, int vbytes)
 // Totals of the row-products pass are kept in ROW_TOTAL_SLOTS slots of ROW_TOTAL_STRIDE 64-bit words each (256
 // bytes apart): [0] sum of products, [1] largest row, [2] products of the heavy rows, [3] rows of A without a product,
 // [4 + c] rows of sort class c (the smallest that holds the row; 0: none does), then the most LDS that four rows from
-// a multiple of four on take where a wave sorts a row (sort_row_bytes), then products, different columns and number of the
-// rows whose columns were counted (MERGE_SAMPLE of them, where asked for); see analysis.hip.
+// a multiple of four on take where a wave sorts a row (sort_row_bytes; no less than that), then products, different
+// columns and number of the rows whose columns were counted (MERGE_SAMPLE of them, where asked for); see analysis.hip.
 constexpr int ROW_TOTAL_SLOTS = 32;
 constexpr int ROW_TOTAL_STRIDE = 32;
 constexpr int ROW_TOTAL_CLASS = 4;

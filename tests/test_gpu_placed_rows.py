@@ -128,6 +128,23 @@ def test_rows_of_64_entries_among_short_ones(ob, products, short, dtype):
     _check(ob, A, B, "65 entries", placed=False, workflow=ob.WF_UPPER_BOUND)
 
 
+# more than 64 and 128 entries a row on average: groups of 32 and 64 lanes
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("entries", [100, 300])
+@pytest.mark.parametrize("products", [257, 800, 2048])
+def test_sorted_rows_among_long_ones_without_products(ob, products, entries, dtype):
+    rng = np.random.default_rng(products + entries)
+    B = _b(rng, 5000, dtype, "sorted")
+    lists = [[0] * entries for _ in range(1500)]        # of B's empty row: in no sort class, and none is needed
+    for r in range(0, 1500, 7):
+        lists[r] = _row(rng, products - r % 5)
+    lists[640:644] = [_wide_row(rng, 64, products) for _ in range(4)]
+    A = _csr(len(lists), B.rows, lists, rng, dtype)
+    assert A.row_ptr[-1] > (128 if entries == 300 else 64) * A.rows
+    for wf in (ob.WF_UPPER_BOUND, ob.WF_AUTO):
+        _check(ob, A, B, f"{products} products among rows of {entries} entries", workflow=wf)
+
+
 # units of 32, 16, 8 and 4 rows: around a wave of counts, the 1024 of a turn and several turns
 @pytest.mark.parametrize("units", [1, 63, 64, 65, 1023, 1024, 1025, 5000])
 @pytest.mark.parametrize("rows_per_unit, products", [(32, 20), (16, 60), (8, 150), (4, 300)])
