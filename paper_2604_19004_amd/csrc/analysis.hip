@@ -722,13 +722,15 @@ __device__ __forceinline__ void hll_walk(const int64_t *__restrict__ a_rp, const
 // by a hash of the stratum's number and the seed: the same rows as the host helper behind ocean_sample_rows gives.
 struct SampleOf {
     int64_t rows, ns;
+    int64_t first;                  // number of the launch's first sampled row
     uint32_t seed;
     int64_t whole_from;             // rows of so many entries count as reaching everywhere
     const int32_t *b_col;           // null: reach not asked for
     int64_t *prod_out;              // products of the sampled rows
     int32_t *span_out;              // columns they can reach, 0: none, the largest number: everywhere
-    __device__ __forceinline__ int64_t row(int64_t t) const
+    __device__ __forceinline__ int64_t row(int64_t slot) const
     {
+        const int64_t t = first + slot;
         const uint64_t lo = (uint64_t)t * (uint64_t)rows / (uint64_t)ns;
         const uint64_t hi = (uint64_t)(t + 1) * (uint64_t)rows / (uint64_t)ns;
         return (int64_t)(lo + fmix32(seed + 0x9E3779B9u * (uint32_t)(t + 1)) % (hi - lo));
@@ -957,12 +959,15 @@ hipError_t launch_sample(const Csr &A, const Csr *B, int64_t b_cols, const uint8
     while ((1 << g_log2) < L) ++g_log2;
     const int64_t long_from = 8.0 * avg > (double)MG_LONG ? (int64_t)(8.0 * avg) : MG_LONG;
     const int64_t whole_from = ((int64_t)64 << ilog2_ceil(avg / 4.0, 1, 6)) + 1;   // (as k_row_spans)
-    const SampleOf sample{A.rows, ns, seed, whole_from < long_from ? whole_from : long_from, B ? B->col : nullptr, prod_out, span_out};
+    const int64_t whole = whole_from < long_from ? whole_from : long_from;
     const auto kernel = m == 32 ? k_hll_merge<32, true> : m == 64 ? k_hll_merge<64, true> : k_hll_merge<128, true>;
-    const int64_t blocks = ((ns << g_log2) + TPB - 1) / TPB;
-    if (blocks > most_blocks(TPB)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, reinterpret_cast<const uint64_t *>(sketches), nullptr,
-                       ns, g_log2, long_from, long_from, true, 0, prod, maxb, B ? B->rp : nullptr, b_cols, est, nullptr, sample);
+    const int rows_per_block = TPB >> g_log2;
+    launch_in_pieces(ns, rows_per_block, TPB, [&](int64_t first, int64_t n) {
+        const SampleOf sample{A.rows, ns, first, seed, whole, B ? B->col : nullptr, prod_out + first, span_out + first};
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((n + rows_per_block - 1) / rows_per_block)), dim3(TPB), 0, s, A.rp, A.col,
+                           reinterpret_cast<const uint64_t *>(sketches), nullptr, n, g_log2, long_from, long_from, true, 0, prod, maxb,
+                           B ? B->rp : nullptr, b_cols, est + first, nullptr, sample);
+    });
     return hipGetLastError();
 }
 

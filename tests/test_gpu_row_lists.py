@@ -89,3 +89,46 @@ def test_more_estimates_than_one_launch_takes(ob):
     assert bool(((est.view(-1, PERIOD) - want).abs() <= 1e-12 * want).all())
     del dA, est
     torch.cuda.empty_cache()
+
+
+def test_larger_sample_than_one_launch_takes(ob):
+    """Every row sampled, sketches of 128 registers merged along rows of 5 entries in a matrix with one far larger row: 64
+    threads a row."""
+    import torch
+    rng = np.random.default_rng(5)
+    rows, entries, n, m = (1 << 26) + 1024, 5, 5000, 128
+    lengths = np.concatenate([rng.integers(0, 4, PERIOD - 1), [300]])
+    b_ptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    B = CSR(PERIOD, n, b_ptr, np.concatenate([np.sort(rng.choice(n, k, replace=False)) for k in lengths]).astype(np.int32),
+            rng.uniform(-1, 1, int(b_ptr[-1])).astype(np.float32))
+    head_col = rng.integers(0, PERIOD - 1, (PERIOD + 1, entries)).astype(np.int32)
+    head_col[PERIOD] = head_col[PERIOD - 1]              # the matrix's last row: that of the period, and the long row of B
+    head_col[PERIOD, -1] = PERIOD - 1
+    head = CSR(PERIOD + 1, PERIOD, np.arange(PERIOD + 2, dtype=np.int64) * entries, head_col.reshape(-1),
+               np.ones(head_col.size, np.float32))
+    prod = O.row_products(head, B)
+    longest = lengths[head_col].max(axis=1)
+    est = np.clip(ohll.estimate(ohll.merge_rows(head, ohll.sketch_rows(B, m))), longest, np.minimum(prod, n))
+    times = np.concatenate([np.full(PERIOD, rows // PERIOD), [1]])
+    times[PERIOD - 1] -= 1
+    assert prod[PERIOD] > 16 * (prod * times).sum() / rows
+    col = torch.from_numpy(head_col[:PERIOD].reshape(-1)).cuda().repeat(rows // PERIOD)
+    col[-entries:] = torch.from_numpy(head_col[PERIOD]).cuda()
+    dA = ob.DeviceCSR(rows, PERIOD, torch.arange(rows + 1, dtype=torch.int64, device="cuda:0") * entries, col,
+                      torch.ones(rows * entries, device="cuda:0"))
+    print(f"{rows} sampled rows", flush=True)
+    nnz, st = ob.symbolic(dA, ob.to_device(B), ob.default_options(assisted_symbolic=2, hll_registers=m, sample_ratio=1.0,
+                                                                   sample_max=2 ** 31 - 1))
+    some = est > 0
+    ratio = np.divide(prod, est, where=some, out=np.zeros(est.size))
+    mean = (ratio * times).sum() / times[some].sum()
+    # (sums of at most 2^26 terms of equal sign in 64 bits)
+    assert st["sampled_rows"] == rows
+    assert abs(st["sampled_cr"] - (prod * times).sum() / (est * times).sum()) < 1e-8
+    assert abs(st["cr_mean"] - mean) < 1e-8
+    assert abs(st["cr_std"] ** 2 - ((ratio - mean) ** 2 * times)[some].sum() / times[some].sum()) < 1e-7
+    ref = O.multiply_rows(head, B)
+    want = torch.from_numpy(np.diff(ref.row_ptr).astype(np.int32)).cuda()
+    assert bool((nnz[:rows - PERIOD].view(-1, PERIOD) == want[:PERIOD]).all()) and int(nnz[-1]) == int(want[PERIOD])
+    del dA, nnz, col
+    torch.cuda.empty_cache()
