@@ -728,6 +728,8 @@ struct SampleOf {
     const int32_t *b_col;           // null: reach not asked for
     int64_t *prod_out;              // products of the sampled rows
     int32_t *span_out;              // columns they can reach, 0: none, the largest number: everywhere
+    const int32_t *count_col;       // B's columns, for the rows whose columns are counted
+    double *count_out;              // products and columns of each
     __device__ __forceinline__ int64_t row(int64_t slot) const
     {
         const int64_t t = first + slot;
@@ -805,9 +807,63 @@ __device__ __forceinline__ void hll_row_by_all(Regs16 (*s_regs)[M / 16], long lo
     __syncthreads();
 }
 
+// The different columns of a row of C, by a workgroup: a bit for each by 17 bits of its hash, and what that many places with
+// so many taken stand for (linear counting: of up to 8192 columns some 0.2 % off at one standard deviation; sketches of 64
+// registers are 13 %, and rows over the same columns all err alike).  A wave takes an entry of A, four in flight: the chain
+// offsets -> entries -> offsets of B -> columns, up to four times over, ends before the merge of the sample that runs
+// beside it.  A row with more than COUNT_ENTRIES entries would not; its products count as so many columns.
+constexpr int COUNT_LOG2 = 17;
+__device__ __forceinline__ void count_columns(uint32_t *s_bits, int *s_n, const int64_t *__restrict__ a_rp,
+                                              const int32_t *__restrict__ a_col, const int64_t *__restrict__ b_rp,
+                                              const int32_t *__restrict__ b_col, int64_t row, int64_t products, double *__restrict__ out)
+{
+    constexpr int WORDS = 1 << (COUNT_LOG2 - 5), U = 4, NW = TPB / WAVE;
+    const int tid = threadIdx.x;
+    for (int i = tid; i < WORDS; i += TPB) s_bits[i] = 0u;
+    if (tid == 0) *s_n = 0;
+    __syncthreads();
+    const int64_t e0 = a_rp[row], e1 = a_rp[row + 1];
+    const bool walked = products <= COUNT_PRODUCTS && e1 - e0 <= COUNT_ENTRIES;   // uniform
+    for (int64_t e = e0 + tid / WAVE; walked && e < e1; e += U * NW) {
+        int32_t k[U];
+        RowEnds ends[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) k[i] = a_col[e + i * NW < e1 ? e + i * NW : e];
+#pragma unroll
+        for (int i = 0; i < U; ++i) ends[i] = *reinterpret_cast<const RowEnds *>(b_rp + k[i]);
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int64_t p0 = (int64_t)(((unsigned long long)ends[i].y << 32) | ends[i].x);
+            const int len = e + i * NW < e1 ? (int)row_length(ends[i]) : 0;
+            for (int q0 = lane_id(); q0 < len; q0 += U * WAVE) {
+                int32_t c[U];
+#pragma unroll
+                for (int j = 0; j < U; ++j) c[j] = b_col[p0 + (q0 + j * WAVE < len ? q0 + j * WAVE : q0)];
+#pragma unroll
+                for (int j = 0; j < U; ++j) {   // (a column twice is no harm)
+                    const uint32_t h = hll_hash(c[j]) >> (32 - COUNT_LOG2);
+                    atomicOr(&s_bits[h >> 5], 1u << (h & 31u));
+                }
+            }
+        }
+    }
+    __syncthreads();
+    int ones = 0;
+    for (int i = tid; i < WORDS; i += TPB) ones += __popc(s_bits[i]);
+    ones = group_reduce_sum(ones, WAVE);
+    if (lane_id() == 0) atomicAdd(s_n, ones);
+    __syncthreads();
+    if (tid == 0) {
+        const double places = (double)(1 << COUNT_LOG2), columns = -places * log1p(-(double)*s_n / places);
+        out[0] = (double)products;
+        out[1] = walked && columns < (double)products ? columns : (double)products;
+    }
+}
+
 // (8: with the code for long rows beside it the compiler would take 96 registers and leave 5 waves per SIMD; 10 % slower
 // on 256 000 rows of 34 entries)
-// SAMPLE: the rows are the sample's, whose products and reach are written beside their estimates.
+// SAMPLE: the rows are the sample's, whose products and reach are written beside their estimates; n_long workgroups at the front
+// count the columns of rows of it.
 template <int M, bool SAMPLE>
 __global__ void __launch_bounds__(TPB, 8)
 k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
@@ -822,7 +878,13 @@ k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
     __shared__ int s_nlong;
     __shared__ Regs16 s_regs[TPB / WAVE][L];
     __shared__ long long s_blen[TPB / WAVE];
+    __shared__ uint32_t s_bits[SAMPLE ? 1 << (COUNT_LOG2 - 5) : 1];
     const int G = 1 << g_log2;  // >= L
+    if (SAMPLE && (int)blockIdx.x < n_long) {   // uniform
+        const int64_t row = sample.row((int64_t)blockIdx.x * sample.ns / n_long);
+        count_columns(s_bits, &s_nlong, a_rp, a_col, b_rp, sample.count_col, row, prod[row], sample.count_out + 2 * blockIdx.x);
+        return;
+    }
     auto take = [&](int64_t t2) {
         hll_row_by_all<M, TPB, 4>(s_regs, s_blen, a_rp, a_col, sk, t2, row_of(t2), prod, maxb, b_rp, b_cols, est, merged);
     };
@@ -864,7 +926,7 @@ k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
         mine = ne < long_from;
         if (SAMPLE && ne < sample.whole_from) reach.b_col = sample.b_col;
         if (mine) hll_walk<L, 4, SAMPLE>(a_rp, a_col, sk, b_rp, row, slice, part, parts, acc, blen_max, &reach);
-        else if (n_long == 0 && sub == 0) s_long[atomicAdd(&s_nlong, 1)] = (int32_t)t;
+        else if ((SAMPLE || n_long == 0) && sub == 0) s_long[atomicAdd(&s_nlong, 1)] = (int32_t)t;
     }
     const Regs16 all = lanes_max(acc.get(), L, G);
     if (SAMPLE) {
@@ -947,10 +1009,11 @@ hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const 
     return hipGetLastError();
 }
 
-// Estimates, products and, with B given, reach of the ns sampled rows: one launch for what the sample looks at.
-hipError_t launch_sample(const Csr &A, const Csr *B, int64_t b_cols, const uint8_t *sketches, int m, int64_t ns, uint32_t seed,
-                         const int64_t *prod, const int32_t *maxb, double *est, int64_t *prod_out, int32_t *span_out, int lanes_div,
-                         hipStream_t s)
+// Estimates, products and, with `reach` (B) given, reach of the ns sampled rows, and, with `count` (B) given, products and
+// columns of count_rows(ns) of them: one launch for what the sample looks at.
+hipError_t launch_sample(const Csr &A, const Csr *reach, const Csr *count, int64_t b_cols, const uint8_t *sketches, int m, int64_t ns,
+                         uint32_t seed, const int64_t *prod, const int32_t *maxb, double *est, int64_t *prod_out, int32_t *span_out,
+                         double *count_out, int lanes_div, hipStream_t s)
 {
     if (ns <= 0) return hipSuccess;
     const int L = m / 16;
@@ -961,13 +1024,18 @@ hipError_t launch_sample(const Csr &A, const Csr *B, int64_t b_cols, const uint8
     const int64_t whole_from = ((int64_t)64 << ilog2_ceil(avg / 4.0, 1, 6)) + 1;   // (as k_row_spans)
     const int64_t whole = whole_from < long_from ? whole_from : long_from;
     const auto kernel = m == 32 ? k_hll_merge<32, true> : m == 64 ? k_hll_merge<64, true> : k_hll_merge<128, true>;
+    const int64_t *b_rp = reach ? reach->rp : count ? count->rp : nullptr;
     const int rows_per_block = TPB >> g_log2;
-    launch_in_pieces(ns, rows_per_block, TPB, [&](int64_t first, int64_t n) {
-        const SampleOf sample{A.rows, ns, first, seed, whole, B ? B->col : nullptr, prod_out + first, span_out + first};
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((n + rows_per_block - 1) / rows_per_block)), dim3(TPB), 0, s, A.rp, A.col,
-                           reinterpret_cast<const uint64_t *>(sketches), nullptr, n, g_log2, long_from, long_from, true, 0, prod, maxb,
-                           B ? B->rp : nullptr, b_cols, est + first, nullptr, sample);
-    });
+    const int64_t most = (most_blocks(TPB) - COUNT_ROWS) * rows_per_block;
+    for (int64_t first = 0; first < ns; first += most) {
+        const int64_t n = ns - first < most ? ns - first : most;
+        const int n_count = first == 0 && count ? count_rows(ns) : 0;
+        const SampleOf sample{A.rows, ns, first, seed, whole, reach ? reach->col : nullptr, prod_out + first, span_out + first,
+                              count ? count->col : nullptr, count_out};
+        const int64_t blocks = (n + rows_per_block - 1) / rows_per_block + n_count;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, reinterpret_cast<const uint64_t *>(sketches),
+                           nullptr, n, g_log2, long_from, long_from, true, n_count, prod, maxb, b_rp, b_cols, est + first, nullptr, sample);
+    }
     return hipGetLastError();
 }
 
@@ -1112,15 +1180,16 @@ hipError_t launch_check_sorted(const Csr &B, int32_t *flags, int64_t *ends, hipS
 // out[0] = sum of products, out[1] = sum of estimates (their ratio is the sampled CR, Section 3.2);
 // out[2], out[3] = sum and sum of squares of the per-row ratios products / estimate, out[4] = rows counted
 // (mean and standard deviation of the compression ratio over the sample, Section 4.1); out[5] = sampled rows
-// whose column range is narrow enough for the dense accumulator to pay.
+// whose column range is narrow enough for the dense accumulator to pay; out[6] .. [10] = sums of the products, the columns,
+// and their squares and product (products, columns, both) over the n_count rows whose columns were counted.
 constexpr int SR_THREADS = 1024;
-constexpr int SR_SUMS = 6;
+constexpr int SR_SUMS = SAMPLE_SUMS;
 __global__ void __launch_bounds__(SR_THREADS)
 k_sample_reduce(int64_t n_rows, const int64_t *__restrict__ prod, const double *__restrict__ est, const int32_t *__restrict__ span,
-                int64_t n_cols, int vbytes, double bound_coef, double *out)
+                int64_t n_cols, int vbytes, double bound_coef, const double *__restrict__ counted, int n_count, double *out)
 {
     __shared__ double s_acc[SR_THREADS / WAVE][SR_SUMS];
-    double acc[SR_SUMS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    double acc[SR_SUMS] = {};
     // four sampled rows per thread and turn, their loads issued together
     for (int64_t t0 = threadIdx.x; t0 < n_rows; t0 += 4 * SR_THREADS) {
         double e[4], p[4];
@@ -1145,9 +1214,14 @@ k_sample_reduce(int64_t n_rows, const int64_t *__restrict__ prod, const double *
             }
         }
     }
+    static_assert(COUNT_ROWS <= SR_THREADS, "one per thread");
+    if ((int)threadIdx.x < n_count) {
+        const double p = counted[2 * threadIdx.x], q = counted[2 * threadIdx.x + 1];
+        acc[6] = p; acc[7] = q; acc[8] = p * p; acc[9] = q * q; acc[10] = p * q;
+    }
 #pragma unroll
     for (int k = 0; k < SR_SUMS; ++k) {
-        const double wave = group_reduce_sum(acc[k], WAVE);
+        const double wave = k < 6 || n_count > 0 ? group_reduce_sum(acc[k], WAVE) : 0.0;   // (uniform)
         if (lane_id() == 0) s_acc[threadIdx.x / WAVE][k] = wave;
     }
     __syncthreads();
@@ -1159,9 +1233,10 @@ k_sample_reduce(int64_t n_rows, const int64_t *__restrict__ prod, const double *
 }
 
 hipError_t launch_sample_reduce(int64_t n_rows, const int64_t *prod, const double *est, const int32_t *span, int64_t n_cols, int vbytes,
-                                double bound_coef, double *out, hipStream_t s)
+                                double bound_coef, const double *counted, int n_count, double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_sample_reduce, dim3(1), dim3(SR_THREADS), 0, s, n_rows, prod, est, span, n_cols, vbytes, bound_coef, out);
+    hipLaunchKernelGGL(k_sample_reduce, dim3(1), dim3(SR_THREADS), 0, s, n_rows, prod, est, span, n_cols, vbytes, bound_coef, counted,
+                       n_count, out);
     return hipGetLastError();
 }
 

@@ -47,7 +47,7 @@ struct Scalars {
     unsigned long long max_cap;
     unsigned long long ovf_count;
     unsigned long long queue[4];
-    double sample_sums[6];                        // products, estimates, per-row CR, its squares, rows counted
+    double sample_sums[SAMPLE_SUMS];              // see k_sample_reduce
     int32_t flags;
     int32_t pad;
     unsigned long long span_totals[SPAN_SLOTS * SPAN_STRIDE];   // see k_row_spans
@@ -273,6 +273,8 @@ struct Work {
     int64_t *sample_prod = nullptr;                       // of the sampled rows: products, estimates, columns in reach
     double *sample_est = nullptr;
     int32_t *sample_span = nullptr;
+    double *counted = nullptr;                            // products and columns of the sampled rows whose columns are counted
+    double count_cr = 0.0, count_error = 0.0;             // their products / columns, 0: not counted, and its relative error
     // rows that are placed as they are sorted (placed.hip): words for units of four rows and more, cleared by the analysis
     unsigned long long *places = nullptr;
     uint32_t *counts = nullptr;
@@ -298,7 +300,7 @@ int work_alloc(Ctx &c, Work &w, int64_t m, int64_t n_sample, bool placing)
     const size_t o_est = take(mm * 8);
     const size_t o_sp = take((size_t)(n_sample + 1) * 8), o_se = take((size_t)(n_sample + 1) * 8);
     const size_t o_cmin = take(mm * 4), o_cmax = take(mm * 4);
-    const size_t o_span = take((size_t)(n_sample + 1) * 4);
+    const size_t o_span = take((size_t)(n_sample + 1) * 4), o_counted = take((size_t)COUNT_ROWS * 16);
     const size_t units = (mm + 3) / 4;
     const size_t place_words = placing ? units + (units + 1) / 2 : 0, o_places = take(place_words * 8);
     char *b = static_cast<char *>(c.alloc(off));
@@ -327,6 +329,7 @@ int work_alloc(Ctx &c, Work &w, int64_t m, int64_t n_sample, bool placing)
     w.cmin = reinterpret_cast<int32_t *>(b + o_cmin);
     w.cmax = reinterpret_cast<int32_t *>(b + o_cmax);
     w.sample_span = reinterpret_cast<int32_t *>(b + o_span);
+    w.counted = reinterpret_cast<double *>(b + o_counted);
     HIP_TRY(hipMemsetAsync(w.sc, 0, sizeof(Scalars), c.s));
     w.bins_clean = true;
     return OCEAN_OK;
@@ -452,14 +455,16 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
 
 // ---- sampled compression ratio (Section 3.2) and its spread over the sample (Section 4.1) ------------
 // With B given (dense_range = 1) the column ranges of the sampled rows are looked at too: S->dense_range_rows is
-// the number of sampled rows for which the dense accumulator over the row's range would be chosen.
-int run_sample(Ctx &c, Work &w, const Csr &A, const Csr *B, int vbytes, int64_t n_cols, const uint8_t *sketches, int m_regs,
+// the number of sampled rows for which the dense accumulator over the row's range would be chosen.  count: so are the columns
+// of some of them.
+int run_sample(Ctx &c, Work &w, const Csr &A, const Csr *B, bool count, int vbytes, int64_t n_cols, const uint8_t *sketches, int m_regs,
                int64_t n_sample, const ocean_options &o, ocean_stats *S)
 {
-    HIP_TRY(launch_sample(A, o.dense_range == 1 ? B : nullptr, n_cols, sketches, m_regs, n_sample, o.sample_seed, w.prod, w.maxb, w.sample_est,
-                          w.sample_prod, w.sample_span, c.lanes_div, c.s));
-    HIP_TRY(launch_sample_reduce(n_sample, w.sample_prod, w.sample_est, w.sample_span, n_cols, vbytes, o.bound_load_coef,
-                                 w.sc->sample_sums, c.s));
+    const int n_count = count ? count_rows(n_sample) : 0;
+    HIP_TRY(launch_sample(A, o.dense_range == 1 ? B : nullptr, count ? B : nullptr, n_cols, sketches, m_regs, n_sample, o.sample_seed, w.prod,
+                          w.maxb, w.sample_est, w.sample_prod, w.sample_span, w.counted, c.lanes_div, c.s));
+    HIP_TRY(launch_sample_reduce(n_sample, w.sample_prod, w.sample_est, w.sample_span, n_cols, vbytes, o.bound_load_coef, w.counted,
+                                 n_count, w.sc->sample_sums, c.s));
     OC_TRY(fetch_scalars(c, w.sc));
     const double *ss = c.h->sample_sums;
     S->dense_range_rows = (int32_t)ss[5];
@@ -469,6 +474,12 @@ int run_sample(Ctx &c, Work &w, const Csr &A, const Csr *B, int vbytes, int64_t 
         S->cr_mean = ss[2] / ss[4];
         const double var = ss[3] / ss[4] - S->cr_mean * S->cr_mean;
         S->cr_std = var > 0.0 ? std::sqrt(var) : 0.0;
+    }
+    if (n_count >= 32 && ss[7] > 0.0) {
+        // standard error of a ratio of sums: the residuals columns - products / CR
+        const double per = ss[7] / ss[6], rest = ss[9] - 2.0 * per * ss[10] + per * per * ss[8];
+        w.count_cr = ss[6] / ss[7];
+        w.count_error = rest > 0.0 ? std::sqrt(rest) / ss[7] : 0.0;
     }
     return OCEAN_OK;
 }
@@ -921,10 +932,12 @@ bool choose_placed(const Csr &A, const Work &w, const Ctx &c, int64_t products, 
     return true;
 }
 
-// C in one pass over the products.  What is reserved for it is the products, or, where the sample knows how they merge, an
-// eighth more than that promises (estimates are cut off at the products, which makes the ratio of rows that hardly merge up
-// to 7 % too large: 1.09 for 1.03); what does not fit is not written, the total tells, and the pass is repeated with as much as it needs.  *done = false: a
-// reservation was refused or a wait ran out, nothing is kept and the general way is open.
+// C in one pass over the products.  What is reserved for it is a bound (the products, or the lesser of them and the ranges), or,
+// where the columns of sampled rows were counted, what they promise, four standard errors and a 64th more, if that is less.  (Not
+// what the sketches promise: rows over the same columns all err alike, and by more than an eighth for a tenth, with 64 registers a
+// third, of the numbers of columns up to 6000.  An eighth more than the estimates, 200 000 rows of 2040 products on 1500 columns:
+// 2967 us, the pass twice; general 1854.)  What does not fit is not written, the total tells, and the pass is repeated with as much
+// as it needs.  *done = false: a reservation was refused or a wait ran out, nothing is kept and the general way is open.
 int run_placed(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, const Placed &how, int workflow, const ocean_options &o, ocean_stats *st,
                ocean_stats *S, int64_t *c_rp, ocean_csr *C, bool *done)
 {
@@ -932,8 +945,8 @@ int run_placed(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, const Pla
     const int64_t m = A.rows;
     const size_t vbytes = dtype == OCEAN_F64 ? 8 : 4;
     int64_t slots = how.span_cols != 0 ? (int64_t)w.span_totals[3] : S->products;
-    if (workflow != OCEAN_WF_UPPER_BOUND && S->sampled_rows > 0 && S->sampled_cr > 1.0) {
-        const double want = (double)S->products / S->sampled_cr * 1.125 + 4096.0;
+    if (workflow != OCEAN_WF_UPPER_BOUND && w.count_cr > 0.0) {
+        const double want = (double)S->products / w.count_cr * (1.0 + 1.0 / 64.0 + 4.0 * w.count_error) + 4096.0;
         if (want < (double)slots) slots = (int64_t)want;
     }
     // The upper-bound workflow samples nothing, but the analysis counted the columns of MERGE_SAMPLE rows: an eighth is some
@@ -1128,7 +1141,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         } else {
             OC_TRY(build_sketches());
             OC_TRY(mark(c, OCEAN_ST_SAMPLE));
-            OC_TRY(run_sample(c, w, A, &B, (int)vbytes, n, sketches, m_regs, n_sample, o, S));
+            OC_TRY(run_sample(c, w, A, &B, placing && S->max_row_products <= COUNT_PRODUCTS, (int)vbytes, n, sketches, m_regs, n_sample, o, S));
             workflow = o.selector == OCEAN_SEL_MI355X
                            ? select_tuned(S->avg_products, S->er, S->sampled_cr, (double)P, (double)S->heavy_products, o)
                            : select_of(S->avg_products, S->er, S->sampled_cr, o);
@@ -1137,7 +1150,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     if (workflow == OCEAN_WF_SYMBOLIC && o.assisted_symbolic == 2 && S->sampled_rows == 0) {
         OC_TRY(build_sketches());
         OC_TRY(mark(c, OCEAN_ST_SAMPLE));
-        OC_TRY(run_sample(c, w, A, &B, (int)vbytes, n, sketches, m_regs, n_sample, o, S));
+        OC_TRY(run_sample(c, w, A, &B, placing && S->max_row_products <= COUNT_PRODUCTS, (int)vbytes, n, sketches, m_regs, n_sample, o, S));
     }
 
     // Section 4.1 / 4.3: dense accumulators query the bitmap before writing when the (sampled) CR is at least 2
@@ -1633,7 +1646,7 @@ int ocean_symbolic(const ocean_csr *A, const ocean_csr *B, int32_t *nnz_per_row,
             if (!sketches) return fail(OCEAN_EALLOC, "sketch allocation failed");
             c.lanes_div = lanes_div_of(S);
             HIP_TRY(launch_hll_sketch(b, m_regs, sketches, c.lanes_div, c.s));
-            OC_TRY(run_sample(c, w, a, nullptr, 8, b.cols, sketches, m_regs, n_sample, o, S));
+            OC_TRY(run_sample(c, w, a, nullptr, false, 8, b.cols, sketches, m_regs, n_sample, o, S));
             S->hll_registers = m_regs;
             assist_cr = conservative_cr(S, o);
             if (!(assist_cr > 1.0)) assist_cr = 0.0;

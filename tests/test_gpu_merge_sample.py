@@ -1,8 +1,10 @@
-"""What the upper-bound workflow reserves for placed rows: an eighth more than the columns counted for 512 rows promise, or, where
-they were not all counted or say nothing about the others, every product; and a pass repeated because the counted rows misled."""
+"""What is reserved for placed rows.  Upper-bound workflow: an eighth more than the columns counted for 512 rows promise, or, where
+they were not all counted or say nothing about the others, every product; and a pass repeated because the counted rows misled.
+The other workflows: what the columns of sampled rows promise."""
 import numpy as np
 import pytest
 
+from oracle import hll as ohll
 from oracle import spgemm as O
 from test_gpu_placed_rows import _csr, ob  # noqa: F401
 from test_gpu_spgemm import check_result
@@ -64,3 +66,42 @@ def test_reservation(ob, rows, entries, merging, expect, dtype):  # noqa: F811
         assert C.col_idx.untyped_storage().nbytes() // 4 == (st["nnz_c"] if trimmed else had)
         assert trimmed == (merging in ("all", "others") and expect == "products")
         assert st["temp_slots"] == (int(products / 4 * 1.125 + 4096.0) if expect == "counted" else products)
+
+
+def _count(hashes):
+    """Columns as the sample counts them: by 17 bits of their hashes (linear counting)."""
+    places = 1 << 17
+    return -places * np.log1p(-np.unique(hashes >> (32 - 17)).size / places)
+
+
+# entries of A of a row, rows of B, their entries, columns; numbers of columns for which sketches say an eighth too little
+@pytest.mark.parametrize("entries, k, length, n, all_counted", [(34, 2000, 60, 1500, True), (40, 1000, 30, 400, True), (20, 1000, 20, 300, True),
+                                                                (2, 40, 1000, 3500, True), (0, 1000, 8, 5000, True), (257, 2000, 9, 1500, False)])
+def test_sample_counts_columns(ob, entries, k, length, n, all_counted):  # noqa: F811
+    """What the other workflows reserve: what up to 512 sampled rows' columns promise, four standard errors and a 64th more; no
+    pass is repeated for an error that all rows' sketches have in common."""
+    rng = np.random.default_rng(n)
+    B = _csr(k, n, [[]] + [np.sort(rng.choice(n, length, replace=False)) for _ in range(k - 1)], rng, np.float64)
+    lists = [rng.choice(k, entries or int(rng.integers(0, 65)), replace=False) for _ in range(4000)]
+    lists[7] = []
+    if entries == 0:                                     # half of the rows merge four times over
+        lists = [np.resize(x[: (len(x) + 3) // 4], len(x)) if r % 2 else x for r, x in enumerate(lists)]
+    A = _csr(len(lists), k, lists, rng, np.float64)
+    C, st = ob.spgemm(ob.to_device(A), ob.to_device(B), tuned_min_products=0.0)
+    check_result(C, O.multiply_rows(A, B), A, f"{entries} entries, {n} columns")
+    assert st["stage_ms"]["binning"] == 0.0 and st["sampled_rows"] > 512
+    sampled = ob.sample_rows(A.rows)
+    counted = sampled[np.arange(512) * sampled.size // 512]
+    prod = O.row_products(A, B)
+    of = [B.col_idx[np.concatenate([np.arange(B.row_ptr[j], B.row_ptr[j + 1]) for j in lists[r]])].astype(np.int64)
+          if prod[r] else np.zeros(0, np.int64) for r in counted]
+    p = prod[counted].astype(float)
+    c = np.array([min(x, _count(ohll.hash32(cols))) if len(lists[r]) <= 256 else x for r, x, cols in zip(counted, p, of)])
+    per = c.sum() / p.sum()
+    error = np.sqrt(max(0.0, ((c - per * p) ** 2).sum())) / c.sum()
+    promised = int(prod.sum() * per * (1 + 1 / 64 + 4 * error) + 4096)
+    slots = C.col_idx.untyped_storage().nbytes() // 4
+    if all_counted:
+        assert st["nnz_c"] < slots < prod.sum() and abs(slots - promised) <= 2
+    else:                                                # a bound was reserved, and C trimmed
+        assert promised > prod.sum() and slots == st["nnz_c"]
