@@ -729,7 +729,7 @@ struct SampleOf {
     int64_t *prod_out;              // products of the sampled rows
     int32_t *span_out;              // columns they can reach, 0: none, the largest number: everywhere
     const int32_t *count_col;       // B's columns, for the rows whose columns are counted
-    double *count_out;              // products and columns of each
+    unsigned long long *count_totals;   // and the sums over them
     __device__ __forceinline__ int64_t row(int64_t slot) const
     {
         const int64_t t = first + slot;
@@ -812,10 +812,13 @@ __device__ __forceinline__ void hll_row_by_all(Regs16 (*s_regs)[M / 16], long lo
 // registers are 13 %, and rows over the same columns all err alike).  A wave takes an entry of A, four in flight: the chain
 // offsets -> entries -> offsets of B -> columns, up to four times over, ends before the merge of the sample that runs
 // beside it.  A row with more than COUNT_ENTRIES entries would not; its products count as so many columns.
+// totals: COUNT_SLOTS slots of COUNT_STRIDE words, where the sums over the rows of products, columns (to the nearest whole one),
+// products squared, columns squared and products times columns are spread.
 constexpr int COUNT_LOG2 = 17;
 __device__ __forceinline__ void count_columns(uint32_t *s_bits, int *s_n, const int64_t *__restrict__ a_rp,
                                               const int32_t *__restrict__ a_col, const int64_t *__restrict__ b_rp,
-                                              const int32_t *__restrict__ b_col, int64_t row, int64_t products, double *__restrict__ out)
+                                              const int32_t *__restrict__ b_col, int64_t row, int64_t products,
+                                              unsigned long long *totals)
 {
     constexpr int WORDS = 1 << (COUNT_LOG2 - 5), U = 4, NW = TPB / WAVE;
     const int tid = threadIdx.x;
@@ -853,10 +856,12 @@ __device__ __forceinline__ void count_columns(uint32_t *s_bits, int *s_n, const 
     ones = group_reduce_sum(ones, WAVE);
     if (lane_id() == 0) atomicAdd(s_n, ones);
     __syncthreads();
-    if (tid == 0) {
-        const double places = (double)(1 << COUNT_LOG2), columns = -places * log1p(-(double)*s_n / places);
-        out[0] = (double)products;
-        out[1] = walked && columns < (double)products ? columns : (double)products;
+    if (tid < COUNT_SUMS) {
+        const double places = (double)(1 << COUNT_LOG2);
+        const unsigned long long p = (unsigned long long)products, of = (unsigned long long)llrint(-places * log1p(-(double)*s_n / places));
+        const unsigned long long n = walked && of < p ? of : p;
+        const unsigned long long sum = tid == 0 ? p : tid == 1 ? n : tid == 2 ? p * p : tid == 3 ? n * n : p * n;
+        atomicAdd(totals + (size_t)(blockIdx.x % COUNT_SLOTS) * COUNT_STRIDE + tid, sum);
     }
 }
 
@@ -882,7 +887,7 @@ k_hll_merge(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
     const int G = 1 << g_log2;  // >= L
     if (SAMPLE && (int)blockIdx.x < n_long) {   // uniform
         const int64_t row = sample.row((int64_t)blockIdx.x * sample.ns / n_long);
-        count_columns(s_bits, &s_nlong, a_rp, a_col, b_rp, sample.count_col, row, prod[row], sample.count_out + 2 * blockIdx.x);
+        count_columns(s_bits, &s_nlong, a_rp, a_col, b_rp, sample.count_col, row, prod[row], sample.count_totals);
         return;
     }
     auto take = [&](int64_t t2) {
@@ -1009,11 +1014,11 @@ hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const 
     return hipGetLastError();
 }
 
-// Estimates, products and, with `reach` (B) given, reach of the ns sampled rows, and, with `count` (B) given, products and
-// columns of count_rows(ns) of them: one launch for what the sample looks at.
+// Estimates, products and, with `reach` (B) given, reach of the ns sampled rows, and, with `count` (B) given, the sums of
+// count_columns over count_rows(ns) of them: one launch for what the sample looks at.
 hipError_t launch_sample(const Csr &A, const Csr *reach, const Csr *count, int64_t b_cols, const uint8_t *sketches, int m, int64_t ns,
                          uint32_t seed, const int64_t *prod, const int32_t *maxb, double *est, int64_t *prod_out, int32_t *span_out,
-                         double *count_out, int lanes_div, hipStream_t s)
+                         unsigned long long *count_totals, int lanes_div, hipStream_t s)
 {
     if (ns <= 0) return hipSuccess;
     const int L = m / 16;
@@ -1031,11 +1036,34 @@ hipError_t launch_sample(const Csr &A, const Csr *reach, const Csr *count, int64
         const int64_t n = ns - first < most ? ns - first : most;
         const int n_count = first == 0 && count ? count_rows(ns) : 0;
         const SampleOf sample{A.rows, ns, first, seed, whole, reach ? reach->col : nullptr, prod_out + first, span_out + first,
-                              count ? count->col : nullptr, count_out};
+                              count ? count->col : nullptr, count_totals};
         const int64_t blocks = (n + rows_per_block - 1) / rows_per_block + n_count;
         hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(TPB), 0, s, A.rp, A.col, reinterpret_cast<const uint64_t *>(sketches),
                            nullptr, n, g_log2, long_from, long_from, true, n_count, prod, maxb, b_rp, b_cols, est + first, nullptr, sample);
     }
+    return hipGetLastError();
+}
+
+// The sums of count_columns over count_rows(ns) of ns sampled rows, without the sample; nothing where flags say that the inputs
+// are not valid.
+__global__ void __launch_bounds__(TPB)
+k_count_columns(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, const int64_t *__restrict__ b_rp,
+                const int64_t *__restrict__ prod, const int32_t *__restrict__ flags, const SampleOf sample)
+{
+    __shared__ uint32_t s_bits[1 << (COUNT_LOG2 - 5)];
+    __shared__ int s_n;
+    if (*flags & 7) return;   // uniform
+    const int64_t row = sample.row((int64_t)blockIdx.x * sample.ns / gridDim.x);
+    count_columns(s_bits, &s_n, a_rp, a_col, b_rp, sample.count_col, row, prod[row], sample.count_totals);
+}
+
+hipError_t launch_count(const Csr &A, const Csr &B, int64_t ns, uint32_t seed, const int64_t *prod, const int32_t *flags,
+                        unsigned long long *count_totals, hipStream_t s)
+{
+    const int n = count_rows(ns);
+    if (n <= 0) return hipSuccess;
+    const SampleOf sample{A.rows, ns, 0, seed, 0, nullptr, nullptr, nullptr, B.col, count_totals};
+    hipLaunchKernelGGL(k_count_columns, dim3((unsigned)n), dim3(TPB), 0, s, A.rp, A.col, B.rp, prod, flags, sample);
     return hipGetLastError();
 }
 
@@ -1180,16 +1208,15 @@ hipError_t launch_check_sorted(const Csr &B, int32_t *flags, int64_t *ends, hipS
 // out[0] = sum of products, out[1] = sum of estimates (their ratio is the sampled CR, Section 3.2);
 // out[2], out[3] = sum and sum of squares of the per-row ratios products / estimate, out[4] = rows counted
 // (mean and standard deviation of the compression ratio over the sample, Section 4.1); out[5] = sampled rows
-// whose column range is narrow enough for the dense accumulator to pay; out[6] .. [10] = sums of the products, the columns,
-// and their squares and product (products, columns, both) over the n_count rows whose columns were counted.
+// whose column range is narrow enough for the dense accumulator to pay.
 constexpr int SR_THREADS = 1024;
-constexpr int SR_SUMS = SAMPLE_SUMS;
+constexpr int SR_SUMS = 6;
 __global__ void __launch_bounds__(SR_THREADS)
 k_sample_reduce(int64_t n_rows, const int64_t *__restrict__ prod, const double *__restrict__ est, const int32_t *__restrict__ span,
-                int64_t n_cols, int vbytes, double bound_coef, const double *__restrict__ counted, int n_count, double *out)
+                int64_t n_cols, int vbytes, double bound_coef, double *out)
 {
     __shared__ double s_acc[SR_THREADS / WAVE][SR_SUMS];
-    double acc[SR_SUMS] = {};
+    double acc[SR_SUMS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     // four sampled rows per thread and turn, their loads issued together
     for (int64_t t0 = threadIdx.x; t0 < n_rows; t0 += 4 * SR_THREADS) {
         double e[4], p[4];
@@ -1214,14 +1241,9 @@ k_sample_reduce(int64_t n_rows, const int64_t *__restrict__ prod, const double *
             }
         }
     }
-    static_assert(COUNT_ROWS <= SR_THREADS, "one per thread");
-    if ((int)threadIdx.x < n_count) {
-        const double p = counted[2 * threadIdx.x], q = counted[2 * threadIdx.x + 1];
-        acc[6] = p; acc[7] = q; acc[8] = p * p; acc[9] = q * q; acc[10] = p * q;
-    }
 #pragma unroll
     for (int k = 0; k < SR_SUMS; ++k) {
-        const double wave = k < 6 || n_count > 0 ? group_reduce_sum(acc[k], WAVE) : 0.0;   // (uniform)
+        const double wave = group_reduce_sum(acc[k], WAVE);
         if (lane_id() == 0) s_acc[threadIdx.x / WAVE][k] = wave;
     }
     __syncthreads();
@@ -1233,10 +1255,9 @@ k_sample_reduce(int64_t n_rows, const int64_t *__restrict__ prod, const double *
 }
 
 hipError_t launch_sample_reduce(int64_t n_rows, const int64_t *prod, const double *est, const int32_t *span, int64_t n_cols, int vbytes,
-                                double bound_coef, const double *counted, int n_count, double *out, hipStream_t s)
+                                double bound_coef, double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_sample_reduce, dim3(1), dim3(SR_THREADS), 0, s, n_rows, prod, est, span, n_cols, vbytes, bound_coef, counted,
-                       n_count, out);
+    hipLaunchKernelGGL(k_sample_reduce, dim3(1), dim3(SR_THREADS), 0, s, n_rows, prod, est, span, n_cols, vbytes, bound_coef, out);
     return hipGetLastError();
 }
 

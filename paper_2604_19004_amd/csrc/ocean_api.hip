@@ -47,10 +47,11 @@ struct Scalars {
     unsigned long long max_cap;
     unsigned long long ovf_count;
     unsigned long long queue[4];
-    double sample_sums[SAMPLE_SUMS];              // see k_sample_reduce
+    double sample_sums[6];                        // products, estimates, per-row CR, its squares, rows counted
     int32_t flags;
     int32_t pad;
     unsigned long long span_totals[SPAN_SLOTS * SPAN_STRIDE];   // see k_row_spans
+    unsigned long long count_totals[COUNT_SLOTS * COUNT_STRIDE];   // see count_columns
     unsigned long long near_pairs[2];             // sampled entries of B, and those whose successor's column is 1 .. 4 larger
     unsigned long long row_totals[ROW_TOTAL_SLOTS * ROW_TOTAL_STRIDE];   // totals of the row-products pass, by slot
 };
@@ -273,14 +274,14 @@ struct Work {
     int64_t *sample_prod = nullptr;                       // of the sampled rows: products, estimates, columns in reach
     double *sample_est = nullptr;
     int32_t *sample_span = nullptr;
-    double *counted = nullptr;                            // products and columns of the sampled rows whose columns are counted
-    double count_cr = 0.0, count_error = 0.0;             // their products / columns, 0: not counted, and its relative error
+    double count_cr = 0.0, count_error = 0.0;             // products / columns of rows whose columns were counted (0: none were), its relative error
     // rows that are placed as they are sorted (placed.hip): words for units of four rows and more, cleared by the analysis
     unsigned long long *places = nullptr;
     uint32_t *counts = nullptr;
     int64_t place_words = 0;                               // 64-bit words of both
     int four_rows_lds = 0;                                 // see ROW_TOTAL_LDS
     bool merge_sample = false;                             // the different columns of a few rows are to be counted
+    int64_t count_sample = 0;                              // .. of some rows of a sample of so many, of more products
     double merge_cr = 0.0;                                 // products / columns of those that could be counted
     bool merge_all = false;                                // which were all of them
     unsigned long long span_totals[SPAN_TOTALS] = {};      // of the ranges of all rows
@@ -300,7 +301,7 @@ int work_alloc(Ctx &c, Work &w, int64_t m, int64_t n_sample, bool placing)
     const size_t o_est = take(mm * 8);
     const size_t o_sp = take((size_t)(n_sample + 1) * 8), o_se = take((size_t)(n_sample + 1) * 8);
     const size_t o_cmin = take(mm * 4), o_cmax = take(mm * 4);
-    const size_t o_span = take((size_t)(n_sample + 1) * 4), o_counted = take((size_t)COUNT_ROWS * 16);
+    const size_t o_span = take((size_t)(n_sample + 1) * 4);
     const size_t units = (mm + 3) / 4;
     const size_t place_words = placing ? units + (units + 1) / 2 : 0, o_places = take(place_words * 8);
     char *b = static_cast<char *>(c.alloc(off));
@@ -329,7 +330,6 @@ int work_alloc(Ctx &c, Work &w, int64_t m, int64_t n_sample, bool placing)
     w.cmin = reinterpret_cast<int32_t *>(b + o_cmin);
     w.cmax = reinterpret_cast<int32_t *>(b + o_cmax);
     w.sample_span = reinterpret_cast<int32_t *>(b + o_span);
-    w.counted = reinterpret_cast<double *>(b + o_counted);
     HIP_TRY(hipMemsetAsync(w.sc, 0, sizeof(Scalars), c.s));
     w.bins_clean = true;
     return OCEAN_OK;
@@ -346,8 +346,21 @@ int zero_bins(Ctx &c, Work &w)
     return OCEAN_OK;
 }
 
+// The compression ratio of the rows whose columns were counted, from the fetched sums, and the standard error of such a ratio of
+// sums: by the residuals columns - products / CR.
+void counted_ratio(const Ctx &c, Work &w, int n_count)
+{
+    double sum[COUNT_SUMS] = {};
+    for (int i = 0; i < COUNT_SLOTS; ++i)
+        for (int k = 0; k < COUNT_SUMS; ++k) sum[k] += (double)c.h->count_totals[i * COUNT_STRIDE + k];
+    if (n_count < 32 || sum[1] == 0.0) return;
+    const double per = sum[1] / sum[0], rest = sum[3] - 2.0 * per * sum[4] + per * per * sum[2];
+    w.count_cr = sum[0] / sum[1];
+    w.count_error = rest > 0.0 ? std::sqrt(rest) / sum[1] : 0.0;
+}
+
 // ---- analysis: validation + products per row ------------------------------------------------------
-int run_analysis(Ctx &c, Work &w, const Csr &A, const Csr &B, int vbytes, bool validate, ocean_stats *st)
+int run_analysis(Ctx &c, Work &w, const Csr &A, const Csr &B, int vbytes, bool validate, uint32_t sample_seed, ocean_stats *st)
 {
     // (the same arrays under another number of entries are two matrices, of which one is not valid)
     const bool same = B.rp == A.rp && B.col == A.col && B.rows == A.rows && B.cols == A.cols && B.nnz == A.nnz;
@@ -355,7 +368,10 @@ int run_analysis(Ctx &c, Work &w, const Csr &A, const Csr &B, int vbytes, bool v
     HIP_TRY(launch_row_products(A, B.rp, B.rows, w.prod, w.maxb, w.sc->row_totals, &w.sc->flags, validate,
                                 validate && same ? w.sc->near_pairs : nullptr, w.places, w.place_words, vbytes,
                                 w.merge_sample ? &B : nullptr, c.s));
+    if (w.count_sample > 0)
+        HIP_TRY(launch_count(A, B, w.count_sample, sample_seed, w.prod, &w.sc->flags, w.sc->count_totals, c.s));
     OC_TRY(fetch_scalars(c, w.sc));
+    if (w.count_sample > 0) counted_ratio(c, w, count_rows(w.count_sample));
     RowTotals tot;
     sum_row_totals(c.h, tot);
     std::memcpy(w.class_rows, tot + ROW_TOTAL_CLASS, sizeof(w.class_rows));
@@ -460,11 +476,10 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
 int run_sample(Ctx &c, Work &w, const Csr &A, const Csr *B, bool count, int vbytes, int64_t n_cols, const uint8_t *sketches, int m_regs,
                int64_t n_sample, const ocean_options &o, ocean_stats *S)
 {
-    const int n_count = count ? count_rows(n_sample) : 0;
     HIP_TRY(launch_sample(A, o.dense_range == 1 ? B : nullptr, count ? B : nullptr, n_cols, sketches, m_regs, n_sample, o.sample_seed, w.prod,
-                          w.maxb, w.sample_est, w.sample_prod, w.sample_span, w.counted, c.lanes_div, c.s));
-    HIP_TRY(launch_sample_reduce(n_sample, w.sample_prod, w.sample_est, w.sample_span, n_cols, vbytes, o.bound_load_coef, w.counted,
-                                 n_count, w.sc->sample_sums, c.s));
+                          w.maxb, w.sample_est, w.sample_prod, w.sample_span, w.sc->count_totals, c.lanes_div, c.s));
+    HIP_TRY(launch_sample_reduce(n_sample, w.sample_prod, w.sample_est, w.sample_span, n_cols, vbytes, o.bound_load_coef,
+                                 w.sc->sample_sums, c.s));
     OC_TRY(fetch_scalars(c, w.sc));
     const double *ss = c.h->sample_sums;
     S->dense_range_rows = (int32_t)ss[5];
@@ -475,12 +490,7 @@ int run_sample(Ctx &c, Work &w, const Csr &A, const Csr *B, bool count, int vbyt
         const double var = ss[3] / ss[4] - S->cr_mean * S->cr_mean;
         S->cr_std = var > 0.0 ? std::sqrt(var) : 0.0;
     }
-    if (n_count >= 32 && ss[7] > 0.0) {
-        // standard error of a ratio of sums: the residuals columns - products / CR
-        const double per = ss[7] / ss[6], rest = ss[9] - 2.0 * per * ss[10] + per * per * ss[8];
-        w.count_cr = ss[6] / ss[7];
-        w.count_error = rest > 0.0 ? std::sqrt(rest) / ss[7] : 0.0;
-    }
+    if (count) counted_ratio(c, w, count_rows(n_sample));
     return OCEAN_OK;
 }
 
@@ -874,32 +884,57 @@ struct Placed {
 // 2025 among every thousand: 308 / 297, 395 / 305, 795 / 311; 347 / 452, 431 / 457, 831 / 471; 410 / 603, 490 / 615, 876 / 625.  Equal
 // rows: 25 products 221 / 330 (400 000), 225 390 / 560, 484 689 / 944, 961 929 / 1272 (150 000), 2025 1390 / 1709 (100 000).
 // Dense ranges, where every row has one and it is the accumulator for four fifths of them: a row waits 3 us for its place, with
-// 2048 in flight, so placing pays from some 450 products a row on; sorting, where every row can be sorted, up to 700.
+// 2048 in flight (fewer where ranges are longer than 2048 columns: 60 000 rows of 1920 products on 3840 columns 703 us, sorted 758,
+// general 815), so placing pays from some 450 products a row on; sorting, where every row can be sorted, up to 700.
 // Block-diagonal matrices, fp64, whole call in us, placed dense / placed sorted / general: 300 000 rows of 324 products in blocks
 // of 300 columns 1352 / 734 / 1245, 200 000 of 399 in 500 970 / 636 / 950, 150 000 of 900 in 500 863 / 1104 / 1022, 100 000 of 1600
 // in 1000 749 / - / 886, of 1522 in 1300 787 / - / 929, 60 000 of 3602 in 1000 698 / - / 1030.
 //
+// Rows that merge into few columns are cheaper either way, the general one's more so, as tables of few columns take them: the
+// costs lie between kWavePs and kMergedPs by the share of the products that are entries of C, and the estimation workflow's follow
+// its products (0.7 of what they take where B is larger than 16 MB), entries of A and entries of C.  250 000 rows, fp64, whole call in
+// us, placed dense / placed sorted / general: 640 products on 32 columns 1043 / 802 / 764, on 128 1090 / 852 / 999, 1024 on 85 1110 /
+// 1154 / 991, on 512 1267 / 1219 / 1386; band of 25 of 200 000 rows 898 / 706 / 737, of 33 of 100 000 585 / 756 / 747.  By costs that
+// took no account of it the first was placed dense, and the band of 25 (755 us before rows were placed, 909 then).
+//
 // The upper-bound workflow has no symbolic pass to leave out, only the copy out of the reserved rows, 4.8 (fp64) or 3.6 ps an entry
-// of C; and where C has to be trimmed placing does not leave that out either.  It needs no trim where the reservation follows all
-// of the counted rows, or where those that were counted hardly merge; otherwise nothing is counted on.  Upper bound forced,
+// of C; and where C has to be trimmed placing does not leave that out either.  It needs no trim where the reservation follows
+// counted rows, or where those that were counted hardly merge; otherwise nothing is counted on.  Upper bound forced,
 // whole call, fp32 rows of 762 products that merge into 234: placed 2.58 ms, general 2.07; fp64 rows of 270 that hardly merge:
 // placed 1.17, general 1.72.
-bool choose_placed(const Csr &A, const Work &w, const Ctx &c, int64_t products, int workflow, size_t vbytes, Placed *how)
+bool choose_placed(const Csr &A, const Csr &B, const Work &w, const Ctx &c, int64_t products, int workflow, size_t vbytes, Placed *how)
 {
     constexpr double kWavePs[SORT_CLASSES] = {0, 1050, 1050, 1050, 1050, 1300, 1600, 2300, 2950, 4300, 5600, 10000, 12900};
-    const double rows = (double)A.rows;
-    double general = 60e6 + 3.0 * (double)products;   // ps
-    if (workflow == OCEAN_WF_UPPER_BOUND) {
+    constexpr double kMergedPs[SORT_CLASSES] = {0, 1050, 1050, 1050, 1050, 1050, 1250, 1800, 2300, 2750, 4000, 6200, 11500};
+    const double rows = (double)A.rows, prods = (double)products;
+    const bool counted = w.count_cr > 0.0;
+    const double part = counted ? 1.0 / w.count_cr : 1.0;   // of the products that are entries of C
+    const double entries = prods * part;
+    double general = 60e6 + 3.0 * prods;   // ps
+    bool by_class = !w.spans;              // .. and the sorted rows'
+    double wary = 1.0;                     // placed rows of mixed sizes take up to 1.3 times what is reckoned here
+    if (workflow == OCEAN_WF_UPPER_BOUND && counted) {
+        general = 60e6 + (vbytes == 8 ? 5.5 : 4.0) * entries;
+        wary = vbytes == 4 && (w.class_rows[11] != 0 || w.class_rows[12] != 0) ? 0.9 : 1.15;   // (4 bytes: half the LDS)
+    } else if (workflow == OCEAN_WF_UPPER_BOUND) {
         const bool trimmed = !(w.merge_cr > 0.0 && (w.merge_all || w.merge_cr < 1.1));
-        general = 60e6 + (trimmed ? 0.0 : (vbytes == 8 ? 4.8 : 3.6) * (double)products / w.merge_cr);
+        general = 60e6 + (trimmed ? 0.0 : (vbytes == 8 ? 4.8 : 3.6) * prods / w.merge_cr);
+    } else if (workflow == OCEAN_WF_HLL && counted) {
+        const bool far = (double)B.nnz * (double)(4 + vbytes) > 16e6;
+        general = 110e6 + 400.0 * rows + 10.0 * (double)A.nnz + (w.spans ? 2.6 : 3.9) * (far ? 1.0 : 0.7) * prods +
+                  (vbytes == 8 ? 8.0 : 5.3) * entries;
+        by_class = false;
+    } else if (w.spans) {
+        general = 120e6 + 2400.0 * rows + 2.2 * prods;
     }
     bool found = false;
     if (w.spans) {
         const unsigned long long *t = w.span_totals;
         if (c.h->flags & 8) return false;   // (B's rows are out of column order: the ranges are guesses)
-        general = 120e6 + 2400.0 * rows + 2.2 * (double)products;
         if (t[0] != 0 && t[1] == 0 && t[4] * 5 >= t[0] * 4 && A.rows + 1 <= most_blocks(256)) {
-            const double placed = (t[2] > 2048 ? 4100.0 : t[2] > 1024 ? 3600.0 : 3100.0) * rows + 1.5 * (double)products;
+            const bool longest = t[2] > 2048;
+            if (longest && workflow != OCEAN_WF_HLL) general = 120e6 + 7500.0 * rows + 2.2 * prods;
+            const double placed = longest ? 8000.0 * rows + 1.8 * prods : (t[2] > 1024 ? 3600.0 : 3100.0) * rows + 1.5 * prods;
             if (placed < general) {
                 found = true;
                 how->span_cols = (int)t[2];
@@ -913,9 +948,12 @@ bool choose_placed(const Csr &A, const Work &w, const Ctx &c, int64_t products, 
         if (w.class_rows[k] != 0) cls = k;
     if (cls == 0 || !((c.sort_mask >> cls) & 1u)) return found;
     if (placed_units(A.rows, cls) + 1 > most_blocks(256)) return found;
+    for (int k = 1; by_class && k <= cls; ++k) {
+        // (of rows that merge, the least that was measured: 0.45 to 0.57 of a row's that do not)
+        const double merged = !counted || workflow != OCEAN_WF_UPPER_BOUND ? 1.0 : k <= 9 ? 0.5 : k <= 11 ? 0.55 : 0.45;
+        general += (double)w.class_rows[k] * kSortClass[k].ps * (merged + (1.0 - merged) * part);
+    }
     double placed;
-    if (!w.spans)
-        for (int k = 1; k <= cls; ++k) general += (double)w.class_rows[k] * kSortClass[k].ps;
     if (kPlacedRows[cls] > 4) {
         placed = rows * kSortClass[cls].ps;
     } else {
@@ -923,10 +961,10 @@ bool choose_placed(const Csr &A, const Work &w, const Ctx &c, int64_t products, 
         const double in_flight = 4.0 * c.n_cu * (by_lds < by_registers ? by_lds : by_registers);
         placed = rows / in_flight * (7.5e6 + 3.4e3 * kSortClass[cls].cap);   // the longest row's time
         double sorted = 0.0;
-        for (int k = 1; k <= cls; ++k) sorted += (double)w.class_rows[k] * kWavePs[k];
+        for (int k = 1; k <= cls; ++k) sorted += (double)w.class_rows[k] * (kMergedPs[k] + (kWavePs[k] - kMergedPs[k]) * part);
         if (sorted > placed) placed = sorted;
     }
-    if (placed >= general) return found;
+    if (placed * wary >= general) return found;
     how->cls = cls;
     how->span_cols = 0;
     return true;
@@ -945,15 +983,15 @@ int run_placed(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, const Pla
     const int64_t m = A.rows;
     const size_t vbytes = dtype == OCEAN_F64 ? 8 : 4;
     int64_t slots = how.span_cols != 0 ? (int64_t)w.span_totals[3] : S->products;
-    if (workflow != OCEAN_WF_UPPER_BOUND && w.count_cr > 0.0) {
+    if (w.count_cr > 0.0) {
         const double want = (double)S->products / w.count_cr * (1.0 + 1.0 / 64.0 + 4.0 * w.count_error) + 4096.0;
         if (want < (double)slots) slots = (int64_t)want;
     }
-    // The upper-bound workflow samples nothing, but the analysis counted the columns of MERGE_SAMPLE rows: an eighth is some
+    // Where the upper-bound workflow counted none, the analysis counted the columns of MERGE_SAMPLE rows: an eighth is some
     // standard deviations of what so many rows say, unless few rows hold most of the products.  Reserving every product and
     // copying C out of it was 53 of the 354 us of a Laplacian of 1024^2 (297 now), 10 of the 116 of one of 257^2; the count
     // ends before the pass that it is part of does (31 us, as before).
-    if (workflow == OCEAN_WF_UPPER_BOUND && w.merge_all && w.merge_cr > 1.0 && (double)S->max_row_products <= 8.0 * S->avg_products) {
+    if (workflow == OCEAN_WF_UPPER_BOUND && w.count_cr == 0.0 && w.merge_all && w.merge_cr > 1.0 && (double)S->max_row_products <= 8.0 * S->avg_products) {
         const double want = (double)S->products / w.merge_cr * 1.125 + 4096.0;
         if (want < (double)slots) slots = (int64_t)want;
     }
@@ -1090,9 +1128,15 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     const double expect = B.rows > 0 ? (double)A.nnz * ((double)B.nnz / (double)B.rows) : 0.0;
     w.merge_sample = placing && expect >= 8.0 * 65536.0 &&
                      (o.workflow == OCEAN_WF_UPPER_BOUND || expect < o.upper_bound_avg_products * (double)m);
+    // With larger rows and many products, where the wrong way costs up to 0.3 of the call and a reservation of every product a trim,
+    // in a launch of its own (15 us).
+    if (placing && o.workflow == OCEAN_WF_UPPER_BOUND && expect >= 5e7 && expect >= 128.0 * (double)m) {
+        w.merge_sample = false;
+        w.count_sample = n_sample;
+    }
     ocean_stats local{};
     ocean_stats *S = st ? st : &local;
-    OC_TRY(run_analysis(c, w, A, B, (int)vbytes, o.validate_inputs != 0, S));
+    OC_TRY(run_analysis(c, w, A, B, (int)vbytes, o.validate_inputs != 0, o.sample_seed, S));
     const int64_t P = S->products;
     if (P == 0) {
         HIP_TRY(hipMemsetAsync(c_rp, 0, (size_t)(m + 1) * 8, c.s));
@@ -1186,7 +1230,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
             }
         }
         bool done = false;
-        if (choose_placed(A, w, c, P, workflow, vbytes, &how)) {
+        if (choose_placed(A, B, w, c, P, workflow, vbytes, &how)) {
             S->hll_registers = m_regs;
             OC_TRY(run_placed(c, w, A, B, dtype, how, workflow, o, st, S, c_rp, C, &done));
         }
@@ -1637,7 +1681,7 @@ int ocean_symbolic(const ocean_csr *A, const ocean_csr *B, int32_t *nnz_per_row,
         const int64_t n_sample = o.assisted_symbolic == 2 ? sample_size_of(A->rows, o) : 0;
         OC_TRY(work_alloc(c, w, A->rows, n_sample, false));
         const Csr a = view(A), b = view(B);
-        OC_TRY(run_analysis(c, w, a, b, A->dtype == OCEAN_F64 ? 8 : 4, o.validate_inputs != 0, S));
+        OC_TRY(run_analysis(c, w, a, b, A->dtype == OCEAN_F64 ? 8 : 4, o.validate_inputs != 0, o.sample_seed, S));
         const int gb_log2 = ilog2_ceil_d(S->er, 0, 6);
         double assist_cr = 0.0;
         if (n_sample > 0 && S->products > 0) {

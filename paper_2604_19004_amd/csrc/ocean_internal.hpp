@@ -250,9 +250,10 @@ constexpr int MERGE_SAMPLE = 512;        // rows
 constexpr int MERGE_PRODUCTS = 256;      // of a row whose columns are counted, at most
 constexpr int MERGE_LENGTH = 32;         // of the rows of B that it names: a lane walks one
 
-// Rows of the sample whose columns are counted, the products that none may have more of for that, the entries of A from which
-// on they count as all different, and the sums of a sample.
-constexpr int COUNT_ROWS = 512, COUNT_PRODUCTS = 8192, COUNT_ENTRIES = 256, SAMPLE_SUMS = 11;
+// Rows of the sample whose columns are counted, the products and entries of A from which on they count as all different, and
+// where the sums over them are (count_columns).
+constexpr int COUNT_ROWS = 512, COUNT_PRODUCTS = 8192, COUNT_ENTRIES = 256;
+constexpr int COUNT_SUMS = 5, COUNT_SLOTS = 16, COUNT_STRIDE = 8;
 inline int count_rows(int64_t n_sample) { return (int)(n_sample < COUNT_ROWS ? n_sample : COUNT_ROWS); }
 
 constexpr int SPAN_TOTALS = 5, SPAN_SLOTS = 8, SPAN_STRIDE = 16;   // see k_row_spans (a slot has a line of its own)
@@ -283,12 +284,15 @@ hipError_t launch_hll_merge(const Csr &A, const uint8_t *sketches, int m, const 
 hipError_t launch_sample(const Csr &A, const Csr *reach /*B; null: reach not asked for*/, const Csr *count /*B; null: nothing counted*/,
                          int64_t b_cols, const uint8_t *sketches, int m, int64_t ns, uint32_t seed, const int64_t *prod,
                          const int32_t *maxb, double *est, int64_t *prod_out, int32_t *span_out,
-                         double *count_out /*two per counted row*/, int lanes_div, hipStream_t s);
+                         unsigned long long *count_totals, int lanes_div, hipStream_t s);
+hipError_t launch_count(const Csr &A, const Csr &B, int64_t ns, uint32_t seed, const int64_t *prod, const int32_t *flags,
+                        unsigned long long *count_totals, hipStream_t s);
 hipError_t launch_row_spans(const Csr &A, const Csr &B, const int64_t *ends, const int64_t *prod, int vbytes, double bound_coef,
                                 int32_t *cmin, int32_t *cmax, unsigned long long *totals, hipStream_t s);
 hipError_t launch_check_sorted(const Csr &B, int32_t *flags, int64_t *ends /*a word per row of B*/, hipStream_t s);
 hipError_t launch_sample_reduce(int64_t n_rows, const int64_t *prod, const double *est, const int32_t *span, int64_t n_cols, int vbytes,
-                                double bound_coef, const double *counted, int n_count, double *out /*[SAMPLE_SUMS], see there*/,
+                                double bound_coef,
+                                double *out /*[6]: sum prod, sum est, sum cr, sum cr^2, rows, rows a dense range pays for*/,
                                 hipStream_t s);
 
 // binning.hip

@@ -68,18 +68,32 @@ def test_reservation(ob, rows, entries, merging, expect, dtype):  # noqa: F811
         assert st["temp_slots"] == (int(products / 4 * 1.125 + 4096.0) if expect == "counted" else products)
 
 
-def _count(hashes):
-    """Columns as the sample counts them: by 17 bits of their hashes (linear counting)."""
+def _count(cols):
+    """Different columns as they are counted: by 17 bits of their hashes (linear counting)."""
     places = 1 << 17
-    return -places * np.log1p(-np.unique(hashes >> (32 - 17)).size / places)
+    return np.rint(-places * np.log1p(-np.unique(ohll.hash32(cols) >> (32 - 17)).size / places))
+
+
+def _promised(ob, A, B, prod):
+    """What the counted rows of a sample promise, four standard errors and a 64th more."""
+    sampled = ob.sample_rows(A.rows)
+    counted = sampled[np.arange(512) * sampled.size // 512]
+    p, c = np.zeros(512), np.zeros(512)
+    for i, r in enumerate(counted):
+        entries = A.col_idx[A.row_ptr[r]:A.row_ptr[r + 1]]
+        p[i] = c[i] = prod[r]
+        if 0 < entries.size <= 256:
+            c[i] = min(p[i], _count(np.concatenate([B.col_idx[B.row_ptr[k]:B.row_ptr[k + 1]] for k in entries])))
+    per = c.sum() / p.sum()
+    error = np.sqrt(max(0.0, ((c - per * p) ** 2).sum())) / c.sum()
+    return int(prod.sum() * per * (1 + 1 / 64 + 4 * error) + 4096)
 
 
 # entries of A of a row, rows of B, their entries, columns; numbers of columns for which sketches say an eighth too little
 @pytest.mark.parametrize("entries, k, length, n, all_counted", [(34, 2000, 60, 1500, True), (40, 1000, 30, 400, True), (20, 1000, 20, 300, True),
                                                                 (2, 40, 1000, 3500, True), (0, 1000, 8, 5000, True), (257, 2000, 9, 1500, False)])
 def test_sample_counts_columns(ob, entries, k, length, n, all_counted):  # noqa: F811
-    """What the other workflows reserve: what up to 512 sampled rows' columns promise, four standard errors and a 64th more; no
-    pass is repeated for an error that all rows' sketches have in common."""
+    """No pass is repeated for an error that all rows' sketches have in common."""
     rng = np.random.default_rng(n)
     B = _csr(k, n, [[]] + [np.sort(rng.choice(n, length, replace=False)) for _ in range(k - 1)], rng, np.float64)
     lists = [rng.choice(k, entries or int(rng.integers(0, 65)), replace=False) for _ in range(4000)]
@@ -90,18 +104,27 @@ def test_sample_counts_columns(ob, entries, k, length, n, all_counted):  # noqa:
     C, st = ob.spgemm(ob.to_device(A), ob.to_device(B), tuned_min_products=0.0)
     check_result(C, O.multiply_rows(A, B), A, f"{entries} entries, {n} columns")
     assert st["stage_ms"]["binning"] == 0.0 and st["sampled_rows"] > 512
-    sampled = ob.sample_rows(A.rows)
-    counted = sampled[np.arange(512) * sampled.size // 512]
     prod = O.row_products(A, B)
-    of = [B.col_idx[np.concatenate([np.arange(B.row_ptr[j], B.row_ptr[j + 1]) for j in lists[r]])].astype(np.int64)
-          if prod[r] else np.zeros(0, np.int64) for r in counted]
-    p = prod[counted].astype(float)
-    c = np.array([min(x, _count(ohll.hash32(cols))) if len(lists[r]) <= 256 else x for r, x, cols in zip(counted, p, of)])
-    per = c.sum() / p.sum()
-    error = np.sqrt(max(0.0, ((c - per * p) ** 2).sum())) / c.sum()
-    promised = int(prod.sum() * per * (1 + 1 / 64 + 4 * error) + 4096)
+    promised = _promised(ob, A, B, prod)
     slots = C.col_idx.untyped_storage().nbytes() // 4
     if all_counted:
         assert st["nnz_c"] < slots < prod.sum() and abs(slots - promised) <= 2
     else:                                                # a bound was reserved, and C trimmed
         assert promised > prod.sum() and slots == st["nnz_c"]
+
+
+@pytest.mark.parametrize("validate", [1, 0])
+def test_upper_bound_counts_columns_of_large_rows(ob, validate):  # noqa: F811
+    """50 million products in rows of more than 128: counted, and sorted straight to C or not; an A out of range is refused."""
+    rng = np.random.default_rng(11)
+    B = _csr(2000, 1500, [np.sort(rng.choice(1500, 25, replace=False)) for _ in range(2000)], rng, np.float32)
+    A = _csr(170000, 2000, list(rng.integers(0, 2000, (170000, 12))), rng, np.float32)
+    dA, dB = ob.to_device(A), ob.to_device(B)
+    C, st = ob.spgemm(dA, dB, workflow=ob.WF_UPPER_BOUND, validate_inputs=validate)
+    check_result(C, O.multiply_rows(A, B), A, "counted")
+    assert st["stage_ms"]["binning"] == 0.0 and abs(st["temp_slots"] - _promised(ob, A, B, O.row_products(A, B))) <= 2
+    assert st["nnz_c"] < st["temp_slots"] == C.col_idx.untyped_storage().nbytes() // 4
+    if validate:
+        dA.col_idx[12345] = 2000
+        with pytest.raises(ob.OceanError):
+            ob.spgemm(dA, dB, workflow=ob.WF_UPPER_BOUND)

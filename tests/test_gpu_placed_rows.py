@@ -211,3 +211,19 @@ def test_dense_ranges(ob, span, dtype):
     C, st = ob.spgemm(ob.to_device(A), ob.to_device(mixed), tuned_min_products=0.0)
     check_result(C, O.multiply_rows(A, mixed), A, f"{span} columns, rows of B in no order")
     assert st["stage_ms"]["binning"] > 0.0
+
+
+def test_ranges_of_rows_that_merge_much(ob):
+    """A band of 25 diagonals, 625 products on 49 columns a row: sorted takes 0.8 of what the dense accumulator over the ranges
+    does."""
+    n, w = 100000, 25
+    rng = np.random.default_rng(w)
+    cols = np.arange(n)[:, None] + np.arange(w) - w // 2
+    inside = (cols >= 0) & (cols < n)
+    A = CSR(n, n, np.concatenate([[0], np.cumsum(inside.sum(1))]).astype(np.int64), cols[inside].astype(np.int32),
+            rng.uniform(-1, 1, int(inside.sum())))
+    dA = ob.to_device(A)
+    C, st = ob.spgemm(dA, dA)
+    check_result(C, O.multiply_rows(A, A), A, "band of 25")
+    assert st["dense_range_rows"] == st["sampled_rows"] and st["rows_per_bin"][len(ob.bin_layout()[0])] == 0
+    assert st["stage_ms"]["binning"] == 0.0
