@@ -80,13 +80,15 @@ hipError_t launch_validate(const Csr &B, int32_t *flags, unsigned long long *nea
 // own, the first n_long of the same launch: workgroup b of them looks at rows 4 b .. 4 b + 3 of every stretch of 4 n_long
 // rows and takes the long ones among them.  n_long is a prime and not near a power of two: the long rows of a power-law matrix
 // have few one bits in their numbers, and of the 3981 rows of 256 entries and more of R-MAT scale 18 one workgroup of 1023 had
-// 35, one of 997 has 12.  A second launch for them cost matrices without any 5 us.
+// 35, one of 997 has 12.  A second launch for them cost matrices without any 5 us.  One for every 16 rows, rounded down by an eighth
+// at most: where every row is long (4000 rows of 3000 entries, row products) 127 workgroups took 155 us, 241 take 111.
 constexpr int LONG_ROWS = 4;        // neighbouring rows that such a workgroup looks at together
 constexpr int WAVE_ROW = 2048;      // up to here a wave takes a long row of k_row_products, four turns of eight entries a lane
 
 static int long_row_blocks(int64_t rows)
 {
-    for (int n : {997, 499, 251, 127, 61, 31, 13, 7, 3})
+    for (int n : {997, 881, 787, 691, 613, 547, 487, 431, 383, 347, 307, 277, 241, 211, 191, 167, 149, 137, 113, 101, 89, 79, 71, 59, 53,
+                  47, 41, 37, 29, 23, 19, 17, 13, 11, 7, 5, 3})
         if ((int64_t)n * 16 <= rows) return n;
     return 1;
 }
