@@ -626,7 +626,7 @@ k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
     __shared__ long long s_place;
     const int tid = threadIdx.x;
     if (PLACED && blockIdx.x == 0) {   // uniform
-        place_units(p.counts, p.places, p.m, p.total, p.flags, *reinterpret_cast<Turn *>(s_vals));
+        place_units(p.counts, p.places, p.m, p.total, p.flags, p.placer_polls, *reinterpret_cast<Turn *>(s_vals));
         return;
     }
     const int64_t r = (int64_t)blockIdx.x - (PLACED ? 1 : 0);
@@ -683,7 +683,7 @@ k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
             }
         }
         if (tid < WAVE) {
-            const int64_t place = wait_for_place(p.places + row, p.flags);
+            const int64_t place = wait_for_place(p.places + row, p.flags, p.unit_polls);
             if (tid == 0) {
                 s_place = place;
                 if (place >= 0) {
@@ -738,7 +738,7 @@ static hipError_t dispatch_placed_span(const Csr &A, const Csr &B, const PlacedL
     const V *av = static_cast<const V *>(A.val);
     const V *bv = static_cast<const V *>(B.val);
     V *ov = static_cast<V *>(l.out_val);
-    const Placing<V> p{A.rows, l.c_rp, l.out_col, ov, l.slots, l.counts, l.places, l.total, l.flags};
+    const Placing<V> p{A.rows, l.c_rp, l.out_col, ov, l.slots, l.counts, l.places, l.total, l.flags, l.placer_polls, l.unit_polls};
     const auto kernel = l.query_bitmap ? (l.span_cols <= 1024   ? k_numeric_dspan<V, true, 1024, true>
                                           : l.span_cols <= 2048 ? k_numeric_dspan<V, true, 2048, true>
                                                                 : k_numeric_dspan<V, true, (int)DS_MAX_COLS, true>)

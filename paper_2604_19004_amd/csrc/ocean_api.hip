@@ -17,6 +17,7 @@ using namespace ocean;
 namespace {
 
 thread_local std::string g_err;
+thread_local int g_placer_polls = 1 << 20, g_unit_polls = 1 << 21;   // see PlacedLaunch
 
 int fail(int code, const std::string &msg)
 {
@@ -1009,6 +1010,8 @@ int run_placed(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, const Pla
     l.places = w.places;
     l.total = &w.sc->totals[0];
     l.flags = &w.sc->flags;
+    l.placer_polls = g_placer_polls;
+    l.unit_polls = g_unit_polls;
     int64_t place_words = w.place_words;
     if (how.span_cols != 0) {   // (units of one row)
         place_words = m + (m + 1) / 2;
@@ -1608,6 +1611,13 @@ int ocean_init(void)
     g_err.clear();
     unsigned char *p = nullptr;
     return scratch_of_current_device(&p);
+}
+
+// (for tests of what follows when a wait for a row's place runs out: how long the calling thread's later calls wait)
+void ocean_test_wait_polls(int placer, int unit)
+{
+    g_placer_polls = placer;
+    g_unit_polls = unit;
 }
 
 int ocean_row_products_noalloc(const ocean_csr *A, const ocean_csr *B, int64_t *prod, int64_t *totals,

@@ -21,7 +21,7 @@ k_placed_group(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
     const bool first_wave = threadIdx.x < WAVE;
     const int64_t units = (p.m + R - 1) / R;
     if (blockIdx.x == 0) {   // uniform
-        place_units(p.counts, p.places, units, p.total, p.flags, *reinterpret_cast<Turn *>(s_row));
+        place_units(p.counts, p.places, units, p.total, p.flags, p.placer_polls, *reinterpret_cast<Turn *>(s_row));
         return;
     }
     const int64_t unit = (int64_t)blockIdx.x - 1;
@@ -42,7 +42,7 @@ k_placed_group(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
     }
     c.template accumulate<true>(sr, sub);
     if (first_wave) {
-        const int64_t o = wait_for_place(p.places + unit, p.flags);
+        const int64_t o = wait_for_place(p.places + unit, p.flags, p.unit_polls);
         if (lane == 0) s_place = o;
     }
     __syncthreads();
@@ -81,7 +81,7 @@ template <typename V>
 __device__ __forceinline__ int64_t place_row(FourRows &f, int wave, int64_t unit, const Placing<V> &p)
 {
     if (wave == 0) {
-        const int64_t o = wait_for_place(p.places + unit, p.flags);
+        const int64_t o = wait_for_place(p.places + unit, p.flags, p.unit_polls);
         if (lane_id() == 0)
             __hip_atomic_store(&f.place, o < 0 ? NO_PLACE : (unsigned long long)o + 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         return o;
@@ -141,7 +141,7 @@ k_placed_wave(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_co
     __shared__ FourRows s_four;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
     if (blockIdx.x == 0) {   // uniform
-        place_units(p.counts, p.places, (p.m + 3) / 4, p.total, p.flags, *reinterpret_cast<Turn *>(s_pool));
+        place_units(p.counts, p.places, (p.m + 3) / 4, p.total, p.flags, p.placer_polls, *reinterpret_cast<Turn *>(s_pool));
         return;
     }
     const int64_t unit = (int64_t)blockIdx.x - 1, row = unit * 4 + wave;
@@ -206,7 +206,7 @@ static hipError_t dispatch_placed(const Csr &A, const Csr &B, const PlacedLaunch
 {
     const V *av = static_cast<const V *>(A.val);
     const V *bv = static_cast<const V *>(B.val);
-    const Placing<V> p{A.rows, l.c_rp, l.out_col, static_cast<V *>(l.out_val), l.slots, l.counts, l.places, l.total, l.flags};
+    const Placing<V> p{A.rows, l.c_rp, l.out_col, static_cast<V *>(l.out_val), l.slots, l.counts, l.places, l.total, l.flags, l.placer_polls, l.unit_polls};
     const unsigned blocks = (unsigned)(placed_units(A.rows, l.cls) + 1);
 #define OCEAN_GROUP(CLS, G, PPT)                                                                                         \
     case CLS:                                                                                                           \

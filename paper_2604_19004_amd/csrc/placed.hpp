@@ -21,7 +21,6 @@ namespace {
 
 constexpr unsigned long long NO_PLACE = ~0ull;   // the placing wave gave up
 constexpr int FLAG_GAVE_UP = 32;
-constexpr int PLACER_POLLS = 1 << 20, UNIT_POLLS = 1 << 21;   // about a microsecond each
 
 template <typename T>
 __device__ __forceinline__ T peek(const T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -37,7 +36,7 @@ struct Turn {
     unsigned int sum[2][4];      // entries among them that are new
 };
 __device__ __forceinline__ void place_units(const uint32_t *counts, unsigned long long *places, int64_t units,
-                                            unsigned long long *total_out, int32_t *flags, Turn &turn)
+                                            unsigned long long *total_out, int32_t *flags, int polls, Turn &turn)
 {
     constexpr int U = 4, QUARTER = U * WAVE;
     const int lane = lane_id();
@@ -113,7 +112,7 @@ __device__ __forceinline__ void place_units(const uint32_t *counts, unsigned lon
             at = next;
             run = after;
             idle = 0;
-        } else if (++idle > PLACER_POLLS) {   // (all waves at the same turn)
+        } else if (++idle > polls) {   // (all waves at the same turn)
             for (int64_t i = at + (int)threadIdx.x; i < units; i += 256) post(places + i, NO_PLACE);
             if (threadIdx.x == 0) atomicOr(flags, FLAG_GAVE_UP);
             return;
@@ -123,9 +122,9 @@ __device__ __forceinline__ void place_units(const uint32_t *counts, unsigned lon
 }
 
 // The place of a unit, or -1.  The whole wave.
-__device__ __forceinline__ int64_t wait_for_place(const unsigned long long *place, int32_t *flags)
+__device__ __forceinline__ int64_t wait_for_place(const unsigned long long *place, int32_t *flags, int polls)
 {
-    for (int i = 0; i < UNIT_POLLS; ++i) {
+    for (int i = 0; i < polls; ++i) {
         if (i > 0) __builtin_amdgcn_s_sleep(1);
         const unsigned long long v = peek(place);
         const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
@@ -153,6 +152,7 @@ struct Placing {
     unsigned long long *places;
     unsigned long long *total;
     int32_t *flags;
+    int placer_polls, unit_polls;   // before workgroup 0 and a unit give up
 };
 
 }  // namespace ocean

@@ -96,11 +96,11 @@ def test_all_sizes_in_one_matrix(ob, most, dtype):
     A = _csr(len(lists), B.rows, lists, rng, dtype)
     for wf in (ob.WF_UPPER_BOUND, ob.WF_AUTO):
         _check(ob, A, B, f"up to {most} products", workflow=wf)
-    # a row with an entry more than the sort takes, or a product: the general way
-    for extra in ([0] * 65, _row(rng, 2048) + [1] if most == 2048 else [0] * 65):
+    # a row with an entry more than the sort takes, or a product: the general way; the same entries without a product are none
+    for extra, placed in (([1] * 65, False), ([0] * 65, True), (_row(rng, 2048) + [1], False)):
         A = _csr(len(lists) + 1, B.rows, lists + [extra], rng, dtype)
-        if len(extra) > 64 or O.row_products(A, B)[-1] > 2048:
-            _check(ob, A, B, "a row too long", placed=extra == [0] * 65, workflow=ob.WF_UPPER_BOUND)
+        assert O.row_products(A, B)[-1] == {65: 65 * (extra[0] > 0)}.get(len(extra), 2049)
+        _check(ob, A, B, f"a row of {len(extra)} entries", placed=placed, workflow=ob.WF_UPPER_BOUND)
 
 
 def _wide_row(rng, entries, total):
