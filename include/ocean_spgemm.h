@@ -195,10 +195,11 @@ typedef struct ocean_stats {
      * ocean_bin_layout run in ONE launch of the column-window kernel: its time is reported under the last
      * bin and bin_ms of the two before it is 0.  Rows of few products are sorted instead of hashed, in one launch
      * per size class whatever their bins (a class whose rows merge into few columns: in one hash table): a launch's
-     * time is reported under the bin that holds most of its products.  Where every row is one of those (at most 2048 products
-     * and 64 entries of A), or the columns of nearly every row lie in a short range, nothing else was asked for and it
-     * is expected to be faster, AUTO and the upper-bound workflow accumulate all rows in one launch and write them straight to C: no symbolic pass (symbolic_rows_per_bin and assist_cr stay 0), no binning stage, no
-     * overflow; rows count in the bin that the workflow's prediction, exact for the two others, would have given them. */
+     * time is reported under the bin that holds most of its products.  Where every row is one of those (at most 2048
+     * products and 64 entries of A), or the columns of every row lie in a short range, nothing else was asked for and
+     * it is expected to be faster, AUTO and the upper-bound workflow accumulate all rows in one launch and write them
+     * straight to C: no symbolic pass (symbolic_rows_per_bin and assist_cr stay 0), no binning stage, no overflow; rows
+     * count in the bin that the workflow's prediction, exact for the two others, would have given them. */
     float bin_ms[OCEAN_MAX_BINS];
     int64_t bin_products[OCEAN_MAX_BINS];
     int64_t bin_nnz_a[OCEAN_MAX_BINS];
@@ -213,7 +214,9 @@ void ocean_default_options(ocean_options *opt /* host */);
  * dtype(B) == dtype(C).  C is a host struct the call fills in: its three
  * arrays come from opt->allocator (or hipMalloc) and belong to the caller,
  * who returns them with ocean_csr_release.  col_idx / val may be larger than
- * nnz entries.  opt and stats are host pointers and may be NULL.  Work is
+ * nnz entries, in every workflow: by an eighth or 65536 entries where rows were
+ * written straight to C (see ocean_stats), by whatever was reserved where rows
+ * were compacted in place or there was no memory for a smaller copy.  opt and stats are host pointers and may be NULL.  Work is
  * enqueued on `stream`; the call blocks the host wherever a total has to be
  * read back to size an allocation and returns after the stream has drained,
  * so C is complete on return.  On failure *C is zeroed and everything the

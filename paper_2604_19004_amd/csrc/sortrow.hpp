@@ -13,10 +13,14 @@
 //   compress  a key whose column differs from its predecessor's opens an entry of C; a prefix sum numbers them, a lane adds
 //             up its keys between one head and the next, what an entry has in lanes before comes by a prefix sum over
 //             lanes, and the row leaves through LDS with coalesced stores, in column order.
+// The steps below are those of rows placed in C (placed.hip) and of listed rows of more than 1024 products
+// (k_numeric_sort_long); k_numeric_sort, for smaller listed rows, takes the network and the scans from here and has its own
+// expand and accumulate: the values of 8 bytes that it adds up in LDS are faster where LDS is not short (sortrow.hip).
 // What bounds it is vector issue: 880 vector instructions per row of the 512-product class, of which the sort is 530, are
 // 489 us for 341 000 rows (of the rectangular input, before there was a class of 384) at one per four cycles and SIMD,
-// 541 us measured.  The work
-// does not depend on where the columns lie or how many products merge.  Sizes of 3 * 2^i products cost a third less
+// 541 us measured by k_numeric_sort.  Placed, issue is 87 % of the cycles of 762 products a row (2111 instructions) and 67 % of
+// those of 264 (861 instructions; a wave waits, for loads above all, in 69 % of its cycles, with 6.8 of them on a SIMD).
+// The work does not depend on where the columns lie or how many products merge.  Sizes of 3 * 2^i products cost a third less
 // per row than the next power of two (see settle).  Against the hash kernels (one MI355X, fp64 unless said): numeric
 // stage of the rectangular input (264 products a row) 1.50 -> 0.94 ms, clustered fp32 (762 products, 234 columns) 2.55 ->
 // 1.50 ms, 100 003 uniform rows of 1023 products fp32 1.29 -> 0.40 ms, Laplacian (25 products) 0.22 -> 0.19 ms.
