@@ -877,70 +877,71 @@ struct Placed {
     int span_cols = 0;
 };
 
-// Placing leaves out the binning (60 us with its read-back) and the symbolic pass or the compaction (3 ps a product and more:
-// 3.2 and 5.1 for 200 000 rows of 361 products in fp64).
-// Sorted rows: below a wave's class every row is sorted as the largest class; of rows that have a wave each, all that are in
-// flight wait for the longest among them, and a long row is nearly always among them.  Measured, 200 000 rows, fp64, whole call
-// in us, placed / general (the faster of compaction and symbolic pass), rows of 49, 121 and 196 products with one of 361, 1024 or
-// 2025 among every thousand: 308 / 297, 395 / 305, 795 / 311; 347 / 452, 431 / 457, 831 / 471; 410 / 603, 490 / 615, 876 / 625.  Equal
-// rows: 25 products 221 / 330 (400 000), 225 390 / 560, 484 689 / 944, 961 929 / 1272 (150 000), 2025 1390 / 1709 (100 000).
-// Dense ranges, where every row has one and it is the accumulator for four fifths of them: a row waits 3 us for its place, with
-// 2048 in flight (fewer where ranges are longer than 2048 columns: 60 000 rows of 1920 products on 3840 columns 703 us, sorted 758,
-// general 815), so placing pays from some 450 products a row on; sorting, where every row can be sorted, up to 700.
-// Block-diagonal matrices, fp64, whole call in us, placed dense / placed sorted / general: 300 000 rows of 324 products in blocks
-// of 300 columns 1352 / 734 / 1245, 200 000 of 399 in 500 970 / 636 / 950, 150 000 of 900 in 500 863 / 1104 / 1022, 100 000 of 1600
-// in 1000 749 / - / 886, of 1522 in 1300 787 / - / 929, 60 000 of 3602 in 1000 698 / - / 1030.
-//
-// Rows that merge into few columns are cheaper either way, the general one's more so, as tables of few columns take them: the
-// costs lie between kWavePs and kMergedPs by the share of the products that are entries of C, and the estimation workflow's follow
-// its products (0.7 of what they take where B is larger than 16 MB), entries of A and entries of C.  250 000 rows, fp64, whole call in
-// us, placed dense / placed sorted / general: 640 products on 32 columns 1043 / 802 / 764, on 128 1090 / 852 / 999, 1024 on 85 1110 /
-// 1154 / 991, on 512 1267 / 1219 / 1386; band of 25 of 200 000 rows 898 / 706 / 737, of 33 of 100 000 585 / 756 / 747.  By costs that
-// took no account of it the first was placed dense, and the band of 25 (755 us before rows were placed, 909 then).
-//
-// The upper-bound workflow has no symbolic pass to leave out, only the copy out of the reserved rows, 4.8 (fp64) or 3.6 ps an entry
-// of C; and where C has to be trimmed placing does not leave that out either.  It needs no trim where the reservation follows
-// counted rows, or where those that were counted hardly merge; otherwise nothing is counted on.  Upper bound forced,
-// whole call, fp32 rows of 762 products that merge into 234: placed 2.58 ms, general 2.07; fp64 rows of 270 that hardly merge:
-// placed 1.17, general 1.72.
-bool choose_placed(const Csr &A, const Csr &B, const Work &w, const Ctx &c, int64_t products, int workflow, size_t vbytes, Placed *how)
+// What a call costs either way, whole calls in us, the parts that both ways share left out: a sum over rows, entries of A, products,
+// entries of C (as far as counted rows tell how products merge) and, where rows are placed, waves of rows in flight.  A place comes
+// in row order, so the rows in flight wait for the largest of them: in_flight.  Weights by least squares (relative error, fp64 and
+// fp32) over 64 000 inputs of 600 to 1 000 000 rows, 0.3 to 400 M products, equal, uniform, skewed and mixed rows, columns anywhere or
+// in windows, each timed placed by sorting, placed by dense ranges and the general way: 0.09 to 0.15 of the placed pass
+// at one standard deviation, 0.08 to 0.13 of the whole call the general way.  By the sum the call is 0.792 of its time before rows were
+// placed (the better of the ways each time: 0.784), and 0.6 % of the inputs are slower by more than 4 %; the costs that were used
+// before took the longest row in flight or the sum of the rows, whichever is more, not both, and had each row of small classes cost
+// what the largest does: 0.806, and 3.3 % slower (of calls beyond 0.8 ms 11 %, up to 2.1 times: 219 000 rows of 12 to 1903 products
+// on 512 columns 1434 us for 660).
+struct CallCost {
+    double fixed, row, entry, product, out, wide_row;   // us, ns a row, ps each of the others, ns a row where ranges exceed 2048 columns
+};
+// [values of 8 bytes]
+constexpr CallCost kSymbolicCost[2] = {{100, 0.35, 3.4, 4.4, 2.15, 0}, {94, 0.39, 5.5, 3.9, 3.7, 0}};
+constexpr CallCost kSmallSymbolicCost[2] = {{64, 1.25, 0, 4.8, 0, 0}, {65, 1.3, 0, 4.1, 0, 0}};      // nothing counted
+constexpr CallCost kHllCost[2] = {{98, 0.17, 8.2, 2.4, 8.4, 0}, {99, 0.18, 9.7, 2.35, 10.3, 0}};
+constexpr CallCost kBoundCost[2] = {{75, 0.10, 4.0, 2.8, 5.4, 0}, {72, 0.09, 5.5, 2.9, 7.8, 0}};
+constexpr CallCost kUncountedBoundCost[2] = {{67, 0.21, 7.1, 5.1, 0, 0}, {67, 0.23, 7.4, 5.7, 0, 0}};   // nothing counted: placed, C would be copied too
+constexpr CallCost kRangesCost[2] = {{74, 1.6, 4.9, 1.8, 2.1, 2.8}, {72, 1.6, 4.9, 2.2, 1.9, 2.7}};     // four fifths of the rows in dense ranges
+constexpr CallCost kHllRangesCost[2] = {{80, 1.1, 12.1, 2.0, 1.4, 10.3}, {84, 1.0, 14.6, 2.2, 1.9, 7.1}};
+
+// The mean over stretches of `flying` rows of the largest of them, where a row of class k (0: of no class) has size[k].
+double largest_in_flight(const Work &w, double rows, double flying, const double (&size)[SORT_CLASSES])
 {
-    constexpr double kWavePs[SORT_CLASSES] = {0, 1050, 1050, 1050, 1050, 1300, 1600, 2300, 2950, 4300, 5600, 10000, 12900};
-    constexpr double kMergedPs[SORT_CLASSES] = {0, 1050, 1050, 1050, 1050, 1050, 1250, 1800, 2300, 2750, 4000, 6200, 11500};
-    const double rows = (double)A.rows, prods = (double)products;
-    const bool counted = w.count_cr > 0.0;
-    const double part = counted ? 1.0 / w.count_cr : 1.0;   // of the products that are entries of C
-    const double entries = prods * part;
-    double general = 60e6 + 3.0 * prods;   // ps
-    bool by_class = !w.spans;              // .. and the sorted rows'
-    double wary = 1.0;                     // placed rows of mixed sizes take up to 1.3 times what is reckoned here
-    if (workflow == OCEAN_WF_UPPER_BOUND && counted) {
-        general = 60e6 + (vbytes == 8 ? 5.5 : 4.0) * entries;
-        wary = vbytes == 4 && (w.class_rows[11] != 0 || w.class_rows[12] != 0) ? 0.9 : 1.15;   // (4 bytes: half the LDS)
-    } else if (workflow == OCEAN_WF_UPPER_BOUND) {
-        const bool trimmed = !(w.merge_cr > 0.0 && (w.merge_all || w.merge_cr < 1.1));
-        general = 60e6 + (trimmed ? 0.0 : (vbytes == 8 ? 4.8 : 3.6) * prods / w.merge_cr);
-    } else if (workflow == OCEAN_WF_HLL && counted) {
-        const bool far = (double)B.nnz * (double)(4 + vbytes) > 16e6;
-        general = 110e6 + 400.0 * rows + 10.0 * (double)A.nnz + (w.spans ? 2.6 : 3.9) * (far ? 1.0 : 0.7) * prods +
-                  (vbytes == 8 ? 8.0 : 5.3) * entries;
-        by_class = false;
-    } else if (w.spans) {
-        general = 120e6 + 2400.0 * rows + 2.2 * prods;
+    double from = (double)w.class_rows[0], mean = from > 0.0 ? size[0] * -std::expm1(flying * std::log1p(-std::fmin(from / rows, 1.0))) : 0.0;
+    double above = mean > 0.0 ? -std::expm1(flying * std::log1p(-std::fmin(from / rows, 1.0))) : 0.0;
+    for (int k = SORT_CLASSES - 1; k > 0; --k) {
+        from += (double)w.class_rows[k];
+        const double met = -std::expm1(flying * std::log1p(-std::fmin(from / rows, 1.0)));   // one of class k or larger
+        mean += (met - above) * size[k];
+        above = met;
     }
+    return mean;
+}
+
+bool choose_placed(const Csr &A, const Work &w, const Ctx &c, int64_t products, int64_t max_row, int workflow, size_t vbytes, Placed *how)
+{
+    const unsigned long long *t = w.span_totals;
+    if (w.spans && (c.h->flags & 8)) return false;   // (B's rows are out of column order: the ranges are guesses)
+    const int d = vbytes == 8;
+    const double rows = (double)A.rows, krows = 1e-3 * rows, mprods = 1e-6 * (double)products;
+    const double cr = w.count_cr > 0.0 ? w.count_cr : w.merge_all ? w.merge_cr : 0.0;
+    const double mouts = cr > 0.0 ? mprods / cr : mprods;
+    const bool ranges = w.spans && t[0] != 0 && t[1] == 0 && t[4] * 5 >= t[0] * 4 && A.rows + 1 <= most_blocks(256);
+    const CallCost &g = ranges ? (workflow == OCEAN_WF_HLL ? kHllRangesCost[d] : kRangesCost[d])
+                        : workflow == OCEAN_WF_HLL ? kHllCost[d]
+                        : workflow == OCEAN_WF_UPPER_BOUND ? (cr > 0.0 ? kBoundCost[d] : kUncountedBoundCost[d])
+                        : cr > 0.0 ? kSymbolicCost[d] : kSmallSymbolicCost[d];
+    const double general = g.fixed + (g.row + (t[2] > 2048 ? g.wide_row : 0.0)) * krows + g.entry * 1e-6 * (double)A.nnz +
+                           g.product * mprods + g.out * mouts;
+    double least = general / 1.05;
     bool found = false;
-    if (w.spans) {
-        const unsigned long long *t = w.span_totals;
-        if (c.h->flags & 8) return false;   // (B's rows are out of column order: the ranges are guesses)
-        if (t[0] != 0 && t[1] == 0 && t[4] * 5 >= t[0] * 4 && A.rows + 1 <= most_blocks(256)) {
-            const bool longest = t[2] > 2048;
-            if (longest && workflow != OCEAN_WF_HLL) general = 120e6 + 7500.0 * rows + 2.2 * prods;
-            const double placed = longest ? 8000.0 * rows + 1.8 * prods : (t[2] > 1024 ? 3600.0 : 3100.0) * rows + 1.5 * prods;
-            if (placed < general) {
-                found = true;
-                how->span_cols = (int)t[2];
-                general = placed;
-            }
+    if (ranges) {   // a workgroup per row
+        const int of = t[2] > 2048 ? 2 : t[2] > 1024 ? 1 : 0;
+        constexpr double kRow[2][3] = {{3.05, 3.75, 8.5}, {3.1, 4.2, 8.4}};
+        const double flying = (of == 2 ? 4.0 : 8.0) * c.n_cu;
+        double size[SORT_CLASSES];
+        for (int k = 0; k < SORT_CLASSES; ++k) size[k] = 1e-3 * std::fmin((double)(k > 0 ? kSortClass[k].cap : max_row), (double)max_row);
+        const double placed = 11.0 + kRow[d][of] * krows + (d ? 0.53 : 0.64) * rows / flying * largest_in_flight(w, rows, flying, size) +
+                              (d ? 0.89 : 0.73) * mprods;
+        if (placed < least) {
+            found = true;
+            how->span_cols = (int)t[2];
+            least = placed;
         }
     }
     if (w.class_rows[0] != 0) return found;   // a row with more products or entries than the sort takes
@@ -949,23 +950,19 @@ bool choose_placed(const Csr &A, const Csr &B, const Work &w, const Ctx &c, int6
         if (w.class_rows[k] != 0) cls = k;
     if (cls == 0 || !((c.sort_mask >> cls) & 1u)) return found;
     if (placed_units(A.rows, cls) + 1 > most_blocks(256)) return found;
-    for (int k = 1; by_class && k <= cls; ++k) {
-        // (of rows that merge, the least that was measured: 0.45 to 0.57 of a row's that do not)
-        const double merged = !counted || workflow != OCEAN_WF_UPPER_BOUND ? 1.0 : k <= 9 ? 0.5 : k <= 11 ? 0.55 : 0.45;
-        general += (double)w.class_rows[k] * kSortClass[k].ps * (merged + (1.0 - merged) * part);
-    }
     double placed;
-    if (kPlacedRows[cls] > 4) {
-        placed = rows * kSortClass[cls].ps;
-    } else {
+    if (kPlacedRows[cls] > 4) {   // every row is sorted as the largest class
+        constexpr double kRow[7] = {0, 0.117, 0.24, 0.31, 0.40, 0.595, 0.76};
+        placed = 9.0 + kRow[cls] * krows + (d ? 2.0 : 1.3) * mouts;
+    } else {   // a wave per row
         const int by_lds = 160 * 1024 / w.four_rows_lds, by_registers = cls <= 10 ? 7 : cls == 11 ? 5 : 4;   // workgroups of a CU
-        const double in_flight = 4.0 * c.n_cu * (by_lds < by_registers ? by_lds : by_registers);
-        placed = rows / in_flight * (7.5e6 + 3.4e3 * kSortClass[cls].cap);   // the longest row's time
-        double sorted = 0.0;
-        for (int k = 1; k <= cls; ++k) sorted += (double)w.class_rows[k] * (kMergedPs[k] + (kWavePs[k] - kMergedPs[k]) * part);
-        if (sorted > placed) placed = sorted;
+        const double flying = 4.0 * c.n_cu * (by_lds < by_registers ? by_lds : by_registers);
+        double size[SORT_CLASSES];
+        for (int k = 0; k < SORT_CLASSES; ++k) size[k] = 3.4e-3 * kSortClass[k].cap;
+        placed = 12.0 + (d ? 0.87 : 0.80) * rows / flying * (7.5 + largest_in_flight(w, rows, flying, size)) + (d ? 1.98 : 2.45) * mprods +
+                 (d ? 0.88 : 0.5) * mouts;
     }
-    if (placed * wary >= general) return found;
+    if (placed >= least) return found;
     how->cls = cls;
     how->span_cols = 0;
     return true;
@@ -1233,7 +1230,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
             }
         }
         bool done = false;
-        if (choose_placed(A, B, w, c, P, workflow, vbytes, &how)) {
+        if (choose_placed(A, w, c, P, S->max_row_products, workflow, vbytes, &how)) {
             S->hll_registers = m_regs;
             OC_TRY(run_placed(c, w, A, B, dtype, how, workflow, o, st, S, c_rp, C, &done));
         }
