@@ -879,49 +879,251 @@ k_numeric_hybrid(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a
 
 // ======================================================== heavy kernel ====
 // Rows whose output exceeds the 4096-slot LDS table, when B's rows are sorted.
-// The column range is cut into windows of WIN columns and
+// The column range is cut into windows of HV_WIN columns and
 // bw[k*(n_win+1)+w] is the position in B's arrays of the first entry of row k
-// with column >= w*WIN, so any run of windows can be visited on its own.  One
+// with column >= w*HV_WIN, so any run of windows can be visited on its own.  One
 // workgroup first counts the row's products per window (an upper bound of the
 // entries of that window), then walks the windows in order, carrying the
 // running output offset.  Both kinds of pass accumulate in LDS only, need no
 // hash table, and leave their entries in column order:
-//   * a window with more products than a sparse pass can stage is accumulated
-//     densely (Section 2.2 dense accumulator, iterated over the row's column
-//     range as in Section 3.2): WIN values + a presence bitmap in LDS, one LDS
-//     add + one LDS or per product; the bitmap's prefix popcount places each
-//     present column at its sorted position;
-//   * consecutive windows whose products fit the staging memory left beside
-//     their bitmap (a sparse stretch: up to 8192 products over 10 windows,
-//     fewer over more) share one pass in the manner of an
-//     expand-sort-compress accumulator whose sort is a bitmap rank: every
-//     product is written to LDS at its own number (no atomics) and marks its
-//     column in a bitmap over the stretch; the prefix popcount of the bitmap is
-//     the position of each column in the output, so a second sweep over the
-//     staged products adds each value at its column's rank.  No probing, no
-//     compare-and-swap, no divergence.
-// More than half of the kernel's time is the gather of B's entries, which runs
-// at what the memory system gives for pieces of rows this short; the rest is
-// instruction issue of the work every pass repeats (planning, prefix sums,
-// barriers), which is why sparse stretches are merged into few passes and why
-// every pass spreads its products over the whole workgroup.
+//   * a window with more products than a ranked pass may have entries is
+//     accumulated densely (Section 2.2 dense accumulator, iterated over the row's
+//     column range as in Section 3.2): an accumulator per column, one LDS add per
+//     product.  -0 stands for a column without products (no addend is ever -0), so
+//     there are no presence bits; the window is read once, a ballot per 64 columns
+//     numbers its entries;
+//   * consecutive lighter windows (a stretch of up to 16, 262 144 columns) are ranked:
+//     a first walk over their products marks the columns in a bitmap, whose prefix
+//     popcounts number the entries of C, and a second one adds every product at its
+//     column's number - 8192 accumulators a pass, as many windows at a time as have
+//     so many entries, however many products they are.  A stretch of few tiles keeps
+//     its products in registers between the two.
+// The products are walked in tiles of 64 of one piece of a row of B, 16 lanes a tile, four
+// consecutive products a lane (one 16-byte load of columns, two of fp64 values), tiles dealt
+// out evenly to the waves.  What a tile needs (position, length, A's value) is found by one
+// search per 64 tiles and reaches the 16 lanes by DPP moves: no search, LDS read or 64-bit
+// prefix per product.  R-MAT scale 18 (68 800 rows, 3.0 G products, most rows 4 to 90 long pieces):
+// 11.29 -> 9.98 ms against products numbered one by one, single sparse passes of at most 8192
+// products and presence bits (whole
+// calls: 14.6 -> 13.1 ms; scale 20 110.1 -> 106.5; scale 14 in fp32 0.74 -> 0.71).  By parts, from variants that leave one out (of 10.3 ms): row
+// and pass set-up 3.4 (the sweep of dense windows 1.0, opening the pieces 1.0), search 0.6, loads
+// 2.2 (1.3 of it where every load hits the L2), LDS work and output 4.0.  The LDS is the busiest
+// unit (50 % of the cycles, 8.6 per instruction: randomly addressed 8-byte adds), vector issue 44 %;
+// what bounds the kernel is that one workgroup fills the compute unit, so its phases do not overlap.
+// Two workgroups of 512 threads, windows of half the size: 9.6 ms before the last steps on scale 18, but
+// 0.22 against 0.15 on scale 15 and twice the window table; tiles of 64 lanes, 8 products a batch,
+// the tile's numbers in scalar registers: the same time with 15 % more vector instructions.
 constexpr int HV_THREADS = 1024;
-constexpr int HV_REGION = 131072;                  // bytes of LDS that hold the accumulator of a pass
-constexpr int HV_WG_PER_CU = 1;                    // (two workgroups of half the size each measured 13 % slower)
-constexpr int HV_PPT = 8;                          // products of a sparse pass per thread, at most
-constexpr int HV_HCAP = HV_PPT * HV_THREADS;       // products one sparse pass takes at most: 8192
+constexpr int HV_WAVES = HV_THREADS / WAVE;
+constexpr int HV_WG_PER_CU = 1;
+constexpr int HV_WIN = 16384;                      // columns of a window, and accumulators of a dense pass
+constexpr int HV_RUN = 16;                         // windows of a stretch, at most
+constexpr int HV_CAP = 8192;                       // entries of C that a ranked pass accumulates, products of a light window
 constexpr int HV_MAXWIN = 512;                     // windows per row the kernel can plan for
-constexpr int HV_RPT = 48;                         // chunks of up to 48 products per thread find their entries by rank
-                                                   // (most dense windows then do: 96.8 -> 94.9 ms; 4 KB more LDS)
+constexpr int HV_CHUNK = 512;                      // entries of A whose pieces of B are laid end to end at a time
+constexpr int HV_KEEP = 8;                         // tiles per wave up to which a stretch's products stay in registers
+static_assert(HV_RUN <= HV_WAVES && HV_WIN / 32 == 8 * WAVE, "a wave per window and eight words per lane");
 
+// The region's parts in a ranked pass (bytes): accumulators and columns by rank, prefix counts and bitmap by column.
+constexpr int HV_AT_COL = (HV_CAP + WAVE) * 8;
+constexpr int HV_AT_PRE = HV_AT_COL + (HV_CAP + WAVE) * 4;
+constexpr int HV_AT_MAP = HV_AT_PRE + HV_RUN * (HV_WIN / 32) * 2;
+constexpr int HV_REGION = HV_AT_MAP + HV_RUN * (HV_WIN / 8) + WAVE * 4;
+static_assert(HV_REGION >= (HV_WIN + WAVE) * 8 && HV_AT_PRE % 16 == 0 && HV_AT_MAP % 16 == 0, "a dense pass takes the region from its start");
+
+// Pieces of rows of B (position, entries, A's value) of up to HV_CHUNK entries of A, and the tiles of 64 products before each.
 template <typename V>
-struct DenseCfg {
-    static constexpr int WIN = HV_REGION / (int)sizeof(acc_t<V>);   // columns of a window: a region full of accumulators
-    static constexpr int WORDS = WIN / 32;
+struct HvChunk {
+    uint32_t first[HV_CHUNK], pos[HV_CHUNK], len[HV_CHUNK];
+    V a[HV_CHUNK];
+    uint32_t wsum[HV_CHUNK / WAVE];
+    uint32_t total;
 };
 
-// QUERY: dense windows read a column's presence bit and set it only when it is clear (Section 4.1).
-template <typename V, bool QUERY>
+// The pieces that the first nent threads hold (len = 0 in all others) into c; returns their tiles.  Every thread calls
+// it; c must be free on entry, and is ready behind the barrier that this ends with.
+template <typename V>
+__device__ __forceinline__ uint32_t hv_open(HvChunk<V> &c, int nent, uint32_t p, uint32_t len, V a)
+{
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const uint32_t tiles = (len + (WAVE - 1)) / WAVE;
+    if (nent <= WAVE) {   // uniform
+        if (tid < WAVE) {
+            const uint32_t incl = wave_inclusive_scan_u32(tiles);
+            c.first[tid] = incl - tiles;
+            c.pos[tid] = p;
+            c.len[tid] = len;
+            c.a[tid] = a;
+            if (lane == WAVE - 1) c.total = incl;
+        }
+        lds_barrier();
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)c.total);
+    }
+    uint32_t incl = 0;
+    if (tid < HV_CHUNK) {
+        incl = wave_inclusive_scan_u32(tiles);
+        if (lane == WAVE - 1) c.wsum[tid / WAVE] = incl;
+    }
+    lds_barrier();
+    uint32_t total;
+    const uint32_t before = waves_before_u32<HV_CHUNK / WAVE>(c.wsum, tid < HV_CHUNK ? tid / WAVE : 0, total);
+    if (tid < HV_CHUNK) {
+        c.first[tid] = before + incl - tiles;
+        c.pos[tid] = p;
+        c.len[tid] = len;
+        c.a[tid] = a;
+    }
+    lds_barrier();
+    return total;
+}
+
+// v of lane J of every row of 16 lanes, in all of them.
+template <int J>
+__device__ __forceinline__ uint32_t row_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + J, 0xf, 0xf, false); }   // row_newbcast
+template <int J>
+__device__ __forceinline__ float row_lane(float v) { return __uint_as_float(row_lane<J>(__float_as_uint(v))); }
+template <int J>
+__device__ __forceinline__ double row_lane(double v)
+{
+    const unsigned long long x = (unsigned long long)__double_as_longlong(v);
+    return __longlong_as_double((long long)(((unsigned long long)row_lane<J>((uint32_t)(x >> 32)) << 32) | row_lane<J>((uint32_t)x)));
+}
+// Every row of 16 lanes moved down by J lanes.
+template <int J>
+__device__ __forceinline__ uint32_t row_down(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x100 + J, 0xf, 0xf, false); }   // row_shl
+template <int J>
+__device__ __forceinline__ float row_down(float v) { return __uint_as_float(row_down<J>(__float_as_uint(v))); }
+template <int J>
+__device__ __forceinline__ double row_down(double v)
+{
+    const unsigned long long x = (unsigned long long)__double_as_longlong(v);
+    return __longlong_as_double((long long)(((unsigned long long)row_down<J>((uint32_t)(x >> 32)) << 32) | row_down<J>((uint32_t)x)));
+}
+
+// A tile per lane: 64 products of a piece, or fewer at its end (n).  A row of 16 lanes walks a tile, four products a lane, so a
+// wave walks four tiles in a step; step j's are with lanes j, 16 + j, 32 + j and 48 + j.
+constexpr int HV_ROW = 16, HV_STEP = WAVE / HV_ROW;
+template <typename V>
+struct HvTiles {
+    uint32_t p;
+    int32_t n;    // 0: no tile (with p = 4, so that four entries before p are there to be read)
+    V a;
+    bool edge;    // (uniform) a tile ends among B's first three entries
+
+    // tiles from..to-1 of the chunk (to - from <= 64, to <= total)
+    __device__ __forceinline__ void find(const HvChunk<V> &c, int nent, uint32_t total, uint32_t from, uint32_t to)
+    {
+        const uint32_t mine = from + (uint32_t)(lane_id() % HV_ROW * HV_STEP + lane_id() / HV_ROW);
+        const uint32_t t = mine < total ? mine : total - 1u;
+        int e = 0;   // the last piece that starts at or before tile t (pieces without products start where the next one does)
+        for (int step = nent > 1 ? 1 << (31 - __clz(nent - 1)) : 0; step > 0; step >>= 1)
+            if (c.first[e + step] <= t) e += step;
+        const uint32_t off = (t - c.first[e]) * WAVE;
+        const uint32_t left = c.len[e] - off;
+        p = mine < to ? c.pos[e] + off : 4u;
+        n = mine < to ? (int32_t)(left < WAVE ? left : (uint32_t)WAVE) : 0;
+        a = c.a[e];
+        edge = __ballot(p + (uint32_t)n < 4u) != 0ull;
+    }
+    // step J from now on is the first
+    template <int J>
+    __device__ __forceinline__ void advance()
+    {
+        p = row_down<J>(p);
+        n = (int32_t)row_down<J>((uint32_t)n);
+        a = row_down<J>(a);
+    }
+};
+
+// A lane's four entries of B in a step.  They are its four of the tile, or the tile's last four where those would
+// reach beyond its end: the first `skip` of them are then another lane's (all four: the lane has none).
+template <typename V>
+struct HvFour {
+    int32_t col[4];
+    V val[4];
+    int32_t skip;
+};
+struct alignas(4) HvCols { int32_t v[4]; };
+template <typename V> struct alignas(sizeof(V)) HvVals { V v[4]; };
+
+template <int J, bool VALS, typename V>
+__device__ __forceinline__ void hv_load(const HvTiles<V> &t, const int32_t *__restrict__ b_col, const V *__restrict__ b_val, HvFour<V> &f)
+{
+    const int32_t sub = 4 * (lane_id() % HV_ROW);
+    const uint32_t p = row_lane<J>(t.p);
+    const int32_t n = (int32_t)row_lane<J>((uint32_t)t.n);
+    int32_t at = sub < n - 4 ? sub : n - 4;
+    const int32_t least = -(int32_t)(p < 4u ? p : 4u);
+    at = at > least ? at : least;   // (a tile that ends among B's first three entries)
+    f.skip = sub - at;
+    const size_t q = (size_t)(p + (uint32_t)at);
+    const HvCols c = *reinterpret_cast<const HvCols *>(b_col + q);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f.col[i] = c.v[i];
+    if constexpr (VALS) {
+        const HvVals<V> v = *reinterpret_cast<const HvVals<V> *>(b_val + q);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f.val[i] = v.v[i];
+    }
+    if (t.edge) {   // uniform
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f.col[i] = at + i < n ? f.col[i] : -1;
+    }
+}
+
+// Every product of the open chunk once: use(fours, t) for the lane's part of two steps at a time, t's first two, the tiles dealt out evenly to the waves.
+// mine: the wave's tiles (its first 64) where `found` says so, and on return where there are no more.
+template <bool VALS, typename V, typename F>
+__device__ __forceinline__ void hv_walk(const HvChunk<V> &c, int nent, uint32_t total, const int32_t *__restrict__ b_col,
+                                        const V *__restrict__ b_val, HvTiles<V> &mine, bool found, F use)
+{
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
+    const uint32_t span = (total + HV_WAVES * HV_STEP - 1) / (HV_WAVES * HV_STEP) * HV_STEP;
+    const uint32_t t0 = wave * span, t1 = t0 + span < total ? t0 + span : total;
+    for (uint32_t from = t0; from < t1; from += WAVE) {   // uniform for the wave
+        if (!found || from > t0) mine.find(c, nent, total, from, t1);
+        HvTiles<V> t = mine;
+        int left = (int)(t1 - from < WAVE ? t1 - from : WAVE);   // tiles
+        HvFour<V> f[2], g[2];
+        hv_load<0, VALS>(t, b_col, b_val, f[0]);
+        hv_load<1, VALS>(t, b_col, b_val, f[1]);
+        for (; left > 2 * HV_STEP; left -= 2 * HV_STEP) {   // (the next two steps are on their way while these are used)
+            hv_load<2, VALS>(t, b_col, b_val, g[0]);
+            hv_load<3, VALS>(t, b_col, b_val, g[1]);
+            use(f, t);
+            t.template advance<2>();
+            f[0] = g[0];
+            f[1] = g[1];
+        }
+        use(f, t);
+    }
+}
+
+// x, as a number that the compiler doesn't know: what is computed from it stays inside the loop that it is taken in,
+// instead of a register of its own through all of it.
+__device__ __forceinline__ int hv_hide(int x)
+{
+    asm("" : "+v"(x));
+    return x;
+}
+
+// A product as it is added to an accumulator that says by -0 that nothing has been added yet: never -0 itself.  (As a
+// multiplication and an addition of their own: contracted, a negative product that underflows would stay -0.)
+template <typename V>
+__device__ __forceinline__ double hv_addend(V v)
+{
+#pragma clang fp contract(off)
+    return (double)v + 0.0;
+}
+
+// Whether something has been added to an accumulator of a dense window.
+__device__ __forceinline__ bool hv_there(double v) { return __double_as_longlong(v) != (long long)0x8000000000000000ull; }
+
+// p[i], the byte offset in 32 bits (an address of one register beside the uniform p).
+template <typename T>
+__device__ __forceinline__ T *hv_at(T *p, uint32_t i) { return reinterpret_cast<T *>(reinterpret_cast<char *>(p) + i * (uint32_t)sizeof(T)); }
+
+template <typename V>
 __global__ void __launch_bounds__(HV_THREADS)
 k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, const V *__restrict__ a_val,
                 const uint32_t *__restrict__ bw, int n_win, const int32_t *__restrict__ b_col,
@@ -929,59 +1131,45 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                 unsigned long long *queue, const int64_t *__restrict__ out_ptr, int32_t *__restrict__ out_col,
                 V *__restrict__ out_val, int32_t *__restrict__ row_nnz)
 {
-    constexpr int WIN = DenseCfg<V>::WIN;
-    constexpr int WORDS = DenseCfg<V>::WORDS;
-    // one 128 KB region, used either as the dense window or as hash table + bucket counts
     __shared__ __align__(16) unsigned char s_u[HV_REGION];
-    __shared__ uint32_t s_dbm[WORDS];
-    __shared__ WgChunk<V, HV_THREADS, HV_RPT> s_fc;
-    __shared__ int s_wave[HV_THREADS / WAVE];
-    __shared__ uint32_t s_pw[HV_MAXWIN + 1];   // s_pw[w]: products of the row in the windows before w
-    __shared__ int s_ovf;
+    __shared__ HvChunk<V> s_ch;
+    __shared__ uint32_t s_pw[HV_MAXWIN];                  // products of the row per window
+    __shared__ __align__(16) uint32_t s_grp[HV_WIN / WAVE];   // dense pass: entries of C per 64 columns
+    __shared__ uint32_t s_win[HV_WAVES];                  // ranked pass: entries of C per window
     __shared__ long long s_row;
-    static_assert(WORDS <= HV_THREADS, "the prefix counts of a dense window reuse the chunk's array of prefix sums");
-    uint32_t *s_dpre = s_fc.excl;   // (free between the traversal of a pass and the next one)
-    using AV = acc_t<V>;
-    AV *s_vals = reinterpret_cast<AV *>(s_u);                                      // dense: WIN accumulators
-    // sparse pass: staged products (column, value) by product number; once every thread holds its
-    // products in registers the same memory takes the output (columns, accumulated values) by rank
-    // Its memory is laid out per pass: the more windows a stretch spans, the more of the region goes to
-    // the bitmap (WIN/8 bytes per window) and its prefix counts (WIN/16), the less to staged products
-    // (4 + sizeof(AV) bytes each, in multiples of one product per thread).
-    constexpr int OV = WIN / 8 + WIN / 16;
-    auto sparse_cap = [](int run) {
-        const int c = (HV_REGION - run * OV) / (4 + (int)sizeof(AV)) / HV_THREADS * HV_THREADS;
-        return c > HV_HCAP ? HV_HCAP : (c < 0 ? 0 : c);
-    };
-    int32_t *s_scol = reinterpret_cast<int32_t *>(s_u);
-    const int tid = threadIdx.x;
+    double *s_vals = reinterpret_cast<double *>(s_u);
+    int32_t *s_col = reinterpret_cast<int32_t *>(s_u + HV_AT_COL);
+    uint16_t *s_pre = reinterpret_cast<uint16_t *>(s_u + HV_AT_PRE);
+    uint32_t *s_map = reinterpret_cast<uint32_t *>(s_u + HV_AT_MAP);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
     const size_t stride = (size_t)n_win + 1;
 
-    for (int j = tid; j < WIN; j += HV_THREADS) s_vals[j] = (AV)0;
-    for (int j = tid; j < WORDS; j += HV_THREADS) s_dbm[j] = 0u;
-    bool dense_clean = true;   // the region is an all-zero dense window
-    bool chunk_clean = false;  // the traversal's marks are as wg_flat_chunk_keep leaves them
+    for (int j = threadIdx.x; j < HV_WIN; j += HV_THREADS) s_vals[j] = -0.0;
+    for (int w = threadIdx.x; w < HV_MAXWIN; w += HV_THREADS) s_pw[w] = 0u;
+    if (threadIdx.x == 0) s_row = (long long)atomicAdd(queue, 1ull);
+    bool clean = true;   // every accumulator of the dense window is -0; the first HV_CAP always are between passes
+    lds_barrier();
 
     for (;;) {
-        if (tid == 0) {
-            s_row = (long long)atomicAdd(queue, 1ull);
-            s_ovf = 0;
-        }
-        for (int w = tid; w <= n_win; w += HV_THREADS) s_pw[w] = 0u;
-        __syncthreads();
-        if (s_row >= count) break;   // uniform exit
-        const int64_t r = count - 1 - s_row;   // from the end of the list, where the rows with the largest bounds are
-        const int64_t row = rows[r];
-        const int64_t e0 = a_rp[row], e1 = a_rp[row + 1];
+        const int tid = hv_hide((int)threadIdx.x), lane = tid & (WAVE - 1);
+        // where lanes without a product add and mark, so that none has to be switched off: behind the arrays' own places
+        const uint32_t dump = (uint32_t)(HV_WIN + lane), rank_dump = (uint32_t)(HV_CAP + lane), map_dump = (uint32_t)(HV_RUN * (HV_WIN / 32) + lane);
+        const long long ticket = wave_first(s_row);
+        if (ticket >= count) break;   // uniform exit
+        const int64_t row = rows[count - 1 - ticket];   // from the end of the list, where the rows with the largest bounds are
+        const int64_t e0 = a_rp[row];
         const int64_t o = out_ptr[row];
         const int64_t cap = out_ptr[row + 1] - o;
-        const int64_t ne = e1 - e0;
+        const int64_t ne = a_rp[row + 1] - e0;
         long long done = 0;
+        unsigned long long drawn = 0;
+        if (tid == 0) drawn = atomicAdd(queue, 1ull);
 
-        // the first HV_THREADS entries of the row stay in registers over all passes
+        // the first HV_CHUNK entries of the row stay in registers over all passes
+        const int nent0 = ne < HV_CHUNK ? (int)ne : HV_CHUNK;
         int32_t ek = 0;
         V ea = V();
-        if (tid < ne) { ek = a_col[e0 + tid]; ea = a_val[e0 + tid]; }
+        if (tid < nent0) { ek = a_col[e0 + tid]; ea = a_val[e0 + tid]; }
         // ---- products of the row per window: one (entry, window) pair per thread and step
         {
             const int de = HV_THREADS / n_win, dw = HV_THREADS % n_win;
@@ -1009,39 +1197,26 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (d[i]) atomicAdd(&s_pw[pw[i] + 1], d[i]);
+                    if (d[i]) atomicAdd(&s_pw[pw[i]], d[i]);
             }
         }
-        __syncthreads();
-        {   // counts -> running sums (n_win <= HV_MAXWIN <= HV_THREADS: one window per thread)
-            const int mine = tid < n_win ? (int)s_pw[tid + 1] : 0;
-            int all;
-            const int before = block_exclusive_scan_i32<HV_THREADS>(mine, s_wave, all);
-            if (tid < n_win) s_pw[tid + 1] = (uint32_t)(before + mine);
-        }
-        __syncthreads();
+        lds_barrier();
+        if (tid == 0) s_row = (long long)drawn;   // (read by all before that barrier; the next row's behind one more)
 
-        // ---- walk the windows, pass by pass
-        // next pass from window `from` on: a window with more products than a sparse pass can stage (dense),
-        // or a run of windows whose products fit the staging memory that is left beside the run's bitmap
-        // (sparse); p0 == n_win when nothing is left
-        // Every wave plans for itself, 64 windows at a look: lane l holds the running sum behind window
-        // from + l, a ballot finds the first window with products, and since the products of a stretch
-        // grow with its length while its capacity shrinks, a second ballot finds how far the stretch goes.
-        const int lane = tid & (WAVE - 1);
+        // ---- walk the windows, pass by pass.  Next pass from window `from` on: p0 == n_win when nothing is left.
+        // Every wave plans for itself, 64 windows at a look, lane l window x + l.
         auto plan = [&](int from, int &p0, int &p1, bool &pdense) {
             p0 = n_win; p1 = n_win; pdense = false;
             for (int x = from; x < n_win; x += WAVE) {   // uniform
-                const uint32_t before = s_pw[x];
-                const int wl = x + lane;   // this lane's window
-                const uint32_t upto = s_pw[(wl < n_win ? wl : n_win - 1) + 1] - before;   // products of [x, wl]
-                const unsigned long long some = __ballot(wl < n_win && upto > 0u);
+                const int wl = x + lane;
+                const uint32_t n = wl < n_win ? s_pw[wl] : 0u;
+                const unsigned long long some = __ballot(n > 0u);
                 if (some == 0ull) continue;
                 const int k = __ffsll((long long)some) - 1;   // windows x .. x+k-1 are empty
-                const unsigned long long fits = __ballot(lane >= k && wl < n_win && upto <= (uint32_t)sparse_cap(lane - k + 1));
-                // lanes k, k+1, ... that fit in a row: the stretch
-                const unsigned long long stop = ~(fits >> k);
-                const int run = stop ? __ffsll((long long)stop) - 1 : WAVE - k;
+                const unsigned long long light = __ballot(wl < n_win && n <= (uint32_t)HV_CAP) >> k;
+                int run = light == ~0ull ? WAVE : __ffsll((long long)~light) - 1;   // light windows in a row from x + k on
+                run = run < WAVE - k ? run : WAVE - k;
+                run = run < HV_RUN ? run : HV_RUN;
                 p0 = x + k;
                 pdense = run == 0;
                 p1 = p0 + (run == 0 ? 1 : run);
@@ -1051,8 +1226,9 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
         int w, w1;
         bool dense;
         plan(0, w, w1, dense);
+        if (w == n_win) lds_barrier();   // (nothing at all: the counts are cleared below)
         // window boundaries of this thread's entry: those of the next pass are fetched one pass ahead
-        const bool have0 = tid < ne;
+        const bool have0 = tid < nent0;
         const uint32_t *t0 = bw + (size_t)ek * stride;
         uint32_t c_lo = have0 ? t0[w] : 0u, c_hi = have0 ? t0[w1] : 0u;
         while (w < n_win) {
@@ -1061,205 +1237,227 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
             plan(w1, nx0, nx1, nxdense);
             // (no entry has products in the windows skipped between two passes: the next pass starts at c_hi)
             const uint32_t n_hi = have0 ? t0[nx1] : 0u;
-            // memory of a sparse pass (see above)
-            const int scap = sparse_cap(w1 - w);
-            AV *s_sval = reinterpret_cast<AV *>(s_u + (size_t)scap * 4);
-            uint16_t *s_hpre = reinterpret_cast<uint16_t *>(s_u + (size_t)scap * (4 + sizeof(AV)));
-            uint32_t *s_hbm = reinterpret_cast<uint32_t *>(s_u + (size_t)scap * (4 + sizeof(AV)) + (size_t)(w1 - w) * (WIN / 16));
-            const int hwords = (w1 - w) * (WIN / 32);
-            // accumulator of this pass
-            if (dense) {
-                if (!dense_clean) {
-                    for (int j = tid; j < WIN; j += HV_THREADS) s_vals[j] = (AV)0;
-                    dense_clean = true;
-                }
-            } else {
-                for (int j = tid; j < (w1 - w) * (WIN / 32); j += HV_THREADS) s_hbm[j] = 0u;
-                dense_clean = false;
-            }
-            // (no barrier: the traversal below has barriers of its own before the first product arrives)
-            // products of windows [w, w1)
-            const int32_t col0 = w * WIN;
-            uint32_t staged = 0;   // products of this pass staged so far (sparse pass, uniform)
-            auto f = [&](const auto &cj, const auto &cv, uint32_t q0) {
-                constexpr int U = sizeof(cj) / sizeof(cj[0]);
-                if (dense) {
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const unsigned d = (unsigned)(cj[u] - col0);
-                        if (cj[u] >= 0 && d < (unsigned)WIN) {   // d is in range for a consistent window table
-                            lds_add(&s_vals[d], (AV)cv[u]);
-                            // Section 4.1: with many products per output entry most presence bits are set already;
-                            // reading the bit first then saves the write (a stale read only costs a redundant OR)
-                            const uint32_t bit = 1u << (d & 31);
-                            if (!QUERY || !(s_dbm[d >> 5] & bit)) atomicOr(&s_dbm[d >> 5], bit);
-                        }
-                    }
-                } else {
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const uint32_t at = staged + q0 + (uint32_t)u * WAVE + (uint32_t)(tid & (WAVE - 1));
-                        const uint32_t d = (uint32_t)(cj[u] - col0);
-                        if (cj[u] >= 0 && at < (uint32_t)scap && d < (uint32_t)hwords * 32u) {   // both hold by construction
-                            s_scol[at] = cj[u];
-                            s_sval[at] = (AV)cv[u];
-                            atomicOr(&s_hbm[d >> 5], 1u << (d & 31u));
-                        }
+            const uint32_t col0 = (uint32_t)w * HV_WIN;
+            const int run = w1 - w;
+            // opens the pieces of entries base .. base + HV_CHUNK - 1 in windows [from, to) of the stretch
+            auto open = [&](int64_t base, int from, int to, int &nent) {
+                const int64_t left = ne - base;
+                nent = left < HV_CHUNK ? (int)left : HV_CHUNK;
+                uint32_t lo = 0u, hi = 0u;
+                V a = V();
+                if (tid < nent) {
+                    if (base == 0) {
+                        a = ea;
+                        lo = from == w ? c_lo : t0[from];
+                        hi = to == w1 ? c_hi : t0[to];
+                    } else {
+                        const uint32_t *t = bw + (size_t)a_col[e0 + base + tid] * stride;
+                        a = a_val[e0 + base + tid];
+                        lo = t[from];
+                        hi = t[to];
                     }
                 }
+                return hv_open(s_ch, nent, lo, hi - lo, a);
             };
-            if (!dense && ne <= HV_THREADS) {
-                // ---- sparse pass of a row whose entries fit one chunk: no staging, every product stays in the
-                // registers of the thread that fetched it, from the sweep that marks the columns to the sweep
-                // that adds the values at their ranks
-                constexpr int NBATCH = HV_PPT / FLAT_U;
-                static_assert(HV_PPT % FLAT_U == 0, "whole batches");
-                int32_t kc[HV_PPT];
-                V kv[HV_PPT];
-                auto mark = [&](int32_t col) {
-                    const uint32_t d = (uint32_t)(col - col0);
-                    if (d < (uint32_t)hwords * 32u) atomicOr(&s_hbm[d >> 5], 1u << (d & 31u));   // holds by construction
-                };
-                bool fits;
-                wg_flat_chunk_keep<HV_THREADS, NBATCH>(s_fc, (int)ne, (int64_t)c_lo, c_hi - c_lo, ea, b_col, b_val, kc, kv,
-                                                       mark, fits, chunk_clean);
-                chunk_clean = true;
-                if (!fits && tid == 0) s_ovf = 1;   // cannot happen: passes are planned from the counts
-                const int wpt = (hwords + HV_THREADS - 1) / HV_THREADS;   // bitmap words per thread (consecutive)
-                int mine = 0;
-                for (int q = 0; q < wpt; ++q) {
-                    const int j = tid * wpt + q;
-                    if (j < hwords) mine += __popc(s_hbm[j]);
+            if (dense) {
+                if (!clean) {   // uniform
+                    lds_barrier();   // (the pass before may still be reading its columns there)
+                    for (int j = HV_CAP + tid; j < HV_WIN; j += HV_THREADS) s_vals[j] = -0.0;
+                    clean = true;
                 }
-                int htotal;
-                int run = block_exclusive_scan_i32<HV_THREADS, false>(mine, s_wave, htotal);   // (barrier below)
-                for (int q = 0; q < wpt; ++q) {
-                    const int j = tid * wpt + q;
-                    if (j < hwords) { s_hpre[j] = (uint16_t)run; run += __popc(s_hbm[j]); }
-                }
-                for (int i = tid; i < htotal; i += HV_THREADS) s_sval[i] = (AV)0;   // (htotal <= products <= scap)
-                __syncthreads();
+                for (int64_t base = 0; base < ne; base += HV_CHUNK) {
+                    int nent;
+                    if (base > 0) lds_barrier();
+                    const uint32_t total = open(base, w, w1, nent);
+                    HvTiles<V> tiles;
+                    if (total > 0u)
+                        hv_walk<true>(s_ch, nent, total, b_col, b_val, tiles, false, [&](const HvFour<V> (&f)[2], const HvTiles<V> &t) {
+                            const V a[2] = {row_lane<0>(t.a), row_lane<1>(t.a)};
 #pragma unroll
-                for (int i = 0; i < HV_PPT; ++i) {
-                    const uint32_t d = (uint32_t)(kc[i] - col0);
-                    if (kc[i] >= 0 && d < (uint32_t)hwords * 32u) {
-                        const int rank = (int)s_hpre[d >> 5] + __popc(s_hbm[d >> 5] & ((1u << (d & 31u)) - 1u));
-                        s_scol[rank] = kc[i];           // products of one column all write the same id
-                        lds_add(&s_sval[rank], (AV)kv[i]);
+                            for (int u = 0; u < 2; ++u) {
+                                if (f[u].skip >= 4) continue;
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) {
+                                    const uint32_t d = (uint32_t)f[u].col[i] - col0;
+                                    lds_add(&s_vals[i >= f[u].skip && d < (uint32_t)HV_WIN ? d : dump], hv_addend(a[u] * f[u].val[i]));   // (d holds for a consistent table)
+                                }
+                            }
+                        });
+                }
+                lds_barrier();
+                // ---- window -> output, in column order: thread t holds columns t, t + 1024, ...
+                constexpr int STEPS = HV_WIN / HV_THREADS;
+                double v[STEPS];
+#pragma unroll
+                for (int i = 0; i < STEPS; ++i) v[i] = s_vals[i * HV_THREADS + tid];
+                uint32_t count = 0u;   // lane i: entries of C among the wave's 64 columns of step i
+#pragma unroll
+                for (int i = 0; i < STEPS; ++i) {
+                    s_vals[i * HV_THREADS + tid] = -0.0;
+                    const uint32_t n = (uint32_t)__popcll(__ballot(hv_there(v[i])));
+                    count = lane == i ? n : count;
+                }
+                if (lane < STEPS) s_grp[lane * HV_WAVES + wave] = count;
+                lds_barrier();
+                // entries before each group of 64 columns: lane l has groups 4 l .. 4 l + 3
+                const uint4 g = reinterpret_cast<const uint4 *>(s_grp)[lane];
+                const uint32_t sum = g.x + g.y + g.z + g.w;
+                const uint32_t incl = wave_inclusive_scan_u32(sum);
+                const uint32_t all = wave_read_lane_u32(incl, WAVE - 1);
+                const int q = wave & 3;   // (group i * 16 + wave is number q of lane 4 i + wave / 4)
+                const uint32_t before = incl - sum + (q > 0 ? g.x : 0u) + (q > 1 ? g.y : 0u) + (q > 2 ? g.z : 0u);
+                const uint32_t room = cap - done < (long long)HV_WIN ? (cap > done ? (uint32_t)(cap - done) : 0u) : (uint32_t)HV_WIN;
+                int32_t *to_col = out_col + o + done;
+                V *to_val = out_val + o + done;
+#pragma unroll
+                for (int i = 0; i < STEPS; ++i) {
+                    const bool there = hv_there(v[i]);
+                    const unsigned long long all_there = __ballot(there);
+                    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(all_there >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all_there, 0u)) +
+                                          wave_read_lane_u32(before, 4 * i + (wave >> 2));
+                    if (there && rank < room) {
+                        __builtin_nontemporal_store((int32_t)(col0 + (uint32_t)(i * HV_THREADS + tid)), hv_at(to_col, rank));
+                        __builtin_nontemporal_store((V)v[i], hv_at(to_val, rank));
                     }
                 }
-                __syncthreads();
-                const long long room = cap - done;
-                const int n_out = (long long)htotal < room ? htotal : (room > 0 ? (int)room : 0);
-                for (int i = tid; i < n_out; i += HV_THREADS) {
-                    __builtin_nontemporal_store(s_scol[i], &out_col[o + done + i]);
-                    __builtin_nontemporal_store((V)s_sval[i], &out_val[o + done + i]);
-                }
-                done += htotal;
-                __syncthreads();
+                done += all;
             } else {
-                for (int64_t base = 0; base < ne; base += HV_THREADS) {
-                    int32_t k = ek;
-                    V a = ea;
-                    const bool have = base + tid < ne;
-                    if (base > 0 && have) { k = a_col[e0 + base + tid]; a = a_val[e0 + base + tid]; }
-                    uint32_t c0 = c_lo, c1 = c_hi;
-                    if (base > 0) {
-                        c0 = c1 = 0;
-                        if (have) {
-                            const uint32_t *t = bw + (size_t)k * stride;
-                            c0 = t[w];
-                            c1 = t[w1];
+                clean = false;
+                uint4 *map4 = reinterpret_cast<uint4 *>(s_map);
+                for (int j = tid; j < run * (HV_WIN / 128); j += HV_THREADS) map4[j] = make_uint4(0u, 0u, 0u, 0u);
+                const uint32_t cols = (uint32_t)run * HV_WIN;
+                auto mark = [&](const HvFour<V> (&f)[2], const HvTiles<V> &) {
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        if (f[u].skip >= 4) continue;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const uint32_t d = (uint32_t)f[u].col[i] - col0;
+                            atomicOr(&s_map[i >= f[u].skip && d < cols ? d >> 5 : map_dump], 1u << (d & 31u));
                         }
                     }
-                    const int64_t left = ne - base;
-                    staged += wg_flat_chunk<HV_THREADS, true>(s_fc, left < HV_THREADS ? (int)left : HV_THREADS, (int64_t)c0,
-                                                              c1 - c0, a, b_col, b_val, f);
-                    chunk_clean = false;
-                }
-                if (dense) {
-                    // ---- dense window -> output, in column order
-                    const uint32_t word = tid < WORDS ? s_dbm[tid] : 0u;
-                    int wtotal;
-                    const int ex = block_exclusive_scan_i32<HV_THREADS>(__popc(word), s_wave, wtotal);
-                    if (tid < WORDS) s_dpre[tid] = (uint32_t)ex;
-                    __syncthreads();
-                    // Thread t looks at columns t, t + 1024, ...: in every step the lanes of a wave read
-                    // consecutive values (no LDS bank conflicts) and the present ones among them go to
-                    // consecutive places of the output (coalesced stores).
-                    constexpr int STEPS = WIN / HV_THREADS;   // 16 (fp64) or 32 (fp32)
-    #pragma unroll 4
-                    for (int i = 0; i < STEPS; ++i) {
-                        const int j = i * HV_THREADS + tid;
-                        const uint32_t wbits = s_dbm[j >> 5];
-                        if ((wbits >> (j & 31)) & 1u) {
-                            const long long rank = done + (long long)s_dpre[j >> 5] + __popc(wbits & ((1u << (j & 31)) - 1u));
-                            const V val = (V)s_vals[j];
-                            s_vals[j] = (AV)0;
-                            if (rank < cap) { __builtin_nontemporal_store((int32_t)(col0 + j), &out_col[o + rank]); __builtin_nontemporal_store(val, &out_val[o + rank]); }
+                };
+                uint32_t skip = 0u;   // entries of the stretch before the pass's
+                auto add = [&](const HvFour<V> (&f)[2], const HvTiles<V> &t) {
+                    const V a[2] = {row_lane<0>(t.a), row_lane<1>(t.a)};
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        if (f[u].skip >= 4) continue;
+                        uint32_t word[4], pre[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const uint32_t d = (uint32_t)f[u].col[i] - col0;
+                            const uint32_t at = d < cols ? d >> 5 : 0u;
+                            word[i] = s_map[at];
+                            pre[i] = s_pre[at];
+                        }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const uint32_t d = (uint32_t)f[u].col[i] - col0;
+                            const uint32_t rank = (pre[i] + (uint32_t)__popc(word[i] & ((1u << (d & 31u)) - 1u)) - skip) & 0xffffu;
+                            const uint32_t at = i >= f[u].skip && d < cols && rank < (uint32_t)HV_CAP ? rank : rank_dump;   // (the last holds by construction)
+                            s_col[at] = f[u].col[i];   // products of one column all write the same id
+                            lds_add(&s_vals[at], (double)(V)(a[u] * f[u].val[i]));
                         }
                     }
-                    __syncthreads();
-                    if (tid < WORDS) s_dbm[tid] = 0u;
-                    done += wtotal;
-                    __syncthreads();
+                };
+                uint32_t upto = 0u;   // lane l: entries of the stretch up to window l (lanes from `run` on: all)
+                // ranks: entries of the stretch before every word of the bitmap (a wave per window, eight words per lane)
+                auto count = [&]() {
+                    uint4 x0 = make_uint4(0u, 0u, 0u, 0u), x1 = x0;
+                    if (wave < run) {
+                        x0 = map4[wave * (HV_WIN / 128) + lane * 2];
+                        x1 = map4[wave * (HV_WIN / 128) + lane * 2 + 1];
+                    }
+                    const uint32_t n0 = __popc(x0.x), n1 = n0 + __popc(x0.y), n2 = n1 + __popc(x0.z), n3 = n2 + __popc(x0.w),
+                                   n4 = n3 + __popc(x1.x), n5 = n4 + __popc(x1.y), n6 = n5 + __popc(x1.z), n7 = n6 + __popc(x1.w);
+                    const uint32_t incl = wave_inclusive_scan_u32(n7);
+                    if (lane == WAVE - 1) s_win[wave] = incl;
+                    lds_barrier();
+                    const uint32_t per_win = lane < HV_WAVES ? s_win[lane] : 0u;
+                    upto = wave_inclusive_scan_u32(per_win);
+                    if (wave < run) {
+                        const uint32_t b = wave_read_lane_u32(upto - per_win, wave) + incl - n7;
+                        auto two = [&](uint32_t lo, uint32_t hi) { return ((b + lo) & 0xffffu) | ((b + hi) << 16); };
+                        reinterpret_cast<uint4 *>(s_pre)[wave * WAVE + lane] = make_uint4(two(0u, n0), two(n1, n2), two(n3, n4), two(n5, n6));
+                    }
+                    lds_barrier();
+                };
+                // the pass's n entries to C
+                auto write = [&](uint32_t n) {
+                    const uint32_t room = cap - done < (long long)n ? (cap > done ? (uint32_t)(cap - done) : 0u) : n;
+                    int32_t *to_col = out_col + o + done;
+                    V *to_val = out_val + o + done;
+                    for (uint32_t i = (uint32_t)tid; i < n; i += HV_THREADS) {
+                        const double v = s_vals[i] + 0.0;
+                        s_vals[i] = -0.0;
+                        if (i < room) {
+                            __builtin_nontemporal_store(s_col[i], hv_at(to_col, i));
+                            __builtin_nontemporal_store((V)v, hv_at(to_val, i));
+                        }
+                    }
+                    done += n;
+                };
+                int nent;
+                uint32_t total = open(0, w, w1, nent);
+                if (ne <= HV_CHUNK && total <= (uint32_t)(HV_KEEP * HV_WAVES)) {   // uniform
+                    // ---- so few tiles that the products stay in registers from the marking to the adding up
+                    const uint32_t span = (total + HV_WAVES * HV_STEP - 1) / (HV_WAVES * HV_STEP) * HV_STEP;
+                    const uint32_t k0 = (uint32_t)wave * span, k1 = k0 + span < total ? k0 + span : total;
+                    HvFour<V> f[2];
+                    HvTiles<V> t;
+                    if (k0 < total) {   // uniform for the wave
+                        t.find(s_ch, nent, total, k0, k1);
+                        hv_load<0, true>(t, b_col, b_val, f[0]);
+                        hv_load<1, true>(t, b_col, b_val, f[1]);
+                        mark(f, t);
+                    } else {
+                        f[0] = f[1] = HvFour<V>{};
+                        t = HvTiles<V>{};
+                    }
+                    lds_barrier();
+                    count();
+                    if (k0 < total) add(f, t);
+                    lds_barrier();
+                    write(wave_read_lane_u32(upto, WAVE - 1));
                 } else {
-                    // ---- sparse pass: rank of every column = set bits below it in the bitmap of the stretch
-                    const int wpt = (hwords + HV_THREADS - 1) / HV_THREADS;   // bitmap words per thread (consecutive)
-                    int mine = 0;
-                    for (int q = 0; q < wpt; ++q) {
-                        const int j = tid * wpt + q;
-                        if (j < hwords) mine += __popc(s_hbm[j]);
-                    }
-                    int htotal;
-                    int run = block_exclusive_scan_i32<HV_THREADS, false>(mine, s_wave, htotal);   // (barrier below)
-                    for (int q = 0; q < wpt; ++q) {
-                        const int j = tid * wpt + q;
-                        if (j < hwords) { s_hpre[j] = (uint16_t)run; run += __popc(s_hbm[j]); }
-                    }
-                    __syncthreads();
-                    // every thread takes its share of the staged products into registers, with their ranks
-                    if (staged > (uint32_t)scap) staged = scap;   // cannot happen: passes are planned from the counts
-                    int32_t pc[HV_PPT];
-                    AV pv[HV_PPT];
-                    int pr[HV_PPT];
-    #pragma unroll
-                    for (int i = 0; i < HV_PPT; ++i) {
-                        const uint32_t at = (uint32_t)i * HV_THREADS + tid;
-                        pc[i] = -1; pv[i] = AV(); pr[i] = 0;
-                        if (at < staged) {
-                            pc[i] = s_scol[at];
-                            pv[i] = s_sval[at];
-                            s_sval[at] = (AV)0;   // (htotal <= staged: the values of the output start from zero)
-                            const uint32_t d = (uint32_t)(pc[i] - col0);
-                            pr[i] = (int)s_hpre[d >> 5] + __popc(s_hbm[d >> 5] & ((1u << (d & 31u)) - 1u));
+                    HvTiles<V> tiles{};
+                    for (int64_t base = 0; base < ne; base += HV_CHUNK) {
+                        if (base > 0) {
+                            lds_barrier();
+                            total = open(base, w, w1, nent);
                         }
+                        if (total > 0u) hv_walk<false>(s_ch, nent, total, b_col, b_val, tiles, false, mark);
                     }
-                    __syncthreads();
-                    // the staging memory becomes the output of the pass: columns and values by rank
-    #pragma unroll
-                    for (int i = 0; i < HV_PPT; ++i) {
-                        if (pc[i] >= 0) {
-                            s_scol[pr[i]] = pc[i];          // products of one column all write the same id
-                            lds_add(&s_sval[pr[i]], pv[i]);
+                    lds_barrier();
+                    count();
+                    // accumulate and write, as many windows at a time as have HV_CAP entries (all of them, as a rule)
+                    for (int g0 = 0; g0 < run;) {   // uniform
+                        const unsigned long long fit = __ballot(lane >= g0 && lane < run && upto - skip <= (uint32_t)HV_CAP) >> g0;
+                        int g1 = g0 + __ffsll((long long)~fit) - 1;
+                        g1 = g1 > g0 ? g1 : g0 + 1;   // (a window of the stretch fits by itself)
+                        const uint32_t n = wave_read_lane_u32(upto, g1 - 1) - skip;
+                        const bool whole = g0 == 0 && g1 == run;
+                        for (int64_t base = 0; base < ne; base += HV_CHUNK) {
+                            if (!whole || ne > HV_CHUNK) {   // (else the chunk is still open)
+                                lds_barrier();
+                                total = open(base, w + g0, w + g1, nent);
+                            }
+                            if (total > 0u) hv_walk<true>(s_ch, nent, total, b_col, b_val, tiles, whole && ne <= HV_CHUNK && total <= (uint32_t)HV_THREADS, add);
                         }
+                        lds_barrier();
+                        write(n < (uint32_t)HV_CAP ? n : (uint32_t)HV_CAP);
+                        skip += n;
+                        g0 = g1;
                     }
-                    __syncthreads();
-                    const long long room = cap - done;
-                    const int n_out = (long long)htotal < room ? htotal : (room > 0 ? (int)room : 0);
-                    for (int i = tid; i < n_out; i += HV_THREADS) {
-                        __builtin_nontemporal_store(s_scol[i], &out_col[o + done + i]);
-                        __builtin_nontemporal_store((V)s_sval[i], &out_val[o + done + i]);
-                    }
-                    done += htotal;
-                    __syncthreads();
                 }
             }
             c_lo = c_hi; c_hi = n_hi;
             w = nx0; w1 = nx1; dense = nxdense;
         }
-        if (tid == 0) row_nnz[row] = (s_ovf || done > cap) ? -1 : (int32_t)done;
-        __syncthreads();
+        for (int j = tid; j < n_win; j += HV_THREADS) s_pw[j] = 0u;   // (no wave plans behind a pass's barriers)
+        if (tid == 0) row_nnz[row] = done > cap ? -1 : (int32_t)done;
+        lds_barrier();
     }
 }
 
@@ -1334,7 +1532,7 @@ k_window_table(const int64_t *__restrict__ b_rp, const int32_t *__restrict__ b_c
 hipError_t launch_window_table(const Csr &B, int dtype, uint32_t *bw, int *n_win_out, int32_t *flags, hipStream_t s)
 {
     (void)dtype;
-    const int win_log2 = ilog2_const(HV_REGION / 8);   // (both value types accumulate in 8 bytes)
+    const int win_log2 = ilog2_const(HV_WIN);
     const int n_win = (int)((B.cols + (1ll << win_log2) - 1) >> win_log2);
     *n_win_out = n_win;
     if (B.rows == 0) return hipSuccess;
@@ -1353,7 +1551,7 @@ int heavy_workgroups_per_cu() { return HV_WG_PER_CU; }
 int dense_window_count(int64_t n_cols, int dtype)
 {
     (void)dtype;
-    const int win_log2 = ilog2_const(HV_REGION / 8);   // (both value types accumulate in 8 bytes)
+    const int win_log2 = ilog2_const(HV_WIN);
     return (int)((n_cols + (1ll << win_log2) - 1) >> win_log2);
 }
 
@@ -1566,11 +1764,8 @@ static hipError_t dispatch(const Csr &A, const Csr &B, const NumLaunch &l, int /
                                static_cast<uint2 *>(l.pairs), l.out_ptr, l.out_col, ov, l.row_nnz);
         break;
     case NB_GLOBAL:
-        if (l.bw != nullptr && l.query_bitmap)
-            hipLaunchKernelGGL((k_numeric_heavy<V, true>), dim3((unsigned)l.n_wg), dim3(HV_THREADS), 0, s, A.rp, A.col, av, l.bw,
-                               l.n_win, B.col, bv, l.rows, l.count, l.queue, l.out_ptr, l.out_col, ov, l.row_nnz);
-        else if (l.bw != nullptr)
-            hipLaunchKernelGGL((k_numeric_heavy<V, false>), dim3((unsigned)l.n_wg), dim3(HV_THREADS), 0, s, A.rp, A.col, av, l.bw,
+        if (l.bw != nullptr)
+            hipLaunchKernelGGL((k_numeric_heavy<V>), dim3((unsigned)l.n_wg), dim3(HV_THREADS), 0, s, A.rp, A.col, av, l.bw,
                                l.n_win, B.col, bv, l.rows, l.count, l.queue, l.out_ptr, l.out_col, ov, l.row_nnz);
         else
             hipLaunchKernelGGL((k_numeric_global<V>), dim3((unsigned)l.n_wg), dim3(GL_THREADS), 0, s, A.rp, A.col, av,

@@ -647,7 +647,6 @@ int run_numeric(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int gb_l
         } else if (b == NB_GLOBAL && c.bw != nullptr) {
             l.bw = c.bw;
             l.n_win = c.n_win;
-            l.query_bitmap = c.query_bitmap;
             const int64_t resident = (int64_t)c.n_cu * heavy_workgroups_per_cu();
             l.n_wg = (int)(l.count < resident ? l.count : resident);
             l.queue = &w.sc->queue[queue_base + 1];
@@ -1156,7 +1155,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     // needs the window boundaries inside every (sorted) row of B.  Built only when such rows can exist
     // and the table stays small; otherwise, or when a row of B turns out unsorted, they use global tables.
     uint32_t *bw_try = nullptr;
-    if (max_ub > kNumericSlots[NB_S8K] && B.nnz < 0xffffffffLL && !o.force_hash_kernels) {
+    if (max_ub > kNumericSlots[NB_S8K] && B.nnz < 0xffffffffLL && B.nnz >= HEAVY_MIN_ENTRIES && !o.force_hash_kernels) {
         const int nw = dense_window_count(n, dtype);
         const size_t bytes = (size_t)B.rows * ((size_t)nw + 1) * 4;
         if (nw <= 512 && bytes <= ((size_t)6 << 30)) {   // the heavy-row kernel plans at most 512 windows per row
@@ -1201,8 +1200,8 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     }
 
     // Section 4.1 / 4.3: dense accumulators query the bitmap before writing when the (sampled) CR is at least 2
-    // (measured on R-MAT, sampled CR 2.5: the dense windows of the numeric pass gain 2.8 %, the symbolic bitmap kernel,
-    // whose only LDS operation per product is that OR, loses 14 %: it queries only when told to, bitmap_query = 2)
+    // (the rows of a dense range; the symbolic bitmap kernel, whose only LDS operation per product is that OR, loses 14 %
+    // on R-MAT, sampled CR 2.5: it queries only when told to, bitmap_query = 2.  The dense windows of the heavy rows have no bits)
     c.query_bitmap = o.bitmap_query >= 1 || (o.bitmap_query < 0 && S->sampled_rows > 0 && S->sampled_cr >= o.bitmap_query_cr);
     const bool query_bitmap = o.bitmap_query == 2;
     Csr Bnum = B;   // what the numeric kernels read: B, or a copy of it with sorted rows (see below)

@@ -105,6 +105,15 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
+// A barrier of the workgroup that orders its LDS accesses and nothing else: loads from and stores to global memory stay
+// in flight across it (__syncthreads waits for all of them).
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 __device__ __forceinline__ uint32_t fmix32(uint32_t h)
 {
     h ^= h >> 16;
@@ -177,6 +186,13 @@ __device__ __forceinline__ uint32_t group_sum_u32(uint32_t v)
 __device__ __forceinline__ uint32_t wave_read_lane_u32(uint32_t v, int l)
 {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, __builtin_amdgcn_readfirstlane(l));
+}
+// The first lane's value, as a wave-uniform number.
+__device__ __forceinline__ long long wave_first(long long v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((unsigned long long)v >> 32));
+    return (long long)(((unsigned long long)hi << 32) | lo);
 }
 // Sum over the wave, in every lane.
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
@@ -368,12 +384,13 @@ struct NumLaunch {
     double coef;              // global: table slots per reserved output entry
     const uint32_t *bw;       // dense kernel: window boundary table of B, or null to use the global-table kernel
     int n_win;
-    bool query_bitmap;        // dense windows: read a column's presence bit before setting it (Section 4.1)
+    bool query_bitmap;        // dense-range bin: read a column's presence bit before setting it (Section 4.1)
     bool fine_buckets;        // 512- and 1024-slot bins: order the row through 2048 column buckets (clustered columns)
     const int32_t *cmin;      // dense-range bin: first column each row can reach
     int span_cols;            // dense-range bin: the rows' ranges are at most so many columns (kDspanCols or DS_MAX_COLS)
 };
 hipError_t launch_window_table(const Csr &B, int dtype, uint32_t *bw, int *n_win_out, int32_t *flags, hipStream_t s);
+constexpr int64_t HEAVY_MIN_ENTRIES = 8;   // of B: the column-window kernel reads four entries at a time, up to position 7 where a row ends among the first
 int heavy_workgroups_per_cu();   // workgroups of the column-window kernel that one compute unit holds
 int dense_window_count(int64_t n_cols, int dtype);
 hipError_t launch_numeric_bin(const Csr &A, const Csr &B, int dtype, const NumLaunch &l, int gb_log2, hipStream_t s);
