@@ -28,9 +28,11 @@ template <typename T>
 __device__ __forceinline__ void post(T *p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // A workgroup of 256 threads: places[u] = 1 + sum of (counts[v] - 1) over v < u, in the order in which the counts (0: not
-// there yet) arrive.  A turn looks at 1024 counts from the first that is missing on, a quarter per wave.  What bounds it is
-// the instructions of a wave that issues alone: one wave for all gave 380 to 430 places per us with the chip to itself (1024 in
-// 2.7 us; a post is seen by another compute unit after 0.35) and 150 beside the sort, too few for small rows.
+// there yet) arrive.  A turn looks at 256 counts from the first that is missing on, a quarter per wave.  What bounds the rows is not
+// how many places a turn gives but how long it takes, as it is in every row's way: turns of 1024 counts (2.7 us with the
+// chip to themselves, 6 beside the sort) were 1.268 ms instead of 1.240 for the rectangular input, 2.00 instead of 1.95 for the
+// clustered one, 278 us instead of 268 for the Laplacian of 1024^2 (whole calls).  Turns whose loads are on their way two, three
+// or four at a time see older counts: 1.266, 1.378 and 1.430 ms.
 struct Turn {
     int lead[2][4];              // counts of a wave's quarter that are there, by the parity of the turn
     unsigned int sum[2][4];      // entries among them that are new
@@ -38,53 +40,32 @@ struct Turn {
 __device__ __forceinline__ void place_units(const uint32_t *counts, unsigned long long *places, int64_t units,
                                             unsigned long long *total_out, int32_t *flags, int polls, Turn &turn)
 {
-    constexpr int U = 4, QUARTER = U * WAVE;
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
     __builtin_amdgcn_s_setprio(3);
-    uint32_t c[U];
     auto load = [&](int64_t from) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t i = from + wave * QUARTER + u * WAVE + lane;
-            c[u] = i < units ? peek(counts + i) : 0u;
-        }
+        const int64_t i = from + wave * WAVE + lane;
+        return i < units ? peek(counts + i) : 0u;
     };
     int64_t at = 0;                // units before this one have their places
     int64_t from = 0;              // the turn's first count, a multiple of the wave
     unsigned long long run = 0;
     int idle = 0;
-    load(0);
+    uint32_t c = load(0);
     for (int parity = 0; at < units; parity ^= 1) {
-        int lead = 0;
-        bool open = true;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const unsigned long long missing = __ballot(c[u] == 0u);
-            lead += !open ? 0 : missing == 0ull ? WAVE : __builtin_ctzll(missing);   // uniform
-            open = open && missing == 0ull;
-        }
-        const int old = (int)(at - from) - wave * QUARTER;   // counts of the quarter that had been there before
-        uint32_t n[U], upto[U];
-        unsigned int sum = 0;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = u * WAVE + lane;
-            n[u] = i >= old && i < lead ? c[u] - 1u : 0u;
-            upto[u] = wave_inclusive_scan_u32(n[u]);
-            const unsigned int all = wave_read_lane_u32(upto[u], WAVE - 1);
-            upto[u] += sum;
-            sum += all;
-        }
-        if (lane == 0) {
+        const unsigned long long missing = __ballot(c == 0u);
+        const int lead = missing == 0ull ? WAVE : __builtin_ctzll(missing);   // uniform
+        const int old = (int)(at - from) - wave * WAVE;   // counts of the quarter that had been there before
+        const uint32_t n = lane >= old && lane < lead ? c - 1u : 0u;
+        const uint32_t upto = wave_inclusive_scan_u32(n);
+        if (lane == WAVE - 1) {
             turn.lead[parity][wave] = lead;
-            turn.sum[parity][wave] = sum;
+            turn.sum[parity][wave] = upto;
         }
-        __syncthreads();
+        lds_barrier();
         int total_lead = 0;
         unsigned long long before = run, after = run;
-        bool mine = true;          // the quarters before this wave's are complete
-        open = true;
+        bool mine = true, open = true;   // the quarters before this wave's, and so far, are complete
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
             const int l = __builtin_amdgcn_readfirstlane(turn.lead[parity][w]);
@@ -93,22 +74,16 @@ __device__ __forceinline__ void place_units(const uint32_t *counts, unsigned lon
             after += open ? s : 0u;
             if (w < wave) {
                 before += s;
-                mine = mine && l == QUARTER;
+                mine = mine && l == WAVE;
             }
-            open = open && l == QUARTER;
+            open = open && l == WAVE;
         }
-        const int64_t first = from + wave * QUARTER;
+        const int64_t first = from + wave * WAVE;
         const int64_t next = from + total_lead;
         from = next & ~(int64_t)(WAVE - 1);
-        load(from);
+        c = load(from);
         if (next > at) {
-            if (mine) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int i = u * WAVE + lane;
-                    if (i >= old && i < lead) post(places + first + i, before + (unsigned long long)(upto[u] - n[u]) + 1ull);
-                }
-            }
+            if (mine && lane >= old && lane < lead) post(places + first + lane, before + (unsigned long long)(upto - n) + 1ull);
             at = next;
             run = after;
             idle = 0;
