@@ -40,7 +40,7 @@ k_placed_group(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
         if (lane < R) s_before[lane] = inc - v;
         if (lane == WAVE - 1) post(p.counts + unit, inc + 1u);
     }
-    c.template accumulate<true>(sr, sub);
+    c.template accumulate<true>(sr.acc, sub);
     if (first_wave) {
         const int64_t o = wait_for_place(p.places + unit, p.flags, p.unit_polls);
         if (lane == 0) s_place = o;
@@ -52,7 +52,7 @@ k_placed_group(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_c
         p.c_rp[row] = o;
         if (row == p.m - 1) p.c_rp[p.m] = o + c.n_out;
     }
-    c.write(sr, sub, o, live && o + c.n_out <= p.slots ? (int)c.n_out : 0, p.out_col, p.out_val);
+    c.write(sr.acc, sub, o, live && o + c.n_out <= p.slots ? (int)c.n_out : 0, p.out_col, p.out_val);
 }
 
 // What the four waves of a workgroup tell each other: no barrier, so that a wave can be anywhere in its own size of sort.
@@ -98,24 +98,169 @@ __device__ __forceinline__ int64_t place_row(FourRows &f, int wave, int64_t unit
     return o;
 }
 
-// sorted(c, sr, lane) for a row of pr products by a whole wave, c and sr of the row's own size.
-template <typename V, int MAX, typename Sorted>
-__device__ __forceinline__ void sort_by_size(char *lds, int64_t row, int pr, const int64_t *__restrict__ a_rp,
-                                             const int32_t *__restrict__ a_col, const V *__restrict__ a_val,
-                                             const int64_t *__restrict__ b_rp, const int32_t *__restrict__ b_col,
-                                             const V *__restrict__ b_val, Sorted sorted)
+// ---- rows whose products gather: most of them lie in a window of a few hundred columns.  These are added up in an accumulator
+// per column (-0: no product yet, and no addend is -0), and only the others are sorted, in a network of their own number; their
+// entries come before and behind the window's.  A row of 762 products of the clustered input, 105 of them outside: 2111 -> 1160 vector
+// instructions.  The call 2.22 -> 1.93 ms (with shorter placing turns and neighbouring units on one XCD); the rest is waiting: 1.43
+// ms where a row doesn't wait for its place, 1.02 with nothing behind the loads of the products.  Of a row's 18 us 8 are the chain
+// of loads before them, 5 the wait for the rows before.  Limits: below 6 products a lane the sort costs no more than the window; from
+// more than 24 (8-byte values: 12) on the values of a row need registers that the launch does not have.
+// Rows that do not gather pay for five lane reads and a median (rectangular input: within 0.5 %).
+template <typename V> constexpr bool gathers(int ppt) { return ppt >= 6 && ppt <= (sizeof(V) == 4 ? 24 : 12); }   // products per lane of the rows that are looked at
+struct Gathered {
+    int32_t base;                 // first column of the window
+    int width;                    // columns, a multiple of the wave
+    int rest;                     // products outside
+};
+// LDS of the products outside the window: their values, spread as SortRow::acc, and their columns.
+template <typename V>
+__device__ __forceinline__ int rest_places(int rest) { return rest + (rest >> 3) + 1; }
+
+// The window lies around the median column of five products, from rows of B all over the first two thirds of the row's products.  It
+// is none where fewer than three of them are in it, as with columns in no order.
+template <typename V, int PPT>
+__device__ __forceinline__ bool find_window(const SortedRow<V, WAVE, PPT, 64> &c, int bytes, Gathered &g)
+{
+    int32_t m[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) m[i] = (int32_t)((uint32_t)__builtin_amdgcn_readlane((int)c.key[PPT * 2 * i / 15], 13 * i) >> SortedRow<V, WAVE, PPT, 64>::LB);
+    int32_t s[5] = {m[0], m[1], m[2], m[3], m[4]};
+    auto order = [&](int i, int j) {
+        const int32_t lo = s[i] < s[j] ? s[i] : s[j], hi = s[i] < s[j] ? s[j] : s[i];
+        s[i] = lo;
+        s[j] = hi;
+    };
+    order(0, 1); order(3, 4); order(2, 4); order(2, 3); order(1, 4); order(0, 3); order(0, 2); order(1, 3); order(1, 2);
+    g.width = bytes >= 8 * 512 + 1024 ? 512 : 256;
+    const int32_t half = g.width / 2;
+    g.base = s[2] > half ? s[2] - half : 0;
+    int in = 0;
+#pragma unroll
+    for (int i = 0; i < 5; ++i) in += (uint32_t)(m[i] - g.base) < (uint32_t)g.width ? 1 : 0;
+    return in >= 3;
+}
+
+// The products of c (expanded into sr, bytes of LDS) parted into those of the window, added up, and the rest.  False, and nothing has
+// changed, where more than half of them lie outside or the row's LDS does not hold both parts.
+template <typename V, int PPT>
+__device__ __forceinline__ bool part_products(const SortedRow<V, WAVE, PPT, 64> &c, SortRow<V, WAVE, PPT, 64> &sr, int bytes, int lane, Gathered &g)
+{
+    using Row = SortedRow<V, WAVE, PPT, 64>;
+    constexpr uint32_t NO_COL = SR_PAD >> Row::LB;   // a pad's column, above all others
+    const uint32_t base = (uint32_t)g.base;
+    const uint32_t width = (uint32_t)g.width < NO_COL - base ? (uint32_t)g.width : NO_COL - base;
+    int in = 0;
+#pragma unroll
+    for (int u = 0; u < PPT; ++u) in += __popcll(__ballot((c.key[u] >> Row::LB) - base < width));
+    g.rest = (int)c.total - in;
+    if (2 * g.rest > (int)c.total || g.rest > 8 * WAVE ||
+        8 * g.width + (int)sizeof(V) * rest_places<V>(g.rest) + 4 * g.rest > bytes) return false;   // uniform
+    V val[PPT];
+#pragma unroll
+    for (int u = 0; u < PPT; ++u) {
+        const uint32_t q = (uint32_t)(u * WAVE + lane);
+        val[u] = sr.acc[q < c.total ? q : c.total];
+    }
+    wave_sync();
+    double *win = reinterpret_cast<double *>(&sr);
+    V *acc = reinterpret_cast<V *>(win + g.width);
+    uint32_t *cols = reinterpret_cast<uint32_t *>(acc + rest_places<V>(g.rest));
+    for (int i = lane; i < g.width; i += WAVE) win[i] = -0.0;
+    wave_sync();
+    int run = 0;
+#pragma unroll
+    for (int u = 0; u < PPT; ++u) {
+        const uint32_t col = c.key[u] >> Row::LB;
+        const uint32_t d = col - base;
+        const bool inside = d < width, other = !inside && col != NO_COL;
+        if (inside) __hip_atomic_fetch_add(&win[d], (double)val[u] + 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const unsigned long long others = __ballot(other);
+        if (other) {
+            const int at = run + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(others >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)others, 0u));
+            cols[at] = col;
+            acc[at] = val[u];
+        }
+        run += __popcll(others);
+    }
+    wave_sync();
+    return true;
+}
+
+// What part_products has left of a row, to its end: rest <= 64 * R.
+template <typename V, int R, typename Finish>
+__device__ __forceinline__ void finish_gathered(const Gathered &g, char *lds, int lane, int32_t *__restrict__ out_col,
+                                                V *__restrict__ out_val, Finish finish)
+{
+    using Row = SortedRow<V, WAVE, R, 64>;
+    using Lds = SortRow<V, WAVE, R, 64>;
+    const double *win = reinterpret_cast<const double *>(lds);
+    V *acc = reinterpret_cast<V *>(lds + 8 * g.width);
+    const uint32_t *cols = reinterpret_cast<const uint32_t *>(acc + rest_places<V>(g.rest));
+    Row c;
+    c.total = (uint32_t)g.rest;
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        const uint32_t q = (uint32_t)(u * WAVE + lane);
+        c.key[u] = q < c.total ? (cols[q] << Row::LB) | q : SR_PAD;
+    }
+    c.order(lane, lane);
+    uint32_t below = 0;   // entries of the rest before the window
+#pragma unroll
+    for (int u = 0; u < R; ++u) below += ((c.heads >> u) & 1u) && (c.key[u] >> Row::LB) < (uint32_t)g.base ? 1u : 0u;
+    below = wave_sum_u32(below);
+    auto there = [](double v) { return __double_as_longlong(v) != (long long)0x8000000000000000ull; };
+    int inside = 0;
+    for (int i = 0; i < g.width; i += WAVE) inside += __popcll(__ballot(there(win[i + lane])));
+    const int n_rest = (int)c.n_out;
+    finish(c.n_out + (uint32_t)inside, [&]() { c.template accumulate<true>(acc, lane); }, [&](int64_t o) {
+        for (int i = lane; i < n_rest; i += WAVE) out_val[o + i + (i >= (int)below ? inside : 0)] = acc[Lds::place(i)];
+        int64_t at = o + below;
+        for (int i = 0; i < g.width; i += WAVE) {
+            const double v = win[i + lane];
+            const unsigned long long m = __ballot(there(v));
+            if (there(v)) {
+                const int64_t to = at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                out_val[to] = (V)v;
+                out_col[to] = g.base + i + lane;
+            }
+            at += __popcll(m);
+        }
+        wave_sync();
+        c.columns(acc);
+        const int32_t *s_col = reinterpret_cast<const int32_t *>(acc);
+        for (int i = lane; i < n_rest; i += WAVE) out_col[o + i + (i >= (int)below ? inside : 0)] = s_col[Lds::place(i)];
+    });
+}
+
+// A row of pr products by a whole wave, in the size of sort that is the row's own.  finish(n_out, accumulate, write): the row's
+// entries are counted; accumulate() adds its values up, write(o) writes it from entry o of C on.
+template <typename V, int MAX, typename Finish>
+__device__ __forceinline__ void row_by_size(char *lds, int pr, int64_t e0, int ne,
+                                            const int32_t *__restrict__ a_col, const V *__restrict__ a_val,
+                                            const int64_t *__restrict__ b_rp, const int32_t *__restrict__ b_col,
+                                            const V *__restrict__ b_val, int32_t *__restrict__ out_col, V *__restrict__ out_val,
+                                            Finish finish)
 {
     const int lane = lane_id();
-    const int64_t e0 = a_rp[row];
-    const int ne = (int)(a_rp[row + 1] - e0);
+    Gathered g;
+    const int bytes = sort_row_bytes(pr, sizeof(V));
+    const bool parted = [&]() {
 #define OCEAN_PLACED(PPT)                                                                                        \
     if constexpr (PPT <= MAX)                                                                                    \
         if (pr <= 64 * PPT) {                                                                                    \
             SortRow<V, WAVE, PPT, 64> &sr = *reinterpret_cast<SortRow<V, WAVE, PPT, 64> *>(lds);                 \
             SortedRow<V, WAVE, PPT, 64> c;                                                                       \
-            c.template sort<true>(sr, lane, lane, e0, ne, a_col, a_val, b_rp, b_col, b_val);                                    \
-            sorted(c, sr, lane);                                                                                 \
-            return;                                                                                              \
+            bool window = false;                                                                                 \
+            if constexpr (!gathers<V>(PPT)) {                                                                    \
+                c.template sort<true>(sr, lane, lane, e0, ne, a_col, a_val, b_rp, b_col, b_val);                 \
+            } else {                                                                                             \
+                c.template expand<true>(sr, lane, lane, e0, ne, a_col, a_val, b_rp, b_col, b_val);               \
+                if (find_window<V, PPT>(c, bytes, g) && part_products<V, PPT>(c, sr, bytes, lane, g)) return true; \
+                c.order(lane, lane);                                                                             \
+            }                                                                                                    \
+            finish(c.n_out, [&]() { c.template accumulate<true>(sr.acc, lane); },                                \
+                   [&](int64_t o) { c.write(sr.acc, lane, o, (int)c.n_out, out_col, out_val); });                \
+            return false;                                                                                        \
         }
     OCEAN_PLACED(2)
     OCEAN_PLACED(3)
@@ -127,6 +272,17 @@ __device__ __forceinline__ void sort_by_size(char *lds, int64_t row, int pr, con
     OCEAN_PLACED(24)
     OCEAN_PLACED(32)
 #undef OCEAN_PLACED
+        return false;
+    }();
+    if (!parted) return;   // uniform
+#define OCEAN_REST(R) if (g.rest <= 64 * R) return finish_gathered<V, R>(g, lds, lane, out_col, out_val, finish)
+    OCEAN_REST(1);
+    OCEAN_REST(2);
+    OCEAN_REST(3);
+    OCEAN_REST(4);
+    OCEAN_REST(6);
+    OCEAN_REST(8);
+#undef OCEAN_REST
 }
 
 // Rows of at most 64 * MAX products, four neighbouring ones per workgroup and unit, a wave each; the sort's size is the row's
@@ -144,30 +300,47 @@ k_placed_wave(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_co
         place_units(p.counts, p.places, (p.m + 3) / 4, p.total, p.flags, p.placer_polls, *reinterpret_cast<Turn *>(s_pool));
         return;
     }
-    const int64_t unit = (int64_t)blockIdx.x - 1, row = unit * 4 + wave;
+    // Workgroups go to the eight XCDs in turn; of every 64 units, eight neighbours go to one, whose L2 then has the rows of B (and
+    // the lines of A and C) that they share: clustered input 1.96 -> 1.93 ms, rectangular 1.240 -> 1.222.  (A unit may so wait for some
+    // that are dispatched after it, all of these 64, which the chip holds at a time.)
+    int64_t unit = (int64_t)blockIdx.x - 1;
+    const int64_t base = unit & ~(int64_t)63;
+    if (base + 64 <= (p.m + 3) / 4) unit = base + (unit & 7) * 8 + ((unit >> 3) & 7);
+    const int64_t row = unit * 4 + wave;
     if (threadIdx.x == 0) {
         s_four.arrived = 0u;
         s_four.place = 0ull;
     }
     if (threadIdx.x < 4) s_four.n[threadIdx.x] = 0u;
-    int before = 0;   // LDS of the rows before this wave's
-    for (int64_t r = unit * 4; r < row; ++r) before += sort_row_bytes(r < p.m ? (int)prod[r] : 0, sizeof(V));
-    const int pr = row < p.m ? (int)prod[row] : 0;
+    const int64_t own = row < p.m ? row : p.m - 1;
+    const int64_t e0 = a_rp[own];
+    const int ne = (int)(a_rp[own + 1] - e0);
+    int before = 0, pr = 0;   // LDS of the rows before this wave's; its own row's products
+    int of[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) of[r] = (int)prod[unit * 4 + r < p.m ? unit * 4 + r : p.m - 1];   // (all four on their way together)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int n = unit * 4 + r < p.m ? of[r] : 0;
+        before += r < wave ? sort_row_bytes(n, sizeof(V)) : 0;
+        pr = r == wave ? n : pr;
+    }
     __syncthreads();
     if (row >= p.m) {
         publish_row(s_four, wave, 0u, p.counts + unit);
         return;
     }
-    sort_by_size<V, MAX>(s_pool + before, row, pr, a_rp, a_col, a_val, b_rp, b_col, b_val, [&](auto &c, auto &sr, int lane) {
-        publish_row(s_four, wave, c.n_out, p.counts + unit);
-        c.template accumulate<true>(sr, lane);
+    row_by_size<V, MAX>(s_pool + before, pr, e0, ne, a_col, a_val, b_rp, b_col, b_val, p.out_col, p.out_val,
+                        [&](uint32_t n_out, auto accumulate, auto write) {
+        publish_row(s_four, wave, n_out, p.counts + unit);
+        accumulate();
         const int64_t o = place_row(s_four, wave, unit, p);
         if (o < 0) return;
-        if (lane == 0) {
+        if (lane_id() == 0) {
             p.c_rp[row] = o;
-            if (row == p.m - 1) p.c_rp[p.m] = o + c.n_out;
+            if (row == p.m - 1) p.c_rp[p.m] = o + n_out;
         }
-        c.write(sr, lane, o, o + c.n_out <= p.slots ? (int)c.n_out : 0, p.out_col, p.out_val);
+        if (o + n_out <= p.slots) write(o);
     });
 }
 

@@ -195,11 +195,11 @@ k_numeric_sort_long(const int64_t *__restrict__ a_rp, const int32_t *__restrict_
     const int ne = live ? (int)(a_rp[row + 1] - e0) : 0;
     SortedRow<V, G, PPT, ENT> row_c;
     row_c.sort(sr, lane, sub, e0, ne, a_col, a_val, b_rp, b_col, b_val);
-    row_c.accumulate(sr, sub);
+    row_c.accumulate(sr.acc, sub);
     const int64_t o = live ? out_ptr[row] : 0;
     const int64_t cap = live ? out_ptr[row + 1] - o : 0;
     const bool fits = (int64_t)row_c.n_out <= cap;   // (a row that does not fit writes nothing)
-    row_c.write(sr, sub, o, fits ? (int)row_c.n_out : 0, out_col, out_val);
+    row_c.write(sr.acc, sub, o, fits ? (int)row_c.n_out : 0, out_col, out_val);
     if (live && sub == 0) row_nnz[row] = fits ? (int32_t)row_c.n_out : -1;
 }
 

@@ -223,7 +223,7 @@ struct SortedRow {
     static constexpr int CAP = G * PPT;
     static constexpr int LB = log2_of(CAP);
     static constexpr int MW = Lds::MW;
-    static constexpr int BATCH = PPT % 4 == 0 ? 4 : PPT % 3 == 0 ? 3 : PPT % 2 == 0 ? 2 : 1;
+    static constexpr int BATCH = PPT % 6 == 0 ? 6 : PPT % 4 == 0 ? 4 : PPT % 3 == 0 ? 3 : PPT % 2 == 0 ? 2 : 1;
     static_assert(64 % G == 0, "whole groups");
 
     uint32_t key[PPT];
@@ -238,6 +238,16 @@ struct SortedRow {
     __device__ __forceinline__ void sort(Lds &sr, int lane, int sub, int64_t e0, int ne, const int32_t *__restrict__ a_col,
                                          const V *__restrict__ a_val, const int64_t *__restrict__ b_rp,
                                          const int32_t *__restrict__ b_col, const V *__restrict__ b_val)
+    {
+        expand<CUT>(sr, lane, sub, e0, ne, a_col, a_val, b_rp, b_col, b_val);
+        order(lane, sub);
+    }
+
+    // The first half of it: the products, keys unsorted.
+    template <bool CUT>
+    __device__ __forceinline__ void expand(Lds &sr, int lane, int sub, int64_t e0, int ne, const int32_t *__restrict__ a_col,
+                                           const V *__restrict__ a_val, const int64_t *__restrict__ b_rp,
+                                           const int32_t *__restrict__ b_col, const V *__restrict__ b_val)
     {
         ne = ne < ENT ? ne : ENT;   // (holds: the caller lists no other rows)
         open(sr, sub);
@@ -258,7 +268,6 @@ struct SortedRow {
             add(sr, lane, sub, (uint32_t)p0, len, a, nseg);
         }
         products<CUT>(sr, sub, b_col, b_val);
-        order(lane, sub);
     }
 
     __device__ __forceinline__ void open(Lds &sr, int sub)
@@ -364,28 +373,28 @@ struct SortedRow {
         return Lds::place(rank0 + __popc(heads & (uint32_t)((2ull << u) - 1ull)));
     }
 
-    // The row's values into sr.acc, by rank: sums over the keys between a head and its tail, in 64 bits and in the order of
+    // The row's values into acc (that of its SortRow), by rank: sums over the keys between a head and its tail, in 64 bits and in the order of
     // the sort.  A lane's keys before its first head belong to an entry that a lane before has opened: what that lane and
     // those between hold of it comes by a prefix sum that starts anew behind every lane with a head.  (Adding up in LDS, an
     // 8-byte atomic for every key that is no head, took 8 bytes a product also for 4-byte values: 100 000 rows of 1444 and of
     // 2025 products fp32 653 -> 575 and 1085 -> 815 us now that a compute unit holds twice the rows; fp64, and smaller
     // classes, within 2 %.)
     template <bool CUT = false>
-    __device__ __forceinline__ void accumulate(Lds &sr, int sub)
+    __device__ __forceinline__ void accumulate(V *acc, int sub)
     {
         V val[PPT];
 #pragma unroll
         for (int u = 0; u < PPT; ++u) {
             const uint32_t q = key[u] & ((1u << LB) - 1u);
             // (a pad's number is the largest there is)
-            val[u] = sr.acc[CUT ? (q < total ? q : total) : CAP == 1 << LB || q < (uint32_t)CAP ? q : 0u];
+            val[u] = acc[CUT ? (q < total ? q : total) : CAP == 1 << LB || q < (uint32_t)CAP ? q : 0u];
         }
         wave_sync();
         double run = -0.0;
 #pragma unroll
         for (int u = 0; u < PPT; ++u) {
             run = (u == 0 || ((heads >> u) & 1u) ? -0.0 : run) + (double)val[u];
-            if ((tails >> u) & 1u) sr.acc[place(u)] = (V)run;
+            if ((tails >> u) & 1u) acc[place(u)] = (V)run;
         }
         const double carry = carried<G>(run, heads != 0u, sub);
         // the lane's first tail, where it closes an entry that a lane before has opened
@@ -393,21 +402,21 @@ struct SortedRow {
             const int t = __ffs((int)tails) - 1;
             const int at = Lds::place(rank0);
             if constexpr (sizeof(V) == sizeof(double)) {
-                sr.acc[at] = sr.acc[at] + carry;
+                acc[at] = acc[at] + carry;
             } else {   // (one rounding: the 64-bit sum again)
                 run = carry;
 #pragma unroll
                 for (int u = 0; u < PPT; ++u) run += u <= t ? (double)val[u] : -0.0;
-                sr.acc[at] = (V)run;
+                acc[at] = (V)run;
             }
         }
         wave_sync();
     }
 
-    // The row's columns into sr.acc, by rank, when its values are no longer needed there.
-    __device__ __forceinline__ void columns(Lds &sr)
+    // The row's columns into acc, by rank, when its values are no longer needed there.
+    __device__ __forceinline__ void columns(V *acc)
     {
-        int32_t *s_col = reinterpret_cast<int32_t *>(sr.acc);
+        int32_t *s_col = reinterpret_cast<int32_t *>(acc);
 #pragma unroll
         for (int u = 0; u < PPT; ++u)
             if ((heads >> u) & 1u) s_col[place(u)] = (int32_t)(key[u] >> LB);
@@ -415,13 +424,13 @@ struct SortedRow {
     }
 
     // The row to out_col / out_val from position o on.
-    __device__ __forceinline__ void write(Lds &sr, int sub, int64_t o, int n_write, int32_t *__restrict__ out_col,
+    __device__ __forceinline__ void write(V *acc, int sub, int64_t o, int n_write, int32_t *__restrict__ out_col,
                                           V *__restrict__ out_val)
     {
-        for (int i = sub; i < n_write; i += G) out_val[o + i] = sr.acc[Lds::place(i)];
+        for (int i = sub; i < n_write; i += G) out_val[o + i] = acc[Lds::place(i)];
         wave_sync();
-        columns(sr);
-        const int32_t *s_col = reinterpret_cast<const int32_t *>(sr.acc);
+        columns(acc);
+        const int32_t *s_col = reinterpret_cast<const int32_t *>(acc);
         for (int i = sub; i < n_write; i += G) out_col[o + i] = s_col[Lds::place(i)];
     }
 };
