@@ -8,7 +8,12 @@ fallback: if the library is missing or no GPU is present the calls raise.
 from __future__ import annotations
 
 import ctypes as C
+import functools
+import itertools
 import os
+import struct
+import weakref
+from contextlib import nullcontext
 from dataclasses import dataclass, field
 
 import numpy as np
@@ -62,17 +67,34 @@ class ocean_stats(C.Structure):
                 ("bin_nnz_c", C.c_int64 * MAX_BINS)]
 
     def as_dict(self) -> dict:
-        d = {k: getattr(self, k) for k in ("products", "max_row_products", "heavy_products", "nnz_c", "er", "avg_products", "sampled_cr",
-                                           "cr_mean", "cr_std", "assist_cr", "symbolic_overflow_rows", "compacted_in_place", "b_sorted_copy", "dense_range_rows",
-                                           "hll_registers", "sampled_rows", "fell_back", "overflow_rows", "temp_slots",
-                                           "peak_bytes", "total_ms")}
-        d["workflow"] = WORKFLOW_NAMES.get(self.workflow, str(self.workflow))
-        d["rows_per_bin"] = list(self.rows_per_bin)
-        d["symbolic_rows_per_bin"] = list(self.symbolic_rows_per_bin)
-        for k in ("bin_ms", "bin_products", "bin_nnz_a", "bin_nnz_c"):
-            d[k] = list(getattr(self, k))
-        d["stage_ms"] = {n: float(self.stage_ms[i]) for i, n in enumerate(STAGES)}
+        # (one unpack of the whole struct: 2 us instead of 9 for getattr by getattr, which every call pays)
+        x = _STATS.unpack_from(self)
+        d = {k: x[_STATS_AT[k]] for k in ("products", "max_row_products", "heavy_products", "nnz_c", "er", "avg_products", "sampled_cr",
+                                          "cr_mean", "cr_std", "assist_cr", "symbolic_overflow_rows", "compacted_in_place", "b_sorted_copy", "dense_range_rows",
+                                          "hll_registers", "sampled_rows", "fell_back", "overflow_rows", "temp_slots",
+                                          "peak_bytes", "total_ms")}
+        workflow = x[_STATS_AT["workflow"]]
+        d["workflow"] = WORKFLOW_NAMES.get(workflow, str(workflow))
+        for k in ("rows_per_bin", "symbolic_rows_per_bin", "bin_ms", "bin_products", "bin_nnz_a", "bin_nnz_c"):
+            d[k] = list(x[_STATS_AT[k]])
+        d["stage_ms"] = dict(zip(STAGES, x[_STATS_AT["stage_ms"]]))
         return d
+
+
+def _layout(cls):
+    """struct format of a ctypes Structure of numbers and arrays of numbers, and where every field is in the unpacked tuple."""
+    codes = {C.c_int64: "q", C.c_int32: "i", C.c_double: "d", C.c_float: "f"}
+    fmt, at, i = "@", {}, 0
+    for name, kind in cls._fields_:
+        count = getattr(kind, "_length_", 0)
+        fmt += f"{count or 1}{codes[kind._type_ if count else kind]}"
+        at[name] = slice(i, i + count) if count else i
+        i += count or 1
+    assert struct.calcsize(fmt) <= C.sizeof(cls)
+    return struct.Struct(fmt), at
+
+
+_STATS, _STATS_AT = _layout(ocean_stats)
 
 
 class OceanError(RuntimeError):
@@ -177,11 +199,23 @@ def bin_layout():
 
 
 # ---------------------------------------------------------------- device side
+_gpu_seen = False
+
+
 def _torch():
+    global _gpu_seen
     import torch
-    if not torch.cuda.is_available():
-        raise RuntimeError("no GPU visible: the Ocean SpGEMM path has no CPU fallback")
+    if not _gpu_seen:
+        if not torch.cuda.is_available():
+            raise RuntimeError("no GPU visible: the Ocean SpGEMM path has no CPU fallback")
+        _gpu_seen = True
     return torch
+
+
+def _on(device):
+    """Context in which `device` is the current one: none where it is already."""
+    torch = _torch()
+    return nullcontext() if device.index == torch.cuda.current_device() else torch.cuda.device(device)
 
 
 @dataclass
@@ -212,29 +246,57 @@ def to_device(m, device="cuda:0") -> DeviceCSR:
                      torch.from_numpy(m.val).to(device))
 
 
+_allocators = weakref.WeakValueDictionary()   # by the ctx that their struct carries
+_allocator_ids = itertools.count(1)
+
+
+def _alloc(ctx, nbytes, out):
+    a = _allocators.get(ctx)
+    return 1 if a is None else a.alloc(nbytes, out)
+
+
+def _release(ctx, ptr):
+    a = _allocators.get(ctx)
+    if a is not None:
+        a.release(ptr)
+
+
 class TorchAllocator:
-    """ocean_allocator whose memory comes from torch's caching allocator."""
+    """ocean_allocator whose memory comes from torch's caching allocator, one for every call.  The C callbacks of its struct are
+    shared by all and find theirs by ctx: a pair of callbacks of its own takes 22 us to make."""
+
+    _shared = (ALLOC_FN(_alloc), RELEASE_FN(_release))
 
     def __init__(self, device):
         torch = _torch()
         self.device = device
         self.blocks: dict[int, object] = {}
+        self._empty, self._uint8 = torch.empty, torch.uint8
+        ctx = next(_allocator_ids)
+        _allocators[ctx] = self
+        self.struct = ocean_allocator(ctx, *self._shared)
 
-        def _alloc(_ctx, nbytes, out):
-            try:
-                t = torch.empty(max(int(nbytes), 1), dtype=torch.uint8, device=self.device)
-            except Exception:   # out of memory -> the library reports OCEAN_EALLOC
-                return 1
-            self.blocks[t.data_ptr()] = t
-            out[0] = t.data_ptr()
-            return 0
+    def alloc(self, nbytes, out):
+        try:
+            t = self._empty(max(int(nbytes), 1), dtype=self._uint8, device=self.device)
+        except Exception:   # out of memory -> the library reports OCEAN_EALLOC
+            return 1
+        ptr = t.data_ptr()
+        self.blocks[ptr] = t
+        out[0] = ptr
+        return 0
 
-        def _release(_ctx, ptr):
-            self.blocks.pop(int(ptr), None)
+    def release(self, ptr):
+        self.blocks.pop(int(ptr), None)
 
-        self._alloc_cb = ALLOC_FN(_alloc)
-        self._release_cb = RELEASE_FN(_release)
-        self.struct = ocean_allocator(None, self._alloc_cb, self._release_cb)
+    @functools.cached_property
+    def _alloc_cb(self):
+        """C callbacks of this allocator whatever ctx they are given, for a struct put together elsewhere."""
+        return ALLOC_FN(lambda _ctx, nbytes, out: self.alloc(nbytes, out))
+
+    @functools.cached_property
+    def _release_cb(self):
+        return RELEASE_FN(lambda _ctx, ptr: self.release(ptr))
 
     def take(self, ptr: int):
         """Detach the tensor behind a pointer the library handed to the caller."""
@@ -255,7 +317,7 @@ def spgemm(A: DeviceCSR, B: DeviceCSR, opt: ocean_options | None = None, stream=
     alloc = TorchAllocator(A.row_ptr.device)
     o.allocator = C.pointer(alloc.struct)
     a, b, c, st = A.c_struct(), B.c_struct(), ocean_csr(), ocean_stats()
-    with torch.cuda.device(A.row_ptr.device):
+    with _on(A.row_ptr.device):
         rc = lib.ocean_spgemm(C.byref(a), C.byref(b), C.byref(c), C.byref(o), C.byref(st), _stream_ptr(stream))
     o.allocator = None
     _check(rc)
@@ -282,7 +344,7 @@ def row_products(A: DeviceCSR, B: DeviceCSR, stream=None):
     prod = torch.empty(A.rows, dtype=torch.int64, device=A.row_ptr.device)
     tot, mx = C.c_int64(), C.c_int64()
     a, b = A.c_struct(), B.c_struct()
-    with torch.cuda.device(A.row_ptr.device):
+    with _on(A.row_ptr.device):
         _check(load().ocean_row_products(C.byref(a), C.byref(b), prod.data_ptr(), C.byref(tot), C.byref(mx),
                                          _stream_ptr(stream)))
     return prod, tot.value, mx.value
@@ -307,7 +369,7 @@ def row_products_noalloc(A: DeviceCSR, B: DeviceCSR, prod, totals, stream=None):
     device tensors of the caller; the call only enqueues work on the stream."""
     torch = _torch()
     a, b = A.c_struct(), B.c_struct()
-    with torch.cuda.device(A.row_ptr.device):
+    with _on(A.row_ptr.device):
         _check(load().ocean_row_products_noalloc(C.byref(a), C.byref(b), prod.data_ptr(), totals.data_ptr(),
                                                  _stream_ptr(stream)))
 
@@ -316,7 +378,7 @@ def hll_sketch_rows(B: DeviceCSR, m: int, stream=None):
     torch = _torch()
     out = torch.empty((B.rows, m), dtype=torch.uint8, device=B.row_ptr.device)
     b = B.c_struct()
-    with torch.cuda.device(B.row_ptr.device):
+    with _on(B.row_ptr.device):
         _check(load().ocean_hll_sketch_rows(C.byref(b), m, out.data_ptr(), _stream_ptr(stream)))
     return out
 
@@ -330,7 +392,7 @@ def hll_merge_estimate(A: DeviceCSR, sketches, m: int, rows=None, prod=None, B: 
     est = torch.empty(n_rows, dtype=torch.float64, device=dev)
     merged = torch.empty((n_rows, m), dtype=torch.uint8, device=dev) if want_merged else None
     a = A.c_struct()
-    with torch.cuda.device(dev):
+    with _on(dev):
         _check(load().ocean_hll_merge_estimate(
             C.byref(a), sketches.data_ptr(), m, rows.data_ptr() if rows is not None else None, n_rows,
             prod.data_ptr() if prod is not None else None, B.row_ptr.data_ptr() if B is not None else None,
@@ -348,7 +410,7 @@ def symbolic(A: DeviceCSR, B: DeviceCSR, opt: ocean_options | None = None, strea
     o.allocator = C.pointer(alloc.struct)
     st = ocean_stats()
     a, b = A.c_struct(), B.c_struct()
-    with torch.cuda.device(A.row_ptr.device):
+    with _on(A.row_ptr.device):
         rc = load().ocean_symbolic(C.byref(a), C.byref(b), out.data_ptr(), C.byref(o), C.byref(st), _stream_ptr(stream))
     o.allocator = None
     _check(rc)

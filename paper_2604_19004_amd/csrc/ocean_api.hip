@@ -1045,6 +1045,7 @@ int run_placed(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, const Pla
             HIP_TRY(launch_row_stats(m, workflow == OCEAN_WF_UPPER_BOUND ? 0 : 2, fixed_bin, o.exact_load_coef, o.bound_load_coef, B.cols, w.prod,
                                      A.rp, c_rp, w.sc->bin_count, w.sc->bin_prod, w.sc->bin_work, c.s));
         }
+        OC_TRY(mark(c, -1));   // (here, so that nothing is left to wait for behind the read-back)
         OC_TRY(fetch_scalars(c, w.sc));
         nnz_c = (int64_t)c.h->totals[0];
         if ((c.h->flags & 32) == 0 && nnz_c <= slots) break;
@@ -1059,13 +1060,14 @@ int run_placed(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, const Pla
         int32_t *t_col = static_cast<int32_t *>(c.alloc((size_t)nnz_c * 4));
         void *t_val = t_col ? c.alloc((size_t)nnz_c * vbytes) : nullptr;
         if (t_val) {
+            OC_TRY(mark(c, OCEAN_ST_COMPACT));
             HIP_TRY(launch_trim(dtype, col, val, nnz_c, t_col, t_val, c.s));
+            OC_TRY(mark(c, -1));
+            HIP_TRY(hipStreamSynchronize(c.s));
             col = t_col;
             val = t_val;
         }
     }
-    OC_TRY(mark(c, -1));
-    HIP_TRY(hipStreamSynchronize(c.s));
     if (st) {
         int most = 0;
         for (int b = 0; b < OCEAN_MAX_BINS; ++b) {
