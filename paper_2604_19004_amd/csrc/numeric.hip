@@ -22,6 +22,7 @@
 // by the caller with bound-sized tables (Section 3.2, overflow handling).
 #include "ocean_internal.hpp"
 #include "placed.hpp"
+#include "tiles.hpp"
 #include "traverse.hpp"
 
 namespace ocean {
@@ -931,174 +932,6 @@ constexpr int HV_AT_MAP = HV_AT_PRE + HV_RUN * (HV_WIN / 32) * 2;
 constexpr int HV_REGION = HV_AT_MAP + HV_RUN * (HV_WIN / 8) + WAVE * 4;
 static_assert(HV_REGION >= (HV_WIN + WAVE) * 8 && HV_AT_PRE % 16 == 0 && HV_AT_MAP % 16 == 0, "a dense pass takes the region from its start");
 
-// Pieces of rows of B (position, entries, A's value) of up to HV_CHUNK entries of A, and the tiles of 64 products before each.
-template <typename V>
-struct HvChunk {
-    uint32_t first[HV_CHUNK], pos[HV_CHUNK], len[HV_CHUNK];
-    V a[HV_CHUNK];
-    uint32_t wsum[HV_CHUNK / WAVE];
-    uint32_t total;
-};
-
-// The pieces that the first nent threads hold (len = 0 in all others) into c; returns their tiles.  Every thread calls
-// it; c must be free on entry, and is ready behind the barrier that this ends with.
-template <typename V>
-__device__ __forceinline__ uint32_t hv_open(HvChunk<V> &c, int nent, uint32_t p, uint32_t len, V a)
-{
-    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
-    const uint32_t tiles = (len + (WAVE - 1)) / WAVE;
-    if (nent <= WAVE) {   // uniform
-        if (tid < WAVE) {
-            const uint32_t incl = wave_inclusive_scan_u32(tiles);
-            c.first[tid] = incl - tiles;
-            c.pos[tid] = p;
-            c.len[tid] = len;
-            c.a[tid] = a;
-            if (lane == WAVE - 1) c.total = incl;
-        }
-        lds_barrier();
-        return (uint32_t)__builtin_amdgcn_readfirstlane((int)c.total);
-    }
-    uint32_t incl = 0;
-    if (tid < HV_CHUNK) {
-        incl = wave_inclusive_scan_u32(tiles);
-        if (lane == WAVE - 1) c.wsum[tid / WAVE] = incl;
-    }
-    lds_barrier();
-    uint32_t total;
-    const uint32_t before = waves_before_u32<HV_CHUNK / WAVE>(c.wsum, tid < HV_CHUNK ? tid / WAVE : 0, total);
-    if (tid < HV_CHUNK) {
-        c.first[tid] = before + incl - tiles;
-        c.pos[tid] = p;
-        c.len[tid] = len;
-        c.a[tid] = a;
-    }
-    lds_barrier();
-    return total;
-}
-
-// v of lane J of every row of 16 lanes, in all of them.
-template <int J>
-__device__ __forceinline__ uint32_t row_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x150 + J, 0xf, 0xf, false); }   // row_newbcast
-template <int J>
-__device__ __forceinline__ float row_lane(float v) { return __uint_as_float(row_lane<J>(__float_as_uint(v))); }
-template <int J>
-__device__ __forceinline__ double row_lane(double v)
-{
-    const unsigned long long x = (unsigned long long)__double_as_longlong(v);
-    return __longlong_as_double((long long)(((unsigned long long)row_lane<J>((uint32_t)(x >> 32)) << 32) | row_lane<J>((uint32_t)x)));
-}
-// Every row of 16 lanes moved down by J lanes.
-template <int J>
-__device__ __forceinline__ uint32_t row_down(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x100 + J, 0xf, 0xf, false); }   // row_shl
-template <int J>
-__device__ __forceinline__ float row_down(float v) { return __uint_as_float(row_down<J>(__float_as_uint(v))); }
-template <int J>
-__device__ __forceinline__ double row_down(double v)
-{
-    const unsigned long long x = (unsigned long long)__double_as_longlong(v);
-    return __longlong_as_double((long long)(((unsigned long long)row_down<J>((uint32_t)(x >> 32)) << 32) | row_down<J>((uint32_t)x)));
-}
-
-// A tile per lane: 64 products of a piece, or fewer at its end (n).  A row of 16 lanes walks a tile, four products a lane, so a
-// wave walks four tiles in a step; step j's are with lanes j, 16 + j, 32 + j and 48 + j.
-constexpr int HV_ROW = 16, HV_STEP = WAVE / HV_ROW;
-template <typename V>
-struct HvTiles {
-    uint32_t p;
-    int32_t n;    // 0: no tile (with p = 4, so that four entries before p are there to be read)
-    V a;
-    bool edge;    // (uniform) a tile ends among B's first three entries
-
-    // tiles from..to-1 of the chunk (to - from <= 64, to <= total)
-    __device__ __forceinline__ void find(const HvChunk<V> &c, int nent, uint32_t total, uint32_t from, uint32_t to)
-    {
-        const uint32_t mine = from + (uint32_t)(lane_id() % HV_ROW * HV_STEP + lane_id() / HV_ROW);
-        const uint32_t t = mine < total ? mine : total - 1u;
-        int e = 0;   // the last piece that starts at or before tile t (pieces without products start where the next one does)
-        for (int step = nent > 1 ? 1 << (31 - __clz(nent - 1)) : 0; step > 0; step >>= 1)
-            if (c.first[e + step] <= t) e += step;
-        const uint32_t off = (t - c.first[e]) * WAVE;
-        const uint32_t left = c.len[e] - off;
-        p = mine < to ? c.pos[e] + off : 4u;
-        n = mine < to ? (int32_t)(left < WAVE ? left : (uint32_t)WAVE) : 0;
-        a = c.a[e];
-        edge = __ballot(p + (uint32_t)n < 4u) != 0ull;
-    }
-    // step J from now on is the first
-    template <int J>
-    __device__ __forceinline__ void advance()
-    {
-        p = row_down<J>(p);
-        n = (int32_t)row_down<J>((uint32_t)n);
-        a = row_down<J>(a);
-    }
-};
-
-// A lane's four entries of B in a step.  They are its four of the tile, or the tile's last four where those would
-// reach beyond its end: the first `skip` of them are then another lane's (all four: the lane has none).
-template <typename V>
-struct HvFour {
-    int32_t col[4];
-    V val[4];
-    int32_t skip;
-};
-struct alignas(4) HvCols { int32_t v[4]; };
-template <typename V> struct alignas(sizeof(V)) HvVals { V v[4]; };
-
-template <int J, bool VALS, typename V>
-__device__ __forceinline__ void hv_load(const HvTiles<V> &t, const int32_t *__restrict__ b_col, const V *__restrict__ b_val, HvFour<V> &f)
-{
-    const int32_t sub = 4 * (lane_id() % HV_ROW);
-    const uint32_t p = row_lane<J>(t.p);
-    const int32_t n = (int32_t)row_lane<J>((uint32_t)t.n);
-    int32_t at = sub < n - 4 ? sub : n - 4;
-    const int32_t least = -(int32_t)(p < 4u ? p : 4u);
-    at = at > least ? at : least;   // (a tile that ends among B's first three entries)
-    f.skip = sub - at;
-    const size_t q = (size_t)(p + (uint32_t)at);
-    const HvCols c = *reinterpret_cast<const HvCols *>(b_col + q);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) f.col[i] = c.v[i];
-    if constexpr (VALS) {
-        const HvVals<V> v = *reinterpret_cast<const HvVals<V> *>(b_val + q);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) f.val[i] = v.v[i];
-    }
-    if (t.edge) {   // uniform
-#pragma unroll
-        for (int i = 0; i < 4; ++i) f.col[i] = at + i < n ? f.col[i] : -1;
-    }
-}
-
-// Every product of the open chunk once: use(fours, t) for the lane's part of two steps at a time, t's first two, the tiles dealt out evenly to the waves.
-// mine: the wave's tiles (its first 64) where `found` says so, and on return where there are no more.
-template <bool VALS, typename V, typename F>
-__device__ __forceinline__ void hv_walk(const HvChunk<V> &c, int nent, uint32_t total, const int32_t *__restrict__ b_col,
-                                        const V *__restrict__ b_val, HvTiles<V> &mine, bool found, F use)
-{
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE);
-    const uint32_t span = (total + HV_WAVES * HV_STEP - 1) / (HV_WAVES * HV_STEP) * HV_STEP;
-    const uint32_t t0 = wave * span, t1 = t0 + span < total ? t0 + span : total;
-    for (uint32_t from = t0; from < t1; from += WAVE) {   // uniform for the wave
-        if (!found || from > t0) mine.find(c, nent, total, from, t1);
-        HvTiles<V> t = mine;
-        int left = (int)(t1 - from < WAVE ? t1 - from : WAVE);   // tiles
-        HvFour<V> f[2], g[2];
-        hv_load<0, VALS>(t, b_col, b_val, f[0]);
-        hv_load<1, VALS>(t, b_col, b_val, f[1]);
-        for (; left > 2 * HV_STEP; left -= 2 * HV_STEP) {   // (the next two steps are on their way while these are used)
-            hv_load<2, VALS>(t, b_col, b_val, g[0]);
-            hv_load<3, VALS>(t, b_col, b_val, g[1]);
-            use(f, t);
-            t.template advance<2>();
-            f[0] = g[0];
-            f[1] = g[1];
-        }
-        use(f, t);
-    }
-}
-
 // x, as a number that the compiler doesn't know: what is computed from it stays inside the loop that it is taken in,
 // instead of a register of its own through all of it.
 __device__ __forceinline__ int hv_hide(int x)
@@ -1132,7 +965,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                 V *__restrict__ out_val, int32_t *__restrict__ row_nnz)
 {
     __shared__ __align__(16) unsigned char s_u[HV_REGION];
-    __shared__ HvChunk<V> s_ch;
+    __shared__ TileChunk<V, uint32_t, HV_CHUNK> s_ch;
     __shared__ uint32_t s_pw[HV_MAXWIN];                  // products of the row per window
     __shared__ __align__(16) uint32_t s_grp[HV_WIN / WAVE];   // dense pass: entries of C per 64 columns
     __shared__ uint32_t s_win[HV_WAVES];                  // ranked pass: entries of C per window
@@ -1148,7 +981,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
     for (int w = threadIdx.x; w < HV_MAXWIN; w += HV_THREADS) s_pw[w] = 0u;
     if (threadIdx.x == 0) s_row = (long long)atomicAdd(queue, 1ull);
     bool clean = true;   // every accumulator of the dense window is -0; the first HV_CAP always are between passes
-    lds_barrier();
+    __syncthreads();
 
     for (;;) {
         const int tid = hv_hide((int)threadIdx.x), lane = tid & (WAVE - 1);
@@ -1200,7 +1033,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                     if (d[i]) atomicAdd(&s_pw[pw[i]], d[i]);
             }
         }
-        lds_barrier();
+        __syncthreads();
         if (tid == 0) s_row = (long long)drawn;   // (read by all before that barrier; the next row's behind one more)
 
         // ---- walk the windows, pass by pass.  Next pass from window `from` on: p0 == n_win when nothing is left.
@@ -1226,7 +1059,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
         int w, w1;
         bool dense;
         plan(0, w, w1, dense);
-        if (w == n_win) lds_barrier();   // (nothing at all: the counts are cleared below)
+        if (w == n_win) __syncthreads();   // (nothing at all: the counts are cleared below)
         // window boundaries of this thread's entry: those of the next pass are fetched one pass ahead
         const bool have0 = tid < nent0;
         const uint32_t *t0 = bw + (size_t)ek * stride;
@@ -1257,21 +1090,21 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                         hi = t[to];
                     }
                 }
-                return hv_open(s_ch, nent, lo, hi - lo, a);
+                return tile_open<HV_THREADS>(s_ch, nent, lo, hi - lo, a);
             };
             if (dense) {
                 if (!clean) {   // uniform
-                    lds_barrier();   // (the pass before may still be reading its columns there)
+                    __syncthreads();   // (the pass before may still be reading its columns there)
                     for (int j = HV_CAP + tid; j < HV_WIN; j += HV_THREADS) s_vals[j] = -0.0;
                     clean = true;
                 }
                 for (int64_t base = 0; base < ne; base += HV_CHUNK) {
                     int nent;
-                    if (base > 0) lds_barrier();
+                    if (base > 0) __syncthreads();
                     const uint32_t total = open(base, w, w1, nent);
-                    HvTiles<V> tiles;
+                    Tiles<V, uint32_t> tiles;
                     if (total > 0u)
-                        hv_walk<true>(s_ch, nent, total, b_col, b_val, tiles, false, [&](const HvFour<V> (&f)[2], const HvTiles<V> &t) {
+                        tile_walk<HV_THREADS, 2, true>(s_ch, nent, total, b_col, b_val, tiles, false, [&](const TileFour<V> (&f)[2], const Tiles<V, uint32_t> &t) {
                             const V a[2] = {row_lane<0>(t.a), row_lane<1>(t.a)};
 #pragma unroll
                             for (int u = 0; u < 2; ++u) {
@@ -1284,7 +1117,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                             }
                         });
                 }
-                lds_barrier();
+                __syncthreads();
                 // ---- window -> output, in column order: thread t holds columns t, t + 1024, ...
                 constexpr int STEPS = HV_WIN / HV_THREADS;
                 double v[STEPS];
@@ -1298,7 +1131,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                     count = lane == i ? n : count;
                 }
                 if (lane < STEPS) s_grp[lane * HV_WAVES + wave] = count;
-                lds_barrier();
+                __syncthreads();
                 // entries before each group of 64 columns: lane l has groups 4 l .. 4 l + 3
                 const uint4 g = reinterpret_cast<const uint4 *>(s_grp)[lane];
                 const uint32_t sum = g.x + g.y + g.z + g.w;
@@ -1326,7 +1159,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                 uint4 *map4 = reinterpret_cast<uint4 *>(s_map);
                 for (int j = tid; j < run * (HV_WIN / 128); j += HV_THREADS) map4[j] = make_uint4(0u, 0u, 0u, 0u);
                 const uint32_t cols = (uint32_t)run * HV_WIN;
-                auto mark = [&](const HvFour<V> (&f)[2], const HvTiles<V> &) {
+                auto mark = [&](const TileFour<V> (&f)[2], const Tiles<V, uint32_t> &) {
 #pragma unroll
                     for (int u = 0; u < 2; ++u) {
                         if (f[u].skip >= 4) continue;
@@ -1338,7 +1171,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                     }
                 };
                 uint32_t skip = 0u;   // entries of the stretch before the pass's
-                auto add = [&](const HvFour<V> (&f)[2], const HvTiles<V> &t) {
+                auto add = [&](const TileFour<V> (&f)[2], const Tiles<V, uint32_t> &t) {
                     const V a[2] = {row_lane<0>(t.a), row_lane<1>(t.a)};
 #pragma unroll
                     for (int u = 0; u < 2; ++u) {
@@ -1373,7 +1206,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                                    n4 = n3 + __popc(x1.x), n5 = n4 + __popc(x1.y), n6 = n5 + __popc(x1.z), n7 = n6 + __popc(x1.w);
                     const uint32_t incl = wave_inclusive_scan_u32(n7);
                     if (lane == WAVE - 1) s_win[wave] = incl;
-                    lds_barrier();
+                    __syncthreads();
                     const uint32_t per_win = lane < HV_WAVES ? s_win[lane] : 0u;
                     upto = wave_inclusive_scan_u32(per_win);
                     if (wave < run) {
@@ -1381,7 +1214,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                         auto two = [&](uint32_t lo, uint32_t hi) { return ((b + lo) & 0xffffu) | ((b + hi) << 16); };
                         reinterpret_cast<uint4 *>(s_pre)[wave * WAVE + lane] = make_uint4(two(0u, n0), two(n1, n2), two(n3, n4), two(n5, n6));
                     }
-                    lds_barrier();
+                    __syncthreads();
                 };
                 // the pass's n entries to C
                 auto write = [&](uint32_t n) {
@@ -1402,34 +1235,34 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                 uint32_t total = open(0, w, w1, nent);
                 if (ne <= HV_CHUNK && total <= (uint32_t)(HV_KEEP * HV_WAVES)) {   // uniform
                     // ---- so few tiles that the products stay in registers from the marking to the adding up
-                    const uint32_t span = (total + HV_WAVES * HV_STEP - 1) / (HV_WAVES * HV_STEP) * HV_STEP;
+                    const uint32_t span = (total + HV_WAVES * TILE_STEP - 1) / (HV_WAVES * TILE_STEP) * TILE_STEP;
                     const uint32_t k0 = (uint32_t)wave * span, k1 = k0 + span < total ? k0 + span : total;
-                    HvFour<V> f[2];
-                    HvTiles<V> t;
+                    TileFour<V> f[2];
+                    Tiles<V, uint32_t> t;
                     if (k0 < total) {   // uniform for the wave
                         t.find(s_ch, nent, total, k0, k1);
-                        hv_load<0, true>(t, b_col, b_val, f[0]);
-                        hv_load<1, true>(t, b_col, b_val, f[1]);
+                        tile_load<0, true>(t, b_col, b_val, f[0]);
+                        tile_load<1, true>(t, b_col, b_val, f[1]);
                         mark(f, t);
                     } else {
-                        f[0] = f[1] = HvFour<V>{};
-                        t = HvTiles<V>{};
+                        f[0] = f[1] = TileFour<V>{};
+                        t = Tiles<V, uint32_t>{};
                     }
-                    lds_barrier();
+                    __syncthreads();
                     count();
                     if (k0 < total) add(f, t);
-                    lds_barrier();
+                    __syncthreads();
                     write(wave_read_lane_u32(upto, WAVE - 1));
                 } else {
-                    HvTiles<V> tiles{};
+                    Tiles<V, uint32_t> tiles{};
                     for (int64_t base = 0; base < ne; base += HV_CHUNK) {
                         if (base > 0) {
-                            lds_barrier();
+                            __syncthreads();
                             total = open(base, w, w1, nent);
                         }
-                        if (total > 0u) hv_walk<false>(s_ch, nent, total, b_col, b_val, tiles, false, mark);
+                        if (total > 0u) tile_walk<HV_THREADS, 2, false>(s_ch, nent, total, b_col, b_val, tiles, false, mark);
                     }
-                    lds_barrier();
+                    __syncthreads();
                     count();
                     // accumulate and write, as many windows at a time as have HV_CAP entries (all of them, as a rule)
                     for (int g0 = 0; g0 < run;) {   // uniform
@@ -1440,12 +1273,12 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                         const bool whole = g0 == 0 && g1 == run;
                         for (int64_t base = 0; base < ne; base += HV_CHUNK) {
                             if (!whole || ne > HV_CHUNK) {   // (else the chunk is still open)
-                                lds_barrier();
+                                __syncthreads();
                                 total = open(base, w + g0, w + g1, nent);
                             }
-                            if (total > 0u) hv_walk<true>(s_ch, nent, total, b_col, b_val, tiles, whole && ne <= HV_CHUNK && total <= (uint32_t)HV_THREADS, add);
+                            if (total > 0u) tile_walk<HV_THREADS, 2, true>(s_ch, nent, total, b_col, b_val, tiles, whole && ne <= HV_CHUNK && total <= (uint32_t)HV_THREADS, add);
                         }
-                        lds_barrier();
+                        __syncthreads();
                         write(n < (uint32_t)HV_CAP ? n : (uint32_t)HV_CAP);
                         skip += n;
                         g0 = g1;
@@ -1457,7 +1290,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
         }
         for (int j = tid; j < n_win; j += HV_THREADS) s_pw[j] = 0u;   // (no wave plans behind a pass's barriers)
         if (tid == 0) row_nnz[row] = done > cap ? -1 : (int32_t)done;
-        lds_barrier();
+        __syncthreads();
     }
 }
 

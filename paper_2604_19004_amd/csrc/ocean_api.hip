@@ -411,6 +411,7 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
     // window costs less than building a key table of 16384 or 32768 slots: those two bins go with it
     // (the row lists of consecutive bins are adjacent).
     const bool wide_bitmap = B.cols <= (1 << 20);
+    const bool few_apart = B.cols <= SYMBOLIC_FEW_COLS;   // rows of few products have a launch of smaller workgroups
     for (int round = 0; round < 2; ++round) {
         const bool assisted = round == 0 && assist_cr > 1.0;
         BinParams bp{};
@@ -448,18 +449,24 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
         const int64_t by_range = start[SB_ALL] - start[SB_SPAN] - (few_by_keys ? few : 0);
         if (st && round == 0) st->symbolic_rows_per_bin[few_by_keys ? SB_S1K : SB_SPAN] += few;
         for (int b = SB_ALL - 1; b >= 0; --b) {
-            SymLaunch l{w.bin_rows + start[b], start[b + 1] - start[b], b, query_bitmap, spans ? w.cmin : nullptr, assisted};
+            SymLaunch l{w.bin_rows + start[b], start[b + 1] - start[b], b, query_bitmap, spans ? w.cmin : nullptr, false, assisted};
             if (b == SB_SPAN_FEW && !few_by_keys) continue;
             if (b == SB_SPAN_FEW) l.bin = SB_S1K;
             if (b == SB_SPAN) l.count = by_range;
-            if (wide_bitmap && (b == SB_S16K || b == SB_S32K)) continue;
-            if (wide_bitmap && b == SB_BITMAP) {
+            if (wide_bitmap && b == SB_S32K) {
+                if (!few_apart) continue;
+                l.rows = w.bin_rows + start[SB_S16K];
+                l.count = start[SB_BITMAP] - start[SB_S16K];
+                l.bin = SB_BITMAP;
+                l.few = true;
+            }
+            if (wide_bitmap && b == SB_S16K) continue;
+            if (wide_bitmap && b == SB_BITMAP && !few_apart) {
                 l.rows = w.bin_rows + start[SB_S16K];
                 l.count = start[SB_COUNT] - start[SB_S16K];
             }
             if (l.count == 0) continue;
-            const int n_wg = (int)(l.count < c.n_cu ? l.count : c.n_cu);
-            HIP_TRY(launch_symbolic_bin(A, B, l, gb_log2, nnz_out, n_wg, &w.sc->queue[round], c.s));
+            HIP_TRY(launch_symbolic_bin(A, B, l, gb_log2, nnz_out, c.n_cu, &w.sc->queue[round], c.s));
         }
         if (!assisted && by_range == 0) break;   // (no row's table or range can have been too small)
         HIP_TRY(launch_count_rows(A.rows, nnz_out, nullptr, nullptr, nullptr, &w.sc->ovf_count, nullptr, nullptr, c.s));
@@ -1157,7 +1164,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     // needs the window boundaries inside every (sorted) row of B.  Built only when such rows can exist
     // and the table stays small; otherwise, or when a row of B turns out unsorted, they use global tables.
     uint32_t *bw_try = nullptr;
-    if (max_ub > kNumericSlots[NB_S8K] && B.nnz < 0xffffffffLL && B.nnz >= HEAVY_MIN_ENTRIES && !o.force_hash_kernels) {
+    if (max_ub > kNumericSlots[NB_S8K] && B.nnz < 0xffffffffLL && B.nnz >= TILE_MIN_ENTRIES && !o.force_hash_kernels) {
         const int nw = dense_window_count(n, dtype);
         const size_t bytes = (size_t)B.rows * ((size_t)nw + 1) * 4;
         if (nw <= 512 && bytes <= ((size_t)6 << 30)) {   // the heavy-row kernel plans at most 512 windows per row

@@ -105,15 +105,6 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
-// A barrier of the workgroup that orders its LDS accesses and nothing else: loads from and stores to global memory stay
-// in flight across it (__syncthreads waits for all of them).
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 __device__ __forceinline__ uint32_t fmix32(uint32_t h)
 {
     h ^= h >> 16;
@@ -347,12 +338,14 @@ int64_t scan_tmp_elems(int64_t n);   // words of tile sums for n rows
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, unsigned long long v, hipStream_t s);
 
 // symbolic.hip
+constexpr int64_t SYMBOLIC_FEW_COLS = 1 << 18;
 struct SymLaunch {
     const int32_t *rows;   // row ids of this bin
     int64_t count;
     int bin;
     bool query_bitmap;     // bitmap kernel: read a column's bit before setting it (Section 4.1)
     const int32_t *cmin;   // SB_SPAN: first column each row can reach
+    bool few;              // SB_BITMAP: rows of at most kSymbolicSlots[SB_S32K] products
     bool may_overflow;     // tables were sized from a guess (assisted binning): a row whose table fills up
                            // reports -1 instead of a count and probing gives up early
 };
@@ -389,8 +382,8 @@ struct NumLaunch {
     const int32_t *cmin;      // dense-range bin: first column each row can reach
     int span_cols;            // dense-range bin: the rows' ranges are at most so many columns (kDspanCols or DS_MAX_COLS)
 };
+constexpr int64_t TILE_MIN_ENTRIES = 8;   // that B has where its rows are walked in tiles (tiles.hpp)
 hipError_t launch_window_table(const Csr &B, int dtype, uint32_t *bw, int *n_win_out, int32_t *flags, hipStream_t s);
-constexpr int64_t HEAVY_MIN_ENTRIES = 8;   // of B: the column-window kernel reads four entries at a time, up to position 7 where a row ends among the first
 int heavy_workgroups_per_cu();   // workgroups of the column-window kernel that one compute unit holds
 int dense_window_count(int64_t n_cols, int dtype);
 hipError_t launch_numeric_bin(const Csr &A, const Csr &B, int dtype, const NumLaunch &l, int gb_log2, hipStream_t s);

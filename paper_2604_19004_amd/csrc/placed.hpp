@@ -62,7 +62,7 @@ __device__ __forceinline__ void place_units(const uint32_t *counts, unsigned lon
             turn.lead[parity][wave] = lead;
             turn.sum[parity][wave] = upto;
         }
-        lds_barrier();
+        __syncthreads();
         int total_lead = 0;
         unsigned long long before = run, after = run;
         bool mine = true, open = true;   // the quarters before this wave's, and so far, are complete

@@ -6,11 +6,10 @@
 // any key table an LDS bitmap over windows of 2^20 columns (one fire-and-forget
 // LDS OR per product, a popcount at the end).
 #include "ocean_internal.hpp"
+#include "tiles.hpp"
 #include "traverse.hpp"
 
 namespace ocean {
-
-using NoVal = unsigned char;   // the symbolic pass carries no values
 
 // Insert a batch of column ids into a key-only LDS table and return how many
 // were new.  Double hashing, and every lane walks its own ids at its own pace
@@ -210,31 +209,35 @@ k_symbolic_span(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
 }
 
 // --------------------------------------------------------- bitmap kernel
-constexpr int BM_THREADS = 1024;
-constexpr int BM_U = 16;                 // column ids per lane and batch (R-MAT: 16.2 ms against 16.9 with 8, 20.9 with 4)
+constexpr int BM_CHUNK = 512;             // entries of A whose rows of B are walked at a time
+constexpr int BM_STEPS = 2;               // steps of tiles per batch
 constexpr int BM_WIN = 1 << 20;          // columns per window
 constexpr int BM_MAX_WORDS = BM_WIN / 32;    // 32768 words = 128 KB
+static_assert(SYMBOLIC_FEW_COLS == 32 * 8192, "four bitmaps per compute unit");
 
 // BM_WORDS: words of the bitmap, 32 columns each: 32768, or fewer where B has fewer columns - a smaller bitmap is swept
-// (counted and cleared) faster after every row, and leaves room for a second workgroup on the compute unit (64
+// (counted and cleared) faster after every row, and leaves room for more workgroups on the compute unit (64
 // registers): symbolic stage of R-MAT scale 18 (16384 words) 2.80 -> 1.94 ms, whole call of scale 17 (4096) 1.39 -> 0.99
-// ms.  Eight workgroups of 256 threads for the rows of up to 32768 products were slower (1.33 ms): the set-up of a
-// chunk is most of such a row's time, and smaller chunks are more of them.
+// ms, the same with rows in tiles (tiles.hpp) instead of runs of 16 found by a search each 0.935 -> 0.875.
+// BM_THREADS: 1024; 512 for rows of at most 32768 products where the bitmap leaves room for four workgroups, in a launch of their
+// own, as the largest row decides how long a launch takes: scale 17 0.875 -> 0.850 ms (256 threads: 0.839), scale 14 in fp32 whole
+// product 663 -> 626 us (659), all rows by 512 threads 1.016 ms and 718 us.
 // ONE_WINDOW: B has at most 32 * BM_WORDS columns, so every column id falls into the one window.
 // QUERY: a column's bit is read first and set only when it is clear (Section 4.1).
-template <int BM_WORDS, bool ONE_WINDOW, bool QUERY>
+template <typename P, int BM_THREADS, int BM_WORDS, bool ONE_WINDOW, bool QUERY>
 __global__ void __launch_bounds__(BM_THREADS, BM_WORDS < BM_MAX_WORDS ? 8 : 4)
 k_symbolic_bitmap(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
                   const int64_t *__restrict__ b_rp, const int32_t *__restrict__ b_col,
-                  const int32_t *__restrict__ rows, int64_t count, int64_t n_cols,
+                  const int32_t *__restrict__ rows, int64_t count, int64_t n_cols, int64_t b_nnz,
                   unsigned long long *queue, int32_t *__restrict__ nnz_out)
 {
+    constexpr int CHUNK = BM_THREADS < BM_CHUNK ? BM_THREADS : BM_CHUNK;
     __shared__ __align__(16) uint32_t s_bm[BM_WORDS];
-    __shared__ WgChunk<NoVal, BM_THREADS> s_fc;
+    __shared__ TileChunk<NoVal, P, CHUNK> s_ch;
     // Rows come from a shared counter.  The chain counter -> row id -> offsets of the row -> entries -> their
     // segments of B is five memory round trips before the first column id of a row can be asked for, so it runs
     // ahead of the work, one link per turn: at the start of a turn the ticket of the row six turns ahead is
-    // drawn and the row id (four ahead), the offsets (three), the first BM_THREADS entries (two) and their
+    // drawn and the row id (four ahead), the offsets (three), the first CHUNK entries (two) and their
     // segments (one) are asked for, all of which arrive under the traversal of the current row.  s_ticket: ring
     // of eight tickets (count >= 1); a ticket is first read two turns after it was stored, behind the barriers
     // of the turn between, and the row counts alternate between two cells, so a turn ends without a barrier.
@@ -242,8 +245,12 @@ k_symbolic_bitmap(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ 
     __shared__ int s_count[2];
     const int tid = threadIdx.x;
     for (int s = tid; s < BM_WORDS; s += BM_THREADS) s_bm[s] = 0u;
+    // (rows of about the same size need no counter, which hands out 83 tickets per us to the whole chip)
+    auto draw = [&](unsigned turn) {
+        return queue != nullptr ? atomicAdd(queue, 1ull) : (unsigned long long)blockIdx.x + (unsigned long long)turn * gridDim.x;
+    };
     if (tid == 0) {
-        for (int j = 0; j < 6; ++j) s_ticket[j] = atomicAdd(queue, 1ull);
+        for (int j = 0; j < 6; ++j) s_ticket[j] = draw((unsigned)j);
         s_count[0] = s_count[1] = 0;
     }
     __syncthreads();
@@ -252,7 +259,7 @@ k_symbolic_bitmap(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ 
         const unsigned long long t = s_ticket[turn & 7u];
         return (int64_t)rows[t < (unsigned long long)count ? count - 1 - (int64_t)t : (int64_t)0];   // (the largest bounds are at the end)
     };
-    auto entry_of = [&](int64_t f0, int64_t f1) { return f0 + tid < f1 ? a_col[f0 + tid] : (int32_t)-1; };
+    auto entry_of = [&](int64_t f0, int64_t f1) { return tid < CHUNK && f0 + tid < f1 ? a_col[f0 + tid] : (int32_t)-1; };
     auto segment_of = [&](int32_t k, int64_t &p0, uint32_t &len) {
         p0 = 0; len = 0u;
         if (k >= 0) {
@@ -268,30 +275,24 @@ k_symbolic_bitmap(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ 
     int64_t fp0;
     uint32_t flen;
     segment_of(entry_of(e0, e1), fp0, flen);
-    auto mark = [&](const auto &cj, uint32_t w0, auto all_valid) {
-        constexpr int U = sizeof(cj) / sizeof(cj[0]);
-        constexpr bool ALL = decltype(all_valid)::value;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            // (32-bit arithmetic: a column before the window wraps to a large number)
-            const uint32_t d = ONE_WINDOW ? (uint32_t)cj[u] : (uint32_t)cj[u] - w0;
-            // Only the number of set bits matters, so neighbouring columns (the sorted entries of one row of
-            // B in neighbouring lanes) go to neighbouring words, i.e. different LDS banks, not to one word.
-            if ((ALL || cj[u] >= 0) && (ONE_WINDOW || d < (uint32_t)BM_WIN)) {
-                // Columns BM_WORDS apart share neither word nor bank (each bit's columns are turned by another amount):
-                // the much used columns of a power-law matrix are powers of two apart, and lanes that meet at one word
-                // take turns.
-                const uint32_t h = d / (uint32_t)BM_WORDS;
-                const uint32_t bit = 1u << h;
-                uint32_t *word = &s_bm[(d + h * 1021u) & (uint32_t)(BM_WORDS - 1)];
-                if (!QUERY || !(*word & bit)) atomicOr(word, bit);
-            }
-        }
+    auto mark = [&](int32_t col, uint32_t w0, bool ok) {
+        // (32-bit arithmetic: a column before the window wraps to a large number)
+        const uint32_t d = ONE_WINDOW ? (uint32_t)col : (uint32_t)col - w0;
+        if (!ok || (!ONE_WINDOW && d >= (uint32_t)BM_WIN)) return;
+        // Only the number of set bits matters, so neighbouring columns (the sorted entries of one row of
+        // B in neighbouring lanes) go to neighbouring words, i.e. different LDS banks, not to one word.
+        // Columns BM_WORDS apart share neither word nor bank (each bit's columns are turned by another amount):
+        // the much used columns of a power-law matrix are powers of two apart, and lanes that meet at one word
+        // take turns.
+        const uint32_t h = d / (uint32_t)BM_WORDS;
+        const uint32_t bit = 1u << h;
+        uint32_t *word = &s_bm[(d + h * 1021u) & (uint32_t)(BM_WORDS - 1)];
+        if (!QUERY || !(*word & bit)) atomicOr(word, bit);
     };
     for (unsigned turn = 0;; ++turn) {
         if (s_ticket[turn & 7u] >= (unsigned long long)count) break;   // uniform exit (tickets only grow)
         unsigned long long drawn = 0;
-        if (tid == 0) drawn = atomicAdd(queue, 1ull);                  // ticket of turn + 6
+        if (tid == 0) drawn = draw(turn + 6u);
         const int64_t row4 = row_of(turn + 4u);
         const int64_t e0_3 = a_rp[row3], e1_3 = a_rp[row3 + 1];
         const int32_t k2 = entry_of(e0_2, e1_2);
@@ -300,17 +301,38 @@ k_symbolic_bitmap(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ 
         segment_of(k1, fp0_1, flen_1);
         const int64_t ne = e1 - e0;
         for (int64_t w0 = 0; w0 < n_cols; w0 += BM_WIN) {
-            auto f = [&](const auto &cj, const auto &, auto... tag) {
-                mark(cj, (uint32_t)w0, std::bool_constant<(std::is_same_v<decltype(tag), AllValid> || ...)>{});
-            };
-            if (ne > 0)
-                wg_flat_chunk<BM_THREADS, false, BM_U>(s_fc, ne < BM_THREADS ? (int)ne : BM_THREADS, fp0, flen, NoVal(), b_col,
-                                                       (const NoVal *)nullptr, f);
-            if (ne > BM_THREADS)
-                wg_traverse<BM_THREADS, false, BM_U>(a_col, (const NoVal *)nullptr, e0 + BM_THREADS, e1,
-                                                     [&](int32_t k, int64_t &p0, int64_t &len) { p0 = b_rp[k]; len = b_rp[k + 1] - p0; },
-                                                     b_col, (const NoVal *)nullptr, s_fc, f);
-            // (both end with a barrier)  count and clear the window, 16 bytes per thread and step
+            if (b_nnz < TILE_MIN_ENTRIES) {   // uniform: (many entries of A, none with eight products)
+                for (int64_t e = e0 + tid; e < e1; e += BM_THREADS) {
+                    const int32_t k = a_col[e];
+                    for (int64_t p = b_rp[k]; p < b_rp[k + 1]; ++p) mark(b_col[p], (uint32_t)w0, true);
+                }
+            } else {
+                for (int64_t base = 0; base < ne; base += CHUNK) {
+                    int64_t p0 = fp0;
+                    uint32_t len = flen;
+                    if (base > 0) {
+                        __syncthreads();
+                        segment_of(entry_of(e0 + base, e1), p0, len);
+                    }
+                    const int nent = (int)(ne - base < CHUNK ? ne - base : CHUNK);
+                    const uint32_t total = tile_open<BM_THREADS>(s_ch, nent, (P)p0, len, NoVal());
+                    if (total == 0u) continue;   // uniform
+                    Tiles<NoVal, P> tiles{};
+                    tile_walk<BM_THREADS, BM_STEPS, false>(s_ch, nent, total, b_col, (const NoVal *)nullptr, tiles, false,
+                                                           [&](const TileFour<NoVal> (&f)[BM_STEPS], const Tiles<NoVal, P> &t) {
+                        // (a set of columns: an entry of the same row of B seen twice does no harm, so only those are left out that
+                        // may be of another row)
+#pragma unroll
+                        for (int u = 0; u < BM_STEPS; ++u) {
+                            if (f[u].skip >= 4) continue;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) mark(f[u].col[i], (uint32_t)w0, !t.small || (i >= f[u].skip && f[u].col[i] >= 0));
+                        }
+                    });
+                }
+            }
+            __syncthreads();
+            // count and clear the window, 16 bytes per thread and step
             int c = 0;
             uint4 *bm4 = reinterpret_cast<uint4 *>(s_bm);
 #pragma unroll
@@ -377,23 +399,34 @@ hipError_t launch_symbolic_bin(const Csr &A, const Csr &B, const SymLaunch &l, i
         });
         break;
     case SB_BITMAP: {
-#define OCEAN_SYM_BM(WORDS, ONE, QUERY)                                                                            \
-    hipLaunchKernelGGL((k_symbolic_bitmap<WORDS, ONE, QUERY>), dim3((unsigned)(n_wg < l.count ? n_wg : l.count)),           \
-                       dim3(BM_THREADS), 0, s, A.rp, A.col, B.rp, B.col, l.rows, l.count, B.cols, queue, nnz_out)
-#define OCEAN_SYM_BM_Q(WORDS, ONE)                                                                                 \
+#define OCEAN_SYM_BM_P(P, THREADS, WORDS, ONE, QUERY)                                                               \
+    hipLaunchKernelGGL((k_symbolic_bitmap<P, THREADS, WORDS, ONE, QUERY>), dim3((unsigned)(n_wg < l.count ? n_wg : l.count)), \
+                       dim3(THREADS), 0, s, A.rp, A.col, B.rp, B.col, l.rows, l.count, B.cols, B.nnz, queue, nnz_out)
+#define OCEAN_SYM_BM(THREADS, WORDS, ONE)                                                                           \
     do {                                                                                                          \
-        if (l.query_bitmap) OCEAN_SYM_BM(WORDS, ONE, true);                                                        \
-        else OCEAN_SYM_BM(WORDS, ONE, false);                                                                      \
+        const bool narrow = B.nnz < 0xffffffffLL;   /* positions in 32 bits */                                     \
+        if (l.query_bitmap && narrow) OCEAN_SYM_BM_P(uint32_t, THREADS, WORDS, ONE, true);                         \
+        else if (l.query_bitmap) OCEAN_SYM_BM_P(unsigned long long, THREADS, WORDS, ONE, true);                    \
+        else if (narrow) OCEAN_SYM_BM_P(uint32_t, THREADS, WORDS, ONE, false);                                     \
+        else OCEAN_SYM_BM_P(unsigned long long, THREADS, WORDS, ONE, false);                                       \
     } while (0)
-        if (B.cols > BM_WIN) OCEAN_SYM_BM_Q(BM_MAX_WORDS, false);
-        else if (B.cols > 32 * 16384) OCEAN_SYM_BM_Q(BM_MAX_WORDS, true);
-        else {
+        if (B.cols > BM_WIN) OCEAN_SYM_BM(1024, BM_MAX_WORDS, false);
+        else if (B.cols > 32 * 16384) OCEAN_SYM_BM(1024, BM_MAX_WORDS, true);
+        else if (B.cols > SYMBOLIC_FEW_COLS) {
             n_wg *= 2;   // (two workgroups per compute unit)
-            if (B.cols > 32 * 4096) OCEAN_SYM_BM_Q(16384, true);
-            else OCEAN_SYM_BM_Q(4096, true);
+            OCEAN_SYM_BM(1024, 16384, true);
+        } else if (l.few) {
+            n_wg *= 4;
+            queue = nullptr;
+            if (B.cols > 32 * 4096) OCEAN_SYM_BM(512, 8192, true);
+            else OCEAN_SYM_BM(512, 4096, true);
+        } else {
+            n_wg *= 2;
+            if (B.cols > 32 * 4096) OCEAN_SYM_BM(1024, 8192, true);
+            else OCEAN_SYM_BM(1024, 4096, true);
         }
-#undef OCEAN_SYM_BM_Q
 #undef OCEAN_SYM_BM
+#undef OCEAN_SYM_BM_P
         break;
     }
     default: return hipErrorInvalidValue;

@@ -31,8 +31,6 @@ namespace ocean {
 constexpr int T_LONG = 128;
 constexpr int FLAT_U = 4;
 
-// Third argument of an accumulator's batch function when every column id of the batch is a real one.
-struct AllValid {};
 // 16 bytes of column ids at any 4-byte boundary (one load instruction).
 struct alignas(4) Int4U { int32_t v[4]; };
 
@@ -158,7 +156,7 @@ struct WgChunk {
     V a[THREADS];
     union alignas(8) {
         uint16_t first[THREADS + 2];       // entry of the first product of every block of 2^bshift products
-        uint32_t start[START_WORDS];       // bit q set: a segment starts at product q (RANK_CAP bits + padding for batches of up to 16 per lane)
+        uint32_t start[START_WORDS];       // bit q set: a segment starts at product q (RANK_CAP bits + padding for the batches of a lane)
     };
     uint32_t wsum[THREADS / WAVE];
     uint32_t wcnt[THREADS / WAVE];
@@ -183,14 +181,14 @@ struct WgChunk {
 //     the same, wave-uniform number of steps and run interleaved.  Without values (the symbolic
 //     pass) such a chunk is walked in runs of WU consecutive column ids per lane instead, its
 //     batches handed out from a counter rather than in equal spans (see there).
-// WU is the number of products per lane and batch.  The products of one chunk must number less
-// than 2^31.
+// The products of one chunk must number less than 2^31.
 // Every thread calls it; the chunk arrays must be free on entry (the call ends with a barrier).
 // Returns the number of products of the chunk.
-template <int THREADS, bool HAS_VAL, int WU = FLAT_U, typename V, typename F>
+template <int THREADS, bool HAS_VAL, typename V, typename F>
 __device__ __forceinline__ uint32_t wg_flat_chunk(WgChunk<V, THREADS> &c, int nent, int64_t p0, uint32_t len, V a,
                                               const int32_t *__restrict__ b_col, const V *__restrict__ b_val, F &f)
 {
+    constexpr int WU = FLAT_U;   // products per lane and batch
     constexpr int NW = THREADS / WAVE;
     constexpr uint32_t RANK_CAP = WgChunk<V, THREADS>::RANK_CAP;
     constexpr int START_WORDS = WgChunk<V, THREADS>::START_WORDS;
@@ -203,7 +201,7 @@ __device__ __forceinline__ uint32_t wg_flat_chunk(WgChunk<V, THREADS> &c, int ne
     const unsigned long long live = __ballot(len > 0);
     if (lane == WAVE - 1) { c.wsum[wave] = incl; c.wcnt[wave] = (uint32_t)__popcll(live); }
     // column ids only: the same sums over the lengths rounded up to whole runs of WU (see below)
-    constexpr bool RUNS = !HAS_VAL && WU % 4 == 0;
+    constexpr bool RUNS = !HAS_VAL;
     const uint32_t lenr = (len + (uint32_t)(WU - 1)) & ~(uint32_t)(WU - 1);
     uint32_t inclr = 0;
     if constexpr (RUNS) {
@@ -226,19 +224,8 @@ __device__ __forceinline__ uint32_t wg_flat_chunk(WgChunk<V, THREADS> &c, int ne
     V cb[WU];   // values of B
     int cp[WU];
     // Runs (column ids only, below) pay when the segments are at least a run long on average - shorter ones leave
-    // most of a run's slots empty (rows of B of 8 entries in runs of 16: 0.93 against 0.60 ms on a test input, rows
-    // of 24: 0.86 against 1.62 ms) - and long runs are worth more than the marks even for a small chunk (R-MAT,
-    // 16 ids per run: 15.7 against 15.9 ms), short ones are not (rect, 4 ids per run: 0.78 against 0.68 ms).
-    const bool use_runs = RUNS && (unsigned long long)total >= (unsigned long long)ctotal * (unsigned)WU &&
-                          (WU >= 8 || total > RANK_CAP);   // uniform
-    if constexpr (RUNS && WU > 4) {
-        // (a chunk of short segments: the same with four column ids per lane and batch - the marks, runs of four
-        // or the search, whichever applies - which also keeps the registers of those paths out of this one)
-        if (!use_runs) {   // uniform
-            __syncthreads();   // (everyone has read the waves' sums)
-            return wg_flat_chunk<THREADS, HAS_VAL, 4>(c, nent, p0, len, a, b_col, b_val, f);
-        }
-    }
+    // most of a run's slots empty - and not for a small chunk, whose entries the marks find faster (rect: 0.78 against 0.68 ms).
+    const bool use_runs = RUNS && (unsigned long long)total >= (unsigned long long)ctotal * (unsigned)WU && total > RANK_CAP;   // uniform
     if (!use_runs && total <= RANK_CAP) {   // uniform
         const uint32_t ex = incl - len;
         if (len > 0) {
@@ -381,8 +368,7 @@ __device__ __forceinline__ uint32_t wg_flat_chunk(WgChunk<V, THREADS> &c, int ne
 #pragma unroll
                     for (int i = 0; i < 4; ++i) cj[g * 4 + i] = x.v[i];
                 }
-                if constexpr (std::is_invocable_v<F &, int32_t(&)[WU], V(&)[WU], AllValid>) f(cj, cv, AllValid{});
-                else f(cj, cv);
+                f(cj, cv);
             } else {
 #pragma unroll
                 for (int u = 0; u < WU; ++u) {
@@ -489,7 +475,7 @@ __device__ __forceinline__ uint32_t wg_flat_chunk(WgChunk<V, THREADS> &c, int ne
 // Workgroup version of the row traversal: chunks of THREADS entries of A, each flattened over the
 // whole workgroup.  Every thread of the (1-D) workgroup must call it.  seg(k, p0, len) gives the
 // segment of B's arrays that entry k expands to.  Ends with a barrier.
-template <int THREADS, bool HAS_VAL, int WU = FLAT_U, typename V, typename SegFn, typename F>
+template <int THREADS, bool HAS_VAL, typename V, typename SegFn, typename F>
 __device__ __forceinline__ void wg_traverse(const int32_t *__restrict__ a_col, const V *__restrict__ a_val,
                                             int64_t e0, int64_t e1, SegFn seg, const int32_t *__restrict__ b_col,
                                             const V *__restrict__ b_val, WgChunk<V, THREADS> &c, F f)
@@ -505,7 +491,7 @@ __device__ __forceinline__ void wg_traverse(const int32_t *__restrict__ a_col, c
             seg(k, p0, len);
         }
         const int64_t left = e1 - base;
-        wg_flat_chunk<THREADS, HAS_VAL, WU>(c, left < THREADS ? (int)left : THREADS, p0, (uint32_t)len, a, b_col, b_val, f);
+        wg_flat_chunk<THREADS, HAS_VAL>(c, left < THREADS ? (int)left : THREADS, p0, (uint32_t)len, a, b_col, b_val, f);
     }
 }
 
