@@ -73,19 +73,19 @@ k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coe
            const int32_t *__restrict__ cmin, const int32_t *__restrict__ cmax, int vbytes, unsigned sort_mask,
            const int64_t *__restrict__ a_rp, uint8_t *__restrict__ bin_of_row, int32_t *__restrict__ cap,
            int64_t *__restrict__ tile_cap, int32_t *zero, unsigned long long *bin_count, unsigned long long *bin_prod,
-           unsigned long long *max_cap, unsigned long long *work)
+           unsigned long long *max_cap, unsigned long long *uncounted, unsigned long long *work)
 {
     constexpr int ROW_TILE = TPB * ROW_ITEMS;
     __shared__ unsigned int s_cnt[ROW_KEYS];
     __shared__ unsigned long long s_prod[ROW_KEYS];
-    __shared__ unsigned int s_maxcap;
+    __shared__ unsigned int s_maxcap, s_uncounted;
     static_assert(ROW_KEYS <= TPB && ROW_KEYS <= BIN_NONE, "one thread per key, keys in a byte");
     if (threadIdx.x < ROW_KEYS) { s_cnt[threadIdx.x] = 0; s_prod[threadIdx.x] = 0ull; }
     // (2048 rows of fewer than 2^20 entries: below 2^31; longer rows are added to the totals one by one)
     __shared__ unsigned int s_nnz_a[OCEAN_MAX_BINS], s_nnz_c[OCEAN_MAX_BINS];
     __shared__ long long s_part[TPB / WAVE];
     if (threadIdx.x < OCEAN_MAX_BINS) { s_nnz_a[threadIdx.x] = 0u; s_nnz_c[threadIdx.x] = 0u; }
-    if (threadIdx.x == 0) s_maxcap = 0;
+    if (threadIdx.x == 0) s_maxcap = s_uncounted = 0;
     __syncthreads();
     long long caps = 0;
 #pragma unroll
@@ -113,6 +113,10 @@ k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coe
                 if (need < 1) need = 1;
             } else if (mode == 2) {
                 c = nnz_exact[i];
+                if (c < 0) {
+                    c = 0;
+                    atomicAdd(&s_uncounted, 1u);
+                }
                 double want = ceil(coef * (double)c);
                 need = want >= (double)ub_slots ? ub_slots : (long long)want;
                 if (need < c) need = c;
@@ -183,15 +187,17 @@ k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coe
     if (threadIdx.x < ROW_KEYS && s_cnt[threadIdx.x]) atomicAdd(&bin_count[threadIdx.x], (unsigned long long)s_cnt[threadIdx.x]);
     if (bin_prod != nullptr && threadIdx.x < ROW_KEYS && s_prod[threadIdx.x]) atomicAdd(&bin_prod[threadIdx.x], s_prod[threadIdx.x]);
     if (threadIdx.x == 0 && s_maxcap && max_cap != nullptr) atomicMax(max_cap, (unsigned long long)s_maxcap);
+    if (threadIdx.x == 0 && s_uncounted && uncounted != nullptr) atomicAdd(uncounted, (unsigned long long)s_uncounted);
 }
 
 // tile_cap (may be null): receives the sum of the capacities of every tile of rows (scan_tmp_elems(m) words).
 // zero (may be null): an array of m words to clear.  work (may be null): [0 .. bins) += entries of A, [bins .. 2 bins) +=
-// exact entries of C (mode 2) of the rows of each bin.
+// exact entries of C (mode 2) of the rows of each bin.  uncounted (may be null): += rows without an exact number (mode 2, below 0).
 hipError_t launch_classify(int64_t m, const BinParams &p, double scale, const int64_t *prod, const double *est,
                            const int32_t *nnz_exact, const int32_t *row_mask, const int32_t *lower_bound,
                            uint8_t *bin_of_row, int32_t *cap, int64_t *tile_cap, int32_t *zero, unsigned long long *bin_count,
-                           unsigned long long *bin_prod, unsigned long long *max_cap, unsigned long long *work, hipStream_t s)
+                           unsigned long long *bin_prod, unsigned long long *max_cap, unsigned long long *uncounted,
+                           unsigned long long *work, hipStream_t s)
 {
     static_assert(NB_ALL <= OCEAN_MAX_BINS, "the dense-range bin has a place in the per-bin arrays");
     if (m == 0) return hipSuccess;
@@ -203,7 +209,7 @@ hipError_t launch_classify(int64_t m, const BinParams &p, double scale, const in
     const auto kernel = row_items(m) == 1 ? k_classify<1> : row_items(m) == 4 ? k_classify<4> : k_classify<8>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(TPB), 0, s, m, p.mode, p.coef, table_coef, p.bound_coef, scale, bt,
                        p.n_cols, prod, est, nnz_exact, row_mask, lower_bound, p.cmin, p.cmax, p.vbytes,
-                       p.sort_mask, p.a_rp, bin_of_row, cap, tile_cap, zero, bin_count, bin_prod, max_cap, work);
+                       p.sort_mask, p.a_rp, bin_of_row, cap, tile_cap, zero, bin_count, bin_prod, max_cap, uncounted, work);
     return hipGetLastError();
 }
 

@@ -404,15 +404,17 @@ void sample_rows_of(int64_t rows, const ocean_options &o, int64_t *out);
 // ---- exact symbolic pass ---------------------------------------------------------------------------
 // assist_cr > 1: assisted binning (Section 4.1) - key tables are sized from products / assist_cr, rows
 // whose table fills up report -1 and are recounted in a second round with tables sized from the products.
+// first_round 1: only those.  unchecked (may be null): set where there may be such rows and the caller finds out by itself (a
+// row of -1), which spares a launch and a read-back.
 int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, double assist_cr, bool query_bitmap,
-                 int32_t *nnz_out, ocean_stats *st)
+                 int32_t *nnz_out, ocean_stats *st, int first_round, bool *unchecked)
 {
     // With at most 2^20 columns the bitmap kernel covers a row in one window, and one pass over such a
     // window costs less than building a key table of 16384 or 32768 slots: those two bins go with it
     // (the row lists of consecutive bins are adjacent).
     const bool wide_bitmap = B.cols <= (1 << 20);
     const bool few_apart = B.cols <= SYMBOLIC_FEW_COLS;   // rows of few products have a launch of smaller workgroups
-    for (int round = 0; round < 2; ++round) {
+    for (int round = first_round; round < 2; ++round) {
         const bool assisted = round == 0 && assist_cr > 1.0;
         BinParams bp{};
         bp.mode = 3;
@@ -424,7 +426,7 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
         if (spans) { bp.cmin = w.cmin; bp.cmax = w.cmax; }
         OC_TRY(zero_bins(c, w));
         HIP_TRY(launch_classify(A.rows, bp, 1.0, w.prod, nullptr, nullptr, round == 0 ? nullptr : nnz_out, w.maxb, w.bin,
-                                nullptr, nullptr, round == 0 ? nnz_out : nullptr, w.sc->bin_count, nullptr, nullptr, nullptr, c.s));
+                                nullptr, nullptr, round == 0 ? nnz_out : nullptr, w.sc->bin_count, nullptr, nullptr, nullptr, nullptr, c.s));
         HIP_TRY(launch_place(A.rows, nullptr, nullptr, nullptr, nullptr, SB_ALL, w.bin, w.sc->bin_count, w.sc->bin_cursor,
                              w.bin_rows, c.s));
         OC_TRY(fetch_scalars(c, w.sc));
@@ -469,6 +471,10 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
             HIP_TRY(launch_symbolic_bin(A, B, l, gb_log2, nnz_out, c.n_cu, &w.sc->queue[round], c.s));
         }
         if (!assisted && by_range == 0) break;   // (no row's table or range can have been too small)
+        if (unchecked != nullptr) {
+            *unchecked = true;
+            break;
+        }
         HIP_TRY(launch_count_rows(A.rows, nnz_out, nullptr, nullptr, nullptr, &w.sc->ovf_count, nullptr, nullptr, c.s));
         OC_TRY(fetch_scalars(c, w.sc));
         if (st) st->symbolic_overflow_rows = (int64_t)c.h->ovf_count;
@@ -1253,6 +1259,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     const int64_t *out_ptr = nullptr;
     for (;;) {   // at most two rounds: an estimation workflow may fall back to the two-pass one when memory is short
         // ---- size prediction ----
+        bool unchecked = false;   // the symbolic pass may have rows to count again
         BinParams bp{};
         bp.n_bins = NB_COUNT;
         for (int b = 0; b < NB_COUNT; ++b) bp.slots[b] = kNumericSlots[b];
@@ -1270,7 +1277,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
             OC_TRY(mark(c, OCEAN_ST_PREDICT));
             S->assist_cr = o.assisted_symbolic ? conservative_cr(S, o) : 1.0;
             if (!(S->assist_cr > 1.0)) S->assist_cr = 0.0;
-            OC_TRY(run_symbolic(c, w, A, B, gb_log2, S->assist_cr, query_bitmap, w.nnz_final, S));
+            OC_TRY(run_symbolic(c, w, A, B, gb_log2, S->assist_cr, query_bitmap, w.nnz_final, S, 0, &unchecked));
             bp.mode = 2;
             bp.coef = o.exact_load_coef;
         } else {
@@ -1288,13 +1295,21 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
 
         // ---- binning + output placement ----
         OC_TRY(mark(c, OCEAN_ST_BINNING));
-        OC_TRY(zero_bins(c, w));
         int64_t *ptr = workflow == OCEAN_WF_SYMBOLIC ? c_rp : w.tmp_ptr;
-        HIP_TRY(launch_classify(m, bp, o.estimate_scale, w.prod, w.est, w.nnz_final, nullptr, nullptr, w.bin, w.cap, w.scan_tmp,
-                                w.row_nnz, w.sc->bin_count, w.sc->bin_prod, &w.sc->max_cap, st ? w.sc->bin_work : nullptr, c.s));
-        HIP_TRY(launch_place(m, w.cap, w.scan_tmp, ptr, &w.sc->totals[0], ROW_KEYS, w.bin, w.sc->bin_count, w.sc->bin_cursor,
-                             w.bin_rows, c.s));   // totals[0]: total slots
-        OC_TRY(fetch_scalars(c, w.sc));
+        for (;;) {   // once, or again after rows of the symbolic pass that had to be counted again
+            OC_TRY(zero_bins(c, w));
+            HIP_TRY(launch_classify(m, bp, o.estimate_scale, w.prod, w.est, w.nnz_final, nullptr, nullptr, w.bin, w.cap, w.scan_tmp,
+                                    w.row_nnz, w.sc->bin_count, w.sc->bin_prod, &w.sc->max_cap, &w.sc->ovf_count,
+                                    st ? w.sc->bin_work : nullptr, c.s));
+            HIP_TRY(launch_place(m, w.cap, w.scan_tmp, ptr, &w.sc->totals[0], ROW_KEYS, w.bin, w.sc->bin_count, w.sc->bin_cursor,
+                                 w.bin_rows, c.s));   // totals[0]: total slots
+            OC_TRY(fetch_scalars(c, w.sc));
+            if (!unchecked) break;
+            unchecked = false;
+            S->symbolic_overflow_rows = (int64_t)c.h->ovf_count;
+            if (c.h->ovf_count == 0) break;
+            OC_TRY(run_symbolic(c, w, A, B, gb_log2, S->assist_cr, query_bitmap, w.nnz_final, S, 1, nullptr));
+        }
         total_slots = (int64_t)c.h->totals[0];
         for (int b = 0; b < NB_ALL; ++b) {
             S->rows_per_bin[b] = 0;
@@ -1407,7 +1422,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         bp.a_rp = A.rp;
         OC_TRY(zero_bins(c, w));
         HIP_TRY(launch_classify(m, bp, 1.0, w.prod, nullptr, nullptr, w.row_nnz, nullptr, w.bin, w.cap, w.scan_tmp, w.row_nnz2,
-                                w.sc->bin_count, w.sc->bin_prod, &w.sc->max_cap, nullptr, c.s));
+                                w.sc->bin_count, w.sc->bin_prod, &w.sc->max_cap, nullptr, nullptr, c.s));
         HIP_TRY(launch_place(m, w.cap, w.scan_tmp, w.tmp_ptr2, &w.sc->totals[0], ROW_KEYS, w.bin, w.sc->bin_count,
                              w.sc->bin_cursor, w.bin_rows, c.s));
         OC_TRY(fetch_scalars(c, w.sc));
@@ -1714,7 +1729,7 @@ int ocean_symbolic(const ocean_csr *A, const ocean_csr *B, int32_t *nnz_per_row,
             if (!(assist_cr > 1.0)) assist_cr = 0.0;
         }
         S->assist_cr = assist_cr;
-        OC_TRY(run_symbolic(c, w, a, b, gb_log2, assist_cr, o.bitmap_query == 2, nnz_per_row, S));
+        OC_TRY(run_symbolic(c, w, a, b, gb_log2, assist_cr, o.bitmap_query == 2, nnz_per_row, S, 0, nullptr));
         HIP_TRY(hipStreamSynchronize(c.s));
         return OCEAN_OK;
     }();

@@ -325,7 +325,7 @@ hipError_t launch_classify(int64_t m, const BinParams &p, double scale, const in
                            const int32_t *nnz_exact, const int32_t *row_mask, const int32_t *lower_bound,
                            uint8_t *bin_of_row, int32_t *cap, int64_t *tile_cap, int32_t *zero, unsigned long long *bin_count,
                            unsigned long long *bin_prod /*products per key, may be null*/, unsigned long long *max_cap,
-                           unsigned long long *work, hipStream_t s);
+                           unsigned long long *uncounted, unsigned long long *work, hipStream_t s);
 hipError_t launch_place(int64_t m, const int32_t *in, int64_t *tile_sum, int64_t *out, unsigned long long *total_out,
                         int n_keys, const uint8_t *bin_of_row, const unsigned long long *bin_count,
                         unsigned long long *bin_cursor, int32_t *bin_rows, hipStream_t s);
