@@ -594,39 +594,58 @@ k_numeric_wg(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col
     }
 }
 
+// A product as it is added to an accumulator that says by -0 that nothing has been added yet: never -0 itself.  (As a
+// multiplication and an addition of their own: contracted, a negative product that underflows would stay -0.)
+template <typename V>
+__device__ __forceinline__ double dense_addend(V v)
+{
+#pragma clang fp contract(off)
+    return (double)v + 0.0;
+}
+
+// Whether something has been added to such an accumulator.
+__device__ __forceinline__ bool dense_there(double v) { return __double_as_longlong(v) != (long long)0x8000000000000000ull; }
+
 // ================================================== dense-range kernel ====
 // Dense accumulator (Section 2.2) over the row's own column range, for rows whose range [cmin, cmin + DS_MAX_COLS)
-// is no larger than the hash table they would get (Section 3.3, accumulator selection): one value and one presence
-// bit per column of the range in LDS, no keys, no probing, and the row leaves in column order by the bitmap's
-// prefix popcount.  QUERY: the presence bit is read first and set only when it is clear (Section 4.1).  A product
+// is no larger than the hash table they would get (Section 3.3, accumulator selection): an accumulator per column of
+// the range in LDS, no keys, no probing.  As in the dense windows of the heavy rows, -0 says that nothing has been added
+// to a column, so a product is one LDS add and nothing else; a ballot per 64 columns numbers the row's entries in
+// column order.  A product
 // outside the range (B's rows not in column order: the range was a guess) makes the row report overflow, like a
 // row with more entries than were reserved for it; the caller redoes such rows with hash tables.
 // COLS: columns the range may have (4096, or less where the rows' ranges allow it: what LDS a row takes decides how many
 // rows a compute unit works on, and every column is cleared and looked at.  100 000 rows of 2500 products in blocks of
 // 1000 columns: 842 us with 4096).
+// TILED: products in tiles of 64 entries of a row of B (tiles.hpp) instead of numbered one by one.  dspan_in_tiles says where.
+// What bounds it is what its waves issue and wait for, row by row: 60 000 rows in blocks of 1000 columns, rows of B of 50 entries, fp64,
+// numeric stage 393 us with presence bits that were read before they were set, 370 without them, 378 in tiles whose next
+// steps were loaded ahead (78 registers, 6 waves a SIMD), 342 in tiles loaded when they are used (55 registers, 8 waves): so
+// where fp64 values would cost the waves.  Rows of 78 entries 675, 605, 511, 467; blocks of 4000 columns (LDS for four waves),
+// 50 entries: 736, 650, 594, 605; fp32, 1000 columns, 50 entries: 347, 318, 289, 289.
 // PLACED: all rows in order, a workgroup each, which waits for the row's place in C (placed.hpp; rows, out_ptr and row_nnz are
 // not used); a product outside the range ends the attempt.  Workgroup 0 gives the places.
 constexpr int DS_THREADS = 256;
-template <typename V, bool QUERY, int COLS, bool PLACED>
-__global__ void __launch_bounds__(DS_THREADS)
+template <typename V, bool TILED, int COLS, bool PLACED>
+__global__ void __launch_bounds__(DS_THREADS, COLS <= 1024 ? 8 : COLS <= 2048 ? 7 : 4)   // (waves a SIMD that the LDS allows)
 k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, const V *__restrict__ a_val,
                 const int64_t *__restrict__ b_rp, const int32_t *__restrict__ b_col, const V *__restrict__ b_val,
                 const int32_t *__restrict__ rows, int64_t count, const int32_t *__restrict__ cmin,
                 const int64_t *__restrict__ out_ptr, int32_t *__restrict__ out_col, V *__restrict__ out_val,
                 int32_t *__restrict__ row_nnz, const Placing<V> p)
 {
-    constexpr int DS_WORDS = COLS / 32;
-    static_assert(DS_WORDS <= DS_THREADS, "one bitmap word per thread in the prefix sum");
-    using AV = acc_t<V>;
-    __shared__ AV s_vals[COLS];
-    __shared__ uint32_t s_bm[DS_WORDS];
-    __shared__ uint32_t s_pre[DS_WORDS];
-    __shared__ WgChunk<V, DS_THREADS> s_fc;
-    __shared__ int s_wave[DS_THREADS / WAVE];
+    constexpr int WAVES = DS_THREADS / WAVE;
+    constexpr int PER = COLS / DS_THREADS;   // a wave looks at PER times 64 columns that lie together
+    using Chunk = std::conditional_t<TILED, TileChunk<V, uint32_t, DS_THREADS>, WgChunk<V, DS_THREADS>>;
+    __shared__ double s_vals[COLS + (TILED ? WAVE : 0)];   // (behind the columns: a place per lane for what is no product)
+    __shared__ Chunk s_ch;
+    __shared__ uint32_t s_wave[WAVES];
     __shared__ int s_bad;
     __shared__ long long s_place;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
     if (PLACED && blockIdx.x == 0) {   // uniform
+        static_assert(sizeof(Turn) <= sizeof(s_vals), "the places are given from the accumulators' memory");
         place_units(p.counts, p.places, p.m, p.total, p.flags, p.placer_polls, *reinterpret_cast<Turn *>(s_vals));
         return;
     }
@@ -634,58 +653,84 @@ k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
     if (!PLACED && r >= count) return;
     const int64_t row = PLACED ? r : (int64_t)rows[r];
     const int32_t c0 = cmin[row];
-    for (int j = tid; j < COLS; j += DS_THREADS) s_vals[j] = (AV)0;
-    if (tid < DS_WORDS) s_bm[tid] = 0u;
+    for (int j = tid; j < COLS; j += DS_THREADS) s_vals[j] = -0.0;
     if (tid == 0) s_bad = 0;
-    __syncthreads();
-    wg_traverse<DS_THREADS, true>(a_col, a_val, a_rp[row], a_rp[row + 1],
-                                  [&](int32_t k, int64_t &p0, int64_t &len) { p0 = b_rp[k]; len = b_rp[k + 1] - p0; },
-                                  b_col, b_val, s_fc, [&](const auto &cj, const auto &cv) {
-                                      constexpr int U = sizeof(cj) / sizeof(cj[0]);
-#pragma unroll
-                                      for (int u = 0; u < U; ++u) {
-                                          if (cj[u] < 0) continue;
-                                          const uint32_t d = (uint32_t)(cj[u] - c0);   // (a column before c0 wraps to a large number)
-                                          if (d < (uint32_t)COLS) {
-                                              lds_add(&s_vals[d], (AV)cv[u]);
-                                              const uint32_t bit = 1u << (d & 31u);
-                                              if (!QUERY || !(s_bm[d >> 5] & bit)) atomicOr(&s_bm[d >> 5], bit);
-                                          } else {
-                                              s_bad = 1;
-                                          }
-                                      }
-                                  });
-    // (wg_traverse ends with a barrier)
-    const uint32_t word = tid < DS_WORDS ? s_bm[tid] : 0u;
-    int total;
-    const int ex = block_exclusive_scan_i32<DS_THREADS>(__popc(word), s_wave, total);
-    if (tid < DS_WORDS) s_pre[tid] = (uint32_t)ex;
-    // thread t looks at columns t, t + 256, ...: the lanes of a wave read consecutive values and the present ones
-    // among them go to consecutive places of the output
-    auto rank_of = [&](int j) {   // -1: column j of the range is not there
-        const uint32_t wbits = s_bm[j >> 5];
-        return (wbits >> (j & 31)) & 1u ? (int)s_pre[j >> 5] + __popc(wbits & ((1u << (j & 31)) - 1u)) : -1;
-    };
-    if constexpr (PLACED) {
-        if (tid == 0) {
-            if (s_bad) atomicOr(p.flags, FLAG_GAVE_UP);
-            post(p.counts + row, (uint32_t)total + 1u);
-        }
-        __syncthreads();
-        // what goes out is put together while the place is being found (not for the widest ranges: 48 registers)
-        constexpr int PER = COLS <= 2048 ? COLS / DS_THREADS : 1;
-        int rank[PER];
-        V val[PER];
-        if constexpr (COLS <= 2048) {
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                rank[i] = rank_of(i * DS_THREADS + tid);
-                val[i] = (V)s_vals[i * DS_THREADS + tid];
+    if constexpr (TILED) {
+        const int64_t e0 = a_rp[row], e1 = a_rp[row + 1];
+        uint32_t farthest = 0u;   // columns from c0 on, of this lane's products
+        for (int64_t base = e0; base < e1; base += DS_THREADS) {
+            const int64_t e = base + tid;
+            int64_t p0 = 0, len = 0;
+            V a = V();
+            if (e < e1) {
+                const int32_t k = a_col[e];
+                a = a_val[e];
+                p0 = b_rp[k];
+                len = b_rp[k + 1] - p0;
             }
+            if (base > e0) __syncthreads();   // (the chunk may still be read)
+            const int nent = e1 - base < DS_THREADS ? (int)(e1 - base) : DS_THREADS;
+            const uint32_t total = tile_open<DS_THREADS>(s_ch, nent, (uint32_t)p0, (uint32_t)len, a);   // (the accumulators are clear, too)
+            if (total == 0u) continue;   // uniform
+            Tiles<V, uint32_t> tiles;
+            constexpr bool AHEAD = sizeof(V) == 4 || COLS > 2048;
+            tile_walk<DS_THREADS, 2, true, AHEAD>(s_ch, nent, total, b_col, b_val, tiles, false, [&](const TileFour<V> (&f)[2], const Tiles<V, uint32_t> &t) {
+                const V av[2] = {row_lane<0>(t.a), row_lane<1>(t.a)};
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    if (f[u].skip >= 4) continue;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t d = (uint32_t)(f[u].col[i] - c0);   // (a column before c0 wraps to a large number)
+                        const bool own = i >= f[u].skip && f[u].col[i] >= 0;
+                        farthest = own && d > farthest ? d : farthest;
+                        lds_add(&s_vals[own && d < (uint32_t)COLS ? d : (uint32_t)(COLS + lane)], dense_addend(av[u] * f[u].val[i]));
+                    }
+                }
+            });
         }
-        if (tid < WAVE) {
+        if (farthest >= (uint32_t)COLS) s_bad = 1;
+        __syncthreads();
+    } else {
+        __syncthreads();
+        wg_traverse<DS_THREADS, true>(a_col, a_val, a_rp[row], a_rp[row + 1],
+                                      [&](int32_t k, int64_t &p0, int64_t &len) { p0 = b_rp[k]; len = b_rp[k + 1] - p0; },
+                                      b_col, b_val, s_ch, [&](const auto &cj, const auto &cv) {
+                                          constexpr int U = sizeof(cj) / sizeof(cj[0]);
+#pragma unroll
+                                          for (int u = 0; u < U; ++u) {
+                                              if (cj[u] < 0) continue;
+                                              const uint32_t d = (uint32_t)(cj[u] - c0);
+                                              if (d < (uint32_t)COLS) lds_add(&s_vals[d], dense_addend(cv[u]));
+                                              else s_bad = 1;
+                                          }
+                                      });
+        // (wg_traverse ends with a barrier)
+    }
+    const int j0 = wave * (COLS / WAVES) + lane;   // the lane's columns: j0, j0 + 64, ...
+    double v[PER];
+    unsigned long long there[PER];
+    uint32_t mine = 0u;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) v[i] = s_vals[j0 + i * WAVE];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        there[i] = __ballot(dense_there(v[i]));
+        mine += (uint32_t)__popcll(there[i]);
+    }
+    if (lane == 0) s_wave[wave] = mine;
+    __syncthreads();
+    uint32_t total;
+    const uint32_t before = waves_before_u32<WAVES>(s_wave, wave, total);
+    int64_t o;
+    if constexpr (PLACED) {
+        if (wave == 0) {
+            if (lane == 0) {
+                if (s_bad) atomicOr(p.flags, FLAG_GAVE_UP);
+                post(p.counts + row, total + 1u);
+            }
             const int64_t place = wait_for_place(p.places + row, p.flags, p.unit_polls);
-            if (tid == 0) {
+            if (lane == 0) {
                 s_place = place;
                 if (place >= 0) {
                     p.c_rp[row] = place;
@@ -694,41 +739,28 @@ k_numeric_dspan(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
             }
         }
         __syncthreads();
-        const int64_t o = s_place;
+        o = s_place;
         if (o < 0 || o + total > p.slots) return;   // uniform
-        if constexpr (COLS <= 2048) {
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                if (rank[i] >= 0) {
-                    out_col[o + rank[i]] = c0 + i * DS_THREADS + tid;
-                    out_val[o + rank[i]] = val[i];
-                }
-            }
-        } else {
-            for (int j = tid; j < COLS; j += DS_THREADS) {
-                const int rank_j = rank_of(j);
-                if (rank_j >= 0) {
-                    out_col[o + rank_j] = c0 + j;
-                    out_val[o + rank_j] = (V)s_vals[j];
-                }
-            }
-        }
     } else {
-        __syncthreads();
-        const int64_t o = out_ptr[row];
+        o = out_ptr[row];
         const int64_t cap = out_ptr[row + 1] - o;
         if (s_bad || (int64_t)total > cap) {   // uniform
             if (tid == 0) row_nnz[row] = -1;
             return;
         }
-        for (int j = tid; j < COLS; j += DS_THREADS) {
-            const int rank = rank_of(j);
-            if (rank >= 0) {
-                out_col[o + rank] = c0 + j;
-                out_val[o + rank] = (V)s_vals[j];
-            }
+        if (tid == 0) row_nnz[row] = (int)total;
+    }
+    int32_t *to_col = out_col + o;
+    V *to_val = out_val + o;
+    uint32_t at = before;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(there[i] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)there[i], at));
+        if ((there[i] >> lane) & 1ull) {
+            to_col[rank] = c0 + j0 + i * WAVE;
+            to_val[rank] = (V)v[i];
         }
-        if (tid == 0) row_nnz[row] = total;
+        at += (uint32_t)__popcll(there[i]);
     }
 }
 
@@ -740,12 +772,12 @@ static hipError_t dispatch_placed_span(const Csr &A, const Csr &B, const PlacedL
     const V *bv = static_cast<const V *>(B.val);
     V *ov = static_cast<V *>(l.out_val);
     const Placing<V> p{A.rows, l.c_rp, l.out_col, ov, l.slots, l.counts, l.places, l.total, l.flags, l.placer_polls, l.unit_polls};
-    const auto kernel = l.query_bitmap ? (l.span_cols <= 1024   ? k_numeric_dspan<V, true, 1024, true>
-                                          : l.span_cols <= 2048 ? k_numeric_dspan<V, true, 2048, true>
-                                                                : k_numeric_dspan<V, true, (int)DS_MAX_COLS, true>)
-                                       : (l.span_cols <= 1024   ? k_numeric_dspan<V, false, 1024, true>
-                                          : l.span_cols <= 2048 ? k_numeric_dspan<V, false, 2048, true>
-                                                                : k_numeric_dspan<V, false, (int)DS_MAX_COLS, true>);
+    const auto kernel = l.tiled ? (l.span_cols <= 1024   ? k_numeric_dspan<V, true, 1024, true>
+                                   : l.span_cols <= 2048 ? k_numeric_dspan<V, true, 2048, true>
+                                                         : k_numeric_dspan<V, true, (int)DS_MAX_COLS, true>)
+                                : (l.span_cols <= 1024   ? k_numeric_dspan<V, false, 1024, true>
+                                   : l.span_cols <= 2048 ? k_numeric_dspan<V, false, 2048, true>
+                                                         : k_numeric_dspan<V, false, (int)DS_MAX_COLS, true>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)(A.rows + 1)), dim3(DS_THREADS), 0, s, A.rp, A.col, av, B.rp, B.col, bv, nullptr, A.rows,
                        l.cmin, nullptr, l.out_col, ov, nullptr, p);
     return hipGetLastError();
@@ -940,18 +972,6 @@ __device__ __forceinline__ int hv_hide(int x)
     return x;
 }
 
-// A product as it is added to an accumulator that says by -0 that nothing has been added yet: never -0 itself.  (As a
-// multiplication and an addition of their own: contracted, a negative product that underflows would stay -0.)
-template <typename V>
-__device__ __forceinline__ double hv_addend(V v)
-{
-#pragma clang fp contract(off)
-    return (double)v + 0.0;
-}
-
-// Whether something has been added to an accumulator of a dense window.
-__device__ __forceinline__ bool hv_there(double v) { return __double_as_longlong(v) != (long long)0x8000000000000000ull; }
-
 // p[i], the byte offset in 32 bits (an address of one register beside the uniform p).
 template <typename T>
 __device__ __forceinline__ T *hv_at(T *p, uint32_t i) { return reinterpret_cast<T *>(reinterpret_cast<char *>(p) + i * (uint32_t)sizeof(T)); }
@@ -1112,7 +1132,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
 #pragma unroll
                                 for (int i = 0; i < 4; ++i) {
                                     const uint32_t d = (uint32_t)f[u].col[i] - col0;
-                                    lds_add(&s_vals[i >= f[u].skip && d < (uint32_t)HV_WIN ? d : dump], hv_addend(a[u] * f[u].val[i]));   // (d holds for a consistent table)
+                                    lds_add(&s_vals[i >= f[u].skip && d < (uint32_t)HV_WIN ? d : dump], dense_addend(a[u] * f[u].val[i]));   // (d holds for a consistent table)
                                 }
                             }
                         });
@@ -1127,7 +1147,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
 #pragma unroll
                 for (int i = 0; i < STEPS; ++i) {
                     s_vals[i * HV_THREADS + tid] = -0.0;
-                    const uint32_t n = (uint32_t)__popcll(__ballot(hv_there(v[i])));
+                    const uint32_t n = (uint32_t)__popcll(__ballot(dense_there(v[i])));
                     count = lane == i ? n : count;
                 }
                 if (lane < STEPS) s_grp[lane * HV_WAVES + wave] = count;
@@ -1144,7 +1164,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
                 V *to_val = out_val + o + done;
 #pragma unroll
                 for (int i = 0; i < STEPS; ++i) {
-                    const bool there = hv_there(v[i]);
+                    const bool there = dense_there(v[i]);
                     const unsigned long long all_there = __ballot(there);
                     const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(all_there >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all_there, 0u)) +
                                           wave_read_lane_u32(before, 4 * i + (wave >> 2));
@@ -1572,19 +1592,19 @@ static hipError_t dispatch(const Csr &A, const Csr &B, const NumLaunch &l, int /
     case NB_S8K: OCEAN_WG(13, 1024); break;
     case NB_DSPAN:
         if (l.cmin == nullptr) return hipErrorInvalidValue;
-#define OCEAN_DSPAN(QUERY, COLS)                                                                                          \
+#define OCEAN_DSPAN(TILED, COLS)                                                                                          \
     launch_in_pieces(l.count, 1, DS_THREADS, [&](int64_t first, int64_t n) {                                              \
-        hipLaunchKernelGGL((k_numeric_dspan<V, QUERY, COLS, false>), dim3((unsigned)n), dim3(DS_THREADS), 0, s, A.rp, A.col,   \
+        hipLaunchKernelGGL((k_numeric_dspan<V, TILED, COLS, false>), dim3((unsigned)n), dim3(DS_THREADS), 0, s, A.rp, A.col,   \
                            av, B.rp, B.col, bv, l.rows + first, n, l.cmin, l.out_ptr, l.out_col, ov, l.row_nnz,           \
                            Placing<V>{});                                                                                 \
     })
-#define OCEAN_DSPAN_COLS(QUERY)                                                                                           \
+#define OCEAN_DSPAN_COLS(TILED)                                                                                           \
     do {                                                                                                                  \
-        if (l.span_cols <= 1024) OCEAN_DSPAN(QUERY, 1024);                                                                \
-        else if (l.span_cols <= 2048) OCEAN_DSPAN(QUERY, 2048);                                                           \
-        else OCEAN_DSPAN(QUERY, (int)DS_MAX_COLS);                                                                        \
+        if (l.span_cols <= 1024) OCEAN_DSPAN(TILED, 1024);                                                                \
+        else if (l.span_cols <= 2048) OCEAN_DSPAN(TILED, 2048);                                                           \
+        else OCEAN_DSPAN(TILED, (int)DS_MAX_COLS);                                                                        \
     } while (0)
-        if (l.query_bitmap) OCEAN_DSPAN_COLS(true);
+        if (l.tiled) OCEAN_DSPAN_COLS(true);
         else OCEAN_DSPAN_COLS(false);
 #undef OCEAN_DSPAN_COLS
 #undef OCEAN_DSPAN

@@ -90,7 +90,7 @@ struct Ctx {
     // column-window boundary table of B for the dense kernel (null: heavy rows use global hash tables)
     uint32_t *bw = nullptr;
     int n_win = 0;
-    bool query_bitmap = false;
+    bool dspan_tiled = false;
     bool fine_buckets = false;
     unsigned sort_mask = 0;   // sort classes this call may use
 
@@ -630,7 +630,7 @@ int run_numeric(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int gb_l
         l.fine_buckets = c.fine_buckets;
         if (b == NB_DSPAN) {   // rows whose column range got them the dense accumulator over that range
             l.cmin = w.cmin;
-            l.query_bitmap = c.query_bitmap;
+            l.tiled = c.dspan_tiled;
         }
         if (c.bw != nullptr && b >= HEAVY_FROM && b < NB_GLOBAL) continue;   // went with the last bin, see below
         if (!esc && b == NB_E16) continue;   // same kernel as the 32-slot bin: one launch for both (adjacent row lists)
@@ -1015,7 +1015,7 @@ int run_placed(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, const Pla
     l.prod = w.prod;
     l.cmin = w.cmin;
     l.span_cols = how.span_cols;
-    l.query_bitmap = c.query_bitmap;
+    l.tiled = c.dspan_tiled;
     l.pool = w.four_rows_lds;
     l.c_rp = c_rp;
     l.counts = w.counts;
@@ -1214,10 +1214,9 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         OC_TRY(run_sample(c, w, A, &B, placing && S->max_row_products <= COUNT_PRODUCTS, (int)vbytes, n, sketches, m_regs, n_sample, o, S));
     }
 
-    // Section 4.1 / 4.3: dense accumulators query the bitmap before writing when the (sampled) CR is at least 2
-    // (the rows of a dense range; the symbolic bitmap kernel, whose only LDS operation per product is that OR, loses 14 %
-    // on R-MAT, sampled CR 2.5: it queries only when told to, bitmap_query = 2.  The dense windows of the heavy rows have no bits)
-    c.query_bitmap = o.bitmap_query >= 1 || (o.bitmap_query < 0 && S->sampled_rows > 0 && S->sampled_cr >= o.bitmap_query_cr);
+    c.dspan_tiled = dspan_in_tiles(B.nnz, S->products, A.nnz);
+    // Section 4.1 / 4.3: the dense accumulators have no presence bits to query, and the symbolic bitmap kernel, whose only LDS
+    // operation per product is the OR that a query could save, loses 14 % by it (R-MAT, sampled CR 2.5): only when told to
     const bool query_bitmap = o.bitmap_query == 2;
     Csr Bnum = B;   // what the numeric kernels read: B, or a copy of it with sorted rows (see below)
     bool tried_sorted_copy = false, sorted_copy = false;

@@ -164,7 +164,9 @@ __device__ __forceinline__ void tile_load(const Tiles<V, P> &t, const int32_t *_
 
 // Every product of the open chunk once: use(fours, t) for the lane's part of U steps at a time, t's first U (2 or 4).
 // mine: the wave's tiles (its first 64) where `found` says so, and on return where there are no more.
-template <int THREADS, int U, bool VALS, typename V, typename P, int N, typename F>
+// AHEAD: the next U steps are on their way while these are used.  That takes the registers of U steps more (13 U with
+// fp64 values), worth it where they don't cost waves in flight.
+template <int THREADS, int U, bool VALS, bool AHEAD = true, typename V, typename P, int N, typename F>
 __device__ __forceinline__ void tile_walk(const TileChunk<V, P, N> &c, int nent, uint32_t total, const int32_t *__restrict__ b_col,
                                           const V *__restrict__ b_val, Tiles<V, P> &mine, bool found, F use)
 {
@@ -177,14 +179,26 @@ __device__ __forceinline__ void tile_walk(const TileChunk<V, P, N> &c, int nent,
         if (!found || from > t0) mine.find(c, nent, total, from, t1);
         Tiles<V, P> t = mine;
         int left = (int)(t1 - from < WAVE ? t1 - from : WAVE);   // tiles
-        TileFour<V> f[U], g[U];
+        TileFour<V> f[U];
+        if constexpr (!AHEAD) {
+            static_assert(U == 2);
+            for (;; left -= U * TILE_STEP) {
+                tile_load<0, VALS>(t, b_col, b_val, f[0]);
+                tile_load<1, VALS>(t, b_col, b_val, f[1]);
+                use(f, t);
+                if (left <= U * TILE_STEP) break;
+                t.template advance<U>();
+            }
+            continue;
+        }
+        TileFour<V> g[U];
         tile_load<0, VALS>(t, b_col, b_val, f[0]);
         tile_load<1, VALS>(t, b_col, b_val, f[1]);
         if constexpr (U == 4) {
             tile_load<2, VALS>(t, b_col, b_val, f[2]);
             tile_load<3, VALS>(t, b_col, b_val, f[3]);
         }
-        for (; left > U * TILE_STEP; left -= U * TILE_STEP) {   // (the next steps are on their way while these are used)
+        for (; left > U * TILE_STEP; left -= U * TILE_STEP) {
             tile_load<U, VALS>(t, b_col, b_val, g[0]);
             tile_load<U + 1, VALS>(t, b_col, b_val, g[1]);
             if constexpr (U == 4) {
