@@ -91,6 +91,7 @@ struct Ctx {
     uint32_t *bw = nullptr;
     int n_win = 0;
     bool dspan_tiled = false;
+    int heavy_from = NB_S8K;   // smallest bin whose rows the column-window kernel takes where there is the window table
     bool fine_buckets = false;
     unsigned sort_mask = 0;   // sort classes this call may use
 
@@ -524,9 +525,7 @@ int run_numeric(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int gb_l
                 const unsigned long long *bin_prod, int64_t max_cap_global, double global_coef, const int64_t *out_ptr, int32_t *out_col, void *out_val,
                 int32_t *row_nnz, int queue_base, int stage, bool time_bins, bool esc)
 {
-    // With the window table, the column-window kernel takes every row beyond the 4096-slot table (measured:
-    // a row of the 8192-slot bin costs less there than a hash table of its own; smaller rows do not).
-    constexpr int HEAVY_FROM = NB_S8K;
+    const int heavy_from = c.heavy_from;
     int64_t start[NB_ALL + 1];
     start[0] = 0;
     for (int b = 0; b < NB_ALL; ++b) start[b + 1] = start[b] + (int64_t)count[b];
@@ -632,7 +631,7 @@ int run_numeric(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int gb_l
             l.cmin = w.cmin;
             l.tiled = c.dspan_tiled;
         }
-        if (c.bw != nullptr && b >= HEAVY_FROM && b < NB_GLOBAL) continue;   // went with the last bin, see below
+        if (c.bw != nullptr && b >= heavy_from && b < NB_GLOBAL) continue;   // went with the last bin, see below
         if (!esc && b == NB_E16) continue;   // same kernel as the 32-slot bin: one launch for both (adjacent row lists)
         if (!esc && b == NB_G8) {
             l.rows = w.bin_rows + start[NB_E16];
@@ -640,13 +639,13 @@ int run_numeric(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int gb_l
         }
         if (c.bw != nullptr && b == NB_GLOBAL) {
             // the windowed kernel takes the rows of those bins in one launch (their row lists are adjacent)
-            l.rows = w.bin_rows + start[HEAVY_FROM];
-            l.count = start[NB_GLOBAL + 1] - start[HEAVY_FROM];
+            l.rows = w.bin_rows + start[heavy_from];
+            l.count = start[NB_GLOBAL + 1] - start[heavy_from];
             // longest rows first (the kernel takes rows from the end of the list); skipped when memory is short
             const size_t sort_bytes = sort_rows_scratch_bytes(l.count);
             void *sort_tmp = sort_bytes ? c.alloc(sort_bytes) : nullptr;
             if (sort_tmp)
-                HIP_TRY(launch_sort_rows_by_products(w.prod, w.bin_rows + start[HEAVY_FROM], l.count, sort_tmp, c.s));
+                HIP_TRY(launch_sort_rows_by_products(w.prod, w.bin_rows + start[heavy_from], l.count, sort_tmp, c.s));
         }
         if (l.count == 0) continue;
         if (b == NB_HYBRID) {
@@ -1215,6 +1214,12 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     }
 
     c.dspan_tiled = dspan_in_tiles(B.nnz, S->products, A.nnz);
+    // Rows of the 8192-slot bin always cost less in the column-window kernel than in hash tables.  Those of the 4096-slot bin do
+    // where rows of B fill its tiles by half: 12 000 rows of 3040 products, fp64, symbolic workflow, whole call hashed and in
+    // windows, 16384 / 262144 / 1048576 columns: rows of B of 8 entries 810 -> 999, 1142 -> 1175, 1378 -> 3102 us; of 16
+    // 783 -> 844, 1362 -> 969, 1614 -> 2232; of 32 775 -> 721, 1814 -> 1440, 2065 -> 1709; of 256 1069 -> 802, 1804 -> 1290,
+    // 4317 -> 3715.  R-MAT of scale 14 642 -> 619 us, of scale 18 (16 windows) 13.03 -> 12.86 ms; scale 20 (64) 105.6 and 105.8.
+    c.heavy_from = dense_window_count(n, dtype) <= 32 && S->products >= 32 * A.nnz ? NB_S4K : NB_S8K;
     // Section 4.1 / 4.3: the dense accumulators have no presence bits to query, and the symbolic bitmap kernel, whose only LDS
     // operation per product is the OR that a query could save, loses 14 % by it (R-MAT, sampled CR 2.5): only when told to
     const bool query_bitmap = o.bitmap_query == 2;

@@ -1,0 +1,42 @@
+"""Rows of the 4096-slot bin, which go with the heavy rows through the column-window kernel where rows of B have 32 entries on
+average and there are at most 32 windows of 16384 columns, and keep their hash tables elsewhere, against the CPU oracle."""
+import numpy as np
+import pytest
+
+from oracle import spgemm as O
+from paper_2604_19004_amd.workloads import CSR
+from test_gpu_spgemm import check_result
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ob():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2604_19004_amd import binding
+    binding.load()
+    return binding
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("length", [31, 32])
+@pytest.mark.parametrize("n", [16384, 32 * 16384, 32 * 16384 + 1])
+def test_rows_on_both_sides_of_the_line(ob, n, length, dtype):
+    rng = np.random.default_rng(n + length)
+
+    def csr(rows, cols):
+        ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64)
+        idx = np.concatenate(rows).astype(np.int32)
+        return CSR(len(rows), cols, ptr, idx, rng.uniform(-1, 1, idx.size).astype(dtype))
+    B = csr([np.sort(rng.choice(n, length, replace=False)) for _ in range(2000)], n)
+    # (rows of 1400 to 2700 entries take 4096 slots; one row is beyond 8192; short ones and an empty one between them)
+    sizes = [45, 60, 75, 84, 2, 0, 30] * 30 + [700]
+    A = csr([np.sort(rng.choice(2000, k, replace=False)) for k in sizes], 2000)
+    ref = O.multiply_rows(A, B)
+    dA, dB = ob.to_device(A), ob.to_device(B)
+    for kw in (dict(workflow=ob.WF_SYMBOLIC), dict(workflow=ob.WF_HLL), dict(workflow=ob.WF_UPPER_BOUND), dict(force_hash_kernels=1)):
+        C, st = ob.spgemm(dA, dB, **kw)
+        check_result(C, ref, A, f"n={n} length={length} {kw}")
+        if kw.get("workflow") == ob.WF_SYMBOLIC:
+            assert st["rows_per_bin"][ob.bin_layout()[0].index(4096)] > 0
