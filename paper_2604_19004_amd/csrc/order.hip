@@ -89,59 +89,169 @@ k_order_scatter(const int64_t *__restrict__ prod, const int32_t *__restrict__ ro
 // ---- a copy of B with every row's entries in column order -------------------------------------------
 // Needed when B's rows come unsorted and so much work sits in heavy rows that the kernels which accumulate
 // in global memory would be bound by atomic throughput (the case Section 5.4 reports for the enhanced hash
-// accumulator): the column-window kernel needs sorted rows.  One workgroup per row: column ids and the
-// entries' positions go to LDS, a bitonic network orders them, the values follow their positions (indirect
-// sort, Section 4.2).  Rows longer than SB_MAX are copied unsorted: flags |= 16 and the caller keeps B as it is.
+// accumulator): the column-window kernel needs sorted rows.
+// Rows of up to SB_SHORT entries: a wave per row, up to two entries a lane, and every entry's place is the number of entries
+// before it - each key is read from its lane once and compared with all, so the values go straight to their places.
+// Longer rows: a workgroup per row.  A bitmap over the columns numbers them (prefix popcounts), and every entry goes to its
+// column's number; where B has many columns, or a column comes twice, (column id, position) pairs in LDS are ordered by a
+// bitonic network instead and the values follow their positions (indirect sort, Section 4.2); its steps of at most 64 places
+// stay within a wave and need no barrier.  Rows longer than SB_MAX are copied unsorted: flags |= 16 and the caller keeps B
+// as it is.
+// R-MAT of scale 15, 216 000 entries in 32768 rows, of which a few hold thousands, fp64: 100 us with a workgroup of 256 threads and
+// a network for every row, 78 (28 + 50) without the bitmap and with up to 256 entries for a wave, 43 (20 + 23) as it is (whole call 838 -> 749).
 namespace {
-constexpr int SB_THREADS = 256;
+constexpr int SB_GROUPS = 2;
+constexpr int SB_SHORT = SB_GROUPS * WAVE;
+constexpr int SB_WAVES = 4;
+constexpr int SB_THREADS = 1024;
 constexpr int SB_MAX = 4096;
+constexpr int SB_WORDS = SB_MAX * 2;          // of the bitmap, in the pairs' memory
+constexpr int64_t SB_MAX_COLS = 4ll * 32 * SB_WORDS;   // four turns of the bitmap
 
 template <typename V>
-__global__ void __launch_bounds__(SB_THREADS)
-k_sort_b_rows(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, const V *__restrict__ val, int64_t rows,
-              int32_t *__restrict__ col_out, V *__restrict__ val_out, int32_t *flags)
+__global__ void __launch_bounds__(WAVE * SB_WAVES)
+k_sort_b_short(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, const V *__restrict__ val, int64_t rows,
+               int32_t *__restrict__ col_out, V *__restrict__ val_out)
 {
-    __shared__ int32_t s_key[SB_MAX];
-    __shared__ uint16_t s_pos[SB_MAX];
-    for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
+    const int lane = lane_id();
+    const int64_t stride = (int64_t)gridDim.x * SB_WAVES;
+    for (int64_t row = (int64_t)blockIdx.x * SB_WAVES + __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE); row < rows; row += stride) {
         const int64_t p0 = rp[row];
         const int64_t full = rp[row + 1] - p0;
-        const int len = (int)(full > SB_MAX + 1 ? SB_MAX + 1 : full);
-        if (len > SB_MAX) {   // uniform: copied as it is, so that the copy stays a valid matrix (its column ids are in range)
-            if (threadIdx.x == 0) atomicOr(flags, 16);
-            for (int64_t i = threadIdx.x; i < full; i += SB_THREADS) { col_out[p0 + i] = col[p0 + i]; val_out[p0 + i] = val[p0 + i]; }
-            continue;
+        if (full > SB_SHORT) continue;   // uniform for the wave
+        const int len = (int)full;
+        const int groups = (len + WAVE - 1) / WAVE;
+        uint32_t key[SB_GROUPS];   // (the lane's entries: number lane and 64 + lane; the largest number where there is none)
+        int32_t place[SB_GROUPS] = {};
+#pragma unroll
+        for (int q = 0; q < SB_GROUPS; ++q) key[q] = q * WAVE + lane < len ? (uint32_t)col[p0 + q * WAVE + lane] : ~0u;
+#pragma unroll
+        for (int g = 0; g < SB_GROUPS; ++g) {
+            if (g >= groups) break;   // uniform
+            const int n = len - g * WAVE < WAVE ? len - g * WAVE : WAVE;
+            for (int j = 0; j < n; ++j) {
+                const uint32_t k = wave_read_lane_u32(key[g], j);
+#pragma unroll
+                for (int q = 0; q < SB_GROUPS; ++q) {   // (equal columns stay in their order)
+                    if (q >= groups) break;
+                    const bool before = q == g ? k < key[q] || (k == key[q] && j < lane) : q > g ? k <= key[q] : k < key[q];
+                    place[q] += before;
+                }
+            }
         }
-        if (len <= 1) {
-            if (len == 1 && threadIdx.x == 0) { col_out[p0] = col[p0]; val_out[p0] = val[p0]; }
-            continue;
+#pragma unroll
+        for (int q = 0; q < SB_GROUPS; ++q) {
+            if (q * WAVE + lane < len) {
+                col_out[p0 + place[q]] = (int32_t)key[q];
+                val_out[p0 + place[q]] = val[p0 + q * WAVE + lane];
+            }
         }
-        int n = 2;
-        while (n < len) n <<= 1;
-        for (int i = threadIdx.x; i < n; i += SB_THREADS) {
-            s_key[i] = i < len ? col[p0 + i] : SORT_PAD;
-            s_pos[i] = (uint16_t)i;
-        }
+    }
+}
+
+// Workgroup b has rows b, b + gridDim.x, ... that are longer than SB_SHORT.
+template <typename V>
+__global__ void __launch_bounds__(SB_THREADS)
+k_sort_b_long(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, const V *__restrict__ val, int64_t rows,
+              int64_t cols, int32_t *__restrict__ col_out, V *__restrict__ val_out, int32_t *flags)
+{
+    __shared__ unsigned long long s_key[SB_MAX];   // column id, position
+    __shared__ uint16_t s_pre[SB_WORDS];           // entries before each word of the bitmap
+    __shared__ uint32_t s_sum[SB_THREADS / WAVE];
+    uint32_t *const s_bits = reinterpret_cast<uint32_t *>(s_key);
+    __shared__ unsigned long long s_long[SB_THREADS / WAVE];
+    const int tid = threadIdx.x;
+    for (int64_t from = blockIdx.x; from < rows; from += (int64_t)gridDim.x * SB_THREADS) {
+        const int64_t mine = from + (int64_t)tid * gridDim.x;
+        const unsigned long long there = __ballot(mine < rows && rp[mine < rows ? mine + 1 : 0] - rp[mine < rows ? mine : 0] > SB_SHORT);
+        if (lane_id() == 0) s_long[tid / WAVE] = there;
         __syncthreads();
-        for (int k = 2; k <= n; k <<= 1) {
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                for (int i = threadIdx.x; i < (n >> 1); i += SB_THREADS) {
-                    const int lo = ((i & ~(j - 1)) << 1) | (i & (j - 1));
-                    const int hi = lo | j;
-                    const int32_t x = s_key[lo], y = s_key[hi];
-                    if ((x > y) == ((lo & k) == 0)) {
-                        s_key[lo] = y; s_key[hi] = x;
-                        const uint16_t t = s_pos[lo]; s_pos[lo] = s_pos[hi]; s_pos[hi] = t;
+        for (int w = 0; w < SB_THREADS / WAVE; ++w) {
+            for (unsigned long long left = s_long[w]; left != 0ull; left &= left - 1ull) {   // uniform
+                const int64_t row = from + (int64_t)(w * WAVE + __ffsll(left) - 1) * gridDim.x;
+                const int64_t p0 = rp[row];
+                const int64_t full = rp[row + 1] - p0;
+                if (full > SB_MAX) {   // uniform: copied as it is, so that the copy stays a valid matrix (its column ids are in range)
+                    if (tid == 0) atomicOr(flags, 16);
+                    for (int64_t i = tid; i < full; i += SB_THREADS) { col_out[p0 + i] = col[p0 + i]; val_out[p0 + i] = val[p0 + i]; }
+                    continue;
+                }
+                const int len = (int)full;
+                bool done = cols <= SB_MAX_COLS;
+                uint32_t before = 0u;   // entries with columns of the turns before
+                for (int64_t c0 = 0; done && c0 < cols; c0 += 32 * SB_WORDS) {   // (all uniform)
+                    const int words = (int)(cols - c0 < 32 * SB_WORDS ? (cols - c0 + 31) / 32 : SB_WORDS);
+                    const int per = (words + SB_THREADS - 1) / SB_THREADS;
+                    for (int i = tid; i < words; i += SB_THREADS) s_bits[i] = 0u;
+                    __syncthreads();
+                    bool twice = false;
+                    for (int i = tid; i < len; i += SB_THREADS) {
+                        const int64_t d = (int64_t)col[p0 + i] - c0;
+                        if (d < 0 || d >= 32 * (int64_t)words) continue;
+                        const uint32_t bit = 1u << (d & 31);
+                        twice |= (atomicOr(&s_bits[d >> 5], bit) & bit) != 0u;
+                    }
+                    if (__syncthreads_or(twice)) {
+                        done = false;
+                        break;
+                    }
+                    uint32_t mine = 0u;
+                    for (int i = tid * per; i < (tid + 1) * per && i < words; ++i) mine += (uint32_t)__popc(s_bits[i]);
+                    const uint32_t incl = wave_inclusive_scan_u32(mine);
+                    if (lane_id() == WAVE - 1) s_sum[tid / WAVE] = incl;
+                    __syncthreads();
+                    uint32_t all;
+                    uint32_t run = waves_before_u32<SB_THREADS / WAVE>(s_sum, tid / WAVE, all) + incl - mine;
+                    for (int i = tid * per; i < (tid + 1) * per && i < words; ++i) {
+                        s_pre[i] = (uint16_t)run;
+                        run += (uint32_t)__popc(s_bits[i]);
+                    }
+                    __syncthreads();
+                    for (int i = tid; i < len; i += SB_THREADS) {
+                        const int32_t c = col[p0 + i];
+                        const int64_t d = (int64_t)c - c0;
+                        if (d < 0 || d >= 32 * (int64_t)words) continue;
+                        const uint32_t at = before + s_pre[d >> 5] + (uint32_t)__popc(s_bits[d >> 5] & ((1u << (d & 31)) - 1u));
+                        col_out[p0 + at] = c;
+                        val_out[p0 + at] = val[p0 + i];
+                    }
+                    before += all;
+                    __syncthreads();   // the bitmap is cleared for the next turn or row
+                }
+                if (done && before == (uint32_t)len) continue;
+                __syncthreads();
+                int n = 2 * SB_SHORT;
+                while (n < len) n <<= 1;
+                for (int i = tid; i < n; i += SB_THREADS)
+                    s_key[i] = i < len ? ((unsigned long long)(uint32_t)col[p0 + i] << 32) | (uint32_t)i : ~0ull;
+                __syncthreads();
+                for (int k = 2; k <= n; k <<= 1) {
+                    for (int j = k >> 1; j > 0; j >>= 1) {
+                        for (int i = tid; i < (n >> 1); i += SB_THREADS) {
+                            const int lo = ((i & ~(j - 1)) << 1) | (i & (j - 1));
+                            const int hi = lo | j;
+                            const unsigned long long x = s_key[lo], y = s_key[hi];
+                            if ((x > y) == ((lo & k) == 0)) { s_key[lo] = y; s_key[hi] = x; }
+                        }
+                        // pairs i .. i + 63 of a wave lie in 128 places of its own while j <= 64
+                        if (j > WAVE || (j == 1 && k >= 2 * WAVE)) {
+                            __syncthreads();
+                        } else {
+                            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                            __builtin_amdgcn_wave_barrier();
+                        }
                     }
                 }
                 __syncthreads();
+                for (int i = tid; i < len; i += SB_THREADS) {
+                    const unsigned long long x = s_key[i];
+                    col_out[p0 + i] = (int32_t)(x >> 32);
+                    val_out[p0 + i] = val[p0 + (uint32_t)x];
+                }
+                __syncthreads();   // the places are rewritten for the next row
             }
         }
-        for (int i = threadIdx.x; i < len; i += SB_THREADS) {
-            col_out[p0 + i] = s_key[i];
-            val_out[p0 + i] = val[p0 + s_pos[i]];
-        }
-        __syncthreads();   // the arrays are rewritten for the next row
+        __syncthreads();
     }
 }
 }  // namespace
@@ -149,13 +259,20 @@ k_sort_b_rows(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, c
 hipError_t launch_sort_b_rows(const Csr &B, int dtype, int32_t *col_out, void *val_out, int32_t *flags, hipStream_t s)
 {
     if (B.rows == 0 || B.nnz == 0) return hipSuccess;
-    const int64_t blocks = B.rows < 65536 ? B.rows : 65536;
-    if (dtype == OCEAN_F64)
-        hipLaunchKernelGGL(k_sort_b_rows<double>, dim3((unsigned)blocks), dim3(SB_THREADS), 0, s, B.rp, B.col,
-                           static_cast<const double *>(B.val), B.rows, col_out, static_cast<double *>(val_out), flags);
-    else
-        hipLaunchKernelGGL(k_sort_b_rows<float>, dim3((unsigned)blocks), dim3(SB_THREADS), 0, s, B.rp, B.col,
-                           static_cast<const float *>(B.val), B.rows, col_out, static_cast<float *>(val_out), flags);
+    const int64_t waves = (B.rows + SB_WAVES - 1) / SB_WAVES;
+    const dim3 short_grid((unsigned)(waves < 65536 ? waves : 65536));
+    // (an odd number: long rows of a power-law matrix are powers of two apart)
+    const dim3 long_grid((unsigned)(B.rows < 1023 ? B.rows : 1023));
+    auto launch = [&](auto zero) {
+        using V = decltype(zero);
+        const V *val = static_cast<const V *>(B.val);
+        V *out = static_cast<V *>(val_out);
+        hipLaunchKernelGGL(k_sort_b_short<V>, short_grid, dim3(WAVE * SB_WAVES), 0, s, B.rp, B.col, val, B.rows, col_out, out);
+        hipLaunchKernelGGL(k_sort_b_long<V>, long_grid, dim3(SB_THREADS), 0, s, B.rp, B.col, val, B.rows, B.cols,
+                           col_out, out, flags);
+    };
+    if (dtype == OCEAN_F64) launch(0.0);
+    else launch(0.0f);
     return hipGetLastError();
 }
 
