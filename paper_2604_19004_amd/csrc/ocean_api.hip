@@ -415,6 +415,12 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
     // (the row lists of consecutive bins are adjacent).
     const bool wide_bitmap = B.cols <= (1 << 20);
     const bool few_apart = B.cols <= SYMBOLIC_FEW_COLS;   // rows of few products have a launch of smaller workgroups
+    // That launch takes the rows of the 4096-slot bin, too, where rows of B fill the bitmap kernel's tiles: 12 000 rows of 3040
+    // products, predict stage with key tables and with bitmaps, 16384 / 131072 / 262144 columns: rows of B of 16 entries
+    // 186 -> 113, 199 -> 141, 195 -> 145 us, of 32 181 -> 107, 194 -> 122, 199 -> 129, of 64 181 -> 105, 197 -> 112, 199 -> 119;
+    // rows of 1200 products: of 16 112 -> 101, 105 -> 119, 104 -> 122, of 32 111 -> 101, 106 -> 107, 107 -> 113, of 64
+    // 113 -> 100, 107 -> 104, 110 -> 110.
+    const int few_from = few_apart && st->er >= (B.cols <= SYMBOLIC_FEW_COLS / 2 ? 32.0 : 64.0) ? SB_S4K : SB_S16K;
     for (int round = first_round; round < 2; ++round) {
         const bool assisted = round == 0 && assist_cr > 1.0;
         BinParams bp{};
@@ -458,12 +464,12 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
             if (b == SB_SPAN) l.count = by_range;
             if (wide_bitmap && b == SB_S32K) {
                 if (!few_apart) continue;
-                l.rows = w.bin_rows + start[SB_S16K];
-                l.count = start[SB_BITMAP] - start[SB_S16K];
+                l.rows = w.bin_rows + start[few_from];
+                l.count = start[SB_BITMAP] - start[few_from];
                 l.bin = SB_BITMAP;
                 l.few = true;
             }
-            if (wide_bitmap && b == SB_S16K) continue;
+            if (wide_bitmap && b >= few_from && b <= SB_S16K) continue;
             if (wide_bitmap && b == SB_BITMAP && !few_apart) {
                 l.rows = w.bin_rows + start[SB_S16K];
                 l.count = start[SB_COUNT] - start[SB_S16K];

@@ -40,3 +40,24 @@ def test_rows_on_both_sides_of_the_line(ob, n, length, dtype):
         check_result(C, ref, A, f"n={n} length={length} {kw}")
         if kw.get("workflow") == ob.WF_SYMBOLIC:
             assert st["rows_per_bin"][ob.bin_layout()[0].index(4096)] > 0
+
+
+@pytest.mark.parametrize("length", [31, 32, 63, 64])
+@pytest.mark.parametrize("n", [16384, 1 << 17, (1 << 17) + 1, 1 << 18, (1 << 18) + 1])
+def test_counts_on_both_sides_of_the_line(ob, n, length):
+    """Rows of 1025 to 4096 products are counted by a bitmap where rows of B have 32 entries (64 beyond 2^17 columns)."""
+    rng = np.random.default_rng(n + length)
+
+    def csr(rows, cols):
+        ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64)
+        idx = np.concatenate(rows).astype(np.int32)
+        return CSR(len(rows), cols, ptr, idx, rng.uniform(-1, 1, idx.size))
+    B = csr([np.sort(rng.choice(n, length, replace=False)) for _ in range(2000)], n)
+    A = csr([np.sort(rng.choice(2000, k, replace=False)) for k in [1025 // length + 1, 50, 4096 // length, 3, 0, 4096 // length + 1, 600, 1100] * 30], 2000)
+    ref = O.multiply_rows(A, B)
+    dA, dB = ob.to_device(A), ob.to_device(B)
+    for kw in (dict(), dict(bitmap_query=2), dict(assisted_symbolic=2)):
+        counts, _ = ob.symbolic(dA, dB, opt=ob.default_options(**kw))
+        assert np.array_equal(counts.cpu().numpy(), np.diff(ref.row_ptr)), f"{kw}"
+    C, _ = ob.spgemm(dA, dB, workflow=ob.WF_SYMBOLIC)
+    check_result(C, ref, A, f"n={n} length={length}")
