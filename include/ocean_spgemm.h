@@ -190,7 +190,7 @@ typedef struct ocean_stats {
     float total_ms;            /* host wall clock of the call */
     /* per numeric bin (first attempt only): kernel time from events on the call's stream, and the
      * work it covered: intermediate products, entries of A read, entries of C produced.  When B's rows
-     * are sorted and some row outgrows the largest LDS hash table, the rows of the last three bins of
+     * are sorted and some row outgrows the largest LDS hash table, the rows of the last three (or four) bins of
      * ocean_bin_layout run in ONE launch of the column-window kernel: its time is reported under the last
      * bin and bin_ms of the two before it is 0.  Rows of few products are sorted instead of hashed, in one launch
      * per size class whatever their bins (a class whose rows merge into few columns: in one hash table): a launch's

@@ -911,7 +911,7 @@ k_numeric_hybrid(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a
 }
 
 // ======================================================== heavy kernel ====
-// Rows whose output exceeds the 4096-slot LDS table, when B's rows are sorted.
+// Rows whose output exceeds the 4096-slot LDS table (or the 2048-slot one, see heavy_from), when B's rows are sorted.
 // The column range is cut into windows of HV_WIN columns and
 // bw[k*(n_win+1)+w] is the position in B's arrays of the first entry of row k
 // with column >= w*HV_WIN, so any run of windows can be visited on its own.  One
