@@ -192,7 +192,7 @@ typedef struct ocean_stats {
      * work it covered: intermediate products, entries of A read, entries of C produced.  When B's rows
      * are sorted and some row outgrows the largest LDS hash table, the rows of the last three (or four) bins of
      * ocean_bin_layout run in ONE launch of the column-window kernel: its time is reported under the last
-     * bin and bin_ms of the two before it is 0.  Rows of few products are sorted instead of hashed, in one launch
+     * bin and bin_ms of those before it is 0.  Rows of few products are sorted instead of hashed, in one launch
      * per size class whatever their bins (a class whose rows merge into few columns: in one hash table): a launch's
      * time is reported under the bin that holds most of its products.  Where every row is one of those (at most 2048
      * products and 64 entries of A), or the columns of every row lie in a short range, nothing else was asked for and
