@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "ocean_internal.hpp"
+#include "units.hpp"
 
 using namespace ocean;
 
@@ -1029,6 +1030,7 @@ int run_placed(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, const Pla
     l.flags = &w.sc->flags;
     l.placer_polls = g_placer_polls;
     l.unit_polls = g_unit_polls;
+    l.by_xcd = units_by_xcd(c.n_cu);
     int64_t place_words = w.place_words;
     if (how.span_cols != 0) {   // (units of one row)
         place_words = m + (m + 1) / 2;

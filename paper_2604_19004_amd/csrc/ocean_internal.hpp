@@ -441,6 +441,7 @@ struct PlacedLaunch {
     unsigned long long *total;    // receives the entries of C
     int32_t *flags;           // |= 32: a wait ran out and the result is not complete
     int placer_polls, unit_polls;   // polls, about a microsecond each, after which waits run out
+    bool by_xcd;              // units_by_xcd of the device (units.hpp)
 };
 hipError_t launch_placed(const Csr &A, const Csr &B, int dtype, const PlacedLaunch &l, hipStream_t s);
 hipError_t launch_placed_span(const Csr &A, const Csr &B, int dtype, const PlacedLaunch &l, hipStream_t s);   // numeric.hip; units of a row

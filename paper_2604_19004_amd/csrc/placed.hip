@@ -300,12 +300,7 @@ k_placed_wave(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_co
         place_units(p.counts, p.places, (p.m + 3) / 4, p.total, p.flags, p.placer_polls, *reinterpret_cast<Turn *>(s_pool));
         return;
     }
-    // Workgroups go to the eight XCDs in turn; of every 64 units, eight neighbours go to one, whose L2 then has the rows of B (and
-    // the lines of A and C) that they share: clustered input 1.96 -> 1.93 ms, rectangular 1.240 -> 1.222.  (A unit may so wait for some
-    // that are dispatched after it, all of these 64, which the chip holds at a time.)
-    int64_t unit = (int64_t)blockIdx.x - 1;
-    const int64_t base = unit & ~(int64_t)63;
-    if (base + 64 <= (p.m + 3) / 4) unit = base + (unit & 7) * 8 + ((unit >> 3) & 7);
+    const int64_t unit = unit_of_workgroup((int64_t)blockIdx.x - 1, (p.m + 3) / 4, p.by_xcd);
     const int64_t row = unit * 4 + wave;
     if (threadIdx.x == 0) {
         s_four.arrived = 0u;
@@ -379,7 +374,7 @@ static hipError_t dispatch_placed(const Csr &A, const Csr &B, const PlacedLaunch
 {
     const V *av = static_cast<const V *>(A.val);
     const V *bv = static_cast<const V *>(B.val);
-    const Placing<V> p{A.rows, l.c_rp, l.out_col, static_cast<V *>(l.out_val), l.slots, l.counts, l.places, l.total, l.flags, l.placer_polls, l.unit_polls};
+    const Placing<V> p{A.rows, l.c_rp, l.out_col, static_cast<V *>(l.out_val), l.slots, l.counts, l.places, l.total, l.flags, l.placer_polls, l.unit_polls, l.by_xcd};
     const unsigned blocks = (unsigned)(placed_units(A.rows, l.cls) + 1);
 #define OCEAN_GROUP(CLS, G, PPT)                                                                                         \
     case CLS:                                                                                                           \

@@ -8,12 +8,13 @@
 // back over the units before it, because thousands of units are between their two steps at any time: each would
 // read that many words.
 //
-// Every wait ends: units wait only for units of lower numbers, which are dispatched before them, and whatever the order
-// of dispatch, the number of polls is limited.  A wait that runs out leaves bit 32 in flags and the call goes
+// Every wait ends: units wait only for units of lower numbers, which their XCD starts before them (units.hpp), and whatever the
+// order in which workgroups start, the number of polls is limited.  A wait that runs out leaves bit 32 in flags and the call goes
 // another way.  Workgroup 0 is dispatched first and holds its place until the last unit has published.
 #pragma once
 
 #include "ocean_internal.hpp"
+#include "units.hpp"
 
 namespace ocean {
 
@@ -128,6 +129,7 @@ struct Placing {
     unsigned long long *total;
     int32_t *flags;
     int placer_polls, unit_polls;   // before workgroup 0 and a unit give up
+    bool by_xcd;                    // unit_of_workgroup's
 };
 
 }  // namespace ocean
