@@ -246,7 +246,30 @@ def to_device(m, device="cuda:0") -> DeviceCSR:
                      torch.from_numpy(m.val).to(device))
 
 
-_allocators = weakref.WeakValueDictionary()   # by the ctx that their struct carries
+class _Blocks:
+    """The memory of one allocator: torch tensors by their address."""
+
+    def __init__(self, device):
+        torch = _torch()
+        self.device = device
+        self.held: dict[int, object] = {}
+        self._empty, self._uint8 = torch.empty, torch.uint8
+
+    def alloc(self, nbytes, out):
+        try:
+            t = self._empty(max(int(nbytes), 1), dtype=self._uint8, device=self.device)
+        except Exception:   # out of memory -> the library reports OCEAN_EALLOC
+            return 1
+        ptr = t.data_ptr()
+        self.held[ptr] = t
+        out[0] = ptr
+        return 0
+
+    def release(self, ptr):
+        self.held.pop(int(ptr), None)
+
+
+_allocators = weakref.WeakValueDictionary()   # _Blocks by the ctx that their struct carries
 _allocator_ids = itertools.count(1)
 
 
@@ -263,31 +286,24 @@ def _release(ctx, ptr):
 
 class TorchAllocator:
     """ocean_allocator whose memory comes from torch's caching allocator, one for every call.  The C callbacks of its struct are
-    shared by all and find theirs by ctx: a pair of callbacks of its own takes 22 us to make."""
+    shared by all and find theirs by ctx: a pair of callbacks of its own takes 22 us to make.  The struct keeps the memory alive:
+    it works as long as it, or a pointer to it, is held."""
 
     _shared = (ALLOC_FN(_alloc), RELEASE_FN(_release))
 
     def __init__(self, device):
-        torch = _torch()
-        self.device = device
-        self.blocks: dict[int, object] = {}
-        self._empty, self._uint8 = torch.empty, torch.uint8
+        self._blocks = _Blocks(device)
+        self.device, self.blocks = device, self._blocks.held
         ctx = next(_allocator_ids)
-        _allocators[ctx] = self
+        _allocators[ctx] = self._blocks
         self.struct = ocean_allocator(ctx, *self._shared)
+        self.struct.blocks = self._blocks   # (not self: no cycle is left behind for every call)
 
     def alloc(self, nbytes, out):
-        try:
-            t = self._empty(max(int(nbytes), 1), dtype=self._uint8, device=self.device)
-        except Exception:   # out of memory -> the library reports OCEAN_EALLOC
-            return 1
-        ptr = t.data_ptr()
-        self.blocks[ptr] = t
-        out[0] = ptr
-        return 0
+        return self._blocks.alloc(nbytes, out)
 
     def release(self, ptr):
-        self.blocks.pop(int(ptr), None)
+        self._blocks.release(ptr)
 
     @functools.cached_property
     def _alloc_cb(self):
