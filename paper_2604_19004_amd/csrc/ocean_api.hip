@@ -1320,7 +1320,9 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
             unchecked = false;
             S->symbolic_overflow_rows = (int64_t)c.h->ovf_count;
             if (c.h->ovf_count == 0) break;
+            OC_TRY(mark(c, OCEAN_ST_PREDICT));
             OC_TRY(run_symbolic(c, w, A, B, gb_log2, S->assist_cr, query_bitmap, w.nnz_final, S, 1, nullptr));
+            OC_TRY(mark(c, OCEAN_ST_BINNING));
         }
         total_slots = (int64_t)c.h->totals[0];
         for (int b = 0; b < NB_ALL; ++b) {
@@ -1379,7 +1381,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     // ---- numeric ----
     {   // (the first launch marks the stage, unless the heavy rows are put in order before theirs)
         unsigned long long heavy = 0;
-        for (int b = NB_S8K; b < NB_COUNT; ++b) heavy += bin_count[b];
+        for (int b = c.bw != nullptr ? c.heavy_from : NB_S8K; b < NB_COUNT; ++b) heavy += bin_count[b];
         if (heavy > 0) OC_TRY(mark(c, OCEAN_ST_NUMERIC));
     }
     // expand-sort-compress needs every row of its bins to have no more products than lanes (true when the bins come

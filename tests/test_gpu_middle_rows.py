@@ -61,3 +61,25 @@ def test_counts_on_both_sides_of_the_line(ob, n, length):
         assert np.array_equal(counts.cpu().numpy(), np.diff(ref.row_ptr)), f"{kw}"
     C, _ = ob.spgemm(dA, dB, workflow=ob.WF_SYMBOLIC)
     check_result(C, ref, A, f"n={n} length={length}")
+
+
+def test_stage_of_the_order(ob):
+    """Rows of the 4096-slot bin alone: putting them in order for the column-window kernel is part of the numeric stage.  (Three
+    kernels, a fill and a copy, against the two kernels of the binning stage; the least of many calls.)"""
+    n = 16384
+    rng = np.random.default_rng(7)
+
+    def csr(rows, cols):
+        ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64)
+        idx = np.concatenate(rows).astype(np.int32)
+        return CSR(len(rows), cols, ptr, idx, rng.uniform(-1, 1, idx.size))
+    B = csr([np.sort(rng.choice(n, 40, replace=False)) for _ in range(3000)] + [np.sort(rng.choice(2500, 40, replace=False)) for _ in range(600)], n)
+    # (the last row has more than 8192 products, on 2500 columns, so that the window table is built)
+    A = csr([np.sort(rng.choice(3000, 60, replace=False)) for _ in range(5000)] + [np.arange(3000, 3600)], 3600)
+    dA, dB = ob.to_device(A), ob.to_device(B)
+    least = {}
+    for hashed in (0, 1):
+        calls = [ob.spgemm(dA, dB, workflow=ob.WF_SYMBOLIC, force_hash_kernels=hashed)[1] for _ in range(30)]
+        assert calls[0]["rows_per_bin"][ob.bin_layout()[0].index(4096)] > 4000 and sum(calls[0]["rows_per_bin"][8:11]) == 0
+        least[hashed] = min(st["stage_ms"]["binning"] for st in calls)
+    assert least[0] < least[1] + 0.008, least   # ms; the order takes about 20 us
