@@ -105,15 +105,17 @@ typedef struct ocean_options {
                                         Rows whose table fills up are recounted with product-sized tables */
     double assist_sigmas;            /* conservative CR = max(1, mean - assist_sigmas * std) of the per-row ratio
                                         products / estimate over the sampled rows (1.0) */
-    int32_t bitmap_query;            /* a column's presence bit is read and set only when it is clear (Section 4.1): 2 in
-                                        the bitmap kernel of the symbolic pass (where it measured slower); 0, 1 and -1
-                                        (default) nowhere, as the dense accumulators of the numeric pass have no bits */
+    int32_t bitmap_query;            /* a column's presence bit is read and set only when it is clear (Section 4.1): 0 never;
+                                        1 in the column windows of the numeric pass that are walked product by product (those in
+                                        tiles, and the dense ranges, have no bits); 2 also in the bitmap kernel of the
+                                        symbolic pass (where it measured slower); -1 (default) as 1 when a sampled CR is known
+                                        and >= bitmap_query_cr */
     int32_t esc_short_rows;          /* 1: rows with at most 16 / 32 intermediate products are accumulated by
                                         expand-sort-compress, 4 / 2 rows per wave, wherever accumulators are sized from
                                         the product bound (upper-bound workflow, retry; Section 3.3); 0 (default): by the
                                         8-lanes-per-row hash kernel, which measured faster on this GPU (one product per
                                         lane leaves the sort network's lanes a quarter as busy) */
-    double bitmap_query_cr;          /* 2.0 (Section 4.3); without effect, see bitmap_query */
+    double bitmap_query_cr;          /* 2.0 (Section 4.3) */
     int32_t selector;                /* OCEAN_SEL_MI355X (default) or OCEAN_SEL_TABLE1 (the paper's thresholds as printed) */
     int32_t compact_in_place;        /* estimation workflows: rows are compacted inside the temporary output, which then
                                         becomes C (col_idx / val stay as large as the reservation), instead of into a

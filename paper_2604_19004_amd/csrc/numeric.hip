@@ -9,11 +9,12 @@
 //   k_numeric_wg      one workgroup per row, keys + values + sort buffer in LDS (512..8192 slots)
 //   k_numeric_hybrid  32768 keys in LDS, values accumulated in a global slab (Section 3.3,
 //                     enhanced hash accumulator); rows leave sorted through an LDS bitmap rank
-//   k_numeric_heavy   rows beyond the 4096-slot table when B's rows are sorted: column windows, each
-//                     accumulated in LDS either densely (values + bitmap, Section 2.2 dense
-//                     accumulator iterated over the row's column range as in Section 3.2) or, for
-//                     sparse stretches of several windows, by staging the products in LDS and
-//                     adding them at the bitmap rank of their column (no hash table)
+//   k_numeric_heavy   rows beyond the 4096-slot table (or the 2048-slot one) when B's rows are sorted: column
+//                     windows, each accumulated in LDS either densely (Section 2.2 dense accumulator iterated over
+//                     the row's column range as in Section 3.2) or, for stretches of several light windows, at the
+//                     bitmap rank of the product's column (no hash table); products in tiles of 64
+//   k_numeric_heavy_flat  rows beyond the 4096-slot table where the pieces of rows of B are short: the same
+//                     windows, products numbered one by one
 //   k_numeric_global  whole table in global memory, and k_numeric_hybrid: the path of such rows
 //                     when B's rows are unsorted (or the window table would be too large)
 //
@@ -911,7 +912,8 @@ k_numeric_hybrid(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a
 }
 
 // ======================================================== heavy kernel ====
-// Rows whose output exceeds the 4096-slot LDS table (or the 2048-slot one, see heavy_from), when B's rows are sorted.
+// Rows whose output exceeds the 4096-slot LDS table (or the 2048-slot one, see choose_heavy), when B's rows are sorted and the
+// pieces that a pass finds of them fill tiles by half (heavy_in_tiles).
 // The column range is cut into windows of HV_WIN columns and
 // bw[k*(n_win+1)+w] is the position in B's arrays of the first entry of row k
 // with column >= w*HV_WIN, so any run of windows can be visited on its own.  One
@@ -1314,6 +1316,372 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
     }
 }
 
+// ================================ heavy kernel, product by product ====
+// The same rows where the pieces of rows of B that a pass finds are short, so that tiles of 64 entries would be mostly empty
+// (heavy_in_tiles says where): the products of a pass are numbered one by one, and a lane has one at a time, whatever
+// the lengths of the pieces.  Windows and window table are k_numeric_heavy's; a pass is
+//   * a window with more products than a sparse pass can stage: HV_WIN accumulators and a presence bitmap in LDS, one
+//     LDS add and one LDS or per product; the bitmap's prefix popcount places each present column at its sorted position;
+//   * consecutive windows whose products fit the staging memory left beside their bitmap (a sparse stretch: up to 8192
+//     products over 10 windows, fewer over more): an expand-sort-compress accumulator whose sort is a bitmap rank.  Every
+//     product is written to LDS at its own number (no atomics), or stays in its thread's registers, and marks its
+//     column in a bitmap over the stretch; the prefix popcount of the bitmap is the position of each column in the
+//     output, so a second sweep over the products adds each value at its column's rank.
+// What bounds it is the gather of B's entries, at what the memory system gives for pieces this short, and the search for the
+// entry of every product.  2000 rows of 24 000 products on 262 144 columns, fp64, numeric stage in tiles and here: rows of B
+// of 2 entries 4493 and 1994 us, of 8 2996 and 1496, of 32 1469 and 1079, of 64 936 and 833, of 512 746 and 819.
+constexpr int HF_THREADS = 1024;
+constexpr int HF_REGION = 131072;                  // bytes of LDS that hold the accumulator of a pass
+constexpr int HF_PPT = 8;                          // products of a sparse pass per thread, at most
+constexpr int HF_HCAP = HF_PPT * HF_THREADS;       // products one sparse pass takes at most: 8192
+constexpr int HF_RPT = 48;                         // chunks of up to 48 products per thread find their entries by rank
+                                                   // (most dense windows then do: 96.8 -> 94.9 ms; 4 KB more LDS)
+
+// QUERY: dense windows read a column's presence bit and set it only when it is clear (Section 4.1).
+template <typename V, bool QUERY>
+__global__ void __launch_bounds__(HF_THREADS)
+k_numeric_heavy_flat(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col, const V *__restrict__ a_val,
+                const uint32_t *__restrict__ bw, int n_win, const int32_t *__restrict__ b_col,
+                const V *__restrict__ b_val, const int32_t *__restrict__ rows, int64_t count,
+                unsigned long long *queue, const int64_t *__restrict__ out_ptr, int32_t *__restrict__ out_col,
+                V *__restrict__ out_val, int32_t *__restrict__ row_nnz)
+{
+    constexpr int WIN = HV_WIN;
+    constexpr int WORDS = HV_WIN / 32;
+    // one 128 KB region, used either as the dense window or as a sparse pass's products, bitmap and prefix counts
+    __shared__ __align__(16) unsigned char s_u[HF_REGION];
+    __shared__ uint32_t s_dbm[WORDS];
+    __shared__ WgChunk<V, HF_THREADS, HF_RPT> s_fc;
+    __shared__ int s_wave[HF_THREADS / WAVE];
+    __shared__ uint32_t s_pw[HV_MAXWIN + 1];   // s_pw[w]: products of the row in the windows before w
+    __shared__ int s_ovf;
+    __shared__ unsigned long long s_alloc;   // wg_flat_chunk_keep's
+    __shared__ long long s_row;
+    static_assert(WORDS <= HF_THREADS, "the prefix counts of a dense window reuse the chunk's array of prefix sums");
+    uint32_t *s_dpre = s_fc.excl;   // (free between the traversal of a pass and the next one)
+    using AV = acc_t<V>;
+    static_assert(sizeof(AV) == 8 && HF_REGION == WIN * 8, "a region full of accumulators is a window");
+    AV *s_vals = reinterpret_cast<AV *>(s_u);                                      // dense: WIN accumulators
+    // sparse pass: staged products (column, value) by product number; once every thread holds its
+    // products in registers the same memory takes the output (columns, accumulated values) by rank
+    // Its memory is laid out per pass: the more windows a stretch spans, the more of the region goes to
+    // the bitmap (WIN/8 bytes per window) and its prefix counts (WIN/16), the less to staged products
+    // (4 + sizeof(AV) bytes each, in multiples of one product per thread).
+    constexpr int OV = WIN / 8 + WIN / 16;
+    auto sparse_cap = [](int run) {
+        const int c = (HF_REGION - run * OV) / (4 + (int)sizeof(AV)) / HF_THREADS * HF_THREADS;
+        return c > HF_HCAP ? HF_HCAP : (c < 0 ? 0 : c);
+    };
+    int32_t *s_scol = reinterpret_cast<int32_t *>(s_u);
+    const int tid = threadIdx.x;
+    const size_t stride = (size_t)n_win + 1;
+
+    for (int j = tid; j < WIN; j += HF_THREADS) s_vals[j] = (AV)0;
+    for (int j = tid; j < WORDS; j += HF_THREADS) s_dbm[j] = 0u;
+    bool dense_clean = true;   // the region is an all-zero dense window
+    bool chunk_clean = false;  // the traversal's marks are as wg_flat_chunk_keep leaves them
+
+    for (;;) {
+        if (tid == 0) {
+            s_row = (long long)atomicAdd(queue, 1ull);
+            s_ovf = 0;
+        }
+        for (int w = tid; w <= n_win; w += HF_THREADS) s_pw[w] = 0u;
+        __syncthreads();
+        if (s_row >= count) break;   // uniform exit
+        const int64_t r = count - 1 - s_row;   // from the end of the list, where the rows with the largest bounds are
+        const int64_t row = rows[r];
+        const int64_t e0 = a_rp[row], e1 = a_rp[row + 1];
+        const int64_t o = out_ptr[row];
+        const int64_t cap = out_ptr[row + 1] - o;
+        const int64_t ne = e1 - e0;
+        long long done = 0;
+
+        // the first HF_THREADS entries of the row stay in registers over all passes
+        int32_t ek = 0;
+        V ea = V();
+        if (tid < ne) { ek = a_col[e0 + tid]; ea = a_val[e0 + tid]; }
+        // ---- products of the row per window: one (entry, window) pair per thread and step
+        {
+            const int de = HF_THREADS / n_win, dw = HF_THREADS % n_win;
+            int64_t e = tid / n_win;
+            int w = tid % n_win;
+            while (e < ne) {
+                // four pairs per turn, so that their dependent loads (entry -> boundaries) overlap
+                int64_t pe[4];
+                int pw[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    pe[i] = e; pw[i] = w;
+                    e += de;
+                    w += dw;
+                    if (w >= n_win) { w -= n_win; ++e; }
+                }
+                int32_t k[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) k[i] = pe[i] < ne ? a_col[e0 + pe[i]] : 0;
+                uint32_t d[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t *t = bw + (size_t)k[i] * stride;
+                    d[i] = pe[i] < ne ? t[pw[i] + 1] - t[pw[i]] : 0u;
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (d[i]) atomicAdd(&s_pw[pw[i] + 1], d[i]);
+            }
+        }
+        __syncthreads();
+        {   // counts -> running sums (n_win <= HV_MAXWIN <= HF_THREADS: one window per thread)
+            const int mine = tid < n_win ? (int)s_pw[tid + 1] : 0;
+            int all;
+            const int before = block_exclusive_scan_i32<HF_THREADS>(mine, s_wave, all);
+            if (tid < n_win) s_pw[tid + 1] = (uint32_t)(before + mine);
+        }
+        __syncthreads();
+
+        // ---- walk the windows, pass by pass
+        // next pass from window `from` on: a window with more products than a sparse pass can stage (dense),
+        // or a run of windows whose products fit the staging memory that is left beside the run's bitmap
+        // (sparse); p0 == n_win when nothing is left
+        // Every wave plans for itself, 64 windows at a look: lane l holds the running sum behind window
+        // from + l, a ballot finds the first window with products, and since the products of a stretch
+        // grow with its length while its capacity shrinks, a second ballot finds how far the stretch goes.
+        const int lane = tid & (WAVE - 1);
+        auto plan = [&](int from, int &p0, int &p1, bool &pdense) {
+            p0 = n_win; p1 = n_win; pdense = false;
+            for (int x = from; x < n_win; x += WAVE) {   // uniform
+                const uint32_t before = s_pw[x];
+                const int wl = x + lane;   // this lane's window
+                const uint32_t upto = s_pw[(wl < n_win ? wl : n_win - 1) + 1] - before;   // products of [x, wl]
+                const unsigned long long some = __ballot(wl < n_win && upto > 0u);
+                if (some == 0ull) continue;
+                const int k = __ffsll((long long)some) - 1;   // windows x .. x+k-1 are empty
+                const unsigned long long fits = __ballot(lane >= k && wl < n_win && upto <= (uint32_t)sparse_cap(lane - k + 1));
+                // lanes k, k+1, ... that fit in a row: the stretch
+                const unsigned long long stop = ~(fits >> k);
+                const int run = stop ? __ffsll((long long)stop) - 1 : WAVE - k;
+                p0 = x + k;
+                pdense = run == 0;
+                p1 = p0 + (run == 0 ? 1 : run);
+                return;
+            }
+        };
+        int w, w1;
+        bool dense;
+        plan(0, w, w1, dense);
+        // window boundaries of this thread's entry: those of the next pass are fetched one pass ahead
+        const bool have0 = tid < ne;
+        const uint32_t *t0 = bw + (size_t)ek * stride;
+        uint32_t c_lo = have0 ? t0[w] : 0u, c_hi = have0 ? t0[w1] : 0u;
+        while (w < n_win) {
+            int nx0, nx1;
+            bool nxdense;
+            plan(w1, nx0, nx1, nxdense);
+            // (no entry has products in the windows skipped between two passes: the next pass starts at c_hi)
+            const uint32_t n_hi = have0 ? t0[nx1] : 0u;
+            // memory of a sparse pass (see above)
+            const int scap = sparse_cap(w1 - w);
+            AV *s_sval = reinterpret_cast<AV *>(s_u + (size_t)scap * 4);
+            uint16_t *s_hpre = reinterpret_cast<uint16_t *>(s_u + (size_t)scap * (4 + sizeof(AV)));
+            uint32_t *s_hbm = reinterpret_cast<uint32_t *>(s_u + (size_t)scap * (4 + sizeof(AV)) + (size_t)(w1 - w) * (WIN / 16));
+            const int hwords = (w1 - w) * (WIN / 32);
+            // accumulator of this pass
+            if (dense) {
+                if (!dense_clean) {
+                    for (int j = tid; j < WIN; j += HF_THREADS) s_vals[j] = (AV)0;
+                    dense_clean = true;
+                }
+            } else {
+                for (int j = tid; j < (w1 - w) * (WIN / 32); j += HF_THREADS) s_hbm[j] = 0u;
+                dense_clean = false;
+            }
+            // (no barrier: the traversal below has barriers of its own before the first product arrives)
+            // products of windows [w, w1)
+            const int32_t col0 = w * WIN;
+            uint32_t staged = 0;   // products of this pass staged so far (sparse pass, uniform)
+            auto f = [&](const auto &cj, const auto &cv, uint32_t q0) {
+                constexpr int U = sizeof(cj) / sizeof(cj[0]);
+                if (dense) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const unsigned d = (unsigned)(cj[u] - col0);
+                        if (cj[u] >= 0 && d < (unsigned)WIN) {   // d is in range for a consistent window table
+                            lds_add(&s_vals[d], (AV)cv[u]);
+                            // Section 4.1: with many products per output entry most presence bits are set already;
+                            // reading the bit first then saves the write (a stale read only costs a redundant OR)
+                            const uint32_t bit = 1u << (d & 31);
+                            if (!QUERY || !(s_dbm[d >> 5] & bit)) atomicOr(&s_dbm[d >> 5], bit);
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const uint32_t at = staged + q0 + (uint32_t)u * WAVE + (uint32_t)(tid & (WAVE - 1));
+                        const uint32_t d = (uint32_t)(cj[u] - col0);
+                        if (cj[u] >= 0 && at < (uint32_t)scap && d < (uint32_t)hwords * 32u) {   // both hold by construction
+                            s_scol[at] = cj[u];
+                            s_sval[at] = (AV)cv[u];
+                            atomicOr(&s_hbm[d >> 5], 1u << (d & 31u));
+                        }
+                    }
+                }
+            };
+            if (!dense && ne <= HF_THREADS) {
+                // ---- sparse pass of a row whose entries fit one chunk: no staging, every product stays in the
+                // registers of the thread that fetched it, from the sweep that marks the columns to the sweep
+                // that adds the values at their ranks
+                constexpr int NBATCH = HF_PPT / FLAT_U;
+                static_assert(HF_PPT % FLAT_U == 0, "whole batches");
+                int32_t kc[HF_PPT];
+                V kv[HF_PPT];
+                auto mark = [&](int32_t col) {
+                    const uint32_t d = (uint32_t)(col - col0);
+                    if (d < (uint32_t)hwords * 32u) atomicOr(&s_hbm[d >> 5], 1u << (d & 31u));   // holds by construction
+                };
+                bool fits;
+                wg_flat_chunk_keep<HF_THREADS, NBATCH>(s_fc, (int)ne, (int64_t)c_lo, c_hi - c_lo, ea, b_col, b_val, kc, kv,
+                                                       mark, fits, chunk_clean, s_alloc);
+                chunk_clean = true;
+                if (!fits && tid == 0) s_ovf = 1;   // cannot happen: passes are planned from the counts
+                const int wpt = (hwords + HF_THREADS - 1) / HF_THREADS;   // bitmap words per thread (consecutive)
+                int mine = 0;
+                for (int q = 0; q < wpt; ++q) {
+                    const int j = tid * wpt + q;
+                    if (j < hwords) mine += __popc(s_hbm[j]);
+                }
+                int htotal;
+                int run = block_exclusive_scan_i32<HF_THREADS, false>(mine, s_wave, htotal);   // (barrier below)
+                for (int q = 0; q < wpt; ++q) {
+                    const int j = tid * wpt + q;
+                    if (j < hwords) { s_hpre[j] = (uint16_t)run; run += __popc(s_hbm[j]); }
+                }
+                for (int i = tid; i < htotal; i += HF_THREADS) s_sval[i] = (AV)0;   // (htotal <= products <= scap)
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < HF_PPT; ++i) {
+                    const uint32_t d = (uint32_t)(kc[i] - col0);
+                    if (kc[i] >= 0 && d < (uint32_t)hwords * 32u) {
+                        const int rank = (int)s_hpre[d >> 5] + __popc(s_hbm[d >> 5] & ((1u << (d & 31u)) - 1u));
+                        s_scol[rank] = kc[i];           // products of one column all write the same id
+                        lds_add(&s_sval[rank], (AV)kv[i]);
+                    }
+                }
+                __syncthreads();
+                const long long room = cap - done;
+                const int n_out = (long long)htotal < room ? htotal : (room > 0 ? (int)room : 0);
+                for (int i = tid; i < n_out; i += HF_THREADS) {
+                    __builtin_nontemporal_store(s_scol[i], &out_col[o + done + i]);
+                    __builtin_nontemporal_store((V)s_sval[i], &out_val[o + done + i]);
+                }
+                done += htotal;
+                __syncthreads();
+            } else {
+                for (int64_t base = 0; base < ne; base += HF_THREADS) {
+                    int32_t k = ek;
+                    V a = ea;
+                    const bool have = base + tid < ne;
+                    if (base > 0 && have) { k = a_col[e0 + base + tid]; a = a_val[e0 + base + tid]; }
+                    uint32_t c0 = c_lo, c1 = c_hi;
+                    if (base > 0) {
+                        c0 = c1 = 0;
+                        if (have) {
+                            const uint32_t *t = bw + (size_t)k * stride;
+                            c0 = t[w];
+                            c1 = t[w1];
+                        }
+                    }
+                    const int64_t left = ne - base;
+                    staged += wg_flat_chunk<HF_THREADS, true>(s_fc, left < HF_THREADS ? (int)left : HF_THREADS, (int64_t)c0,
+                                                              c1 - c0, a, b_col, b_val, f);
+                    chunk_clean = false;
+                }
+                if (dense) {
+                    // ---- dense window -> output, in column order
+                    const uint32_t word = tid < WORDS ? s_dbm[tid] : 0u;
+                    int wtotal;
+                    const int ex = block_exclusive_scan_i32<HF_THREADS>(__popc(word), s_wave, wtotal);
+                    if (tid < WORDS) s_dpre[tid] = (uint32_t)ex;
+                    __syncthreads();
+                    // Thread t looks at columns t, t + 1024, ...: in every step the lanes of a wave read
+                    // consecutive values (no LDS bank conflicts) and the present ones among them go to
+                    // consecutive places of the output (coalesced stores).
+                    constexpr int STEPS = WIN / HF_THREADS;
+#pragma unroll 4
+                    for (int i = 0; i < STEPS; ++i) {
+                        const int j = i * HF_THREADS + tid;
+                        const uint32_t wbits = s_dbm[j >> 5];
+                        if ((wbits >> (j & 31)) & 1u) {
+                            const long long rank = done + (long long)s_dpre[j >> 5] + __popc(wbits & ((1u << (j & 31)) - 1u));
+                            const V val = (V)s_vals[j];
+                            s_vals[j] = (AV)0;
+                            if (rank < cap) { __builtin_nontemporal_store((int32_t)(col0 + j), &out_col[o + rank]); __builtin_nontemporal_store(val, &out_val[o + rank]); }
+                        }
+                    }
+                    __syncthreads();
+                    if (tid < WORDS) s_dbm[tid] = 0u;
+                    done += wtotal;
+                    __syncthreads();
+                } else {
+                    // ---- sparse pass: rank of every column = set bits below it in the bitmap of the stretch
+                    const int wpt = (hwords + HF_THREADS - 1) / HF_THREADS;   // bitmap words per thread (consecutive)
+                    int mine = 0;
+                    for (int q = 0; q < wpt; ++q) {
+                        const int j = tid * wpt + q;
+                        if (j < hwords) mine += __popc(s_hbm[j]);
+                    }
+                    int htotal;
+                    int run = block_exclusive_scan_i32<HF_THREADS, false>(mine, s_wave, htotal);   // (barrier below)
+                    for (int q = 0; q < wpt; ++q) {
+                        const int j = tid * wpt + q;
+                        if (j < hwords) { s_hpre[j] = (uint16_t)run; run += __popc(s_hbm[j]); }
+                    }
+                    __syncthreads();
+                    // every thread takes its share of the staged products into registers, with their ranks
+                    if (staged > (uint32_t)scap) staged = scap;   // cannot happen: passes are planned from the counts
+                    int32_t pc[HF_PPT];
+                    AV pv[HF_PPT];
+                    int pr[HF_PPT];
+#pragma unroll
+                    for (int i = 0; i < HF_PPT; ++i) {
+                        const uint32_t at = (uint32_t)i * HF_THREADS + tid;
+                        pc[i] = -1; pv[i] = AV(); pr[i] = 0;
+                        if (at < staged) {
+                            pc[i] = s_scol[at];
+                            pv[i] = s_sval[at];
+                            s_sval[at] = (AV)0;   // (htotal <= staged: the values of the output start from zero)
+                            const uint32_t d = (uint32_t)(pc[i] - col0);
+                            pr[i] = (int)s_hpre[d >> 5] + __popc(s_hbm[d >> 5] & ((1u << (d & 31u)) - 1u));
+                        }
+                    }
+                    __syncthreads();
+                    // the staging memory becomes the output of the pass: columns and values by rank
+#pragma unroll
+                    for (int i = 0; i < HF_PPT; ++i) {
+                        if (pc[i] >= 0) {
+                            s_scol[pr[i]] = pc[i];          // products of one column all write the same id
+                            lds_add(&s_sval[pr[i]], pv[i]);
+                        }
+                    }
+                    __syncthreads();
+                    const long long room = cap - done;
+                    const int n_out = (long long)htotal < room ? htotal : (room > 0 ? (int)room : 0);
+                    for (int i = tid; i < n_out; i += HF_THREADS) {
+                        __builtin_nontemporal_store(s_scol[i], &out_col[o + done + i]);
+                        __builtin_nontemporal_store((V)s_sval[i], &out_val[o + done + i]);
+                    }
+                    done += htotal;
+                    __syncthreads();
+                }
+            }
+            c_lo = c_hi; c_hi = n_hi;
+            w = nx0; w1 = nx1; dense = nxdense;
+        }
+        if (tid == 0) row_nnz[row] = (s_ovf || done > cap) ? -1 : (int32_t)done;
+        __syncthreads();
+    }
+}
+
 // Positions of the column-window boundaries inside every row of B:
 // bw[k*(n_win+1)+w] = first position p in row k with col[p] >= w*win (row end if none).
 // One 16-lane group per row; a row of WT_LONG or more entries is left to the whole workgroup (every entry is
@@ -1617,7 +1985,11 @@ static hipError_t dispatch(const Csr &A, const Csr &B, const NumLaunch &l, int /
                                static_cast<uint2 *>(l.pairs), l.out_ptr, l.out_col, ov, l.row_nnz);
         break;
     case NB_GLOBAL:
-        if (l.bw != nullptr)
+        if (l.bw != nullptr && !l.tiled) {
+            const auto kernel = l.query_bitmap ? k_numeric_heavy_flat<V, true> : k_numeric_heavy_flat<V, false>;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)l.n_wg), dim3(HF_THREADS), 0, s, A.rp, A.col, av, l.bw,
+                               l.n_win, B.col, bv, l.rows, l.count, l.queue, l.out_ptr, l.out_col, ov, l.row_nnz);
+        } else if (l.bw != nullptr)
             hipLaunchKernelGGL((k_numeric_heavy<V>), dim3((unsigned)l.n_wg), dim3(HV_THREADS), 0, s, A.rp, A.col, av, l.bw,
                                l.n_win, B.col, bv, l.rows, l.count, l.queue, l.out_ptr, l.out_col, ov, l.row_nnz);
         else

@@ -92,7 +92,10 @@ struct Ctx {
     uint32_t *bw = nullptr;
     int n_win = 0;
     bool dspan_tiled = false;
-    int heavy_from = NB_S8K;   // smallest bin whose rows the column-window kernel takes where there is the window table
+    bool middle_in_windows = false;   // the column-window kernel takes rows of the 4096-slot bin, too, where it walks in tiles
+    int heavy_from = NB_S8K;   // smallest bin whose rows the column-window kernels take where there is the window table
+    bool heavy_tiled = true;   // in tiles (see choose_heavy)
+    bool query_bitmap = false;
     bool fine_buckets = false;
     unsigned sort_mask = 0;   // sort classes this call may use
 
@@ -525,6 +528,20 @@ double conservative_cr(const ocean_stats *S, const ocean_options &o)
     return v > 1.0 ? v : 1.0;
 }
 
+// How the rows that go through column windows are walked, from the rows, products and entries of A per key, and the smallest
+// bin of them.
+void choose_heavy(Ctx &c, const Csr &B, const unsigned long long *count, const unsigned long long *prod, const unsigned long long *entries)
+{
+    double rows = 0.0, products = 0.0, nnz_a = 0.0;
+    for (int b = NB_S8K; b < NB_COUNT; ++b) {
+        rows += (double)count[b];
+        products += (double)prod[b];
+        nnz_a += (double)entries[b];
+    }
+    c.heavy_tiled = B.nnz >= TILE_MIN_ENTRIES && (rows > 0.0 ? heavy_in_tiles(products, rows, nnz_a, c.n_win) : c.middle_in_windows);
+    c.heavy_from = c.heavy_tiled && c.middle_in_windows ? NB_S4K : NB_S8K;
+}
+
 // ---- numeric bins ------------------------------------------------------------------------------------
 // Launches every non-empty bin, largest tables first.  Scratch for the hybrid
 // and global bins is obtained here and kept until the caller releases all.
@@ -666,6 +683,8 @@ int run_numeric(Ctx &c, Work &w, const Csr &A, const Csr &B, int dtype, int gb_l
         } else if (b == NB_GLOBAL && c.bw != nullptr) {
             l.bw = c.bw;
             l.n_win = c.n_win;
+            l.tiled = c.heavy_tiled;
+            l.query_bitmap = c.query_bitmap;
             const int64_t resident = (int64_t)c.n_cu * heavy_workgroups_per_cu();
             l.n_wg = (int)(l.count < resident ? l.count : resident);
             l.queue = &w.sc->queue[queue_base + 1];
@@ -1177,7 +1196,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     // needs the window boundaries inside every (sorted) row of B.  Built only when such rows can exist
     // and the table stays small; otherwise, or when a row of B turns out unsorted, they use global tables.
     uint32_t *bw_try = nullptr;
-    if (max_ub > kNumericSlots[NB_S8K] && B.nnz < 0xffffffffLL && B.nnz >= TILE_MIN_ENTRIES && !o.force_hash_kernels) {
+    if (max_ub > kNumericSlots[NB_S8K] && B.nnz < 0xffffffffLL && !o.force_hash_kernels) {
         const int nw = dense_window_count(n, dtype);
         const size_t bytes = (size_t)B.rows * ((size_t)nw + 1) * 4;
         if (nw <= 512 && bytes <= ((size_t)6 << 30)) {   // the heavy-row kernel plans at most 512 windows per row
@@ -1222,14 +1241,16 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     }
 
     c.dspan_tiled = dspan_in_tiles(B.nnz, S->products, A.nnz);
-    // Rows of the 8192-slot bin always cost less in the column-window kernel than in hash tables.  Those of the 4096-slot bin do
-    // where rows of B fill its tiles by half: 12 000 rows of 3040 products, fp64, symbolic workflow, whole call hashed and in
+    // Rows of the 8192-slot bin always cost less in column windows than in hash tables.  Those of the 4096-slot bin do
+    // where rows of B fill the tiles by half: 12 000 rows of 3040 products, fp64, symbolic workflow, whole call hashed and in
     // windows, 16384 / 262144 / 1048576 columns: rows of B of 8 entries 810 -> 999, 1142 -> 1175, 1378 -> 3102 us; of 16
     // 783 -> 844, 1362 -> 969, 1614 -> 2232; of 32 775 -> 721, 1814 -> 1440, 2065 -> 1709; of 256 1069 -> 802, 1804 -> 1290,
     // 4317 -> 3715.  R-MAT of scale 14 642 -> 619 us, of scale 18 (16 windows) 13.03 -> 12.86 ms; scale 20 (64) 105.6 and 105.8.
-    c.heavy_from = dense_window_count(n, dtype) <= 32 && S->products >= 32 * A.nnz ? NB_S4K : NB_S8K;
-    // Section 4.1 / 4.3: the dense accumulators have no presence bits to query, and the symbolic bitmap kernel, whose only LDS
-    // operation per product is the OR that a query could save, loses 14 % by it (R-MAT, sampled CR 2.5): only when told to
+    c.middle_in_windows = dense_window_count(n, dtype) <= 32 && S->products >= 32 * A.nnz;
+    // Section 4.1 / 4.3: dense windows that are walked product by product query the bitmap before writing when the (sampled) CR is at
+    // least 2 (measured on R-MAT, sampled CR 2.5: 2.8 %); those in tiles and the dense ranges have no presence bits.  The symbolic
+    // bitmap kernel, whose only LDS operation per product is that OR, loses 14 %: it queries only when told to, bitmap_query = 2
+    c.query_bitmap = o.bitmap_query >= 1 || (o.bitmap_query < 0 && S->sampled_rows > 0 && S->sampled_cr >= o.bitmap_query_cr);
     const bool query_bitmap = o.bitmap_query == 2;
     Csr Bnum = B;   // what the numeric kernels read: B, or a copy of it with sorted rows (see below)
     bool tried_sorted_copy = false, sorted_copy = false;
@@ -1311,8 +1332,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         for (;;) {   // once, or again after rows of the symbolic pass that had to be counted again
             OC_TRY(zero_bins(c, w));
             HIP_TRY(launch_classify(m, bp, o.estimate_scale, w.prod, w.est, w.nnz_final, nullptr, nullptr, w.bin, w.cap, w.scan_tmp,
-                                    w.row_nnz, w.sc->bin_count, w.sc->bin_prod, &w.sc->max_cap, &w.sc->ovf_count,
-                                    st ? w.sc->bin_work : nullptr, c.s));
+                                    w.row_nnz, w.sc->bin_count, w.sc->bin_prod, &w.sc->max_cap, &w.sc->ovf_count, w.sc->bin_work, c.s));
             HIP_TRY(launch_place(m, w.cap, w.scan_tmp, ptr, &w.sc->totals[0], ROW_KEYS, w.bin, w.sc->bin_count, w.sc->bin_cursor,
                                  w.bin_rows, c.s));   // totals[0]: total slots
             OC_TRY(fetch_scalars(c, w.sc));
@@ -1375,6 +1395,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     unsigned long long bin_count[ROW_KEYS], bin_prod[ROW_KEYS];
     std::memcpy(bin_count, c.h->bin_count, sizeof(bin_count));
     std::memcpy(bin_prod, c.h->bin_prod, sizeof(bin_prod));
+    choose_heavy(c, Bnum, bin_count, bin_prod, c.h->bin_work);
     const int64_t max_cap = (int64_t)c.h->max_cap;
     double global_coef = workflow == OCEAN_WF_SYMBOLIC ? o.exact_load_coef : 1.25;
 
@@ -1436,7 +1457,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         bp.a_rp = A.rp;
         OC_TRY(zero_bins(c, w));
         HIP_TRY(launch_classify(m, bp, 1.0, w.prod, nullptr, nullptr, w.row_nnz, nullptr, w.bin, w.cap, w.scan_tmp, w.row_nnz2,
-                                w.sc->bin_count, w.sc->bin_prod, &w.sc->max_cap, nullptr, nullptr, c.s));
+                                w.sc->bin_count, w.sc->bin_prod, &w.sc->max_cap, nullptr, w.sc->bin_work, c.s));
         HIP_TRY(launch_place(m, w.cap, w.scan_tmp, w.tmp_ptr2, &w.sc->totals[0], ROW_KEYS, w.bin, w.sc->bin_count,
                              w.sc->bin_cursor, w.bin_rows, c.s));
         OC_TRY(fetch_scalars(c, w.sc));
@@ -1447,6 +1468,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
         unsigned long long bc2[ROW_KEYS], bp2[ROW_KEYS];
         std::memcpy(bc2, c.h->bin_count, sizeof(bc2));
         std::memcpy(bp2, c.h->bin_prod, sizeof(bp2));
+        choose_heavy(c, Bnum, bc2, bp2, c.h->bin_work);
         OC_TRY(run_numeric(c, w, A, Bnum, dtype, gb_log2, bc2, bp2, (int64_t)c.h->max_cap, 1.25, w.tmp_ptr2, r_col, r_val,
                            w.row_nnz2, 2, OCEAN_ST_RETRY, false, esc_ok));
         HIP_TRY(launch_count_rows(m, w.row_nnz, w.row_nnz2, w.nnz_final, w.scan_tmp, nullptr, nullptr, nullptr, c.s));

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "ocean_spgemm.h"
+#include "rules.hpp"
 
 namespace ocean {
 
@@ -377,19 +378,12 @@ struct NumLaunch {
     double coef;              // global: table slots per reserved output entry
     const uint32_t *bw;       // dense kernel: window boundary table of B, or null to use the global-table kernel
     int n_win;
-    bool tiled;               // dense-range bin: dspan_in_tiles
+    bool tiled;               // dense-range bin: dspan_in_tiles; rows in column windows: heavy_in_tiles
+    bool query_bitmap;        // rows in column windows, not in tiles: read a column's presence bit before setting it (Section 4.1)
     bool fine_buckets;        // 512- and 1024-slot bins: order the row through 2048 column buckets (clustered columns)
     const int32_t *cmin;      // dense-range bin: first column each row can reach
     int span_cols;            // dense-range bin: the rows' ranges are at most so many columns (kDspanCols or DS_MAX_COLS)
 };
-constexpr int64_t TILE_MIN_ENTRIES = 8;   // that B has where its rows are walked in tiles (tiles.hpp)
-// Whether the dense-range kernel walks its rows in tiles of 64 entries of a row of B: where these have 32 on average.  (60 000 rows
-// in blocks of 1000 columns, fp64, whole call, one by one and in tiles: rows of B of 24 entries 416 and 426 us, of 36 488 and 484,
-// of 50 564 and 535, of 78 811 and 675; fp32 400 and 398, 445 and 435, 512 and 481, 787 and 610.)
-inline bool dspan_in_tiles(int64_t b_nnz, int64_t products, int64_t a_nnz)
-{
-    return b_nnz >= TILE_MIN_ENTRIES && b_nnz < 0xffffffffLL && products >= 32 * a_nnz;
-}
 hipError_t launch_window_table(const Csr &B, int dtype, uint32_t *bw, int *n_win_out, int32_t *flags, hipStream_t s);
 int heavy_workgroups_per_cu();   // workgroups of the column-window kernel that one compute unit holds
 int dense_window_count(int64_t n_cols, int dtype);

@@ -145,10 +145,10 @@ __device__ __forceinline__ void wave_traverse(const int32_t *__restrict__ a_col,
     }
 }
 
-// LDS scratch of a workgroup-wide flattened chunk of up to THREADS entries.
-template <typename V, int THREADS>
+// LDS scratch of a workgroup-wide flattened chunk of up to THREADS entries.  RPT: products per thread up to which
+// the entries of a chunk are found by rank (below); the mark bitmap grows with it.
+template <typename V, int THREADS, int RPT = 16>
 struct WgChunk {
-    static constexpr int RPT = 16;   // products per thread up to which the entries of a chunk are found by rank (below)
     static constexpr uint32_t RANK_CAP = (uint32_t)RPT * THREADS;   // most products of a chunk whose entries are found by rank
     static constexpr int START_WORDS = THREADS * RPT / 32 + 32;
     uint32_t excl[THREADS + 1];
@@ -170,7 +170,7 @@ struct WgChunk {
 // that point to long rows of B keeps every wave as busy as a row with a thousand short ones.
 // Every wave takes one contiguous span of the products, 256 at a time.  The entry a product
 // belongs to is found in one of two ways:
-//   * a chunk of at most RPT products per thread marks the first product of every non-empty
+//   * a chunk of at most RPT (16, or what the chunk type says) products per thread marks the first product of every non-empty
 //     segment in a bitmap; the entry of product q (counting non-empty entries only, which are
 //     stored compacted) is the number of marks at or before q, minus one: one broadcast read of
 //     the 64 marks of the wave's batch and a population count, on top of a running count that the
@@ -184,14 +184,14 @@ struct WgChunk {
 // The products of one chunk must number less than 2^31.
 // Every thread calls it; the chunk arrays must be free on entry (the call ends with a barrier).
 // Returns the number of products of the chunk.
-template <int THREADS, bool HAS_VAL, typename V, typename F>
-__device__ __forceinline__ uint32_t wg_flat_chunk(WgChunk<V, THREADS> &c, int nent, int64_t p0, uint32_t len, V a,
+template <int THREADS, bool HAS_VAL, typename V, typename F, int RPT>
+__device__ __forceinline__ uint32_t wg_flat_chunk(WgChunk<V, THREADS, RPT> &c, int nent, int64_t p0, uint32_t len, V a,
                                               const int32_t *__restrict__ b_col, const V *__restrict__ b_val, F &f)
 {
     constexpr int WU = FLAT_U;   // products per lane and batch
     constexpr int NW = THREADS / WAVE;
-    constexpr uint32_t RANK_CAP = WgChunk<V, THREADS>::RANK_CAP;
-    constexpr int START_WORDS = WgChunk<V, THREADS>::START_WORDS;
+    constexpr uint32_t RANK_CAP = WgChunk<V, THREADS, RPT>::RANK_CAP;
+    constexpr int START_WORDS = WgChunk<V, THREADS, RPT>::START_WORDS;
     static_assert(THREADS <= 1024, "entry ids are kept in 16 bits and one block table entry per thread");
     const int tid = threadIdx.x;
     const int lane = tid & (WAVE - 1), wave = tid / WAVE;
@@ -280,7 +280,8 @@ __device__ __forceinline__ uint32_t wg_flat_chunk(WgChunk<V, THREADS> &c, int ne
                     if constexpr (HAS_VAL) cv[u] = av[u] * cb[u];
                     else cv[u] = V();
                 }
-                f(cj, cv);
+                if constexpr (std::is_invocable_v<F &, int32_t(&)[WU], V(&)[WU], uint32_t>) f(cj, cv, q0);
+                else f(cj, cv);
             }
         }
         __syncthreads();
@@ -465,20 +466,130 @@ __device__ __forceinline__ uint32_t wg_flat_chunk(WgChunk<V, THREADS> &c, int ne
                 if constexpr (HAS_VAL) cv[u] = c.a[cp[u]] * cb[u];
                 else cv[u] = V();
             }
-            f(cj, cv);
+            // an accumulator may ask for the number of the batch's first product inside the chunk: the
+            // product of lane l, position u is number q0 + u*64 + l
+            if constexpr (std::is_invocable_v<F &, int32_t(&)[WU], V(&)[WU], uint32_t>) f(cj, cv, q0);
+            else f(cj, cv);
         }
     }
     __syncthreads();
     return total;
 }
 
+// The same flattening for a chunk whose products the caller keeps: every thread ends up with its
+// share of the products (column id, a*b) in registers, kc[i] < 0 where it has none, and mark(col)
+// has been called once per product.  Needs at most NB * FLAT_U products per thread
+// (total <= NB * FLAT_U * THREADS) and total <= WgChunk::RANK_CAP; otherwise nothing is fetched and
+// fits = false.  The segments are laid end to end wave by wave, in the order in which the waves draw their share
+// of the product numbers from `alloc`, a counter in LDS (products in the low word, non-empty segments in the high one;
+// the order of the products of a chunk means nothing), which spares the barrier and the scan over the waves' sums
+// that a fixed order would need.  clean: the marks and the counter are as this function leaves them (all zero); after any
+// other use of the chunk pass false and they are cleared first.  Every thread calls it; ends with a barrier; returns
+// the number of products.
+template <int THREADS, int NB, typename V, typename M, int RPT>
+__device__ __forceinline__ uint32_t wg_flat_chunk_keep(WgChunk<V, THREADS, RPT> &c, int /*nent*/, int64_t p0, uint32_t len, V a,
+                                                   const int32_t *__restrict__ b_col, const V *__restrict__ b_val,
+                                                   int32_t (&kc)[NB * FLAT_U], V (&kv)[NB * FLAT_U], M &mark,
+                                                   bool &fits, bool clean, unsigned long long &alloc)
+{
+    constexpr int NW = THREADS / WAVE;
+    constexpr uint32_t RANK_CAP = WgChunk<V, THREADS, RPT>::RANK_CAP;
+    constexpr int START_WORDS = WgChunk<V, THREADS, RPT>::START_WORDS;
+    const int tid = threadIdx.x;
+    const int lane = tid & (WAVE - 1), wave = tid / WAVE;
+    if (!clean) {   // uniform
+        for (int j = tid; j < START_WORDS; j += THREADS) c.start[j] = 0u;
+        if (tid == 0) alloc = 0ull;
+        __syncthreads();
+    }
+    uint32_t incl = wave_inclusive_scan_u32(len);
+    const unsigned long long live = __ballot(len > 0);
+    unsigned long long got = 0ull;
+    if (lane == WAVE - 1) got = atomicAdd(&alloc, (unsigned long long)incl | ((unsigned long long)__popcll(live) << 32));
+#pragma unroll
+    for (int i = 0; i < NB * FLAT_U; ++i) { kc[i] = -1; kv[i] = V(); }
+    const uint32_t before = wave_read_lane_u32((uint32_t)got, WAVE - 1);
+    const uint32_t cbefore = wave_read_lane_u32((uint32_t)(got >> 32), WAVE - 1);
+    incl += before;
+    const uint32_t ex = incl - len;
+    if (len > 0 && incl <= RANK_CAP) {   // (beyond the marks nothing is fetched anyway, see fits)
+        const uint32_t ce = cbefore + __builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0u));
+        c.pbase[ce] = (long long)p0 - (long long)ex;
+        c.a[ce] = a;
+        atomicOr(&c.start[ex >> 5], 1u << (ex & 31u));
+    }
+    __syncthreads();
+    const uint32_t total = (uint32_t)alloc;
+    fits = total <= RANK_CAP && total <= (uint32_t)(NB * FLAT_U * THREADS);
+    if (total == 0 || !fits) {   // uniform
+        __syncthreads();
+        for (int j = tid; j < START_WORDS; j += THREADS) c.start[j] = 0u;
+        if (tid == 0) alloc = 0ull;
+        return total;
+    }
+    const uint32_t span = ((total + NW - 1) / NW + (WAVE - 1)) & ~(uint32_t)(WAVE - 1);   // <= NB * FLAT_U * WAVE
+    const uint32_t qs = (uint32_t)wave * span;
+    const uint32_t qe = qs + span < total ? qs + span : total;
+    if (qs < total) {   // uniform for the wave
+        const unsigned long long *marks = reinterpret_cast<const unsigned long long *>(c.start);
+        uint32_t run = 0;
+        for (uint32_t j = (uint32_t)lane; j < (qs >> 6); j += WAVE) run += (uint32_t)__popcll(marks[j]);
+        run = wave_sum_u32(run);
+        const unsigned long long upto = (2ull << lane) - 1ull;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const uint32_t q0 = qs + (uint32_t)b * WAVE * FLAT_U;
+            if (q0 < qe) {   // uniform for the wave
+                unsigned long long m[FLAT_U];
+#pragma unroll
+                for (int u = 0; u < FLAT_U; ++u) m[u] = marks[(q0 >> 6) + u];
+                bool ok[FLAT_U];
+                int cp[FLAT_U];
+#pragma unroll
+                for (int u = 0; u < FLAT_U; ++u) {
+                    const uint32_t q = q0 + u * WAVE + lane;
+                    ok[u] = q < qe;
+                    const uint32_t rank = run + (uint32_t)__popcll(m[u] & upto);
+                    run += (uint32_t)__popcll(m[u]);
+                    cp[u] = ok[u] ? (int)rank - 1 : 0;
+                }
+                long long pb[FLAT_U];
+                V av[FLAT_U];
+#pragma unroll
+                for (int u = 0; u < FLAT_U; ++u) {
+                    pb[u] = c.pbase[cp[u]];
+                    av[u] = c.a[cp[u]];
+                }
+                V cb[FLAT_U];
+#pragma unroll
+                for (int u = 0; u < FLAT_U; ++u) {
+                    const int64_t p = pb[u] + (long long)(q0 + u * WAVE + lane);
+                    kc[b * FLAT_U + u] = ok[u] ? b_col[p] : -1;
+                    cb[u] = ok[u] ? b_val[p] : V();
+                }
+#pragma unroll
+                for (int u = 0; u < FLAT_U; ++u) {
+                    kv[b * FLAT_U + u] = av[u] * cb[u];
+                    if (kc[b * FLAT_U + u] >= 0) mark(kc[b * FLAT_U + u]);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    // (left clean for the next call; whatever the caller does next has a barrier before the chunk is used again)
+    for (int j = tid; j < (int)((total >> 5) + 2u) && j < START_WORDS; j += THREADS) c.start[j] = 0u;
+    if (tid == 0) alloc = 0ull;
+    return total;
+}
+
 // Workgroup version of the row traversal: chunks of THREADS entries of A, each flattened over the
 // whole workgroup.  Every thread of the (1-D) workgroup must call it.  seg(k, p0, len) gives the
 // segment of B's arrays that entry k expands to.  Ends with a barrier.
-template <int THREADS, bool HAS_VAL, typename V, typename SegFn, typename F>
+template <int THREADS, bool HAS_VAL, typename V, typename SegFn, typename F, int RPT>
 __device__ __forceinline__ void wg_traverse(const int32_t *__restrict__ a_col, const V *__restrict__ a_val,
                                             int64_t e0, int64_t e1, SegFn seg, const int32_t *__restrict__ b_col,
-                                            const V *__restrict__ b_val, WgChunk<V, THREADS> &c, F f)
+                                            const V *__restrict__ b_val, WgChunk<V, THREADS, RPT> &c, F f)
 {
     const int tid = threadIdx.x;
     for (int64_t base = e0; base < e1; base += THREADS) {

@@ -1,0 +1,31 @@
+"""The dispatch's rules (csrc/rules.hpp) as the host applies them, compiled for the CPU."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2604_19004_amd", "csrc")
+SOURCE = """
+#include "rules.hpp"
+extern "C" int heavy_in_tiles(double products, double rows, double entries, int n_win) { return ocean::heavy_in_tiles(products, rows, entries, n_win); }
+"""
+
+
+@functools.lru_cache(maxsize=None)
+def load():
+    with tempfile.TemporaryDirectory() as d:
+        src, lib = os.path.join(d, "rules.cpp"), os.path.join(d, "rules.so")
+        with open(src, "w") as f:
+            f.write(SOURCE)
+        subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, src, "-o", lib], check=True)
+        so = ctypes.CDLL(lib)
+    so.heavy_in_tiles.argtypes = [ctypes.c_double] * 3 + [ctypes.c_int]
+    return so
+
+
+def heavy_in_tiles(st, cols):
+    """Whether the rows of a call's column windows are walked in tiles, from its statistics."""
+    bins = range(8, 11)
+    rows, products, entries = (sum(st[k][b] for b in bins) for k in ("rows_per_bin", "bin_products", "bin_nnz_a"))
+    return bool(load().heavy_in_tiles(products, rows, entries, (cols + 16383) >> 14))

@@ -1,0 +1,29 @@
+"""The rules that choose between two kernels, held against times of both on one MI355X: the rule has the faster one wherever they
+differ by more than an eighth."""
+import pytest
+
+import rules
+
+# rows of `products` products, `length` entries in every row of B, columns anywhere in `windows` windows of 16384: numeric stage in us
+# with products one by one, and in tiles
+HEAVY = [
+    # windows, products, length, one by one, tiles
+    (1, 15728, 16, 242, 297), (1, 56376, 16, 380, 480), (1, 222971, 16, 284, 389), (1, 58934, 64, 373, 308), (1, 277121, 64, 334, 205),
+    (1, 284059, 95.7, 311, 209), (1, 290552, 190.9, 301, 240), (2, 15733, 16, 364, 647), (2, 223011, 16, 389, 710), (2, 15861, 32, 331, 409),
+    (2, 257558, 32, 339, 450), (2, 284523, 95.9, 328, 274), (2, 287892, 127.8, 360, 275), (2, 287213, 255, 324, 255), (2, 24000, 2, 822, 1892),
+    (2, 24000, 8, 622, 1048), (4, 56392, 16, 901, 1574), (4, 223041, 16, 649, 1370), (4, 257635, 32, 523, 842), (4, 270715, 48, 461, 625),
+    (4, 277493, 64, 430, 532), (4, 59334, 95.9, 557, 644), (4, 287848, 255.5, 378, 321), (8, 56391, 16, 1752, 4001), (8, 58761, 48, 1258, 1778),
+    (8, 59356, 96, 866, 1146), (8, 288433, 127.9, 561, 643), (16, 15736, 16, 501, 783), (16, 56398, 16, 1957, 4228), (16, 277669, 64, 1141, 1937),
+    (16, 288160, 255.9, 613, 736), (16, 24000, 2, 1994, 4493), (16, 24000, 32, 1079, 1469), (32, 15736, 16, 735, 1018), (32, 56398, 16, 2333, 4851),
+    (32, 15830, 256, 1.0, 0.93), (64, 24000, 8, 2713, 5268), (64, 24000, 32, 1671, 2274), (64, 15830, 256, 1.0, 0.88), (64, 15841, 512, 1.0, 0.85),
+    (128, 15836, 32, 1.0, 1.68), (128, 15890, 96, 1.0, 1.48), (128, 15964, 128, 1.0, 1.17), (128, 293767, 512, 1026, 1626),
+    # power-law matrices: mean products and length of the rows that go through windows
+    (1, 10279, 95.8, 195, 164), (1, 15336, 226.6, 367, 304), (2, 18071, 313.9, 754, 625), (4, 22856, 424.3, 1899, 1531), (8, 28879, 569.1, 4769, 3950),
+    (16, 39606, 758.3, 13017, 10808),
+]
+
+
+@pytest.mark.parametrize("windows, products, length, one_by_one, tiles", HEAVY)
+def test_heavy_rows_go_the_faster_way(windows, products, length, one_by_one, tiles):
+    chosen = tiles if rules.load().heavy_in_tiles(1000.0 * products, 1000.0, 1000.0 * products / length, windows) else one_by_one
+    assert chosen <= 1.125 * min(one_by_one, tiles)
