@@ -1001,7 +1001,9 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
 
     for (int j = threadIdx.x; j < HV_WIN; j += HV_THREADS) s_vals[j] = -0.0;
     for (int w = threadIdx.x; w < HV_MAXWIN; w += HV_THREADS) s_pw[w] = 0u;
-    if (threadIdx.x == 0) s_row = (long long)atomicAdd(queue, 1ull);
+    // The first row of a workgroup is that of its number, the next ones are drawn from a counter, a row ahead.  (With the first one
+    // drawn, too, some workgroups had two of 250 rows and others none: rows of 400 000 products in 2 windows 306 us, 197 now.)
+    if (threadIdx.x == 0) s_row = (long long)blockIdx.x;
     bool clean = true;   // every accumulator of the dense window is -0; the first HV_CAP always are between passes
     __syncthreads();
 
@@ -1056,7 +1058,7 @@ k_numeric_heavy(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
             }
         }
         __syncthreads();
-        if (tid == 0) s_row = (long long)drawn;   // (read by all before that barrier; the next row's behind one more)
+        if (tid == 0) s_row = (long long)(gridDim.x + drawn);   // (read by all before that barrier; the next row's behind one more)
 
         // ---- walk the windows, pass by pass.  Next pass from window `from` on: p0 == n_win when nothing is left.
         // Every wave plans for itself, 64 windows at a look, lane l window x + l.

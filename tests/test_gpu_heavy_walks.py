@@ -100,3 +100,20 @@ def test_a_matrix_of_fewer_entries_than_a_lane_reads(ob):
         C, _ = ob.spgemm(ob.to_device(A), ob.to_device(B), workflow=workflow)
         assert np.array_equal(C.row_ptr.cpu().numpy(), ref.row_ptr) and np.array_equal(C.col_idx.cpu().numpy(), ref.col_idx)
         assert np.all(np.abs(C.val.cpu().numpy() - ref.val) <= 1e-11 * ref.absval)   # (up to 15 000 terms)
+
+
+def test_every_workgroup_has_one_of_as_many_rows(ob):
+    """Equal rows, nearly one for every compute unit, take about as long as half as many (the least of many calls; 1.25 times with a
+    row each, 1.7 where some workgroups have two and others none)."""
+    import torch
+    rng = np.random.default_rng(1)
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    B = _csr(2 * WIN, [np.sort(rng.choice(2 * WIN, 256, replace=False)) for _ in range(1500)], lambda n: rng.uniform(-1, 1, n))
+    row = np.sort(rng.choice(1500, 400, replace=False))
+    least = []
+    for rows in (units // 2, units - 6):
+        dA, dB = ob.to_device(_csr(1500, [row] * rows, lambda n: rng.uniform(-1, 1, n))), ob.to_device(B)
+        calls = [ob.spgemm(dA, dB, workflow=ob.WF_SYMBOLIC)[1] for _ in range(30)]
+        assert sum(calls[0]["rows_per_bin"][8:11]) == rows and rules.heavy_in_tiles(calls[0], B.cols)
+        least.append(min(st["stage_ms"]["numeric"] for st in calls))
+    assert least[1] < 1.45 * least[0], least
