@@ -418,7 +418,8 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
     // window costs less than building a key table of 16384 or 32768 slots: those two bins go with it
     // (the row lists of consecutive bins are adjacent).
     const bool wide_bitmap = B.cols <= (1 << 20);
-    const bool few_apart = B.cols <= SYMBOLIC_FEW_COLS;   // rows of few products have a launch of smaller workgroups
+    const bool tiled = symbolic_in_tiles(B.nnz, B.cols, st->products, A.nnz);
+    const bool few_apart = tiled && B.cols <= SYMBOLIC_FEW_COLS;   // rows of few products have a launch of smaller workgroups
     // That launch takes the rows of the 4096-slot bin, too, where rows of B fill the bitmap kernel's tiles: 12 000 rows of 3040
     // products, predict stage with key tables and with bitmaps, 16384 / 131072 / 262144 columns: rows of B of 16 entries
     // 186 -> 113, 199 -> 141, 195 -> 145 us, of 32 181 -> 107, 194 -> 122, 199 -> 129, of 64 181 -> 105, 197 -> 112, 199 -> 119;
@@ -462,7 +463,7 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
         const int64_t by_range = start[SB_ALL] - start[SB_SPAN] - (few_by_keys ? few : 0);
         if (st && round == 0) st->symbolic_rows_per_bin[few_by_keys ? SB_S1K : SB_SPAN] += few;
         for (int b = SB_ALL - 1; b >= 0; --b) {
-            SymLaunch l{w.bin_rows + start[b], start[b + 1] - start[b], b, query_bitmap, spans ? w.cmin : nullptr, false, assisted};
+            SymLaunch l{w.bin_rows + start[b], start[b + 1] - start[b], b, query_bitmap, spans ? w.cmin : nullptr, tiled, false, assisted};
             if (b == SB_SPAN_FEW && !few_by_keys) continue;
             if (b == SB_SPAN_FEW) l.bin = SB_S1K;
             if (b == SB_SPAN) l.count = by_range;

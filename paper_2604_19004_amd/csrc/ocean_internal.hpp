@@ -346,6 +346,7 @@ struct SymLaunch {
     int bin;
     bool query_bitmap;     // bitmap kernel: read a column's bit before setting it (Section 4.1)
     const int32_t *cmin;   // SB_SPAN: first column each row can reach
+    bool tiled;            // SB_BITMAP: symbolic_in_tiles
     bool few;              // SB_BITMAP: rows of at most kSymbolicSlots[SB_S32K] products
     bool may_overflow;     // tables were sized from a guess (assisted binning): a row whose table fills up
                            // reports -1 instead of a count and probing gives up early

@@ -33,4 +33,15 @@ constexpr bool heavy_in_tiles(double products, double rows, double entries, int 
     return products * share >= 32.0 * entries;
 }
 
+// Whether the symbolic pass marks its bitmaps in tiles (from the mean entries of a row of B per entry of A).  Call in us one by one
+// and in tiles, rows of B of equal length with columns anywhere: 65 536 columns, rows of 6000 products 332 and 503 (2 entries),
+// 202 and 189 (8), 194 and 156 (12), 202 and 141 (16), rows of 24 000 434 and 714 (2), 258 and 277 (8), 187 and 177 (12);
+// 2^20 columns, where a compute unit has one workgroup, 6000 217 and 287 (8), 237 and 215 (16), 226 and 201 (24), 100 000 373 and
+// 535 (8), 312 and 398 (16), 303 and 323 (24), 271 and 287 (32), 215 and 204 (48); 2^22 columns, four windows, 100 000 742 and
+// 1472 (8), 671 and 824 (24), 564 and 676 (32), 419 and 412 (48).
+constexpr bool symbolic_in_tiles(int64_t b_nnz, int64_t b_cols, int64_t products, int64_t a_nnz)
+{
+    return b_nnz >= TILE_MIN_ENTRIES && products >= (b_cols <= 1 << 18 ? 10 : b_cols <= 1 << 20 ? 20 : 40) * a_nnz;
+}
+
 }  // namespace ocean

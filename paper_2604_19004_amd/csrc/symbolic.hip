@@ -211,6 +211,7 @@ k_symbolic_span(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_
 // --------------------------------------------------------- bitmap kernel
 constexpr int BM_CHUNK = 512;             // entries of A whose rows of B are walked at a time
 constexpr int BM_STEPS = 2;               // steps of tiles per batch
+constexpr int BM_U = 16;                  // column ids per lane and batch, not in tiles (R-MAT: 16.2 ms against 16.9 with 8, 20.9 with 4)
 constexpr int BM_WIN = 1 << 20;          // columns per window
 constexpr int BM_MAX_WORDS = BM_WIN / 32;    // 32768 words = 128 KB
 static_assert(SYMBOLIC_FEW_COLS == 32 * 8192, "four bitmaps per compute unit");
@@ -223,17 +224,20 @@ static_assert(SYMBOLIC_FEW_COLS == 32 * 8192, "four bitmaps per compute unit");
 // own, as the largest row decides how long a launch takes: scale 17 0.875 -> 0.850 ms (256 threads: 0.839), scale 14 in fp32 whole
 // product 663 -> 626 us (659), all rows by 512 threads 1.016 ms and 718 us.
 // ONE_WINDOW: B has at most 32 * BM_WORDS columns, so every column id falls into the one window.
+// TILED: symbolic_in_tiles says where; otherwise products are found one by one, or in runs of 16 where a chunk's segments are that
+// long (2000 rows of 24 000 products, rows of B of 2 entries, whole call 714 us in tiles and 434).
 // QUERY: a column's bit is read first and set only when it is clear (Section 4.1).
-template <typename P, int BM_THREADS, int BM_WORDS, bool ONE_WINDOW, bool QUERY>
+template <bool TILED, typename P, int BM_THREADS, int BM_WORDS, bool ONE_WINDOW, bool QUERY>
 __global__ void __launch_bounds__(BM_THREADS, BM_WORDS < BM_MAX_WORDS ? 8 : 4)
 k_symbolic_bitmap(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a_col,
                   const int64_t *__restrict__ b_rp, const int32_t *__restrict__ b_col,
-                  const int32_t *__restrict__ rows, int64_t count, int64_t n_cols, int64_t b_nnz,
+                  const int32_t *__restrict__ rows, int64_t count, int64_t n_cols,
                   unsigned long long *queue, int32_t *__restrict__ nnz_out)
 {
-    constexpr int CHUNK = BM_THREADS < BM_CHUNK ? BM_THREADS : BM_CHUNK;
+    constexpr int CHUNK = !TILED || BM_THREADS < BM_CHUNK ? BM_THREADS : BM_CHUNK;
+    using Chunk = std::conditional_t<TILED, TileChunk<NoVal, P, CHUNK>, WgChunk<NoVal, BM_THREADS>>;
     __shared__ __align__(16) uint32_t s_bm[BM_WORDS];
-    __shared__ TileChunk<NoVal, P, CHUNK> s_ch;
+    __shared__ Chunk s_ch;
     // Rows come from a shared counter.  The chain counter -> row id -> offsets of the row -> entries -> their
     // segments of B is five memory round trips before the first column id of a row can be asked for, so it runs
     // ahead of the work, one link per turn: at the start of a turn the ticket of the row six turns ahead is
@@ -301,12 +305,7 @@ k_symbolic_bitmap(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ 
         segment_of(k1, fp0_1, flen_1);
         const int64_t ne = e1 - e0;
         for (int64_t w0 = 0; w0 < n_cols; w0 += BM_WIN) {
-            if (b_nnz < TILE_MIN_ENTRIES) {   // uniform: (many entries of A, none with eight products)
-                for (int64_t e = e0 + tid; e < e1; e += BM_THREADS) {
-                    const int32_t k = a_col[e];
-                    for (int64_t p = b_rp[k]; p < b_rp[k + 1]; ++p) mark(b_col[p], (uint32_t)w0, true);
-                }
-            } else {
+            if constexpr (TILED) {
                 for (int64_t base = 0; base < ne; base += CHUNK) {
                     int64_t p0 = fp0;
                     uint32_t len = flen;
@@ -330,8 +329,20 @@ k_symbolic_bitmap(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ 
                         }
                     });
                 }
+                __syncthreads();
+            } else {
+                auto f = [&](const auto &cj, const auto &) {
+                    constexpr int U = sizeof(cj) / sizeof(cj[0]);
+#pragma unroll
+                    for (int u = 0; u < U; ++u) mark(cj[u], (uint32_t)w0, cj[u] >= 0);
+                };
+                if (ne > 0) wg_flat_chunk<BM_THREADS, false, BM_U>(s_ch, ne < CHUNK ? (int)ne : CHUNK, fp0, flen, NoVal(), b_col, (const NoVal *)nullptr, f);
+                if (ne > CHUNK)
+                    wg_traverse<BM_THREADS, false, BM_U>(a_col, (const NoVal *)nullptr, e0 + CHUNK, e1,
+                                                         [&](int32_t k, int64_t &p0, int64_t &len) { p0 = b_rp[k]; len = b_rp[k + 1] - p0; },
+                                                         b_col, (const NoVal *)nullptr, s_ch, f);
+                // (both end with a barrier)
             }
-            __syncthreads();
             // count and clear the window, 16 bytes per thread and step
             int c = 0;
             uint4 *bm4 = reinterpret_cast<uint4 *>(s_bm);
@@ -399,33 +410,37 @@ hipError_t launch_symbolic_bin(const Csr &A, const Csr &B, const SymLaunch &l, i
         });
         break;
     case SB_BITMAP: {
-#define OCEAN_SYM_BM_P(P, THREADS, WORDS, ONE, QUERY)                                                               \
-    hipLaunchKernelGGL((k_symbolic_bitmap<P, THREADS, WORDS, ONE, QUERY>), dim3((unsigned)(n_wg < l.count ? n_wg : l.count)), \
-                       dim3(THREADS), 0, s, A.rp, A.col, B.rp, B.col, l.rows, l.count, B.cols, B.nnz, queue, nnz_out)
-#define OCEAN_SYM_BM(THREADS, WORDS, ONE)                                                                           \
+#define OCEAN_SYM_BM_P(TILED, P, THREADS, WORDS, ONE)                                                               \
     do {                                                                                                          \
-        const bool narrow = B.nnz < 0xffffffffLL;   /* positions in 32 bits */                                     \
-        if (l.query_bitmap && narrow) OCEAN_SYM_BM_P(uint32_t, THREADS, WORDS, ONE, true);                         \
-        else if (l.query_bitmap) OCEAN_SYM_BM_P(unsigned long long, THREADS, WORDS, ONE, true);                    \
-        else if (narrow) OCEAN_SYM_BM_P(uint32_t, THREADS, WORDS, ONE, false);                                     \
-        else OCEAN_SYM_BM_P(unsigned long long, THREADS, WORDS, ONE, false);                                       \
+        const auto kernel = l.query_bitmap ? k_symbolic_bitmap<TILED, P, THREADS, WORDS, ONE, true> : k_symbolic_bitmap<TILED, P, THREADS, WORDS, ONE, false>; \
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(n_wg < l.count ? n_wg : l.count)), dim3(THREADS), 0, s, A.rp, A.col, B.rp, B.col, \
+                           l.rows, l.count, B.cols, queue, nnz_out);                                               \
     } while (0)
-        if (B.cols > BM_WIN) OCEAN_SYM_BM(1024, BM_MAX_WORDS, false);
-        else if (B.cols > 32 * 16384) OCEAN_SYM_BM(1024, BM_MAX_WORDS, true);
-        else if (B.cols > SYMBOLIC_FEW_COLS) {
-            n_wg *= 2;   // (two workgroups per compute unit)
-            OCEAN_SYM_BM(1024, 16384, true);
-        } else if (l.few) {
+#define OCEAN_SYM_BM_TILED(THREADS, WORDS, ONE)                                                                     \
+    do {   /* positions in 32 bits, or in 64 */                                                                    \
+        if (B.nnz < 0xffffffffLL) OCEAN_SYM_BM_P(true, uint32_t, THREADS, WORDS, ONE);                             \
+        else OCEAN_SYM_BM_P(true, unsigned long long, THREADS, WORDS, ONE);                                        \
+    } while (0)
+#define OCEAN_SYM_BM(WORDS, ONE)                                                                                    \
+    do {                                                                                                          \
+        if (l.tiled) OCEAN_SYM_BM_TILED(1024, WORDS, ONE);                                                         \
+        else OCEAN_SYM_BM_P(false, uint32_t, 1024, WORDS, ONE);                                                    \
+    } while (0)
+        if (B.cols > BM_WIN) OCEAN_SYM_BM(BM_MAX_WORDS, false);
+        else if (B.cols > 32 * 16384) OCEAN_SYM_BM(BM_MAX_WORDS, true);
+        else if (l.few) {
             n_wg *= 4;
             queue = nullptr;
-            if (B.cols > 32 * 4096) OCEAN_SYM_BM(512, 8192, true);
-            else OCEAN_SYM_BM(512, 4096, true);
+            if (B.cols > 32 * 4096) OCEAN_SYM_BM_TILED(512, 8192, true);
+            else OCEAN_SYM_BM_TILED(512, 4096, true);
         } else {
-            n_wg *= 2;
-            if (B.cols > 32 * 4096) OCEAN_SYM_BM(1024, 8192, true);
-            else OCEAN_SYM_BM(1024, 4096, true);
+            n_wg *= 2;   // (two workgroups per compute unit)
+            if (B.cols > SYMBOLIC_FEW_COLS) OCEAN_SYM_BM(16384, true);
+            else if (B.cols > 32 * 4096) OCEAN_SYM_BM(8192, true);
+            else OCEAN_SYM_BM(4096, true);
         }
 #undef OCEAN_SYM_BM
+#undef OCEAN_SYM_BM_TILED
 #undef OCEAN_SYM_BM_P
         break;
     }

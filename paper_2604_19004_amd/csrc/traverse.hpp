@@ -156,7 +156,7 @@ struct WgChunk {
     V a[THREADS];
     union alignas(8) {
         uint16_t first[THREADS + 2];       // entry of the first product of every block of 2^bshift products
-        uint32_t start[START_WORDS];       // bit q set: a segment starts at product q (RANK_CAP bits + padding for the batches of a lane)
+        uint32_t start[START_WORDS];       // bit q set: a segment starts at product q (RANK_CAP bits + padding for batches of up to 16 per lane)
     };
     uint32_t wsum[THREADS / WAVE];
     uint32_t wcnt[THREADS / WAVE];
@@ -181,14 +181,14 @@ struct WgChunk {
 //     the same, wave-uniform number of steps and run interleaved.  Without values (the symbolic
 //     pass) such a chunk is walked in runs of WU consecutive column ids per lane instead, its
 //     batches handed out from a counter rather than in equal spans (see there).
-// The products of one chunk must number less than 2^31.
+// WU is the number of products per lane and batch.  The products of one chunk must number less
+// than 2^31.
 // Every thread calls it; the chunk arrays must be free on entry (the call ends with a barrier).
 // Returns the number of products of the chunk.
-template <int THREADS, bool HAS_VAL, typename V, typename F, int RPT>
+template <int THREADS, bool HAS_VAL, int WU = FLAT_U, typename V, typename F, int RPT>
 __device__ __forceinline__ uint32_t wg_flat_chunk(WgChunk<V, THREADS, RPT> &c, int nent, int64_t p0, uint32_t len, V a,
                                               const int32_t *__restrict__ b_col, const V *__restrict__ b_val, F &f)
 {
-    constexpr int WU = FLAT_U;   // products per lane and batch
     constexpr int NW = THREADS / WAVE;
     constexpr uint32_t RANK_CAP = WgChunk<V, THREADS, RPT>::RANK_CAP;
     constexpr int START_WORDS = WgChunk<V, THREADS, RPT>::START_WORDS;
@@ -201,7 +201,7 @@ __device__ __forceinline__ uint32_t wg_flat_chunk(WgChunk<V, THREADS, RPT> &c, i
     const unsigned long long live = __ballot(len > 0);
     if (lane == WAVE - 1) { c.wsum[wave] = incl; c.wcnt[wave] = (uint32_t)__popcll(live); }
     // column ids only: the same sums over the lengths rounded up to whole runs of WU (see below)
-    constexpr bool RUNS = !HAS_VAL;
+    constexpr bool RUNS = !HAS_VAL && WU % 4 == 0;
     const uint32_t lenr = (len + (uint32_t)(WU - 1)) & ~(uint32_t)(WU - 1);
     uint32_t inclr = 0;
     if constexpr (RUNS) {
@@ -224,8 +224,19 @@ __device__ __forceinline__ uint32_t wg_flat_chunk(WgChunk<V, THREADS, RPT> &c, i
     V cb[WU];   // values of B
     int cp[WU];
     // Runs (column ids only, below) pay when the segments are at least a run long on average - shorter ones leave
-    // most of a run's slots empty - and not for a small chunk, whose entries the marks find faster (rect: 0.78 against 0.68 ms).
-    const bool use_runs = RUNS && (unsigned long long)total >= (unsigned long long)ctotal * (unsigned)WU && total > RANK_CAP;   // uniform
+    // most of a run's slots empty (rows of B of 8 entries in runs of 16: 0.93 against 0.60 ms on a test input, rows
+    // of 24: 0.86 against 1.62 ms) - and long runs are worth more than the marks even for a small chunk (R-MAT,
+    // 16 ids per run: 15.7 against 15.9 ms), short ones are not (rect, 4 ids per run: 0.78 against 0.68 ms).
+    const bool use_runs = RUNS && (unsigned long long)total >= (unsigned long long)ctotal * (unsigned)WU &&
+                          (WU >= 8 || total > RANK_CAP);   // uniform
+    if constexpr (RUNS && WU > 4) {
+        // (a chunk of short segments: the same with four column ids per lane and batch - the marks, runs of four
+        // or the search, whichever applies - which also keeps the registers of those paths out of this one)
+        if (!use_runs) {   // uniform
+            __syncthreads();   // (everyone has read the waves' sums)
+            return wg_flat_chunk<THREADS, HAS_VAL, 4>(c, nent, p0, len, a, b_col, b_val, f);
+        }
+    }
     if (!use_runs && total <= RANK_CAP) {   // uniform
         const uint32_t ex = incl - len;
         if (len > 0) {
@@ -586,7 +597,7 @@ __device__ __forceinline__ uint32_t wg_flat_chunk_keep(WgChunk<V, THREADS, RPT> 
 // Workgroup version of the row traversal: chunks of THREADS entries of A, each flattened over the
 // whole workgroup.  Every thread of the (1-D) workgroup must call it.  seg(k, p0, len) gives the
 // segment of B's arrays that entry k expands to.  Ends with a barrier.
-template <int THREADS, bool HAS_VAL, typename V, typename SegFn, typename F, int RPT>
+template <int THREADS, bool HAS_VAL, int WU = FLAT_U, typename V, typename SegFn, typename F, int RPT>
 __device__ __forceinline__ void wg_traverse(const int32_t *__restrict__ a_col, const V *__restrict__ a_val,
                                             int64_t e0, int64_t e1, SegFn seg, const int32_t *__restrict__ b_col,
                                             const V *__restrict__ b_val, WgChunk<V, THREADS, RPT> &c, F f)
@@ -602,7 +613,7 @@ __device__ __forceinline__ void wg_traverse(const int32_t *__restrict__ a_col, c
             seg(k, p0, len);
         }
         const int64_t left = e1 - base;
-        wg_flat_chunk<THREADS, HAS_VAL>(c, left < THREADS ? (int)left : THREADS, p0, (uint32_t)len, a, b_col, b_val, f);
+        wg_flat_chunk<THREADS, HAS_VAL, WU>(c, left < THREADS ? (int)left : THREADS, p0, (uint32_t)len, a, b_col, b_val, f);
     }
 }
 

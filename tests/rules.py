@@ -9,6 +9,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SOURCE = """
 #include "rules.hpp"
 extern "C" int heavy_in_tiles(double products, double rows, double entries, int n_win) { return ocean::heavy_in_tiles(products, rows, entries, n_win); }
+extern "C" int symbolic_in_tiles(int64_t b_nnz, int64_t b_cols, int64_t products, int64_t a_nnz) { return ocean::symbolic_in_tiles(b_nnz, b_cols, products, a_nnz); }
 """
 
 
@@ -21,6 +22,7 @@ def load():
         subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, src, "-o", lib], check=True)
         so = ctypes.CDLL(lib)
     so.heavy_in_tiles.argtypes = [ctypes.c_double] * 3 + [ctypes.c_int]
+    so.symbolic_in_tiles.argtypes = [ctypes.c_int64] * 4
     return so
 
 

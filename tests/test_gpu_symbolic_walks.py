@@ -1,0 +1,46 @@
+"""Rows whose columns a bitmap counts, on both sides of the line between products in tiles and one by one (symbolic_in_tiles in
+csrc/rules.hpp), at every size of the bitmap, against the CPU oracle: more entries of A than a chunk holds, rows of B of one entry
+beside long ones, and chunks whose segments are runs of 16 on average beside others."""
+import numpy as np
+import pytest
+
+import rules
+from oracle import spgemm as O
+from paper_2604_19004_amd.workloads import CSR
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ob():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2604_19004_amd import binding
+    binding.load()
+    return binding
+
+
+def _csr(cols, lists):
+    ptr = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int64)
+    idx = np.concatenate([np.asarray(x, dtype=np.int64) for x in lists]).astype(np.int32)
+    return CSR(len(lists), cols, ptr, idx, np.ones(idx.size))
+
+
+@pytest.mark.parametrize("bitmap_query", [-1, 2])
+@pytest.mark.parametrize("tiles", [False, True])
+@pytest.mark.parametrize("cols", [9000, 1 << 17, (1 << 17) + 1, (1 << 18) + 1, (1 << 19) + 5, (1 << 21) + 7])
+def test_counts_both_ways(ob, cols, tiles, bitmap_query):
+    rng = np.random.default_rng(cols)
+    short = [np.sort(rng.choice(cols, int(n), replace=False)) for n in rng.integers(0, 6, 3200)]
+    long = [np.sort(rng.choice(cols, int(n), replace=False)) for n in (400, 63, 64, 65, 1, 2, 3, 4000)]
+    B = _csr(cols, short + long)
+    k = len(short)
+    every = list(range(k))
+    some = list(range(k, B.rows))
+    rows = [every, every[:1023] + some, every[:1024] + some, every[:1025] + some, [], every[:511] + some * 3, every[:512] + some * 3, every[:513], some * 9, every[5:900]]
+    rows += [some * 40] * 60 if tiles else [every] * 20   # (which moves the mean over the line)
+    A = _csr(B.rows, rows)
+    products = int(O.row_products(A, B).sum())
+    assert bool(rules.load().symbolic_in_tiles(B.col_idx.size, cols, products, A.col_idx.size)) == tiles
+    got = ob.symbolic(ob.to_device(A), ob.to_device(B), opt=ob.default_options(bitmap_query=bitmap_query))[0].cpu().numpy()
+    assert np.array_equal(got, O.count_rows(A, B))

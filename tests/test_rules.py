@@ -27,3 +27,23 @@ HEAVY = [
 def test_heavy_rows_go_the_faster_way(windows, products, length, one_by_one, tiles):
     chosen = tiles if rules.load().heavy_in_tiles(1000.0 * products, 1000.0, 1000.0 * products / length, windows) else one_by_one
     assert chosen <= 1.125 * min(one_by_one, tiles)
+
+
+# columns, products of a row, length of the rows of B: a call for the sizes of the rows in us with products one by one, and in tiles
+SYMBOLIC = [
+    (65536, 6000, 2, 332, 503), (65536, 24000, 2, 434, 714), (65536, 24000, 4, 306, 415), (65536, 6000, 12, 194, 156), (65536, 6000, 16, 202, 141),
+    (65536, 6000, 32, 199, 124), (65536, 24000, 16, 200, 159), (65536, 24000, 48, 179, 123), (262144, 24000, 2, 449, 713), (262144, 6000, 12, 193, 157),
+    (524288, 24000, 4, 310, 509), (524288, 24000, 12, 190, 241), (524288, 100000, 8, 335, 450), (524288, 24000, 48, 186, 170), (1 << 20, 24000, 8, 262, 382),
+    (1 << 20, 24000, 12, 190, 259), (1 << 20, 100000, 16, 312, 398), (1 << 20, 6000, 24, 226, 201), (1 << 20, 24000, 48, 182, 162), (1 << 22, 100000, 4, 994, 2406),
+    (1 << 22, 100000, 8, 742, 1472), (1 << 22, 100000, 24, 671, 824), (1 << 22, 100000, 32, 564, 676),
+]
+
+
+@pytest.mark.parametrize("cols, products, length, one_by_one, tiles", SYMBOLIC)
+def test_symbolic_rows_go_the_faster_way(cols, products, length, one_by_one, tiles):
+    chosen = tiles if rules.load().symbolic_in_tiles(10 ** 6, cols, 1000 * products, 1000 * products // length) else one_by_one
+    assert chosen <= 1.125 * min(one_by_one, tiles)
+
+
+def test_no_tiles_of_a_matrix_smaller_than_what_a_lane_reads():
+    assert not rules.load().symbolic_in_tiles(7, 1000, 10 ** 9, 1) and rules.load().symbolic_in_tiles(8, 1000, 10 ** 9, 1)
