@@ -249,12 +249,12 @@ k_symbolic_bitmap(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ 
     __shared__ int s_count[2];
     const int tid = threadIdx.x;
     for (int s = tid; s < BM_WORDS; s += BM_THREADS) s_bm[s] = 0u;
-    // (rows of about the same size need no counter, which hands out 83 tickets per us to the whole chip)
-    auto draw = [&](unsigned turn) {
-        return queue != nullptr ? atomicAdd(queue, 1ull) : (unsigned long long)blockIdx.x + (unsigned long long)turn * gridDim.x;
-    };
+    // (rows of about the same size need no counter, which hands out 83 tickets per us to the whole chip, and the first six of a
+    // workgroup come without one: of a few rows the first workgroups would have six each, and the others none)
+    auto own = [&](unsigned turn) { return (unsigned long long)blockIdx.x + (unsigned long long)turn * gridDim.x; };
+    auto draw = [&](unsigned turn) { return queue != nullptr ? 6ull * gridDim.x + atomicAdd(queue, 1ull) : own(turn); };
     if (tid == 0) {
-        for (int j = 0; j < 6; ++j) s_ticket[j] = draw((unsigned)j);
+        for (int j = 0; j < 6; ++j) s_ticket[j] = own((unsigned)j);
         s_count[0] = s_count[1] = 0;
     }
     __syncthreads();

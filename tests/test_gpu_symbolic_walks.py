@@ -44,3 +44,28 @@ def test_counts_both_ways(ob, cols, tiles, bitmap_query):
     assert bool(rules.load().symbolic_in_tiles(B.col_idx.size, cols, products, A.col_idx.size)) == tiles
     got = ob.symbolic(ob.to_device(A), ob.to_device(B), opt=ob.default_options(bitmap_query=bitmap_query))[0].cpu().numpy()
     assert np.array_equal(got, O.count_rows(A, B))
+
+
+def test_every_workgroup_has_one_of_a_few_rows(ob):
+    """Four rows of many products beside smaller ones take about as long as one (median of many calls; 1.7 times where one workgroup
+    had two of them and another none)."""
+    import time
+
+    import torch
+    rng = np.random.default_rng(4)
+    cols = 100000
+    B = ob.to_device(_csr(cols, [np.sort(rng.choice(cols, 250, replace=False)) for _ in range(16000)]))
+    small = [np.sort(rng.choice(16000, 40, replace=False)) for _ in range(4000)]
+    median = []
+    for rows in (1, 4):
+        A = ob.to_device(_csr(16000, [np.arange(16000)] * rows + small))
+        times = []
+        for _ in range(30):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            st = ob.symbolic(A, B)[1]
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t0)
+        assert st["symbolic_rows_per_bin"][6] == rows
+        median.append(sorted(times)[15])
+    assert median[1] < 1.3 * median[0], median
