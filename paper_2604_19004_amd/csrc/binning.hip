@@ -67,7 +67,7 @@ __device__ __forceinline__ int sort_class(long long pr, long long ne, int bin, u
 // sorted; bin_count and bin_prod have one counter per key.
 template <int ROW_ITEMS>
 __global__ void __launch_bounds__(TPB)
-k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coef, double scale, BinTable bt, int64_t n_cols,
+k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coef, double scale, BinTable bt, int64_t n_cols, int64_t few_products,
            const int64_t *__restrict__ prod, const double *__restrict__ est, const int32_t *__restrict__ nnz_exact,
            const int32_t *__restrict__ row_mask, const int32_t *__restrict__ lower_bound,
            const int32_t *__restrict__ cmin, const int32_t *__restrict__ cmax, int vbytes, unsigned sort_mask,
@@ -135,6 +135,8 @@ k_classify(int64_t m, int mode, double coef, double table_coef, double bound_coe
             bin = bt.n - 1;
             for (int b = 0; b < bt.n; ++b)
                 if ((long long)bt.slots[b] >= need) { bin = b; break; }
+            // (by what the row's work is: its bound stops at the columns, or is divided)
+            if (few_products > 0 && bin >= SB_S16K) bin = pr > few_products ? SB_BITMAP : bin == SB_BITMAP ? SB_S32K : bin;
             if (cmin != nullptr) {
                 // Section 3.3, accumulator selection: the dense accumulator over the row's own column range where
                 // it needs no more memory than the hash table the row would get
@@ -208,7 +210,7 @@ hipError_t launch_classify(int64_t m, const BinParams &p, double scale, const in
     const double table_coef = (p.table_coef > 0.0 && p.table_coef < p.coef) ? p.table_coef : p.coef;
     const auto kernel = row_items(m) == 1 ? k_classify<1> : row_items(m) == 4 ? k_classify<4> : k_classify<8>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(TPB), 0, s, m, p.mode, p.coef, table_coef, p.bound_coef, scale, bt,
-                       p.n_cols, prod, est, nnz_exact, row_mask, lower_bound, p.cmin, p.cmax, p.vbytes,
+                       p.n_cols, p.few_products, prod, est, nnz_exact, row_mask, lower_bound, p.cmin, p.cmax, p.vbytes,
                        p.sort_mask, p.a_rp, bin_of_row, cap, tile_cap, zero, bin_count, bin_prod, max_cap, uncounted, work);
     return hipGetLastError();
 }

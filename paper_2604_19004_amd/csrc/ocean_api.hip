@@ -420,6 +420,7 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
     const bool wide_bitmap = B.cols <= (1 << 20);
     const bool tiled = symbolic_in_tiles(B.nnz, B.cols, st->products, A.nnz);
     const bool few_apart = tiled && B.cols <= SYMBOLIC_FEW_COLS;   // rows of few products have a launch of smaller workgroups
+    const int64_t few_products = symbolic_few_products(st->products, st->max_row_products, c.n_cu);
     // That launch takes the rows of the 4096-slot bin, too, where rows of B fill the bitmap kernel's tiles: 12 000 rows of 3040
     // products, predict stage with key tables and with bitmaps, 16384 / 131072 / 262144 columns: rows of B of 16 entries
     // 186 -> 113, 199 -> 141, 195 -> 145 us, of 32 181 -> 107, 194 -> 122, 199 -> 129, of 64 181 -> 105, 197 -> 112, 199 -> 119;
@@ -434,6 +435,7 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
         bp.n_bins = SB_COUNT;
         for (int b = 0; b < SB_COUNT; ++b) bp.slots[b] = kSymbolicSlots[b];
         bp.n_cols = B.cols;
+        bp.few_products = few_apart ? few_products : 0;
         const bool spans = round == 0 && w.spans;
         if (spans) { bp.cmin = w.cmin; bp.cmax = w.cmax; }
         OC_TRY(zero_bins(c, w));

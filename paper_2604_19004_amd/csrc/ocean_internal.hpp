@@ -321,6 +321,7 @@ struct BinParams {
     int n_bins;
     int32_t slots[OCEAN_MAX_BINS];
     int64_t n_cols;
+    int64_t few_products; // mode 3, 0: none: rows beyond the 4096-slot bin go to SB_S32K with at most so many products, to SB_BITMAP with more
 };
 hipError_t launch_classify(int64_t m, const BinParams &p, double scale, const int64_t *prod, const double *est,
                            const int32_t *nnz_exact, const int32_t *row_mask, const int32_t *lower_bound,
@@ -347,7 +348,7 @@ struct SymLaunch {
     bool query_bitmap;     // bitmap kernel: read a column's bit before setting it (Section 4.1)
     const int32_t *cmin;   // SB_SPAN: first column each row can reach
     bool tiled;            // SB_BITMAP: symbolic_in_tiles
-    bool few;              // SB_BITMAP: rows of at most kSymbolicSlots[SB_S32K] products
+    bool few;              // SB_BITMAP: rows of at most symbolic_few_products, by smaller workgroups
     bool may_overflow;     // tables were sized from a guess (assisted binning): a row whose table fills up
                            // reports -1 instead of a count and probing gives up early
 };

@@ -44,4 +44,17 @@ constexpr bool symbolic_in_tiles(int64_t b_nnz, int64_t b_cols, int64_t products
     return b_nnz >= TILE_MIN_ENTRIES && products >= (b_cols <= 1 << 18 ? 10 : b_cols <= 1 << 20 ? 20 : 40) * a_nnz;
 }
 
+// Products up to which a row is counted by a workgroup of 512 threads, in a launch of its own behind that of the larger ones (a
+// workgroup of 1024, drawn from a counter).  The largest row decides how long a launch takes, so where none stands out (by 65536
+// products, or by twice a compute unit's share of all products and 2^19) every row goes with the smaller workgroups, of which the
+// chip works on twice as many.  Call in us with all rows in the smaller ones, split at 32768, at 65536 and at 524288: one row of 4 M
+// products beside 4000 of 10 000 535, 394, 392, 393; 250 rows of 1.5 M (rows of B of 1000) 280, 215, 214, 212; 64 of 256 000 beside
+// 40 000 of 2500 244, 275, 268, 244; 1000 of 300 000 (32) 416, 458, 457, 417; 2000 of 60 000 (64) 164, 178, 164, 162; R-MAT (16)
+// of scale 13 144, 151, 158, 144, 14 177, 184, 189, 178, 16 440, 446, 451, 529, 17 883, 818, 830, 955, 18 1980, 1664, 1730, 2066.
+constexpr int64_t symbolic_few_products(int64_t products, int64_t max_row, int n_cu)
+{
+    const int64_t share = 2 * products / n_cu < 1 << 19 ? 2 * products / n_cu : 1 << 19;
+    return max_row <= (share > 65536 ? share : 65536) ? max_row : 32768;
+}
+
 }  // namespace ocean

@@ -220,9 +220,8 @@ static_assert(SYMBOLIC_FEW_COLS == 32 * 8192, "four bitmaps per compute unit");
 // (counted and cleared) faster after every row, and leaves room for more workgroups on the compute unit (64
 // registers): symbolic stage of R-MAT scale 18 (16384 words) 2.80 -> 1.94 ms, whole call of scale 17 (4096) 1.39 -> 0.99
 // ms, the same with rows in tiles (tiles.hpp) instead of runs of 16 found by a search each 0.935 -> 0.875.
-// BM_THREADS: 1024; 512 for rows of at most 32768 products where the bitmap leaves room for four workgroups, in a launch of their
-// own, as the largest row decides how long a launch takes: scale 17 0.875 -> 0.850 ms (256 threads: 0.839), scale 14 in fp32 whole
-// product 663 -> 626 us (659), all rows by 512 threads 1.016 ms and 718 us.
+// BM_THREADS: 1024; 512 for rows of at most symbolic_few_products where the bitmap leaves room for four workgroups, in a launch of
+// their own.
 // ONE_WINDOW: B has at most 32 * BM_WORDS columns, so every column id falls into the one window.
 // TILED: symbolic_in_tiles says where; otherwise products are found one by one, or in runs of 16 where a chunk's segments are that
 // long (2000 rows of 24 000 products, rows of B of 2 entries, whole call 714 us in tiles and 434).

@@ -1,9 +1,10 @@
 """Rows of many products in the symbolic pass (bitmaps marked tile by tile) against the CPU oracle: numbers of columns at which
-the bitmap's size and the workgroup's change, rows at the limit between the two launches, more entries than a chunk holds, rows of B of
+the bitmap's size and the workgroup's change, rows at the limits between the two launches, more entries than a chunk holds, rows of B of
 fewer than four entries, and a B of fewer entries than a tile's lane reads."""
 import numpy as np
 import pytest
 
+import rules
 from oracle import spgemm as O
 from paper_2604_19004_amd.workloads import CSR
 
@@ -26,8 +27,9 @@ def _csr(rows, cols, lists):
 
 
 def _counts(ob, A, B, **options):
-    got = ob.symbolic(ob.to_device(A), ob.to_device(B), opt=ob.default_options(**options))[0].cpu().numpy()
-    assert np.array_equal(got, O.count_rows(A, B))
+    got, st = ob.symbolic(ob.to_device(A), ob.to_device(B), opt=ob.default_options(**options))
+    assert np.array_equal(got.cpu().numpy(), O.count_rows(A, B))
+    return st
 
 
 @pytest.mark.parametrize("bitmap_query", [-1, 2])
@@ -39,11 +41,19 @@ def test_counts_at_the_bitmap_sizes(ob, cols, bitmap_query):
     lists += [np.sort(rng.choice(cols, n, replace=False)) for n in (8192, 4096, 4097, 63, 64, 65)]
     B = _csr(len(lists), cols, lists)
     k, long = len(lists), len(lists) - 6
-    rows = [list(range(k)), [], [long] * 4, [long] * 4 + [0], [0, 1, 2, 3, 4, long + 2], [long + 1, 1], list(range(5, 600)), list(range(0, k, 3)) + [long, long]]
+    rows = [list(range(k)), [], [long] * 4, [long] * 4 + [0], [0, 1, 2, 3, 4, long + 2], [long + 1, 1], list(range(5, 600)), list(range(0, k, 3)) + [long, long],
+            [long] * 8, [long] * 8 + [0]]
     A = _csr(len(rows), k, [np.asarray(r) for r in rows])
     prod = O.row_products(A, B)
-    assert prod[2] == 32768 and prod[3] == 32769 and prod[4] > 4096   # (both sides of the limit between the launches)
-    _counts(ob, A, B, bitmap_query=bitmap_query)
+    assert prod[2] == 32768 and prod[3] == 32769 and prod[4] > 4096 and prod[8] == 65536 and prod[9] == 65537
+    apart = cols <= 1 << 18
+    for n in (9, 10):   # without the last row none has more than 65536 products, and no row stands out
+        part = CSR(n, A.cols, A.row_ptr[: n + 1], A.col_idx[: A.row_ptr[n]], A.val[: A.row_ptr[n]])
+        st = _counts(ob, part, B, bitmap_query=bitmap_query)
+        if apart:   # (both sides of the limit between the launches)
+            limit = rules.load().symbolic_few_products(int(prod[:n].sum()), int(prod[:n].max()), 256)
+            assert limit == (65536 if n == 9 else 32768)
+            assert st["symbolic_rows_per_bin"][6] == int((prod[:n] > limit).sum()) == (0 if n == 9 else int((prod[:n] > 32768).sum()))
 
 
 def test_a_matrix_of_fewer_entries_than_a_lane_reads(ob):

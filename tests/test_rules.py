@@ -47,3 +47,19 @@ def test_symbolic_rows_go_the_faster_way(cols, products, length, one_by_one, til
 
 def test_no_tiles_of_a_matrix_smaller_than_what_a_lane_reads():
     assert not rules.load().symbolic_in_tiles(7, 1000, 10 ** 9, 1) and rules.load().symbolic_in_tiles(8, 1000, 10 ** 9, 1)
+
+
+# products, the largest row's, a call for the sizes of the rows in us with the rows above 32768 products in a launch of larger
+# workgroups, and with all rows in smaller ones (256 compute units)
+FEW = [
+    (44 * 10 ** 6, 4 * 10 ** 6, 394, 535), (406 * 10 ** 6, 4 * 10 ** 6, 604, 688), (375 * 10 ** 6, 1500000, 215, 280), (75 * 10 ** 6, 300000, 325, 343),
+    (300 * 10 ** 6, 300000, 458, 416), (120 * 10 ** 6, 60000, 218, 196), (120 * 10 ** 6, 60000, 178, 164), (118 * 10 ** 6, 256000, 275, 244),
+    (179 * 10 ** 6, 256000, 295, 267), (1136 * 10 ** 6, 17 * 10 ** 6, 818, 883), (3005 * 10 ** 6, 40 * 10 ** 6, 1664, 1980),
+]
+
+
+@pytest.mark.parametrize("products, largest, apart, together", FEW)
+def test_rows_of_many_products_are_apart_where_that_is_faster(products, largest, apart, together):
+    limit = rules.load().symbolic_few_products(products, largest, 256)
+    assert limit in (32768, largest)
+    assert (together if limit == largest else apart) <= 1.06 * min(apart, together)
