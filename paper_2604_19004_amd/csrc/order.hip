@@ -92,21 +92,24 @@ k_order_scatter(const int64_t *__restrict__ prod, const int32_t *__restrict__ ro
 // accumulator): the column-window kernel needs sorted rows.
 // Rows of up to SB_SHORT entries: a wave per row, up to two entries a lane, and every entry's place is the number of entries
 // before it - each key is read from its lane once and compared with all, so the values go straight to their places.
-// Longer rows: a workgroup per row.  A bitmap over the columns numbers them (prefix popcounts), and every entry goes to its
-// column's number; where B has many columns, or a column comes twice, (column id, position) pairs in LDS are ordered by a
-// bitonic network instead and the values follow their positions (indirect sort, Section 4.2); its steps of at most 64 places
-// stay within a wave and need no barrier.  Rows longer than SB_MAX are copied unsorted: flags |= 16 and the caller keeps B
+// Rows of fewer than sort_bitmap_from entries: a workgroup of 256 threads per row, a bitonic network orders (column id, position) in
+// LDS and the values follow their positions (indirect sort, Section 4.2).
+// Longer rows: a workgroup of 1024 per row.  A bitmap over the columns, 262 144 at a time, numbers them (prefix popcounts), and every
+// entry goes to its column's number; where a column comes twice, a network orders the row instead, whose steps of at most
+// 64 places stay within a wave and need no barrier.  Rows longer than SB_MAX are copied unsorted: flags |= 16 and the caller keeps B
 // as it is.
-// R-MAT of scale 15, 216 000 entries in 32768 rows, of which a few hold thousands, fp64: 100 us with a workgroup of 256 threads and
-// a network for every row, 78 (28 + 50) without the bitmap and with up to 256 entries for a wave, 43 (20 + 23) as it is (whole call 838 -> 749).
+// R-MAT of scale 15, 216 000 entries in 32768 rows, of which a few hold thousands, fp64: 100 us with a network for every row, 36 as it
+// is (20 + 16).  6 M entries in rows of equal length, stage with the copy in us, network and bitmap: 131 072 columns, rows of 200 249
+// and 386, of 300 260 and 284, of 1000 148 and 121, of 3000 459 and 210; 2^20 columns, four turns, of 200 255 and 1927, of 1000
+// 152 and 286, of 3000 463 and 395; 32 768 columns, of 130 350 and 463, of 300 258 and 244, of 600 281 and 168.
 namespace {
 constexpr int SB_GROUPS = 2;
 constexpr int SB_SHORT = SB_GROUPS * WAVE;
 constexpr int SB_WAVES = 4;
 constexpr int SB_THREADS = 1024;
-constexpr int SB_MAX = 4096;
+constexpr int SB_MAX = SORT_BITMAP_NONE - 1;
 constexpr int SB_WORDS = SB_MAX * 2;          // of the bitmap, in the pairs' memory
-constexpr int64_t SB_MAX_COLS = 4ll * 32 * SB_WORDS;   // four turns of the bitmap
+constexpr int SB_NET_THREADS = 256;
 
 template <typename V>
 __global__ void __launch_bounds__(WAVE * SB_WAVES)
@@ -149,11 +152,64 @@ k_sort_b_short(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, 
     }
 }
 
-// Workgroup b has rows b, b + gridDim.x, ... that are longer than SB_SHORT.
+// Workgroup b has rows b, b + gridDim.x, ... of SB_SHORT + 1 .. CAP entries that are fewer than `below`.
+template <typename V, int CAP>
+__global__ void __launch_bounds__(SB_NET_THREADS)
+k_sort_b_middle(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, const V *__restrict__ val, int64_t rows,
+                int below, int32_t *__restrict__ col_out, V *__restrict__ val_out)
+{
+    __shared__ int32_t s_key[CAP];
+    __shared__ uint16_t s_pos[CAP];
+    __shared__ unsigned long long s_mine[SB_NET_THREADS / WAVE];
+    const int tid = threadIdx.x;
+    for (int64_t from = blockIdx.x; from < rows; from += (int64_t)gridDim.x * SB_NET_THREADS) {
+        const int64_t r = from + (int64_t)tid * gridDim.x;
+        const int64_t entries = r < rows ? rp[r + 1] - rp[r] : 0;
+        const unsigned long long there = __ballot(entries > SB_SHORT && entries < below);
+        if (lane_id() == 0) s_mine[tid / WAVE] = there;
+        __syncthreads();
+        for (int w = 0; w < SB_NET_THREADS / WAVE; ++w) {
+            for (unsigned long long left = s_mine[w]; left != 0ull; left &= left - 1ull) {   // uniform
+                const int64_t row = from + (int64_t)(w * WAVE + __ffsll(left) - 1) * gridDim.x;
+                const int64_t p0 = rp[row];
+                const int len = (int)(rp[row + 1] - p0);
+                int n = 2 * SB_SHORT;
+                while (n < len) n <<= 1;
+                for (int i = tid; i < n; i += SB_NET_THREADS) {
+                    s_key[i] = i < len ? col[p0 + i] : SORT_PAD;
+                    s_pos[i] = (uint16_t)i;
+                }
+                __syncthreads();
+                for (int k = 2; k <= n; k <<= 1) {
+                    for (int j = k >> 1; j > 0; j >>= 1) {
+                        for (int i = tid; i < (n >> 1); i += SB_NET_THREADS) {
+                            const int lo = ((i & ~(j - 1)) << 1) | (i & (j - 1));
+                            const int hi = lo | j;
+                            const int32_t x = s_key[lo], y = s_key[hi];
+                            if ((x > y) == ((lo & k) == 0)) {
+                                s_key[lo] = y; s_key[hi] = x;
+                                const uint16_t t = s_pos[lo]; s_pos[lo] = s_pos[hi]; s_pos[hi] = t;
+                            }
+                        }
+                        __syncthreads();
+                    }
+                }
+                for (int i = tid; i < len; i += SB_NET_THREADS) {
+                    col_out[p0 + i] = s_key[i];
+                    val_out[p0 + i] = val[p0 + s_pos[i]];
+                }
+                __syncthreads();   // the arrays are rewritten for the next row
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Workgroup b has rows b, b + gridDim.x, ... of `least` entries or more.
 template <typename V>
 __global__ void __launch_bounds__(SB_THREADS)
 k_sort_b_long(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, const V *__restrict__ val, int64_t rows,
-              int64_t cols, int32_t *__restrict__ col_out, V *__restrict__ val_out, int32_t *flags)
+              int64_t cols, int least, int32_t *__restrict__ col_out, V *__restrict__ val_out, int32_t *flags)
 {
     __shared__ unsigned long long s_key[SB_MAX];   // column id, position
     __shared__ uint16_t s_pre[SB_WORDS];           // entries before each word of the bitmap
@@ -163,7 +219,7 @@ k_sort_b_long(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, c
     const int tid = threadIdx.x;
     for (int64_t from = blockIdx.x; from < rows; from += (int64_t)gridDim.x * SB_THREADS) {
         const int64_t mine = from + (int64_t)tid * gridDim.x;
-        const unsigned long long there = __ballot(mine < rows && rp[mine < rows ? mine + 1 : 0] - rp[mine < rows ? mine : 0] > SB_SHORT);
+        const unsigned long long there = __ballot(mine < rows && rp[mine < rows ? mine + 1 : 0] - rp[mine < rows ? mine : 0] >= least);
         if (lane_id() == 0) s_long[tid / WAVE] = there;
         __syncthreads();
         for (int w = 0; w < SB_THREADS / WAVE; ++w) {
@@ -177,7 +233,7 @@ k_sort_b_long(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, c
                     continue;
                 }
                 const int len = (int)full;
-                bool done = cols <= SB_MAX_COLS;
+                bool done = true;
                 uint32_t before = 0u;   // entries with columns of the turns before
                 for (int64_t c0 = 0; done && c0 < cols; c0 += 32 * SB_WORDS) {   // (all uniform)
                     const int words = (int)(cols - c0 < 32 * SB_WORDS ? (cols - c0 + 31) / 32 : SB_WORDS);
@@ -220,7 +276,7 @@ k_sort_b_long(const int64_t *__restrict__ rp, const int32_t *__restrict__ col, c
                 }
                 if (done && before == (uint32_t)len) continue;
                 __syncthreads();
-                int n = 2 * SB_SHORT;
+                int n = 512;
                 while (n < len) n <<= 1;
                 for (int i = tid; i < n; i += SB_THREADS)
                     s_key[i] = i < len ? ((unsigned long long)(uint32_t)col[p0 + i] << 32) | (uint32_t)i : ~0ull;
@@ -261,14 +317,21 @@ hipError_t launch_sort_b_rows(const Csr &B, int dtype, int32_t *col_out, void *v
     if (B.rows == 0 || B.nnz == 0) return hipSuccess;
     const int64_t waves = (B.rows + SB_WAVES - 1) / SB_WAVES;
     const dim3 short_grid((unsigned)(waves < 65536 ? waves : 65536));
-    // (an odd number: long rows of a power-law matrix are powers of two apart)
-    const dim3 long_grid((unsigned)(B.rows < 1023 ? B.rows : 1023));
+    // (primes of which two is no small root: long rows of a power-law matrix are sums of few powers of two)
+    auto grid = [&](int64_t most) { return dim3((unsigned)(B.rows < most ? B.rows : most)); };
+    const dim3 long_grid = grid(1019);
     auto launch = [&](auto zero) {
         using V = decltype(zero);
         const V *val = static_cast<const V *>(B.val);
         V *out = static_cast<V *>(val_out);
         hipLaunchKernelGGL(k_sort_b_short<V>, short_grid, dim3(WAVE * SB_WAVES), 0, s, B.rp, B.col, val, B.rows, col_out, out);
-        hipLaunchKernelGGL(k_sort_b_long<V>, long_grid, dim3(SB_THREADS), 0, s, B.rp, B.col, val, B.rows, B.cols,
+        const int bitmap_from = sort_bitmap_from(B.cols);
+        static_assert(SB_SHORT < SORT_BITMAP_LEAST, "rows of a wave come first");
+        const auto middle = bitmap_from <= 512 ? k_sort_b_middle<V, 512> : bitmap_from <= 1024 ? k_sort_b_middle<V, 1024>
+                            : bitmap_from <= 2048 ? k_sort_b_middle<V, 2048> : k_sort_b_middle<V, SB_MAX>;
+        if (bitmap_from > SORT_BITMAP_LEAST)
+            hipLaunchKernelGGL(middle, grid(bitmap_from <= 2048 ? 2039 : 1531 /* that the LDS leaves room for */), dim3(SB_NET_THREADS), 0, s, B.rp, B.col, val, B.rows, bitmap_from, col_out, out);
+        hipLaunchKernelGGL(k_sort_b_long<V>, long_grid, dim3(SB_THREADS), 0, s, B.rp, B.col, val, B.rows, B.cols, bitmap_from,
                            col_out, out, flags);
     };
     if (dtype == OCEAN_F64) launch(0.0);

@@ -57,4 +57,14 @@ constexpr int64_t symbolic_few_products(int64_t products, int64_t max_row, int n
     return max_row <= (share > 65536 ? share : 65536) ? max_row : 32768;
 }
 
+// ---- the copy of B with its rows in column order (order.hip) ----
+// Entries from which a row of more than 128 is ordered by a bitmap over the columns, 262 144 at a time, instead of a network: the
+// bitmap is cleared and counted whatever the row, and beyond four turns of it is not worth it at 4096 entries, where both end.
+// (Figures at the kernels.)
+constexpr int SORT_BITMAP_LEAST = 129, SORT_BITMAP_NONE = 4097;
+constexpr int sort_bitmap_from(int64_t cols)
+{
+    return cols > 1 << 20 ? SORT_BITMAP_NONE : cols / 384 > SORT_BITMAP_LEAST ? (int)(cols / 384) : SORT_BITMAP_LEAST;
+}
+
 }  // namespace ocean

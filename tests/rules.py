@@ -11,6 +11,7 @@ SOURCE = """
 extern "C" int heavy_in_tiles(double products, double rows, double entries, int n_win) { return ocean::heavy_in_tiles(products, rows, entries, n_win); }
 extern "C" int symbolic_in_tiles(int64_t b_nnz, int64_t b_cols, int64_t products, int64_t a_nnz) { return ocean::symbolic_in_tiles(b_nnz, b_cols, products, a_nnz); }
 extern "C" int64_t symbolic_few_products(int64_t products, int64_t max_row, int n_cu) { return ocean::symbolic_few_products(products, max_row, n_cu); }
+extern "C" int sort_bitmap_from(int64_t cols) { return ocean::sort_bitmap_from(cols); }
 """
 
 
@@ -24,6 +25,7 @@ def load():
         so = ctypes.CDLL(lib)
     so.heavy_in_tiles.argtypes = [ctypes.c_double] * 3 + [ctypes.c_int]
     so.symbolic_in_tiles.argtypes = [ctypes.c_int64] * 4
+    so.sort_bitmap_from.argtypes = [ctypes.c_int64]
     so.symbolic_few_products.argtypes, so.symbolic_few_products.restype = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int], ctypes.c_int64
     return so
 

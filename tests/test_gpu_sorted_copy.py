@@ -20,14 +20,18 @@ def ob():
 
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
-@pytest.mark.parametrize("n", [50000, 262144, 262145, 1 << 20, (1 << 20) + 1])
+@pytest.mark.parametrize("n", [40000, 50000, 262144, 262145, 1 << 20, (1 << 20) + 1])
 @pytest.mark.parametrize("longest", [4096, 4097])
 def test_rows_of_every_length(ob, dtype, n, longest):
-    """Rows of more than 4096 entries aren't sorted, and B stays as it is.  Long rows are ordered by a bitmap of 2^18 columns at
-    a time up to 2^20, by a network beyond."""
+    """Rows of more than 4096 entries aren't sorted, and B stays as it is.  Rows from a 384th of the columns on are ordered by a bitmap
+    of 2^18 columns at a time up to 2^20, shorter ones, and all beyond, by a network, in which equal columns need not stay in order."""
     rng = np.random.default_rng(longest + n)
     lengths = [0, 1, 2, 3, 63, 64, 65, 127, 128, 129, 191, 192, 193, 255, 256, 257, 511, 512, 513, 1000, 2047, 2048, 2049, 4095, longest]
-    rows = [rng.choice(n, length, replace=False) for length in lengths * 45]   # (1125: more than one turn of the long rows' workgroups)
+    lengths += [n // 384 - 1, n // 384, n // 384 + 1]
+    rows = [rng.choice(n, length, replace=False) for length in lengths * 45]   # (1260: more than one turn of the long rows' workgroups)
+    for i, row in enumerate(rows):
+        if i % 5 == 0 and row.size > 100:
+            row[7:10] = row[50]   # (the bitmap finds a column twice)
     order = rng.permutation(len(rows))
     rows = [rows[i] for i in order]
 

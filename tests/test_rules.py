@@ -63,3 +63,21 @@ def test_rows_of_many_products_are_apart_where_that_is_faster(products, largest,
     limit = rules.load().symbolic_few_products(products, largest, 256)
     assert limit in (32768, largest)
     assert (together if limit == largest else apart) <= 1.06 * min(apart, together)
+
+
+# columns, entries of every row of B, 6 M entries in all: the stage with its sorted copy in us, by a network and by the bitmap
+SORTED = [
+    (32768, 300, 258, 244), (32768, 600, 281, 168), (32768, 3000, 455, 199), (65536, 300, 260, 254), (65536, 1000, 149, 117), (131072, 200, 249, 384),
+    (131072, 600, 279, 191), (131072, 3000, 459, 212), (262144, 200, 255, 590), (262144, 300, 260, 420), (262144, 2000, 254, 190), (524288, 200, 249, 1020),
+    (524288, 600, 279, 407), (524288, 1000, 152, 188), (524288, 3000, 465, 279), (1 << 20, 200, 256, 1918), (1 << 20, 1000, 153, 287), (1 << 20, 2000, 260, 341),
+    (1 << 20, 3000, 463, 395),
+]
+
+
+@pytest.mark.parametrize("cols, length, network, bitmap", SORTED)
+def test_rows_of_the_sorted_copy_go_the_faster_way(cols, length, network, bitmap):
+    assert (bitmap if length >= rules.load().sort_bitmap_from(cols) else network) <= 1.125 * min(network, bitmap)
+
+
+def test_no_bitmap_of_more_than_four_turns():
+    assert rules.load().sort_bitmap_from((1 << 20) + 1) == 4097 and rules.load().sort_bitmap_from(1) == 129
