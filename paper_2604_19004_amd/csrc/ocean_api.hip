@@ -531,18 +531,21 @@ double conservative_cr(const ocean_stats *S, const ocean_options &o)
     return v > 1.0 ? v : 1.0;
 }
 
-// How the rows that go through column windows are walked, from the rows, products and entries of A per key, and the smallest
-// bin of them.
+// How the rows that go through column windows are walked, and the smallest bin of them, from the rows, products and entries of A
+// per key.  Rows of the 4096-slot bin only go there with the others in tiles.
 void choose_heavy(Ctx &c, const Csr &B, const unsigned long long *count, const unsigned long long *prod, const unsigned long long *entries)
 {
-    double rows = 0.0, products = 0.0, nnz_a = 0.0;
-    for (int b = NB_S8K; b < NB_COUNT; ++b) {
-        rows += (double)count[b];
-        products += (double)prod[b];
-        nnz_a += (double)entries[b];
-    }
-    c.heavy_tiled = B.nnz >= TILE_MIN_ENTRIES && (rows > 0.0 ? heavy_in_tiles(products, rows, nnz_a, c.n_win) : c.middle_in_windows);
-    c.heavy_from = c.heavy_tiled && c.middle_in_windows ? NB_S4K : NB_S8K;
+    auto tiles_from = [&](int bin) {
+        double rows = 0.0, products = 0.0, nnz_a = 0.0;
+        for (int b = bin; b < NB_COUNT; ++b) {
+            rows += (double)count[b];
+            products += (double)prod[b];
+            nnz_a += (double)entries[b];
+        }
+        return B.nnz >= TILE_MIN_ENTRIES && rows > 0.0 && heavy_in_tiles(products, rows, nnz_a, c.n_win);
+    };
+    c.heavy_from = c.middle_in_windows && tiles_from(NB_S4K) ? NB_S4K : NB_S8K;
+    c.heavy_tiled = c.heavy_from == NB_S4K || tiles_from(NB_S8K);
 }
 
 // ---- numeric bins ------------------------------------------------------------------------------------

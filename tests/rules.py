@@ -32,6 +32,9 @@ def load():
 
 def heavy_in_tiles(st, cols):
     """Whether the rows of a call's column windows are walked in tiles, from its statistics."""
-    bins = range(8, 11)
-    rows, products, entries = (sum(st[k][b] for b in bins) for k in ("rows_per_bin", "bin_products", "bin_nnz_a"))
-    return bool(load().heavy_in_tiles(products, rows, entries, (cols + 16383) >> 14))
+    windows = (cols + 16383) >> 14
+
+    def tiles_from(first):
+        rows, products, entries = (sum(st[k][b] for b in range(first, 11)) for k in ("rows_per_bin", "bin_products", "bin_nnz_a"))
+        return rows > 0 and bool(load().heavy_in_tiles(products, rows, entries, windows))
+    return (windows <= 32 and st["er"] >= 32 and tiles_from(7)) or tiles_from(8)

@@ -3,6 +3,7 @@ average and there are at most 32 windows of 16384 columns, and keep their hash t
 import numpy as np
 import pytest
 
+import rules
 from oracle import spgemm as O
 from paper_2604_19004_amd.workloads import CSR
 from test_gpu_spgemm import check_result
@@ -61,6 +62,26 @@ def test_counts_on_both_sides_of_the_line(ob, n, length):
         assert np.array_equal(counts.cpu().numpy(), np.diff(ref.row_ptr)), f"{kw}"
     C, _ = ob.spgemm(dA, dB, workflow=ob.WF_SYMBOLIC)
     check_result(C, ref, A, f"n={n} length={length}")
+
+
+@pytest.mark.parametrize("heavy", [0, 1, 400])
+def test_rows_of_both_kinds(ob, heavy):
+    """Rows of the 4096-slot bin beside none, one or many rows whose pieces would not fill tiles: these few follow the others, and
+    where they are most, nobody goes in tiles."""
+    n = 4 * 16384
+    rng = np.random.default_rng(heavy)
+
+    def csr(rows, cols):
+        ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64)
+        idx = np.concatenate(rows).astype(np.int32)
+        return CSR(len(rows), cols, ptr, idx, rng.uniform(-1, 1, idx.size))
+    B = csr([np.sort(rng.choice(n, 64, replace=False)) for _ in range(2000)] + [np.sort(rng.choice(2500, 40, replace=False)) for _ in range(300)], n)
+    # (the last row has more than 8192 products, on 2500 columns, so that the window table is built)
+    A = csr([np.sort(rng.choice(2000, 46, replace=False)) for _ in range(300)] + [np.sort(rng.choice(2000, 700, replace=False)) for _ in range(heavy)] + [np.arange(2000, 2300)], 2300)
+    C, st = ob.spgemm(ob.to_device(A), ob.to_device(B), workflow=ob.WF_SYMBOLIC)
+    assert st["er"] >= 32 and st["rows_per_bin"][7] >= 300 and sum(st["rows_per_bin"][8:11]) == heavy
+    assert rules.heavy_in_tiles(st, n) == (heavy < 400)
+    check_result(C, O.multiply_rows(A, B), A, f"{heavy} heavy rows")
 
 
 def test_stage_of_the_order(ob):
