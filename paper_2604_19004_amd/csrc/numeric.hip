@@ -1689,20 +1689,24 @@ k_numeric_heavy_flat(const int64_t *__restrict__ a_rp, const int32_t *__restrict
 // One 16-lane group per row; a row of WT_LONG or more entries is left to the whole workgroup (every entry is
 // looked at on its own, together with its predecessor), which takes the long rows of its 16 one after the other:
 // the longest row of a power-law matrix, walked by 16 lanes, was most of the kernel's time.
-// flags |= 8 when a row is not sorted ascending.
+// flags |= 8 when a row is not sorted ascending.  spread: some 256 workgroups, every step-th, add the entries of their rows, and
+// these times the windows from the row's first to its last.
 constexpr int WT_LONG = 1024;
 __global__ void __launch_bounds__(256)
 k_window_table(const int64_t *__restrict__ b_rp, const int32_t *__restrict__ b_col, int64_t rows, int win_log2,
-               int n_win, int64_t long_from, uint32_t *__restrict__ bw, int32_t *flags)
+               int n_win, int64_t long_from, uint32_t *__restrict__ bw, int32_t *flags, unsigned long long *spread, int step)
 {
     __shared__ long long s_long[16];
     __shared__ int s_nlong;
+    __shared__ unsigned long long s_spread[2];
     const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t k = gt >> 4;
     const int sub = (int)(gt & 15);
     if (threadIdx.x == 0) s_nlong = 0;
+    if (threadIdx.x < 2) s_spread[threadIdx.x] = 0ull;
     __syncthreads();
     bool unsorted = false;
+    const bool sampled = blockIdx.x % (unsigned)step == 0u;   // uniform
     // entries first, first + step, ... of row r (positions p0 .. p1 - 1, p0 < p1), four per lane and turn
     // (unconditional reads, index clamped), so that a long row is not bound by the latency of one load after the other
     auto walk = [&](int64_t r, int64_t p0, int64_t p1, int first, int step) {
@@ -1734,6 +1738,11 @@ k_window_table(const int64_t *__restrict__ b_rp, const int32_t *__restrict__ b_c
     };
     if (k < rows) {
         const int64_t p0 = b_rp[k], p1 = b_rp[k + 1];
+        if (sampled && sub == 0 && p1 > p0) {
+            const int64_t windows = (int64_t)(b_col[p1 - 1] >> win_log2) - (b_col[p0] >> win_log2);
+            atomicAdd(&s_spread[0], (unsigned long long)(p1 - p0));
+            atomicAdd(&s_spread[1], (unsigned long long)((p1 - p0) * ((windows < 0 ? -windows : windows) + 1)));
+        }
         if (p0 == p1) {
             uint32_t *t = bw + (size_t)k * ((size_t)n_win + 1);
             for (int w = sub; w <= n_win; w += 16) t[w] = (uint32_t)p0;
@@ -1744,6 +1753,7 @@ k_window_table(const int64_t *__restrict__ b_rp, const int32_t *__restrict__ b_c
         }
     }
     __syncthreads();
+    if (sampled && threadIdx.x < 2) atomicAdd(&spread[threadIdx.x], s_spread[threadIdx.x]);
     const int nlong = s_nlong;
     for (int i = 0; i < nlong; ++i) {   // uniform
         const int64_t r = s_long[i];
@@ -1752,7 +1762,7 @@ k_window_table(const int64_t *__restrict__ b_rp, const int32_t *__restrict__ b_c
     if (unsorted) atomicOr(flags, 8);
 }
 
-hipError_t launch_window_table(const Csr &B, int dtype, uint32_t *bw, int *n_win_out, int32_t *flags, hipStream_t s)
+hipError_t launch_window_table(const Csr &B, int dtype, uint32_t *bw, int *n_win_out, int32_t *flags, unsigned long long *spread, hipStream_t s)
 {
     (void)dtype;
     const int win_log2 = ilog2_const(HV_WIN);
@@ -1762,9 +1772,10 @@ hipError_t launch_window_table(const Csr &B, int dtype, uint32_t *bw, int *n_win
     // ("long" is relative: 1024 entries or eight times the average row, whichever is more)
     const double avg = (double)B.nnz / (double)B.rows;
     const int64_t long_from = 8.0 * avg > (double)WT_LONG ? (int64_t)(8.0 * avg) : (int64_t)WT_LONG;
+    const int step = (int)(B.rows / (16 * 256)) | 1;   // (odd: the long rows of a power-law matrix are powers of two apart)
     launch_in_pieces(B.rows, 16, 256, [&](int64_t first, int64_t n) {
         hipLaunchKernelGGL(k_window_table, dim3((unsigned)((n + 15) / 16)), dim3(256), 0, s, B.rp + first, B.col, n, win_log2,
-                           n_win, long_from, bw + (size_t)first * ((size_t)n_win + 1), flags);
+                           n_win, long_from, bw + (size_t)first * ((size_t)n_win + 1), flags, spread, step);
     });
     return hipGetLastError();
 }

@@ -54,6 +54,7 @@ struct Scalars {
     int32_t pad;
     unsigned long long span_totals[SPAN_SLOTS * SPAN_STRIDE];   // see k_row_spans
     unsigned long long count_totals[COUNT_SLOTS * COUNT_STRIDE];   // see count_columns
+    unsigned long long window_spread[2];          // entries of sampled rows of B, and times the windows each row reaches over
     unsigned long long near_pairs[2];             // sampled entries of B, and those whose successor's column is 1 .. 4 larger
     unsigned long long row_totals[ROW_TOTAL_SLOTS * ROW_TOTAL_STRIDE];   // totals of the row-products pass, by slot
 };
@@ -535,6 +536,8 @@ double conservative_cr(const ocean_stats *S, const ocean_options &o)
 // per key.  Rows of the 4096-slot bin only go there with the others in tiles.
 void choose_heavy(Ctx &c, const Csr &B, const unsigned long long *count, const unsigned long long *prod, const unsigned long long *entries)
 {
+    const unsigned long long *spread = c.h->window_spread;
+    const double windows = spread[0] > 0 ? (double)spread[1] / (double)spread[0] : 1.0;
     auto tiles_from = [&](int bin) {
         double rows = 0.0, products = 0.0, nnz_a = 0.0;
         for (int b = bin; b < NB_COUNT; ++b) {
@@ -542,7 +545,7 @@ void choose_heavy(Ctx &c, const Csr &B, const unsigned long long *count, const u
             products += (double)prod[b];
             nnz_a += (double)entries[b];
         }
-        return B.nnz >= TILE_MIN_ENTRIES && rows > 0.0 && heavy_in_tiles(products, rows, nnz_a, c.n_win);
+        return B.nnz >= TILE_MIN_ENTRIES && rows > 0.0 && heavy_in_tiles(products, rows, nnz_a, windows);
     };
     c.heavy_from = c.middle_in_windows && tiles_from(NB_S4K) ? NB_S4K : NB_S8K;
     c.heavy_tiled = c.heavy_from == NB_S4K || tiles_from(NB_S8K);
@@ -1209,7 +1212,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
             bw_try = static_cast<uint32_t *>(c.alloc(bytes));
             // (not for a B that the sample of the input check has shown to be out of column order: its table would be of no
             // use, and where it pays a sorted copy gets one below.  43 us of 1.05 ms on an unsorted R-MAT of scale 15)
-            if (bw_try && !(c.h->flags & 8)) HIP_TRY(launch_window_table(B, dtype, bw_try, &c.n_win, &w.sc->flags, c.s));
+            if (bw_try && !(c.h->flags & 8)) HIP_TRY(launch_window_table(B, dtype, bw_try, &c.n_win, &w.sc->flags, w.sc->window_spread, c.s));
         }
     }
 
@@ -1371,7 +1374,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
                 Csr Bs = B;
                 Bs.col = s_col;
                 Bs.val = s_val;
-                HIP_TRY(launch_window_table(Bs, dtype, bw_try, &c.n_win, &w.sc->flags, c.s));
+                HIP_TRY(launch_window_table(Bs, dtype, bw_try, &c.n_win, &w.sc->flags, w.sc->window_spread, c.s));
                 OC_TRY(fetch_scalars(c, w.sc));
                 if (!(c.h->flags & (8 | 16))) {
                     Bnum = Bs;

@@ -16,19 +16,19 @@ constexpr bool dspan_in_tiles(int64_t b_nnz, int64_t products, int64_t a_nnz)
     return b_nnz >= TILE_MIN_ENTRIES && b_nnz < 0xffffffffLL && products >= 32 * a_nnz;
 }
 
-// Whether rows that are accumulated in n_win column windows (`rows` of them, `products` products, `entries` entries of A) are walked
-// in tiles: where what a pass finds of a row of B fills half a tile on average.  A pass has as many windows as hold 8192
-// entries of C, one at least and sixteen at most; a row of B's entries lie all over the windows.
+// Whether rows that are accumulated in column windows (`rows` of them, `products` products, `entries` entries of A) are walked in
+// tiles: where what a pass finds of a row of B fills half a tile on average.  A pass has as many windows as hold 8192
+// entries of C, one at least and sixteen at most; the entries of a row of B lie all over `windows` windows.
 // Numeric stage one by one and in tiles, fp64, rows of B of equal length with columns anywhere, us (entries per pass): 1 window, rows
 // of 223 000 products 284 and 389 (16), 273 and 273 (32), 277 and 223 (48), 334 and 205 (64); 4 windows, 260 000 649 and 1370 (4),
 // 523 and 842 (8), 430 and 532 (16), 383 and 433 (24), 393 and 381 (32); 8 windows, 59 000 1258 and 1778 (7), 791 and 892 (18),
 // 753 and 765 (26), 644 and 645 (35); 64 windows, 16 000 1.31 times (8), 1.12 (16), 0.95 (32); 128 windows 1.17 (16), 1.10 (24),
-// 1.06 (32).  Power-law matrices are in favour of tiles by 0.77 to 1.02 from 41 entries per pass on: their products lie in long rows.
-constexpr bool heavy_in_tiles(double products, double rows, double entries, int n_win)
+// 1.06 (32).  Columns in blocks of 8000 of 800 000 (1.5 windows), rows of 100 000 866 and 764 (67), of 60 000 1352 and 1496 (20).  Power-law matrices are in favour of tiles by 0.77 to 1.02 from 41 entries per pass on: their products lie in long rows.
+constexpr bool heavy_in_tiles(double products, double rows, double entries, double windows)
 {
     double share = 8192.0 * rows / products;   // of the columns, in a pass
-    if (share > 16.0 / n_win) share = 16.0 / n_win;
-    if (share < 1.0 / n_win) share = 1.0 / n_win;
+    if (share > 16.0 / windows) share = 16.0 / windows;
+    if (share < 1.0 / windows) share = 1.0 / windows;
     if (share > 1.0) share = 1.0;
     return products * share >= 32.0 * entries;
 }

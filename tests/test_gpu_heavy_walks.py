@@ -35,7 +35,7 @@ def _check(ob, A, B, tiles, exact=False, **options):
     C, st = ob.spgemm(ob.to_device(A), ob.to_device(B), **options)
     assert sum(st["rows_per_bin"][8:11]) > 0, "no row reaches the kernels under test"
     if options.get("workflow") == ob.WF_SYMBOLIC and tiles is not None:
-        assert rules.heavy_in_tiles(st, B.cols) == tiles
+        assert rules.heavy_in_tiles(st, B) == tiles
     assert np.array_equal(C.row_ptr.cpu().numpy(), ref.row_ptr) and np.array_equal(C.col_idx.cpu().numpy(), ref.col_idx)
     val = C.val.cpu().numpy().astype(np.float64)
     if exact:
@@ -114,6 +114,6 @@ def test_every_workgroup_has_one_of_as_many_rows(ob):
     for rows in (units // 2, units - 6):
         dA, dB = ob.to_device(_csr(1500, [row] * rows, lambda n: rng.uniform(-1, 1, n))), ob.to_device(B)
         calls = [ob.spgemm(dA, dB, workflow=ob.WF_SYMBOLIC)[1] for _ in range(30)]
-        assert sum(calls[0]["rows_per_bin"][8:11]) == rows and rules.heavy_in_tiles(calls[0], B.cols)
+        assert sum(calls[0]["rows_per_bin"][8:11]) == rows and rules.heavy_in_tiles(calls[0], B)
         least.append(min(st["stage_ms"]["numeric"] for st in calls))
     assert least[1] < 1.45 * least[0], least

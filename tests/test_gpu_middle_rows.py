@@ -80,7 +80,7 @@ def test_rows_of_both_kinds(ob, heavy):
     A = csr([np.sort(rng.choice(2000, 46, replace=False)) for _ in range(300)] + [np.sort(rng.choice(2000, 700, replace=False)) for _ in range(heavy)] + [np.arange(2000, 2300)], 2300)
     C, st = ob.spgemm(ob.to_device(A), ob.to_device(B), workflow=ob.WF_SYMBOLIC)
     assert st["er"] >= 32 and st["rows_per_bin"][7] >= 300 and sum(st["rows_per_bin"][8:11]) == heavy
-    assert rules.heavy_in_tiles(st, n) == (heavy < 400)
+    assert rules.heavy_in_tiles(st, B) == (heavy < 400)
     check_result(C, O.multiply_rows(A, B), A, f"{heavy} heavy rows")
 
 

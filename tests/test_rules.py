@@ -20,6 +20,9 @@ HEAVY = [
     # power-law matrices: mean products and length of the rows that go through windows
     (1, 10279, 95.8, 195, 164), (1, 15336, 226.6, 367, 304), (2, 18071, 313.9, 754, 625), (4, 22856, 424.3, 1899, 1531), (8, 28879, 569.1, 4769, 3950),
     (16, 39606, 758.3, 13017, 10808),
+    # columns in blocks of 8000, 20 000 and 60 000
+    (1.5, 100000, 100, 866, 764), (1.5, 150000, 300, 994, 861), (1.5, 60000, 30, 1352, 1496), (2.2, 150000, 300, 1157, 1034), (2.2, 60000, 30, 1615, 1906),
+    (2.2, 400000, 1000, 1846, 1589), (4.7, 100000, 100, 1554, 1740), (4.7, 60000, 30, 2385, 2918), (4.7, 400000, 1000, 2450, 2190),
 ]
 
 
