@@ -1250,12 +1250,7 @@ int spgemm_impl(Ctx &c, const ocean_csr *Ain, const ocean_csr *Bin, ocean_csr *C
     }
 
     c.dspan_tiled = dspan_in_tiles(B.nnz, S->products, A.nnz);
-    // Rows of the 8192-slot bin always cost less in column windows than in hash tables.  Those of the 4096-slot bin do
-    // where rows of B fill the tiles by half: 12 000 rows of 3040 products, fp64, symbolic workflow, whole call hashed and in
-    // windows, 16384 / 262144 / 1048576 columns: rows of B of 8 entries 810 -> 999, 1142 -> 1175, 1378 -> 3102 us; of 16
-    // 783 -> 844, 1362 -> 969, 1614 -> 2232; of 32 775 -> 721, 1814 -> 1440, 2065 -> 1709; of 256 1069 -> 802, 1804 -> 1290,
-    // 4317 -> 3715.  R-MAT of scale 14 642 -> 619 us, of scale 18 (16 windows) 13.03 -> 12.86 ms; scale 20 (64) 105.6 and 105.8.
-    c.middle_in_windows = dense_window_count(n, dtype) <= 32 && S->products >= 32 * A.nnz;
+    c.middle_in_windows = middle_in_windows(dense_window_count(n, dtype), S->products, A.nnz);
     // Section 4.1 / 4.3: dense windows that are walked product by product query the bitmap before writing when the (sampled) CR is at
     // least 2 (measured on R-MAT, sampled CR 2.5: 2.8 %); those in tiles and the dense ranges have no presence bits.  The symbolic
     // bitmap kernel, whose only LDS operation per product is that OR, loses 14 %: it queries only when told to, bitmap_query = 2

@@ -11,6 +11,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SOURCE = """
 #include "rules.hpp"
 extern "C" int heavy_in_tiles(double products, double rows, double entries, double windows) { return ocean::heavy_in_tiles(products, rows, entries, windows); }
+extern "C" int middle_in_windows(int n_win, int64_t products, int64_t a_nnz) { return ocean::middle_in_windows(n_win, products, a_nnz); }
 extern "C" int symbolic_in_tiles(int64_t b_nnz, int64_t b_cols, int64_t products, int64_t a_nnz) { return ocean::symbolic_in_tiles(b_nnz, b_cols, products, a_nnz); }
 extern "C" int64_t symbolic_few_products(int64_t products, int64_t max_row, int n_cu) { return ocean::symbolic_few_products(products, max_row, n_cu); }
 extern "C" int sort_bitmap_from(int64_t cols) { return ocean::sort_bitmap_from(cols); }
@@ -26,6 +27,7 @@ def load():
         subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, src, "-o", lib], check=True)
         so = ctypes.CDLL(lib)
     so.heavy_in_tiles.argtypes = [ctypes.c_double] * 4
+    so.middle_in_windows.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64]
     so.symbolic_in_tiles.argtypes = [ctypes.c_int64] * 4
     so.sort_bitmap_from.argtypes = [ctypes.c_int64]
     so.symbolic_few_products.argtypes, so.symbolic_few_products.restype = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int], ctypes.c_int64
@@ -43,4 +45,5 @@ def heavy_in_tiles(st, B):
     def tiles_from(bin_):
         rows, products, entries = (sum(st[k][b] for b in range(bin_, 11)) for k in ("rows_per_bin", "bin_products", "bin_nnz_a"))
         return rows > 0 and bool(load().heavy_in_tiles(products, rows, entries, spread))
-    return ((B.cols + 16383) >> 14 <= 32 and st["er"] >= 32 and tiles_from(7)) or tiles_from(8)
+    middle = load().middle_in_windows((B.cols + 16383) >> 14, st["products"], round(st["products"] / st["er"]))
+    return bool(middle and tiles_from(7)) or tiles_from(8)

@@ -84,3 +84,15 @@ def test_rows_of_the_sorted_copy_go_the_faster_way(cols, length, network, bitmap
 
 def test_no_bitmap_of_more_than_four_turns():
     assert rules.load().sort_bitmap_from((1 << 20) + 1) == 4097 and rules.load().sort_bitmap_from(1) == 129
+
+
+# windows, entries of a row of B, numeric stage in us of rows of 3000 products hashed, and in windows
+MIDDLE = [
+    (1, 64, 683, 594), (1, 250, 691, 573), (1, 1000, 725, 573), (4, 64, 727, 596), (4, 250, 745, 583), (16, 64, 798, 624), (16, 250, 816, 602),
+    (16, 1000, 847, 617), (32, 64, 847, 918), (32, 250, 856, 803), (32, 1000, 886, 799),
+]
+
+
+@pytest.mark.parametrize("windows, length, hashed, windowed", MIDDLE)
+def test_middle_rows_go_the_faster_way(windows, length, hashed, windowed):
+    assert (windowed if rules.load().middle_in_windows(windows, length * 1000, 1000) else hashed) <= 1.05 * min(hashed, windowed)
