@@ -1,6 +1,6 @@
 """The dense-range kernel where it walks the products in tiles of 64 entries of a row of B, and where it does not, against the
 CPU oracle: rows of B shorter than a lane's four entries (among them B's first), at and around a tile's length, rows of A
-of more entries than the kernel takes at a time, and products that are -0, +0 or underflow to them."""
+of more entries than the kernel takes at a time, and products that are -0, +0, underflow to them or are no numbers."""
 import numpy as np
 import pytest
 
@@ -59,3 +59,27 @@ def test_tiles_of_dense_rows(ob, span, dtype, kind):
     mixed = _csr([rng.permutation(r) for r in b_rows], n, rng, dtype)
     C, st = ob.spgemm(dA, ob.to_device(mixed), dense_range=2, workflow=ob.WF_UPPER_BOUND)
     check_result(C, O.multiply_rows(A, mixed), A, f"{kind} {span}, rows of B in no order")
+
+
+@pytest.mark.parametrize("kind", LENGTHS)
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("span", [900, 2000, 4096])
+def test_infinities_and_nan_among_dense_rows(ob, span, dtype, kind):
+    """A column's accumulator tells by -0 that it has no product: infinities, their differences and NaN are products like others."""
+    rng = np.random.default_rng(span + 1)
+    b_rows = [17 + np.sort(rng.choice(span, length, replace=False)) for length in LENGTHS[kind] for _ in range(40)]
+    B = _csr(b_rows, span + 40, rng, dtype)
+    A = _csr([np.sort(rng.choice(len(b_rows), min(e, len(b_rows)), replace=False)) for e in (520, 256, 300, 513) * 8], len(b_rows), rng, dtype)
+    A.val[:] = rng.choice(np.array([1.0, -2.0, 0.5, 0.0, -0.0], dtype=dtype), A.val.size)
+    B.val[:] = rng.choice(np.array([1.0, -1.0, 0.25, -0.0], dtype=dtype), B.val.size)
+    B.val[rng.choice(B.val.size, 30, replace=False)] = rng.choice([np.inf, -np.inf, np.nan], 30)
+    with np.errstate(invalid="ignore"):
+        ref = O.multiply_rows(A, B)
+    nb = len(ob.bin_layout()[0])
+    for kw in (dict(workflow=ob.WF_SYMBOLIC, dense_range=2), dict(workflow=ob.WF_UPPER_BOUND, dense_range=2), dict(tuned_min_products=0.0)):
+        C, st = ob.spgemm(ob.to_device(A), ob.to_device(B), **kw)
+        assert st["rows_per_bin"][nb] > 0
+        assert np.array_equal(C.row_ptr.cpu().numpy(), ref.row_ptr) and np.array_equal(C.col_idx.cpu().numpy(), ref.col_idx)
+        val = C.val.cpu().numpy().astype(np.float64)
+        assert np.array_equal(val, ref.val.astype(np.float64), equal_nan=True)   # (sums of few small numbers: exact)
+        assert np.isnan(val).any() and np.isinf(val).any() and not np.any(np.signbit(val) & (val == 0))

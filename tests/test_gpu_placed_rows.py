@@ -202,10 +202,9 @@ def test_dense_ranges(ob, span, dtype):
     a_lists[0] = a_lists[rows // 3] = []
     A = _csr(rows, B.rows, a_lists, rng, dtype)
     nb = len(ob.bin_layout()[0])
-    for options in (dict(), dict(bitmap_query=0)):
-        C, st = _check(ob, A, B, f"{span} columns", placed=span <= 4096, tuned_min_products=0.0, **options)
-        if span <= 4096:
-            assert st["rows_per_bin"][nb] == rows - 2
+    C, st = _check(ob, A, B, f"{span} columns", placed=span <= 4096, tuned_min_products=0.0)
+    if span <= 4096:
+        assert st["rows_per_bin"][nb] == rows - 2
     mixed = _csr(len(lists), n, [rng.permutation(x) for x in lists], rng, dtype)
     mixed.val[:] = B.val
     C, st = ob.spgemm(ob.to_device(A), ob.to_device(mixed), tuned_min_products=0.0)

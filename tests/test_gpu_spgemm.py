@@ -145,10 +145,18 @@ def test_assisted_symbolic_binning(ob, name):
     assert np.array_equal(over.cpu().numpy().astype(np.int64), want)
     if name != "rect":   # (rect: CR ~ 1 everywhere, no spread to exaggerate)
         assert st2["symbolic_overflow_rows"] > 0
-    # the whole path with the forced two-pass workflow and assisted binning
-    Cd, st3 = ob.spgemm(dA, dB, workflow=ob.WF_SYMBOLIC, assisted_symbolic=2, assist_sigmas=-2.0)
-    check_result(Cd, ref, A, f"{name}/symbolic assisted")
-    assert st3["assist_cr"] > 0.0 or name == "rect"
+    # the whole path with the forced two-pass workflow and assisted binning; with the larger ratio rows are found to have no count
+    # when the numeric pass is binned, and all of that is done again
+    plain = ob.spgemm(dA, dB, workflow=ob.WF_SYMBOLIC, assisted_symbolic=2, assist_sigmas=1e9)[1]   # (the same sample, a ratio of 1)
+    assert plain["assist_cr"] == 0.0 and plain["symbolic_overflow_rows"] == 0
+    for sigmas in (-2.0, -6.0):
+        Cd, st3 = ob.spgemm(dA, dB, workflow=ob.WF_SYMBOLIC, assisted_symbolic=2, assist_sigmas=sigmas)
+        check_result(Cd, ref, A, f"{name}/symbolic assisted")
+        assert st3["assist_cr"] > 0.0 or name == "rect"
+        for key in ("rows_per_bin", "bin_products", "bin_nnz_a", "bin_nnz_c", "nnz_c"):
+            assert st3[key] == plain[key], key
+    if name != "rect":
+        assert st3["symbolic_overflow_rows"] > 0
 
 
 def test_host_helpers_match_oracle(ob):
