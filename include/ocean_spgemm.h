@@ -135,9 +135,9 @@ typedef struct ocean_options {
                                         32 registers the factor 2.0 sends a quarter of the rows of a 234-entries-per-row
                                         input to tables twice the size they need; 0 = the expansion factor itself */
     int32_t dense_range;             /* accumulator selection of Section 3.3: a row whose column range (first to last
-                                        column of the rows of B it references) is at most 4096 columns and needs no
-                                        more LDS as values + presence bits than the hash table the row would get
-                                        (512 slots or more) is accumulated densely over that range.  0 never; 1
+                                        column of the rows of B it references) is at most 4096 columns, whose values
+                                        and a bit each would need no more memory than the hash table the row would get
+                                        (512 slots or more), is accumulated densely over that range.  0 never; 1
                                         (default) when 2 % or more of the sampled rows are such rows (then the ranges
                                         of all rows are computed, one more pass over A); 2 always compute the ranges */
     double sort_b_ratio;             /* detector for the throughput-bound case of the accumulators that keep values in
@@ -179,7 +179,9 @@ typedef struct ocean_stats {
     int64_t rows_per_bin[OCEAN_MAX_BINS];          /* numeric bins: the hash bins of ocean_bin_layout, then (at index
                                                       n_numeric) the rows of the dense accumulator over the row's range */
     int64_t symbolic_rows_per_bin[OCEAN_MAX_BINS]; /* symbolic bins (two-pass workflow), then (at index n_symbolic) the
-                                                      rows counted by a bitmap over their own column range */
+                                                      rows counted by a bitmap over their own column range.  Where rows
+                                                      beyond the 4096-slot bin are counted by bitmaps of two sizes of
+                                                      workgroup, the last bin has those of the larger one, by products */
     int64_t overflow_rows;
     int64_t symbolic_overflow_rows; /* rows whose assisted key table filled up and that were recounted */
     int64_t temp_slots;        /* output slots reserved at first (estimation workflows) */

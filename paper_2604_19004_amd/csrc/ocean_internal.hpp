@@ -54,9 +54,10 @@ constexpr int32_t kSymbolicSlots[SB_COUNT] = {64, 256, 1024, 4096, 16384, 32768,
 constexpr int32_t BIN_NONE = 255;          // row takes no part in this launch set
 
 // Dense accumulator over a row's own column range (Section 3.3, accumulator selection: the kind that needs fewer
-// resources, dense when both need the same): values and one presence bit per column of the range against keys
-// and values of a hash table.  Rows of the 512-slot bin and beyond are candidates; the range must fit the
-// kernel's LDS window.
+// resources, dense when both need the same).  Rows of the 512-slot bin and beyond are candidates; the range must fit the
+// kernel's LDS window.  The line is that of values of the type's own size and a presence bit per column against keys and values of
+// a hash table, where it was measured.  The accumulators hold 8 bytes a column in either type now, and no bits, and the kernel takes
+// 0.4 to 1.0 of its time of then, so rows at the line are on its better side (not measured again: more rows might be).
 constexpr int NB_DSPAN = NB_COUNT;          // index of that bin in the per-bin arrays (after the hash bins)
 constexpr int NB_ALL = NB_COUNT + 1;
 constexpr int64_t DS_MAX_COLS = 4096;
