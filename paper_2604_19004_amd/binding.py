@@ -246,64 +246,52 @@ def to_device(m, device="cuda:0") -> DeviceCSR:
                      torch.from_numpy(m.val).to(device))
 
 
-class _Blocks:
-    """The memory of one allocator: torch tensors by their address."""
-
-    def __init__(self, device):
-        torch = _torch()
-        self.device = device
-        self.held: dict[int, object] = {}
-        self._empty, self._uint8 = torch.empty, torch.uint8
-
-    def alloc(self, nbytes, out):
-        try:
-            t = self._empty(max(int(nbytes), 1), dtype=self._uint8, device=self.device)
-        except Exception:   # out of memory -> the library reports OCEAN_EALLOC
-            return 1
-        ptr = t.data_ptr()
-        self.held[ptr] = t
-        out[0] = ptr
-        return 0
-
-    def release(self, ptr):
-        self.held.pop(int(ptr), None)
-
-
-_allocators = weakref.WeakValueDictionary()   # _Blocks by the ctx that their struct carries
+_allocators = weakref.WeakValueDictionary()   # allocator structs by the ctx that they carry
 _allocator_ids = itertools.count(1)
 
 
 def _alloc(ctx, nbytes, out):
     a = _allocators.get(ctx)
-    return 1 if a is None else a.alloc(nbytes, out)
+    return 1 if a is None else _alloc_from(a, nbytes, out)
 
 
 def _release(ctx, ptr):
     a = _allocators.get(ctx)
     if a is not None:
-        a.release(ptr)
+        a.blocks.pop(int(ptr), None)
+
+
+def _alloc_from(struct, nbytes, out):
+    try:
+        t = struct.empty(max(int(nbytes), 1), dtype=struct.uint8, device=struct.device)
+    except Exception:   # out of memory -> the library reports OCEAN_EALLOC
+        return 1
+    ptr = t.data_ptr()
+    struct.blocks[ptr] = t
+    out[0] = ptr
+    return 0
 
 
 class TorchAllocator:
     """ocean_allocator whose memory comes from torch's caching allocator, one for every call.  The C callbacks of its struct are
-    shared by all and find theirs by ctx: a pair of callbacks of its own takes 22 us to make.  The struct keeps the memory alive:
-    it works as long as it, or a pointer to it, is held."""
+    shared by all and find theirs by ctx: a pair of callbacks of its own takes 22 us to make.  The struct has the memory:
+    it works as long as it, or a pointer to it, is held (and this object is not: no cycle is left behind by a call)."""
 
     _shared = (ALLOC_FN(_alloc), RELEASE_FN(_release))
 
     def __init__(self, device):
-        self._blocks = _Blocks(device)
-        self.device, self.blocks = device, self._blocks.held
+        torch = _torch()
         ctx = next(_allocator_ids)
-        _allocators[ctx] = self._blocks
-        self.struct = ocean_allocator(ctx, *self._shared)
-        self.struct.blocks = self._blocks   # (not self: no cycle is left behind for every call)
+        self.struct = self._own = s = _allocators[ctx] = ocean_allocator(ctx, *self._shared)
+        self.device = s.device = device
+        self.blocks = s.blocks = {}   # tensors by their address
+        s.empty, s.uint8 = torch.empty, torch.uint8
 
     def alloc(self, nbytes, out):
-        return self._blocks.alloc(nbytes, out)
+        return _alloc_from(self._own, nbytes, out)   # (also where `struct` was replaced)
 
     def release(self, ptr):
-        self._blocks.release(ptr)
+        self.blocks.pop(int(ptr), None)
 
     @functools.cached_property
     def _alloc_cb(self):
