@@ -940,11 +940,10 @@ k_numeric_hybrid(const int64_t *__restrict__ a_rp, const int32_t *__restrict__ a
 // prefix per product.  R-MAT scale 18 (68 800 rows, 3.0 G products, most rows 4 to 90 long pieces):
 // 11.29 -> 9.98 ms against products numbered one by one, single sparse passes of at most 8192
 // products and presence bits (whole
-// calls: 14.6 -> 13.1 ms; scale 20 110.1 -> 106.5; scale 14 in fp32 0.74 -> 0.71).  By parts, from variants that leave one out (of 10.3 ms): row
-// and pass set-up 3.4 (the sweep of dense windows 1.0, opening the pieces 1.0), search 0.6, loads
-// 2.2 (1.3 of it where every load hits the L2), LDS work and output 4.0.  The LDS is the busiest
-// unit (50 % of the cycles, 8.6 per instruction: randomly addressed 8-byte adds), vector issue 44 %;
-// what bounds the kernel is that one workgroup fills the compute unit, so its phases do not overlap.
+// calls: 14.6 -> 13.1 ms; scale 20 110.1 -> 106.5; scale 14 in fp32 0.74 -> 0.71).  Counters of scale 20 (89.9 ms): 73 vector
+// and 9 LDS instructions per 64 products, vector issue 43 % of the cycles, bank conflicts 18 % (3.5 an LDS instruction); a wave
+// waits for data or at a barrier in 55 % of its cycles, for its turn to issue in 24 %.  No unit is full: one workgroup fills
+// the compute unit, so that its phases do not overlap.
 // Two workgroups of 512 threads, windows of half the size: 9.6 ms before the last steps on scale 18, but
 // 0.22 against 0.15 on scale 15 and twice the window table; tiles of 64 lanes, 8 products a batch,
 // the tile's numbers in scalar registers: the same time with 15 % more vector instructions.

@@ -426,7 +426,7 @@ int run_symbolic(Ctx &c, Work &w, const Csr &A, const Csr &B, int gb_log2, doubl
     // products, predict stage with key tables and with bitmaps, 16384 / 131072 / 262144 columns: rows of B of 16 entries
     // 186 -> 113, 199 -> 141, 195 -> 145 us, of 32 181 -> 107, 194 -> 122, 199 -> 129, of 64 181 -> 105, 197 -> 112, 199 -> 119;
     // rows of 1200 products: of 16 112 -> 101, 105 -> 119, 104 -> 122, of 32 111 -> 101, 106 -> 107, 107 -> 113, of 64
-    // 113 -> 100, 107 -> 104, 110 -> 110.
+    // 113 -> 100, 107 -> 104, 110 -> 110.  The line is the lower rows' (1200 products); 3040 would gain from 16 entries on.
     const int few_from = few_apart && st->er >= (B.cols <= SYMBOLIC_FEW_COLS / 2 ? 32.0 : 64.0) ? SB_S4K : SB_S16K;
     for (int round = first_round; round < 2; ++round) {
         const bool assisted = round == 0 && assist_cr > 1.0;

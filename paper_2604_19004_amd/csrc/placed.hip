@@ -100,7 +100,7 @@ __device__ __forceinline__ int64_t place_row(FourRows &f, int wave, int64_t unit
 
 // ---- rows whose products gather: most of them lie in a window of a few hundred columns.  These are added up in an accumulator
 // per column (-0: no product yet, and no addend is -0), and only the others are sorted, in a network of their own number; their
-// entries come before and behind the window's.  A row of 762 products of the clustered input, 105 of them outside: 2111 -> 1160 vector
+// entries come before and behind the window's.  A row of 762 products of the clustered input, 105 of them outside: 2111 -> 1198 vector
 // instructions.  The call 2.22 -> 1.93 ms (with shorter placing turns and neighbouring units on one XCD); the rest is waiting: 1.43
 // ms where a row doesn't wait for its place, 1.02 with nothing behind the loads of the products.  Of a row's 18 us 8 are the chain
 // of loads before them, 5 the wait for the rows before.  Limits: below 6 products a lane the sort costs no more than the window; from

@@ -37,8 +37,8 @@ constexpr bool heavy_in_tiles(double products, double rows, double entries, doub
 // than in hash tables.  12 000 rows of 3040 products, fp64, symbolic workflow, whole call hashed and in windows, 1 / 16 / 64 windows: rows
 // of B of 8 entries 810 -> 999, 1142 -> 1175, 1378 -> 3102 us; of 16 783 -> 844, 1362 -> 969, 1614 -> 2232; of 32 775 -> 721, 1814 -> 1440,
 // 2065 -> 1709; of 256 1069 -> 802, 1804 -> 1290, 4317 -> 3715; numeric stage of 20 000 rows of 3000, 32 windows, of 64 847 -> 918, of 250
-// 856 -> 803, of 1000 886 -> 799.  R-MAT of scale 14 642 -> 619 us, of scale 18 (16 windows) 13.03 -> 12.86 ms; scale 20 (64) 105.6
-// and 105.8.
+// 856 -> 803, of 1000 886 -> 799.  R-MAT of scale 14 642 -> 619 us, of scale 18 (16 windows) 13.03 -> 12.86 ms.  With 64 windows rows
+// of equal length gain, the power-law matrix does not (scale 20 105.6 and 105.8): there the tables stay.
 constexpr bool middle_in_windows(int n_win, int64_t products, int64_t a_nnz)
 {
     return n_win <= 32 && products >= (n_win <= 16 ? 32 : 128) * a_nnz;

@@ -18,8 +18,8 @@
 // expand and accumulate: the values of 8 bytes that it adds up in LDS are faster where LDS is not short (sortrow.hip).
 // What bounds it is vector issue: 880 vector instructions per row of the 512-product class, of which the sort is 530, are
 // 489 us for 341 000 rows (of the rectangular input, before there was a class of 384) at one per four cycles and SIMD,
-// 541 us measured by k_numeric_sort.  Placed, issue is 87 % of the cycles of 762 products a row (2111 instructions) and 67 % of
-// those of 264 (861 instructions; a wave waits, for loads above all, in 69 % of its cycles, with 6.8 of them on a SIMD).
+// 541 us measured by k_numeric_sort.  Placed, issue was 87 % of the cycles of 762 products a row (2111 instructions, before rows gathered) and is
+// 72 % of those of 264 (906 instructions; a wave waits, for loads above all, in 64 % of its cycles, with 6.8 of them on a SIMD).
 // The work does not depend on where the columns lie or how many products merge.  Sizes of 3 * 2^i products cost a third less
 // per row than the next power of two (see settle).  Against the hash kernels (one MI355X, fp64 unless said): numeric
 // stage of the rectangular input (264 products a row) 1.50 -> 0.94 ms, clustered fp32 (762 products, 234 columns) 2.55 ->
